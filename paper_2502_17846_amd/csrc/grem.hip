@@ -42,6 +42,7 @@ constexpr int kDefaultColBits = 17;        // 2^17 labels, two per byte: 64 KB o
 constexpr int kDefaultColBits32 = 16;      // k > 16: 2^16 labels, a byte each
 constexpr int kDefaultHubDegree = 8192;
 constexpr int64_t kMaxSegments = 1ll << 22;   // chunks * column blocks
+constexpr int64_t kCutPackMinN = 1 << 20;  // edge cut: int32 labels of more vertices outgrow an XCD's 4 MB of L2
 constexpr int kMaxParts = kPlanParts;      // parts of a slice (hub share) in the re-layout
 
 // ---- process-wide state: the optional workspace and the measurement aids --------------------------
@@ -1158,11 +1159,37 @@ int run_edge_cut(const RowT *rowptr, const int32_t *colidx, int64_t n, const int
                  int64_t *out, void *stream) {
     if (!rowptr || !colidx || !labels || !out || n < 1 || n > (int64_t)INT32_MAX) return GREM_ERR_ARG;
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, (unsigned long long *)out, 1);
-    const unsigned blocks = (unsigned)((n + 255) / 256);
-    hipLaunchKernelGGL((k_edge_cut<RowT>), dim3(blocks), dim3(256), 0, s, rowptr, colidx, n, labels,
-                       (unsigned long long *)out);
-    return hipGetLastError() == hipSuccess ? GREM_OK : GREM_ERR_HIP;
+    const int64_t tiles = (n + kCutTile - 1) / kCutTile;
+    const dim3 grid((unsigned)(tiles < (int64_t)kCutGrid ? tiles : (int64_t)kCutGrid));
+    auto walk = [&](const uint32_t *words, const LabelSpan *span) {
+        hipLaunchKernelGGL((k_edge_cut<RowT>), grid, dim3(kCutTile), 0, s, rowptr, colidx, n, labels, words, span,
+                           (unsigned long long *)out);
+        return hipGetLastError() == hipSuccess ? GREM_OK : GREM_ERR_HIP;
+    };
+    // the packed table: from where the labels as they are outgrow the L2, unless the stream is being captured
+    // or there is no memory for it (then the walk reads the labels themselves)
+    char *block = nullptr;
+    if (n >= kCutPackMinN) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
+        if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+        else if (cap == hipStreamCaptureStatusNone &&
+                 hipMallocAsync((void **)&block, 256 + align_up((size_t)n), s) != hipSuccess) {
+            (void)hipGetLastError();
+            block = nullptr;
+        }
+    }
+    if (!block) {
+        hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, (unsigned long long *)out, 1);
+        return walk(nullptr, nullptr);
+    }
+    LabelSpan *span = (LabelSpan *)block;
+    uint32_t *words = (uint32_t *)(block + 256);
+    hipLaunchKernelGGL(k_label_range_init, dim3(1), dim3(64), 0, s, span, (unsigned long long *)out);
+    hipLaunchKernelGGL(k_label_range, dim3(2048), dim3(256), 0, s, labels, n, span);
+    hipLaunchKernelGGL(k_pack_labels, dim3(2048), dim3(256), 0, s, labels, n, (const LabelSpan *)span, words);
+    int rc = walk(words, span);
+    if (hipFreeAsync(block, s) != hipSuccess) rc = GREM_ERR_HIP;
+    return rc;
 }
 
 }  // namespace
