@@ -202,7 +202,9 @@ int grem_plan_edge_cut(const grem_plan *plan, int32_t k, const int32_t *labels,
 /* Number of CSR entries (v,u) with labels[v] != labels[u] (Sec. 1: cut edges have their endpoints
  * in different partitions), written to the single device int64 *cut_entries_out.  For a symmetric
  * loop-free CSR the undirected cut is half of it and the cut fraction is cut_entries / nnz.
- * labels: n int32 values, any values. */
+ * labels: n int32 values, any values.  From 2^20 vertices on a packed copy of the labels (at most n bytes) is
+ * allocated stream-ordered for the call; where it cannot be had, or while the stream is being captured, the
+ * call works without it. */
 int grem_edge_cut(const int64_t *rowptr, const int32_t *colidx, int64_t n, const int32_t *labels,
                   int64_t *cut_entries_out, void *stream);
 int grem_edge_cut_r32(const int32_t *rowptr, const int32_t *colidx, int64_t n,
@@ -334,7 +336,8 @@ int grem_edge_buckets(const int32_t *src, const int32_t *dst, int64_t m, int64_t
  * Every edge of a symmetric CSR is seen from both ends.  The expected cuts with refinement over two
  * chunks are the same expression at 2x.  rowptr (rowptr_bits 32 or 64), colidx, labels (n int32), out
  * (2 doubles): device pointers.  Floating point: the tail is summed in double (in the log domain when a node has more than 256 draws);
- * agreement with an exact evaluation to about 1e-9 relative.  Errors: GREM_ERR_ARG (null pointer,
+ * agreement with an exact evaluation to about 1e-9 relative.  Scratch (8.25 bytes per node) is allocated on
+ * `stream`.  Errors: GREM_ERR_ARG (null pointer,
  * n < 1, bad rowptr_bits, x outside (0, 1]), GREM_ERR_NOMEM, GREM_ERR_HIP. */
 int grem_expected_cut(const void *rowptr, int32_t rowptr_bits, const int32_t *colidx, int64_t n,
                       const int32_t *labels, double x, double *out, void *stream);
@@ -342,18 +345,19 @@ int grem_expected_cut(const void *rowptr, int32_t rowptr_bits, const int32_t *co
 /* Eq. (1) for the graph of a plan: the same two sums as grem_expected_cut (up to the order of the
  * additions: about 1e-13 relative), with the neighbour counts taken from grem_plan_neighbour_counts.
  * labels: n device int32, each -1, 0 or 1 (GREM_ERR_SEED otherwise).  Allocates n*8 bytes and the
- * per-workgroup sums stream-ordered, beside what grem_plan_neighbour_counts takes.
+ * workgroups' sums stream-ordered, beside what grem_plan_neighbour_counts takes.
  * Errors: GREM_ERR_ARG (null pointer, x outside (0, 1]), GREM_ERR_SEED, GREM_ERR_NOMEM, GREM_ERR_HIP. */
 int grem_plan_expected_cut(const grem_plan *plan, const int32_t *labels, double x, double *out,
                            void *stream);
 
 /* grem_expected_cut for callers that cannot allocate device memory: code under HIP graph capture,
- * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and the same
- * result, bit for bit, as grem_expected_cut, but the per-workgroup partial sums go to a fixed 4 MiB
- * buffer that is part of the library's device image (one copy per GPU, held until the process
- * ends) instead of a stream-ordered allocation; the call allocates and frees nothing.
- *   - n may be at most grem_expected_cut_noalloc_max_n() (4,194,304 rows: one workgroup per 16
- *     rows, two doubles per workgroup); a larger n returns GREM_ERR_LIMIT and launches nothing.
+ * tight serving loops, harnesses that forbid hipMalloc.  Same arguments and the same result, bit for
+ * bit, as grem_expected_cut, but the per-workgroup partial sums and the packed labels go to a fixed
+ * 4 MiB buffer that is part of the library's device image (one copy per GPU, held until the process
+ * ends) instead of a stream-ordered allocation, and the terms are summed where the labels are counted
+ * (no room for the counts of all nodes: slower than grem_expected_cut); the call allocates and frees nothing.
+ *   - n may be at most grem_expected_cut_noalloc_max_n() (4,194,304 rows); a larger n returns
+ *     GREM_ERR_LIMIT and launches nothing.
  *   - The device that owns the arrays and `stream` must be the current device.  The first call on
  *     a device looks up that device's copy of the buffer (hipGetSymbolAddress; no allocation, but
  *     make that first call outside graph capture).
