@@ -284,8 +284,9 @@ int grem_profile_read_marks(double *ms_out, int32_t capacity);
  * src, dst: m int32 each; seed_parts: n int32, read only at the first chunk's nodes; parts_out: n
  * int32; sizes_out: 2 int64 or NULL; nbr_counts_out: n*2 doubles, row-major, or NULL (when given it
  * is the working storage).  All device pointers.  Scratch memory is allocated on `stream` for the
- * call (about 9n bytes, plus 16n when nbr_counts_out is NULL).  The call checks the endpoints' range
- * and the seed (two small read-backs) before it enqueues the remaining chunks.
+ * call (about 10n bytes, or, from 2^22 nodes on, 2n + 8*c_size plus 8 KB per chunk; 16n more when
+ * nbr_counts_out is NULL).  The call checks the endpoints' range and the seed (one small read-back) before
+ * it enqueues the remaining chunks.
  * Errors: GREM_ERR_ARG (null pointer, m < 1, n < 1, n > 2^31-1, c_size < 1, P < 1, 2P < n, unknown
  * mode, an endpoint outside [0,n)), GREM_ERR_SEED (a first-chunk node whose seed is not 0 or 1, or
  * a seeded partition above P), GREM_ERR_NOMEM, GREM_ERR_HIP. */
@@ -306,8 +307,8 @@ int grem_edge_stream_bipartition(const int32_t *src, const int32_t *dst, int64_t
  * the group that no such edge touches are then placed one by one, ascending id, in the currently
  * smaller half (0 on a tie).  A node of group g in half b moves to group 2g + b.
  * seed_bits: levels*n int32; labels_out: n int32, each in [0, 2^levels).  Device pointers.  Scratch
- * (about 25 bytes per edge and 30 per node) is allocated on `stream`; the call reads back a few
- * counters per group.  Errors as for grem_edge_stream_bipartition, plus GREM_ERR_ARG for levels
+ * (about 25 bytes per edge and 60 per node) is allocated on `stream`; the groups of a level run side by
+ * side, and the call reads back a few counters per level.  Errors as for grem_edge_stream_bipartition, plus GREM_ERR_ARG for levels
  * outside 1..20, chunks < 1, balance_slack < 1. */
 int grem_recursive_bisection(const int32_t *src, const int32_t *dst, int64_t m, int64_t n,
                              int32_t levels, int64_t chunks, double balance_slack,

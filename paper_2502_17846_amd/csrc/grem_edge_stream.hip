@@ -7,47 +7,95 @@
 // moves are admitted in ascending node id while the target has room; rejected refined nodes stay;
 // rejected new nodes are placed one by one, ascending id, in the currently smaller partition.
 //
-// Data layout (device memory)
-//   Lb    uint8[n]      label 0/1, 0xFF = unassigned (one byte per random look-up)
-//   hc    uint64[n]     fresh counts of the current chunk: low half = neighbours in partition 0, high
-//                       half = neighbours in partition 1; one 64-bit atomic per edge end.  All zero
-//                       between chunks (the scoring kernel clears what it reads).
-//   est   double[n][2]  Alg. 1's nbr_counts
-//   mark  uint64[n/64]  bit v set = v is an endpoint of a chunk edge whose other end has no label.
-//                       A node belongs to the current chunk iff hc[v] != 0 or its bit is set.
-//                       Bitmaps are ordered sets: bit order is id order, so ranks by id are prefix
-//                       pop-counts.
-//   mv0, mv1, ov        bitmaps of the same shape: nodes asking to move to partition 0 / 1, and new
-//                       nodes whose request was rejected
-// Per chunk: k_es_count (the edges: two label look-ups, bitmap marks and count atomics per edge) ->
-// k_es_score (one lane per node, a wave walking over its 64 bitmap words: blend, assign, mover
-// ballots) -> a one-workgroup scan of the per-workgroup mover counts -> k_es_apply (ranks = scanned
-// offset + pop-count prefix; admitted moves relabel) -> a one-workgroup scan (overflow ranks, size
-// deltas, closed-form sizes after the spill) -> k_es_spill (closed-form target of the j-th rejected
-// node).
+// One run works on several groups of nodes side by side, each with its own edges, chunk length, capacity
+// and sizes: a plain call is a run of one group, a level of the recursive bisection one of all its groups
+// (chunk i of every group in the same launches).  In the run's state a group's nodes are consecutive and
+// padded to whole blocks, a block of nodes being what one workgroup of the per-node kernels owns.
+//
+// Data layout (device memory, by node of the state)
+//   Lb    uint8     label 0/1, 0xFF = unassigned (one byte per random look-up)
+//   est   double[2] Alg. 1's nbr_counts
+//   mv0, mv1, ov    bitmaps: nodes asking to move to partition 0 / 1, and new nodes whose request was
+//                   rejected.  Bitmaps are ordered sets: bit order is id order, so ranks by id are prefix
+//                   pop-counts.
+//   mark            bitmap: v is an endpoint of a chunk edge whose other end has no label
+// The chunk's fresh counts (Alg. 2 cnt_nbrs) come in one of two ways, the same integers either way:
+//   in memory (small graphs)  hc, uint64 per node: low half = neighbours in partition 0, high half = in
+//                   partition 1; k_es_count adds one 64-bit atomic per edge end, k_es_score reads and clears.
+//   binned (large graphs)     k_es_bin looks the other end's label up for every edge end and sorts the
+//                   (node, label) pairs by ranges of nodes; k_es_score_bins counts a block's pairs in LDS.
+// Per chunk: count or bin -> score (blend, assign, mover ballots) -> k_es_apply (ranks = movers of the earlier
+// blocks + pop-count prefix; admitted moves relabel) -> k_es_spill (closed-form target of the j-th rejected node,
+// sizes).  The sizes live in two copies that take turns from chunk to chunk.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "grem.h"
 
 namespace {
 
+typedef unsigned long long u64;
+
 constexpr int kBlock = 1024;                 // per-node kernels: 16 waves
-constexpr int kWordsPerBlock = kBlock / 64;   // waves per workgroup
-constexpr int kWaveWords = 64;               // bitmap words a wave of the per-node kernels owns
+constexpr int kWaves = kBlock / 64;
+constexpr int kMaxWaveWords = 64;            // most bitmap words a wave of the per-node kernels owns
 constexpr uint32_t kNone = 0xFFu;
 constexpr int kCountBlock = 256;
 constexpr int kCountUnroll = 4;              // edges in flight per thread of k_es_count
+constexpr int kTurn = 4;                     // bitmap words a wave has in flight
 
-typedef unsigned long long u64;
+// One group of a run.
+struct EsGroup {
+    int64_t e_lo, m, c_size;                 // its edges in the list, edges per chunk
+    long long P;                             // capacity of a partition
+    int64_t v_lo;                            // its first node in the caller's arrays
+    uint32_t node0, nv;                      // its first node in the state, its nodes
+    uint32_t blk0, nblk;                     // its blocks of nodes
+    uint32_t tile0, id;                      // bisection: its first tile of edges, its number in the level
+};
+
+// What the kernels of a run share.
+struct EsRun {
+    const EsGroup* groups;
+    const uint32_t* blk_group;               // group of a block
+    u64* S;                                  // [2][groups][2]: sizes, two copies
+    uint8_t* Lb;
+    double2* est;
+    u64 *mark, *mv0, *mv1, *ov;
+    uint32_t *bs0, *bs1;                     // per block: movers to 0 / 1
+    uint32_t* bso;                           // per block of k_es_apply: rejected new nodes
+    int32_t *bd0, *bd1;                      // ... size changes
+    uint32_t* flags;                         // [0] an endpoint out of range, [1] a bad seed
+    uint32_t ngroups;
+    int wpw;                                 // bitmap words per wave: a block is kBlock * wpw nodes
+    int awpw;                                // the same in k_es_apply and k_es_spill, a multiple of wpw
+};
+
+// first and last edge of the group's chunk (an empty range past its last chunk)
+__device__ __forceinline__ void es_chunk(const EsGroup& g, int64_t chunk, int64_t& lo, int64_t& hi)
+{
+    const int64_t a = chunk * g.c_size < g.m ? chunk * g.c_size : g.m;
+    const int64_t b = a + g.c_size < g.m ? a + g.c_size : g.m;
+    lo = g.e_lo + a;
+    hi = g.e_lo + b;
+}
 
 __global__ __launch_bounds__(256) void k_es_fill64(u64* p, size_t count, u64 value)
 {
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride) p[i] = value;
+}
+
+__global__ void k_es_one_group(EsGroup* groups, EsGroup g) { if (threadIdx.x == 0) groups[0] = g; }
+
+__global__ __launch_bounds__(256) void k_es_blk_groups(const EsGroup* __restrict__ groups, uint32_t* blk_group)
+{
+    const EsGroup g = groups[blockIdx.x];
+    for (uint32_t b = threadIdx.x; b < g.nblk; b += 256) blk_group[g.blk0 + b] = blockIdx.x;
 }
 
 // flags[0] = 1 if any endpoint lies outside [0, n)
@@ -61,81 +109,25 @@ __global__ __launch_bounds__(256) void k_es_check(const int32_t* __restrict__ sr
     if (bad) flags[0] = 1u;
 }
 
-// c_nodes of a chunk as a bitmap (Alg. 1: unique_nodes_in_edges)
+// c_nodes of the first chunk as a bitmap (Alg. 1: unique_nodes_in_edges).  Runs before the range check has
+// been read back: ends out of range are passed over.  Most ends find their bit set already: a plain look
+// spares them the atomic (a stale word only costs one).
 __global__ __launch_bounds__(kCountBlock) void k_es_mark(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                                         int64_t lo, int64_t hi, u64* mark)
+                                                         EsRun st)
 {
+    const EsGroup g = st.groups[blockIdx.y];
+    int64_t lo, hi;
+    es_chunk(g, 0, lo, hi);
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t e = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < hi; e += stride) {
-        const uint32_t s = (uint32_t)src[e], d = (uint32_t)dst[e];
-        atomicOr(&mark[s >> 6], 1ull << (s & 63u));
-        atomicOr(&mark[d >> 6], 1ull << (d & 63u));
-    }
-}
-
-// Alg. 1, first chunk: the chunk's nodes take seed_algo's labels; sizes are counted.
-// flags[1] = 1 if a node of the chunk has a seed label other than 0 or 1.
-__global__ __launch_bounds__(kBlock) void k_es_seed(int64_t words, const u64* __restrict__ mark,
-                                                    const int32_t* __restrict__ seed, uint8_t* Lb,
-                                                    u64* S, uint32_t* flags)
-{
-    __shared__ uint32_t c0[kWordsPerBlock], c1[kWordsPerBlock];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t w = (int64_t)blockIdx.x * kWordsPerBlock + wave;
-    const u64 word = w < words ? mark[w] : 0ull;
-    const bool on = (word >> lane) & 1ull;
-    int s = -1;
-    if (on) {
-        const int64_t v = w * 64 + lane;
-        s = seed[v];
-        if (s == 0 || s == 1) Lb[v] = (uint8_t)s;
-        else flags[1] = 1u;
-    }
-    const u64 b0 = __ballot(on && s == 0), b1 = __ballot(on && s == 1);
-    if (lane == 0) { c0[wave] = __popcll(b0); c1[wave] = __popcll(b1); }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t a = 0, b = 0;
-        for (int i = 0; i < kWordsPerBlock; ++i) { a += c0[i]; b += c1[i]; }
-        if (a) atomicAdd(&S[0], (u64)a);
-        if (b) atomicAdd(&S[1], (u64)b);
-    }
-}
-
-// cnt_nbrs (Alg. 2) for every node of the chunk at once: each edge adds one to the count its two
-// ends keep for the partition of the other end (a loop counts once, for the node itself).  An
-// unassigned other end adds nothing; the node's bit in `mark` is set instead, so that a node of the
-// chunk is known by a non-zero count or its bit: one atomic per edge end either way.
-__global__ __launch_bounds__(kCountBlock) void k_es_count(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                                          int64_t lo, int64_t hi, const uint8_t* __restrict__ Lb,
-                                                          u64* mark, u64* hc)
-{
-    const int64_t threads = (int64_t)gridDim.x * blockDim.x;
-    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (int64_t base = lo + tid; base < hi; base += threads * kCountUnroll) {
-        uint32_t s[kCountUnroll], d[kCountUnroll], ls[kCountUnroll], ld[kCountUnroll];
-        bool in[kCountUnroll];
+        const uint32_t end[2] = {(uint32_t)src[e], (uint32_t)dst[e]};
 #pragma unroll
-        for (int u = 0; u < kCountUnroll; ++u) {
-            const int64_t e = base + (int64_t)u * threads;
-            in[u] = e < hi;
-            s[u] = in[u] ? (uint32_t)src[e] : 0u;
-            d[u] = in[u] ? (uint32_t)dst[e] : 0u;
-        }
-#pragma unroll
-        for (int u = 0; u < kCountUnroll; ++u) {
-            ls[u] = in[u] ? (uint32_t)Lb[s[u]] : kNone;
-            ld[u] = in[u] ? (uint32_t)Lb[d[u]] : kNone;
-        }
-#pragma unroll
-        for (int u = 0; u < kCountUnroll; ++u) {
-            if (!in[u]) continue;
-            if (ld[u] != kNone) atomicAdd(&hc[s[u]], ld[u] ? (1ull << 32) : 1ull);
-            else atomicOr(&mark[s[u] >> 6], 1ull << (s[u] & 63u));
-            if (d[u] != s[u]) {
-                if (ls[u] != kNone) atomicAdd(&hc[d[u]], ls[u] ? (1ull << 32) : 1ull);
-                else atomicOr(&mark[d[u] >> 6], 1ull << (d[u] & 63u));
-            }
+        for (int i = 0; i < 2; ++i) {
+            if (end[i] >= g.nv) continue;
+            const uint32_t v = g.node0 + end[i];
+            const u64 bit = 1ull << (v & 63u);
+            if (!(__hip_atomic_load(&st.mark[v >> 6], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit))
+                atomicOr(&st.mark[v >> 6], bit);
         }
     }
 }
@@ -180,230 +172,538 @@ __device__ __forceinline__ uint32_t es_wave_exclusive(uint32_t x, int lane)
     return incl - x;
 }
 
-// The per-node kernels: a wave owns kWaveWords = 64 consecutive bitmap words (lane i holds word i)
-// and walks over them (k_es_score: all of them, reading the counts of their nodes; the others: those
-// that have a bit set), one lane per node of the word; a workgroup of 16 waves owns 1024 words =
-// 65536 nodes.
-//
-// k_es_score -- Alg. 1: blend the stored estimate with the fresh counts when the node has a label,
-// store the estimate, ask `assign` for a partition.  Nodes that want to move are recorded in mv0 /
-// mv1 (wave ballots), their numbers per workgroup in bs0 / bs1.  Clears what it consumed (hc, mark).
-// first: the seeded first chunk (estimates only).  fixed: fixed greedy decisions (a node that has a
-// label is left alone).
-__global__ __launch_bounds__(kBlock) void k_es_score(int64_t n, int64_t words, int first, int fixed, long long P,
-                                                     const u64* __restrict__ S, u64* mark, u64* hc,
-                                                     const uint8_t* __restrict__ Lb, double2* est,
-                                                     u64* mv0, u64* mv1, uint32_t* bs0, uint32_t* bs1)
+// sums of a and b over the workgroup (kBlock threads, all of them call it)
+__device__ __forceinline__ void es_block_sums(u64& a, u64& b)
 {
-    __shared__ uint32_t c0[kWordsPerBlock], c1[kWordsPerBlock];
+    __shared__ u64 wa[kWaves], wb[kWaves];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { a += __shfl_xor(a, o); b += __shfl_xor(b, o); }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) { wa[threadIdx.x >> 6] = a; wb[threadIdx.x >> 6] = b; }
+    __syncthreads();
+    a = 0; b = 0;
+    for (int q = 0; q < kWaves; ++q) { a += wa[q]; b += wb[q]; }
+}
+
+// Alg. 1, first chunk: the chunk's nodes take seed_algo's labels; sizes are counted.
+// flags[1] = 1 if a node of the chunk has a seed label other than 0 or 1.
+__global__ __launch_bounds__(kBlock) void k_es_seed(EsRun st, const int32_t* __restrict__ seed)
+{
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t word0 = ((int64_t)blockIdx.x * kWordsPerBlock + wave) * kWaveWords;
-    const bool mine = word0 + lane < words;
-    const u64 myword = mine ? mark[word0 + lane] : 0ull;
-    const long long S0 = (long long)S[0], S1 = (long long)S[1];
-    const int count = words - word0 < kWaveWords ? (int)(words - word0) : kWaveWords;   // <= 0: nothing
-    u64 out0 = 0ull, out1 = 0ull;
-    int64_t v = word0 * 64 + lane;
-    u64 hnext = (count > 0 && v < n) ? hc[v] : 0ull;
-    for (int i = 0; i < count; ++i, v += 64) {
-        const u64 h = hnext;
-        hnext = (i + 1 < count && v + 64 < n) ? hc[v + 64] : 0ull;
-        const u64 word = es_bcast(myword, i);
+    const uint32_t gi = st.blk_group[blockIdx.x];
+    const EsGroup& g = st.groups[gi];
+    const uint32_t word0 = ((uint32_t)blockIdx.x * kWaves + wave) * st.wpw;
+    const u64 mine = lane < st.wpw ? st.mark[word0 + lane] : 0ull;
+    u64 n0 = 0, n1 = 0;
+    for (int i0 = 0; i0 < st.wpw; i0 += kTurn) {
+        int s[kTurn];
+        bool on[kTurn];
+#pragma unroll
+        for (int u = 0; u < kTurn; ++u) {
+            on[u] = i0 + u < st.wpw && ((es_bcast(mine, (i0 + u) & 63) >> lane) & 1ull);
+            s[u] = on[u] ? seed[g.v_lo + ((word0 + i0 + u) * 64u + lane - g.node0)] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < kTurn; ++u) {
+            if (!on[u]) continue;
+            if (s[u] == 0 || s[u] == 1) st.Lb[(size_t)(word0 + i0 + u) * 64 + lane] = (uint8_t)s[u];
+            else st.flags[1] = 1u;
+            n0 += s[u] == 0; n1 += s[u] == 1;
+        }
+    }
+    es_block_sums(n0, n1);
+    if (threadIdx.x == 0) {
+        if (n0) atomicAdd(&st.S[2 * gi], n0);
+        if (n1) atomicAdd(&st.S[2 * gi + 1], n1);
+    }
+}
+
+// flags[1] = 1 if the seeds fill a partition beyond its capacity
+__global__ __launch_bounds__(256) void k_es_seed_sizes(EsRun st)
+{
+    const uint32_t gi = blockIdx.x * blockDim.x + threadIdx.x;
+    if (gi < st.ngroups && ((long long)st.S[2 * gi] > st.groups[gi].P || (long long)st.S[2 * gi + 1] > st.groups[gi].P))
+        st.flags[1] = 1u;
+}
+
+// cnt_nbrs (Alg. 2) for every node of the chunk at once, in memory: each edge adds one to the count its two
+// ends keep for the partition of the other end (a loop counts once, for the node itself).  An
+// unassigned other end adds nothing; the node's bit in `mark` is set instead, so that a node of the
+// chunk is known by a non-zero count or its bit: one atomic per edge end either way.
+// Random look-ups and atomics, 39 G/s of them together once Lb and hc outgrow the L2 (then the ends are binned).
+__global__ __launch_bounds__(kCountBlock) void k_es_count(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                                                          EsRun st, int64_t chunk, u64* hc)
+{
+    const EsGroup g = st.groups[blockIdx.y];
+    int64_t lo, hi;
+    es_chunk(g, chunk, lo, hi);
+    const uint8_t* __restrict__ Lb = st.Lb + g.node0;
+    hc += g.node0;
+    u64* mark = st.mark + (g.node0 >> 6);          // (a group starts at a whole block)
+    const int64_t threads = (int64_t)gridDim.x * blockDim.x;
+    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t base = lo + tid; base < hi; base += threads * kCountUnroll) {
+        uint32_t s[kCountUnroll], d[kCountUnroll], ls[kCountUnroll], ld[kCountUnroll];
+        bool in[kCountUnroll];
+#pragma unroll
+        for (int u = 0; u < kCountUnroll; ++u) {
+            const int64_t e = base + (int64_t)u * threads;
+            in[u] = e < hi;
+            s[u] = in[u] ? (uint32_t)src[e] : 0u;
+            d[u] = in[u] ? (uint32_t)dst[e] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < kCountUnroll; ++u) {
+            ls[u] = in[u] ? (uint32_t)Lb[s[u]] : kNone;
+            ld[u] = in[u] ? (uint32_t)Lb[d[u]] : kNone;
+        }
+#pragma unroll
+        for (int u = 0; u < kCountUnroll; ++u) {
+            if (!in[u]) continue;
+            if (ld[u] != kNone) atomicAdd(&hc[s[u]], ld[u] ? (1ull << 32) : 1ull);
+            else atomicOr(&mark[s[u] >> 6], 1ull << (s[u] & 63u));
+            if (d[u] != s[u]) {
+                if (ls[u] != kNone) atomicAdd(&hc[d[u]], ls[u] ? (1ull << 32) : 1ull);
+                else atomicOr(&mark[d[u] >> 6], 1ull << (d[u] & 63u));
+            }
+        }
+    }
+}
+
+// ---- the chunk's edge ends binned by ranges of nodes -------------------------------------------------------
+//
+// A bin is 2^cb nodes of the state, at most kBins of them.  All chunks' bin sizes are counted beforehand
+// (k_es_hist, with the range check of the endpoints); table[chunk][bin], scanned (k_es_hist_scan), is where the
+// bin's pairs of that chunk start.
+constexpr int kBins = 1024;
+constexpr int kBinTile = 8192;               // edges per workgroup: 64 KB of pairs, two workgroups per CU
+constexpr int kBinPer = kBinTile / kBlock;
+constexpr int kBinTableStride = kBins + 1;
+
+__global__ __launch_bounds__(kBlock) void k_es_hist(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                                                    EsRun st, int cb, uint32_t* __restrict__ table)
+{
+    __shared__ uint32_t hist[kBins];
+    const EsGroup g = st.groups[blockIdx.y];
+    int64_t lo, hi;
+    es_chunk(g, blockIdx.z, lo, hi);
+    if (lo + (int64_t)blockIdx.x * kBinTile >= hi) return;
+    hist[threadIdx.x] = 0u;
+    __syncthreads();
+    bool bad = false;
+    for (int64_t t = lo + (int64_t)blockIdx.x * kBinTile; t < hi; t += (int64_t)gridDim.x * kBinTile) {
+        uint32_t s[kBinPer], d[kBinPer];
+#pragma unroll
+        for (int u = 0; u < kBinPer; ++u) {
+            const int64_t e = t + u * kBlock + threadIdx.x;
+            s[u] = e < hi ? (uint32_t)src[e] : g.nv;
+            d[u] = e < hi ? (uint32_t)dst[e] : g.nv;
+            bad |= e < hi && (s[u] >= g.nv || d[u] >= g.nv);
+        }
+#pragma unroll
+        for (int u = 0; u < kBinPer; ++u) {
+            if (s[u] >= g.nv || d[u] >= g.nv) continue;
+            atomicAdd(&hist[(g.node0 + s[u]) >> cb], 1u);
+            if (s[u] != d[u]) atomicAdd(&hist[(g.node0 + d[u]) >> cb], 1u);
+        }
+    }
+    if (bad) st.flags[0] = 1u;
+    __syncthreads();
+    const uint32_t c = hist[threadIdx.x];
+    if (c) atomicAdd(&table[(size_t)blockIdx.z * kBinTableStride + threadIdx.x], c);
+}
+
+// exclusive prefix of x over the workgroup's threads; wsum: kWaves words of LDS
+__device__ __forceinline__ uint32_t es_block_exclusive(uint32_t x, uint32_t* wsum)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t excl = es_wave_exclusive(x, lane);
+    if (lane == 63) wsum[wave] = excl + x;
+    __syncthreads();
+    uint32_t before = excl;
+    for (int q = 0; q < wave; ++q) before += wsum[q];
+    return before;
+}
+
+// sizes -> starts (one workgroup per chunk); cursors: a second copy, which k_es_bin moves on
+__global__ __launch_bounds__(kBins) void k_es_hist_scan(uint32_t* table, uint32_t* cursors)
+{
+    __shared__ uint32_t wsum[kWaves];
+    uint32_t* row = table + (size_t)blockIdx.x * kBinTableStride;
+    const uint32_t c = row[threadIdx.x];
+    const uint32_t excl = es_block_exclusive(c, wsum);
+    row[threadIdx.x] = excl;
+    cursors[(size_t)blockIdx.x * kBins + threadIdx.x] = excl;
+    if (threadIdx.x == kBins - 1) row[kBins] = excl + c;
+}
+
+// cnt_nbrs, first half: for every edge end the label of the other end, the pairs sorted by bin.  A pair is the
+// node's place in its bin and 0, 1 or 2 (no label) above it.  What bounds it is the look-up of the labels (57 G/s
+// once they outgrow the L2); the pairs cost 4 bytes written and read where an atomic on the node's counts costs a
+// read and a write of 64.  A tile's pairs are collected in LDS bin by bin and written in runs (16,384 pairs into
+// 848 bins at 111M nodes: some 77 bytes each).
+// 32M edge ends of 111M nodes: 1.61 ms with an atomic per end, 0.62 here.
+__global__ __launch_bounds__(kBlock) void k_es_bin(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                                                   EsRun st, int64_t chunk, int cb, uint32_t* __restrict__ cursors,
+                                                   uint32_t* __restrict__ pairs)
+{
+    extern __shared__ uint32_t items[];            // 2 * kBinTile
+    __shared__ uint32_t hist[kBins], start[kBins], at[kBins], wsum[kWaves];
+    const EsGroup g = st.groups[blockIdx.y];
+    int64_t lo, hi;
+    es_chunk(g, chunk, lo, hi);
+    lo += (int64_t)blockIdx.x * kBinTile;
+    if (lo >= hi) return;
+    const int tid = threadIdx.x;
+    hist[tid] = 0u;
+    constexpr uint32_t kNothing = 0xFFFFFFFFu;
+    uint32_t a[kBinPer], b[kBinPer];               // node of the state | label code << 30 (fewer than 2^30 nodes)
+#pragma unroll
+    for (int u = 0; u < kBinPer; ++u) {
+        const int64_t e = lo + u * kBlock + tid;
+        a[u] = e < hi ? g.node0 + (uint32_t)src[e] : kNothing;
+        b[u] = e < hi ? g.node0 + (uint32_t)dst[e] : kNothing;
+    }
+    uint32_t la[kBinPer], lb[kBinPer];
+#pragma unroll
+    for (int u = 0; u < kBinPer; ++u) {
+        la[u] = a[u] != kNothing ? (uint32_t)st.Lb[a[u]] : 0u;
+        lb[u] = a[u] != kNothing ? (uint32_t)st.Lb[b[u]] : 0u;
+    }
+    __syncthreads();
+    uint32_t ra[kBinPer], rb[kBinPer];             // rank among the tile's pairs of the same bin
+#pragma unroll
+    for (int u = 0; u < kBinPer; ++u) {
+        if (a[u] == kNothing) continue;
+        ra[u] = atomicAdd(&hist[a[u] >> cb], 1u);
+        const bool loop = a[u] == b[u];
+        if (!loop) rb[u] = atomicAdd(&hist[b[u] >> cb], 1u);
+        a[u] |= (lb[u] < 2u ? lb[u] : 2u) << 30;
+        b[u] = loop ? kNothing : b[u] | (la[u] < 2u ? la[u] : 2u) << 30;
+    }
+    __syncthreads();
+    const uint32_t c = hist[tid];
+    const uint32_t excl = es_block_exclusive(c, wsum);
+    start[tid] = excl;
+    if (c) at[tid] = atomicAdd(&cursors[(size_t)chunk * kBins + tid], c) - excl;
+    __syncthreads();
+    auto place = [&](uint32_t x, uint32_t rank) {
+        const uint32_t node = x & 0x3FFFFFFFu, bin = node >> cb;
+        items[start[bin] + rank] = (node & ((1u << cb) - 1u)) | (x >> 30) << cb | bin << (cb + 2);      // (cb <= 20)
+    };
+#pragma unroll
+    for (int u = 0; u < kBinPer; ++u) {
+        if (a[u] != kNothing) place(a[u], ra[u]);
+        if (b[u] != kNothing) place(b[u], rb[u]);
+    }
+    __syncthreads();
+    const uint32_t total = start[kBins - 1] + hist[kBins - 1];
+    for (uint32_t i = tid; i < total; i += kBlock) {
+        const uint32_t x = items[i];
+        pairs[at[x >> (cb + 2)] + i] = x & ((1u << (cb + 2)) - 1u);
+    }
+}
+
+// ---- the per-node kernels: a wave owns wpw consecutive bitmap words (lane i holds word i), a block of 16 waves
+// kBlock * wpw nodes ----------------------------------------------------------------------------------------------
+
+// Alg. 1 for the nodes of up to kTurn bitmap words, one lane per node and word: blend the stored estimate with
+// the fresh counts h when the node has a label, store the estimate, ask `assign` for a partition.  Sets the words of
+// nodes that want to move (lane i0 + u keeps word i0 + u).  on: the node belongs to the chunk.
+__device__ __forceinline__ void es_score_words(const EsRun& st, uint32_t word0, int i0, const bool (&on)[kTurn],
+                                               const uint32_t (&h0)[kTurn], const uint32_t (&h1)[kTurn], int first, int fixed,
+                                               long long P, long long S0, long long S1, u64& out0, u64& out1)
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t old[kTurn];
+    double2 prev[kTurn];
+    bool blend[kTurn];
+#pragma unroll
+    for (int u = 0; u < kTurn; ++u) old[u] = on[u] ? (uint32_t)st.Lb[(size_t)(word0 + i0 + u) * 64 + lane] : kNone;
+#pragma unroll
+    for (int u = 0; u < kTurn; ++u) {
+        blend[u] = on[u] && !first && old[u] != kNone && !fixed;
+        if (blend[u]) prev[u] = st.est[(size_t)(word0 + i0 + u) * 64 + lane];
+    }
+#pragma unroll
+    for (int u = 0; u < kTurn; ++u) {
         int want = -1;
-        if (h != 0ull || ((word >> lane) & 1ull)) {
-            if (h) hc[v] = 0ull;
-            const uint32_t old = Lb[v];
-            double nbrs0 = (double)(uint32_t)h, nbrs1 = (double)(uint32_t)(h >> 32);
-            if (first) {
-                est[v] = make_double2(nbrs0, nbrs1);
-            } else if (!(fixed && old != kNone)) {
-                if (old != kNone) {
-                    const double2 prev = est[v];
-                    nbrs0 = (prev.x + nbrs0) * 0.5;
-                    nbrs1 = (prev.y + nbrs1) * 0.5;
-                }
-                est[v] = make_double2(nbrs0, nbrs1);
-                const int t = es_assign(nbrs0, nbrs1, S0 - (old == 0u), S1 - (old == 1u), P);
-                if ((uint32_t)t != old) want = t;
+        if (on[u] && (first || !(fixed && old[u] != kNone))) {
+            double nbrs0 = (double)h0[u], nbrs1 = (double)h1[u];
+            if (blend[u]) {
+                nbrs0 = (prev[u].x + nbrs0) * 0.5;
+                nbrs1 = (prev[u].y + nbrs1) * 0.5;
+            }
+            st.est[(size_t)(word0 + i0 + u) * 64 + lane] = make_double2(nbrs0, nbrs1);
+            if (!first) {
+                const int t = es_assign(nbrs0, nbrs1, S0 - (old[u] == 0u), S1 - (old[u] == 1u), P);
+                if ((uint32_t)t != old[u]) want = t;
             }
         }
         const u64 m0 = __ballot(want == 0), m1 = __ballot(want == 1);
-        if (lane == i) { out0 = m0; out1 = m1; }
-    }
-    if (mine) {
-        mv0[word0 + lane] = out0; mv1[word0 + lane] = out1;
-        if (myword) mark[word0 + lane] = 0ull;
-    }
-    const uint32_t a = es_wave_sum(__popcll(out0)), b = es_wave_sum(__popcll(out1));
-    if (lane == 0) { c0[wave] = a; c1[wave] = b; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t x = 0, y = 0;
-        for (int q = 0; q < kWordsPerBlock; ++q) { x += c0[q]; y += c1[q]; }
-        bs0[blockIdx.x] = x; bs1[blockIdx.x] = y;
+        if (lane == i0 + u) { out0 = m0; out1 = m1; }
     }
 }
 
-// exclusive prefix sums of in[0..len) into out, by one workgroup of kBlock threads; returns the total
-__device__ uint32_t es_block_scan(const uint32_t* __restrict__ in, uint32_t* __restrict__ out, int64_t len,
-                                  uint32_t* wsum /* kWordsPerBlock words of LDS */)
+__device__ __forceinline__ void es_store_movers(const EsRun& st, u64 movers0, u64 movers1, uint32_t block)
+{
+    es_block_sums(movers0, movers1);
+    if (threadIdx.x == 0) { st.bs0[block] = (uint32_t)movers0; st.bs1[block] = (uint32_t)movers1; }
+}
+
+// From the counts in memory; clears what it consumed (hc, mark).  first: the seeded first chunk (estimates only).
+// fixed: fixed greedy decisions (a node that has a label is left alone).
+// A wave has the counts of kTurn words in flight, and blocks are as small as it takes to fill the chip (es_shape):
+// when every wave walked 64 words one load at a time this took 54 us for 20,000 nodes, 5.3 now.
+__global__ __launch_bounds__(kBlock) void k_es_score(EsRun st, int par, int first, int fixed, u64* hc)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t carry = 0;
-    for (int64_t base = 0; base < len; base += kBlock) {
-        const int64_t i = base + threadIdx.x;
-        const uint32_t x = i < len ? in[i] : 0u;
-        const uint32_t excl = es_wave_exclusive(x, lane);
-        if (lane == 63) wsum[wave] = excl + x;
-        __syncthreads();
-        uint32_t before = 0, all = 0;
-        for (int q = 0; q < kWordsPerBlock; ++q) {
-            const uint32_t t = wsum[q];
-            if (q < wave) before += t;
-            all += t;
+    const uint32_t gi = st.blk_group[blockIdx.x];
+    const long long P = st.groups[gi].P;
+    const long long S0 = (long long)st.S[2 * (par * st.ngroups + gi)], S1 = (long long)st.S[2 * (par * st.ngroups + gi) + 1];
+    const uint32_t word0 = ((uint32_t)blockIdx.x * kWaves + wave) * st.wpw;
+    const bool mine = lane < st.wpw;
+    const u64 myword = mine ? st.mark[word0 + lane] : 0ull;
+    u64 out0 = 0ull, out1 = 0ull;
+    for (int i0 = 0; i0 < st.wpw; i0 += kTurn) {
+        u64 h[kTurn];
+        bool on[kTurn];
+        uint32_t h0[kTurn], h1[kTurn];
+#pragma unroll
+        for (int u = 0; u < kTurn; ++u) h[u] = i0 + u < st.wpw ? hc[(size_t)(word0 + i0 + u) * 64 + lane] : 0ull;
+#pragma unroll
+        for (int u = 0; u < kTurn; ++u) {
+            const u64 word = i0 + u < st.wpw ? es_bcast(myword, (i0 + u) & 63) : 0ull;
+            on[u] = h[u] != 0ull || ((word >> lane) & 1ull);
+            if (h[u]) hc[(size_t)(word0 + i0 + u) * 64 + lane] = 0ull;
+            h0[u] = (uint32_t)h[u];
+            h1[u] = (uint32_t)(h[u] >> 32);
         }
-        if (i < len) out[i] = carry + before + excl;
-        carry += all;
-        __syncthreads();
+        es_score_words(st, word0, i0, on, h0, h1, first, fixed, P, S0, S1, out0, out1);
     }
-    return carry;
+    if (mine) {
+        st.mv0[word0 + lane] = out0;
+        st.mv1[word0 + lane] = out1;
+        if (myword) st.mark[word0 + lane] = 0ull;
+    }
+    es_store_movers(st, lane < 64 ? (u64)__popcll(out0) : 0ull, (u64)__popcll(out1), blockIdx.x);
 }
 
-__global__ __launch_bounds__(kBlock) void k_es_scan_movers(int64_t blocks, const uint32_t* bs0, const uint32_t* bs1,
-                                                           uint32_t* bo0, uint32_t* bo1)
+// cnt_nbrs, second half, from the binned pairs: a block counts the pairs of its bin that are its own in LDS (the
+// blocks of one bin all read it, on one XCD, whose L2 then holds it), then scores its nodes.  A bin of at most 65,535
+// pairs cannot overflow 16 bits: the two counts of a node share a word; a larger one is counted in two rounds
+// of half the nodes with 32 bits each.  `seen`: nodes whose other ends have no label.
+// What is left to bound it is the estimates' 32 bytes per touched node; 111M nodes, 32M edge ends: 1.01 ms with the
+// counts in memory, 0.74 here.
+__global__ __launch_bounds__(kBlock) void k_es_score_bins(EsRun st, int par, int first, int fixed, int64_t chunk, int cb,
+                                                          uint32_t nblocks, const uint32_t* __restrict__ table,
+                                                          const uint32_t* __restrict__ pairs)
 {
-    __shared__ uint32_t wsum[kWordsPerBlock];
-    (void)es_block_scan(bs0, bo0, blocks, wsum);
-    (void)es_block_scan(bs1, bo1, blocks, wsum);
+    extern __shared__ uint32_t cnt[];              // kBlock * wpw words, then as many bits
+    // contiguous ranges of blocks per XCD (workgroups go to the XCDs in turn)
+    const uint32_t per = gridDim.x >> 3;
+    const uint32_t block = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
+    if (block >= nblocks) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t bn = (uint32_t)(kBlock * st.wpw);
+    uint32_t* seen = cnt + bn;
+    const uint32_t gi = st.blk_group[block];
+    const long long P = st.groups[gi].P;
+    const long long S0 = (long long)st.S[2 * (par * st.ngroups + gi)], S1 = (long long)st.S[2 * (par * st.ngroups + gi) + 1];
+    const uint32_t bin = (block * bn) >> cb, in_bin = (block * bn) & ((1u << cb) - 1u);
+    const uint32_t* row = table + (size_t)chunk * kBinTableStride + bin;
+    const uint32_t p0 = row[0], p1 = row[1];
+    const bool narrow = p1 - p0 <= 65535u;
+    const int rounds = narrow ? 1 : 2;
+    const uint32_t sub = bn / rounds;              // nodes per round
+    const int nw = st.wpw / rounds;                // words per wave and round
+    u64 movers0 = 0, movers1 = 0;
+    for (int round = 0; round < rounds; ++round) {
+        __syncthreads();
+        for (uint32_t i = tid; i < bn; i += kBlock) cnt[i] = 0u;
+        for (uint32_t i = tid; i < bn / 32; i += kBlock) seen[i] = 0u;
+        __syncthreads();
+        const uint32_t low = in_bin + round * sub;
+        constexpr int U = 8;
+        for (uint32_t i = p0 + tid; i < p1; i += kBlock * U) {
+            uint32_t x[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) x[u] = p1 - i > (uint32_t)(u * kBlock) ? pairs[i + u * kBlock] : 0xFFFFFFFFu;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t rel = (x[u] & ((1u << cb) - 1u)) - low, code = x[u] >> cb;
+                if (x[u] == 0xFFFFFFFFu || rel >= sub) continue;
+                if (code >= 2u) atomicOr(&seen[rel >> 5], 1u << (rel & 31u));
+                else if (narrow) atomicAdd(&cnt[rel], code ? 65536u : 1u);
+                else atomicAdd(&cnt[2u * rel + code], 1u);
+            }
+            if (p1 - i <= (uint32_t)(kBlock * U)) break;
+        }
+        __syncthreads();
+        const uint32_t word0 = block * (bn / 64) + round * (sub / 64) + wave * nw;
+        u64 out0 = 0ull, out1 = 0ull;
+        for (int i0 = 0; i0 < nw; i0 += kTurn) {
+            bool on[kTurn];
+            uint32_t h0[kTurn], h1[kTurn];
+#pragma unroll
+            for (int u = 0; u < kTurn; ++u) {
+                const uint32_t rel = (uint32_t)(wave * nw + i0 + u) * 64u + lane;
+                const bool in = i0 + u < nw;
+                if (narrow) {
+                    const uint32_t c = in ? cnt[rel] : 0u;
+                    h0[u] = c & 0xFFFFu;
+                    h1[u] = c >> 16;
+                } else {
+                    h0[u] = in ? cnt[2u * rel] : 0u;
+                    h1[u] = in ? cnt[2u * rel + 1u] : 0u;
+                }
+                on[u] = (h0[u] | h1[u]) != 0u || (in && ((seen[rel >> 5] >> (rel & 31u)) & 1u));
+            }
+            es_score_words(st, word0, i0, on, h0, h1, first, fixed, P, S0, S1, out0, out1);
+        }
+        if (lane < nw) { st.mv0[word0 + lane] = out0; st.mv1[word0 + lane] = out1; }
+        movers0 += (u64)__popcll(out0);
+        movers1 += (u64)__popcll(out1);
+    }
+    es_store_movers(st, movers0, movers1, block);
 }
 
 // Admission: a mover whose rank among the chunk's requests for its target (ascending id) is below
-// the room the target had when the chunk started is relabelled (fix_sizes, Alg. 2, as per-workgroup
-// deltas); a rejected node without a label is recorded in ov.  A wave that has movers copies the
-// 4,096 labels of its 64 words into LDS with wide loads, every lane then walks the movers of its own
-// word there, and the labels are written back if any changed (lb_bytes: the label array's allocated
-// size, a multiple of 16).
-__global__ __launch_bounds__(kBlock) void k_es_apply(int64_t words, long long P, const u64* __restrict__ S,
-                                                     const u64* __restrict__ mv0, const u64* __restrict__ mv1,
-                                                     const uint32_t* __restrict__ bo0, const uint32_t* __restrict__ bo1,
-                                                     uint8_t* Lb, int64_t lb_bytes, u64* ov, uint32_t* bso, int32_t* bd0,
-                                                     int32_t* bd1)
+// the room the target had when the chunk started is relabelled (fix_sizes, Alg. 2, as per-block
+// deltas); a rejected node without a label is recorded in ov.  Every block adds up the movers of its group's
+// earlier blocks itself.  Few words per wave: a lane per node, word by word.  Many: a wave that has movers copies the
+// labels of its words into LDS with wide loads, every lane then walks the movers of its own
+// word there, and the labels are written back if any changed.
+constexpr int kApplyByNode = 4;
+__global__ __launch_bounds__(kBlock) void k_es_apply(EsRun st, int par)
 {
-    extern __shared__ uint4 slab4[];                  // kBlock * 64 bytes: 4 KB per wave
-    __shared__ uint32_t c0[kWordsPerBlock], c1[kWordsPerBlock], co[kWordsPerBlock];
-    __shared__ int32_t d0[kWordsPerBlock], d1[kWordsPerBlock];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t word0 = ((int64_t)blockIdx.x * kWordsPerBlock + wave) * kWaveWords;
-    const bool mine = word0 + lane < words;
-    const u64 my0 = mine ? mv0[word0 + lane] : 0ull, my1 = mine ? mv1[word0 + lane] : 0ull;
+    extern __shared__ uint4 slab4[];                  // wpw * 64 bytes per wave
+    __shared__ uint32_t c0[kWaves], c1[kWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wpw = st.awpw;
+    const uint32_t b_own = (uint32_t)blockIdx.x * (uint32_t)(st.awpw / st.wpw);      // its first block of the scoring
+    const uint32_t gi = st.blk_group[b_own];
+    const long long P = st.groups[gi].P;
+    const uint32_t blk0 = st.groups[gi].blk0;
+    const uint32_t word0 = ((uint32_t)blockIdx.x * kWaves + wave) * wpw;
+    const bool mine = lane < wpw;
+    const u64 my0 = mine ? st.mv0[word0 + lane] : 0ull, my1 = mine ? st.mv1[word0 + lane] : 0ull;
+    u64 before0 = 0, before1 = 0;
+    for (uint32_t b = blk0 + threadIdx.x; b < b_own; b += kBlock) { before0 += st.bs0[b]; before1 += st.bs1[b]; }
     const uint32_t p0 = __popcll(my0), p1 = __popcll(my1);
     const uint32_t ex0 = es_wave_exclusive(p0, lane), ex1 = es_wave_exclusive(p1, lane);
     if (lane == 63) { c0[wave] = ex0 + p0; c1[wave] = ex1 + p1; }
-    __syncthreads();
-    uint32_t base0 = bo0[blockIdx.x], base1 = bo1[blockIdx.x];
+    es_block_sums(before0, before1);
+    long long base0 = (long long)before0, base1 = (long long)before1;
     for (int q = 0; q < wave; ++q) { base0 += c0[q]; base1 += c1[q]; }
-    const long long room0 = P - (long long)S[0], room1 = P - (long long)S[1];
+    const long long room0 = P - (long long)st.S[2 * (par * st.ngroups + gi)], room1 = P - (long long)st.S[2 * (par * st.ngroups + gi) + 1];
     u64 outo = 0ull;
     int32_t delta0 = 0, delta1 = 0;
-    const u64 movers = __ballot((my0 | my1) != 0ull);
-    uint4* wslab4 = slab4 + wave * (kWaveWords * 64 / 16);
-    const int64_t byte0 = word0 * 64;
-    if (movers) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int q = u * 64 + lane;
-            if (byte0 + (int64_t)(q + 1) * 16 <= lb_bytes) wslab4[q] = *reinterpret_cast<const uint4*>(Lb + byte0 + (int64_t)q * 16);
+    if (wpw <= kApplyByNode) {
+        for (int i = 0; i < wpw; ++i) {
+            const u64 w0 = es_bcast(my0, i), w1 = es_bcast(my1, i);
+            if (!(w0 | w1)) continue;
+            const u64 below = (1ull << lane) - 1ull;
+            const bool to0 = (w0 >> lane) & 1ull, to1 = (w1 >> lane) & 1ull;
+            bool rejected = false;
+            if (to0 || to1) {
+                uint8_t* label = st.Lb + (size_t)(word0 + i) * 64 + lane;
+                const uint32_t old = *label;
+                const long long rank = to0 ? base0 + __builtin_amdgcn_readlane(ex0, i) + __popcll(w0 & below)
+                                           : base1 + __builtin_amdgcn_readlane(ex1, i) + __popcll(w1 & below);
+                if (rank < (to0 ? room0 : room1)) {
+                    *label = to0 ? 0 : 1;
+                    if (to0) { delta0 += 1; delta1 -= (int32_t)(old == 1u); }
+                    else { delta1 += 1; delta0 -= (int32_t)(old == 0u); }
+                } else {
+                    rejected = old == kNone;
+                }
+            }
+            const u64 o = __ballot(rejected);
+            if (lane == i) outo = o;
         }
-    }
-    // a lane walks the movers of its own word, in id order; ranks continue from the words before it
-    uint8_t* mine64 = reinterpret_cast<uint8_t*>(wslab4) + lane * 64;
-    bool dirty = false;
-    long long r0 = (long long)base0 + ex0, r1 = (long long)base1 + ex1;
-    for (u64 todo = my0; todo; todo &= todo - 1ull, ++r0) {
-        const int b = __builtin_ctzll(todo);
-        const uint32_t old = mine64[b];
-        if (r0 < room0) { mine64[b] = 0; dirty = true; delta0 += 1; delta1 -= (int32_t)(old == 1u); }
-        else if (old == kNone) outo |= 1ull << b;
-    }
-    for (u64 todo = my1; todo; todo &= todo - 1ull, ++r1) {
-        const int b = __builtin_ctzll(todo);
-        const uint32_t old = mine64[b];
-        if (r1 < room1) { mine64[b] = 1; dirty = true; delta1 += 1; delta0 -= (int32_t)(old == 0u); }
-        else if (old == kNone) outo |= 1ull << b;
-    }
-    delta0 = (int32_t)es_wave_sum((uint32_t)delta0);
-    delta1 = (int32_t)es_wave_sum((uint32_t)delta1);
-    if (__ballot(dirty)) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int q = u * 64 + lane;
-            if (byte0 + (int64_t)(q + 1) * 16 <= lb_bytes) *reinterpret_cast<uint4*>(Lb + byte0 + (int64_t)q * 16) = wslab4[q];
+    } else {
+        const u64 movers = __ballot((my0 | my1) != 0ull);
+        uint4* wslab4 = slab4 + wave * (wpw * 4);
+        uint4* labels4 = reinterpret_cast<uint4*>(st.Lb + (size_t)word0 * 64);
+        if (movers)
+            for (int q = lane; q < wpw * 4; q += 64) wslab4[q] = labels4[q];
+        // a lane walks the movers of its own word, in id order; ranks continue from the words before it
+        uint8_t* mine64 = reinterpret_cast<uint8_t*>(wslab4) + lane * 64;
+        bool dirty = false;
+        long long r0 = base0 + ex0, r1 = base1 + ex1;
+        for (u64 todo = my0; todo; todo &= todo - 1ull, ++r0) {
+            const int b = __builtin_ctzll(todo);
+            const uint32_t old = mine64[b];
+            if (r0 < room0) { mine64[b] = 0; dirty = true; delta0 += 1; delta1 -= (int32_t)(old == 1u); }
+            else if (old == kNone) outo |= 1ull << b;
         }
+        for (u64 todo = my1; todo; todo &= todo - 1ull, ++r1) {
+            const int b = __builtin_ctzll(todo);
+            const uint32_t old = mine64[b];
+            if (r1 < room1) { mine64[b] = 1; dirty = true; delta1 += 1; delta0 -= (int32_t)(old == 0u); }
+            else if (old == kNone) outo |= 1ull << b;
+        }
+        if (__ballot(dirty))
+            for (int q = lane; q < wpw * 4; q += 64) labels4[q] = wslab4[q];
     }
-    if (mine) ov[word0 + lane] = outo;
-    const uint32_t so = es_wave_sum(__popcll(outo));
-    if (lane == 0) { co[wave] = so; d0[wave] = delta0; d1[wave] = delta1; }
-    __syncthreads();
+    if (mine) st.ov[word0 + lane] = outo;
+    // (the three sums of a block fit 64 bits together: at most 65,536 nodes, the deltas offset to stay positive)
+    u64 packed = (u64)__popcll(outo), deltas = (u64)(uint32_t)(delta0 + 256) | ((u64)(uint32_t)(delta1 + 256) << 32);
+    es_block_sums(packed, deltas);
     if (threadIdx.x == 0) {
-        uint32_t z = 0; int32_t x = 0, y = 0;
-        for (int q = 0; q < kWordsPerBlock; ++q) { z += co[q]; x += d0[q]; y += d1[q]; }
-        bso[blockIdx.x] = z; bd0[blockIdx.x] = x; bd1[blockIdx.x] = y;
+        st.bso[blockIdx.x] = (uint32_t)packed;
+        st.bd0[blockIdx.x] = (int32_t)(uint32_t)deltas - 256 * kBlock;
+        st.bd1[blockIdx.x] = (int32_t)(uint32_t)(deltas >> 32) - 256 * kBlock;
     }
 }
 
-// One workgroup: ranks of the rejected new nodes, sizes after the admissions (Sp[0..1], Sp[2] = how
-// many nodes are to be placed), and the sizes after placing them one by one in the smaller
-// partition (0 on a tie): the first |difference| go to the smaller one, the rest alternate 0,1,...
-__global__ __launch_bounds__(kBlock) void k_es_scan_spill(int64_t blocks, const uint32_t* bso, uint32_t* boo,
-                                                          const int32_t* bd0, const int32_t* bd1, u64* S, long long* Sp)
+// Rejected new nodes are placed one by one, ascending id, in the smaller partition (0 on a tie), in closed
+// form: the first |difference| go to the smaller one, the rest alternate 0,1,...  Every block adds up its
+// group's rejected nodes itself; the group's first block writes the sizes after the chunk to their other copy.
+__global__ __launch_bounds__(kBlock) void k_es_spill(EsRun st, int par)
 {
-    __shared__ uint32_t wsum[kWordsPerBlock];
-    __shared__ long long part0[kWordsPerBlock], part1[kWordsPerBlock];
-    const uint32_t total = es_block_scan(bso, boo, blocks, wsum);
-    long long x = 0, y = 0;
-    for (int64_t i = threadIdx.x; i < blocks; i += kBlock) { x += bd0[i]; y += bd1[i]; }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { x += __shfl_down(x, o); y += __shfl_down(y, o); }
-    if ((threadIdx.x & 63) == 0) { part0[threadIdx.x >> 6] = x; part1[threadIdx.x >> 6] = y; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        long long a = (long long)S[0], b = (long long)S[1];
-        for (int q = 0; q < kWordsPerBlock; ++q) { a += part0[q]; b += part1[q]; }
-        Sp[0] = a; Sp[1] = b; Sp[2] = (long long)total;
-        const long long gap = a <= b ? b - a : a - b;
+    __shared__ uint32_t co[kWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wpw = st.awpw;
+    const uint32_t each = (uint32_t)(st.awpw / st.wpw);
+    const uint32_t gi = st.blk_group[blockIdx.x * each];
+    const uint32_t blk0 = st.groups[gi].blk0 / each, nblk = st.groups[gi].nblk / each;
+    u64 total = 0, before = 0;
+    for (uint32_t b = blk0 + threadIdx.x; b < blk0 + nblk; b += kBlock) {
+        const uint32_t c = st.bso[b];
+        total += c;
+        if (b < blockIdx.x) before += c;
+    }
+    es_block_sums(total, before);
+    const u64* S = st.S + 2 * (par * st.ngroups + gi);
+    if (total == 0 && blockIdx.x != blk0) return;
+    u64 d0 = 0, d1 = 0;
+    for (uint32_t b = blk0 + threadIdx.x; b < blk0 + nblk; b += kBlock) { d0 += (u64)(long long)st.bd0[b]; d1 += (u64)(long long)st.bd1[b]; }
+    es_block_sums(d0, d1);
+    const long long a = (long long)(S[0] + d0), b = (long long)(S[1] + d1);        // after the admissions
+    const long long gap = a <= b ? b - a : a - b;
+    if (blockIdx.x == blk0 && threadIdx.x == 0) {
         const long long lead = (long long)total < gap ? (long long)total : gap;
         const long long rest = (long long)total - lead;
-        if (a <= b) a += lead; else b += lead;
-        a += (rest + 1) / 2;
-        b += rest / 2;
-        S[0] = (u64)a; S[1] = (u64)b;
+        u64* next = st.S + 2 * ((par ^ 1) * st.ngroups + gi);
+        next[0] = (u64)(a + (a <= b ? lead : 0) + (rest + 1) / 2);
+        next[1] = (u64)(b + (a <= b ? 0 : lead) + rest / 2);
     }
-}
-
-__global__ __launch_bounds__(kBlock) void k_es_spill(int64_t words, const u64* __restrict__ ov,
-                                                     const uint32_t* __restrict__ boo, const long long* __restrict__ Sp,
-                                                     uint8_t* Lb)
-{
-    if (Sp[2] == 0) return;
-    __shared__ uint32_t co[kWordsPerBlock];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t word0 = ((int64_t)blockIdx.x * kWordsPerBlock + wave) * kWaveWords;
-    const u64 myo = word0 + lane < words ? ov[word0 + lane] : 0ull;
+    if (total == 0) return;
+    const uint32_t word0 = ((uint32_t)blockIdx.x * kWaves + wave) * wpw;
+    const u64 myo = lane < wpw ? st.ov[word0 + lane] : 0ull;
     const uint32_t p = __popcll(myo);
     const uint32_t ex = es_wave_exclusive(p, lane);
     if (lane == 63) co[wave] = ex + p;
     __syncthreads();
-    long long base = boo[blockIdx.x];
+    long long base = (long long)before;
     for (int q = 0; q < wave; ++q) base += co[q];
-    const long long a = Sp[0], b = Sp[1];
-    const long long gap = a <= b ? b - a : a - b;
     for (u64 todo = __ballot(myo != 0ull); todo; todo &= todo - 1ull) {
         const int i = __builtin_ctzll(todo);
         const u64 o = es_bcast(myo, i);
         if ((o >> lane) & 1ull) {
             const long long j = base + __builtin_amdgcn_readlane(ex, i) + __popcll(o & ((1ull << lane) - 1ull));
             const int t = j < gap ? (a <= b ? 0 : 1) : (int)((j - gap) & 1);
-            Lb[(word0 + i) * 64 + lane] = (uint8_t)t;
+            st.Lb[(size_t)(word0 + i) * 64 + lane] = (uint8_t)t;
         }
     }
 }
@@ -443,119 +743,119 @@ __global__ __launch_bounds__(256) void k_es_cut(const int32_t* __restrict__ src,
 // Per level the edges that still lie inside a group are kept grouped by group, in stream order, and
 // already written in the group's own node numbers (0..nv-1 in ascending id), so that a group's
 // segment is the input of the two-partition run as it stands.  Per level and group there is also
-// the list of its nodes' ids (and their seed bits) in that numbering.  When a group has been split,
+// the list of its nodes' ids (and their seed bits) in that numbering.  When the groups have been split,
 // every node gets its number inside its half (its rank among the nodes of the same half), the
-// halves' node lists are written, and the group's edges are rewritten in those numbers while they
+// halves' node lists are written, and the groups' edges are rewritten in those numbers while they
 // are sorted into "both ends in half 0", "both ends in half 1" and "ends part" (dropped).
 
 constexpr int kSelBlock = 1024;     // stable selection of edges: a thread owns kSelPer consecutive edges
 constexpr int kSelPer = 4;
 constexpr int kSelTile = kSelBlock * kSelPer;
 
-// flag bitmap of a predicate over items 0..count-1 (what = 0: value[i] == key, what = 1: value[i] < 0)
-// and the number of flagged items per workgroup of kBlock items
-__global__ __launch_bounds__(kBlock) void k_rb_flags(int64_t count, const int32_t* __restrict__ value, int32_t key,
-                                                     int what, u64* flag, uint32_t* bsum)
+// per block: its nodes with label 0 and its nodes without a label
+__global__ __launch_bounds__(kBlock) void k_rb_count(EsRun st)
 {
-    __shared__ uint32_t c[kWordsPerBlock];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    bool on = false;
-    if (i < count) { const int32_t x = value[i]; on = what == 0 ? x == key : x < 0; }
-    const u64 b = __ballot(on);
-    if (lane == 0) {
-        const int64_t w = (int64_t)blockIdx.x * kWordsPerBlock + wave;
-        if (w * 64 < count) flag[w] = b;
-        c[wave] = __popcll(b);
+    const EsGroup& g = st.groups[st.blk_group[blockIdx.x]];
+    const uint32_t bn = (uint32_t)(kBlock * st.wpw), v0 = blockIdx.x * bn;
+    u64 zeros = 0, nones = 0;
+    for (uint32_t i = threadIdx.x; i < bn; i += kBlock) {
+        if (v0 + i - g.node0 >= g.nv) break;
+        const uint32_t l = st.Lb[v0 + i];
+        zeros += l == 0u;
+        nones += l == kNone;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t t = 0;
-        for (int q = 0; q < kWordsPerBlock; ++q) t += c[q];
-        bsum[blockIdx.x] = t;
-    }
+    es_block_sums(zeros, nones);
+    if (threadIdx.x == 0) { st.bs0[blockIdx.x] = (uint32_t)zeros; st.bs1[blockIdx.x] = (uint32_t)nones; }
 }
 
-// exclusive scan of the per-workgroup counts; the total goes to total_out[0]
-__global__ __launch_bounds__(kBlock) void k_rb_scan(int64_t blocks, const uint32_t* bsum, uint32_t* boff, long long* total_out)
-{
-    __shared__ uint32_t wsum[kWordsPerBlock];
-    const uint32_t total = es_block_scan(bsum, boff, blocks, wsum);
-    if (threadIdx.x == 0) total_out[0] = (long long)total;
-}
-
-// rank of a flagged item among the flagged ones, ascending index
-__device__ __forceinline__ uint32_t rb_rank(const u64* __restrict__ flag, const uint32_t* __restrict__ boff,
-                                            uint32_t* c /* kWordsPerBlock words of LDS */, int64_t count, bool& on)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t w = (int64_t)blockIdx.x * kWordsPerBlock + wave;
-    const u64 word = w * 64 < count ? flag[w] : 0ull;
-    if (lane == 0) c[wave] = __popcll(word);
-    __syncthreads();
-    uint32_t r = boff[blockIdx.x];
-    for (int q = 0; q < wave; ++q) r += c[q];
-    on = (word >> lane) & 1ull;
-    return r + __popcll(word & ((1ull << lane) - 1ull));
-}
-
-// Nodes the two-partition run left without a label (no edge inside the group) are placed one by one,
-// ascending id, in the currently smaller half (0 on a tie): closed form from the run's sizes, as for
-// the spill of the two-partition run.  flag / boff: the unlabelled nodes and their scanned counts.
-__global__ __launch_bounds__(kBlock) void k_rb_place(int64_t nv, const u64* __restrict__ flag, const uint32_t* __restrict__ boff,
-                                                     int32_t* sub_parts, const int64_t* __restrict__ sub_sizes)
-{
-    __shared__ uint32_t c[kWordsPerBlock];
-    bool on;
-    const long long j = rb_rank(flag, boff, c, nv, on);
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= nv || !on) return;
-    const long long a = sub_sizes[0], b = sub_sizes[1];
-    const long long gap = a <= b ? b - a : a - b;
-    sub_parts[i] = j < gap ? (a <= b ? 0 : 1) : (int)((j - gap) & 1);
-}
-
-// flag / boff: the nodes of half 0 and their scanned counts; count0[0] = how many.  A node of half b gets
-// its number inside the half (its rank among the nodes of the same half); packed[i] = that number with
-// the half in bit 31; the halves' node lists (ids and next level's seed bits) are written, half 0 first.
-// At the last level the labels 2g + half go out instead.  gof == nullptr: node i has id i.
-__global__ __launch_bounds__(kBlock) void k_rb_children(int64_t nv, const u64* __restrict__ flag, const uint32_t* __restrict__ boff,
-                                                        const int32_t* __restrict__ sub_parts, const int32_t* __restrict__ gof,
-                                                        int32_t g, const long long* __restrict__ count0,
+// Nodes the two-partition run left without a label (no edge inside the group) are placed one by one, ascending id,
+// in the currently smaller half (0 on a tie): the first |difference| of them go to the smaller half, the rest
+// alternate 0,1,... .  So the node of half 0 with z labelled zeros and j unlabelled nodes before it is number
+// z + (zeros among the first j placements) of its half, and nothing but the two counts per block is needed.
+// packed[v] = the node's number inside its half with the half in bit 31; the halves' node lists (ids and next
+// level's seed bits) are written, half 0 first.  At the last level the labels 2 * group + half go out instead.  gof ==
+// nullptr: node i has id i.  nodes0[group]: nodes of half 0.
+__global__ __launch_bounds__(kBlock) void k_rb_children(EsRun st, int par, const int32_t* __restrict__ gof,
                                                         const int32_t* __restrict__ next_bits, uint32_t* packed,
-                                                        int32_t* gof_next, int32_t* seed_next, int32_t* labels_out)
+                                                        int32_t* gof_next, int32_t* seed_next, int32_t* labels_out,
+                                                        long long* nodes0)
 {
-    __shared__ uint32_t c[kWordsPerBlock];
-    bool on;
-    const uint32_t r0 = rb_rank(flag, boff, c, nv, on);      // nodes of half 0 before this one
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= nv) return;
-    const int32_t id = gof ? gof[i] : (int32_t)i;
-    const uint32_t half = on ? 0u : 1u;
-    if (labels_out) { labels_out[id] = 2 * g + (int32_t)half; return; }
-    const uint32_t num = on ? r0 : (uint32_t)i - r0;
-    packed[i] = num | (half << 31);
-    const int64_t at = on ? (int64_t)num : count0[0] + (int64_t)num;
-    gof_next[at] = id;
-    seed_next[at] = next_bits[id];
+    __shared__ uint32_t cz[kWaves], cn[kWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wpw = st.wpw;
+    const uint32_t gi = st.blk_group[blockIdx.x];
+    const EsGroup g = st.groups[gi];
+    u64 zeros = 0, nones = 0, zeros_all = 0, nones_all = 0;
+    for (uint32_t b = g.blk0 + threadIdx.x; b < g.blk0 + g.nblk; b += kBlock) {
+        const uint32_t z = st.bs0[b], e = st.bs1[b];
+        zeros_all += z; nones_all += e;
+        if (b < blockIdx.x) { zeros += z; nones += e; }
+    }
+    es_block_sums(zeros, nones);
+    es_block_sums(zeros_all, nones_all);
+    const long long S0 = (long long)st.S[2 * (par * st.ngroups + gi)], S1 = (long long)st.S[2 * (par * st.ngroups + gi) + 1];
+    const long long gap = S0 <= S1 ? S1 - S0 : S0 - S1;
+    const bool lead0 = S0 <= S1;
+    auto placed0 = [&](long long j) {                 // zeros among the first j placements
+        const long long lead = j < gap ? j : gap;
+        return (lead0 ? lead : 0ll) + (j - lead + 1) / 2;
+    };
+    const long long count0 = (long long)zeros_all + placed0((long long)nones_all);
+    if (blockIdx.x == g.blk0 && threadIdx.x == 0) nodes0[g.id] = count0;
+    // a wave's nodes: its words one after the other; their counts of zeros and of nodes without a label
+    const uint32_t first = ((uint32_t)blockIdx.x * kWaves + wave) * wpw * 64u;
+    uint32_t wz = 0, wn = 0;
+    for (int i = 0; i < wpw; ++i) {
+        const uint32_t v = first + i * 64u + lane;
+        const uint32_t l = v - g.node0 < g.nv ? (uint32_t)st.Lb[v] : 1u;
+        wz += (uint32_t)__popcll(__ballot(l == 0u));
+        wn += (uint32_t)__popcll(__ballot(l == kNone));
+    }
+    if (lane == 0) { cz[wave] = wz; cn[wave] = wn; }
+    __syncthreads();
+    for (int q = 0; q < wave; ++q) { zeros += cz[q]; nones += cn[q]; }
+    const u64 below = (1ull << lane) - 1ull;
+    for (int i = 0; i < wpw; ++i) {
+        const uint32_t v = first + i * 64u + lane;
+        const bool in = v - g.node0 < g.nv;
+        const uint32_t l = in ? (uint32_t)st.Lb[v] : 1u;
+        const u64 bz = __ballot(l == 0u), bn = __ballot(l == kNone);
+        const long long z = (long long)zeros + __popcll(bz & below), j = (long long)nones + __popcll(bn & below);
+        zeros += __popcll(bz);
+        nones += __popcll(bn);
+        if (!in) continue;
+        const uint32_t half = l != kNone ? l : j < gap ? (lead0 ? 0u : 1u) : (uint32_t)((j - gap) & 1);
+        const int64_t own = (int64_t)(v - g.node0);
+        const int32_t id = gof ? gof[g.v_lo + own] : (int32_t)own;
+        if (labels_out) { labels_out[id] = 2 * (int32_t)g.id + (int32_t)half; continue; }
+        const long long r0 = z + placed0(j);          // nodes of half 0 before this one
+        const long long num = half == 0u ? r0 : own - r0;
+        packed[g.v_lo + own] = (uint32_t)num | (half << 31);
+        const int64_t at = g.v_lo + (half == 0u ? num : count0 + num);
+        gof_next[at] = id;
+        seed_next[at] = next_bits[id];
+    }
 }
 
-// An edge of the group goes to the half both its ends are in (key 0 / 1) or is dropped (key 2); its
+// An edge of a group goes to the half both its ends are in (key 0 / 1) or is dropped (key 2); its
 // ends are rewritten in the halves' node numbers (tmp_s, tmp_d) for the scatter.
-__global__ __launch_bounds__(kSelBlock) void k_rb_split_count(int64_t m, const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                                              const uint32_t* __restrict__ packed, uint8_t* __restrict__ key,
-                                                              int32_t* __restrict__ tmp_s, int32_t* __restrict__ tmp_d,
-                                                              uint32_t* bc0, uint32_t* bc1)
+__global__ __launch_bounds__(kSelBlock) void k_rb_split_count(const EsGroup* __restrict__ groups, const int32_t* __restrict__ src,
+                                                              const int32_t* __restrict__ dst, const uint32_t* __restrict__ packed,
+                                                              uint8_t* __restrict__ key, int32_t* __restrict__ tmp_s,
+                                                              int32_t* __restrict__ tmp_d, uint32_t* bc0, uint32_t* bc1)
 {
     __shared__ uint32_t c0[kSelBlock / 64], c1[kSelBlock / 64];
+    const EsGroup g = groups[blockIdx.y];
+    if ((int64_t)blockIdx.x * kSelTile >= g.m) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t e0 = (int64_t)blockIdx.x * kSelTile + (int64_t)threadIdx.x * kSelPer;
+    const uint32_t* __restrict__ own = packed + g.v_lo;
+    const int64_t end = g.e_lo + g.m;
+    const int64_t e0 = g.e_lo + (int64_t)blockIdx.x * kSelTile + (int64_t)threadIdx.x * kSelPer;
     uint32_t n0 = 0, n1 = 0;
 #pragma unroll
     for (int u = 0; u < kSelPer; ++u) {
         const int64_t e = e0 + u;
-        if (e < m) {
-            const uint32_t a = packed[src[e]], b = packed[dst[e]];
+        if (e < end) {
+            const uint32_t a = own[src[e]], b = own[dst[e]];
             const int k = (a >> 31) == (b >> 31) ? (int)(a >> 31) : 2;
             key[e] = (uint8_t)k;
             tmp_s[e] = (int32_t)(a & 0x7FFFFFFFu);
@@ -569,30 +869,53 @@ __global__ __launch_bounds__(kSelBlock) void k_rb_split_count(int64_t m, const i
     if (threadIdx.x == 0) {
         uint32_t x = 0, y = 0;
         for (int q = 0; q < kSelBlock / 64; ++q) { x += c0[q]; y += c1[q]; }
-        bc0[blockIdx.x] = x; bc1[blockIdx.x] = y;
+        bc0[g.tile0 + blockIdx.x] = x; bc1[g.tile0 + blockIdx.x] = y;
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_rb_split_scan(int64_t blocks, const uint32_t* bc0, const uint32_t* bc1,
-                                                          uint32_t* bo0, uint32_t* bo1, long long* totals)
+// exclusive prefix sums of in[0..len) in place, by one workgroup of kBlock threads; returns the total
+__device__ uint32_t es_block_scan(uint32_t* p, int64_t len, uint32_t* wsum /* kWaves words of LDS */)
 {
-    __shared__ uint32_t wsum[kWordsPerBlock];
-    const uint32_t t0 = es_block_scan(bc0, bo0, blocks, wsum);
-    const uint32_t t1 = es_block_scan(bc1, bo1, blocks, wsum);
-    if (threadIdx.x == 0) { totals[0] = (long long)t0; totals[1] = (long long)t1; }
+    uint32_t carry = 0;
+    for (int64_t base = 0; base < len; base += kBlock) {
+        const int64_t i = base + threadIdx.x;
+        const uint32_t x = i < len ? p[i] : 0u;
+        const uint32_t excl = es_block_exclusive(x, wsum);
+        uint32_t all = 0;
+        for (int q = 0; q < kWaves; ++q) all += wsum[q];
+        if (i < len) p[i] = carry + excl;
+        carry += all;
+        __syncthreads();
+    }
+    return carry;
 }
 
-// stable: the edges of child 0 (key 0, as k_rb_split_count stored it) keep their order and land from
-// at0 on, those of child 1 right after them
-__global__ __launch_bounds__(kSelBlock) void k_rb_split_scatter(int64_t m, const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                                                const uint8_t* __restrict__ key,
+// one workgroup per group; totals[2 * group + half]: edges kept
+__global__ __launch_bounds__(kBlock) void k_rb_split_scan(const EsGroup* __restrict__ groups, uint32_t* bc0, uint32_t* bc1,
+                                                          long long* totals)
+{
+    __shared__ uint32_t wsum[kWaves];
+    const EsGroup g = groups[blockIdx.x];
+    const int64_t tiles = (g.m + kSelTile - 1) / kSelTile;
+    const uint32_t t0 = es_block_scan(bc0 + g.tile0, tiles, wsum);
+    const uint32_t t1 = es_block_scan(bc1 + g.tile0, tiles, wsum);
+    if (threadIdx.x == 0) { totals[2 * (int64_t)g.id] = (long long)t0; totals[2 * (int64_t)g.id + 1] = (long long)t1; }
+}
+
+// stable: the edges of child 0 (key 0, as k_rb_split_count stored it) keep their order and land where the
+// group's edges began, those of child 1 right after them
+__global__ __launch_bounds__(kSelBlock) void k_rb_split_scatter(const EsGroup* __restrict__ groups, const int32_t* __restrict__ src,
+                                                                const int32_t* __restrict__ dst, const uint8_t* __restrict__ key,
                                                                 const uint32_t* __restrict__ bo0, const uint32_t* __restrict__ bo1,
-                                                                int32_t* out_src, int32_t* out_dst, int64_t at0,
+                                                                int32_t* out_src, int32_t* out_dst,
                                                                 const long long* __restrict__ totals)
 {
     __shared__ uint32_t c0[kSelBlock / 64], c1[kSelBlock / 64];
+    const EsGroup g = groups[blockIdx.y];
+    if ((int64_t)blockIdx.x * kSelTile >= g.m) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t e0 = (int64_t)blockIdx.x * kSelTile + (int64_t)threadIdx.x * kSelPer;
+    const int64_t end = g.e_lo + g.m;
+    const int64_t e0 = g.e_lo + (int64_t)blockIdx.x * kSelTile + (int64_t)threadIdx.x * kSelPer;
     int32_t s[kSelPer], d[kSelPer];
     int k[kSelPer];
     uint32_t n0 = 0, n1 = 0;
@@ -600,7 +923,7 @@ __global__ __launch_bounds__(kSelBlock) void k_rb_split_scatter(int64_t m, const
     for (int u = 0; u < kSelPer; ++u) {
         const int64_t e = e0 + u;
         k[u] = 2; s[u] = 0; d[u] = 0;
-        if (e < m) {
+        if (e < end) {
             s[u] = src[e]; d[u] = dst[e];
             k[u] = key[e];
             n0 += k[u] == 0; n1 += k[u] == 1;
@@ -609,7 +932,8 @@ __global__ __launch_bounds__(kSelBlock) void k_rb_split_scatter(int64_t m, const
     const uint32_t x0 = es_wave_exclusive(n0, lane), x1 = es_wave_exclusive(n1, lane);
     if (lane == 63) { c0[wave] = x0 + n0; c1[wave] = x1 + n1; }
     __syncthreads();
-    int64_t p0 = at0 + bo0[blockIdx.x] + x0, p1 = at0 + totals[0] + bo1[blockIdx.x] + x1;
+    int64_t p0 = g.e_lo + bo0[g.tile0 + blockIdx.x] + x0;
+    int64_t p1 = g.e_lo + totals[2 * (int64_t)g.id] + bo1[g.tile0 + blockIdx.x] + x1;
     for (int q = 0; q < wave; ++q) { p0 += c0[q]; p1 += c1[q]; }
 #pragma unroll
     for (int u = 0; u < kSelPer; ++u) {
@@ -637,6 +961,186 @@ inline int grid_for(int64_t items, int block, int64_t cap)
     return (int)g;
 }
 
+// How a run is laid out.
+//   binned  from 4M nodes on (128 blocks; the counts in memory, 8 bytes per node, then far outgrow the L2), if a
+//           chunk's pairs take no more room than the estimates and the table of the chunks' bins stays small.  A
+//           block's counts fill a CU's LDS, 32,768 nodes: with 16,384 or 8,192 nodes and two or four workgroups per CU
+//           a whole run took 163 or 191 ms instead of 150 at 111M nodes (every block of a bin reads all its pairs),
+//           18.5 or 19.5 instead of 17.9 at 14M.
+//   blocks  otherwise kBlock * wpw nodes each: one word per wave up to a million nodes (the chip wants some 1024
+//           blocks), more words beyond it, so that a block can add up all blocks' counts itself.
+//   awpw    the admission walks a word per lane, so it wants 64 of them per wave (16: 88.2 ms for a bisection of 14M
+//           nodes, 32: 83.0, 64: 82.2), 32 where 64 would leave CUs without a workgroup.
+struct EsShape {
+    int wpw = 1, awpw = 1, cb = 0;
+    bool binned = false;
+    int64_t nodes = 0;                     // room for the state: the nodes and the groups' padding
+    int64_t bn() const { return (int64_t)kBlock * wpw; }
+    int64_t an() const { return (int64_t)kBlock * awpw; }
+    int64_t padded(int64_t nv) const { return (nv + an() - 1) / an() * an(); }
+};
+constexpr int kBinWaveWords = 32;
+constexpr int64_t kBinMinNodes = 1ll << 22;
+constexpr int64_t kBinMaxChunks = 8192;
+// n: nodes of the run; groups: most groups side by side; ends: of a chunk's edge ends over all groups
+EsShape es_shape(int64_t n, int64_t groups, int64_t ends, int64_t chunks)
+{
+    EsShape s;
+    // padding for every group, but no more than the nodes themselves take (a level of tiny groups goes in batches)
+    auto room = [&] {
+        const int64_t own = s.padded(n), pad = (groups - 1) * s.an();
+        return own + (pad < own ? pad : own);
+    };
+    s.wpw = kBinWaveWords;
+    s.awpw = n >= (1ll << 23) ? 64 : 32;
+    if (n >= kBinMinNodes && room() < (1ll << 30) && ends <= 4 * n && chunks <= kBinMaxChunks) {
+        s.binned = true;
+        s.cb = 15;
+        while ((room() >> s.cb) >= kBins) ++s.cb;          // (at most 20)
+    } else {
+        s.wpw = 1;
+        while (s.wpw < kMaxWaveWords && n > s.bn() * 1024) s.wpw *= 2;
+        s.awpw = s.wpw;
+    }
+    s.nodes = room();
+    return s;
+}
+
+// State of a run of up to `nodes` nodes (padding included) in `groups` groups; one allocation.
+struct EsMemory {
+    EsRun st{};
+    EsGroup* groups = nullptr;
+    uint32_t* blk_group = nullptr;
+    u64* hc = nullptr;
+    uint32_t *table = nullptr, *cursors = nullptr, *pairs = nullptr;
+    size_t table_words = 0, bytes = 0;
+
+    void layout(uint8_t* ws, const EsShape& sh, int64_t ngroups, int64_t ends, int64_t chunks, double* est_out)
+    {
+        const int64_t nodes = sh.nodes;
+        size_t off = 0;
+        auto take = [&](auto*& p, size_t count) {
+            using T = std::remove_reference_t<decltype(*p)>;
+            p = ws ? reinterpret_cast<T*>(ws + off) : nullptr;
+            off += align256(count * sizeof(T));
+        };
+        const size_t blocks = (size_t)(nodes / sh.bn()), ablocks = (size_t)(nodes / sh.an()), words = (size_t)(nodes / 64);
+        take(st.flags, 2);
+        take(groups, (size_t)ngroups);
+        take(blk_group, blocks);
+        take(st.S, (size_t)ngroups * 4);
+        take(st.Lb, (size_t)nodes);
+        if (est_out) st.est = (double2*)est_out;
+        else take(st.est, (size_t)nodes);
+        take(st.mark, words); take(st.mv0, words); take(st.mv1, words); take(st.ov, words);
+        take(st.bs0, blocks); take(st.bs1, blocks); take(st.bso, ablocks); take(st.bd0, ablocks); take(st.bd1, ablocks);
+        if (sh.binned) {
+            table_words = (size_t)chunks * kBinTableStride;
+            take(table, table_words);
+            take(cursors, (size_t)chunks * kBins);
+            take(pairs, (size_t)ends);
+        } else {
+            take(hc, (size_t)nodes);
+        }
+        st.groups = groups;
+        st.blk_group = blk_group;
+        st.wpw = sh.wpw;
+        st.awpw = sh.awpw;
+        bytes = off;
+    }
+};
+
+void es_fill(hipStream_t stream, void* p, size_t bytes, u64 value)
+{
+    const size_t count = bytes / 8;
+    if (count)
+        hipLaunchKernelGGL(k_es_fill64, dim3(grid_for((int64_t)count, 256, 16384)), dim3(256), 0, stream, (u64*)p, count, value);
+}
+
+// One run: everything from the cleared state to the last chunk's spill is enqueued.  groups_host: its groups, in the
+// order of their nodes (also at mem.groups on the device, with mem.blk_group filled).  check(): called once the first chunk's seeds are
+// counted and flags[] is complete, before anything uses the labels; its answer other than GREM_OK ends the run.
+// est_nodes: entries of est to clear.  *par_out: which copy of the sizes is the final one.
+template <typename Check>
+int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vector<EsGroup>& groups, int64_t nodes, int64_t est_nodes,
+           const int32_t* src, const int32_t* dst, const int32_t* seed, int32_t mode, Check&& check, int* par_out)
+{
+    EsRun& st = mem.st;
+    st.ngroups = (uint32_t)groups.size();
+    const unsigned ng = (unsigned)groups.size(), blocks = (unsigned)(nodes / sh.bn()), ablocks = (unsigned)(nodes / sh.an());
+    int64_t most = 1, chunks = 1;                              // most edges in a chunk of one group; most chunks
+    for (const EsGroup& g : groups) {
+        if (g.m == 0) continue;
+        if (g.c_size < g.m ? g.c_size > most : g.m > most) most = g.c_size < g.m ? g.c_size : g.m;
+        const int64_t c = (g.m + g.c_size - 1) / g.c_size;
+        if (c > chunks) chunks = c;
+    }
+    es_fill(stream, st.S, align256((size_t)ng * 32), 0ull);
+    es_fill(stream, st.Lb, (size_t)nodes, ~0ull);
+    es_fill(stream, st.est, (size_t)est_nodes * 16, 0ull);
+    es_fill(stream, st.mark, (size_t)nodes / 8, 0ull);
+    if (sh.binned) {
+        es_fill(stream, mem.table, align256((size_t)chunks * kBinTableStride * 4), 0ull);
+        // (workgroups of several tiles each: a workgroup's 1024 counts are added to the table once)
+        const int parts = grid_for((most + kBinTile - 1) / kBinTile, 4, 256);
+        hipLaunchKernelGGL(k_es_hist, dim3((unsigned)parts, ng, (unsigned)chunks), dim3(kBlock), 0, stream, src, dst, st, sh.cb, mem.table);
+        hipLaunchKernelGGL(k_es_hist_scan, dim3((unsigned)chunks), dim3(kBins), 0, stream, mem.table, mem.cursors);
+    } else {
+        es_fill(stream, mem.hc, (size_t)nodes * 8, 0ull);
+    }
+    hipLaunchKernelGGL(k_es_mark, dim3((unsigned)grid_for(most, kCountBlock, 8192), ng), dim3(kCountBlock), 0, stream, src, dst, st);
+    hipLaunchKernelGGL(k_es_seed, dim3(blocks), dim3(kBlock), 0, stream, st, seed);
+    hipLaunchKernelGGL(k_es_seed_sizes, dim3((ng + 255) / 256), dim3(256), 0, stream, st);
+    const int rc = check();
+    if (rc != GREM_OK) return rc;
+    const size_t slab = sh.awpw > kApplyByNode ? (size_t)kBlock * sh.awpw : 0;
+    const size_t bins_lds = (size_t)sh.bn() * 4 + (size_t)sh.bn() / 8;
+    if ((slab && hipFuncSetAttribute((const void*)k_es_apply, hipFuncAttributeMaxDynamicSharedMemorySize, (int)slab) != hipSuccess) ||
+        (sh.binned &&
+         (hipFuncSetAttribute((const void*)k_es_bin, hipFuncAttributeMaxDynamicSharedMemorySize, kBinTile * 8) != hipSuccess ||
+          hipFuncSetAttribute((const void*)k_es_score_bins, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bins_lds) != hipSuccess)))
+        return GREM_ERR_HIP;
+    bool profile;
+    { std::lock_guard<std::mutex> lock(es_prof.mu); profile = es_prof.on; }
+    const int fixed = mode == GREM_EDGE_FIXED ? 1 : 0;
+    int par = 0;
+    for (int64_t i = 0; i < chunks; ++i) {
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        if (profile) {
+            // timing only: no system-scope fence when the events complete
+            if (hipEventCreateWithFlags(&e0, hipEventDisableSystemFence) != hipSuccess ||
+                hipEventCreateWithFlags(&e1, hipEventDisableSystemFence) != hipSuccess)
+                return GREM_ERR_HIP;
+            (void)hipEventRecord(e0, stream);
+        }
+        if (sh.binned)
+            hipLaunchKernelGGL(k_es_bin, dim3((unsigned)((most + kBinTile - 1) / kBinTile), ng), dim3(kBlock), kBinTile * 8, stream, src, dst,
+                               st, i, sh.cb, mem.cursors, mem.pairs);
+        else
+            hipLaunchKernelGGL(k_es_count, dim3((unsigned)grid_for((most + kCountUnroll - 1) / kCountUnroll, kCountBlock, 1 << 20), ng),
+                               dim3(kCountBlock), 0, stream, src, dst, st, i, mem.hc);
+        if (profile) {
+            (void)hipEventRecord(e1, stream);
+            std::lock_guard<std::mutex> lock(es_prof.mu);
+            es_prof.count_events.emplace_back(e0, e1);
+            for (const EsGroup& g : groups)
+                if (i * g.c_size < g.m) es_prof.edges += g.m - i * g.c_size < g.c_size ? g.m - i * g.c_size : g.c_size;
+        }
+        const int first = i == 0 ? 1 : 0;
+        if (sh.binned)
+            hipLaunchKernelGGL(k_es_score_bins, dim3((blocks + 7) / 8 * 8), dim3(kBlock), bins_lds, stream, st, par, first, fixed, i, sh.cb,
+                               blocks, (const uint32_t*)mem.table, (const uint32_t*)mem.pairs);
+        else
+            hipLaunchKernelGGL(k_es_score, dim3(blocks), dim3(kBlock), 0, stream, st, par, first, fixed, mem.hc);
+        if (first) continue;
+        hipLaunchKernelGGL(k_es_apply, dim3(ablocks), dim3(kBlock), slab, stream, st, par);
+        hipLaunchKernelGGL(k_es_spill, dim3(ablocks), dim3(kBlock), 0, stream, st, par);
+        par ^= 1;
+    }
+    *par_out = par;
+    return hipGetLastError() == hipSuccess ? GREM_OK : GREM_ERR_HIP;
+}
+
 }  // namespace
 
 extern "C" {
@@ -650,99 +1154,40 @@ int grem_edge_stream_bipartition(const int32_t* src, const int32_t* dst, int64_t
         P < 1 || 2 * P < n || (mode != GREM_EDGE_REFINE && mode != GREM_EDGE_FIXED))
         return GREM_ERR_ARG;
     hipStream_t stream = (hipStream_t)stream_;
-    const int64_t words = (n + 63) / 64;
-    const int64_t seed_blocks = (words + kWordsPerBlock - 1) / kWordsPerBlock;         // a wave per word
-    const int64_t blocks = (words + kWordsPerBlock * kWaveWords - 1) / (kWordsPerBlock * kWaveWords);
-
-    // one stream-ordered allocation, carved up
-    size_t off = 0;
-    auto carve = [&](size_t bytes) { const size_t at = off; off += align256(bytes); return at; };
-    const size_t o_small = carve(256);                       // S[2], Sp[3], flags[2]
-    const size_t o_lb = carve((size_t)n);
-    const size_t o_hc = carve((size_t)n * 8);
-    const size_t o_est = nbr_counts_out ? 0 : carve((size_t)n * 16);
-    const size_t o_mark = carve((size_t)words * 8), o_mv0 = carve((size_t)words * 8);
-    const size_t o_mv1 = carve((size_t)words * 8), o_ov = carve((size_t)words * 8);
-    size_t o_b[8];
-    for (int i = 0; i < 8; ++i) o_b[i] = carve((size_t)blocks * 4);
+    if (c_size > m) c_size = m;
+    const int64_t chunks = (m + c_size - 1) / c_size, ends = 2 * c_size;
+    const EsShape sh = es_shape(n, 1, ends, chunks);
+    const int64_t nodes = sh.nodes;
+    EsMemory mem;
+    mem.layout(nullptr, sh, 1, ends, chunks, nbr_counts_out);
     uint8_t* ws = nullptr;
-    if (hipMallocAsync((void**)&ws, off, stream) != hipSuccess) { (void)hipGetLastError(); return GREM_ERR_NOMEM; }
-    u64* S = (u64*)(ws + o_small);
-    long long* Sp = (long long*)(ws + o_small + 16);
-    uint32_t* flags = (uint32_t*)(ws + o_small + 64);
-    uint8_t* Lb = ws + o_lb;
-    u64* hc = (u64*)(ws + o_hc);
-    double2* est = nbr_counts_out ? (double2*)nbr_counts_out : (double2*)(ws + o_est);
-    u64 *mark = (u64*)(ws + o_mark), *mv0 = (u64*)(ws + o_mv0), *mv1 = (u64*)(ws + o_mv1), *ov = (u64*)(ws + o_ov);
-    uint32_t *bs0 = (uint32_t*)(ws + o_b[0]), *bs1 = (uint32_t*)(ws + o_b[1]), *bso = (uint32_t*)(ws + o_b[2]);
-    uint32_t *bo0 = (uint32_t*)(ws + o_b[3]), *bo1 = (uint32_t*)(ws + o_b[4]), *boo = (uint32_t*)(ws + o_b[5]);
-    int32_t *bd0 = (int32_t*)(ws + o_b[6]), *bd1 = (int32_t*)(ws + o_b[7]);
-
-    int rc = GREM_OK;
-    auto fail = [&](int code) { (void)hipGetLastError(); (void)hipFreeAsync(ws, stream); return code; };
-    auto fill = [&](void* p, size_t bytes, u64 value) {
-        const size_t count = bytes / 8;
-        hipLaunchKernelGGL(k_es_fill64, dim3(grid_for((int64_t)count, 256, 16384)), dim3(256), 0, stream, (u64*)p, count, value);
-    };
-    fill(ws + o_small, 256, 0ull);
-    fill(Lb, align256((size_t)n), ~0ull);
-    fill(hc, (size_t)n * 8, 0ull);
-    fill(est, (size_t)n * 16, 0ull);
-    fill(mark, (size_t)words * 8, 0ull);
-
-    const int egrid_all = grid_for(m, 256, 8192);
-    hipLaunchKernelGGL(k_es_check, dim3(egrid_all), dim3(256), 0, stream, src, dst, m, (uint32_t)n, flags);
+    if (hipMallocAsync((void**)&ws, mem.bytes, stream) != hipSuccess) { (void)hipGetLastError(); return GREM_ERR_NOMEM; }
+    mem.layout(ws, sh, 1, ends, chunks, nbr_counts_out);
+    std::vector<EsGroup> groups(1);
+    groups[0] = EsGroup{0, m, c_size, (long long)P, 0, 0u, (uint32_t)n, 0u, (uint32_t)(nodes / sh.bn()), 0u, 0u};
+    es_fill(stream, mem.st.flags, 8, 0ull);
+    hipLaunchKernelGGL(k_es_one_group, dim3(1), dim3(64), 0, stream, mem.groups, groups[0]);
+    hipLaunchKernelGGL(k_es_blk_groups, dim3(1), dim3(256), 0, stream, (const EsGroup*)mem.groups, mem.blk_group);
+    // (a binned run checks the endpoints where it counts the bins)
+    if (!sh.binned)
+        hipLaunchKernelGGL(k_es_check, dim3(grid_for(m, 256, 8192)), dim3(256), 0, stream, src, dst, m, (uint32_t)n, mem.st.flags);
+    int par = 0;
     // the range check must be known before any kernel indexes with the endpoints
-    struct { u64 S[2]; long long Sp[3]; long long pad[3]; uint32_t flags[2]; } host;
-    static_assert(sizeof(host) >= 72, "layout");
-    if (hipMemcpyAsync(&host, ws + o_small, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess ||
-        hipStreamSynchronize(stream) != hipSuccess)
-        return fail(GREM_ERR_HIP);
-    if (host.flags[0]) return fail(GREM_ERR_ARG);
-
-    if (hipFuncSetAttribute((const void*)k_es_apply, hipFuncAttributeMaxDynamicSharedMemorySize, kBlock * 64) != hipSuccess)
-        return fail(GREM_ERR_HIP);
-    const int64_t nchunks = (m + c_size - 1) / c_size;
-    bool profile;
-    { std::lock_guard<std::mutex> lock(es_prof.mu); profile = es_prof.on; }
-    for (int64_t i = 0; i < nchunks; ++i) {
-        const int64_t lo = i * c_size, hi = (lo + c_size < m) ? lo + c_size : m;
-        const int egrid = grid_for((hi - lo + kCountUnroll - 1) / kCountUnroll, kCountBlock, 1 << 20);
-        if (i == 0) {
-            hipLaunchKernelGGL(k_es_mark, dim3(grid_for(hi - lo, kCountBlock, 8192)), dim3(kCountBlock), 0, stream, src, dst, lo, hi, mark);
-            hipLaunchKernelGGL(k_es_seed, dim3((int)seed_blocks), dim3(kBlock), 0, stream, words, mark, seed_parts, Lb, S, flags);
-            if (hipMemcpyAsync(&host, ws + o_small, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess ||
-                hipStreamSynchronize(stream) != hipSuccess)
-                return fail(GREM_ERR_HIP);
-            if (host.flags[1] || (long long)host.S[0] > P || (long long)host.S[1] > P) return fail(GREM_ERR_SEED);
-        }
-        hipEvent_t e0 = nullptr, e1 = nullptr;
-        if (profile) {
-            // timing only: no system-scope fence when the events complete
-            if (hipEventCreateWithFlags(&e0, hipEventDisableSystemFence) != hipSuccess ||
-                hipEventCreateWithFlags(&e1, hipEventDisableSystemFence) != hipSuccess)
-                return fail(GREM_ERR_HIP);
-            (void)hipEventRecord(e0, stream);
-        }
-        hipLaunchKernelGGL(k_es_count, dim3(egrid), dim3(kCountBlock), 0, stream, src, dst, lo, hi, Lb, mark, hc);
-        if (profile) {
-            (void)hipEventRecord(e1, stream);
-            std::lock_guard<std::mutex> lock(es_prof.mu);
-            es_prof.count_events.emplace_back(e0, e1);
-            es_prof.edges += hi - lo;
-        }
-        hipLaunchKernelGGL(k_es_score, dim3((int)blocks), dim3(kBlock), 0, stream, n, words, i == 0 ? 1 : 0,
-                           mode == GREM_EDGE_FIXED ? 1 : 0, (long long)P, S, mark, hc, Lb, est, mv0, mv1, bs0, bs1);
-        if (i == 0) continue;
-        hipLaunchKernelGGL(k_es_scan_movers, dim3(1), dim3(kBlock), 0, stream, blocks, bs0, bs1, bo0, bo1);
-        hipLaunchKernelGGL(k_es_apply, dim3((int)blocks), dim3(kBlock), (size_t)kBlock * 64, stream, words, (long long)P, S, mv0,
-                           mv1, bo0, bo1, Lb, (int64_t)align256((size_t)n), ov, bso, bd0, bd1);
-        hipLaunchKernelGGL(k_es_scan_spill, dim3(1), dim3(kBlock), 0, stream, blocks, bso, boo, bd0, bd1, S, Sp);
-        hipLaunchKernelGGL(k_es_spill, dim3((int)blocks), dim3(kBlock), 0, stream, words, ov, boo, Sp, Lb);
+    int rc = es_run(stream, mem, sh, groups, nodes, n, src, dst, seed_parts, mode, [&]() -> int {
+        uint32_t flags[2] = {0, 0};
+        if (hipMemcpyAsync(flags, mem.st.flags, sizeof(flags), hipMemcpyDeviceToHost, stream) != hipSuccess ||
+            hipStreamSynchronize(stream) != hipSuccess)
+            return GREM_ERR_HIP;
+        return flags[0] ? GREM_ERR_ARG : flags[1] ? GREM_ERR_SEED : GREM_OK;
+    }, &par);
+    if (rc == GREM_OK) {
+        hipLaunchKernelGGL(k_es_expand, dim3(grid_for(n, 256, 16384)), dim3(256), 0, stream, n, (const uint8_t*)mem.st.Lb, parts_out,
+                           (const u64*)(mem.st.S + 2 * par), sizes_out);
+        if (hipGetLastError() != hipSuccess) rc = GREM_ERR_HIP;
+    } else {
+        (void)hipGetLastError();
     }
-    hipLaunchKernelGGL(k_es_expand, dim3(grid_for(n, 256, 16384)), dim3(256), 0, stream, n, Lb, parts_out, S, sizes_out);
-    if (hipGetLastError() != hipSuccess) rc = GREM_ERR_HIP;
-    if (hipFreeAsync(ws, stream) != hipSuccess) rc = GREM_ERR_HIP;
+    if (hipFreeAsync(ws, stream) != hipSuccess && rc == GREM_OK) rc = GREM_ERR_HIP;
     return rc;
 }
 
@@ -754,113 +1199,122 @@ int grem_recursive_bisection(const int32_t* src, const int32_t* dst, int64_t m, 
         chunks < 1 || !(balance_slack >= 1.0) || (mode != GREM_EDGE_REFINE && mode != GREM_EDGE_FIXED))
         return GREM_ERR_ARG;
     hipStream_t stream = (hipStream_t)stream_;
-    const int64_t node_blocks = (n + kBlock - 1) / kBlock;
-    const int64_t sel_blocks = (m + kSelTile - 1) / kSelTile;
+    // The groups of a level run side by side, as many as the state has room for (a level of very many, tiny,
+    // groups takes several batches).
+    const int64_t c_max = chunks < m ? chunks : m;             // chunks a group can have
+    constexpr int64_t kMaxBatch = 1024;
+    const int64_t most_groups = (int64_t)1 << (levels - 1);
+    const int64_t ends = 2 * ((m + c_max - 1) / c_max + kMaxBatch);         // of one step: each group's chunk is rounded up
+    const EsShape sh = es_shape(n, most_groups < kMaxBatch ? most_groups : kMaxBatch, ends, c_max);
+    EsMemory mem;
+    mem.layout(nullptr, sh, kMaxBatch, ends, c_max, nullptr);
+    const int64_t sel_blocks = (m + kSelTile - 1) / kSelTile + kMaxBatch;
     size_t off = 0;
     auto carve = [&](size_t bytes) { const size_t at = off; off += align256(bytes); return at; };
-    const size_t o_small = carve(256);                 // totals[3], flags
+    const size_t o_totals = carve((size_t)most_groups * 24);     // per group: edges kept per half, nodes in half 0
     size_t o_gof[2], o_seed[2];                        // two generations of the groups' node lists
     for (int i = 0; i < 2; ++i) { o_gof[i] = carve((size_t)n * 4); o_seed[i] = carve((size_t)n * 4); }
     const size_t o_packed = carve((size_t)n * 4);
-    const size_t o_parts = carve((size_t)n * 4 + 8), o_sizes = carve(16);
-    const size_t o_flag = carve((size_t)((n + 63) / 64) * 8);
-    const size_t o_bsum = carve((size_t)node_blocks * 4), o_boff = carve((size_t)node_blocks * 4);
-    size_t o_sel[4];
-    for (int i = 0; i < 4; ++i) o_sel[i] = carve((size_t)sel_blocks * 4);
+    const size_t o_bc0 = carve((size_t)sel_blocks * 4), o_bc1 = carve((size_t)sel_blocks * 4);
     const size_t o_tmps = carve((size_t)m * 4), o_tmpd = carve((size_t)m * 4), o_key = carve((size_t)m);
     size_t o_lev[4];                                   // two generations of the grouped edge list
     for (int i = 0; i < 4; ++i) o_lev[i] = carve((size_t)m * 4);
+    const size_t o_run = carve(mem.bytes);
     uint8_t* ws = nullptr;
     if (hipMallocAsync((void**)&ws, off, stream) != hipSuccess) { (void)hipGetLastError(); return GREM_ERR_NOMEM; }
+    mem.layout(ws + o_run, sh, kMaxBatch, ends, c_max, nullptr);
     auto fail = [&](int code) { (void)hipGetLastError(); (void)hipStreamSynchronize(stream); (void)hipFreeAsync(ws, stream); return code; };
-    long long* totals = (long long*)(ws + o_small);    // [0..1] edges kept per half, [2] nodes in half 0
-    uint32_t* flags = (uint32_t*)(ws + o_small + 64);
+    long long* totals = (long long*)(ws + o_totals);
+    long long* nodes0 = totals + 2 * most_groups;
     uint32_t* packed = (uint32_t*)(ws + o_packed);
-    int32_t* sub_parts = (int32_t*)(ws + o_parts);
-    int64_t* sub_sizes = (int64_t*)(ws + o_sizes);
-    u64* flag = (u64*)(ws + o_flag);
-    uint32_t *bsum = (uint32_t*)(ws + o_bsum), *boff = (uint32_t*)(ws + o_boff);
-    uint32_t *bc0 = (uint32_t*)(ws + o_sel[0]), *bc1 = (uint32_t*)(ws + o_sel[1]);
-    uint32_t *bo0 = (uint32_t*)(ws + o_sel[2]), *bo1 = (uint32_t*)(ws + o_sel[3]);
+    uint32_t *bc0 = (uint32_t*)(ws + o_bc0), *bc1 = (uint32_t*)(ws + o_bc1);
     int32_t *tmp_s = (int32_t*)(ws + o_tmps), *tmp_d = (int32_t*)(ws + o_tmpd);
     uint8_t* key = ws + o_key;
 
-    auto fill = [&](void* p, size_t bytes, u64 value) {
-        const size_t count = bytes / 8;
-        hipLaunchKernelGGL(k_es_fill64, dim3(grid_for((int64_t)count, 256, 16384)), dim3(256), 0, stream, (u64*)p, count, value);
-    };
-    struct { long long totals[3]; long long pad[5]; uint32_t flags[2]; } host;
-    auto read_small = [&]() {
-        return hipMemcpyAsync(&host, ws + o_small, sizeof(host), hipMemcpyDeviceToHost, stream) == hipSuccess &&
+    es_fill(stream, mem.st.flags, 8, 0ull);
+    hipLaunchKernelGGL(k_es_check, dim3(grid_for(m, 256, 8192)), dim3(256), 0, stream, src, dst, m, (uint32_t)n, mem.st.flags);
+    uint32_t flags[2] = {0, 0};
+    auto read_flags = [&]() {
+        return hipMemcpyAsync(flags, mem.st.flags, sizeof(flags), hipMemcpyDeviceToHost, stream) == hipSuccess &&
                hipStreamSynchronize(stream) == hipSuccess;
     };
-    fill(ws + o_small, 256, 0ull);
-    hipLaunchKernelGGL(k_es_check, dim3(grid_for(m, 256, 8192)), dim3(256), 0, stream, src, dst, m, (uint32_t)n, flags);
-    if (!read_small()) return fail(GREM_ERR_HIP);
-    if (host.flags[0]) return fail(GREM_ERR_ARG);
+    if (!read_flags()) return fail(GREM_ERR_HIP);
+    if (flags[0]) return fail(GREM_ERR_ARG);
 
     // level 0: one group, everyone, numbered by id; its edges and seed bits are the inputs themselves
+    struct Part { int64_t e_lo, m, v_lo, nv; };
+    std::vector<Part> parts{{0, m, 0, n}}, next;
     const int32_t *cur_s = src, *cur_d = dst;
     const int32_t *cur_gof = nullptr, *cur_seed = seed_bits;
-    std::vector<int64_t> eoff{0, m}, noff{0, n};
+    std::vector<long long> host;
     for (int32_t level = 0; level < levels; ++level) {
         const bool last = level + 1 == levels;
         int32_t* out_s = (int32_t*)(ws + o_lev[(level & 1) * 2]);
         int32_t* out_d = (int32_t*)(ws + o_lev[(level & 1) * 2 + 1]);
         int32_t* gof_next = (int32_t*)(ws + o_gof[level & 1]);
         int32_t* seed_next = (int32_t*)(ws + o_seed[level & 1]);
-        const int32_t groups = 1 << level;
-        std::vector<int64_t> eoff_next((size_t)2 * groups + 1, 0), noff_next((size_t)2 * groups + 1, 0);
+        const size_t count = parts.size();
         const int32_t* next_bits = last ? seed_bits : seed_bits + (size_t)(level + 1) * (size_t)n;
-        for (int32_t g = 0; g < groups; ++g) {
-            const int64_t e_lo = eoff[g], mg = eoff[g + 1] - eoff[g];
-            const int64_t v_lo = noff[g], nv = noff[g + 1] - noff[g];
-            eoff_next[2 * g + 1] = eoff_next[2 * g + 2] = eoff_next[2 * g];
-            noff_next[2 * g + 1] = noff_next[2 * g + 2] = noff_next[2 * g];
-            if (nv == 0) continue;
-            if (mg > 0) {
-                const int64_t c_size = (mg + chunks - 1) / chunks;
-                const int64_t P = grem_capacity(nv, 2, balance_slack);
-                const int rc = grem_edge_stream_bipartition(cur_s + e_lo, cur_d + e_lo, mg, nv, c_size, P, cur_seed + v_lo, mode,
-                                                            sub_parts, sub_sizes, nullptr, stream_);
-                if (rc != GREM_OK) return fail(rc);
-            } else {
-                fill(sub_parts, ((size_t)nv * 4 + 7) & ~(size_t)7, ~0ull);
-                fill(sub_sizes, 16, 0ull);
+        es_fill(stream, ws + o_totals, (size_t)most_groups * 24, 0ull);
+        std::vector<std::vector<EsGroup>> batches;       // (copied to the device: kept until the level's read-back)
+        for (size_t g0 = 0; g0 < count;) {
+            // the next batch: groups that have nodes, as many as fit
+            batches.emplace_back();
+            std::vector<EsGroup>& groups = batches.back();
+            int64_t nodes = 0, tiles = 0;
+            size_t g1 = g0;
+            for (; g1 < count && (int64_t)groups.size() < kMaxBatch; ++g1) {
+                const Part& p = parts[g1];
+                if (p.nv == 0) continue;
+                const int64_t padded = sh.padded(p.nv);
+                if (nodes + padded > sh.nodes) break;
+                groups.push_back(EsGroup{p.e_lo, p.m, p.m > 0 ? (p.m + chunks - 1) / chunks : 1,
+                                         (long long)grem_capacity(p.nv, 2, balance_slack), p.v_lo, (uint32_t)nodes, (uint32_t)p.nv,
+                                         (uint32_t)(nodes / sh.bn()), (uint32_t)(padded / sh.bn()), (uint32_t)tiles, (uint32_t)g1});
+                nodes += padded;
+                tiles += (p.m + kSelTile - 1) / kSelTile;
             }
-            const int64_t vb = (nv + kBlock - 1) / kBlock;
-            // unlabelled nodes are placed
-            hipLaunchKernelGGL(k_rb_flags, dim3((int)vb), dim3(kBlock), 0, stream, nv, sub_parts, 0, 1, flag, bsum);
-            hipLaunchKernelGGL(k_rb_scan, dim3(1), dim3(kBlock), 0, stream, vb, bsum, boff, totals + 2);
-            hipLaunchKernelGGL(k_rb_place, dim3((int)vb), dim3(kBlock), 0, stream, nv, flag, boff, sub_parts, sub_sizes);
-            // numbers inside the halves, the halves' node lists (or, at the last level, the labels)
-            hipLaunchKernelGGL(k_rb_flags, dim3((int)vb), dim3(kBlock), 0, stream, nv, sub_parts, 0, 0, flag, bsum);
-            hipLaunchKernelGGL(k_rb_scan, dim3(1), dim3(kBlock), 0, stream, vb, bsum, boff, totals + 2);
-            hipLaunchKernelGGL(k_rb_children, dim3((int)vb), dim3(kBlock), 0, stream, nv, flag, boff, sub_parts,
-                               cur_gof ? cur_gof + v_lo : (const int32_t*)nullptr, g, totals + 2, next_bits, packed,
-                               gof_next + v_lo, seed_next + v_lo, last ? labels_out : (int32_t*)nullptr);
-            if (last) continue;
-            // the group's edges that stay inside a half, in the halves' numbers, for the next level
-            if (mg > 0) {
-                const int64_t sb = (mg + kSelTile - 1) / kSelTile;
-                hipLaunchKernelGGL(k_rb_split_count, dim3((int)sb), dim3(kSelBlock), 0, stream, mg, cur_s + e_lo, cur_d + e_lo,
-                                   packed, key, tmp_s, tmp_d, bc0, bc1);
-                hipLaunchKernelGGL(k_rb_split_scan, dim3(1), dim3(kBlock), 0, stream, sb, bc0, bc1, bo0, bo1, totals);
-                hipLaunchKernelGGL(k_rb_split_scatter, dim3((int)sb), dim3(kSelBlock), 0, stream, mg, tmp_s, tmp_d,
-                                   key, bo0, bo1, out_s, out_d, eoff_next[2 * g], totals);
-            } else {
-                fill(totals, 16, 0ull);
+            g0 = g1;
+            if (groups.empty()) continue;
+            const unsigned ng = (unsigned)groups.size(), blocks = (unsigned)(nodes / sh.bn());
+            if (hipMemcpyAsync(mem.groups, groups.data(), groups.size() * sizeof(EsGroup), hipMemcpyHostToDevice, stream) != hipSuccess)
+                return fail(GREM_ERR_HIP);
+            hipLaunchKernelGGL(k_es_blk_groups, dim3(ng), dim3(256), 0, stream, (const EsGroup*)mem.groups, mem.blk_group);
+            int par = 0;
+            // a bad seed is looked for at the end of the level: until then it only leaves a node without a label
+            const int rc = es_run(stream, mem, sh, groups, nodes, nodes, cur_s, cur_d, cur_seed, mode, [] { return GREM_OK; }, &par);
+            if (rc != GREM_OK) return fail(rc);
+            hipLaunchKernelGGL(k_rb_count, dim3(blocks), dim3(kBlock), 0, stream, mem.st);
+            hipLaunchKernelGGL(k_rb_children, dim3(blocks), dim3(kBlock), 0, stream, mem.st, par, cur_gof, next_bits, packed, gof_next,
+                               seed_next, last ? labels_out : (int32_t*)nullptr, nodes0);
+            // the groups' edges that stay inside a half, in the halves' numbers, for the next level
+            int64_t most = 0;
+            for (const EsGroup& g : groups) if (g.m > most) most = g.m;
+            if (!last && most > 0) {
+                const dim3 grid((unsigned)((most + kSelTile - 1) / kSelTile), ng);
+                hipLaunchKernelGGL(k_rb_split_count, grid, dim3(kSelBlock), 0, stream, (const EsGroup*)mem.groups, cur_s, cur_d,
+                                   (const uint32_t*)packed, key, tmp_s, tmp_d, bc0, bc1);
+                hipLaunchKernelGGL(k_rb_split_scan, dim3(ng), dim3(kBlock), 0, stream, (const EsGroup*)mem.groups, bc0, bc1, totals);
+                hipLaunchKernelGGL(k_rb_split_scatter, grid, dim3(kSelBlock), 0, stream, (const EsGroup*)mem.groups, (const int32_t*)tmp_s,
+                                   (const int32_t*)tmp_d, (const uint8_t*)key, (const uint32_t*)bc0, (const uint32_t*)bc1, out_s, out_d,
+                                   (const long long*)totals);
             }
-            if (!read_small()) return fail(GREM_ERR_HIP);
-            eoff_next[2 * g + 1] = eoff_next[2 * g] + host.totals[0];
-            eoff_next[2 * g + 2] = eoff_next[2 * g + 1] + host.totals[1];
-            noff_next[2 * g + 1] = noff_next[2 * g] + host.totals[2];
-            noff_next[2 * g + 2] = noff_next[2 * g] + nv;
         }
+        // one read-back per level: the children's sizes, and whether every seed was sound
+        host.assign((size_t)most_groups * 3, 0);
+        if (hipMemcpyAsync(host.data(), ws + o_totals, (size_t)most_groups * 24, hipMemcpyDeviceToHost, stream) != hipSuccess || !read_flags())
+            return fail(GREM_ERR_HIP);
+        if (flags[1]) return fail(GREM_ERR_SEED);
+        next.clear();
+        for (size_t g = 0; g < count && !last; ++g) {
+            const Part& p = parts[g];
+            const int64_t t0 = host[2 * g], t1 = host[2 * g + 1], c0 = host[(size_t)2 * most_groups + g];
+            next.push_back({p.e_lo, t0, p.v_lo, c0});
+            next.push_back({p.e_lo + t0, t1, p.v_lo + c0, p.nv - c0});
+        }
+        parts.swap(next);
         cur_s = out_s; cur_d = out_d;
         cur_gof = gof_next; cur_seed = seed_next;
-        eoff.swap(eoff_next);
-        noff.swap(noff_next);
     }
     int rc = hipGetLastError() == hipSuccess ? GREM_OK : GREM_ERR_HIP;
     if (hipFreeAsync(ws, stream) != hipSuccess) rc = GREM_ERR_HIP;
