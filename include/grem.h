@@ -121,8 +121,9 @@ typedef struct grem_options {
                                  while (hub_degree - 1) * 2^refine_passes < 65536 (the default: up to 3
                                  refinement passes), else in 32 */
     int32_t long_row_degree;  /* plain route: a tile of rows is scored by one workgroup; rows of at least
-                                 this many entries are taken out of their tile and spread over a grid of
-                                 their own; 0 = default (16384) */
+                                 this many entries are taken out of their tile and spread over workgroups of
+                                 their own; 0 = automatic (8192 or 16384).  With more such rows than a 256th
+                                 of all rows (and 1024) the degree is doubled until they are fewer */
     int32_t plan_max_k;       /* grem_plan_create: the largest k the plan is to serve, 0 = 16, at most 32.
                                  Above 16 the plan is laid out with narrower column blocks (2^16 vertices)
                                  and more hub shares; it still serves every smaller k */

@@ -21,6 +21,7 @@
 #include <vector>
 
 #include "grem_kernels.hip.h"
+#include "grem_plain.hip.h"
 #include "grem_twophase.hip.h"
 
 namespace {
@@ -28,10 +29,17 @@ namespace {
 using namespace grem;
 
 constexpr int kLdsHistBytes = 32 * 1024;   // LDS spent on one tile's histograms
+constexpr int kTileHistBytes = 16 * 1024;  // merged launches: the same (32 KB: 117 ms where 16 KB take 106 and 8 KB 107)
+constexpr int kTileGrid = 2048;            // ... and workgroups per chunk (1024: 2.18 ms on a million vertices, 2048: 1.91,
+                                           // 4096: 2.02, 8192: 2.52)
 constexpr int kLdsMaxK = 1024;             // above this the histograms live in E's rows
 constexpr int kLongRowDegree = 16384;      // plain score kernels: rows this long get a grid of their own ...
 constexpr uint32_t kLongRowPart = 16384;   // ... that many entries per workgroup and turn
 constexpr unsigned kLongRowGrid = 512;
+constexpr int kLongDegree = 8192;          // merged launches: rows this long (4096 and 16384 were slower) are dealt out in parts ...
+constexpr uint32_t kLongPart = 16384;      // ... of that many entries, of up to kLongPartMax when rows are longer than
+constexpr uint32_t kLongPartMax = 65536;   // 64 parts: every part adds its k counts to the same row of estimates (rows of
+                                           // 2M entries, k = 256: 92 ms in parts of 4096, 71.5 of 16384, 67.4 of 32768)
 constexpr int kSweepMaxK = 32;             // two-phase route: 16-bit counters for 2048 rows: 64 KB of LDS up to k = 16
                                            // (4-bit labels), 128 KB up to k = 32 (8-bit labels)
 constexpr int kHubsPerShare16 = 1024;      // hubs one hub share may touch: their 32-bit counters share the
@@ -65,7 +73,7 @@ struct Opts {
     int hist_mode = GREM_HIST_AUTO;
     int col_bits = 0;                       // 0 = automatic
     int hub_degree = kDefaultHubDegree;
-    int long_row_degree = kLongRowDegree;
+    int long_row_degree = 0;                // 0 = automatic: see kLongRowDegree, kLongDegree
     int plan_max_k = 16;
 };
 
@@ -607,21 +615,21 @@ void state_common(Carver &c, CallState<LabelT> &st, int64_t n, int64_t cl, int32
     c.take(st.fillRank, (size_t)k);
     c.take(st.fillSorted, (size_t)k);
     c.take(st.fillC, (size_t)k + 1);
-    c.take(st.misc, 16);
+    c.take(st.misc, 32);
 }
 
 // prepass: compact labels and sizes from the seed, its validity; with rowptr also the largest degree
 template <typename RowT, typename LabelT>
 void launch_prepass(Launcher &L, const RowT *rowptr_or_null, const int32_t *seed, int64_t n, int32_t k, long long P,
-                    CallState<LabelT> &st) {
+                    CallState<LabelT> &st, uint32_t long_degree = 0xFFFFFFFFu) {
     hipStream_t stream = L.stream;
     L.memset(st.S, 0, (size_t)k * 8);
-    L.memset(st.misc, 0, 16 * 8);
+    L.memset(st.misc, 0, 32 * 8);
     int64_t blocks = (n + 255) / 256;
     if (blocks > 256 * 32) blocks = 256 * 32;
     L.run(GREM_KERNEL_PREPASS, [&] {
         hipLaunchKernelGGL((k_prepass<RowT, LabelT>), dim3((unsigned)blocks), dim3(256), 0, stream, rowptr_or_null, seed,
-                           n, (int)k, st.Lc, (unsigned long long *)st.S, st.misc);
+                           n, (int)k, st.Lc, (unsigned long long *)st.S, st.misc, long_degree);
     });
     if (seed)
         L.run(GREM_KERNEL_PREPASS, [&] {
@@ -944,14 +952,166 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
 }
 
 // ---- plain route ------------------------------------------------------------------------------------
+// The plain route takes the merged launches of grem_plain.hip.h for k <= 1024 and chunks of at most kPlainTiles
+// tiles (every workgroup of the admission adds up the tiles' counts), the launches of grem_kernels.hip.h beyond them
+// and where the histograms are forced into E's rows.
+bool plain_merged(int32_t k, int64_t cl, int hist_mode) {
+    return hist_mode != GREM_HIST_GLOBAL && k <= kPlainMaxK && (cl + kAdmitTile - 1) / kAdmitTile <= kPlainTiles;
+}
+
+int plain_long_degree(const Opts &o) { return o.long_row_degree ? o.long_row_degree : kLongDegree; }
+
+// most long rows the merged launches keep a list of; with more the degree from which a row is long is doubled
+size_t plain_long_rows(int64_t n) {
+    const size_t most = (size_t)n / 256 + 1024;
+    return most < (size_t)n ? most : (size_t)n;
+}
+
 struct PlainExtra {
     uint32_t *E = nullptr, *long_cnt = nullptr, *long_list = nullptr;
+    // merged launches
+    uint32_t *cnt = nullptr, *coarse = nullptr;          // two tables of mover counts each
+    unsigned long long *rej = nullptr;
+    uint32_t *nrows = nullptr, *nparts = nullptr, *off = nullptr, *cur = nullptr, *row = nullptr, *pref = nullptr, *ticket = nullptr;
 };
 
-void state_plain(Carver &c, PlainExtra &x, int64_t n, int64_t cl, int32_t k, int64_t nchunks, bool external_E) {
+void state_plain(Carver &c, PlainExtra &x, int64_t n, int64_t cl, int32_t k, int64_t nchunks, bool external_E, bool merged) {
     c.take(x.E, external_E ? 0 : (size_t)n * (size_t)k);
-    c.take(x.long_cnt, (size_t)nchunks);
-    c.take(x.long_list, (size_t)cl);
+    if (!merged) {
+        c.take(x.long_cnt, (size_t)nchunks);
+        c.take(x.long_list, (size_t)cl);
+        return;
+    }
+    const size_t tiles = (size_t)((cl + kAdmitTile - 1) / kAdmitTile), rows = plain_long_rows(n);
+    c.take(x.cnt, 2 * tiles * (size_t)k);
+    c.take(x.coarse, tiles * (size_t)k > (size_t)kPlainCells ? 2 * ((tiles + kPlainCoarse - 1) / kPlainCoarse) * (size_t)k : 0);
+    c.take(x.rej, tiles * (kAdmitTile / 64));
+    c.take(x.nrows, (size_t)nchunks);
+    c.take(x.nparts, (size_t)nchunks);
+    c.take(x.off, (size_t)nchunks);
+    c.take(x.cur, (size_t)nchunks);
+    c.take(x.row, rows);
+    c.take(x.pref, rows);
+    c.take(x.ticket, rows);
+}
+
+// rows per workgroup of the tile kernels by the LDS that their histograms may take
+int plain_tile_rows(int32_t k, int lds_bytes) {
+    int tv = 256;
+    while (tv > 1 && (size_t)tv * k * 4 > (size_t)lds_bytes) tv >>= 1;
+    return tv;
+}
+
+// Alg. 1's loop in the merged launches.  degrees[i]: rows of at least long_row_degree * 2^i entries and fewer than
+// twice as many (the last: and more).
+template <typename RowT, typename LabelT>
+int run_plain_merged(const RowT *rowptr, const int32_t *colidx, int64_t n, int32_t k, double slack, int64_t cl, int32_t R,
+                     const int32_t *seed, int32_t *labels_out, int64_t *sizes_out, uint32_t *estimates_out, const Opts &o,
+                     unsigned long long maxdeg, const unsigned long long *degrees, Arena &mem, Launcher &L, CallState<LabelT> &st) {
+    hipStream_t stream = L.stream;
+    const long long P = grem_capacity(n, k, slack);
+    const bool external_E = estimates_out != nullptr;
+    const int64_t nchunks = (n + cl - 1) / cl;
+    PlainExtra x;
+    if (!carve(mem, [&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E, true); })) return GREM_ERR_NOMEM;
+    uint32_t *E = external_E ? estimates_out : x.E;
+    if (maxdeg * (unsigned long long)plain_tile_rows(k, kLdsHistBytes) >= (1ull << 31)) return GREM_ERR_RANGE;
+    // rows per workgroup: the histograms in 16 KB of LDS, and small enough for 2048 workgroups
+    int tv = plain_tile_rows(k, kTileHistBytes);
+    while (tv > 8 && (cl + tv - 1) / tv < kTileGrid) tv >>= 1;
+    const size_t tile_lds = ((size_t)tv * k + tv + 1 + 2 * (size_t)k) * 4;
+    const int tiles_full = (int)((cl + kAdmitTile - 1) / kAdmitTile);
+    const size_t cells = (size_t)tiles_full * (size_t)k;
+    const size_t coarse_cells = x.coarse ? (size_t)((tiles_full + kPlainCoarse - 1) / kPlainCoarse) * (size_t)k : 0;
+    const size_t admit_lds = admit_tiles_lds(k), spill_lds = spill_tiles_lds(k);
+    if (!set_lds((const void *)k_admit_tiles<LabelT>, admit_lds) || !set_lds((const void *)k_spill_tiles<LabelT>, spill_lds))
+        return GREM_ERR_HIP;
+
+    // the long rows, chunk by chunk
+    std::vector<uint32_t> nrows, nparts, first;
+    unsigned long long degree = (unsigned long long)plain_long_degree(o), rows = 0;
+    for (int i = 0; i < kLongClasses; ++i) rows += degrees[i];
+    for (int i = 0; i < kLongClasses - 1 && rows > plain_long_rows(n); ++i) { rows -= degrees[i]; degree *= 2; }
+    const bool split_long = rows != 0 && rows <= plain_long_rows(n) && degree < (1ull << 32);
+    uint32_t part = kLongPart;
+    while (part < kLongPartMax && maxdeg / part > 64) part *= 2;
+    if (split_long) {
+        nrows.resize((size_t)nchunks);
+        nparts.resize((size_t)nchunks);
+        first.resize((size_t)nchunks);
+        const unsigned blocks = (unsigned)((n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192);
+        L.memset(x.nrows, 0, (size_t)nchunks * 4);
+        L.memset(x.nparts, 0, (size_t)nchunks * 4);
+        L.memset(x.cur, 0, (size_t)nchunks * 4);
+        L.run(GREM_KERNEL_HUBS, [&] {
+            hipLaunchKernelGGL((k_long_count<RowT>), dim3(blocks), dim3(256), 0, stream, rowptr, n, cl, (uint32_t)degree,
+                               part, x.nrows, x.nparts);
+        });
+        L.run(GREM_KERNEL_HUBS, [&] {
+            hipLaunchKernelGGL(k_long_offsets, dim3(1), dim3(kScanThreads), 0, stream, (const uint32_t *)x.nrows, nchunks, x.off);
+        });
+        L.run(GREM_KERNEL_HUBS, [&] {
+            hipLaunchKernelGGL((k_long_list<RowT>), dim3(blocks), dim3(256), 0, stream, rowptr, n, cl, (uint32_t)degree,
+                               (const uint32_t *)x.off, x.cur, x.row, x.ticket);
+        });
+        L.run(GREM_KERNEL_HUBS, [&] {
+            hipLaunchKernelGGL((k_long_parts<RowT>), dim3((unsigned)(nchunks < 1024 ? nchunks : 1024)), dim3(256), 0, stream, rowptr,
+                               nchunks, part, (const uint32_t *)x.nrows, (const uint32_t *)x.off, (const uint32_t *)x.row, x.pref);
+        });
+        L.run(GREM_KERNEL_HUBS, [&] {
+            hipLaunchKernelGGL(k_long_clear, dim3((unsigned)(rows < 2048 ? rows : 2048)), dim3(256), 0, stream, (const uint32_t *)x.row,
+                               (uint32_t)rows, E, (int)k);
+        });
+        if (L.err) return L.err;
+        if (hipMemcpyAsync(nrows.data(), x.nrows, (size_t)nchunks * 4, hipMemcpyDeviceToHost, stream) != hipSuccess)
+            return GREM_ERR_HIP;
+        if (!L.read_back(nparts.data(), x.nparts, (size_t)nchunks * 4)) return L.err;
+        uint32_t at = 0;
+        for (int64_t c = 0; c < nchunks; ++c) { first[(size_t)c] = at; at += nrows[(size_t)c]; }
+    }
+    L.memset(x.cnt, 0, 2 * cells * 4);
+    L.memset(x.coarse, 0, 2 * coarse_cells * 4);
+
+    L.mark();
+    long long *now = st.S, *other = st.S2;
+    uint32_t *cnt = x.cnt, *cnt_other = x.cnt + cells, *coarse = x.coarse, *coarse_other = x.coarse ? x.coarse + coarse_cells : nullptr;
+    for (int pass = 0; pass <= R && !L.err; ++pass) {
+        const int standing = pass > 0 ? kAllLabelled : seed ? kSomeLabelled : kNoneLabelled;
+        const int store_e = (pass < R || external_E) ? 1 : 0;
+        for (int64_t c = 0; c < nchunks && !L.err; ++c) {
+            const int64_t lo = c * cl;
+            const int64_t hi = (lo + cl < n) ? lo + cl : n;
+            const int64_t len = hi - lo;
+            const unsigned tiles = (unsigned)((len + kAdmitTile - 1) / kAdmitTile);
+            LongParts lr{nullptr, nullptr, nullptr, 0u, 0u, (uint32_t)degree, part};
+            if (split_long && nrows[(size_t)c] != 0)
+                lr = LongParts{x.row + first[(size_t)c], x.pref + first[(size_t)c], x.ticket + first[(size_t)c], nrows[(size_t)c],
+                               nparts[(size_t)c], (uint32_t)degree, part};
+            L.run(GREM_KERNEL_SCORE, [&] {
+                hipLaunchKernelGGL((k_score_tile<RowT, LabelT>), dim3(lr.parts + (unsigned)((len + tv - 1) / tv)), dim3(kScoreThreads),
+                                   tile_lds, stream, rowptr, colidx, (const LabelT *)st.Lc, (const long long *)now, other, E, st.prop, cnt,
+                                   coarse, lo, hi, (int)k, tv, pass, P, standing == kNoneLabelled ? lo : n, standing, store_e, lr);
+            });
+            L.run(GREM_KERNEL_APPLY, [&] {
+                hipLaunchKernelGGL((k_admit_tiles<LabelT>), dim3(tiles), dim3(kAdmitTile), admit_lds, stream, st.Lc,
+                                   (const LabelT *)st.prop, lo, hi, (int)k, P, (const uint32_t *)cnt, (const uint32_t *)coarse, cnt_other,
+                                   coarse_other, tiles_full, (const long long *)now, (unsigned long long *)other, x.rej, st.ocnt, standing);
+            });
+            if (pass == 0)
+                L.run(GREM_KERNEL_SPILL_FILL, [&] {
+                    hipLaunchKernelGGL((k_spill_tiles<LabelT>), dim3(tiles), dim3(kAdmitTile), spill_lds, stream, st.Lc, lo, (int)k,
+                                       (const unsigned long long *)x.rej, (const uint32_t *)st.ocnt, (const long long *)other, now);
+                });
+            else std::swap(now, other);
+            std::swap(cnt, cnt_other);
+            std::swap(coarse, coarse_other);
+        }
+        L.mark();
+    }
+    st.S = now;
+    launch_outputs<LabelT>(L, st, n, k, labels_out, sizes_out);
+    L.mark();
+    return L.err;
 }
 
 // Alg. 1's loop straight on the CSR.  `st` is prepared (prepass run, seed and degrees validated).
@@ -965,14 +1125,13 @@ int run_plain(const RowT *rowptr, const int32_t *colidx, int64_t n, int32_t k, d
     const int64_t nchunks = (n + cl - 1) / cl;
     const bool use_lds = o.hist_mode != GREM_HIST_GLOBAL && k <= kLdsMaxK;
     PlainExtra x;
-    if (!carve(mem, [&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E); })) return GREM_ERR_NOMEM;
+    if (!carve(mem, [&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E, false); })) return GREM_ERR_NOMEM;
     uint32_t *E = external_E ? estimates_out : x.E;
 
     // tile shape of the score kernels
     int tv = kGlobalTile;
     if (use_lds) {
-        tv = 256;
-        while (tv > 1 && (size_t)tv * k * 4 > (size_t)kLdsHistBytes) tv >>= 1;
+        tv = plain_tile_rows(k, kLdsHistBytes);
     }
     if (maxdeg * (unsigned long long)tv >= (1ull << 31)) return GREM_ERR_RANGE;
     const size_t score_lds = use_lds ? ((size_t)tv * k + tv + 1 + k) * 4 : ((size_t)tv + 1 + k) * 4;
@@ -981,7 +1140,8 @@ int run_plain(const RowT *rowptr, const int32_t *colidx, int64_t n, int32_t k, d
     if (!set_lds((const void *)k_apply<LabelT, false>, apply_lds)) return GREM_ERR_HIP;
 
     // rows this long are taken out of their tile and spread over a grid of their own
-    const bool split_long = maxdeg >= (unsigned long long)o.long_row_degree;
+    const int long_degree = o.long_row_degree ? o.long_row_degree : kLongRowDegree;
+    const bool split_long = maxdeg >= (unsigned long long)long_degree;
     const size_t long_lds = (size_t)k * 4;
     if (split_long && !set_lds((const void *)k_long_rows<RowT, LabelT>, long_lds)) return GREM_ERR_HIP;
 
@@ -994,7 +1154,7 @@ int run_plain(const RowT *rowptr, const int32_t *colidx, int64_t n, int32_t k, d
             const int64_t len = hi - lo;
             const int64_t gather_limit = (pass == 0 && !seed) ? lo : n;
             const unsigned admit_blocks = (unsigned)((len + kAdmitTile - 1) / kAdmitTile);
-            const LongRows lr{split_long ? (uint32_t)o.long_row_degree : 0xFFFFFFFFu, kLongRowPart, x.long_cnt + c,
+            const LongRows lr{split_long ? (uint32_t)long_degree : 0xFFFFFFFFu, kLongRowPart, x.long_cnt + c,
                               x.long_list};
             const unsigned score_blocks = (unsigned)((len + tv - 1) / tv);
             L.run(GREM_KERNEL_SCORE, [&] {
@@ -1051,7 +1211,11 @@ size_t plain_bytes(int64_t n, int32_t k, int64_t cl, bool external_E) {
         CallState<uint16_t> st;
         a = carve_size([&](Carver &c) { state_common(c, st, n, cl, k); });
     }
-    return a + carve_size([&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E); });
+    // (whichever of the two forms takes more)
+    const size_t one = carve_size([&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E, false); });
+    const size_t two = plain_merged(k, cl, GREM_HIST_AUTO)
+                           ? carve_size([&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E, true); }) : 0;
+    return a + (one > two ? one : two);
 }
 
 // One partition call: route choice, memory, validation, then one of the two loops.
@@ -1124,15 +1288,20 @@ int run_partition(const RowT *rowptr, const int32_t *colidx, int64_t n, int32_t 
         }
     }
     if (!done) {
-        if (!try_sweep) {
-            launch_prepass<RowT, LabelT>(L, rowptr, seed, n, k, P, st);
-            unsigned long long h[16] = {0};
+        const bool merged = plain_merged(k, cl, o.hist_mode);
+        unsigned long long degrees[kLongClasses] = {0};
+        if (!try_sweep || merged) {        // (the merged launches want the rows' degrees by class)
+            launch_prepass<RowT, LabelT>(L, rowptr, seed, n, k, P, st, (uint32_t)plain_long_degree(o));
+            unsigned long long h[32] = {0};
             if (!L.read_back(h, st.misc, sizeof(h))) { mem.release_all(); return L.err; }
             if (h[1] != 0 || h[2] != 0) { mem.release_all(); return GREM_ERR_SEED; }
             maxdeg = h[0];
             if (R >= 32 || (maxdeg << R) >= (1ull << 32)) { mem.release_all(); return GREM_ERR_RANGE; }
+            for (int i = 0; i < kLongClasses; ++i) degrees[i] = h[16 + i];
         }
-        rc = run_plain<RowT, LabelT>(rowptr, colidx, n, k, slack, cl, R, seed, labels_out, sizes_out, estimates_out, o,
+        rc = merged ? run_plain_merged<RowT, LabelT>(rowptr, colidx, n, k, slack, cl, R, seed, labels_out, sizes_out, estimates_out, o,
+                                                     maxdeg, degrees, mem, L, st)
+                    : run_plain<RowT, LabelT>(rowptr, colidx, n, k, slack, cl, R, seed, labels_out, sizes_out, estimates_out, o,
                                      maxdeg, mem, L, st);
     }
     mem.release_all();
@@ -1147,7 +1316,10 @@ int dispatch_labels(const RowT *rowptr, const int32_t *colidx, int64_t n, int32_
     Opts o;
     if (!resolve_options(options, &o)) return GREM_ERR_ARG;
     hipStream_t s = (hipStream_t)stream;
-    if (k <= 255)
+    // a byte per label: 255 marks a vertex without one, which a run that starts without a seed and takes the merged
+    // launches of the plain route never looks at
+    const int64_t cl = chunk < n ? chunk : n;
+    if (k <= 255 || (k == 256 && !seed && plain_merged(k, cl, o.hist_mode)))
         return run_partition<RowT, uint8_t>(rowptr, colidx, n, k, slack, chunk, R, seed, labels_out,
                                             sizes_out, estimates_out, o, s);
     return run_partition<RowT, uint16_t>(rowptr, colidx, n, k, slack, chunk, R, seed, labels_out,

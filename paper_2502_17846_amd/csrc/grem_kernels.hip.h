@@ -46,7 +46,8 @@ __device__ __forceinline__ int owning_row(const uint32_t *rowrel, uint32_t i, in
 // prepass: compact labels from the seed, seed sizes, seed validity, and (when rowptr is given)
 // the maximum degree
 // misc[0] = max degree, misc[1] = number of invalid seed labels, misc[3] = number of entries,
-// misc[5] = number of vertices the seed leaves without a label
+// misc[5] = number of vertices the seed leaves without a label, misc[16 + i] = rows of at least long_degree * 2^i and
+// fewer than long_degree * 2^(i+1) entries (i = 15: and more)
 // ------------------------------------------------------------------------------------------------
 constexpr int kPrepassLdsK = 1024;      // up to this k the seed sizes are counted in LDS first
 template <typename RowT, typename LabelT>
@@ -54,13 +55,15 @@ __global__ __launch_bounds__(256) void k_prepass(const RowT *__restrict__ rowptr
                                                  const int32_t *__restrict__ seed, int64_t n, int k,
                                                  LabelT *__restrict__ Lc,
                                                  unsigned long long *__restrict__ S,
-                                                 unsigned long long *__restrict__ misc) {
+                                                 unsigned long long *__restrict__ misc, uint32_t long_degree) {
+    __shared__ unsigned int s_long[16];
     __shared__ unsigned long long s_maxdeg;
     __shared__ unsigned int s_bad, s_none;
     // (a workgroup's vertices: at most n / gridDim.x + 256 < 2^32)
     __shared__ unsigned int s_size[kPrepassLdsK];
     const bool in_lds = seed && k <= kPrepassLdsK;
     if (threadIdx.x == 0) { s_maxdeg = 0; s_bad = 0; s_none = 0; }
+    if (threadIdx.x < 16) s_long[threadIdx.x] = 0;
     if (in_lds)
         for (int j = threadIdx.x; j < k; j += 256) s_size[j] = 0;
     __syncthreads();
@@ -71,6 +74,11 @@ __global__ __launch_bounds__(256) void k_prepass(const RowT *__restrict__ rowptr
         if (rowptr) {
             unsigned long long d = (unsigned long long)(rowptr[v + 1] - rowptr[v]);
             if (d > mymax) mymax = d;
+            if (d >= long_degree) {
+                const unsigned long long q = d / long_degree;
+                const int c = 63 - __clzll((long long)q);
+                atomicAdd(&s_long[c < 15 ? c : 15], 1u);
+            }
         }
         uint32_t lab = LabelTraits<LabelT>::kUnassigned;
         if (seed) {
@@ -95,8 +103,10 @@ __global__ __launch_bounds__(256) void k_prepass(const RowT *__restrict__ rowptr
     if (in_lds)
         for (int j = threadIdx.x; j < k; j += 256)
             if (s_size[j]) atomicAdd(&S[j], (unsigned long long)s_size[j]);
+    if (rowptr && threadIdx.x < 16 && s_long[threadIdx.x]) atomicAdd(&misc[16 + threadIdx.x], (unsigned long long)s_long[threadIdx.x]);
     if (threadIdx.x == 0) {
-        if (s_maxdeg) atomicMax(&misc[0], s_maxdeg);
+        // (few workgroups raise the maximum: the plain read spares the others the atomic)
+        if (s_maxdeg > __hip_atomic_load(&misc[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&misc[0], s_maxdeg);
         if (s_bad) atomicAdd(&misc[1], (unsigned long long)s_bad);
         if (s_none) atomicAdd(&misc[5], (unsigned long long)s_none);
         if (blockIdx.x == 0 && rowptr) misc[3] = (unsigned long long)rowptr[n];
@@ -1145,10 +1155,8 @@ template <typename LabelT>
 __global__ __launch_bounds__(256) void k_expand(const LabelT *__restrict__ Lc, int64_t n,
                                                 int32_t *__restrict__ out) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
-        uint32_t l = Lc[v];
-        out[v] = (l == LabelTraits<LabelT>::kUnassigned) ? -1 : (int32_t)l;
-    }
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride)
+        out[v] = (int32_t)Lc[v];                    // (after a run every vertex has a label)
 }
 
 // ------------------------------------------------------------------------------------------------
