@@ -18,6 +18,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "grem_kernels.hip.h"
@@ -49,6 +50,8 @@ constexpr int64_t kSweepMinChunk = 1 << 14;   // AUTO: per-chunk launches must h
 constexpr int kDefaultColBits = 17;        // 2^17 labels, two per byte: 64 KB of LDS, two workgroups per CU
 constexpr int kDefaultColBits32 = 16;      // k > 16: 2^16 labels, a byte each
 constexpr int kDefaultHubDegree = 8192;
+constexpr int64_t kMinSlices = 256;        // slices per chunk wanted: one per CU (and with 512 rows, of which two
+                                           // share a tile's row of mover counts, never more than 256 tiles)
 constexpr int64_t kMaxSegments = 1ll << 22;   // chunks * column blocks
 constexpr int64_t kCutPackMinN = 1 << 20;  // edge cut: int32 labels of more vertices outgrow an XCD's 4 MB of L2
 constexpr int kMaxParts = kPlanParts;      // parts of a slice (hub share) in the re-layout
@@ -173,7 +176,7 @@ template <typename F> size_t carve_size(F &&f) {
 
 // ---- geometry of the two-phase route: chunks, row slices and column blocks (grem_twophase.hip.h) ---
 struct TpGeom {
-    int cb = 0, nbc = 0, nblk = 0, nch = 0, nsl = 0, shift = -1, gb = 0, ngroups = 1;
+    int cb = 0, nbc = 0, nblk = 0, nch = 0, nsl = 0, srows = kSliceRows, shift = -1, gb = 0, ngroups = 1;
     uint32_t chunk = 0;
     bool ok = false;
 };
@@ -183,7 +186,6 @@ TpGeom tp_geometry(int64_t n, int64_t chunk, int col_bits_setting, int kmax) {
     TpGeom t;
     const int64_t cl = chunk < n ? chunk : n;
     const int64_t nch = (n + cl - 1) / cl;
-    const int64_t nsl = (cl + kSliceRows - 1) / kSliceRows;
     int cb = col_bits_setting;
     if (cb == 0) {
         const int want = kmax > 16 ? kDefaultColBits32 : kDefaultColBits;
@@ -192,6 +194,11 @@ TpGeom tp_geometry(int64_t n, int64_t chunk, int col_bits_setting, int kmax) {
     }
     const int64_t nbc = (cl + (1ll << cb) - 1) >> cb;
     const int64_t nblk = nch * nbc;
+    // Rows per slice: a workgroup of the score kernel each, so a chunk of fewer slices than the chip has CUs is cut
+    // finer -- as long as a sub-segment still has rows enough to be worth its padding and its table entries (some
+    // two per column block: at the usual degrees tens of entries, padded to a multiple of eight)
+    while (t.srows > 512 && (cl + t.srows - 1) / t.srows < kMinSlices && t.srows / 2 >= 2 * nblk) t.srows /= 2;
+    const int64_t nsl = (cl + t.srows - 1) / t.srows;
     t.cb = cb;
     t.chunk = (uint32_t)cl;
     for (int b = 0; b < 31; ++b)
@@ -394,10 +401,10 @@ int build_plan(PlanData &P, const RowT *rowptr, const int32_t *colidx, int64_t n
     L.memset(P.pmisc, 0, 16 * 8);
     L.run(GREM_KERNEL_RELAYOUT, [&] {
         hipLaunchKernelGGL((k_plan_slices<RowT>), dim3(G), dim3(256), 0, stream, rowptr, n, cl, nsl,
-                           (uint32_t)hub_degree, pl, P.pmisc);
+                           geo.srows, (uint32_t)hub_degree, pl, P.pmisc);
     });
     L.run(GREM_KERNEL_RELAYOUT, [&] {
-        hipLaunchKernelGGL(k_plan_chunks, dim3((unsigned)geo.nch), dim3(256), 0, stream, n, cl, nsl, geo.nblk,
+        hipLaunchKernelGGL(k_plan_chunks, dim3((unsigned)geo.nch), dim3(256), 0, stream, n, cl, nsl, geo.srows, geo.nblk,
                            (uint32_t)(kmax > 16 ? kHubsPerShare32 : kHubsPerShare16), pl, P.pmisc);
     });
     L.run(GREM_KERNEL_RELAYOUT, [&] {
@@ -419,7 +426,7 @@ int build_plan(PlanData &P, const RowT *rowptr, const int32_t *colidx, int64_t n
     if (!carve(keep, [&](Carver &c) { plan_stage2(c, d, pl); })) return GREM_ERR_NOMEM;
     L.run(GREM_KERNEL_RELAYOUT, [&] {
         hipLaunchKernelGGL((k_plan_hubs<RowT>), dim3(G), dim3(256), 0, stream, rowptr, n, cl, nsl,
-                           (uint32_t)hub_degree, pl);
+                           geo.srows, (uint32_t)hub_degree, pl);
     });
     L.run(GREM_KERNEL_RELAYOUT, [&] {
         hipLaunchKernelGGL(k_plan_shares, dim3((G + 255) / 256), dim3(256), 0, stream, n, cl, nsl, (int)G, pl,
@@ -445,9 +452,9 @@ int build_plan(PlanData &P, const RowT *rowptr, const int32_t *colidx, int64_t n
     // a share may touch kMaxShareHubs hubs; sub-segment offsets are 32-bit
     {
         auto score_fits = [&](int kk) {
-            const size_t dyn = ((size_t)kSliceRows / 2 + (size_t)share_hubs * kk + 3 * (size_t)kk) * 4;
-            if (kk <= 16) return dyn + (size_t)kSliceRows * 32 <= 150 * 1024;
-            return geo.cb <= 16 && dyn + (size_t)kSliceRows * 64 <= 158 * 1024;    // (a byte per label in the look-up's LDS)
+            const size_t dyn = ((size_t)geo.srows / 2 + (size_t)share_hubs * kk + 3 * (size_t)kk) * 4;
+            if (kk <= 16) return dyn + (size_t)geo.srows * 32 <= 150 * 1024;
+            return geo.cb <= 16 && dyn + (size_t)geo.srows * 64 <= 158 * 1024;    // (a byte per label in the look-up's LDS)
         };
         int max_k = kmax;
         while (max_k > 1 && !score_fits(max_k) && k == 0) --max_k;
@@ -471,6 +478,7 @@ int build_plan(PlanData &P, const RowT *rowptr, const int32_t *colidx, int64_t n
         return (uint32_t)(kGroupLds > fixed ? (kGroupLds - fixed) / 4 : 0);
     };
     int npr = 1, nps = 1;
+    const int most_parts = geo.srows / kPlanThreads;        // of a slice
     // ... and, if that takes no more than kMaxParts, so small that a thread holds its share of the unit's
     // entries in registers (one round of kTpThreads * kTpBatch entries)
     const unsigned long long one_round = (unsigned long long)kTpThreads * kTpBatch;
@@ -478,7 +486,7 @@ int build_plan(PlanData &P, const RowT *rowptr, const int32_t *colidx, int64_t n
         const unsigned long long unit = most / np + most / (8ull * np) + 64;
         return group_cap(share, np) >= unit && (!in_regs || unit <= one_round);
     };
-    while (npr < kMaxParts && !fits_unit(false, npr, h[9], false)) npr *= 2;
+    while (npr < most_parts && !fits_unit(false, npr, h[9], false)) npr *= 2;
     while (nps < kMaxParts && !fits_unit(true, nps, h[10], false)) nps += 1;
     {
         // slices differ in size: it is the average one whose parts should take one round (the larger ones
@@ -486,7 +494,7 @@ int build_plan(PlanData &P, const RowT *rowptr, const int32_t *colidx, int64_t n
         const unsigned long long avg_slice =
             ((unsigned long long)P.nnz - P.hub_entries) / (unsigned long long)(d.G ? d.G : 1) + 1;
         int a = npr, b = nps;
-        while (a < kMaxParts && !fits_unit(false, a, avg_slice, true)) a *= 2;
+        while (a < most_parts && !fits_unit(false, a, avg_slice, true)) a *= 2;
         while (b < kMaxParts && !fits_unit(true, b, h[10], true)) b += 1;
         if (fits_unit(false, a, avg_slice, true) && fits_unit(false, a, h[9], false)) npr = a;
         if (fits_unit(true, b, h[10], true)) nps = b;
@@ -511,6 +519,7 @@ int build_plan(PlanData &P, const RowT *rowptr, const int32_t *colidx, int64_t n
     }
     tb.nch = geo.nch;
     tb.nsl = geo.nsl;
+    tb.srows = geo.srows;
     tb.nr = d.nr;
     tb.nbc = geo.nbc;
     tb.nblk = geo.nblk;
@@ -519,6 +528,8 @@ int build_plan(PlanData &P, const RowT *rowptr, const int32_t *colidx, int64_t n
     tb.gb = geo.gb;
     tb.ngroups = geo.ngroups;
     tb.npr = npr;
+    tb.prows = geo.srows / npr;
+    tb.pstep = geo.srows / kPlanThreads / npr;
     tb.nps = nps;
     P.lookup_target = geo.cb > 17 ? 256 : 512;
 
@@ -608,7 +619,7 @@ void state_common(Carver &c, CallState<LabelT> &st, int64_t n, int64_t cl, int32
     c.take(st.prop, (size_t)cl);
     c.take(st.S, (size_t)k);
     c.take(st.S2, (size_t)k);                // the sizes' other copy (the one-launch spill reads one, writes the other)
-    c.take(st.cnt, ntiles * (size_t)k);
+    c.take(st.cnt, 2 * ntiles * (size_t)k);      // (a slice of fewer rows than a tile has counts of its own)
     c.take(st.tot, 2 * (size_t)k);
     c.take(st.room, (size_t)k);
     c.take(st.ocnt, ntiles);
@@ -626,7 +637,7 @@ void launch_prepass(Launcher &L, const RowT *rowptr_or_null, const int32_t *seed
     L.memset(st.S, 0, (size_t)k * 8);
     L.memset(st.misc, 0, 32 * 8);
     int64_t blocks = (n + 255) / 256;
-    if (blocks > 256 * 32) blocks = 256 * 32;
+    if (blocks > 256 * 8) blocks = 256 * 8;      // (every workgroup adds its sums at the same few addresses)
     L.run(GREM_KERNEL_PREPASS, [&] {
         hipLaunchKernelGGL((k_prepass<RowT, LabelT>), dim3((unsigned)blocks), dim3(256), 0, stream, rowptr_or_null, seed,
                            n, (int)k, st.Lc, (unsigned long long *)st.S, st.misc, long_degree);
@@ -682,7 +693,7 @@ void state_two_phase(Carver &c, TpState &t, int64_t n, int32_t k, size_t slots, 
     c.take(lx, (k <= 16 ? slots / 2 : slots) + 16);               // label, 4 bits per tuple (8 when k > 16)
     t.Lx = reinterpret_cast<uint32_t *>(lx);
     c.take(t.Hhub, (twice ? 2 : 1) * (max_chunk_hubs + 1) * (size_t)k);
-    c.take(t.Rdyn, seeded ? slots + 8 : 0);                       // seeded runs: R with the unassigned neighbours marked
+    c.take(t.Rdyn, seeded && k == 16 ? slots + 8 : 0);            // seeded runs: R with the unassigned neighbours marked
     c.take(t.E16, use16 ? (size_t)n * (size_t)k : 0);
     c.take(t.E32, (!use16 && !external_E) ? (size_t)n * (size_t)k : 0);
     c.take(t.Ehub, (use16 && !external_E) ? (twice ? 2 : 1) * (total_hubs + 1) * (size_t)k : 0);
@@ -751,24 +762,37 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
     uint32_t *Ehub_rows = (use16 && !external_E) ? nullptr : E32;    // hubs: rows of E32 when there is one, else Ehub
     if (k > P.max_k) return GREM_ERR_ARG;
     const bool wide = k > 16;                     // 8-bit labels in Lx, 128 KB of counters per slice
-    const size_t score_lds = ((size_t)kSliceRows / 2 + (size_t)P.share_hubs * k + 3 * (size_t)k) * 4 +
-                             (wide ? (size_t)kSliceRows * 64 : 0);
+    const size_t score_lds = ((size_t)geo.srows / 2 + (size_t)P.share_hubs * k + 3 * (size_t)k) * 4 +
+                             (wide ? (size_t)geo.srows * 64 : 0);
+    const int cell_rows = geo.srows < kAdmitTile ? geo.srows : kAdmitTile, cpt = kAdmitTile / cell_rows;
     const size_t lookup_lds = wide ? ((size_t)1 << (geo.cb > 4 ? geo.cb : 4)) : ((size_t)1 << (geo.cb > 5 ? geo.cb - 1 : 4));
-    if (wide) {
-        if (!set_lds((const void *)k_tp_lookup<true, false, 8>, lookup_lds) ||
-            !set_lds((const void *)k_tp_lookup<true, true, 8>, lookup_lds) ||
-            !set_lds((const void *)k_tp_score<uint32_t, 32>, score_lds) ||
-            !set_lds((const void *)k_tp_score<uint16_t, 32>, score_lds))
-            return GREM_ERR_HIP;
-    } else {
-        if (!set_lds((const void *)k_tp_lookup<true, false, 4>, lookup_lds) ||
-            !set_lds((const void *)k_tp_lookup<true, true, 4>, lookup_lds) ||
-            !set_lds((const void *)k_tp_score<uint32_t, 16>, score_lds) ||
-            !set_lds((const void *)k_tp_score<uint16_t, 16>, score_lds) ||
-            !set_lds((const void *)k_tp_score<uint32_t, 16, true>, score_lds) ||
-            !set_lds((const void *)k_tp_score<uint16_t, 16, true>, score_lds))
-            return GREM_ERR_HIP;
-    }
+    // f(kernel, estimates): the score kernel for the estimates' type, the partitions and the rows per slice (skip:
+    // neighbours without a label among 32 partitions)
+    auto with_score = [&](bool skip, auto &&f) {
+        auto rows = [&](auto sr) {
+            constexpr int SR = decltype(sr)::value;
+            if (wide) {
+                if (skip) { if (use16) f(k_tp_score<uint16_t, 32, false, SR, true>, t.E16); else f(k_tp_score<uint32_t, 32, false, SR, true>, E32); }
+                else if (use16) f(k_tp_score<uint16_t, 32, false, SR>, t.E16);
+                else f(k_tp_score<uint32_t, 32, false, SR>, E32);
+            } else if (k <= 8) {                         // (a row's few counters spread over the LDS banks)
+                if (use16) f(k_tp_score<uint16_t, 16, true, SR>, t.E16);
+                else f(k_tp_score<uint32_t, 16, true, SR>, E32);
+            } else {
+                if (use16) f(k_tp_score<uint16_t, 16, false, SR>, t.E16);
+                else f(k_tp_score<uint32_t, 16, false, SR>, E32);
+            }
+        };
+        if (geo.srows == 512) rows(std::integral_constant<int, 512>{});
+        else if (geo.srows == 1024) rows(std::integral_constant<int, 1024>{});
+        else rows(std::integral_constant<int, kSliceRows>{});
+    };
+    bool lds_ok = wide ? set_lds((const void *)k_tp_lookup<true, false, 8>, lookup_lds)
+                       : set_lds((const void *)k_tp_lookup<true, false, 4>, lookup_lds) &&
+                             set_lds((const void *)k_tp_lookup<true, true, 4>, lookup_lds);
+    for (int skip = 0; skip < 2; ++skip)
+        with_score(skip != 0, [&](auto kernel, auto *) { lds_ok = lds_ok && set_lds((const void *)kernel, score_lds); });
+    if (!lds_ok) return GREM_ERR_HIP;
     L.memset(t.Hhub, 0, (hubs_in_admission ? 2 : 1) * ((size_t)P.max_chunk_hubs + 1) * (size_t)k * 4);
     const size_t coarse_row = (size_t)(kAdmitTilesMax / kCoarseTiles) * (size_t)k;
     if (hubs_in_admission) L.memset(t.coarse, 0, 2 * coarse_row * 4);
@@ -792,9 +816,7 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
         };
         L.run(GREM_KERNEL_LOOKUP, [&] {
             if (wide) {
-                if (!from_lds) go(k_tp_lookup<false, true, 8>, 0);
-                else if (mark) go(k_tp_lookup<true, true, 8>, lookup_lds);
-                else go(k_tp_lookup<true, false, 8>, lookup_lds);
+                go(k_tp_lookup<true, false, 8>, lookup_lds);
             } else {
                 if (!from_lds) go(k_tp_lookup<false, true, 4>, 0);
                 else if (mark) go(k_tp_lookup<true, true, 4>, lookup_lds);
@@ -802,10 +824,10 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
             }
         });
     };
-    // A seed that leaves vertices without a label: the first pass reads its row fields from Rdyn, where the
-    // initial look-up marks the tuples whose neighbour has none.  A seed that labels every vertex marks
-    // nothing: R serves as it is, and the initial look-up is the one that copies the labels to LDS.
-    const bool marks = seed != nullptr && !st.seed_complete;
+    // A seed that leaves vertices without a label: their entries are told by the label that the look-up stores, except
+    // with 16 partitions in four bits, where the first pass reads its row fields from Rdyn and the initial look-up,
+    // from global memory, marks the entries there.
+    const bool partly = seed != nullptr && !st.seed_complete, marks = partly && k == 16;
     if (seed) {        // the seeds are the labels every first-pass look-up starts from
         for (int c0 = 0; c0 < geo.nch; c0 += 32768) {
             const int count = geo.nch - c0 < 32768 ? geo.nch - c0 : 32768;
@@ -825,7 +847,8 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
             const int64_t hi = (lo + cl < n) ? lo + cl : n;
             const int64_t len = hi - lo;
             const unsigned admit_blocks = (unsigned)((len + kAdmitTile - 1) / kAdmitTile);
-            const unsigned blocks = (unsigned)((len + kSliceRows - 1) / kSliceRows);
+            const unsigned blocks = (unsigned)((len + geo.srows - 1) / geo.srows);
+            const int ncells = (int)((len + cell_rows - 1) / cell_rows);
             const int jlim = (pass == 0 && !seed) ? (int)c * geo.nbc : geo.nblk;
             // the estimates are state between passes and, if the caller asked for them, output: the last
             // pass does not store them otherwise
@@ -843,21 +866,7 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
                                    hubs_in_admission ? t.hub_old : (uint8_t *)nullptr,
                                    hubs_in_admission ? t.coarse + (size_t)(step & 1) * coarse_row : (uint32_t *)nullptr);
             };
-            L.run(GREM_KERNEL_SCORE, [&] {
-                if (wide) {
-                    if (use16) score(k_tp_score<uint16_t, 32>, t.E16);
-                    else score(k_tp_score<uint32_t, 32>, E32);
-                } else {
-                    // (k <= 8: a row's few counters spread over the LDS banks)
-                    if (k <= 8) {
-                        if (use16) score(k_tp_score<uint16_t, 16, true>, t.E16);
-                        else score(k_tp_score<uint32_t, 16, true>, E32);
-                    } else {
-                        if (use16) score(k_tp_score<uint16_t, 16>, t.E16);
-                        else score(k_tp_score<uint32_t, 16>, E32);
-                    }
-                }
-            });
+            L.run(GREM_KERNEL_SCORE, [&] { with_score(partly && pass == 0 && k == 32, score); });
             if (hubs_in_admission) {
                 // one launch: every workgroup works out the chunk's hubs for itself; two tables of hub counts
                 // take turns from chunk to chunk, two tables of hub estimates from pass to pass
@@ -868,19 +877,29 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
                 const uint32_t *Eold = t.Ehub + ((size_t)((pass + 1) & 1) * erow + hub0) * (size_t)k;
                 uint32_t *Enew = t.Ehub + ((size_t)(pass & 1) * erow + hub0) * (size_t)k;
                 L.run(GREM_KERNEL_APPLY, [&] {
-                    const dim3 grid((admit_blocks + kSmallApplyTiles - 1) / kSmallApplyTiles);
+                    const unsigned tpw = admit_blocks <= (unsigned)kAdmitGrid ? 1u : admit_blocks <= 2u * kAdmitGrid ? 2u : 4u;
                     auto go = [&](auto kernel) {
-                        hipLaunchKernelGGL(kernel, grid, dim3(kAdmitTile), 0, stream, (uint8_t *)st.Lc, (const uint8_t *)st.prop,
+                        hipLaunchKernelGGL(kernel, dim3((admit_blocks + tpw - 1) / tpw), dim3(kAdmitTile), 0, stream, (uint8_t *)st.Lc, (const uint8_t *)st.prop,
                                            lo, hi, (int)k, (const uint32_t *)st.cnt, (int)admit_blocks,
                                            (const long long *)st.room, (unsigned long long *)Snow, st.ocnt, pass, packed_now,
                                            (const int32_t *)(pl.hub_row + hub0), (const uint8_t *)t.hub_old, nh,
                                            (const uint32_t *)Hnow, Hother,
                                            prev_hubs, Eold, Enew, store_e,
                                            (const uint32_t *)(t.coarse + (size_t)(step & 1) * coarse_row),
-                                           t.coarse + (size_t)((step + 1) & 1) * coarse_row);
+                                           t.coarse + (size_t)((step + 1) & 1) * coarse_row, ncells);
                     };
-                    if (wide) go(k_admit_hubs<32>);
-                    else go(k_admit_hubs<16>);
+                    // (slices of fewer rows than a tile are those of short chunks: one tile per workgroup)
+                    if (wide) {
+                        if (cpt == 2) go(k_admit_hubs<32, 1, 2>);
+                        else if (tpw == 1) go(k_admit_hubs<32, 1, 1>);
+                        else if (tpw == 2) go(k_admit_hubs<32, 2, 1>);
+                        else go(k_admit_hubs<32, 4, 1>);
+                    } else {
+                        if (cpt == 2) go(k_admit_hubs<16, 1, 2>);
+                        else if (tpw == 1) go(k_admit_hubs<16, 1, 1>);
+                        else if (tpw == 2) go(k_admit_hubs<16, 2, 1>);
+                        else go(k_admit_hubs<16, 4, 1>);
+                    }
                 });
                 prev_hubs = nh;
             } else {
@@ -889,12 +908,12 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
                 if (wide)
                     hipLaunchKernelGGL(k_hub_finalize<32>, dim3((unsigned)((max_chunk_hubs + 7) / 8) + 1), dim3(256), 0,
                                        stream, pl, (const uint8_t *)st.Lc, st.room, Ehub_rows, t.Ehub, t.Hhub,
-                                       (uint8_t *)st.prop, st.cnt, (int)c, lo, (int)k, pass, store_e, (int)admit_blocks,
+                                       (uint8_t *)st.prop, st.cnt, (int)c, lo, (int)k, pass, store_e, ncells, cell_rows,
                                        st.tot);
                 else
                     hipLaunchKernelGGL(k_hub_finalize<16>, dim3((unsigned)((max_chunk_hubs + 15) / 16) + 1), dim3(256), 0,
                                        stream, pl, (const uint8_t *)st.Lc, st.room, Ehub_rows, t.Ehub, t.Hhub,
-                                       (uint8_t *)st.prop, st.cnt, (int)c, lo, (int)k, pass, store_e, (int)admit_blocks,
+                                       (uint8_t *)st.prop, st.cnt, (int)c, lo, (int)k, pass, store_e, ncells, cell_rows,
                                        st.tot);
             });
             if (fixed_labels) continue;          // counts only: nothing to admit, no new labels to look up
@@ -902,14 +921,12 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
             // the tiles are few enough that every workgroup adds up the earlier tiles' counts itself
             L.run(GREM_KERNEL_APPLY, [&] {
                 const dim3 grid((admit_blocks + kSmallApplyTiles - 1) / kSmallApplyTiles);
-                if (wide)
-                    hipLaunchKernelGGL(k_apply_small<32>, grid, dim3(kAdmitTile), 0, stream, (uint8_t *)st.Lc,
-                                       (const uint8_t *)st.prop, lo, hi, (int)k, st.cnt, st.room, st.tot,
-                                       (unsigned long long *)Snow, st.ocnt, pass, (uint8_t *)nullptr);
-                else
-                    hipLaunchKernelGGL(k_apply_small<16>, grid, dim3(kAdmitTile), 0, stream, (uint8_t *)st.Lc,
-                                       (const uint8_t *)st.prop, lo, hi, (int)k, st.cnt, st.room, st.tot,
-                                       (unsigned long long *)Snow, st.ocnt, pass, packed_now);
+                auto go = [&](auto kernel, uint8_t *packed) {
+                    hipLaunchKernelGGL(kernel, grid, dim3(kAdmitTile), 0, stream, (uint8_t *)st.Lc, (const uint8_t *)st.prop, lo, hi,
+                                       (int)k, st.cnt, st.room, st.tot, (unsigned long long *)Snow, st.ocnt, pass, packed, ncells);
+                };
+                if (wide) cpt == 2 ? go(k_apply_small<32, 2>, nullptr) : go(k_apply_small<32, 1>, nullptr);
+                else cpt == 2 ? go(k_apply_small<16, 2>, packed_now) : go(k_apply_small<16, 1>, packed_now);
             });
             }
             if (pass == 0) {

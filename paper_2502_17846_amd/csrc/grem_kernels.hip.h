@@ -734,15 +734,25 @@ __device__ __forceinline__ void wave_counts_to_prefix(uint32_t (*wcnt)[kAdmitTil
 
 // ------------------------------------------------------------------------------------------------
 // apply for k <= KP (16 or 32): the same admission, one vertex of each of kSmallApplyTiles neighbouring
-// tiles per thread, a workgroup of kAdmitTile threads per such group of tiles.  cnt[tile][t] = movers
-// to t in that tile, tot[t] >= movers to t in the whole chunk, room[t] = P - S[t] as of the chunk's
+// tiles per thread, a workgroup of kAdmitTile threads per such group of tiles.  cnt: movers to t, CPT (1 or 2)
+// rows per tile, ncells rows in all, tot[t] >= movers to t in the whole chunk, room[t] = P - S[t] as of the chunk's
 // start.  A partition with no room admits nobody, one with room for all its movers admits everybody;
 // only for the others (room for some) are ranks needed: the workgroup adds up their columns of the
 // earlier tiles' counts and takes one ballot per such partition and tile.
 // ------------------------------------------------------------------------------------------------
 constexpr int kSmallApplyTiles = 4;     // neighbouring tiles per workgroup of k_apply_small
 
-template <int KP>
+// movers of a tile to t: CPT rows of cnt, as far as the chunk has them
+template <int CPT>
+__device__ __forceinline__ uint32_t tile_movers(const uint32_t *__restrict__ cnt, int tile, int k, int t, int ncells) {
+    uint32_t sum = 0;
+#pragma unroll
+    for (int i = 0; i < CPT; ++i)
+        if (tile * CPT + i < ncells) sum += cnt[(size_t)(tile * CPT + i) * k + t];
+    return sum;
+}
+
+template <int KP, int CPT>
 __global__ __launch_bounds__(kAdmitTile) void k_apply_small(uint8_t *__restrict__ Lc, const uint8_t *__restrict__ prop,
                                                             int64_t chunk_lo, int64_t chunk_hi, int k,
                                                             const uint32_t *__restrict__ cnt,
@@ -750,7 +760,7 @@ __global__ __launch_bounds__(kAdmitTile) void k_apply_small(uint8_t *__restrict_
                                                             const uint32_t *__restrict__ tot,
                                                             unsigned long long *__restrict__ S,
                                                             uint32_t *__restrict__ ocnt, int pass,
-                                                            uint8_t *__restrict__ Lc4) {
+                                                            uint8_t *__restrict__ Lc4, int ncells) {
     static_assert(KP == 16 || KP == 32, "partitions per workgroup table");
     constexpr int nwaves = kAdmitTile / 64;
     constexpr int TPW = kSmallApplyTiles;
@@ -779,14 +789,15 @@ __global__ __launch_bounds__(kAdmitTile) void k_apply_small(uint8_t *__restrict_
     // the tiles are few (needed only if the partition turns out to be one with room for some: then the
     // loads' latency is already behind us), else after that is known
     const int col = tid & (KP - 1), seg = tid / KP;
-    const bool early = tile0 <= 16 * SEGS;
+    const int cell0 = tile0 * CPT;
+    const bool early = cell0 <= 16 * SEGS;
     uint32_t before = 0;
     if (early && col < k) {
         uint32_t x[16];
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
             const int r = seg + SEGS * u;
-            x[u] = r < tile0 ? cnt[(size_t)r * k + col] : 0u;
+            x[u] = r < cell0 ? cnt[(size_t)r * k + col] : 0u;
         }
 #pragma unroll
         for (int u = 0; u < 16; ++u) before += x[u];
@@ -794,7 +805,7 @@ __global__ __launch_bounds__(kAdmitTile) void k_apply_small(uint8_t *__restrict_
     uint32_t own[TPW];
 #pragma unroll
     for (int h = 0; h < TPW; ++h)
-        own[h] = (tid < k && chunk_lo + (int64_t)(tile0 + h) * kAdmitTile < chunk_hi) ? cnt[(size_t)(tile0 + h) * k + tid] : 0u;
+        own[h] = tid < k ? tile_movers<CPT>(cnt, tile0 + h, k, tid, ncells) : 0u;
     if (tid < 64) {
         long long rm = 0;
         bool some = false;
@@ -817,7 +828,7 @@ __global__ __launch_bounds__(kAdmitTile) void k_apply_small(uint8_t *__restrict_
         if ((ranked >> col) & 1u) {   // earlier tiles: thread (seg, col) adds up rows seg, seg + SEGS, ...
             uint32_t sum = before;
             if (!early)
-                for (int r = seg; r < tile0; r += SEGS) sum += cnt[(size_t)r * k + col];
+                for (int r = seg; r < cell0; r += SEGS) sum += cnt[(size_t)r * k + col];
             if (sum) atomicAdd(&tbl[col], sum);
         }
 #pragma unroll

@@ -11,7 +11,8 @@
 //
 // How: once per graph the CSR entries are re-laid-out into tuples (row in slice, column in block):
 //   * a column block is 2^cb consecutive vertices counted from the start of their chunk;
-//   * a row slice is 2048 consecutive rows counted from the start of their chunk;
+//   * a row slice is 2048 consecutive rows counted from the start of their chunk, or 1024 or 512 in chunks that
+//     would otherwise have fewer slices than the chip has CUs (tp_geometry);
 //   * rows of degree >= hub_degree ("hubs") are taken out of their slice: the chunk's hub entries,
 //     concatenated in row order, are cut in equal shares (k_plan_chunks picks how many);
 //   * a "row" r of chunk c is slice r (r < nsl) or share r - nsl; there are nr = nsl + (the largest
@@ -48,7 +49,7 @@
 namespace grem {
 
 constexpr int kSliceRowBits = 11;
-constexpr int kSliceRows = 1 << kSliceRowBits;     // rows per slice (row index << 5 fits the 16 bits of R)
+constexpr int kSliceRows = 1 << kSliceRowBits;     // most rows per slice (row index << 5 fits the 16 bits of R)
 constexpr int kPlanThreads = 256;
 constexpr int kPlanParts = kSliceRows / kPlanThreads;     // finest cut of a slice the re-layout uses
 constexpr int kTpThreads = 1024;                   // k_tp_lookup and k_tp_score
@@ -102,6 +103,7 @@ struct TpTables {
     u64 *ustart;      // [nch * nsl * npr]: first tuple of a slice part's range of U (regular entries, compacted)
     u64 *ustart_h;    // [nch * nsl * nps]: the same for the parts of the hub shares (after all regular entries)
     int npr;          // parts per slice (a power of two: equal row ranges)
+    int prows, pstep; // rows of a part, and that in units of kPlanThreads rows
     int nps;          // parts per hub share (equal ranges of its entries)
     int gb;           // log2 of the column blocks per group of the intermediate copy U
     int ngroups;      // ceil(nblk / 2^gb)
@@ -110,6 +112,7 @@ struct TpTables {
     uint32_t chunk_magic, chunk_magic_shift;   // u / chunk = mulhi(u, magic) >> shift for every u < 2^31
     int nch;          // chunks
     int nsl;          // row slices per chunk
+    int srows;        // rows per slice: 2048, 1024 or 512
     int nr;           // rows (slices, then hub shares) per chunk
     int nbc;          // column blocks per chunk
     int nblk;         // nch * nbc
@@ -162,7 +165,7 @@ __device__ __forceinline__ void block_scan2(uint32_t a, u64 b, uint32_t *ea, u64
 // ------------------------------------------------------------------------------------------------
 template <typename RowT>
 __global__ __launch_bounds__(256) void k_plan_slices(const RowT *__restrict__ rowptr, int64_t n,
-                                                     int64_t chunk, int nsl, uint32_t hub_degree,
+                                                     int64_t chunk, int nsl, int srows, uint32_t hub_degree,
                                                      SweepPlan pl, u64 *__restrict__ misc) {
     __shared__ u64 s_reg, s_hent, s_maxdeg;
     __shared__ uint32_t s_nh, s_part[kPlanParts];
@@ -171,7 +174,7 @@ __global__ __launch_bounds__(256) void k_plan_slices(const RowT *__restrict__ ro
     const int i = blockIdx.x % nsl;
     const int64_t chunk_lo = c * chunk;
     const int64_t chunk_hi = (chunk_lo + chunk < n) ? chunk_lo + chunk : n;
-    const int64_t v0 = chunk_lo + (int64_t)i * kSliceRows;
+    const int64_t v0 = chunk_lo + (int64_t)i * srows;
     if (tid == 0) { s_reg = 0; s_hent = 0; s_nh = 0; s_maxdeg = 0; }
     if (tid < kPlanParts) s_part[tid] = 0;
     __syncthreads();
@@ -181,7 +184,7 @@ __global__ __launch_bounds__(256) void k_plan_slices(const RowT *__restrict__ ro
     for (int p = 0; p < kPlanParts; ++p) {          // rows 256 p .. 256 p + 255: one per thread
         const int64_t v = v0 + p * kPlanThreads + tid;
         uint32_t regp = 0;
-        if (v < chunk_hi) {
+        if (p * kPlanThreads < srows && v < chunk_hi) {
             const u64 d = (u64)(rowptr[v + 1] - rowptr[v]);
             if (d >= hub_degree) { nh += 1; hent += d; } else { reg += d; regp = (uint32_t)d; }
             maxdeg = d > maxdeg ? d : maxdeg;
@@ -217,7 +220,7 @@ __global__ __launch_bounds__(256) void k_plan_slices(const RowT *__restrict__ ro
 // from the slices' counts), misc[10] = most entries in a hub share, misc[11] = most hub shares in a
 // chunk, misc[8] = hub entries of all chunks, misc[12] = hubs of all chunks.
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_plan_chunks(int64_t n, int64_t chunk, int nsl, int nblk,
+__global__ __launch_bounds__(256) void k_plan_chunks(int64_t n, int64_t chunk, int nsl, int srows, int nblk,
                                                      uint32_t hubs_per_share, SweepPlan pl, u64 *__restrict__ misc) {
     __shared__ u64 p_reg[256], p_hent[256];
     __shared__ uint32_t p_nh[256];
@@ -260,7 +263,7 @@ __global__ __launch_bounds__(256) void k_plan_chunks(int64_t n, int64_t chunk, i
         pl.ch_reg0[c] = breg;
         pl.ch_hub0[c] = (u64)bnh;
         const int64_t chunk_hi = (chunk_lo + chunk < n) ? chunk_lo + chunk : n;
-        const u64 nsl_c = (u64)((chunk_hi - chunk_lo + kSliceRows - 1) / kSliceRows);
+        const u64 nsl_c = (u64)((chunk_hi - chunk_lo + srows - 1) / srows);
         u64 nvs = 0;
         if (bnh != 0) {
             nvs = bhent / (64ull * (u64)nblk);
@@ -284,7 +287,7 @@ __global__ __launch_bounds__(256) void k_plan_chunks(int64_t n, int64_t chunk, i
 // ------------------------------------------------------------------------------------------------
 template <typename RowT>
 __global__ __launch_bounds__(256) void k_plan_hubs(const RowT *__restrict__ rowptr, int64_t n,
-                                                   int64_t chunk, int nsl, uint32_t hub_degree,
+                                                   int64_t chunk, int nsl, int srows, uint32_t hub_degree,
                                                    SweepPlan pl) {
     __shared__ uint32_t s_a[4];
     __shared__ u64 s_b[4];
@@ -296,10 +299,10 @@ __global__ __launch_bounds__(256) void k_plan_hubs(const RowT *__restrict__ rowp
     if (pl.sl_nh[blockIdx.x] == 0) return;
     const int64_t chunk_lo = c * chunk;
     const int64_t chunk_hi = (chunk_lo + chunk < n) ? chunk_lo + chunk : n;
-    const int64_t v0 = chunk_lo + (int64_t)i * kSliceRows;
+    const int64_t v0 = chunk_lo + (int64_t)i * srows;
     uint32_t run_nh = pl.sl_hub_start[blockIdx.x];
     u64 run_ent = pl.sl_hent_start[blockIdx.x];
-    for (int base = 0; base < kSliceRows; base += 256) {      // same trip count for every thread
+    for (int base = 0; base < srows; base += 256) {      // same trip count for every thread
         const int64_t v = v0 + base + tid;
         u64 d = 0;
         if (v < chunk_hi) d = (u64)(rowptr[v + 1] - rowptr[v]);
@@ -475,8 +478,8 @@ __device__ __forceinline__ bool tp_entry_source(const RowT *__restrict__ rowptr,
     const size_t gs = (size_t)c * tb.nsl + i;
     src->colidx = colidx;
     if (!SHARE) {
-        const int rp = kSliceRows / np;
-        const int64_t v0 = chunk_lo + (int64_t)i * kSliceRows + (int64_t)q * rp;
+        const int rp = tb.prows;
+        const int64_t v0 = chunk_lo + (int64_t)i * tb.srows + (int64_t)q * rp;
         if (v0 >= chunk_hi) return false;                       // part beyond the (ragged) chunk
         uint32_t *rowrel = reinterpret_cast<uint32_t *>(lds);
         const int64_t left = chunk_hi - v0;
@@ -560,7 +563,7 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(8, 8
     const size_t gs_unit = (size_t)c * tb.nsl + i;
     const u64 range0 = SHARE ? pl.ch_hbase[c]
                              : pl.ch_reg0[c] + pl.sl_reg_start[gs_unit] +
-                                   pl.sl_part_reg0[gs_unit * kPlanParts + (size_t)q * (kPlanParts / np)];
+                                   pl.sl_part_reg0[gs_unit * kPlanParts + (size_t)q * tb.pstep];
     for (int j = tid; j < tb.nblk; j += kTpThreads) cntf[j] = 0;    // the source's closing barrier covers this too
     if (!tp_entry_source<RowT, SHARE>(rowptr, colidx, n, hub_degree, pl, tb, c, i, q, np, share_hubs, smem64,
                                       &src)) {
@@ -789,7 +792,7 @@ __global__ __launch_bounds__(kPlaceThreads) void k_tp_place(int64_t n, SweepPlan
     constexpr int kNW = kPlaceThreads / 64, kRU = 4, kXU = 3;
     const int64_t chunk_lo = (int64_t)c * tb.chunk;
     const int64_t chunk_hi = (chunk_lo + tb.chunk < n) ? chunk_lo + tb.chunk : n;
-    const int nsl_c = (int)((chunk_hi - chunk_lo + kSliceRows - 1) / kSliceRows);
+    const int nsl_c = (int)((chunk_hi - chunk_lo + tb.srows - 1) / tb.srows);
     const int nvs = (int)pl.ch_nvs[c];
     const uint32_t gmask = (1u << tb.gb) - 1u, cmask = (1u << tb.cb) - 1u;
     const uint32_t pad = 2048u << tb.cb;
@@ -995,12 +998,12 @@ __global__ __launch_bounds__(kPlaceThreads) void k_tp_place(int64_t n, SweepPlan
 //                 they meet in its L2 (plain stores: the line is kept there until it is complete)
 //   R           : the row field of every tuple << 5 (bit 0: padding), 16 bits each, ordered like Lx; written
 //                 once by the re-layout
-//   FROM_LDS = true : the block's labels are copied to LDS, two per byte (every vertex of the
-//                     block is assigned: the chunk has just been relabelled), from Lc, or from Lc4
-//                     (the same labels already two per byte) when that is given
+//   FROM_LDS = true : the block's labels are copied to LDS, two per byte (four bits of 0xFF for a vertex without
+//                     one: see tp_count_eight), from Lc, or from Lc4 (the same labels already two per byte) when
+//                     that is given
 //   FROM_LDS = false: labels are read from global memory and may be unassigned; used once, for the
-//                     initial labels of a seeded run
-//   WRITE_R         : seeded runs only.  Their first pass reads the row fields from a copy Rdyn in
+//                     initial labels of a partly seeded run of 16 partitions
+//   WRITE_R         : those runs only.  Their first pass reads the row fields from a copy Rdyn in
 //                     which bit 0 also marks tuples whose neighbour is unassigned: the initial
 //                     look-up (FROM_LDS = false) sets it, the first pass's look-ups clear it.
 // A thread takes 8 tuples at a time: 24 bytes of T, one 32-bit word of Lx (16 bytes of R / Rdyn).
@@ -1167,7 +1170,7 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(8, 8
                     const int64_t v = block_lo + (int64_t)col[e];
                     const uint32_t l = v < chunk_hi ? (uint32_t)Lc[v] : 0xFFu;
                     if (l == 0xFFu) unassigned |= 1u << e;
-                    lab = LB == 4 ? (l & 15u) : (l == 0xFFu ? 0u : l);
+                    lab = LB == 4 ? (l & 15u) : l;
                 }
                 if (LB == 4) word |= lab << (4 * e);
                 else if (e < 4) word |= lab << (8 * e);
@@ -1209,6 +1212,7 @@ template <int LB> struct TpLabels;                      // the labels of a group
 template <> struct TpLabels<4> {
     uint32_t w;
     __device__ __forceinline__ uint32_t get(int e) const { return (w >> (4 * e)) & 15u; }
+    __device__ __forceinline__ uint32_t none_bit(int) const { return 0u; }
     __device__ __forceinline__ static TpLabels load(const uint32_t *__restrict__ Lx, u64 base, uint32_t g) {
         TpLabels x;
         x.w = __builtin_nontemporal_load(Lx + (base >> 3) + g);
@@ -1218,7 +1222,8 @@ template <> struct TpLabels<4> {
 };
 template <> struct TpLabels<8> {
     u32x2 w;
-    __device__ __forceinline__ uint32_t get(int e) const { return ((e < 4 ? w.x : w.y) >> (8 * (e & 3))) & 255u; }
+    __device__ __forceinline__ uint32_t get(int e) const { return ((e < 4 ? w.x : w.y) >> (8 * (e & 3))) & 31u; }
+    __device__ __forceinline__ uint32_t none_bit(int e) const { return ((e < 4 ? w.x : w.y) >> (8 * (e & 3) + 7)) & 1u; }
     __device__ __forceinline__ static TpLabels load(const uint32_t *__restrict__ Lx, u64 base, uint32_t g) {
         TpLabels x;
         x.w = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(Lx + (base >> 2)) + g);
@@ -1231,7 +1236,13 @@ template <> struct TpLabels<8> {
 // SW (k <= 8, KP = 16): a row's eight counter words would use two to four of their places only, and the
 // rows' words eight to thirty-two of the 64 LDS banks; the 8-byte piece of partitions 4p .. 4p+3 of row t
 // therefore sits at place p ^ ((t >> 3) & 3) of the row, which spreads them over all banks.
-template <bool COUNT16, int KP, int LB, bool SW>
+//
+// A neighbour without a label (first pass of a seeded run) was looked up as 0xFF.  Of its four or five low bits the
+// label's place is the last of the row's KP counters, which nothing reads while k < KP; hubs' counters have only
+// k places, hence the comparison there.  With k == 32 such a tuple is left out by the label's top bit (MARK); with k ==
+// 16 four bits cannot tell, and the row fields are marked instead (Rdyn: on 400M entries the initial look-up
+// then takes 2.3 ms, from global memory, instead of 0.57, and the first pass's look-ups 15.6 us per chunk instead of 8.6).
+template <bool COUNT16, int KP, int LB, bool SW, bool MARK>
 __device__ __forceinline__ void tp_count_eight(const u32x4 rows, const TpLabels<LB> labels, int k, uint32_t *hist) {
     static_assert(!SW || (COUNT16 && KP == 16), "the swizzle is that of the 16-counter rows");
     const uint32_t w[4] = {rows.x, rows.y, rows.z, rows.w};
@@ -1240,14 +1251,15 @@ __device__ __forceinline__ void tp_count_eight(const u32x4 rows, const TpLabels<
         const uint32_t half = (e & 1) ? (w[e >> 1] >> 16) : w[e >> 1];
         const uint32_t lab = labels.get(e);
         const uint32_t r = half & 0xFFE0u;
-        const uint32_t one = (~half) & 1u;                // bit 0 clear: the tuple is to be counted
+        uint32_t one = (~half) & 1u;                      // bit 0 clear: the tuple is to be counted
+        if (MARK) one &= ~labels.none_bit(e);
         if (COUNT16) {
             // no branch: what is not to be counted adds zero (to a counter its bits happen to name)
             uint32_t off = (KP == 16 ? r : r << 1) | ((lab & ~1u) << 1);
             if (SW) off ^= (r >> 5) & 0x18u;                  // ((row >> 3) & 3) << 3: the piece's place
             uint32_t *ctr = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(hist) + off);
             atomicAdd(ctr, one << ((lab & 1u) << 4));
-        } else if (one) {
+        } else if (one && lab < (uint32_t)k) {
             atomicAdd(&hist[(r >> 5) * (uint32_t)k + lab], 1u);
         }
     }
@@ -1255,7 +1267,7 @@ __device__ __forceinline__ void tp_count_eight(const u32x4 rows, const TpLabels<
 
 // Groups [g0, g1) of a row stream that starts at slot `base` (a multiple of 8) of R and Lx, counted by
 // the whole workgroup, NU groups per thread in flight.
-template <bool COUNT16, int KP, int LB, int NU, bool SW = false>
+template <bool COUNT16, int KP, int LB, int NU, bool SW, bool MARK>
 __device__ __forceinline__ void tp_count_stream(const uint16_t *__restrict__ R, const uint32_t *__restrict__ Lx, u64 base,
                                                 uint32_t g0, uint32_t g1, int k, uint32_t *hist) {
     const u32x4 *R4 = reinterpret_cast<const u32x4 *>(R + base);
@@ -1274,7 +1286,7 @@ __device__ __forceinline__ void tp_count_stream(const uint16_t *__restrict__ R, 
         }
 #pragma unroll
         for (int u = 0; u < NU; ++u)
-            if (g + u * kTpThreads < g1) tp_count_eight<COUNT16, KP, LB, SW>(rows[u], labs[u], k, hist);
+            if (g + u * kTpThreads < g1) tp_count_eight<COUNT16, KP, LB, SW, MARK>(rows[u], labs[u], k, hist);
     }
 }
 
@@ -1301,13 +1313,17 @@ __device__ __forceinline__ unsigned long long tp_xor_lane64(unsigned long long v
 // hub_old: see below (may be null).
 // coarse (may be null): [tiles / kCoarseTiles][k], the mover counts of kCoarseTiles tiles added up (atomic adds
 // into a table that starts at zero), so that the admission need not read every tile's counts.
-// LDS: hist[kSliceRows * KP / 2] (16-bit counters, KP per row; a static array when KP = 16),
-//      meta[kSliceRows / 2] (per row: old label, hub flag << 8), hhist[share_hubs * k], room[k], tcnt[2 * k]
+// cnt has a row per kAdmitTile rows of the chunk, or per SR when slices are smaller.
+// LDS: hist[SR * KP / 2] (16-bit counters, KP per row; a static array when KP = 16),
+//      meta[SR / 2] (per row: old label, hub flag << 8), hhist[share_hubs * k], room[k], tcnt[2 * k]
 // ------------------------------------------------------------------------------------------------
 constexpr int kCoarseTiles = 32;         // tiles per row of the coarse mover counts (a slice's two tiles share one)
 
-template <typename ET, int KP, bool SW = false>
-__global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(KP == 16 ? 8 : 4, KP == 16 ? 8 : 4))) void k_tp_score(
+// SR: rows per slice.  2048 of them fill the LDS of half a CU (of a whole one when KP = 32); a chunk of fewer such
+// slices than CUs is cut in slices of 1024 or 512 rows.  131,072 rows, 3.8M entries: 31.8 us from 64 slices, 15.8 from 256
+// (k = 32); 19.7 and 11.5 us for the counts alone at k = 16.
+template <typename ET, int KP, bool SW = false, int SR = kSliceRows, bool MARK = false>
+__global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(KP == 32 && SR == kSliceRows ? 4 : 8, KP == 32 && SR == kSliceRows ? 4 : 8))) void k_tp_score(
     const uint16_t *__restrict__ R, const uint32_t *__restrict__ Lx, TpTables tb, SweepPlan pl,
     const uint8_t *__restrict__ Lc, const long long *__restrict__ S, ET *__restrict__ E,
     uint32_t *__restrict__ Hhub, uint8_t *__restrict__ prop, uint32_t *__restrict__ cnt,
@@ -1317,17 +1333,18 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(KP =
     extern __shared__ uint32_t smem[];
     constexpr int LB = KP == 16 ? 4 : 8;
     constexpr int LPV = KP / 4;                                 // lanes per vertex in the blend
-    constexpr int hist_words = kSliceRows * KP / 2;
-    constexpr int BU = kSliceRows * LPV / kTpThreads;           // (vertex, lane of the vertex) pairs per thread
+    constexpr int hist_words = SR * KP / 2;
+    constexpr int BU = SR * LPV / kTpThreads;                   // (vertex, lane of the vertex) pairs per thread
     constexpr int IDB = KP == 16 ? 4 : 5;                       // bits of a partition id in the arg-max key
-    static_assert(kSliceRows == 2 * kAdmitTile, "a slice is two admission tiles");
+    constexpr int CELL = SR < kAdmitTile ? SR : kAdmitTile;     // rows per row of cnt
+    static_assert(SR <= 2 * kAdmitTile && kAdmitTile % CELL == 0 && SR * LPV >= kTpThreads, "a slice is at most two rows of cnt");
     // KP = 16: the counters are a static array: its address is a compile-time constant, which spares an
     // add per counted entry
     __shared__ uint32_t hist_static[KP == 16 ? hist_words : 1];
     uint32_t *hist = KP == 16 ? hist_static : smem;
     uint32_t *dyn = KP == 16 ? smem : smem + hist_words;
-    uint16_t *meta = reinterpret_cast<uint16_t *>(dyn);                 // kSliceRows
-    uint32_t *hhist = dyn + kSliceRows / 2;                             // share_hubs * k, 32-bit
+    uint16_t *meta = reinterpret_cast<uint16_t *>(dyn);                 // SR
+    uint32_t *hhist = dyn + SR / 2;                                     // share_hubs * k, 32-bit
     uint32_t *room = hhist + share_hubs * k;    // k
     uint32_t *tcnt = room + k;                  // 2 * k
     const int tid = threadIdx.x;
@@ -1336,9 +1353,9 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(KP =
     // neighbours in memory, meet in one L2.
     const unsigned xcd = blockIdx.x & 7u, turn = blockIdx.x >> 3;
     const unsigned slice = xcd * (gridDim.x >> 3) + (xcd < (gridDim.x & 7u) ? xcd : (gridDim.x & 7u)) + turn;
-    const int64_t v0 = chunk_lo + (int64_t)slice * kSliceRows;
+    const int64_t v0 = chunk_lo + (int64_t)slice * SR;
     const int64_t left = chunk_hi - v0;
-    const int nv = left < kSliceRows ? (int)left : kSliceRows;
+    const int nv = left < SR ? (int)left : SR;
     const bool vec = (k & 3) == 0;
 
     // the hub share this workgroup helps with (nvs: the chunk's number of shares, known to the host, so
@@ -1391,8 +1408,8 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(KP =
         meta[at] |= (uint16_t)0x100u;
     }
 
-    tp_count_stream<true, KP, LB, 3, SW>(R, Lx, sbeg, 0u, slen >> 3, k, hist);
-    if (any_hub) tp_count_stream<false, KP, LB, 2>(R, Lx, hbeg, hg0, hg1, k, hhist);
+    tp_count_stream<true, KP, LB, 3, SW, MARK>(R, Lx, sbeg, 0u, slen >> 3, k, hist);
+    if (any_hub) tp_count_stream<false, KP, LB, 2, false, MARK>(R, Lx, hbeg, hg0, hg1, k, hhist);
     __syncthreads();
 
     // partial counts of the share's hubs -> the chunk's hub table
@@ -1462,17 +1479,17 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(KP =
                 uint32_t bj = (uint32_t)(KP - 1) - ((uint32_t)best & (uint32_t)(KP - 1));
                 if (pass == 0 && old != 0xFFu) bj = old;        // seeded vertex keeps its label
                 prop[v0 + t - chunk_lo] = (uint8_t)bj;
-                if (bj != old) atomicAdd(&tcnt[(t >> 10) * k + (int)bj], 1u);
+                if (bj != old) atomicAdd(&tcnt[t / CELL * k + (int)bj], 1u);
             }
         }
         __syncthreads();
-        const int64_t tile0 = (v0 - chunk_lo) / kAdmitTile;
-        const int ntl = nv > kAdmitTile ? 2 : 1;
-        for (int j = tid; j < ntl * k; j += kTpThreads) cnt[(size_t)tile0 * k + j] = tcnt[j];
+        const int64_t cell0 = (v0 - chunk_lo) / CELL;
+        const int ntl = nv > CELL ? 2 : 1;
+        for (int j = tid; j < ntl * k; j += kTpThreads) cnt[(size_t)cell0 * k + j] = tcnt[j];
         if (coarse)
             for (int j = tid; j < k; j += kTpThreads) {
                 const uint32_t x = tcnt[j] + (ntl > 1 ? tcnt[k + j] : 0u);
-                if (x) atomicAdd(&coarse[(size_t)(tile0 / kCoarseTiles) * k + j], x);
+                if (x) atomicAdd(&coarse[(size_t)((v0 - chunk_lo) / (kAdmitTile * kCoarseTiles)) * k + j], x);
             }
         return;
     }
@@ -1561,18 +1578,18 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(KP =
             uint32_t best = (uint32_t)bestj;
             if (pass == 0 && old != 0xFFu) best = old;      // seeded vertex keeps its label
             prop[v - chunk_lo] = (uint8_t)best;
-            if (best != old) atomicAdd(&tcnt[(t >> 10) * k + (int)best], 1u);
+            if (best != old) atomicAdd(&tcnt[t / CELL * k + (int)best], 1u);
         }
     }
     __syncthreads();
     {
-        const int64_t tile0 = (v0 - chunk_lo) / kAdmitTile;
-        const int ntl = nv > kAdmitTile ? 2 : 1;
-        for (int j = tid; j < ntl * k; j += kTpThreads) cnt[(size_t)tile0 * k + j] = tcnt[j];
+        const int64_t cell0 = (v0 - chunk_lo) / CELL;
+        const int ntl = nv > CELL ? 2 : 1;
+        for (int j = tid; j < ntl * k; j += kTpThreads) cnt[(size_t)cell0 * k + j] = tcnt[j];
         if (coarse)
             for (int j = tid; j < k; j += kTpThreads) {
                 const uint32_t x = tcnt[j] + (ntl > 1 ? tcnt[k + j] : 0u);
-                if (x) atomicAdd(&coarse[(size_t)(tile0 / kCoarseTiles) * k + j], x);
+                if (x) atomicAdd(&coarse[(size_t)((v0 - chunk_lo) / (kAdmitTile * kCoarseTiles)) * k + j], x);
             }
     }
 }
@@ -1592,7 +1609,7 @@ __global__ __launch_bounds__(256) void k_hub_finalize(SweepPlan pl, const uint8_
                                                       uint32_t *__restrict__ Hhub,
                                                       uint8_t *__restrict__ prop, uint32_t *__restrict__ cnt,
                                                       int c, int64_t chunk_lo, int k, int pass, int store_e,
-                                                      int ntiles, uint32_t *__restrict__ tot) {
+                                                      int ncells, int cell_rows, uint32_t *__restrict__ tot) {
     const uint32_t nh = pl.ch_nh[c];
     if (blockIdx.x == gridDim.x - 1) {
         // the tiles' counts as far as they are complete, plus one for every hub
@@ -1601,12 +1618,12 @@ __global__ __launch_bounds__(256) void k_hub_finalize(SweepPlan pl, const uint8_
         const int col = threadIdx.x & (KP - 1), seg = threadIdx.x / KP;
         uint32_t sum = 0;
         if (col < k) {
-            for (int r0 = seg; r0 < ntiles; r0 += SEGS * 16) {   // 16 loads side by side
+            for (int r0 = seg; r0 < ncells; r0 += SEGS * 16) {   // 16 loads side by side
                 uint32_t x[16];
 #pragma unroll
                 for (int u = 0; u < 16; ++u) {
                     const int r = r0 + SEGS * u;
-                    x[u] = r < ntiles ? cnt[(size_t)r * k + col] : 0u;
+                    x[u] = r < ncells ? cnt[(size_t)r * k + col] : 0u;
                 }
 #pragma unroll
                 for (int u = 0; u < 16; ++u) sum += x[u];
@@ -1656,7 +1673,7 @@ __global__ __launch_bounds__(256) void k_hub_finalize(SweepPlan pl, const uint8_
         uint32_t best = (uint32_t)bj;
         if (pass == 0 && old != 0xFFu) best = old;
         prop[v - chunk_lo] = (uint8_t)best;
-        if (best != old) atomicAdd(&cnt[(size_t)((v - chunk_lo) / kAdmitTile) * k + best], 1u);   // after k_tp_score's store
+        if (best != old) atomicAdd(&cnt[(size_t)((v - chunk_lo) / cell_rows) * k + best], 1u);   // after k_tp_score's store
     }
 }
 
@@ -1675,12 +1692,15 @@ __global__ __launch_bounds__(256) void k_hub_finalize(SweepPlan pl, const uint8_
 //     k_apply_small gets an upper bound) and those of the tiles before its own -- from the coarse table
 //     k_tp_score leaves (Cnow; two tables take turns from chunk to chunk, workgroup 0 clears the other one,
 //     Cclear) and the rows of the tiles of its own coarse group.
-// cnt[tile][t]: movers to t among the tile's regular rows (from k_tp_score).
+// cnt: movers to t among the regular rows (from k_tp_score), CPT rows per tile, ncells in all.
 // ------------------------------------------------------------------------------------------------
 constexpr int kAdmitHubsMax = 512;        // hubs of a chunk
 constexpr int kAdmitTilesMax = 1024;      // tiles of a chunk
+constexpr int kAdmitGrid = 256;           // TPW, the tiles per workgroup: 4, or 2 or 1 while the workgroups stay within one per
+                                          // CU (every one of them works the hubs and the prefix out for itself).  A chunk of
+                                          // 128 tiles: 13.7 us with 4, 10.2 with 1 (k = 32)
 
-template <int KP>
+template <int KP, int TPW, int CPT>
 __global__ __launch_bounds__(kAdmitTile) void k_admit_hubs(
     uint8_t *__restrict__ Lc, const uint8_t *__restrict__ prop, int64_t chunk_lo, int64_t chunk_hi, int k,
     const uint32_t *__restrict__ cnt, int ntiles, const long long *__restrict__ room,
@@ -1688,10 +1708,10 @@ __global__ __launch_bounds__(kAdmitTile) void k_admit_hubs(
     const int32_t *__restrict__ hub_row, const uint8_t *__restrict__ hub_old, uint32_t nh,
     const uint32_t *__restrict__ Hnow,
     uint32_t *__restrict__ Hclear, uint32_t nclear, const uint32_t *__restrict__ Eold,
-    uint32_t *__restrict__ Enew, int store_e, const uint32_t *__restrict__ Cnow, uint32_t *__restrict__ Cclear) {
+    uint32_t *__restrict__ Enew, int store_e, const uint32_t *__restrict__ Cnow, uint32_t *__restrict__ Cclear,
+    int ncells) {
     static_assert(KP == 16 || KP == 32, "partitions per workgroup table");
     constexpr int nwaves = kAdmitTile / 64;
-    constexpr int TPW = kSmallApplyTiles;
     constexpr int SEGS = kAdmitTile / KP;           // threads per column of cnt
     constexpr int HPR = kAdmitTile / KP;            // hubs per round of the workgroup
     constexpr int HB = 4;                           // rounds whose loads are issued side by side
@@ -1723,36 +1743,36 @@ __global__ __launch_bounds__(kAdmitTile) void k_admit_hubs(
         // the coarse rows (kCoarseTiles tiles each) for the whole chunk and the groups before the workgroup's,
         // the tiles' own rows only inside its group: (tiles / 32 + 32) * k counts instead of tiles * k
         const int g0 = tile0 / kCoarseTiles, ng = (ntiles + kCoarseTiles - 1) / kCoarseTiles;
-        for (int r0 = seg; r0 < ng + kCoarseTiles; r0 += SEGS) {
+        for (int r0 = seg; r0 < ng + kCoarseTiles * CPT; r0 += SEGS) {
             uint32_t x = 0;
             if (r0 < ng) {
                 x = Cnow[(size_t)r0 * k + col];
                 all += x;
                 if (r0 < g0) before += x;
             } else {
-                const int r = g0 * kCoarseTiles + (r0 - ng);
-                if (r < tile0 && r < ntiles) before += cnt[(size_t)r * k + col];
+                const int r = g0 * kCoarseTiles * CPT + (r0 - ng);
+                if (r < tile0 * CPT && r < ncells) before += cnt[(size_t)r * k + col];
             }
         }
     } else if (col < k) {
-        for (int r0 = seg; r0 < ntiles; r0 += SEGS * 16) {      // (16 loads side by side: one turn when KP = 16)
+        for (int r0 = seg; r0 < ncells; r0 += SEGS * 16) {      // (16 loads side by side: one turn when KP = 16)
             uint32_t x[16];
 #pragma unroll
             for (int u = 0; u < 16; ++u) {
                 const int r = r0 + SEGS * u;
-                x[u] = r < ntiles ? cnt[(size_t)r * k + col] : 0u;
+                x[u] = r < ncells ? cnt[(size_t)r * k + col] : 0u;
             }
 #pragma unroll
             for (int u = 0; u < 16; ++u) {
                 all += x[u];
-                if (r0 + SEGS * u < tile0) before += x[u];
+                if (r0 + SEGS * u < tile0 * CPT) before += x[u];
             }
         }
     }
     uint32_t own[TPW];
 #pragma unroll
     for (int h = 0; h < TPW; ++h)
-        own[h] = (tid < k && tile0 + h < ntiles) ? cnt[(size_t)(tile0 + h) * k + tid] : 0u;
+        own[h] = tid < k ? tile_movers<CPT>(cnt, tile0 + h, k, tid, ncells) : 0u;
     long long rm0 = 0;
     if (tid < k) rm0 = room[tid];
     // the hubs this thread takes part in, HB rounds at a time: KP lanes per hub, lane j takes partition j;
@@ -1777,7 +1797,7 @@ __global__ __launch_bounds__(kAdmitTile) void k_admit_hubs(
         for (int h = 0; h < TPW; ++h) ownh[h][tid] = 0;
     }
     if (tid < TPW) s_unassigned[tid] = 0;
-    reinterpret_cast<uint32_t *>(over)[tid] = 0xFFFFFFFFu;
+    if (tid < TPW * kAdmitTile / 4) reinterpret_cast<uint32_t *>(over)[tid] = 0xFFFFFFFFu;
     if (blockIdx.x == 0) {
         for (uint32_t q = tid; q < nclear * (uint32_t)k; q += kAdmitTile) Hclear[q] = 0;
         if (Cclear)
