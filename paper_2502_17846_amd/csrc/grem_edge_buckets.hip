@@ -7,7 +7,8 @@
 // A stable counting sort by key = label[src]*k + label[dst], one workgroup per tile of the stream:
 //   k_eb_hist     keys of the tile's edges (two look-ups into a byte-per-node label table), stored as
 //                 uint16 for the second pass, and the tile's histogram over the k*k buckets in LDS
-//                 -> H[tile][bucket]
+//                 -> H[tile][bucket].  Where the table outgrows the L2 the look-ups are served from LDS instead
+//                 (k_eb_bin, k_eb_lookup, k_eb_keys: below) and k_eb_hist_keys takes the keys as they are
 //   k_eb_colsum / k_eb_bases / k_eb_colscan
 //                 exclusive prefix sums of H in bucket-major order (bucket, then tile): H[tile][bucket]
 //                 becomes the output position of the tile's first edge of that bucket
@@ -19,6 +20,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "grem.h"
 
@@ -31,6 +33,7 @@ constexpr int kEbMaxK = 128;                       // k*k*4 bytes of LDS: 64 KB 
 constexpr int64_t kEbMaxCells = (int64_t)1 << 27;  // tiles * k*k
 constexpr int64_t kEbMinTile = 4096;
 constexpr uint32_t kBadLabel = 0xFFu;
+constexpr int64_t kEbBinMinN = 1ll << 23, kEbBinMinM = 1 << 22;
 
 __global__ __launch_bounds__(256) void k_eb_zero(uint32_t* p, size_t count)
 {
@@ -38,14 +41,19 @@ __global__ __launch_bounds__(256) void k_eb_zero(uint32_t* p, size_t count)
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride) p[i] = 0u;
 }
 
-// one byte per node; labels outside [0, k) become kBadLabel
-__global__ __launch_bounds__(256) void k_eb_compact(int64_t n, const int32_t* __restrict__ labels, int32_t k, uint8_t* L8)
+// one byte per node; labels outside [0, k) become kBadLabel (*bad_labels = 1 if there are any)
+__global__ __launch_bounds__(256) void k_eb_compact(int64_t n, const int32_t* __restrict__ labels, int32_t k, uint8_t* L8,
+                                                    uint32_t* bad_labels)
 {
+    bool bad = false;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
         const int32_t l = labels[v];
-        L8[v] = (l >= 0 && l < k) ? (uint8_t)l : (uint8_t)kBadLabel;
+        const bool fits = l >= 0 && l < k;
+        L8[v] = fits ? (uint8_t)l : (uint8_t)kBadLabel;
+        bad |= !fits;
     }
+    if (bad) *bad_labels = 1u;
 }
 
 // flags[0]: an endpoint outside [0, n); flags[1]: an endpoint whose label lies outside [0, k)
@@ -144,6 +152,281 @@ __global__ __launch_bounds__(256) void k_eb_colscan(uint32_t* __restrict__ H, in
     }
 }
 
+// ---- the keys of large graphs: look-ups from LDS ------------------------------------------------------------
+//
+// A look-up in a table that outgrows the L2 is a 64-byte miss: 55 G/s at 111M nodes, 57 ms for the two ends of 1.6e9
+// edges.  Instead, a batch of edges at a time:
+//   k_eb_bin      a workgroup sorts the ends of its tile of edges by bins of 2^cb nodes, in LDS, and writes them run by
+//                 run to the bins' lists (the node's place in its bin), beside where its runs went and, per edge,
+//                 the places of its two ends in the sorted tile
+//   k_eb_lookup   a bin's labels in LDS, its list streamed through them: a byte per entry
+//   k_eb_keys     a tile's runs of labels collected in LDS; every edge picks its two up: its key
+// All of it is long streams: 27 bytes per end where the miss moves 64.  (k_eb_bin_count and k_eb_bin_scan beforehand: the
+// lists' sizes for every batch, and the range check of the endpoints; ends out of range count as the last
+// node.)
+// 1.6e9 edges of 111M nodes: 57.4 ms with look-ups in the table, 27.5 in these kernels.  Below 8M nodes the table's
+// look-ups are the faster way (4M nodes, 50M edges: 1.35 ms against 1.5 to 1.7).
+constexpr int kEbBins = 1024;
+constexpr int kEbBinThreads = 1024;
+constexpr int kEbBinTile = 8192;                  // edges per workgroup (16,384 and one workgroup per CU: 47.5 ms a call for 46)
+constexpr int kEbBinPer = kEbBinTile / kEbBinThreads;
+
+// exclusive prefix of x over kEbBinThreads threads; wsum: 16 words of LDS
+__device__ __forceinline__ uint32_t eb_block_exclusive(uint32_t x, uint32_t* wsum)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t incl = x;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(incl, o);
+        if (lane >= o) incl += y;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    uint32_t before = incl - x;
+    for (int q = 0; q < wave; ++q) before += wsum[q];
+    return before;
+}
+
+__device__ __forceinline__ uint32_t eb_end(int32_t id, uint32_t n) { return (uint32_t)id < n ? (uint32_t)id : n - 1u; }
+
+// table[batch][bin]: ends of the batch's edges
+__global__ __launch_bounds__(kEbBinThreads) void k_eb_bin_count(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                                                                int64_t m, int64_t batch, uint32_t n, int cb,
+                                                                uint32_t* __restrict__ table, uint32_t* flags)
+{
+    __shared__ uint32_t hist[kEbBins];
+    const int64_t lo = (int64_t)blockIdx.y * batch, hi = lo + batch < m ? lo + batch : m;
+    hist[threadIdx.x] = 0u;
+    __syncthreads();
+    bool bad = false;
+    for (int64_t t = lo + (int64_t)blockIdx.x * kEbBinTile; t < hi; t += (int64_t)gridDim.x * kEbBinTile) {
+        int32_t s[kEbBinPer], d[kEbBinPer];
+#pragma unroll
+        for (int u = 0; u < kEbBinPer; ++u) {
+            const int64_t e = t + u * kEbBinThreads + threadIdx.x;
+            s[u] = e < hi ? src[e] : 0;
+            d[u] = e < hi ? dst[e] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kEbBinPer; ++u) {
+            if (t + u * kEbBinThreads + threadIdx.x >= hi) continue;
+            bad |= (uint32_t)s[u] >= n || (uint32_t)d[u] >= n;
+            atomicAdd(&hist[eb_end(s[u], n) >> cb], 1u);
+            atomicAdd(&hist[eb_end(d[u], n) >> cb], 1u);
+        }
+    }
+    if (bad) flags[0] = 1u;
+    __syncthreads();
+    const uint32_t c = hist[threadIdx.x];
+    if (c) atomicAdd(&table[(size_t)blockIdx.y * (kEbBins + 1) + threadIdx.x], c);
+}
+
+// sizes -> starts (a workgroup per batch); cursors: a second copy, which k_eb_bin moves on
+__global__ __launch_bounds__(kEbBins) void k_eb_bin_scan(uint32_t* table, uint32_t* cursors)
+{
+    __shared__ uint32_t wsum[16];
+    uint32_t* row = table + (size_t)blockIdx.x * (kEbBins + 1);
+    const uint32_t c = row[threadIdx.x];
+    const uint32_t excl = eb_block_exclusive(c, wsum);
+    row[threadIdx.x] = excl;
+    cursors[(size_t)blockIdx.x * kEbBins + threadIdx.x] = excl;
+    if (threadIdx.x == kEbBins - 1) row[kEbBins] = excl + c;
+}
+
+// runs[tile][bin]: (where the tile's run of the bin went, its start in the sorted tile); places[edge of the batch]: those of
+// its two ends in the sorted tile, 16 bits each
+template <typename Item>
+__global__ __launch_bounds__(kEbBinThreads, 8) void k_eb_bin(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                                                          int64_t count, uint32_t n, int cb, int nbins,
+                                                          uint32_t* __restrict__ cursors, Item* __restrict__ lists,
+                                                          uint2* __restrict__ runs, uint32_t* __restrict__ places)
+{
+    extern __shared__ uint32_t items[];            // 2 * kEbBinTile: place in bin, bin above it
+    __shared__ uint32_t hist[kEbBins], start[kEbBins], at[kEbBins], wsum[16];
+    const int tid = threadIdx.x;
+    const int64_t lo = (int64_t)blockIdx.x * kEbBinTile;
+    hist[tid] = 0u;
+    uint32_t a[kEbBinPer], b[kEbBinPer];
+#pragma unroll
+    for (int u = 0; u < kEbBinPer; ++u) {
+        const int64_t e = lo + u * kEbBinThreads + tid;
+        a[u] = e < count ? eb_end(__builtin_nontemporal_load(src + e), n) : 0u;
+        b[u] = e < count ? eb_end(__builtin_nontemporal_load(dst + e), n) : 0u;
+    }
+    __syncthreads();
+    uint32_t rank[kEbBinPer];                      // of the two ends among their bins, 16 bits each (below 16,384)
+#pragma unroll
+    for (int u = 0; u < kEbBinPer; ++u) {
+        rank[u] = 0u;
+        if (lo + u * kEbBinThreads + tid < count) {
+            rank[u] = atomicAdd(&hist[a[u] >> cb], 1u);
+            rank[u] |= atomicAdd(&hist[b[u] >> cb], 1u) << 16;
+        }
+    }
+    __syncthreads();
+    const uint32_t c = hist[tid];
+    const uint32_t excl = eb_block_exclusive(c, wsum);
+    start[tid] = excl;
+    if (tid < nbins) {
+        const uint32_t to = c ? atomicAdd(&cursors[tid], c) : 0u;
+        at[tid] = to - excl;
+        runs[(size_t)blockIdx.x * nbins + tid] = make_uint2(to, excl);
+    }
+    __syncthreads();
+    const uint32_t mask = (1u << cb) - 1u;
+#pragma unroll
+    for (int u = 0; u < kEbBinPer; ++u) {
+        const int64_t e = lo + u * kEbBinThreads + tid;
+        if (e >= count) continue;
+        const uint32_t pa = start[a[u] >> cb] + (rank[u] & 0xFFFFu), pb = start[b[u] >> cb] + (rank[u] >> 16);
+        items[pa] = a[u];
+        items[pb] = b[u];
+        places[e] = pa | (pb << 16);
+    }
+    __syncthreads();
+    const uint32_t total = start[kEbBins - 1] + hist[kEbBins - 1];
+    for (uint32_t i = tid; i < total; i += kEbBinThreads) {
+        const uint32_t x = items[i];
+        lists[at[x >> cb] + i] = (Item)(x & mask);
+    }
+}
+
+// a part of a bin's list: the labels, one byte per entry.  PACK: two labels per byte in LDS (k <= 16; a node without a
+// valid label is then looked for in the table, if the graph has any: *bad_labels).
+template <typename Item, bool PACK>
+__global__ __launch_bounds__(kEbBinThreads) void k_eb_lookup(const uint8_t* __restrict__ L8, int64_t n, int cb, int parts,
+                                                             const uint32_t* __restrict__ row, const Item* __restrict__ lists,
+                                                             uint8_t* __restrict__ labels, const uint32_t* __restrict__ bad_labels,
+                                                             uint32_t* flags)
+{
+    extern __shared__ uint32_t tab[];              // 2^cb labels, a byte or half a byte each
+    const int tid = threadIdx.x;
+    const uint32_t bin = blockIdx.x / (unsigned)parts, part = blockIdx.x % (unsigned)parts;
+    const uint32_t i0 = row[bin], len = row[bin + 1] - i0;
+    // (parts meet at multiples of four entries)
+    const uint32_t first = (uint32_t)((uint64_t)len * part / parts), last = (uint32_t)((uint64_t)len * (part + 1) / parts);
+    auto edge = [&](uint32_t x) { const uint32_t y = (i0 + x) & ~3u; return y < i0 ? i0 : y; };
+    const uint32_t b = part == 0 ? i0 : edge(first), e = part + 1 == (uint32_t)parts ? i0 + len : edge(last);
+    if (b >= e) return;
+    const int64_t v0 = (int64_t)bin << cb;
+    const uint32_t nodes = n - v0 < (1ll << cb) ? (uint32_t)(n - v0) : 1u << cb;
+    // (L8 is 256-byte aligned and padded to that: whole words)
+    const uint32_t* l4 = reinterpret_cast<const uint32_t*>(L8 + v0);
+    if (PACK) {
+        for (uint32_t w = tid; w < (nodes + 7) / 8; w += kEbBinThreads) {
+            const uint32_t x = l4[2 * w], y = l4[2 * w + 1];
+            const uint32_t p = (x & 15u) | ((x >> 4) & 0xF0u) | ((x >> 8) & 0xF00u) | ((x >> 12) & 0xF000u);
+            const uint32_t q = (y & 15u) | ((y >> 4) & 0xF0u) | ((y >> 8) & 0xF00u) | ((y >> 12) & 0xF000u);
+            tab[w] = p | (q << 16);
+        }
+    } else {
+        for (uint32_t w = tid; w < (nodes + 3) / 4; w += kEbBinThreads) tab[w] = l4[w];
+    }
+    const bool some_bad = *bad_labels != 0u;
+    __syncthreads();
+    const uint8_t* tb = reinterpret_cast<const uint8_t*>(tab);
+    bool bad = false;
+    auto look = [&](uint32_t x) -> uint32_t {
+        if (some_bad) bad |= L8[v0 + x] == kBadLabel;
+        return PACK ? ((uint32_t)tb[x >> 1] >> (4 * (x & 1u))) & 15u : (uint32_t)tb[x];
+    };
+    // four entries per thread and turn, from a multiple of four on; single ones before and after
+    const uint32_t b4 = (b + 3u) & ~3u, e4 = e & ~3u;
+    for (uint32_t i = b + tid; i < (b4 < e ? b4 : e); i += kEbBinThreads) labels[i] = (uint8_t)look(lists[i]);
+    if (b4 < e) for (uint32_t i = (e4 > b4 ? e4 : b4) + tid; i < e; i += kEbBinThreads) labels[i] = (uint8_t)look(lists[i]);
+    struct alignas(4 * sizeof(Item)) Four { Item x[4]; };
+    constexpr int U = 4;
+    for (uint32_t i = b4 + 4 * tid; i < e4; i += 4 * kEbBinThreads * U) {
+        Four f[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i + 4 * kEbBinThreads * u < e4) f[u] = *reinterpret_cast<const Four*>(lists + i + 4 * kEbBinThreads * u);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i + 4 * kEbBinThreads * u < e4)
+                *reinterpret_cast<uint32_t*>(labels + i + 4 * kEbBinThreads * u) =
+                    look(f[u].x[0]) | (look(f[u].x[1]) << 8) | (look(f[u].x[2]) << 16) | (look(f[u].x[3]) << 24);
+    }
+    if (bad) flags[1] = 1u;
+}
+
+// The tile's labels back in its sorted order (sixteen lanes per run, some 20 to 80 bytes each), then the edges' keys.
+__global__ __launch_bounds__(kEbBinThreads, 8) void k_eb_keys(int64_t count, int nbins, int32_t k, const uint2* __restrict__ runs,
+                                                           const uint32_t* __restrict__ places, const uint8_t* __restrict__ labels,
+                                                           uint16_t* __restrict__ key16)
+{
+    __shared__ uint8_t lab[2 * kEbBinTile];
+    const int tid = threadIdx.x, l = tid & 15;
+    const int64_t lo = (int64_t)blockIdx.x * kEbBinTile;
+    const uint32_t total = 2u * (uint32_t)(count - lo < kEbBinTile ? count - lo : kEbBinTile);
+    uint32_t at[kEbBinPer];
+#pragma unroll
+    for (int u = 0; u < kEbBinPer; ++u) {
+        const int64_t e = lo + u * kEbBinThreads + tid;
+        at[u] = e < count ? __builtin_nontemporal_load(places + e) : 0u;
+    }
+    const uint2* own = runs + (size_t)blockIdx.x * nbins;
+    constexpr int U = 2, groups = kEbBinThreads / 16;
+    for (int b0 = tid / 16; b0 < nbins; b0 += groups * U) {
+        uint2 r[U];
+        uint32_t end[U], x[U][2];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int b = b0 + u * groups;
+            r[u] = b < nbins ? own[b] : make_uint2(0u, 0u);
+            end[u] = b + 1 < nbins ? own[b + 1].y : b < nbins ? total : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint32_t i = r[u].y + l + 16 * h;
+                x[u][h] = i < end[u] ? (uint32_t)labels[r[u].x + (i - r[u].y)] : 0u;
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint32_t i = r[u].y + l + 16 * h;
+                if (i < end[u]) lab[i] = (uint8_t)x[u][h];
+            }
+            for (uint32_t i = r[u].y + l + 32; i < end[u]; i += 16) lab[i] = labels[r[u].x + (i - r[u].y)];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kEbBinPer; ++u) {
+        const int64_t e = lo + u * kEbBinThreads + tid;
+        if (e >= count) continue;
+        const uint32_t ls = lab[at[u] & 0xFFFFu], ld = lab[at[u] >> 16];
+        // (an end without a valid label has been flagged: its key is never used, but stays in range)
+        key16[e] = ls < (uint32_t)k && ld < (uint32_t)k ? (uint16_t)(ls * (uint32_t)k + ld) : (uint16_t)0;
+    }
+}
+
+// H[tile][bucket] from the keys
+__global__ __launch_bounds__(kEbBlock) void k_eb_hist_keys(int64_t m, int64_t tile, int32_t k2, const uint16_t* __restrict__ key16,
+                                                           uint32_t* __restrict__ H)
+{
+    extern __shared__ uint32_t hist[];
+    for (int b = threadIdx.x; b < k2; b += kEbBlock) hist[b] = 0u;
+    __syncthreads();
+    const int64_t lo = (int64_t)blockIdx.x * tile, hi = lo + tile < m ? lo + tile : m;
+    constexpr int U = 8;
+    for (int64_t e = lo + threadIdx.x; e < hi; e += kEbBlock * U) {
+        uint32_t key[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) key[u] = e + u * kEbBlock < hi ? (uint32_t)key16[e + u * kEbBlock] : 0xFFFFFFFFu;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (key[u] != 0xFFFFFFFFu) atomicAdd(&hist[key[u]], 1u);
+    }
+    __syncthreads();
+    uint32_t* row = H + (size_t)blockIdx.x * (size_t)k2;
+    for (int b = threadIdx.x; b < k2; b += kEbBlock) row[b] = hist[b];
+}
+
 __global__ __launch_bounds__(kEbBlock) void k_eb_scatter(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                                                          int64_t m, int64_t tile, const uint16_t* __restrict__ key16,
                                                          int32_t k2, int32_t key_bits, const uint32_t* __restrict__ H,
@@ -185,83 +468,110 @@ __global__ __launch_bounds__(kEbBlock) void k_eb_scatter(const int32_t* __restri
 }
 
 // The same placement for tiles of kEbMinTile edges and at most kEbLdsBuckets buckets, with the tile sorted
-// in LDS first so that the output is written in whole runs: each of the four waves owns a quarter of the
+// in LDS first so that the output is written in whole runs: each of the eight waves owns an eighth of the
 // tile (consecutive stream positions), counts it, the counts become per-wave cursors into the tile's sorted
 // order (bucket, then wave, then stream position = stable), every wave places its edges into LDS without
 // waiting for the others, and the sorted tile is written out with consecutive lanes on consecutive
-// addresses of a bucket's run.
+// addresses of a bucket's run.  Bound by latency under its barriers: with four waves to a workgroup (twelve per CU) and
+// one thread adding up the 256 partial counts 1.6e9 edges took 18.1 ms, 11.4 to 13 with eight and a wave's prefix sums.
 constexpr int kEbLdsBuckets = 1024;
-constexpr int kEbSeg = (int)(kEbMinTile / kEbWaves);
+constexpr int kEbScatterThreads = 512;
+constexpr int kEbScatterWaves = kEbScatterThreads / 64;
+constexpr int kEbSeg = (int)(kEbMinTile / kEbScatterWaves);
+constexpr int kEbSegTurns = kEbSeg / 64;
+inline size_t eb_scatter_lds_bytes(int32_t k2) { return (size_t)kEbMinTile * 10 + (size_t)k2 * (4 + 2 + 2 * kEbScatterWaves) + 16; }
 
-__global__ __launch_bounds__(kEbBlock) void k_eb_scatter_lds(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                                             int64_t m, const uint16_t* __restrict__ key16, int32_t k2,
-                                                             int32_t key_bits, const uint32_t* __restrict__ H,
-                                                             int32_t* __restrict__ out_src, int32_t* __restrict__ out_dst)
+__global__ __launch_bounds__(kEbScatterThreads) void k_eb_scatter_lds(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                                                                      int64_t m, const uint16_t* __restrict__ key16, int32_t k2,
+                                                                      int32_t key_bits, const uint32_t* __restrict__ H,
+                                                                      int32_t* __restrict__ out_src, int32_t* __restrict__ out_dst)
 {
     extern __shared__ uint32_t lds[];
     int32_t* ssrc = (int32_t*)lds;                          // kEbMinTile
     int32_t* sdst = ssrc + kEbMinTile;                      // kEbMinTile
     uint32_t* gstart = (uint32_t*)(sdst + kEbMinTile);      // k2: output position of the tile's first edge of a bucket
-    uint32_t* lstart = gstart + k2;                         // k2: the same inside the sorted tile
-    uint32_t* curw = lstart + k2;                           // kEbWaves * k2: counts, then cursors, per wave
-    uint16_t* skey = (uint16_t*)(curw + kEbWaves * k2);     // kEbMinTile
-    __shared__ uint32_t tsum[kEbBlock];
+    uint16_t* lstart = (uint16_t*)(gstart + k2);            // k2: the same inside the sorted tile
+    uint16_t* curw = lstart + k2;                           // kEbScatterWaves * k2: counts, then cursors, per wave
+    uint16_t* skey = curw + kEbScatterWaves * k2;           // kEbMinTile
+    __shared__ uint32_t wsum[kEbScatterWaves];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t lo = (int64_t)blockIdx.x * kEbMinTile, hi = lo + kEbMinTile < m ? lo + kEbMinTile : m;
     const int count = (int)(hi - lo);
     const uint32_t* row = H + (size_t)blockIdx.x * (size_t)k2;
-    for (int b = threadIdx.x; b < k2; b += kEbBlock) gstart[b] = row[b];
-    for (int b = threadIdx.x; b < kEbWaves * k2; b += kEbBlock) curw[b] = 0u;
-    __syncthreads();
-    // counts of the wave's quarter
+    // the wave's edges, kEbSegTurns per lane, requested at once: the keys are needed twice, the ids at the end
     const int seg0 = wave * kEbSeg, seg1 = seg0 + kEbSeg < count ? seg0 + kEbSeg : count;
-    uint32_t* mine = curw + wave * k2;
-    for (int p = seg0 + lane; p < seg1; p += 64) atomicAdd(&mine[key16[lo + p]], 1u);
-    __syncthreads();
-    // exclusive sums over (bucket, wave): a thread owns k2 / kEbBlock consecutive buckets (at least one)
-    const int per = (k2 + kEbBlock - 1) / kEbBlock;
-    const int b0 = threadIdx.x * per, b1 = b0 + per < k2 ? b0 + per : k2;
-    uint32_t own = 0;
-    for (int b = b0; b < b1; ++b)
-        for (int w = 0; w < kEbWaves; ++w) own += curw[w * k2 + b];
-    tsum[threadIdx.x] = own;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t run = 0;
-        for (int t = 0; t < kEbBlock; ++t) { const uint32_t v = tsum[t]; tsum[t] = run; run += v; }
+    uint32_t key[kEbSegTurns];
+    int32_t s[kEbSegTurns], d[kEbSegTurns];
+#pragma unroll
+    for (int u = 0; u < kEbSegTurns; ++u) {
+        const int p = seg0 + u * 64 + lane;
+        key[u] = p < seg1 ? (uint32_t)key16[lo + p] : 0u;
     }
-    __syncthreads();
-    uint32_t run = tsum[threadIdx.x];
-    for (int b = b0; b < b1; ++b) {
-        lstart[b] = run;
-        for (int w = 0; w < kEbWaves; ++w) { const uint32_t c = curw[w * k2 + b]; curw[w * k2 + b] = run; run += c; }
+#pragma unroll
+    for (int u = 0; u < kEbSegTurns; ++u) {
+        const int p = seg0 + u * 64 + lane;
+        s[u] = p < seg1 ? __builtin_nontemporal_load(src + lo + p) : 0;
+        d[u] = p < seg1 ? __builtin_nontemporal_load(dst + lo + p) : 0;
     }
+    for (int b = threadIdx.x; b < k2; b += kEbScatterThreads) gstart[b] = row[b];
+    for (int b = threadIdx.x; b < kEbScatterWaves * k2; b += kEbScatterThreads) curw[b] = 0;
     __syncthreads();
-    // every wave places its quarter, 64 edges at a time in stream order
+    // counts of the wave's eighth: the first lane of those with equal keys adds them up (a wave's own row of curw: no
+    // atomics; the ranks inside the 64 are kept for the placement)
+    uint16_t* mine = curw + wave * k2;
     const u64 below = (1ull << lane) - 1ull;
-    for (int base = seg0; base < seg1; base += 64) {
-        const int p = base + lane;
-        const bool valid = p < seg1;
-        uint32_t key = 0u;
-        int32_t s = 0, d = 0;
-        if (valid) { key = key16[lo + p]; s = src[lo + p]; d = dst[lo + p]; }
+    uint32_t rank[kEbSegTurns];                             // rank | number of equal keys << 8 | first such lane << 16
+#pragma unroll
+    for (int u = 0; u < kEbSegTurns; ++u) {
+        const bool valid = seg0 + u * 64 + lane < seg1;
         u64 same = __ballot(valid);
         for (int bit = 0; bit < key_bits; ++bit) {
-            const bool one = (key >> bit) & 1u;
+            const bool one = (key[u] >> bit) & 1u;
             const u64 b = __ballot(one);
             same &= one ? b : ~b;
         }
-        const uint32_t rank = __popcll(same & below);
-        uint32_t first = 0u;
-        if (valid && rank == 0u) { first = mine[key]; mine[key] = first + (uint32_t)__popcll(same); }
-        const int leader = valid ? __builtin_ctzll(same) : lane;
-        const uint32_t pos = __shfl(first, leader) + rank;
-        if (valid) { ssrc[pos] = s; sdst[pos] = d; skey[pos] = (uint16_t)key; }
+        const uint32_t r = (uint32_t)__popcll(same & below), n = (uint32_t)__popcll(same);
+        rank[u] = r | (n << 8) | ((uint32_t)(valid ? __builtin_ctzll(same) : lane) << 16);
+        if (valid && r == 0u) mine[key[u]] = (uint16_t)(mine[key[u]] + n);
     }
     __syncthreads();
-    for (int p = threadIdx.x; p < count; p += kEbBlock) {
-        const uint32_t key = skey[p];
-        const uint32_t at = gstart[key] + ((uint32_t)p - lstart[key]);
+    // exclusive sums over (bucket, wave): a thread owns up to kEbLdsBuckets / kEbScatterThreads consecutive buckets
+    const int per = (k2 + kEbScatterThreads - 1) / kEbScatterThreads;
+    const int b0 = threadIdx.x * per, b1 = b0 + per < k2 ? b0 + per : k2;
+    uint32_t own = 0;
+    for (int b = b0; b < b1; ++b)
+#pragma unroll
+        for (int w = 0; w < kEbScatterWaves; ++w) own += curw[w * k2 + b];
+    uint32_t incl = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(incl, o);
+        if (lane >= o) incl += y;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    uint32_t run = incl - own;
+    for (int w = 0; w < wave; ++w) run += wsum[w];
+    for (int b = b0; b < b1; ++b) {
+        lstart[b] = (uint16_t)run;
+#pragma unroll
+        for (int w = 0; w < kEbScatterWaves; ++w) { const uint32_t c = curw[w * k2 + b]; curw[w * k2 + b] = (uint16_t)run; run += c; }
+    }
+    __syncthreads();
+    // every wave places its eighth, 64 edges at a time in stream order
+#pragma unroll
+    for (int u = 0; u < kEbSegTurns; ++u) {
+        const bool valid = seg0 + u * 64 + lane < seg1;
+        const uint32_t r = rank[u] & 0xFFu, n = (rank[u] >> 8) & 0xFFu;
+        uint32_t first = 0u;
+        if (valid && r == 0u) { first = mine[key[u]]; mine[key[u]] = (uint16_t)(first + n); }
+        const uint32_t pos = __shfl(first, (int)(rank[u] >> 16)) + r;
+        if (valid) { ssrc[pos] = s[u]; sdst[pos] = d[u]; skey[pos] = (uint16_t)key[u]; }
+    }
+    __syncthreads();
+    for (int p = threadIdx.x; p < count; p += kEbScatterThreads) {
+        const uint32_t kk = skey[p];
+        const uint32_t at = gstart[kk] + ((uint32_t)p - lstart[kk]);
         out_src[at] = ssrc[p];
         out_dst[at] = sdst[p];
     }
@@ -295,8 +605,23 @@ extern "C" int grem_edge_buckets(const int32_t* src, const int32_t* dst, int64_t
     auto carve = [&](size_t bytes) { const size_t at = off; off += eb_align(bytes); return at; };
     const size_t o_flags = carve(256), o_l8 = carve((size_t)n), o_key = carve((size_t)m * 2);
     const size_t o_h = carve((size_t)tiles * k2 * 4), o_part = carve((size_t)k2 * S * 4);
+    // the binned look-ups, where the label table outgrows the L2 and a bin's labels fit LDS; without the memory for their
+    // lists the look-ups go to the table
+    const int cb = n <= (int64_t)kEbBins << 16 ? 16 : 17;
+    const bool pack = k <= 16, small_item = cb == 16;      // (16 bits hold the place in a bin of 2^16 nodes)
+    bool binned = n >= kEbBinMinN && m >= kEbBinMinM && n <= (int64_t)kEbBins << 17;
+    const int nbins = (int)((n + (1ll << cb) - 1) >> cb);
+    // edges per batch: their lists, places and labels take 5 or 7 bytes per end (16M edges of 14M nodes: 5.8 ms for 200M
+    // edges instead of 6.0 with 33M; 33M of 111M nodes: 50.2 ms for 1.6e9 instead of 52.4 with 16M)
+    const int64_t most = small_item ? (int64_t)1 << 24 : (int64_t)1 << 25, batch = m < most ? m : most, batches = (m + batch - 1) / batch;
+    const int64_t bin_tiles = (batch + kEbBinTile - 1) / kEbBinTile;
+    const size_t plain_off = off;
+    const size_t o_table = carve((size_t)batches * (kEbBins + 1) * 4), o_cursors = carve((size_t)batches * kEbBins * 4);
+    const size_t o_lists = carve((size_t)batch * 2 * (small_item ? 2 : 4)), o_labels = carve((size_t)batch * 2 + 4);
+    const size_t o_runs = carve((size_t)bin_tiles * nbins * 8), o_places = carve((size_t)batch * 4);
     uint8_t* ws = nullptr;
-    if (hipMallocAsync((void**)&ws, off, stream) != hipSuccess) { (void)hipGetLastError(); return GREM_ERR_NOMEM; }
+    if (binned && hipMallocAsync((void**)&ws, off, stream) != hipSuccess) { (void)hipGetLastError(); binned = false; ws = nullptr; }
+    if (!binned && hipMallocAsync((void**)&ws, plain_off, stream) != hipSuccess) { (void)hipGetLastError(); return GREM_ERR_NOMEM; }
     auto fail = [&](int code) { (void)hipGetLastError(); (void)hipStreamSynchronize(stream); (void)hipFreeAsync(ws, stream); return code; };
     uint32_t* flags = (uint32_t*)(ws + o_flags);
     uint8_t* L8 = ws + o_l8;
@@ -306,14 +631,53 @@ extern "C" int grem_edge_buckets(const int32_t* src, const int32_t* dst, int64_t
     const size_t lds = (size_t)k2 * 4;
     if (lds > 48 * 1024) {
         if (hipFuncSetAttribute((const void*)k_eb_hist, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+            hipFuncSetAttribute((const void*)k_eb_hist_keys, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
             hipFuncSetAttribute((const void*)k_eb_scatter, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return fail(GREM_ERR_HIP);
     }
     auto grid = [](int64_t items, int64_t cap) { int64_t g = (items + 255) / 256; if (g < 1) g = 1; if (g > cap) g = cap; return (int)g; };
     hipLaunchKernelGGL(k_eb_zero, dim3(1), dim3(256), 0, stream, flags, (size_t)64);
     uint32_t host_flags[2] = {0, 0};
-    hipLaunchKernelGGL(k_eb_compact, dim3(grid(n, 16384)), dim3(256), 0, stream, n, labels, k, L8);
-    hipLaunchKernelGGL(k_eb_hist, dim3((unsigned)tiles), dim3(kEbBlock), lds, stream, src, dst, m, (uint32_t)n, tile, L8, k, key16, H, flags);
+    hipLaunchKernelGGL(k_eb_compact, dim3(grid(n, 16384)), dim3(256), 0, stream, n, labels, k, L8, flags + 2);
+    if (binned) {
+        uint32_t *table = (uint32_t*)(ws + o_table), *cursors = (uint32_t*)(ws + o_cursors), *places = (uint32_t*)(ws + o_places);
+        uint8_t* found = ws + o_labels;
+        uint2* runs = (uint2*)(ws + o_runs);
+        const size_t items_lds = (size_t)kEbBinTile * 8, tab_lds = pack ? (size_t)1 << (cb - 1) : (size_t)1 << cb;
+        const int parts = nbins >= 1024 ? 1 : (1024 + nbins - 1) / nbins;
+        hipLaunchKernelGGL(k_eb_zero, dim3(256), dim3(256), 0, stream, table, (size_t)batches * (kEbBins + 1));
+        hipLaunchKernelGGL(k_eb_bin_count, dim3((unsigned)((bin_tiles + 7) / 8), (unsigned)batches), dim3(kEbBinThreads), 0, stream, src, dst, m, batch,
+                           (uint32_t)n, cb, table, flags);
+        hipLaunchKernelGGL(k_eb_bin_scan, dim3((unsigned)batches), dim3(kEbBins), 0, stream, table, cursors);
+        auto run = [&](auto item, auto packed) {
+            using Item = decltype(item);
+            constexpr bool PACK = decltype(packed)::value;
+            if (hipFuncSetAttribute((const void*)k_eb_bin<Item>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)items_lds) != hipSuccess ||
+                hipFuncSetAttribute((const void*)k_eb_lookup<Item, PACK>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)tab_lds) != hipSuccess)
+                return false;
+            Item* lists = (Item*)(ws + o_lists);
+            for (int64_t i = 0; i < batches; ++i) {
+                const int64_t lo = i * batch, count = m - lo < batch ? m - lo : batch;
+                const unsigned tiles_now = (unsigned)((count + kEbBinTile - 1) / kEbBinTile);
+                hipLaunchKernelGGL((k_eb_bin<Item>), dim3(tiles_now), dim3(kEbBinThreads), items_lds, stream, src + lo, dst + lo, count,
+                                   (uint32_t)n, cb, nbins, cursors + (size_t)i * kEbBins, lists, runs, places);
+                hipLaunchKernelGGL((k_eb_lookup<Item, PACK>), dim3((unsigned)(nbins * parts)), dim3(kEbBinThreads), tab_lds, stream,
+                                   (const uint8_t*)L8, n, cb, parts, (const uint32_t*)(table + (size_t)i * (kEbBins + 1)), (const Item*)lists,
+                                   found, (const uint32_t*)(flags + 2), flags);
+                hipLaunchKernelGGL(k_eb_keys, dim3(tiles_now), dim3(kEbBinThreads), 0, stream, count, nbins, k, (const uint2*)runs,
+                                   (const uint32_t*)places, (const uint8_t*)found, key16 + lo);
+            }
+            return true;
+        };
+        bool ok;
+        if (small_item) ok = pack ? run(uint16_t{}, std::true_type{}) : run(uint16_t{}, std::false_type{});
+        else ok = pack ? run(uint32_t{}, std::true_type{}) : run(uint32_t{}, std::false_type{});
+        if (!ok) return fail(GREM_ERR_HIP);
+        hipLaunchKernelGGL(k_eb_hist_keys, dim3((unsigned)tiles), dim3(kEbBlock), lds, stream, m, tile, k2, (const uint16_t*)key16, H);
+    } else {
+        hipLaunchKernelGGL(k_eb_hist, dim3((unsigned)tiles), dim3(kEbBlock), lds, stream, src, dst, m, (uint32_t)n, tile, L8, k, key16, H,
+                           flags);
+    }
     if (hipMemcpyAsync(host_flags, flags, sizeof(host_flags), hipMemcpyDeviceToHost, stream) != hipSuccess ||
         hipStreamSynchronize(stream) != hipSuccess)
         return fail(GREM_ERR_HIP);
@@ -323,10 +687,10 @@ extern "C" int grem_edge_buckets(const int32_t* src, const int32_t* dst, int64_t
     hipLaunchKernelGGL(k_eb_bases, dim3(1), dim3(1024), 0, stream, partial, cells, k2, S, m, bucket_offsets);
     hipLaunchKernelGGL(k_eb_colscan, dim3(grid(cells, 1 << 20)), dim3(256), 0, stream, H, tiles, k2, S, seg_len, partial);
     if (tile == kEbMinTile && k2 <= kEbLdsBuckets) {
-        const size_t lds2 = (size_t)kEbMinTile * 10 + (size_t)k2 * 4 * (2 + kEbWaves);
+        const size_t lds2 = eb_scatter_lds_bytes(k2);
         if (hipFuncSetAttribute((const void*)k_eb_scatter_lds, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2) != hipSuccess)
             return fail(GREM_ERR_HIP);
-        hipLaunchKernelGGL(k_eb_scatter_lds, dim3((unsigned)tiles), dim3(kEbBlock), lds2, stream, src, dst, m, key16, k2, key_bits, H,
+        hipLaunchKernelGGL(k_eb_scatter_lds, dim3((unsigned)tiles), dim3(kEbScatterThreads), lds2, stream, src, dst, m, key16, k2, key_bits, H,
                            out_src, out_dst);
     } else {
         hipLaunchKernelGGL(k_eb_scatter, dim3((unsigned)tiles), dim3(kEbBlock), lds, stream, src, dst, m, tile, key16, k2, key_bits, H,
