@@ -469,9 +469,9 @@ int build_plan(PlanData &P, const RowT *rowptr, const int32_t *colidx, int64_t n
     // ---- stage 3: shapes of the re-layout kernels, then the tables and streams
     // step 1 collects a unit's tuples in LDS: cut the slices (shares) in as many parts as it takes for
     // the largest to fit, two workgroups per CU
-    constexpr size_t kGroupLds = 79 * 1024, kPlaceLds = 52 * 1024;
+    constexpr size_t kGroupLds = 79 * 1024;
     auto group_fixed = [&](bool share, int np) {
-        return (tp_source_words(share, np, share_hubs) + (size_t)geo.nblk + (size_t)geo.ngroups + 1 + kTpThreads / 64) * 4;
+        return tp_group_words(share, np, share_hubs, geo.nblk, geo.ngroups) * 4;
     };
     auto group_cap = [&](bool share, int np) {
         const size_t fixed = group_fixed(share, np);
@@ -543,22 +543,25 @@ int build_plan(PlanData &P, const RowT *rowptr, const int32_t *colidx, int64_t n
     const uint32_t capR = group_cap(false, npr), capS = group_cap(true, nps);
     const size_t groupR_lds = group_fixed(false, npr) + (size_t)capR * 4;
     const size_t groupS_lds = group_fixed(true, nps) + (size_t)capS * 4;
-    // step 2: up to 8 slices at a time
+    // step 2: up to 8 slices at a time, but no more than fit the stage at the average row's size (a batch that does
+    // not fit is halved by the kernel, at the price of setting its tables up again); four workgroups per CU, or
+    // three if two rows at a time would not fit then (111M vertices: 10.1 ms with four of 39 KB, 10.6 with three)
     const int nbg = geo.nblk < (1 << geo.gb) ? geo.nblk : (1 << geo.gb);
+    const int npm = npr > nps ? npr : nps;
+    const double per_row = (double)d.slots / ((double)geo.nch * (double)d.nr) / (double)geo.ngroups;
+    auto place_cap = [&](size_t lds, int rows) -> size_t {
+        const size_t fixed = tp_place_fixed_bytes(nbg, rows, rows * npm);
+        return lds > fixed ? (lds - fixed) / 4 : 0;
+    };
+    size_t place_room = 39 * 1024;
+    if (per_row * 2.5 > (double)place_cap(place_room, 2)) place_room = 52 * 1024;
     int batch = 8192 / nbg;
     if (batch > 8) batch = 8;
     if (batch < 1) batch = 1;
-    {
-        // ... and no more than fit the stage at the average row's size (a batch that does not fit is halved
-        // by the kernel, at the price of setting its tables up again)
-        const size_t fixed8 = tp_place_fixed_bytes(nbg, 8, 8 * (npr > nps ? npr : nps));
-        const double cap8 = kPlaceLds > fixed8 ? (double)(kPlaceLds - fixed8) / 4.0 : 0.0;
-        const double per_row = (double)d.slots / ((double)geo.nch * (double)d.nr) / (double)geo.ngroups;
-        while (batch > 1 && per_row * 1.25 * batch > cap8) --batch;
-    }
-    const int maxruns = batch * (npr > nps ? npr : nps);
+    while (batch > 1 && per_row * 1.25 * batch > (double)place_cap(place_room, batch)) --batch;
+    const int maxruns = batch * npm;
     const size_t place_fixed = tp_place_fixed_bytes(nbg, batch, maxruns);
-    const uint32_t capP = (uint32_t)(kPlaceLds > place_fixed ? (kPlaceLds - place_fixed) / 4 : 0);
+    const uint32_t capP = (uint32_t)place_cap(place_room, batch);
     const size_t place_lds = place_fixed + (size_t)capP * 4;
     L.memset(tb.cnt, 0, subs * 4);
     if (L.err || !set_lds((const void *)k_tp_group<RowT, false>, groupR_lds) ||

@@ -61,6 +61,7 @@ typedef unsigned long long u64;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x3a __attribute__((ext_vector_type(3), aligned(4)));     // 12 bytes at any 4-byte boundary
+typedef uint32_t u32x4a __attribute__((ext_vector_type(4), aligned(4)));     // 16 bytes at any 4-byte boundary
 
 struct SweepPlan {
     // per slice (global slice index gs = chunk * nsl + i)
@@ -359,7 +360,8 @@ __global__ __launch_bounds__(256) void k_plan_shares(int64_t n, int64_t chunk, i
 // column) for each, the row field being the row's index in the slice, or the hub's index among
 // the hubs the share touches.
 //   regular: rowrel[rp + 1] in LDS (rp rows per part, a power of two), entries colidx[e0 ..);
-//            rows of degree >= hub_degree are skipped
+//            rows of degree >= hub_degree are skipped.  starts: bit x - 1 is set if a row begins at entry x >= 1 of the
+//            first round, so that a lane's row is the count of the bits below it; empty: some rows have no entries
 //   share  : stream positions [a, a + len); hoff[nhs + 1] / hrow[nhs] in LDS
 struct TpEntrySource {
     const int32_t *colidx;
@@ -368,7 +370,8 @@ struct TpEntrySource {
     int64_t e0;
     uint32_t ne, hub_degree, row0;
     int rp;
-    bool has_hubs;
+    bool has_hubs, empty;
+    const u64 *starts;
     // share
     const u64 *hoff, *hrow;
     u64 a;
@@ -376,6 +379,7 @@ struct TpEntrySource {
 };
 
 constexpr int kTpBatch = 8;      // entries per thread and round
+constexpr int kTpStarts = kTpThreads * kTpBatch / 64;      // words of TpEntrySource::starts
 
 // The workgroup visits the unit's entries in rounds of kTpThreads * kTpBatch; tp_load_round gives a
 // thread its kTpBatch entries of a round (row field, column, on[u] = false: no entry), all loads and
@@ -386,30 +390,36 @@ __device__ __forceinline__ uint32_t tp_rounds(const TpEntrySource &src) {
     return (ne + kTpThreads * kTpBatch - 1) / (kTpThreads * kTpBatch);
 }
 
-template <bool SHARE>
+// a thread's place of a round without an entry (columns and positions in blocks stay below 2^31)
+constexpr uint32_t kNoEntry = 0xFFFFFFFFu;
+
+template <bool SHARE, bool ONLY>
 __device__ __forceinline__ void tp_load_round(const TpEntrySource &src, uint32_t round, uint32_t (&row)[kTpBatch],
-                                              uint32_t (&col)[kTpBatch], bool (&on)[kTpBatch]) {
+                                              uint32_t (&col)[kTpBatch]) {
     constexpr int U = kTpBatch;
-    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     constexpr int NW = kTpThreads / 64;
+    const uint32_t blk = (round * NW + (uint32_t)wave) * 64u * U;
+    if (blk >= (SHARE ? src.len : src.ne)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) { col[u] = kNoEntry; row[u] = 0; }
+        return;
+    }
     if (!SHARE) {
-        // a wavefront takes 64 * U consecutive entries: their rows span a short range, found once (two
-        // searches side by side), inside which every lane then looks for its own (U searches side by
-        // side, the same number of steps for all)
-        const int32_t *cbase = src.colidx + src.e0;
-        const uint32_t blk = (round * NW + (uint32_t)wave) * 64u * U;
+        // a wavefront takes 64 * U consecutive entries
+        const char *cbase = reinterpret_cast<const char *>(src.colidx + src.e0 + blk);
+        const uint32_t left = src.ne - blk;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t p = blk + u * 64 + lane;
-            on[u] = p < src.ne;
-            col[u] = on[u] ? (uint32_t)__builtin_nontemporal_load(cbase + p) : 0u;
-            row[u] = 0;
+            const uint32_t at = (uint32_t)(u * 64 + lane), in = at < left ? at : left - 1u;
+            col[u] = (uint32_t)__builtin_nontemporal_load(reinterpret_cast<const int32_t *>(cbase + in * 4u));
+            col[u] = at < left ? col[u] : kNoEntry;
         }
-        if (blk >= src.ne) return;
         // The row of an entry p is the largest r with rowrel[r] <= p (empty rows resolve to the last of equal
         // offsets, the one that holds p).  Lane u < U finds it for the first entry of the wavefront's u-th
-        // run of 64 entries (a binary search each, side by side); every lane then walks on from there: 64
-        // consecutive entries seldom span more than two or three rows.
+        // run of 64 entries (a binary search each, side by side).  In a unit of one round a lane adds the row starts
+        // between that entry and its own; where rows are empty (several starts at one bit), and in units of several
+        // rounds, it walks on through rowrel: 64 consecutive entries seldom span more than two or three rows.
         uint32_t first_row = 0;
         {
             const uint32_t target = blk + 64u * (uint32_t)(lane < U ? lane : 0);
@@ -418,27 +428,34 @@ __device__ __forceinline__ void tp_load_round(const TpEntrySource &src, uint32_t
                 if (src.rowrel[first_row + step] <= tc) first_row += step;
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            row[u] = (uint32_t)__builtin_amdgcn_readlane((int)first_row, u);
-            if (on[u]) {
-                const uint32_t p = blk + u * 64 + lane;
-                while (src.rowrel[row[u] + 1] <= p) ++row[u];
+        for (int u = 0; u < U; ++u) row[u] = (uint32_t)__builtin_amdgcn_readlane((int)first_row, u);
+        if (ONLY) {
+            u64 begin[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) begin[u] = src.starts[wave * U + u];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                row[u] = __builtin_amdgcn_mbcnt_hi((uint32_t)(begin[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)begin[u], row[u]));
+        }
+        if (!ONLY || src.empty) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (col[u] != kNoEntry) {
+                    const uint32_t p = blk + u * 64 + lane;
+                    while (src.rowrel[row[u] + 1] <= p) ++row[u];
+                }
             }
         }
         if (src.has_hubs) {
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (src.rowrel[row[u] + 1] - src.rowrel[row[u]] >= src.hub_degree) on[u] = false;
+                if (col[u] != kNoEntry && src.rowrel[row[u] + 1] - src.rowrel[row[u]] >= src.hub_degree) col[u] = kNoEntry;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) row[u] += src.row0;
     } else {
         // a wavefront takes 64 * U consecutive positions of the hub entry stream: the hub of the first is
         // found once, the others' hubs lie a step or two further on (hubs are long rows)
-        const uint32_t blk = (round * NW + (uint32_t)wave) * 64u * U;
-#pragma unroll
-        for (int u = 0; u < U; ++u) { on[u] = false; col[u] = 0; row[u] = 0; }
-        if (blk >= src.len) return;
         uint32_t first = 0, hi = src.nhs;
         {
             const u64 e = src.a + blk;
@@ -448,8 +465,9 @@ __device__ __forceinline__ void tp_load_round(const TpEntrySource &src, uint32_t
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const uint32_t p = blk + u * 64 + lane;
-            on[u] = p < src.len;
-            if (on[u]) {
+            col[u] = kNoEntry;
+            row[u] = 0;
+            if (p < src.len) {
                 const u64 e = src.a + p;                     // position in the chunk's hub entry stream
                 uint32_t h = first;
                 if (e >= next) {
@@ -463,8 +481,18 @@ __device__ __forceinline__ void tp_load_round(const TpEntrySource &src, uint32_t
     }
 }
 
-// Sets up the entry source of part q (of np) of slice or share (c, i) in LDS (`lds` must hold
-// kSliceRows / np + 1 u32 for a slice, or 2 * share_hubs + 1 u64 for a share); false if the unit
+// columns -> block << cb | column in block (where chunks are whole numbers of blocks that is the column itself)
+__device__ __forceinline__ void tp_block_columns(const TpTables &tb, uint32_t (&col)[kTpBatch]) {
+    if (tb.flat) return;
+#pragma unroll
+    for (int u = 0; u < kTpBatch; ++u) {
+        uint32_t low;
+        const uint32_t jb = tp_block_of(col[u], tb, &low);
+        col[u] = col[u] != kNoEntry ? (jb << tb.cb) | low : kNoEntry;
+    }
+}
+
+// Sets up the entry source of part q (of np) of slice or share (c, i) in LDS (`lds`: tp_source_words()); false if the unit
 // has no rows / does not exist.  Ends with a barrier when it returns true.
 template <typename RowT, bool SHARE>
 __device__ __forceinline__ bool tp_entry_source(const RowT *__restrict__ rowptr,
@@ -481,15 +509,29 @@ __device__ __forceinline__ bool tp_entry_source(const RowT *__restrict__ rowptr,
         const int rp = tb.prows;
         const int64_t v0 = chunk_lo + (int64_t)i * tb.srows + (int64_t)q * rp;
         if (v0 >= chunk_hi) return false;                       // part beyond the (ragged) chunk
-        uint32_t *rowrel = reinterpret_cast<uint32_t *>(lds);
+        u64 *starts = reinterpret_cast<u64 *>(lds);
+        uint32_t *empty = reinterpret_cast<uint32_t *>(starts + kTpStarts);
+        uint32_t *rowrel = empty + 2;
         const int64_t left = chunk_hi - v0;
         const int nv = left < rp ? (int)left : rp;
+        if (tid < kTpStarts) starts[tid] = 0;
+        if (tid == kTpStarts) *empty = 0;
         const int64_t e0 = (int64_t)rowptr[v0];
+        const int t0 = tid < nv ? tid : nv;
+        const uint32_t rel = (uint32_t)((int64_t)rowptr[v0 + t0] - e0);
+        __syncthreads();
         for (int t = tid; t <= rp; t += kTpThreads) {
             const int tt = t < nv ? t : nv;
-            rowrel[t] = (uint32_t)((int64_t)rowptr[v0 + tt] - e0);
+            const uint32_t x = t == tid ? rel : (uint32_t)((int64_t)rowptr[v0 + tt] - e0);
+            rowrel[t] = x;
+            if (t > 0 && t < nv && x <= (uint32_t)(64 * kTpStarts)) {
+                const uint32_t y = x - 1u, bit = 1u << (y & 31u);
+                if (x == 0 || (atomicOr(reinterpret_cast<uint32_t *>(starts) + (y >> 5), bit) & bit)) *empty = 1;
+            }
         }
         __syncthreads();
+        src->starts = starts;
+        src->empty = *empty != 0;
         src->rowrel = rowrel;
         src->e0 = e0;
         src->ne = rowrel[rp];
@@ -523,7 +565,12 @@ __device__ __forceinline__ bool tp_entry_source(const RowT *__restrict__ rowptr,
 
 // u32 words of LDS the entry source takes (even, so that what follows is 8-byte aligned)
 __device__ __host__ inline size_t tp_source_words(bool share, int np, int share_hubs) {
-    return share ? 2 * ((size_t)2 * share_hubs + 1) : (((size_t)kSliceRows / np + 2) & ~(size_t)1);
+    return share ? 2 * ((size_t)2 * share_hubs + 1) : 2 * kTpStarts + 2 + (((size_t)kSliceRows / np + 2) & ~(size_t)1);
+}
+
+// ... and the tables of k_tp_group with it, up to where the tuples are collected (16-byte aligned)
+__device__ __host__ inline size_t tp_group_words(bool share, int np, int share_hubs, int nblk, int ngroups) {
+    return (tp_source_words(share, np, share_hubs) + (size_t)nblk + (size_t)ngroups + 1 + kTpThreads / 64 + 64 + 3) & ~(size_t)3;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -536,7 +583,7 @@ __device__ __host__ inline size_t tp_source_words(bool share, int np, int share_
 // in LDS and written as one contiguous piece (a lane-by-lane scatter would cost one L2 request per
 // tuple); a unit with more than `cap` tuples writes them one by one instead.
 // U tuple: row field << (cb + gb) | block in group << cb | column in block.
-// LDS: the entry source's tables, cntf[nblk], cg[ngroups + 1], wtot[kTpThreads / 64], stage[cap]
+// LDS: the entry source's tables, cntf[nblk], cg[ngroups + 1], wtot[kTpThreads / 64], none[64], stage[cap]
 // ------------------------------------------------------------------------------------------------
 template <typename RowT, bool SHARE>
 __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_tp_group(const RowT *__restrict__ rowptr,
@@ -549,7 +596,8 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(8, 8
     uint32_t *cntf = reinterpret_cast<uint32_t *>(smem64) + tp_source_words(SHARE, np, share_hubs);   // nblk
     uint32_t *cg = cntf + tb.nblk;              // ngroups + 1: starts of the groups' runs
     uint32_t *wtot = cg + tb.ngroups + 1;       // kTpThreads / 64: scratch of the prefix sum
-    uint32_t *stage = wtot + kTpThreads / 64;   // cap
+    uint32_t *none = wtot + kTpThreads / 64;    // 64: counters of the places without an entry
+    uint32_t *stage = reinterpret_cast<uint32_t *>(smem64) + tp_group_words(SHARE, np, share_hubs, tb.nblk, tb.ngroups);   // cap
     const int tid = threadIdx.x;
     const unsigned gs = blockIdx.x / (unsigned)np;
     const int q = (int)(blockIdx.x % (unsigned)np);
@@ -574,19 +622,29 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(8, 8
     // where the unit's tuples go
     const u64 ustart = SHARE ? hub_base + range0 + src.a : range0;
     if (tid == 0) *ustart_out = ustart;
-    // a unit of one round (the usual case) keeps its entries in registers between the two phases
     const uint32_t rounds = tp_rounds<SHARE>(src);
     uint32_t row[kTpBatch], col[kTpBatch];
-    bool on[kTpBatch];
-    // (col[u] becomes block << kMaxColBits | column in block: the second phase does not work it out again)
-    for (uint32_t r = 0; r < rounds; ++r) {
-        tp_load_round<SHARE>(src, r, row, col, on);
+    // A unit of one round (the usual case) keeps its entries in registers between the two phases, and the rank of
+    // each among those of its block, which the counting returns: above the 11 bits of the row field.  Both phases
+    // are straight lines there (places without an entry count in `none`): the kernel is bound by the instructions it
+    // issues.  3.2e9 entries, units of 7,400: 15.3 ms (hub shares among them) when every lane walked to its row, the
+    // two phases both added to the counters, branch by branch, and 42 scalar registers were spilled; 12.5 now.
+    const bool only = rounds <= 1;
+    uint32_t at[kTpBatch];
+    if (only) {
+        tp_load_round<SHARE, true>(src, 0, row, col);
+        tp_block_columns(tb, col);
 #pragma unroll
-        for (int u = 0; u < kTpBatch; ++u) {
-            uint32_t low;
-            const uint32_t jb = tp_block_of(col[u], tb, &low);
-            col[u] = (jb << kMaxColBits) | low;
-            if (on[u]) atomicAdd(&cntf[jb], 1u);
+        for (int u = 0; u < kTpBatch; ++u) at[u] = atomicAdd(col[u] != kNoEntry ? cntf + (col[u] >> tb.cb) : none + lane_id(), 1u);
+#pragma unroll
+        for (int u = 0; u < kTpBatch; ++u) row[u] |= at[u] << kSliceRowBits;
+    } else {
+        for (uint32_t r = 0; r < rounds; ++r) {
+            tp_load_round<SHARE, false>(src, r, row, col);
+            tp_block_columns(tb, col);
+#pragma unroll
+            for (int u = 0; u < kTpBatch; ++u)
+                if (col[u] != kNoEntry) atomicAdd(&cntf[col[u] >> tb.cb], 1u);
         }
     }
     __syncthreads();
@@ -614,7 +672,8 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(8, 8
         if (lane == 63) wtot[wave] = inc;
         __syncthreads();
         uint32_t run = inc - sum;
-        for (int w = 0; w < wave; ++w) run += wtot[w];
+        if (wave * 64 * kPer < tb.nblk)
+            for (int w = 0; w < wave; ++w) run += wtot[w];
         const uint32_t gmask0 = (1u << tb.gb) - 1u;
 #pragma unroll
         for (int x = 0; x < kPer; ++x) {
@@ -624,43 +683,56 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(8, 8
                 if (((uint32_t)j & gmask0) == 0) cg[j >> tb.gb] = run;
             }
             run += mine[x];
+            if (j == tb.nblk - 1) cg[tb.ngroups] = run;
         }
-        if (tid == kTpThreads - 1) cg[tb.ngroups] = run;
     }
     __syncthreads();
     for (int gq = tid; gq <= tb.ngroups; gq += kTpThreads) lo_out[gq] = cg[gq];
     const uint32_t total = cg[tb.ngroups];
     const bool staged = total <= cap;
-    const uint32_t gmask = (1u << tb.gb) - 1u;
+    const uint32_t gcmask = (1u << (tb.cb + tb.gb)) - 1u;
     uint32_t *ubase = U + ustart;
-    for (uint32_t r = 0; r < rounds; ++r) {
-        if (rounds > 1) {
-            tp_load_round<SHARE>(src, r, row, col, on);
+    if (only) {
+#pragma unroll
+        for (int u = 0; u < kTpBatch; ++u) at[u] = *(col[u] != kNoEntry ? cntf + (col[u] >> tb.cb) : none + lane_id());
+#pragma unroll
+        for (int u = 0; u < kTpBatch; ++u) {
+            at[u] += row[u] >> kSliceRowBits;
+            row[u] = ((row[u] & (uint32_t)(kSliceRows - 1)) << (tb.cb + tb.gb)) | (col[u] & gcmask);
+        }
+        if (staged) {
+#pragma unroll
+            for (int u = 0; u < kTpBatch; ++u)
+                if (col[u] != kNoEntry) stage[at[u]] = row[u];
+        } else {
+#pragma unroll
+            for (int u = 0; u < kTpBatch; ++u)
+                if (col[u] != kNoEntry) ubase[at[u]] = row[u];
+        }
+    } else {
+        for (uint32_t r = 0; r < rounds; ++r) {
+            tp_load_round<SHARE, false>(src, r, row, col);
+            tp_block_columns(tb, col);
+#pragma unroll
+            for (int u = 0; u < kTpBatch; ++u) at[u] = col[u] != kNoEntry ? atomicAdd(&cntf[col[u] >> tb.cb], 1u) : 0u;
 #pragma unroll
             for (int u = 0; u < kTpBatch; ++u) {
-                uint32_t low;
-                const uint32_t jb = tp_block_of(col[u], tb, &low);
-                col[u] = (jb << kMaxColBits) | low;
-            }
-        }
-        uint32_t w[kTpBatch], tuple[kTpBatch];
-#pragma unroll
-        for (int u = 0; u < kTpBatch; ++u) {
-            const uint32_t jb = col[u] >> kMaxColBits, low = col[u] & ((1u << kMaxColBits) - 1u);
-            tuple[u] = (row[u] << (tb.cb + tb.gb)) | ((jb & gmask) << tb.cb) | low;
-            w[u] = on[u] ? atomicAdd(&cntf[jb], 1u) : 0u;
-        }
-#pragma unroll
-        for (int u = 0; u < kTpBatch; ++u) {
-            if (on[u]) {
-                if (staged) stage[w[u]] = tuple[u];
-                else ubase[w[u]] = tuple[u];
+                if (col[u] == kNoEntry) continue;
+                const uint32_t tuple = (row[u] << (tb.cb + tb.gb)) | (col[u] & gcmask);
+                if (staged) stage[at[u]] = tuple;
+                else ubase[at[u]] = tuple;
             }
         }
     }
     if (!staged) return;
     __syncthreads();
-    for (uint32_t z = tid; z < total; z += kTpThreads) __builtin_nontemporal_store(stage[z], ubase + z);
+    for (uint32_t z = 4 * tid; z < (total & ~3u); z += 4 * kTpThreads) {
+        const uint4 four = *reinterpret_cast<const uint4 *>(stage + z);
+        u32x4a out;
+        out.x = four.x; out.y = four.y; out.z = four.z; out.w = four.w;
+        __builtin_nontemporal_store(out, reinterpret_cast<u32x4a *>(ubase + z));
+    }
+    for (uint32_t z = (total & ~3u) + tid; z < total; z += kTpThreads) __builtin_nontemporal_store(stage[z], ubase + z);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -763,13 +835,12 @@ __device__ __forceinline__ void tp_unpack_columns(const uint32_t (&w)[5], uint32
 }
 
 __device__ __host__ inline size_t tp_place_fixed_bytes(int nbg, int batch, int maxruns) {
-    return ((size_t)nbg + batch + maxruns) * 8 + ((size_t)2 * maxruns + 1 + 2 * (size_t)nbg + 1 + 4 * (size_t)batch * nbg) * 4;
+    return (((size_t)nbg + batch + maxruns) * 8 + ((size_t)2 * maxruns + 1 + 2 * (size_t)nbg + 1 + 4 * (size_t)batch * nbg) * 4 + 15) & ~(size_t)15;
 }
 
-__global__ __launch_bounds__(kPlaceThreads) void k_tp_place(int64_t n, SweepPlan pl, TpTables tb,
-                                                            const uint32_t *__restrict__ U,
-                                                            uint32_t *__restrict__ T, uint16_t *__restrict__ R,
-                                                            int batch, uint32_t cap) {
+__global__ __launch_bounds__(kPlaceThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_tp_place(
+    int64_t n, SweepPlan pl, TpTables tb, const uint32_t *__restrict__ U, uint32_t *__restrict__ T, uint16_t *__restrict__ R, int batch,
+    uint32_t cap) {
     extern __shared__ u64 smem64[];
     const int g = (int)(blockIdx.x % (unsigned)tb.ngroups), c = (int)(blockIdx.x / (unsigned)tb.ngroups);
     const int jb0 = g << tb.gb;
@@ -787,7 +858,7 @@ __global__ __launch_bounds__(kPlaceThreads) void k_tp_place(int64_t n, SweepPlan
     uint32_t *sub0 = cur + batch * nbg;                         // batch * nbg  its first slot (in stage, or in the segment)
     uint32_t *sublen = sub0 + batch * nbg;                      // batch * nbg  its padded length
     uint32_t *ddv = sublen + batch * nbg;                       // batch * nbg  its start in the row stream
-    uint32_t *stage = ddv + batch * nbg;                        // cap
+    uint32_t *stage = reinterpret_cast<uint32_t *>(smem64) + tp_place_fixed_bytes(nbg, batch, maxruns) / 4;     // cap
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int kNW = kPlaceThreads / 64, kRU = 4, kXU = 3;
     const int64_t chunk_lo = (int64_t)c * tb.chunk;
@@ -934,43 +1005,41 @@ __global__ __launch_bounds__(kPlaceThreads) void k_tp_place(int64_t n, SweepPlan
             }
             __syncthreads();
             if (staged) {
-                // T: a piece per wavefront, a group of eight tuples (24 bytes) per lane; starts and lengths
-                // are multiples of 8 tuples
+                // a piece per wavefront, a group of eight tuples per lane (starts and lengths are multiples of 8): read
+                // once with two wide loads, 24 bytes to T, 16 to R.  (3.2e9 tuples: the whole kernel took 12.2 ms when T
+                // and R were written one after the other from one-word reads eight and four words apart, 10.6 then.)
                 for (int j = wave; j < nbg; j += kNW) {
                     const uint32_t a = joff[j], len8 = (joff[j + 1] - a) >> 3;
                     uint32_t *outT = T + ((tbase[j] + s0[j]) >> 3) * 6ull;
+                    // lane t: the first slot of the batch's row t in the piece
+                    const uint32_t row_first = lane < nb ? sub0[lane * nbg + j] : 0xFFFFFFFFu;
                     for (uint32_t z = lane; z < len8; z += 64) {
                         // the row of the batch whose sub-segment holds the group, and its slot in R / Lx
                         const uint32_t x = a + 8 * z;
                         int t = 0;
-                        while (t + 1 < nb && x >= sub0[(t + 1) * nbg + j]) ++t;
+                        for (int y = 1; y < nb; ++y) t += x >= (uint32_t)__builtin_amdgcn_readlane((int)row_first, y);
                         const u64 at = sbase[t] + ddv[t * nbg + j] + (x - sub0[t * nbg + j]);
-                        uint32_t col[8], w[5];
+                        const uint4 lo4 = *reinterpret_cast<const uint4 *>(stage + x), hi4 = *reinterpret_cast<const uint4 *>(stage + x + 4);
+                        const uint32_t tuple[8] = {lo4.x, lo4.y, lo4.z, lo4.w, hi4.x, hi4.y, hi4.z, hi4.w};
+                        uint32_t col[8], row[8], w[5];
 #pragma unroll
-                        for (int q = 0; q < 8; ++q) col[q] = stage[x + q] & cmask;
+                        for (int q = 0; q < 8; ++q) {
+                            const uint32_t r = tuple[q] >> tb.cb;
+                            row[q] = r >= (uint32_t)kSliceRows ? 1u : r << 5;
+                            col[q] = tuple[q] & cmask;
+                        }
                         tp_pack_columns(col, w);
                         u32x3a lo3, hi3;
                         lo3.x = (uint32_t)(at >> 3); lo3.y = w[0]; lo3.z = w[1];
                         hi3.x = w[2]; hi3.y = w[3]; hi3.z = w[4];
                         __builtin_nontemporal_store(lo3, reinterpret_cast<u32x3a *>(outT + 6 * z));
                         __builtin_nontemporal_store(hi3, reinterpret_cast<u32x3a *>(outT + 6 * z + 3));
-                    }
-                }
-                // R: a sub-segment per quarter wavefront, four tuples (8 bytes) per lane
-                for (int z = wave * 4 + (lane >> 4); z < nb * nbg; z += kNW * 4) {
-                    const uint32_t a = sub0[z], len4 = sublen[z] >> 2;
-                    uint32_t *outR = reinterpret_cast<uint32_t *>(R + sbase[z / nbg] + ddv[z]);
-                    for (uint32_t y = (uint32_t)(lane & 15); y < len4; y += 16) {
-                        uint32_t row[4];
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const uint32_t r = stage[a + 4 * y + q] >> tb.cb;
-                            row[q] = r >= (uint32_t)kSliceRows ? 1u : r << 5;
-                        }
-                        u32x2 r2;
-                        r2.x = row[0] | (row[1] << 16);
-                        r2.y = row[2] | (row[3] << 16);
-                        __builtin_nontemporal_store(r2, reinterpret_cast<u32x2 *>(outR + 2 * y));
+                        u32x4 r4;
+                        r4.x = row[0] | (row[1] << 16);
+                        r4.y = row[2] | (row[3] << 16);
+                        r4.z = row[4] | (row[5] << 16);
+                        r4.w = row[6] | (row[7] << 16);
+                        __builtin_nontemporal_store(r4, reinterpret_cast<u32x4 *>(R + at));
                     }
                 }
             } else {
