@@ -982,8 +982,9 @@ struct EsShape {
 constexpr int kBinWaveWords = 32;
 constexpr int64_t kBinMinNodes = 1ll << 22;
 constexpr int64_t kBinMaxChunks = 8192;
-// n: nodes of the run; groups: most groups side by side; ends: of a chunk's edge ends over all groups
-EsShape es_shape(int64_t n, int64_t groups, int64_t ends, int64_t chunks)
+// n: nodes of the run; groups: most groups side by side; ends: of a chunk's edge ends over all groups; bins: false
+// where there was no memory for the pairs (the counts take 8 bytes per node, the pairs up to 16)
+EsShape es_shape(int64_t n, int64_t groups, int64_t ends, int64_t chunks, bool bins = true)
 {
     EsShape s;
     // padding for every group, but no more than the nodes themselves take (a level of tiny groups goes in batches)
@@ -993,7 +994,7 @@ EsShape es_shape(int64_t n, int64_t groups, int64_t ends, int64_t chunks)
     };
     s.wpw = kBinWaveWords;
     s.awpw = n >= (1ll << 23) ? 64 : 32;
-    if (n >= kBinMinNodes && room() < (1ll << 30) && ends <= 4 * n && chunks <= kBinMaxChunks) {
+    if (bins && n >= kBinMinNodes && room() < (1ll << 30) && ends <= 4 * n && chunks <= kBinMaxChunks) {
         s.binned = true;
         s.cb = 15;
         while ((room() >> s.cb) >= kBins) ++s.cb;          // (at most 20)
@@ -1156,12 +1157,18 @@ int grem_edge_stream_bipartition(const int32_t* src, const int32_t* dst, int64_t
     hipStream_t stream = (hipStream_t)stream_;
     if (c_size > m) c_size = m;
     const int64_t chunks = (m + c_size - 1) / c_size, ends = 2 * c_size;
-    const EsShape sh = es_shape(n, 1, ends, chunks);
-    const int64_t nodes = sh.nodes;
+    EsShape sh;
     EsMemory mem;
-    mem.layout(nullptr, sh, 1, ends, chunks, nbr_counts_out);
     uint8_t* ws = nullptr;
-    if (hipMallocAsync((void**)&ws, mem.bytes, stream) != hipSuccess) { (void)hipGetLastError(); return GREM_ERR_NOMEM; }
+    for (const bool bins : {true, false}) {
+        sh = es_shape(n, 1, ends, chunks, bins);
+        mem.layout(nullptr, sh, 1, ends, chunks, nbr_counts_out);
+        if (hipMallocAsync((void**)&ws, mem.bytes, stream) == hipSuccess) break;
+        (void)hipGetLastError();
+        ws = nullptr;
+        if (!sh.binned) return GREM_ERR_NOMEM;
+    }
+    const int64_t nodes = sh.nodes;
     mem.layout(ws, sh, 1, ends, chunks, nbr_counts_out);
     std::vector<EsGroup> groups(1);
     groups[0] = EsGroup{0, m, c_size, (long long)P, 0, 0u, (uint32_t)n, 0u, (uint32_t)(nodes / sh.bn()), 0u, 0u};
@@ -1205,9 +1212,8 @@ int grem_recursive_bisection(const int32_t* src, const int32_t* dst, int64_t m, 
     constexpr int64_t kMaxBatch = 1024;
     const int64_t most_groups = (int64_t)1 << (levels - 1);
     const int64_t ends = 2 * ((m + c_max - 1) / c_max + kMaxBatch);         // of one step: each group's chunk is rounded up
-    const EsShape sh = es_shape(n, most_groups < kMaxBatch ? most_groups : kMaxBatch, ends, c_max);
+    EsShape sh;
     EsMemory mem;
-    mem.layout(nullptr, sh, kMaxBatch, ends, c_max, nullptr);
     const int64_t sel_blocks = (m + kSelTile - 1) / kSelTile + kMaxBatch;
     size_t off = 0;
     auto carve = [&](size_t bytes) { const size_t at = off; off += align256(bytes); return at; };
@@ -1219,9 +1225,16 @@ int grem_recursive_bisection(const int32_t* src, const int32_t* dst, int64_t m, 
     const size_t o_tmps = carve((size_t)m * 4), o_tmpd = carve((size_t)m * 4), o_key = carve((size_t)m);
     size_t o_lev[4];                                   // two generations of the grouped edge list
     for (int i = 0; i < 4; ++i) o_lev[i] = carve((size_t)m * 4);
-    const size_t o_run = carve(mem.bytes);
+    const size_t o_run = off;                          // the state of a run is the last piece
     uint8_t* ws = nullptr;
-    if (hipMallocAsync((void**)&ws, off, stream) != hipSuccess) { (void)hipGetLastError(); return GREM_ERR_NOMEM; }
+    for (const bool bins : {true, false}) {
+        sh = es_shape(n, most_groups < kMaxBatch ? most_groups : kMaxBatch, ends, c_max, bins);
+        mem.layout(nullptr, sh, kMaxBatch, ends, c_max, nullptr);
+        if (hipMallocAsync((void**)&ws, o_run + mem.bytes, stream) == hipSuccess) break;
+        (void)hipGetLastError();
+        ws = nullptr;
+        if (!sh.binned) return GREM_ERR_NOMEM;
+    }
     mem.layout(ws + o_run, sh, kMaxBatch, ends, c_max, nullptr);
     auto fail = [&](int code) { (void)hipGetLastError(); (void)hipStreamSynchronize(stream); (void)hipFreeAsync(ws, stream); return code; };
     long long* totals = (long long*)(ws + o_totals);
