@@ -285,8 +285,8 @@ int grem_profile_read_marks(double *ms_out, int32_t capacity);
  * src, dst: m int32 each; seed_parts: n int32, read only at the first chunk's nodes; parts_out: n
  * int32; sizes_out: 2 int64 or NULL; nbr_counts_out: n*2 doubles, row-major, or NULL (when given it
  * is the working storage).  All device pointers.  Scratch memory is allocated on `stream` for the
- * call (about 10n bytes, or, from 2^22 nodes on, 2n + 8*c_size plus 8 KB per chunk; 16n more when
- * nbr_counts_out is NULL).  The call checks the endpoints' range and the seed (one small read-back) before
+ * call (about 10n bytes, or, from 2^22 nodes on if there is memory for it, 2n + 8*c_size plus 8 KB per
+ * chunk; 16n more when nbr_counts_out is NULL).  The call checks the endpoints' range and the seed (one small read-back) before
  * it enqueues the remaining chunks.
  * Errors: GREM_ERR_ARG (null pointer, m < 1, n < 1, n > 2^31-1, c_size < 1, P < 1, 2P < n, unknown
  * mode, an endpoint outside [0,n)), GREM_ERR_SEED (a first-chunk node whose seed is not 0 or 1, or
