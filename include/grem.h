@@ -338,7 +338,7 @@ int grem_edge_buckets(const int32_t *src, const int32_t *dst, int64_t m, int64_t
  * Every edge of a symmetric CSR is seen from both ends.  The expected cuts with refinement over two
  * chunks are the same expression at 2x.  rowptr (rowptr_bits 32 or 64), colidx, labels (n int32), out
  * (2 doubles): device pointers.  Floating point: the tail is summed in double (in the log domain when a node has more than 256 draws);
- * agreement with an exact evaluation to about 1e-9 relative.  Scratch (8.25 bytes per node) is allocated on
+ * agreement with an exact evaluation to about 1e-9 relative.  Scratch (8.5 bytes per node and 0.13 MB) is allocated on
  * `stream`.  Errors: GREM_ERR_ARG (null pointer,
  * n < 1, bad rowptr_bits, x outside (0, 1]), GREM_ERR_NOMEM, GREM_ERR_HIP. */
 int grem_expected_cut(const void *rowptr, int32_t rowptr_bits, const int32_t *colidx, int64_t n,
@@ -354,7 +354,7 @@ int grem_plan_expected_cut(const grem_plan *plan, const int32_t *labels, double 
 
 /* grem_expected_cut for callers that cannot allocate device memory: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments and the same result, bit for
- * bit, as grem_expected_cut, but the per-workgroup partial sums and the packed labels go to a fixed
+ * bit, as grem_expected_cut, but the partial sums and the packed labels go to a fixed
  * 4 MiB buffer that is part of the library's device image (one copy per GPU, held until the process
  * ends) instead of a stream-ordered allocation, and the terms are summed where the labels are counted
  * (no room for the counts of all nodes: slower than grem_expected_cut); the call allocates and frees nothing.
