@@ -33,7 +33,7 @@ constexpr int kEbMaxK = 128;                       // k*k*4 bytes of LDS: 64 KB 
 constexpr int64_t kEbMaxCells = (int64_t)1 << 27;  // tiles * k*k
 constexpr int64_t kEbMinTile = 4096;
 constexpr uint32_t kBadLabel = 0xFFu;
-constexpr int64_t kEbBinMinN = 1ll << 23, kEbBinMinM = 1 << 22;
+constexpr int64_t kEbBinMinN = 1ll << 23, kEbBinMinM = 1 << 22, kEbBinMinNM = 200'000'000'000'000;
 
 __global__ __launch_bounds__(256) void k_eb_zero(uint32_t* p, size_t count)
 {
@@ -165,7 +165,9 @@ __global__ __launch_bounds__(256) void k_eb_colscan(uint32_t* __restrict__ H, in
 // lists' sizes for every batch, and the range check of the endpoints; ends out of range count as the last
 // node.)
 // 1.6e9 edges of 111M nodes: 57.4 ms with look-ups in the table, 27.5 in these kernels.  Below 8M nodes the table's
-// look-ups are the faster way (4M nodes, 50M edges: 1.35 ms against 1.5 to 1.7).
+// look-ups are the faster way (4M nodes, 50M edges: 1.35 ms against 1.5 to 1.7), and the lists' memory takes some 0.3 ms to get
+// and give back, which the table's misses must outweigh (binned against table, k = 16: 8.4M nodes and 12M edges 0.68 and 0.52 ms,
+// 24M edges 0.73 and 0.96; 20M nodes and 8.4M edges 0.63 and 0.52, 12M edges 0.57 and 0.64; 60M nodes and 6M edges 0.53 and 0.57).
 constexpr int kEbBins = 1024;
 constexpr int kEbBinThreads = 1024;
 constexpr int kEbBinTile = 8192;                  // edges per workgroup (16,384 and one workgroup per CU: 47.5 ms a call for 46)
@@ -190,7 +192,22 @@ __device__ __forceinline__ uint32_t eb_block_exclusive(uint32_t x, uint32_t* wsu
 
 __device__ __forceinline__ uint32_t eb_end(int32_t id, uint32_t n) { return (uint32_t)id < n ? (uint32_t)id : n - 1u; }
 
-// table[batch][bin]: ends of the batch's edges
+// rank among the ends counted so far of the same bin.  Lanes that share the first active lane's bin (edges sorted by
+// source, popular ids) take one atomic together if they are many: equal addresses are served one after the other.
+__device__ __forceinline__ uint32_t eb_count(uint32_t* hist, uint32_t bin)
+{
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)bin);
+    const u64 same = __ballot(bin == first);
+    if (__popcll(same) < 16) return atomicAdd(&hist[bin], 1u);
+    const u64 below = (1ull << (threadIdx.x & 63)) - 1ull;
+    uint32_t base = 0u;
+    if (bin != first) return atomicAdd(&hist[bin], 1u);
+    if ((same & below) == 0ull) base = atomicAdd(&hist[bin], (uint32_t)__popcll(same));
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)base) + (uint32_t)__popcll(same & below);
+}
+
+// table[batch][bin]: ends of the batch's edges; table[batch][kEbBins]: how many of them lie in bins that its workgroup
+// met at least four times per 128-byte line of their labels
 __global__ __launch_bounds__(kEbBinThreads) void k_eb_bin_count(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                                                                 int64_t m, int64_t batch, uint32_t n, int cb,
                                                                 uint32_t* __restrict__ table, uint32_t* flags)
@@ -212,26 +229,45 @@ __global__ __launch_bounds__(kEbBinThreads) void k_eb_bin_count(const int32_t* _
         for (int u = 0; u < kEbBinPer; ++u) {
             if (t + u * kEbBinThreads + threadIdx.x >= hi) continue;
             bad |= (uint32_t)s[u] >= n || (uint32_t)d[u] >= n;
-            atomicAdd(&hist[eb_end(s[u], n) >> cb], 1u);
-            atomicAdd(&hist[eb_end(d[u], n) >> cb], 1u);
+            (void)eb_count(hist, eb_end(s[u], n) >> cb);
+            (void)eb_count(hist, eb_end(d[u], n) >> cb);
         }
     }
     if (bad) flags[0] = 1u;
     __syncthreads();
     const uint32_t c = hist[threadIdx.x];
-    if (c) atomicAdd(&table[(size_t)blockIdx.y * (kEbBins + 1) + threadIdx.x], c);
+    uint32_t* row = table + (size_t)blockIdx.y * (kEbBins + 1);
+    if (c) atomicAdd(&row[threadIdx.x], c);
+    uint32_t local = c >= 1u << (cb - 5) ? c : 0u;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) local += __shfl_xor(local, o);
+    if (local && (threadIdx.x & 63) == 0) atomicAdd(&row[kEbBins], local);
 }
 
-// sizes -> starts (a workgroup per batch); cursors: a second copy, which k_eb_bin moves on
-__global__ __launch_bounds__(kEbBins) void k_eb_bin_scan(uint32_t* table, uint32_t* cursors)
+// sizes -> starts (a workgroup per batch); cursors: a second copy, which k_eb_bin moves on.  parts: how many workgroups
+// of k_eb_lookup share a bin's list, as starts: in proportion to its length, `want` in all and at most one more per
+// bin.  (Cut into the same number of parts each, lists of popular ids kept a few workgroups busy: ids in order of
+// degree, a batch of 33M edges of 111M nodes: 1139 us for 136 on permuted ids.)
+// A batch of which more than 52 % of the ends are local (see k_eb_bin_count) gets no parts: its look-ups go to the table,
+// whose lines the caches then hold.  400M edges of 111M nodes in order of degree and sorted by source (66 % local):
+// 9.5 ms that way, 11.2 binned; sorted by source alone (50 %) 12.8 and 11.2, in order of degree alone (39 %) 12.9 and 12.5.
+__global__ __launch_bounds__(kEbBins) void k_eb_bin_scan(uint32_t* table, uint32_t* cursors, uint32_t* parts, uint32_t want)
 {
-    __shared__ uint32_t wsum[16];
+    __shared__ uint32_t wsum[16], s_total;
     uint32_t* row = table + (size_t)blockIdx.x * (kEbBins + 1);
-    const uint32_t c = row[threadIdx.x];
+    const uint32_t c = row[threadIdx.x], local = row[kEbBins];
     const uint32_t excl = eb_block_exclusive(c, wsum);
     row[threadIdx.x] = excl;
     cursors[(size_t)blockIdx.x * kEbBins + threadIdx.x] = excl;
-    if (threadIdx.x == kEbBins - 1) row[kEbBins] = excl + c;
+    if (threadIdx.x == kEbBins - 1) { row[kEbBins] = excl + c; s_total = excl + c; }
+    __syncthreads();
+    const uint32_t fair = (uint32_t)(((uint64_t)c * want + s_total / 2u) / s_total);      // (a batch has edges)
+    const bool direct = (uint64_t)local * 25u > (uint64_t)s_total * 13u;
+    const uint32_t mine = c == 0u || direct ? 0u : fair == 0u ? 1u : fair;
+    const uint32_t first = eb_block_exclusive(mine, wsum);
+    uint32_t* prow = parts + (size_t)blockIdx.x * (kEbBins + 1);
+    prow[threadIdx.x] = first;
+    if (threadIdx.x == kEbBins - 1) prow[kEbBins] = first + mine;
 }
 
 // runs[tile][bin]: (where the tile's run of the bin went, its start in the sorted tile); places[edge of the batch]: those of
@@ -239,9 +275,11 @@ __global__ __launch_bounds__(kEbBins) void k_eb_bin_scan(uint32_t* table, uint32
 template <typename Item>
 __global__ __launch_bounds__(kEbBinThreads, 8) void k_eb_bin(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                                                           int64_t count, uint32_t n, int cb, int nbins,
-                                                          uint32_t* __restrict__ cursors, Item* __restrict__ lists,
-                                                          uint2* __restrict__ runs, uint32_t* __restrict__ places)
+                                                          const uint32_t* __restrict__ prow, uint32_t* __restrict__ cursors,
+                                                          Item* __restrict__ lists, uint2* __restrict__ runs,
+                                                          uint32_t* __restrict__ places)
 {
+    if (prow[kEbBins] == 0u) return;               // (look-ups in the table: k_eb_keys)
     extern __shared__ uint32_t items[];            // 2 * kEbBinTile: place in bin, bin above it
     __shared__ uint32_t hist[kEbBins], start[kEbBins], at[kEbBins], wsum[16];
     const int tid = threadIdx.x;
@@ -260,8 +298,8 @@ __global__ __launch_bounds__(kEbBinThreads, 8) void k_eb_bin(const int32_t* __re
     for (int u = 0; u < kEbBinPer; ++u) {
         rank[u] = 0u;
         if (lo + u * kEbBinThreads + tid < count) {
-            rank[u] = atomicAdd(&hist[a[u] >> cb], 1u);
-            rank[u] |= atomicAdd(&hist[b[u] >> cb], 1u) << 16;
+            rank[u] = eb_count(hist, a[u] >> cb);
+            rank[u] |= eb_count(hist, b[u] >> cb) << 16;
         }
     }
     __syncthreads();
@@ -295,19 +333,23 @@ __global__ __launch_bounds__(kEbBinThreads, 8) void k_eb_bin(const int32_t* __re
 // a part of a bin's list: the labels, one byte per entry.  PACK: two labels per byte in LDS (k <= 16; a node without a
 // valid label is then looked for in the table, if the graph has any: *bad_labels).
 template <typename Item, bool PACK>
-__global__ __launch_bounds__(kEbBinThreads) void k_eb_lookup(const uint8_t* __restrict__ L8, int64_t n, int cb, int parts,
-                                                             const uint32_t* __restrict__ row, const Item* __restrict__ lists,
+__global__ __launch_bounds__(kEbBinThreads) void k_eb_lookup(const uint8_t* __restrict__ L8, int64_t n, int cb,
+                                                             const uint32_t* __restrict__ prow, const uint32_t* __restrict__ row, const Item* __restrict__ lists,
                                                              uint8_t* __restrict__ labels, const uint32_t* __restrict__ bad_labels,
                                                              uint32_t* flags)
 {
     extern __shared__ uint32_t tab[];              // 2^cb labels, a byte or half a byte each
     const int tid = threadIdx.x;
-    const uint32_t bin = blockIdx.x / (unsigned)parts, part = blockIdx.x % (unsigned)parts;
+    __shared__ uint32_t s_bin;
+    if (blockIdx.x >= prow[kEbBins]) return;
+    if (blockIdx.x >= prow[tid] && blockIdx.x < prow[tid + 1]) s_bin = (uint32_t)tid;
+    __syncthreads();
+    const uint32_t bin = s_bin, parts = prow[bin + 1] - prow[bin], part = blockIdx.x - prow[bin];
     const uint32_t i0 = row[bin], len = row[bin + 1] - i0;
     // (parts meet at multiples of four entries)
     const uint32_t first = (uint32_t)((uint64_t)len * part / parts), last = (uint32_t)((uint64_t)len * (part + 1) / parts);
     auto edge = [&](uint32_t x) { const uint32_t y = (i0 + x) & ~3u; return y < i0 ? i0 : y; };
-    const uint32_t b = part == 0 ? i0 : edge(first), e = part + 1 == (uint32_t)parts ? i0 + len : edge(last);
+    const uint32_t b = part == 0 ? i0 : edge(first), e = part + 1 == parts ? i0 + len : edge(last);
     if (b >= e) return;
     const int64_t v0 = (int64_t)bin << cb;
     const uint32_t nodes = n - v0 < (1ll << cb) ? (uint32_t)(n - v0) : 1u << cb;
@@ -351,22 +393,45 @@ __global__ __launch_bounds__(kEbBinThreads) void k_eb_lookup(const uint8_t* __re
     if (bad) flags[1] = 1u;
 }
 
-// The tile's labels back in its sorted order (sixteen lanes per run, some 20 to 80 bytes each), then the edges' keys.
-__global__ __launch_bounds__(kEbBinThreads, 8) void k_eb_keys(int64_t count, int nbins, int32_t k, const uint2* __restrict__ runs,
+// The tile's labels back in its sorted order (sixteen lanes per run, some 20 to 80 bytes each; what a run has beyond
+// kEbLongRun is left to the whole workgroup: edges sorted by source put half a tile in one run, 425 us for 161), then
+// the edges' keys.
+constexpr uint32_t kEbLongRun = 256;
+__global__ __launch_bounds__(kEbBinThreads, 8) void k_eb_keys(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                                                           int64_t count, uint32_t n, const uint8_t* __restrict__ L8, int nbins, int32_t k,
+                                                           const uint32_t* __restrict__ prow, const uint2* __restrict__ runs,
                                                            const uint32_t* __restrict__ places, const uint8_t* __restrict__ labels,
-                                                           uint16_t* __restrict__ key16)
+                                                           uint16_t* __restrict__ key16, uint32_t* flags)
 {
     __shared__ uint8_t lab[2 * kEbBinTile];
+    __shared__ uint32_t s_long, longs[2 * kEbBinTile / kEbLongRun];
     const int tid = threadIdx.x, l = tid & 15;
+    if (tid == 0) s_long = 0u;
     const int64_t lo = (int64_t)blockIdx.x * kEbBinTile;
-    const uint32_t total = 2u * (uint32_t)(count - lo < kEbBinTile ? count - lo : kEbBinTile);
-    uint32_t at[kEbBinPer];
+    if (prow[kEbBins] == 0u) {                     // a batch without lists
+        uint32_t ls[kEbBinPer], ld[kEbBinPer];
+        bool bad = false;
 #pragma unroll
-    for (int u = 0; u < kEbBinPer; ++u) {
-        const int64_t e = lo + u * kEbBinThreads + tid;
-        at[u] = e < count ? __builtin_nontemporal_load(places + e) : 0u;
+        for (int u = 0; u < kEbBinPer; ++u) {
+            const int64_t e = lo + u * kEbBinThreads + tid;
+            ls[u] = e < count ? eb_end(__builtin_nontemporal_load(src + e), n) : 0u;
+            ld[u] = e < count ? eb_end(__builtin_nontemporal_load(dst + e), n) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < kEbBinPer; ++u) { ls[u] = L8[ls[u]]; ld[u] = L8[ld[u]]; }
+#pragma unroll
+        for (int u = 0; u < kEbBinPer; ++u) {
+            const int64_t e = lo + u * kEbBinThreads + tid;
+            if (e >= count) continue;
+            bad |= ls[u] == kBadLabel || ld[u] == kBadLabel;
+            key16[e] = ls[u] < (uint32_t)k && ld[u] < (uint32_t)k ? (uint16_t)(ls[u] * (uint32_t)k + ld[u]) : (uint16_t)0;
+        }
+        if (bad) flags[1] = 1u;
+        return;
     }
+    const uint32_t total = 2u * (uint32_t)(count - lo < kEbBinTile ? count - lo : kEbBinTile);
     const uint2* own = runs + (size_t)blockIdx.x * nbins;
+    __syncthreads();
     constexpr int U = 2, groups = kEbBinThreads / 16;
     for (int b0 = tid / 16; b0 < nbins; b0 += groups * U) {
         uint2 r[U];
@@ -391,8 +456,24 @@ __global__ __launch_bounds__(kEbBinThreads, 8) void k_eb_keys(int64_t count, int
                 const uint32_t i = r[u].y + l + 16 * h;
                 if (i < end[u]) lab[i] = (uint8_t)x[u][h];
             }
-            for (uint32_t i = r[u].y + l + 32; i < end[u]; i += 16) lab[i] = labels[r[u].x + (i - r[u].y)];
+            const bool cut = end[u] > r[u].y + kEbLongRun;
+            const uint32_t stop = cut ? r[u].y + kEbLongRun : end[u];
+            for (uint32_t i = r[u].y + l + 32; i < stop; i += 16) lab[i] = labels[r[u].x + (i - r[u].y)];
+            if (cut && l == 0) longs[atomicAdd(&s_long, 1u)] = (uint32_t)(b0 + u * groups);
         }
+    }
+    uint32_t at[kEbBinPer];
+#pragma unroll
+    for (int u = 0; u < kEbBinPer; ++u) {
+        const int64_t e = lo + u * kEbBinThreads + tid;
+        at[u] = e < count ? __builtin_nontemporal_load(places + e) : 0u;
+    }
+    __syncthreads();
+    for (uint32_t j = 0; j < s_long; ++j) {
+        const int b = (int)longs[j];
+        const uint2 r = own[b];
+        const uint32_t end = b + 1 < nbins ? own[b + 1].y : total;
+        for (uint32_t i = r.y + kEbLongRun + tid; i < end; i += kEbBinThreads) lab[i] = labels[r.x + (i - r.y)];
     }
     __syncthreads();
 #pragma unroll
@@ -609,14 +690,14 @@ extern "C" int grem_edge_buckets(const int32_t* src, const int32_t* dst, int64_t
     // lists the look-ups go to the table
     const int cb = n <= (int64_t)kEbBins << 16 ? 16 : 17;
     const bool pack = k <= 16, small_item = cb == 16;      // (16 bits hold the place in a bin of 2^16 nodes)
-    bool binned = n >= kEbBinMinN && m >= kEbBinMinM && n <= (int64_t)kEbBins << 17;
+    bool binned = n >= kEbBinMinN && m >= kEbBinMinM && n <= (int64_t)kEbBins << 17 && n * m >= kEbBinMinNM;
     const int nbins = (int)((n + (1ll << cb) - 1) >> cb);
     // edges per batch: their lists, places and labels take 5 or 7 bytes per end (16M edges of 14M nodes: 5.8 ms for 200M
     // edges instead of 6.0 with 33M; 33M of 111M nodes: 50.2 ms for 1.6e9 instead of 52.4 with 16M)
     const int64_t most = small_item ? (int64_t)1 << 24 : (int64_t)1 << 25, batch = m < most ? m : most, batches = (m + batch - 1) / batch;
     const int64_t bin_tiles = (batch + kEbBinTile - 1) / kEbBinTile;
     const size_t plain_off = off;
-    const size_t o_table = carve((size_t)batches * (kEbBins + 1) * 4), o_cursors = carve((size_t)batches * kEbBins * 4);
+    const size_t o_table = carve((size_t)batches * (kEbBins + 1) * 4), o_parts = carve((size_t)batches * (kEbBins + 1) * 4), o_cursors = carve((size_t)batches * kEbBins * 4);
     const size_t o_lists = carve((size_t)batch * 2 * (small_item ? 2 : 4)), o_labels = carve((size_t)batch * 2 + 4);
     const size_t o_runs = carve((size_t)bin_tiles * nbins * 8), o_places = carve((size_t)batch * 4);
     uint8_t* ws = nullptr;
@@ -640,15 +721,15 @@ extern "C" int grem_edge_buckets(const int32_t* src, const int32_t* dst, int64_t
     uint32_t host_flags[2] = {0, 0};
     hipLaunchKernelGGL(k_eb_compact, dim3(grid(n, 16384)), dim3(256), 0, stream, n, labels, k, L8, flags + 2);
     if (binned) {
-        uint32_t *table = (uint32_t*)(ws + o_table), *cursors = (uint32_t*)(ws + o_cursors), *places = (uint32_t*)(ws + o_places);
+        uint32_t *table = (uint32_t*)(ws + o_table), *part_rows = (uint32_t*)(ws + o_parts), *cursors = (uint32_t*)(ws + o_cursors), *places = (uint32_t*)(ws + o_places);
         uint8_t* found = ws + o_labels;
         uint2* runs = (uint2*)(ws + o_runs);
         const size_t items_lds = (size_t)kEbBinTile * 8, tab_lds = pack ? (size_t)1 << (cb - 1) : (size_t)1 << cb;
-        const int parts = nbins >= 1024 ? 1 : (1024 + nbins - 1) / nbins;
+        const int parts = nbins * (nbins >= 1024 ? 1 : (1024 + nbins - 1) / nbins);
         hipLaunchKernelGGL(k_eb_zero, dim3(256), dim3(256), 0, stream, table, (size_t)batches * (kEbBins + 1));
         hipLaunchKernelGGL(k_eb_bin_count, dim3((unsigned)((bin_tiles + 7) / 8), (unsigned)batches), dim3(kEbBinThreads), 0, stream, src, dst, m, batch,
                            (uint32_t)n, cb, table, flags);
-        hipLaunchKernelGGL(k_eb_bin_scan, dim3((unsigned)batches), dim3(kEbBins), 0, stream, table, cursors);
+        hipLaunchKernelGGL(k_eb_bin_scan, dim3((unsigned)batches), dim3(kEbBins), 0, stream, table, cursors, part_rows, (uint32_t)parts);
         auto run = [&](auto item, auto packed) {
             using Item = decltype(item);
             constexpr bool PACK = decltype(packed)::value;
@@ -659,13 +740,15 @@ extern "C" int grem_edge_buckets(const int32_t* src, const int32_t* dst, int64_t
             for (int64_t i = 0; i < batches; ++i) {
                 const int64_t lo = i * batch, count = m - lo < batch ? m - lo : batch;
                 const unsigned tiles_now = (unsigned)((count + kEbBinTile - 1) / kEbBinTile);
+                const uint32_t* prow = part_rows + (size_t)i * (kEbBins + 1);
                 hipLaunchKernelGGL((k_eb_bin<Item>), dim3(tiles_now), dim3(kEbBinThreads), items_lds, stream, src + lo, dst + lo, count,
-                                   (uint32_t)n, cb, nbins, cursors + (size_t)i * kEbBins, lists, runs, places);
-                hipLaunchKernelGGL((k_eb_lookup<Item, PACK>), dim3((unsigned)(nbins * parts)), dim3(kEbBinThreads), tab_lds, stream,
-                                   (const uint8_t*)L8, n, cb, parts, (const uint32_t*)(table + (size_t)i * (kEbBins + 1)), (const Item*)lists,
+                                   (uint32_t)n, cb, nbins, prow, cursors + (size_t)i * kEbBins, lists, runs, places);
+                hipLaunchKernelGGL((k_eb_lookup<Item, PACK>), dim3((unsigned)(parts + nbins)), dim3(kEbBinThreads), tab_lds, stream,
+                                   (const uint8_t*)L8, n, cb, prow, (const uint32_t*)(table + (size_t)i * (kEbBins + 1)), (const Item*)lists,
                                    found, (const uint32_t*)(flags + 2), flags);
-                hipLaunchKernelGGL(k_eb_keys, dim3(tiles_now), dim3(kEbBinThreads), 0, stream, count, nbins, k, (const uint2*)runs,
-                                   (const uint32_t*)places, (const uint8_t*)found, key16 + lo);
+                hipLaunchKernelGGL(k_eb_keys, dim3(tiles_now), dim3(kEbBinThreads), 0, stream, src + lo, dst + lo, count, (uint32_t)n,
+                                   (const uint8_t*)L8, nbins, k, prow, (const uint2*)runs, (const uint32_t*)places, (const uint8_t*)found,
+                                   key16 + lo, flags);
             }
             return true;
         };

@@ -1,5 +1,5 @@
-"""Edge buckets where the label look-ups are binned (from 2^23 nodes and 2^22 edges on), against a stable sort of the keys
-from plain torch: both sizes of a bin, packed labels and bytes, ragged tiles and batches, tiles of more than 4,096 edges, and
+"""Edge buckets where the label look-ups are binned (from 2^23 nodes, 2^22 edges and 2e14 of their product on) and a little
+below, against a stable sort of the keys from plain torch: both sizes of a bin, packed labels and bytes, ragged tiles and batches, tiles of more than 4,096 edges, and
 what is refused."""
 import pytest
 import torch
@@ -19,8 +19,10 @@ def _edges(n, m, seed):
     return src, dst, gen
 
 
-# the smallest; a bin of 2^16 nodes cut short; bins of 2^17 nodes; two batches (16M edges), the last tile ragged
-@pytest.mark.parametrize("n,m", [(1 << 23, 1 << 22), (8_400_001, 5_000_003), (67_200_000, 4_200_001), (9_000_000, (1 << 24) + 8195)])
+# the smallest of each and one edge less; a bin of 2^16 nodes cut short; bins of 2^17 nodes; two batches (16M edges), the
+# last tile ragged
+@pytest.mark.parametrize("n,m", [(1 << 23, 1 << 22), (8_400_001, 5_000_003), (67_200_000, 4_200_001), (9_000_000, (1 << 24) + 8195),
+                                 (1 << 23, 23_841_858), (1 << 23, 23_841_857), (47_683_716, 1 << 22), (13_000_001, (1 << 24) + 8195)])
 @pytest.mark.parametrize("k", [1, 16, 17, 33, 128])
 def test_binned_buckets_equal_a_stable_sort(n, m, k):
     src, dst, gen = _edges(n, m, k)
@@ -37,7 +39,7 @@ def test_binned_buckets_equal_a_stable_sort(n, m, k):
 
 @pytest.mark.parametrize("k", [16, 40])
 def test_what_is_refused(k):
-    n, m = 1 << 23, 1 << 22
+    n, m = 1 << 23, 24_000_000
     src, dst, gen = _edges(n, m, 1)
     labels = torch.randint(0, k, (n,), generator=gen, device=DEV, dtype=torch.int32)
     for bad in (n, -1, 2**31 - 1):

@@ -92,3 +92,40 @@ def test_expected_cut_in_order_of_degree_is_no_slower():
         print(f"[result] {order}: {took[order]} ms", flush=True)
     for i in range(2):
         assert took["by degree"][i] <= 4 * took["permuted"][i]
+
+
+# binned look-ups of lists that are not spread: long runs and crowded bins, batches of few and of many local ends (the
+# look-ups of the latter go to the table), a batch's worth and a little more, both sizes of a bin
+@pytest.mark.parametrize("order", ["by degree", "permuted sorted", "by degree sorted"])
+@pytest.mark.parametrize("n,m,k", [(13_000_001, (1 << 24) + 4099, 16), (33_000_001, 6_200_003, 40), (68_000_000, 10_000_001, 9)])
+def test_buckets_of_ordered_edges(n, m, k, order):
+    src, dst = _edges(n, m, order)
+    labels = torch.randint(0, k, (n,), device=DEV, dtype=torch.int32)
+    got_s, got_d, offsets = B.grem_edge_buckets(src, dst, n, labels, k)
+    key = labels[src.long()] * k + labels[dst.long()]
+    perm = torch.sort(key, stable=True).indices
+    assert torch.equal(got_s, src[perm])
+    assert torch.equal(got_d, dst[perm])
+    want = torch.zeros(k * k + 1, dtype=torch.int64, device=DEV)
+    want[1:] = torch.cumsum(torch.bincount(key, minlength=k * k), 0)
+    assert torch.equal(offsets, want)
+    bad = labels.clone()
+    bad[src[m // 2]] = k
+    for d, lab in ((dst, bad), (torch.where(torch.arange(m, device=DEV) == m - 1, n, dst).to(torch.int32), labels)):
+        with pytest.raises(B.GremError) as e:
+            B.grem_edge_buckets(src, d, n, lab, k)
+        assert e.value.code == B.ERR_ARG
+
+
+def test_buckets_of_ordered_edges_are_no_slower():
+    # measured 11.5 ms permuted, 9.5 to 12.5 in the other orders; 26, 17 and 29 with every bin cut into the same parts
+    n, m, k = 111_000_000, 400_000_000, 16
+    labels = torch.randint(0, k, (n,), device=DEV, dtype=torch.int32)
+    took = {}
+    for order in ("permuted", "by degree", "permuted sorted", "by degree sorted"):
+        src, dst = _edges(n, m, order)
+        took[order] = _ms(lambda: B.grem_edge_buckets(src, dst, n, labels, k))
+        print(f"[result] {order}: {took[order]:.2f} ms", flush=True)
+        del src, dst
+        torch.cuda.empty_cache()
+    assert max(took.values()) <= 1.35 * took["permuted"]
