@@ -246,7 +246,12 @@ __global__ __launch_bounds__(kXcBlock) void k_xc_terms(const RowT* __restrict__ 
     __shared__ uint32_t s_slot;
     const int tid = threadIdx.x;
     const int64_t tiles = (n + kXcTile - 1) / kXcTile, limit = xc_split_limit((int64_t)rowptr[n], split);
-    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    // four neighbouring tiles at a time (13.9M nodes, 395M entries: 2.18 ms; one at a time 2.24, a contiguous range per
+    // workgroup 2.15, but 130 in order of degree); one where the tails are summed as well (1.03 ms for 1.13 at 4M nodes)
+    constexpr int64_t kTurn = FUSED ? 1 : 4;
+    for (int64_t i = 0;; ++i) {
+        const int64_t tile = ((int64_t)blockIdx.x + i / kTurn * gridDim.x) * kTurn + i % kTurn;
+        if (tile >= tiles) break;
         const int64_t v0 = tile * kXcTile;
         const int nv = n - v0 < kXcTile ? (int)(n - v0) : kXcTile;
         const int64_t e0 = (int64_t)rowptr[v0], ne = (int64_t)rowptr[v0 + nv] - e0;

@@ -80,7 +80,7 @@ def test_expected_cut_of_rows_side_by_side(n, rows):
 
 
 def test_expected_cut_in_order_of_degree_is_no_slower():
-    # measured 1.2 ms permuted at this size, 0.8 in order of degree (37 with a workgroup to every 256 rows)
+    # measured 1.2 ms permuted at this size, 1.5 and 0.8 in order of degree (37 with a workgroup to every 256 rows)
     n, m = 4_000_000, 57_000_000
     out = torch.empty(2, dtype=torch.float64, device=DEV)
     took = {}
