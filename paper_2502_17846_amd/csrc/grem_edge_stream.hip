@@ -325,8 +325,17 @@ __device__ __forceinline__ uint32_t es_block_exclusive(uint32_t x, uint32_t* wsu
     return before;
 }
 
+// The bins of more than `limit` pairs in a chunk, which no workgroup should count alone (k_es_crowd).
+struct EsCrowd {
+    uint16_t* place;                         // [chunk][bin]: 0, or 1 + the bin's place among the chunk's crowded ones
+    uint32_t* bins;                          // [chunk]: how many there are
+    u64* hc;                                 // [place][node of the bin]: counts as in EsMemory::hc, zero between chunks
+    uint32_t* seen;                          // ... and a bit per node
+    uint32_t limit;
+};
+
 // sizes -> starts (one workgroup per chunk); cursors: a second copy, which k_es_bin moves on
-__global__ __launch_bounds__(kBins) void k_es_hist_scan(uint32_t* table, uint32_t* cursors)
+__global__ __launch_bounds__(kBins) void k_es_hist_scan(uint32_t* table, uint32_t* cursors, EsCrowd crowd)
 {
     __shared__ uint32_t wsum[kWaves];
     uint32_t* row = table + (size_t)blockIdx.x * kBinTableStride;
@@ -335,6 +344,11 @@ __global__ __launch_bounds__(kBins) void k_es_hist_scan(uint32_t* table, uint32_
     row[threadIdx.x] = excl;
     cursors[(size_t)blockIdx.x * kBins + threadIdx.x] = excl;
     if (threadIdx.x == kBins - 1) row[kBins] = excl + c;
+    __syncthreads();
+    const uint32_t crowded = c > crowd.limit ? 1u : 0u;
+    const uint32_t place = es_block_exclusive(crowded, wsum);
+    crowd.place[(size_t)blockIdx.x * kBins + threadIdx.x] = crowded ? (uint16_t)(place + 1u) : (uint16_t)0;
+    if (threadIdx.x == kBins - 1) crowd.bins[blockIdx.x] = place + crowded;
 }
 
 // cnt_nbrs, first half: for every edge end the label of the other end, the pairs sorted by bin.  A pair is the
@@ -451,6 +465,65 @@ __device__ __forceinline__ void es_store_movers(const EsRun& st, u64 movers0, u6
     if (threadIdx.x == 0) { st.bs0[block] = (uint32_t)movers0; st.bs1[block] = (uint32_t)movers1; }
 }
 
+// The pairs of the chunk's crowded bins, counted before the scoring by all workgroups: a piece of a bin's pairs and one of
+// its blocks at a time, in LDS, added to the counts in memory that k_es_score_bins then reads instead of the pairs.  Ids in
+// order of degree put a quarter of all ends in one bin, whose four blocks each walked 8M pairs twice: a chunk of 16M
+// edges of 111M nodes took 4.7 ms in k_es_score_bins, 0.75 on permuted ids.
+constexpr uint32_t kCrowdPiece = 65535;            // pairs per turn: the two counts of a node fit 16 bits each
+__global__ __launch_bounds__(kBlock) void k_es_crowd(int64_t chunk, int cb, uint32_t bn, uint32_t nblocks,
+                                                     const uint32_t* __restrict__ table, const uint32_t* __restrict__ pairs, EsCrowd crowd)
+{
+    extern __shared__ uint32_t cnt[];              // bn words, then as many bits
+    __shared__ uint32_t wsum[kWaves], bin_of[kBins], first[kBins + 1];
+    uint32_t* seen = cnt + bn;
+    const int tid = threadIdx.x;
+    const uint32_t* row = table + (size_t)chunk * kBinTableStride;
+    const uint32_t bins = crowd.bins[chunk], blocks = (1u << cb) / bn;
+    const uint32_t place = crowd.place[(size_t)chunk * kBins + tid];
+    if (place) bin_of[place - 1u] = (uint32_t)tid;
+    __syncthreads();
+    const uint32_t bin_t = (uint32_t)tid < bins ? bin_of[tid] : 0u;
+    const uint32_t items = (uint32_t)tid < bins ? (row[bin_t + 1u] - row[bin_t] + kCrowdPiece - 1u) / kCrowdPiece * blocks : 0u;
+    const uint32_t excl = es_block_exclusive(items, wsum);
+    first[tid] = excl;
+    if (tid == kBins - 1) first[kBins] = excl + items;
+    __syncthreads();
+    uint32_t at = 0;                               // the crowded bin of the item
+    for (uint32_t item = blockIdx.x; item < first[kBins]; item += gridDim.x) {
+        while (item >= first[at + 1u]) ++at;
+        const uint32_t bin = bin_of[at], part = item - first[at], low = part % blocks * bn;
+        if (((bin << cb) + low) / bn >= nblocks) continue;                   // (past the last block; the same for all threads)
+        const uint32_t p0 = row[bin] + part / blocks * kCrowdPiece;
+        const uint32_t p1 = row[bin + 1u] - p0 < kCrowdPiece ? row[bin + 1u] : p0 + kCrowdPiece;
+        for (uint32_t i = tid; i < bn; i += kBlock) cnt[i] = 0u;
+        for (uint32_t i = tid; i < bn / 32; i += kBlock) seen[i] = 0u;
+        __syncthreads();
+        constexpr int U = 8;
+        for (uint32_t i = p0 + tid; i < p1; i += kBlock * U) {
+            uint32_t x[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) x[u] = p1 - i > (uint32_t)(u * kBlock) ? pairs[i + u * kBlock] : 0xFFFFFFFFu;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t rel = (x[u] & ((1u << cb) - 1u)) - low, code = x[u] >> cb;
+                if (x[u] == 0xFFFFFFFFu || rel >= bn) continue;
+                if (code >= 2u) atomicOr(&seen[rel >> 5], 1u << (rel & 31u));
+                else atomicAdd(&cnt[rel], code ? 65536u : 1u);
+            }
+            if (p1 - i <= (uint32_t)(kBlock * U)) break;
+        }
+        __syncthreads();
+        const size_t node = ((size_t)at << cb) + low;
+        for (uint32_t i = tid; i < bn; i += kBlock) {
+            const uint32_t c = cnt[i];
+            if (c) atomicAdd(&crowd.hc[node + i], (u64)(c & 0xFFFFu) | (u64)(c >> 16) << 32);
+        }
+        for (uint32_t i = tid; i < bn / 32; i += kBlock)
+            if (seen[i]) atomicOr(&crowd.seen[node / 32 + i], seen[i]);
+        __syncthreads();
+    }
+}
+
 // From the counts in memory; clears what it consumed (hc, mark).  first: the seeded first chunk (estimates only).
 // fixed: fixed greedy decisions (a node that has a label is left alone).
 // A wave has the counts of kTurn words in flight, and blocks are as small as it takes to fill the chip (es_shape):
@@ -497,7 +570,7 @@ __global__ __launch_bounds__(kBlock) void k_es_score(EsRun st, int par, int firs
 // counts in memory, 0.74 here.
 __global__ __launch_bounds__(kBlock) void k_es_score_bins(EsRun st, int par, int first, int fixed, int64_t chunk, int cb,
                                                           uint32_t nblocks, const uint32_t* __restrict__ table,
-                                                          const uint32_t* __restrict__ pairs)
+                                                          const uint32_t* __restrict__ pairs, EsCrowd crowd)
 {
     extern __shared__ uint32_t cnt[];              // kBlock * wpw words, then as many bits
     // contiguous ranges of blocks per XCD (workgroups go to the XCDs in turn)
@@ -513,6 +586,37 @@ __global__ __launch_bounds__(kBlock) void k_es_score_bins(EsRun st, int par, int
     const uint32_t bin = (block * bn) >> cb, in_bin = (block * bn) & ((1u << cb) - 1u);
     const uint32_t* row = table + (size_t)chunk * kBinTableStride + bin;
     const uint32_t p0 = row[0], p1 = row[1];
+    const uint32_t place = crowd.place[(size_t)chunk * kBins + bin];
+    if (place) {                                   // counted by k_es_crowd
+        u64* hc = crowd.hc + (((size_t)place - 1) << cb) + in_bin;
+        uint32_t* was_seen = crowd.seen + ((((size_t)place - 1) << cb) + in_bin) / 32;
+        u64 out0 = 0ull, out1 = 0ull;
+        for (int i0 = 0; i0 < st.wpw; i0 += kTurn) {
+            u64 h[kTurn];
+            uint32_t bits[kTurn], h0[kTurn], h1[kTurn];
+            bool on[kTurn];
+#pragma unroll
+            for (int u = 0; u < kTurn; ++u) {
+                const uint32_t rel = (uint32_t)(wave * st.wpw + i0 + u) * 64u + lane;
+                h[u] = i0 + u < st.wpw ? hc[rel] : 0ull;
+                bits[u] = i0 + u < st.wpw ? was_seen[rel >> 5] : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < kTurn; ++u) {
+                const uint32_t rel = (uint32_t)(wave * st.wpw + i0 + u) * 64u + lane;
+                on[u] = h[u] != 0ull || ((bits[u] >> (rel & 31u)) & 1u);
+                if (h[u]) hc[rel] = 0ull;
+                if (bits[u] && (rel & 31u) == 0u) was_seen[rel >> 5] = 0u;
+                h0[u] = (uint32_t)h[u];
+                h1[u] = (uint32_t)(h[u] >> 32);
+            }
+            es_score_words(st, block * (bn / 64) + wave * st.wpw, i0, on, h0, h1, first, fixed, P, S0, S1, out0, out1);
+        }
+        const uint32_t word0 = block * (bn / 64) + wave * st.wpw;
+        if (lane < st.wpw) { st.mv0[word0 + lane] = out0; st.mv1[word0 + lane] = out1; }
+        es_store_movers(st, (u64)__popcll(out0), (u64)__popcll(out1), block);
+        return;
+    }
     const bool narrow = p1 - p0 <= 65535u;
     const int rounds = narrow ? 1 : 2;
     const uint32_t sub = bn / rounds;              // nodes per round
@@ -975,6 +1079,8 @@ struct EsShape {
     int wpw = 1, awpw = 1, cb = 0;
     bool binned = false;
     int64_t nodes = 0;                     // room for the state: the nodes and the groups' padding
+    uint32_t crowd_limit = 0;              // binned: a bin of more pairs is crowded ...
+    int64_t crowd_bins = 0;                // ... and most bins of a chunk that can be
     int64_t bn() const { return (int64_t)kBlock * wpw; }
     int64_t an() const { return (int64_t)kBlock * awpw; }
     int64_t padded(int64_t nv) const { return (nv + an() - 1) / an() * an(); }
@@ -982,6 +1088,9 @@ struct EsShape {
 constexpr int kBinWaveWords = 32;
 constexpr int64_t kBinMinNodes = 1ll << 22;
 constexpr int64_t kBinMaxChunks = 8192;
+constexpr int64_t kCrowdMin = 65535, kCrowdMean = 8;         // a crowded bin: more pairs than these, and than so many bins hold on
+                                                             // average (their counts then take a byte per node at most)
+constexpr unsigned kCrowdGrid = 512;                         // workgroups of k_es_crowd: one per CU at a time
 // n: nodes of the run; groups: most groups side by side; ends: of a chunk's edge ends over all groups; bins: false
 // where there was no memory for the pairs (the counts take 8 bytes per node, the pairs up to 16)
 EsShape es_shape(int64_t n, int64_t groups, int64_t ends, int64_t chunks, bool bins = true)
@@ -1004,6 +1113,11 @@ EsShape es_shape(int64_t n, int64_t groups, int64_t ends, int64_t chunks, bool b
         s.awpw = s.wpw;
     }
     s.nodes = room();
+    if (s.binned) {
+        const int64_t nbins = (s.nodes + (1ll << s.cb) - 1) >> s.cb, most = kCrowdMean * (ends / nbins + 1);
+        s.crowd_limit = (uint32_t)(most > kCrowdMin ? most : kCrowdMin);
+        s.crowd_bins = ends / ((int64_t)s.crowd_limit + 1);
+    }
     return s;
 }
 
@@ -1014,6 +1128,7 @@ struct EsMemory {
     uint32_t* blk_group = nullptr;
     u64* hc = nullptr;
     uint32_t *table = nullptr, *cursors = nullptr, *pairs = nullptr;
+    EsCrowd crowd{};
     size_t table_words = 0, bytes = 0;
 
     void layout(uint8_t* ws, const EsShape& sh, int64_t ngroups, int64_t ends, int64_t chunks, double* est_out)
@@ -1040,6 +1155,11 @@ struct EsMemory {
             take(table, table_words);
             take(cursors, (size_t)chunks * kBins);
             take(pairs, (size_t)ends);
+            take(crowd.place, (size_t)chunks * kBins);
+            take(crowd.bins, (size_t)chunks);
+            take(crowd.hc, (size_t)sh.crowd_bins << sh.cb);
+            take(crowd.seen, ((size_t)sh.crowd_bins << sh.cb) / 32);
+            crowd.limit = sh.crowd_limit;
         } else {
             take(hc, (size_t)nodes);
         }
@@ -1061,7 +1181,7 @@ void es_fill(hipStream_t stream, void* p, size_t bytes, u64 value)
 // One run: everything from the cleared state to the last chunk's spill is enqueued.  groups_host: its groups, in the
 // order of their nodes (also at mem.groups on the device, with mem.blk_group filled).  check(): called once the first chunk's seeds are
 // counted and flags[] is complete, before anything uses the labels; its answer other than GREM_OK ends the run.
-// est_nodes: entries of est to clear.  *par_out: which copy of the sizes is the final one.
+// check() waits for the stream where the run is binned.  est_nodes: entries of est to clear.  *par_out: which copy of the sizes is the final one.
 template <typename Check>
 int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vector<EsGroup>& groups, int64_t nodes, int64_t est_nodes,
            const int32_t* src, const int32_t* dst, const int32_t* seed, int32_t mode, Check&& check, int* par_out)
@@ -1080,12 +1200,15 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
     es_fill(stream, st.Lb, (size_t)nodes, ~0ull);
     es_fill(stream, st.est, (size_t)est_nodes * 16, 0ull);
     es_fill(stream, st.mark, (size_t)nodes / 8, 0ull);
+    std::vector<uint32_t> crowded;                             // per chunk: its crowded bins
     if (sh.binned) {
         es_fill(stream, mem.table, align256((size_t)chunks * kBinTableStride * 4), 0ull);
         // (workgroups of several tiles each: a workgroup's 1024 counts are added to the table once)
         const int parts = grid_for((most + kBinTile - 1) / kBinTile, 4, 256);
         hipLaunchKernelGGL(k_es_hist, dim3((unsigned)parts, ng, (unsigned)chunks), dim3(kBlock), 0, stream, src, dst, st, sh.cb, mem.table);
-        hipLaunchKernelGGL(k_es_hist_scan, dim3((unsigned)chunks), dim3(kBins), 0, stream, mem.table, mem.cursors);
+        hipLaunchKernelGGL(k_es_hist_scan, dim3((unsigned)chunks), dim3(kBins), 0, stream, mem.table, mem.cursors, mem.crowd);
+        crowded.resize((size_t)chunks);
+        if (hipMemcpyAsync(crowded.data(), mem.crowd.bins, (size_t)chunks * 4, hipMemcpyDeviceToHost, stream) != hipSuccess) return GREM_ERR_HIP;
     } else {
         es_fill(stream, mem.hc, (size_t)nodes * 8, 0ull);
     }
@@ -1094,11 +1217,18 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
     hipLaunchKernelGGL(k_es_seed_sizes, dim3((ng + 255) / 256), dim3(256), 0, stream, st);
     const int rc = check();
     if (rc != GREM_OK) return rc;
+    for (int64_t i = 0; i < (int64_t)crowded.size(); ++i)
+        if (crowded[(size_t)i]) {
+            es_fill(stream, mem.crowd.hc, ((size_t)sh.crowd_bins << sh.cb) * 8, 0ull);
+            es_fill(stream, mem.crowd.seen, ((size_t)sh.crowd_bins << sh.cb) / 8, 0ull);
+            break;
+        }
     const size_t slab = sh.awpw > kApplyByNode ? (size_t)kBlock * sh.awpw : 0;
     const size_t bins_lds = (size_t)sh.bn() * 4 + (size_t)sh.bn() / 8;
     if ((slab && hipFuncSetAttribute((const void*)k_es_apply, hipFuncAttributeMaxDynamicSharedMemorySize, (int)slab) != hipSuccess) ||
         (sh.binned &&
          (hipFuncSetAttribute((const void*)k_es_bin, hipFuncAttributeMaxDynamicSharedMemorySize, kBinTile * 8) != hipSuccess ||
+          hipFuncSetAttribute((const void*)k_es_crowd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bins_lds) != hipSuccess ||
           hipFuncSetAttribute((const void*)k_es_score_bins, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bins_lds) != hipSuccess)))
         return GREM_ERR_HIP;
     bool profile;
@@ -1128,9 +1258,12 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
                 if (i * g.c_size < g.m) es_prof.edges += g.m - i * g.c_size < g.c_size ? g.m - i * g.c_size : g.c_size;
         }
         const int first = i == 0 ? 1 : 0;
+        if (sh.binned && crowded[(size_t)i])
+            hipLaunchKernelGGL(k_es_crowd, dim3(kCrowdGrid), dim3(kBlock), bins_lds, stream, i, sh.cb, (uint32_t)sh.bn(), blocks,
+                               (const uint32_t*)mem.table, (const uint32_t*)mem.pairs, mem.crowd);
         if (sh.binned)
             hipLaunchKernelGGL(k_es_score_bins, dim3((blocks + 7) / 8 * 8), dim3(kBlock), bins_lds, stream, st, par, first, fixed, i, sh.cb,
-                               blocks, (const uint32_t*)mem.table, (const uint32_t*)mem.pairs);
+                               blocks, (const uint32_t*)mem.table, (const uint32_t*)mem.pairs, mem.crowd);
         else
             hipLaunchKernelGGL(k_es_score, dim3(blocks), dim3(kBlock), 0, stream, st, par, first, fixed, mem.hc);
         if (first) continue;
@@ -1295,7 +1428,9 @@ int grem_recursive_bisection(const int32_t* src, const int32_t* dst, int64_t m, 
             hipLaunchKernelGGL(k_es_blk_groups, dim3(ng), dim3(256), 0, stream, (const EsGroup*)mem.groups, mem.blk_group);
             int par = 0;
             // a bad seed is looked for at the end of the level: until then it only leaves a node without a label
-            const int rc = es_run(stream, mem, sh, groups, nodes, nodes, cur_s, cur_d, cur_seed, mode, [] { return GREM_OK; }, &par);
+            const int rc = es_run(stream, mem, sh, groups, nodes, nodes, cur_s, cur_d, cur_seed, mode, [&] {
+                return sh.binned && hipStreamSynchronize(stream) != hipSuccess ? GREM_ERR_HIP : GREM_OK;
+            }, &par);
             if (rc != GREM_OK) return fail(rc);
             hipLaunchKernelGGL(k_rb_count, dim3(blocks), dim3(kBlock), 0, stream, mem.st);
             hipLaunchKernelGGL(k_rb_children, dim3(blocks), dim3(kBlock), 0, stream, mem.st, par, cur_gof, next_bits, packed, gof_next,
