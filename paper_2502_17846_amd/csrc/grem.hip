@@ -54,6 +54,7 @@ constexpr int64_t kMinSlices = 256;        // slices per chunk wanted: one per C
                                            // share a tile's row of mover counts, never more than 256 tiles)
 constexpr int64_t kMaxSegments = 1ll << 22;   // chunks * column blocks
 constexpr int64_t kCutPackMinN = 1 << 20;  // edge cut: int32 labels of more vertices outgrow an XCD's 4 MB of L2
+constexpr int64_t kPlaceGrid = 1024;       // workgroups of k_tp_place wanted: four per CU
 constexpr int kMaxParts = kPlanParts;      // parts of a slice (hub share) in the re-layout
 
 // ---- process-wide state: the optional workspace and the measurement aids --------------------------
@@ -563,6 +564,9 @@ int build_plan(PlanData &P, const RowT *rowptr, const int32_t *colidx, int64_t n
     const size_t place_fixed = tp_place_fixed_bytes(nbg, batch, maxruns);
     const uint32_t capP = (uint32_t)place_cap(place_room, batch);
     const size_t place_lds = place_fixed + (size_t)capP * 4;
+    const int64_t place_wgs = (int64_t)geo.ngroups * geo.nch;
+    int64_t split = (kPlaceGrid + place_wgs - 1) / place_wgs;      // (no more than a batch of rows each)
+    if (split > (d.nr + batch - 1) / batch) split = (d.nr + batch - 1) / batch;
     L.memset(tb.cnt, 0, subs * 4);
     if (L.err || !set_lds((const void *)k_tp_group<RowT, false>, groupR_lds) ||
         !set_lds((const void *)k_tp_group<RowT, true>, groupS_lds) ||
@@ -595,8 +599,8 @@ int build_plan(PlanData &P, const RowT *rowptr, const int32_t *colidx, int64_t n
                            (int64_t)rows_all, (u64 *)nullptr, (int64_t)0);
     });
     L.run(GREM_KERNEL_RELAYOUT, [&] {
-        hipLaunchKernelGGL(k_tp_place, dim3((unsigned)((int64_t)geo.ngroups * geo.nch)), dim3(kPlaceThreads), place_lds,
-                           stream, n, pl, tb, U, P.T, P.R, batch, capP);
+        hipLaunchKernelGGL(k_tp_place, dim3((unsigned)(place_wgs * split)), dim3(kPlaceThreads), place_lds,
+                           stream, n, pl, tb, U, P.T, P.R, batch, capP, (int)split);
     });
     temp.release_to(tmark);
     if (L.err) { P.T = nullptr; return L.err; }

@@ -799,9 +799,10 @@ __global__ __launch_bounds__(1024) void k_tp_scan(u64 *__restrict__ a0, int64_t 
 }
 
 // ------------------------------------------------------------------------------------------------
-// Re-layout, step 2: workgroup c * ngroups + g moves the runs of block group g of every unit of
-// chunk c (slice parts, then share parts) from U to their sub-segments, `batch` rows (slices, then
-// shares) at a time.  In T the sub-segments of consecutive rows are adjacent, so the tuples of a
+// Re-layout, step 2: workgroup (c * ngroups + g) * split + s moves the runs of block group g of the s-th
+// share of the units of chunk c (slice parts, then share parts) from U to their sub-segments, `batch` rows (slices,
+// then shares) at a time.  split: 1, more where the chunks and groups alone would leave the chip idle (27M entries in 16
+// chunks of one group: 6.5 ms a plan with slices of 2048 rows, 12 with the 512 that the score wants, 1.7 split).  In T the sub-segments of consecutive rows are adjacent, so the tuples of a
 // batch form one piece per block of the group; the pieces are put together in LDS, pad tuples
 // included (row field 2048: the score kernel ignores them; they fill every sub-segment up to a
 // multiple of kSubPad), and written out contiguously: the columns (24 bytes per group of eight) to T piece by
@@ -840,9 +841,10 @@ __device__ __host__ inline size_t tp_place_fixed_bytes(int nbg, int batch, int m
 
 __global__ __launch_bounds__(kPlaceThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_tp_place(
     int64_t n, SweepPlan pl, TpTables tb, const uint32_t *__restrict__ U, uint32_t *__restrict__ T, uint16_t *__restrict__ R, int batch,
-    uint32_t cap) {
+    uint32_t cap, int split) {
     extern __shared__ u64 smem64[];
-    const int g = (int)(blockIdx.x % (unsigned)tb.ngroups), c = (int)(blockIdx.x / (unsigned)tb.ngroups);
+    const int s = (int)(blockIdx.x % (unsigned)split);
+    const int g = (int)(blockIdx.x / (unsigned)split % (unsigned)tb.ngroups), c = (int)(blockIdx.x / (unsigned)split / (unsigned)tb.ngroups);
     const int jb0 = g << tb.gb;
     const int nbg = (jb0 + (1 << tb.gb)) <= tb.nblk ? (1 << tb.gb) : tb.nblk - jb0;
     const int npmax = tb.npr > tb.nps ? tb.npr : tb.nps;
@@ -884,12 +886,13 @@ __global__ __launch_bounds__(kPlaceThreads) __attribute__((amdgpu_waves_per_eu(8
         R[at] = (uint16_t)(row >= (uint32_t)kSliceRows ? 1u : row << 5);
     };
     for (int part = 0; part < 2; ++part) {                      // 0: regular slices, 1: hub shares
-        const int count = part == 0 ? nsl_c : nvs;
+        const int all = part == 0 ? nsl_c : nvs;                // rows of the chunk, and this workgroup's
+        const int count = (int)((int64_t)all * (s + 1) / split);
         const int np = part == 0 ? tb.npr : tb.nps;
         const int rfirst = part == 0 ? 0 : tb.nsl;              // the part's first row of the chunk
         const uint32_t *lot = part == 0 ? tb.lo : tb.loh;
         const u64 *ust = part == 0 ? tb.ustart : tb.ustart_h;
-        int i0 = 0;
+        int i0 = (int)((int64_t)all * s / split);
         while (i0 < count) {
             // the largest batch (<= `batch` rows) whose pieces fit the stage; at least one row
             int nb = count - i0 < batch ? count - i0 : batch;
@@ -951,10 +954,10 @@ __global__ __launch_bounds__(kPlaceThreads) __attribute__((amdgpu_waves_per_eu(8
             } else {
                 // the slow way: every group of the sub-segments gets its first word, its columns start at zero
                 __syncthreads();                                // sub0 / sublen / ddv / sbase are complete
-                for (int z = 0; z < nb * nbg; ++z) {
+                for (int z = wave; z < nb * nbg; z += kNW) {
                     const int j = z % nbg;
                     const u64 first = (tbase[j] + sub0[z]) >> 3, dest = (sbase[z / nbg] + ddv[z]) >> 3;
-                    for (uint32_t q = tid; q < (sublen[z] >> 3); q += kPlaceThreads) {
+                    for (uint32_t q = lane; q < (sublen[z] >> 3); q += 64) {
                         uint32_t *grp = T + (first + q) * 6ull;
                         grp[0] = (uint32_t)(dest + q);
                         grp[1] = 0; grp[2] = 0; grp[3] = 0; grp[4] = 0; grp[5] = 0;
@@ -974,7 +977,20 @@ __global__ __launch_bounds__(kPlaceThreads) __attribute__((amdgpu_waves_per_eu(8
                 if (staged) stage[w] = tuple;
                 else put_entry(j, z, w, tuple);
             };
-            for (int z0 = wave; z0 < nruns; z0 += kNW * kRU) {
+            // (a row that does not fit the stage has few runs, and long ones: all wavefronts share each)
+            for (int z = 0; z < nruns && !staged; ++z) {
+                const uint32_t *from = U + runsrc[z];
+                const uint32_t len = runlen[z], sl = runsl[z];
+                for (uint32_t p = tid; p < len; p += kPlaceThreads * kRU) {
+                    uint32_t u[kRU];
+#pragma unroll
+                    for (int r = 0; r < kRU; ++r) u[r] = p + r * kPlaceThreads < len ? __builtin_nontemporal_load(from + p + r * kPlaceThreads) : 0u;
+#pragma unroll
+                    for (int r = 0; r < kRU; ++r)
+                        if (p + r * kPlaceThreads < len) put(u[r], sl);
+                }
+            }
+            for (int z0 = wave; z0 < nruns && staged; z0 += kNW * kRU) {
                 uint32_t u[kRU][kXU], len[kRU], sl[kRU];
                 const uint32_t *from[kRU];
 #pragma unroll
