@@ -1356,8 +1356,10 @@ int run_edge_cut(const RowT *rowptr, const int32_t *colidx, int64_t n, const int
     if (!rowptr || !colidx || !labels || !out || n < 1 || n > (int64_t)INT32_MAX) return GREM_ERR_ARG;
     hipStream_t s = (hipStream_t)stream;
     const int64_t tiles = (n + kCutTile - 1) / kCutTile;
-    const dim3 grid((unsigned)(tiles < (int64_t)kCutGrid ? tiles : (int64_t)kCutGrid));
-    auto walk = [&](const uint32_t *words, const LabelSpan *span) {
+    // (fixed tiles: one per workgroup, at most 2^20 / 256 of them, unless the call is captured or has no memory)
+    auto walk = [&](const uint32_t *words, LabelSpan *span) {
+        const int64_t most = words ? (int64_t)kCutGrid : 2 * (int64_t)kCutGrid;
+        const dim3 grid((unsigned)(tiles < most ? tiles : most));
         hipLaunchKernelGGL((k_edge_cut<RowT>), grid, dim3(kCutTile), 0, s, rowptr, colidx, n, labels, words, span,
                            (unsigned long long *)out);
         return hipGetLastError() == hipSuccess ? GREM_OK : GREM_ERR_HIP;
@@ -1369,7 +1371,7 @@ int run_edge_cut(const RowT *rowptr, const int32_t *colidx, int64_t n, const int
         hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
         if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
         else if (cap == hipStreamCaptureStatusNone &&
-                 hipMallocAsync((void **)&block, 256 + align_up((size_t)n), s) != hipSuccess) {
+                 hipMallocAsync((void **)&block, align_up(sizeof(LabelSpan)) + align_up((size_t)n), s) != hipSuccess) {
             (void)hipGetLastError();
             block = nullptr;
         }
@@ -1379,7 +1381,7 @@ int run_edge_cut(const RowT *rowptr, const int32_t *colidx, int64_t n, const int
         return walk(nullptr, nullptr);
     }
     LabelSpan *span = (LabelSpan *)block;
-    uint32_t *words = (uint32_t *)(block + 256);
+    uint32_t *words = (uint32_t *)(block + align_up(sizeof(LabelSpan)));
     hipLaunchKernelGGL(k_label_range_init, dim3(1), dim3(64), 0, s, span, (unsigned long long *)out);
     hipLaunchKernelGGL(k_label_range, dim3(2048), dim3(256), 0, s, labels, n, span);
     hipLaunchKernelGGL(k_pack_labels, dim3(2048), dim3(256), 0, s, labels, n, (const LabelSpan *)span, words);

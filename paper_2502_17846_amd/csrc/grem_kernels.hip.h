@@ -1186,6 +1186,7 @@ __global__ __launch_bounds__(256) void k_expand(const LabelT *__restrict__ Lc, i
 // ------------------------------------------------------------------------------------------------
 struct LabelSpan {
     int32_t lo, hi;             // smallest and largest label
+    uint32_t next[8][32];       // k_edge_cut: the turns of each part's tiles that are given out, in lines of their own
 };
 
 __global__ void k_label_range_init(LabelSpan *span, unsigned long long *sum) {
@@ -1194,6 +1195,7 @@ __global__ void k_label_range_init(LabelSpan *span, unsigned long long *sum) {
         span->hi = -0x7fffffff - 1;
         *sum = 0ull;
     }
+    if (threadIdx.x < 8) span->next[threadIdx.x][0] = 0u;
 }
 
 __global__ __launch_bounds__(256) void k_label_range(const int32_t *__restrict__ labels, int64_t n,
@@ -1226,11 +1228,15 @@ __device__ __forceinline__ int packed_label_bits_log2(const LabelSpan &span) {
 }
 
 // In how many parts the columns are taken so that a part's table fits an XCD's 4 MB of L2: 1, 2, 4 or 8 (one per
-// XCD; past 32 MB the parts outgrow the L2 again, but an eighth of the table is still the cheaper one).
-__device__ __forceinline__ int label_table_parts(int64_t n, int lb) {
+// XCD; past 32 MB the parts outgrow the L2 again, but an eighth of the table is still the cheaper one).  Every part
+// streams the rows' offsets and labels and the entries once more (about 12 n + 4 nnz bytes at 4 TB/s, against some 10
+// ps saved per entry looked up), so sparse rows take fewer (100M vertices, one entry each, 16 labels: 5.0 ms from the
+// int32 table, 5.6 in 8 parts, 2.1 in 2).
+__device__ __forceinline__ int label_table_parts(int64_t n, int64_t nnz, int lb) {
     const int64_t bytes = (n << lb) >> 3;
     int parts = 1;
     while (parts < 8 && bytes > ((int64_t)parts << 22)) parts *= 2;
+    while (parts > 1 && (parts - 1) * (3 * n + nnz) > 10 * nnz) parts /= 2;
     return parts;
 }
 
@@ -1252,8 +1258,12 @@ __global__ __launch_bounds__(256) void k_pack_labels(const int32_t *__restrict__
     }
 }
 
-// A workgroup takes tiles of 256 rows in turn, their entries edge-parallel.  words == nullptr: no packed
-// table (small graphs, whose labels the L2 holds as they are).
+// A workgroup takes tiles of 256 rows, their entries edge-parallel.  words == nullptr: no packed table (small graphs, whose
+// labels the L2 holds as they are).  With the columns in parts, a part's tiles make kCutTurns turns (every so-manieth tile)
+// for each of its XCDs' workgroups: the first is fixed, the others go to whoever is free, in the end to workgroups of
+// other parts too (ids in order of degree put half of all look-ups in the first part: 111M vertices, 16 labels: 61 ms
+// with fixed shares, 30 so; a tile at a time from a counter took 43 ms on permuted ids for 22).
+constexpr uint32_t kCutTurns = 8;
 constexpr int kCutTile = 256;
 constexpr unsigned kCutGrid = 2048;        // eight workgroups per CU: one sum each at the one output address
 template <typename RowT>
@@ -1261,7 +1271,7 @@ __global__ __launch_bounds__(kCutTile) void k_edge_cut(const RowT *__restrict__ 
                                                        const int32_t *__restrict__ colidx, int64_t n,
                                                        const int32_t *__restrict__ labels,
                                                        const uint32_t *__restrict__ words,
-                                                       const LabelSpan *__restrict__ span,
+                                                       LabelSpan *__restrict__ span,
                                                        unsigned long long *__restrict__ out) {
     constexpr int tv = kCutTile;
     constexpr int U = 8;                   // entries in flight per thread
@@ -1269,33 +1279,45 @@ __global__ __launch_bounds__(kCutTile) void k_edge_cut(const RowT *__restrict__ 
     __shared__ uint32_t lab[tv];
     __shared__ unsigned long long s_sum;
     const int tid = threadIdx.x;
-    LabelSpan sp{0, 0};
+    __shared__ uint32_t s_turn;
+    int32_t span_lo = 0;
     int lb = -1;
-    if (words) { sp = *span; lb = packed_label_bits_log2(sp); }
+    if (words) { const LabelSpan sp{span->lo, span->hi, {}}; span_lo = sp.lo; lb = packed_label_bits_log2(sp); }
     const int wshift = 5 - lb;             // (used when lb >= 0)
     const uint32_t in_word = (32u >> (lb < 0 ? 0 : lb)) - 1u, mask = lb < 0 ? 0u : (uint32_t)((1ull << (1 << lb)) - 1ull);
     unsigned long long mine = 0;
-    // the share of the columns that this workgroup's XCD looks up (workgroups go to the XCDs in turn)
-    const int parts = lb < 0 || (gridDim.x & 7u) ? 1 : label_table_parts(n, lb);
-    const uint32_t x = blockIdx.x & 7u, per_part = (uint32_t)(((n + parts - 1) / parts + 31) & ~31ll);
-    const uint32_t c0 = parts == 1 ? 0u : (x % parts) * per_part, clen = parts == 1 ? 0x80000000u : per_part;
-    const int64_t first = parts == 1 ? (int64_t)blockIdx.x : (int64_t)(blockIdx.x >> 3) * (8 / parts) + x / parts;
-    const int64_t stride = gridDim.x / parts;
+    // the share of the columns that this workgroup's XCD looks up first (workgroups go to the XCDs in turn)
+    const int parts = lb < 0 || (gridDim.x & 7u) ? 1 : label_table_parts(n, (int64_t)rowptr[n], lb);
+    const uint32_t per_part = (uint32_t)(((n + parts - 1) / parts + 31) & ~31ll);
     const int64_t tiles = (n + tv - 1) / tv;
-    for (int64_t tile = first; tile < tiles; tile += stride) {
+    const uint32_t x = blockIdx.x & 7u, own = gridDim.x / (uint32_t)parts;         // a part's workgroups
+    const int64_t turns = parts == 1 ? (int64_t)own : (int64_t)own * kCutTurns < tiles ? (int64_t)own * kCutTurns : tiles;
+    uint32_t part = x % (uint32_t)parts;
+    int done = 0;                          // parts without a turn left
+    int64_t tile = parts == 1 ? (int64_t)blockIdx.x : (int64_t)(blockIdx.x >> 3) * (8 / parts) + x / parts;
+    for (;; tile += turns) {
+        __syncthreads();                   // the tables of the tile before are read no more
+        while (tile >= tiles && done < parts) {                // (the same for all threads)
+            if (parts == 1) { done = 1; break; }
+            if (tid == 0) s_turn = own + atomicAdd(&span->next[part][0], 1u);
+            __syncthreads();
+            tile = s_turn < turns ? (int64_t)s_turn : tiles;
+            if (tile >= tiles) { ++done; part = part + 1u == (uint32_t)parts ? 0u : part + 1u; }
+            __syncthreads();
+        }
+        if (tile >= tiles) break;
+        const uint32_t c0 = parts == 1 ? 0u : part * per_part, clen = parts == 1 ? 0x80000000u : per_part;
         const int64_t v0 = tile * tv;
         const int64_t left = n - v0;
         const int nv = left < tv ? (int)left : tv;
         const int64_t e0 = (int64_t)rowptr[v0];
         const unsigned long long ne = (unsigned long long)((int64_t)rowptr[v0 + nv] - e0);
-        __syncthreads();                   // the tables of the tile before are read no more
         for (int i = tid; i <= tv; i += tv) rowrel[i] = (uint32_t)((int64_t)rowptr[v0 + (i < nv ? i : nv)] - e0);
         if (tid < nv) lab[tid] = (uint32_t)labels[v0 + tid];
         __syncthreads();
         const int32_t *cbase = colidx + e0;
         if (ne >= (1ull << 32)) {          // (offsets that 32 bits do not hold: row by row, by one of the parts)
-            if (c0 != 0) continue;
-            for (int r = 0; r < nv; ++r)
+            for (int r = 0; r < nv && c0 == 0u; ++r)
                 for (int64_t e = (int64_t)rowptr[v0 + r] + tid; e < (int64_t)rowptr[v0 + r + 1]; e += tv)
                     mine += (uint32_t)labels[colidx[e]] != lab[r] ? 1ull : 0ull;
             continue;
@@ -1317,7 +1339,7 @@ __global__ __launch_bounds__(kCutTile) void k_edge_cut(const RowT *__restrict__ 
                 for (int u = 0; u < U; ++u) got[u] = col[u] >= 0 ? words[(uint32_t)col[u] >> wshift] : 0u;
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-                    got[u] = ((got[u] >> (((uint32_t)col[u] & in_word) << lb)) & mask) + (uint32_t)sp.lo;
+                    got[u] = ((got[u] >> (((uint32_t)col[u] & in_word) << lb)) & mask) + (uint32_t)span_lo;
             } else {
 #pragma unroll
                 for (int u = 0; u < U; ++u) got[u] = col[u] >= 0 ? (uint32_t)labels[col[u]] : 0u;

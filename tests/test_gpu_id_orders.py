@@ -191,3 +191,35 @@ def test_plans_of_few_chunks_are_made_by_the_whole_chip():
         took = _ms(lambda: B.Plan(rp, ci, 1_000_000, 1 << 16).close())
         print(f"[result] {order}: {took:.2f} ms", flush=True)
         assert took <= most
+
+
+# columns looked up in 1, 2, 4 and 8 parts whose turns go to whoever is free, dense and sparse rows (fewer parts)
+@pytest.mark.parametrize("n,m,k", [(3_000_001, 24_000_000, 256), (9_000_001, 60_000_000, 16), (9_000_001, 60_000_000, 256),
+                                   (40_000_003, 200_000_000, 256), (40_000_003, 30_000_000, 256)])
+@pytest.mark.parametrize("order", ["permuted", "by degree"])
+def test_edge_cut_in_parts(n, m, k, order):
+    rp, ci = _csr(n, m, order)
+    labels = torch.randint(0, k, (n,), device=DEV, dtype=torch.int32)
+    want = 0
+    for lo in range(0, n, 1 << 23):
+        hi = min(n, lo + (1 << 23))
+        deg = rp[lo + 1:hi + 1] - rp[lo:hi]
+        own = torch.repeat_interleave(labels[lo:hi], deg)
+        want += int((own != labels[ci[int(rp[lo]):int(rp[hi])].long()]).sum())
+    for _ in range(2):
+        assert int(B.grem_edge_cut(rp, ci, n, labels).item()) == want
+
+
+def test_edge_cut_in_order_of_degree_is_no_slower():
+    # measured 21.5 ms permuted, 30 in order of degree (62 with a fixed share of the tiles to every workgroup; most of what
+    # is left is the first 256 rows, 12.8M entries, on one)
+    n = 111_000_000
+    took = {}
+    for order in ("permuted", "by degree"):
+        rp, ci = _csr(n, 800_000_000, order)
+        labels = torch.randint(0, 16, (n,), device=DEV, dtype=torch.int32)
+        took[order] = _ms(lambda: B.grem_edge_cut(rp, ci, n, labels), 3)
+        print(f"[result] {order}: {took[order]:.1f} ms", flush=True)
+        del rp, ci
+        torch.cuda.empty_cache()
+    assert took["by degree"] <= 2.0 * took["permuted"]
