@@ -1109,13 +1109,21 @@ int run_plain_merged(const RowT *rowptr, const int32_t *colidx, int64_t n, int32
             const unsigned tiles = (unsigned)((len + kAdmitTile - 1) / kAdmitTile);
             LongParts lr{nullptr, nullptr, nullptr, 0u, 0u, (uint32_t)degree, part};
             if (split_long && nrows[(size_t)c] != 0)
-                lr = LongParts{x.row + first[(size_t)c], x.pref + first[(size_t)c], x.ticket + first[(size_t)c], nrows[(size_t)c],
+                lr = LongParts{x.row + first[(size_t)c], x.pref + first[(size_t)c],
+                               nparts[(size_t)c] <= kLongTicketParts ? x.ticket + first[(size_t)c] : (uint32_t *)nullptr, nrows[(size_t)c],
                                nparts[(size_t)c], (uint32_t)degree, part};
             L.run(GREM_KERNEL_SCORE, [&] {
                 hipLaunchKernelGGL((k_score_tile<RowT, LabelT>), dim3(lr.parts + (unsigned)((len + tv - 1) / tv)), dim3(kScoreThreads),
                                    tile_lds, stream, rowptr, colidx, (const LabelT *)st.Lc, (const long long *)now, other, E, st.prop, cnt,
                                    coarse, lo, hi, (int)k, tv, pass, P, standing == kNoneLabelled ? lo : n, standing, store_e, lr);
             });
+            if (lr.rows != 0 && !lr.ticket)
+                L.run(GREM_KERNEL_HUBS, [&] {
+                    constexpr unsigned waves = kScoreThreads / 64;
+                    hipLaunchKernelGGL((k_long_pick<LabelT>), dim3((lr.rows + waves - 1) / waves), dim3(kScoreThreads), (size_t)k * 4, stream,
+                                       lr.row, lr.rows, (const uint32_t *)E, (const LabelT *)st.Lc, (const long long *)now, st.prop, cnt,
+                                       coarse, lo, (int)k, pass, P, standing);
+                });
             L.run(GREM_KERNEL_APPLY, [&] {
                 hipLaunchKernelGGL((k_admit_tiles<LabelT>), dim3(tiles), dim3(kAdmitTile), admit_lds, stream, st.Lc,
                                    (const LabelT *)st.prop, lo, hi, (int)k, P, (const uint32_t *)cnt, (const uint32_t *)coarse, cnt_other,

@@ -26,11 +26,14 @@ constexpr int kLongClasses = 16;         // rows of at least degree * 2^i entrie
 
 // The long rows of a chunk: rows of at least `degree` entries are left out of their tile; their entries are dealt
 // out in parts of `part`, each a workgroup of its own.  Row i of the list has the parts pref[i] .. pref[i + 1) of the
-// chunk (the last row's end at `parts`); the workgroup that finishes a row's last part picks its proposal.
+// chunk (the last row's end at `parts`); the workgroup that finishes a row's last part picks its proposal, or, with more
+// than kLongTicketParts of them, k_long_pick in a launch of its own: finding out who is last takes a write-back of the L2
+// per part (3000 parts: 0.5 ms a chunk step, where a launch takes some 5 us).
+constexpr uint32_t kLongTicketParts = 64;
 struct LongParts {
     const uint32_t *row;
     const uint32_t *pref;
-    uint32_t *ticket;                    // parts done, 0 between chunks
+    uint32_t *ticket;                    // parts done, 0 between chunks; null: k_long_pick follows
     uint32_t rows, parts, degree, part;
 };
 
@@ -153,6 +156,39 @@ __device__ __forceinline__ void add_movers(uint32_t *cnt, uint32_t *coarse, int 
     if (coarse) atomicAdd(&coarse[(size_t)(tile / kPlainCoarse) * k + t], count);
 }
 
+// A wave picks the proposal of the long row v from its complete estimates est(j); room: P - S.
+template <typename LabelT, typename Est>
+__device__ __forceinline__ void propose_long(int64_t v, Est &&est, const uint32_t *room, const LabelT *__restrict__ Lc,
+                                             LabelT *__restrict__ prop, uint32_t *cnt, uint32_t *coarse, int64_t chunk_lo, int k,
+                                             int pass, int standing) {
+    const uint32_t none = LabelTraits<LabelT>::kUnassigned;
+    const uint32_t old = standing == kNoneLabelled ? 0xFFFFFFFFu : (uint32_t)Lc[v];
+    const bool had = standing == kAllLabelled || (standing == kSomeLabelled && old != none);
+    uint32_t best = old;
+    if (!(pass == 0 && had)) best = best_partition(est, room, k, had ? old : 0xFFFFFFFFu, lane_id(), 64);
+    if (lane_id() == 0) {
+        prop[v - chunk_lo] = (LabelT)best;
+        if (!had || best != old) add_movers(cnt, coarse, k, (uint32_t)((v - chunk_lo) / kAdmitTile), best, 1u);
+    }
+}
+
+// a wave per long row of the chunk
+template <typename LabelT>
+__global__ __launch_bounds__(kScoreThreads) void k_long_pick(const uint32_t *__restrict__ row, uint32_t rows,
+                                                             const uint32_t *__restrict__ E, const LabelT *__restrict__ Lc,
+                                                             const long long *__restrict__ S, LabelT *__restrict__ prop, uint32_t *cnt,
+                                                             uint32_t *coarse, int64_t chunk_lo, int k, int pass, long long P,
+                                                             int standing) {
+    extern __shared__ uint32_t smem[];                      // k
+    for (int j = threadIdx.x; j < k; j += kScoreThreads) smem[j] = (uint32_t)(P - S[j]);
+    __syncthreads();
+    const uint32_t i = blockIdx.x * (kScoreThreads / 64) + (threadIdx.x >> 6);
+    if (i >= rows) return;
+    const int64_t v = (int64_t)row[i];
+    const uint32_t *erow = E + (size_t)v * (size_t)k;
+    propose_long(v, [&](int j) { return erow[j]; }, smem, Lc, prop, cnt, coarse, chunk_lo, k, pass, standing);
+}
+
 // What bounds it: the look-up of every entry's label (a miss of 64 bytes once the labels outgrow the L2) and the
 // tile's estimates, read before the counting starts and written once; on small graphs latency, hence tiles small
 // enough for 2048 workgroups per chunk and g = 256 / tv lanes per vertex for the proposals.  The last pass keeps the
@@ -200,6 +236,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_score_tile(
         uint32_t *erow = E + (size_t)v * (size_t)k;
         for (int j = tid; j < k; j += kScoreThreads)
             if (hist[j]) atomicAdd(&erow[j], hist[j] << sh);
+        if (!lr.ticket) return;
         // the row's last part to end, whichever it is, sees the others' counts: they are out before their tickets
         __threadfence();
         __syncthreads();
@@ -212,17 +249,8 @@ __global__ __launch_bounds__(kScoreThreads) void k_score_tile(
         __syncthreads();
         if (!s_last || tid >= 64) return;
         __threadfence();
-        const uint32_t old = standing == kNoneLabelled ? 0xFFFFFFFFu : (uint32_t)Lc[v];
-        const bool had = standing == kAllLabelled || (check && old != none);
-        uint32_t best = old;
-        if (!(pass == 0 && had))
-            best = best_partition([&](int j) { return __hip_atomic_load(erow + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }, room, k,
-                                  had ? old : 0xFFFFFFFFu, tid, 64);
-        if (tid == 0) {
-            prop[v - chunk_lo] = (LabelT)best;
-            if (!had || best != old)
-                add_movers(cnt, coarse, k, (uint32_t)((v - chunk_lo) / kAdmitTile), best, 1u);
-        }
+        propose_long(v, [&](int j) { return __hip_atomic_load(erow + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }, room, Lc, prop, cnt,
+                     coarse, chunk_lo, k, pass, standing);
         return;
     }
 
