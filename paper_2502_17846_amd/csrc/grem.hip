@@ -56,6 +56,7 @@ constexpr int64_t kMaxSegments = 1ll << 22;   // chunks * column blocks
 constexpr int64_t kCutPackMinN = 1 << 20;  // edge cut: int32 labels of more vertices outgrow an XCD's 4 MB of L2
 constexpr int64_t kPlaceGrid = 1024;       // workgroups of k_tp_place wanted: four per CU
 constexpr int kMaxParts = kPlanParts;      // parts of a slice (hub share) in the re-layout
+constexpr size_t kScoreLds16 = 150 * 1024, kScoreLds32 = 158 * 1024;   // k_tp_score's LDS: with the static counters for k <= 16
 
 // ---- process-wide state: the optional workspace and the measurement aids --------------------------
 struct Global {
@@ -277,9 +278,13 @@ struct Launcher {
     }
 };
 
-bool set_lds(const void *f, size_t bytes) {
+size_t apply_lds_bytes(int k) { return (size_t)(1 + kAdmitThreads / 64 + 2) * (size_t)k * 4; }
+
+// `most`: what any call of the kernel may need.  The limit is one of the process, so it is always the same: set to a call's own
+// need, it could fall between another thread's setting and its launch.
+bool set_lds(const void *f, size_t bytes, size_t most) {
     return bytes <= 64 * 1024 ||
-           hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
+           hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most) == hipSuccess;
 }
 
 // ======================================================================================================
@@ -454,8 +459,8 @@ int build_plan(PlanData &P, const RowT *rowptr, const int32_t *colidx, int64_t n
     {
         auto score_fits = [&](int kk) {
             const size_t dyn = ((size_t)geo.srows / 2 + (size_t)share_hubs * kk + 3 * (size_t)kk) * 4;
-            if (kk <= 16) return dyn + (size_t)geo.srows * 32 <= 150 * 1024;
-            return geo.cb <= 16 && dyn + (size_t)geo.srows * 64 <= 158 * 1024;    // (a byte per label in the look-up's LDS)
+            if (kk <= 16) return dyn + (size_t)geo.srows * 32 <= kScoreLds16;
+            return geo.cb <= 16 && dyn + (size_t)geo.srows * 64 <= kScoreLds32;    // (a byte per label in the look-up's LDS)
         };
         int max_k = kmax;
         while (max_k > 1 && !score_fits(max_k) && k == 0) --max_k;
@@ -568,9 +573,8 @@ int build_plan(PlanData &P, const RowT *rowptr, const int32_t *colidx, int64_t n
     int64_t split = (kPlaceGrid + place_wgs - 1) / place_wgs;      // (no more than a batch of rows each)
     if (split > (d.nr + batch - 1) / batch) split = (d.nr + batch - 1) / batch;
     L.memset(tb.cnt, 0, subs * 4);
-    if (L.err || !set_lds((const void *)k_tp_group<RowT, false>, groupR_lds) ||
-        !set_lds((const void *)k_tp_group<RowT, true>, groupS_lds) ||
-        !set_lds((const void *)k_tp_place, place_lds)) {
+    if (L.err || !set_lds((const void *)k_tp_group<RowT, false>, groupR_lds, kGroupLds) ||
+        !set_lds((const void *)k_tp_group<RowT, true>, groupS_lds, kGroupLds)) {
         temp.release_to(tmark);
         P.T = nullptr;
         return GREM_ERR_HIP;
@@ -794,11 +798,13 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
         else if (geo.srows == 1024) rows(std::integral_constant<int, 1024>{});
         else rows(std::integral_constant<int, kSliceRows>{});
     };
-    bool lds_ok = wide ? set_lds((const void *)k_tp_lookup<true, false, 8>, lookup_lds)
-                       : set_lds((const void *)k_tp_lookup<true, false, 4>, lookup_lds) &&
-                             set_lds((const void *)k_tp_lookup<true, true, 4>, lookup_lds);
+    constexpr size_t most_lookup = (size_t)1 << (kMaxColBits - 1);         // (a byte per label: 2^16 columns at most)
+    bool lds_ok = wide ? set_lds((const void *)k_tp_lookup<true, false, 8>, lookup_lds, most_lookup)
+                       : set_lds((const void *)k_tp_lookup<true, false, 4>, lookup_lds, most_lookup) &&
+                             set_lds((const void *)k_tp_lookup<true, true, 4>, lookup_lds, most_lookup);
+    const size_t most_score = wide ? kScoreLds32 : kScoreLds16 - (size_t)geo.srows * 32;   // (one kernel per number of rows)
     for (int skip = 0; skip < 2; ++skip)
-        with_score(skip != 0, [&](auto kernel, auto *) { lds_ok = lds_ok && set_lds((const void *)kernel, score_lds); });
+        with_score(skip != 0, [&](auto kernel, auto *) { lds_ok = lds_ok && set_lds((const void *)kernel, score_lds, most_score); });
     if (!lds_ok) return GREM_ERR_HIP;
     L.memset(t.Hhub, 0, (hubs_in_admission ? 2 : 1) * ((size_t)P.max_chunk_hubs + 1) * (size_t)k * 4);
     const size_t coarse_row = (size_t)(kAdmitTilesMax / kCoarseTiles) * (size_t)k;
@@ -1048,8 +1054,7 @@ int run_plain_merged(const RowT *rowptr, const int32_t *colidx, int64_t n, int32
     const size_t cells = (size_t)tiles_full * (size_t)k;
     const size_t coarse_cells = x.coarse ? (size_t)((tiles_full + kPlainCoarse - 1) / kPlainCoarse) * (size_t)k : 0;
     const size_t admit_lds = admit_tiles_lds(k), spill_lds = spill_tiles_lds(k);
-    if (!set_lds((const void *)k_admit_tiles<LabelT>, admit_lds) || !set_lds((const void *)k_spill_tiles<LabelT>, spill_lds))
-        return GREM_ERR_HIP;
+    // (at most 64 KB, which every kernel may have: k <= kPlainMaxK)
 
     // the long rows, chunk by chunk
     std::vector<uint32_t> nrows, nparts, first;
@@ -1168,14 +1173,14 @@ int run_plain(const RowT *rowptr, const int32_t *colidx, int64_t n, int32_t k, d
     if (maxdeg * (unsigned long long)tv >= (1ull << 31)) return GREM_ERR_RANGE;
     const size_t score_lds = use_lds ? ((size_t)tv * k + tv + 1 + k) * 4 : ((size_t)tv + 1 + k) * 4;
     const size_t count_lds = (size_t)k * 4;
-    const size_t apply_lds = ((size_t)k + (size_t)(kAdmitThreads / 64) * k + 2 * (size_t)k) * 4;
-    if (!set_lds((const void *)k_apply<LabelT, false>, apply_lds)) return GREM_ERR_HIP;
+    const size_t apply_lds = apply_lds_bytes(k);
+    if (!set_lds((const void *)k_apply<LabelT, false>, apply_lds, apply_lds_bytes(GREM_MAX_K))) return GREM_ERR_HIP;
 
     // rows this long are taken out of their tile and spread over a grid of their own
     const int long_degree = o.long_row_degree ? o.long_row_degree : kLongRowDegree;
     const bool split_long = maxdeg >= (unsigned long long)long_degree;
     const size_t long_lds = (size_t)k * 4;
-    if (split_long && !set_lds((const void *)k_long_rows<RowT, LabelT>, long_lds)) return GREM_ERR_HIP;
+    // (at most 16 KB)
 
     L.mark();
     for (int pass = 0; pass <= R && !L.err; ++pass) {

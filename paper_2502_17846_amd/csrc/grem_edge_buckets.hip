@@ -710,10 +710,12 @@ extern "C" int grem_edge_buckets(const int32_t* src, const int32_t* dst, int64_t
     uint32_t* H = (uint32_t*)(ws + o_h);
     uint32_t* partial = (uint32_t*)(ws + o_part);
     const size_t lds = (size_t)k2 * 4;
+    // (the limits are the process's: always what any call may need)
     if (lds > 48 * 1024) {
-        if (hipFuncSetAttribute((const void*)k_eb_hist, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-            hipFuncSetAttribute((const void*)k_eb_hist_keys, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-            hipFuncSetAttribute((const void*)k_eb_scatter, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        constexpr int most = kEbMaxK * kEbMaxK * 4;
+        if (hipFuncSetAttribute((const void*)k_eb_hist, hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess ||
+            hipFuncSetAttribute((const void*)k_eb_hist_keys, hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess ||
+            hipFuncSetAttribute((const void*)k_eb_scatter, hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess)
             return fail(GREM_ERR_HIP);
     }
     auto grid = [](int64_t items, int64_t cap) { int64_t g = (items + 255) / 256; if (g < 1) g = 1; if (g > cap) g = cap; return (int)g; };
@@ -771,7 +773,8 @@ extern "C" int grem_edge_buckets(const int32_t* src, const int32_t* dst, int64_t
     hipLaunchKernelGGL(k_eb_colscan, dim3(grid(cells, 1 << 20)), dim3(256), 0, stream, H, tiles, k2, S, seg_len, partial);
     if (tile == kEbMinTile && k2 <= kEbLdsBuckets) {
         const size_t lds2 = eb_scatter_lds_bytes(k2);
-        if (hipFuncSetAttribute((const void*)k_eb_scatter_lds, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2) != hipSuccess)
+        if (hipFuncSetAttribute((const void*)k_eb_scatter_lds, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)eb_scatter_lds_bytes(kEbLdsBuckets)) != hipSuccess)
             return fail(GREM_ERR_HIP);
         hipLaunchKernelGGL(k_eb_scatter_lds, dim3((unsigned)tiles), dim3(kEbScatterThreads), lds2, stream, src, dst, m, key16, k2, key_bits, H,
                            out_src, out_dst);

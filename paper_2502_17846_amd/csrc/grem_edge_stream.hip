@@ -1225,7 +1225,8 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
         }
     const size_t slab = sh.awpw > kApplyByNode ? (size_t)kBlock * sh.awpw : 0;
     const size_t bins_lds = (size_t)sh.bn() * 4 + (size_t)sh.bn() / 8;
-    if ((slab && hipFuncSetAttribute((const void*)k_es_apply, hipFuncAttributeMaxDynamicSharedMemorySize, (int)slab) != hipSuccess) ||
+    // (always what any run may need: the limit is the process's, and other threads' runs are of other sizes)
+    if ((slab && hipFuncSetAttribute((const void*)k_es_apply, hipFuncAttributeMaxDynamicSharedMemorySize, kBlock * kMaxWaveWords) != hipSuccess) ||
         (sh.binned &&
          (hipFuncSetAttribute((const void*)k_es_bin, hipFuncAttributeMaxDynamicSharedMemorySize, kBinTile * 8) != hipSuccess ||
           hipFuncSetAttribute((const void*)k_es_crowd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bins_lds) != hipSuccess ||

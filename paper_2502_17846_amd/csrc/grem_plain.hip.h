@@ -375,7 +375,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_score_tile(
 // chunk's movers.  rej / ocnt: the rejected new vertices of the tile, a bit per vertex and their number (first
 // pass).  Clears the other pair of tables.
 // LDS: base[k], tot[k], dS[k], room[k] (64 bits), wcnt[16][k] (16 bits)
-inline size_t admit_tiles_lds(int k) { return (size_t)k * (3 * 4 + 8 + (kAdmitTile / 64) * 2) + 16; }
+constexpr size_t admit_tiles_lds(int k) { return (size_t)k * (3 * 4 + 8 + (kAdmitTile / 64) * 2) + 16; }
 
 template <typename LabelT>
 __global__ __launch_bounds__(kAdmitTile) void k_admit_tiles(
@@ -482,7 +482,7 @@ __global__ __launch_bounds__(kAdmitTile) void k_admit_tiles(
 // read from Sin and written by workgroup 0 to Sout: the a smallest partitions that are level at the end share what is
 // left over, the others keep theirs.
 // LDS: Sl[k], sorted[k], C[k + 1] (64 bits), rnk[k], list[k]
-inline size_t spill_tiles_lds(int k) { return (size_t)k * (3 * 8 + 2 * 4) + 16; }
+constexpr size_t spill_tiles_lds(int k) { return (size_t)k * (3 * 8 + 2 * 4) + 16; }
 
 template <typename LabelT>
 __global__ __launch_bounds__(kAdmitTile) void k_spill_tiles(LabelT *__restrict__ Lc, int64_t chunk_lo, int k,
@@ -572,5 +572,7 @@ __global__ __launch_bounds__(kAdmitTile) void k_spill_tiles(LabelT *__restrict__
         __syncthreads();
     }
 }
+
+static_assert(admit_tiles_lds(kPlainMaxK) <= 64 * 1024 && spill_tiles_lds(kPlainMaxK) <= 64 * 1024, "LDS that needs no asking for");
 
 }  // namespace grem

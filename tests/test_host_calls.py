@@ -1,0 +1,108 @@
+"""What the library's host code asks of the HIP runtime, recorded by a stand-in for it (fake_hip.c: memory is host
+memory, kernels do not run): how often a call waits for the device, the limits it sets, and which kernels it falls back
+on where there is no memory."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIB = os.path.join(os.path.dirname(HERE), "paper_2502_17846_amd", "libgrem.so")
+
+PRELUDE = """
+import ctypes, sys
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+fake.fake_text.restype = ctypes.c_char_p
+I, L, D = ctypes.c_int32, ctypes.c_int64, ctypes.c_double
+keep = []
+def mem(n):
+    keep.append(ctypes.create_string_buffer(n + 64))
+    a = ctypes.addressof(keep[-1])
+    return ctypes.c_void_p(a + (-a) % 64)
+def reset(limit=2**62):
+    fake.fake_reset(ctypes.c_size_t(limit))
+def text():
+    return [l.split(" ") for l in fake.fake_text().decode().splitlines()]
+def stream(n, m, chunks=4):
+    return lib.grem_edge_stream_bipartition(ends, ends, L(m), L(n), L(-(-m // chunks)), L(n), big, I(0), big, None, None, None)
+def buckets(n, m, k):
+    return lib.grem_edge_buckets(ends, ends, L(m), L(n), big, I(k), big, big, big, None)
+def partition(n, k, chunk, passes=1, options=None):
+    return lib.grem_partition_opt(big, I(32), ends, L(n), I(k), D(1.05), L(chunk), I(passes), None, big, None, None, options, None)
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("fake") / "libamdhip64.so.7")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-w", "-Wl,-soname,libamdhip64.so.7", "-o", out, os.path.join(HERE, "fake_hip.c")],
+                   check=True)
+    if not os.path.exists(LIB):
+        from paper_2502_17846_amd import build
+        build.build_library()
+    return out
+
+
+def _run(fake, body, sizes="big, ends = mem(1 << 27), mem(1 << 27)"):
+    done = subprocess.run([sys.executable, "-c", PRELUDE + sizes + "\n" + textwrap.dedent(body), fake, LIB], capture_output=True, text=True,
+                          timeout=300)
+    assert done.returncode == 0, done.stdout + done.stderr
+
+
+def test_a_limit_on_lds_does_not_depend_on_the_call(fake):
+    _run(fake, """
+    reset()
+    for n, m in ((9_000_000, 100_000), (5_000_000, 100_000), (3_000_000, 50_000), (20_000, 50_000), (30_000_000, 9_000_000)):
+        assert stream(n, m) == 0
+    for n, m, k in ((100_000, 500_000, 128), (100_000, 500_000, 120), (100_000, 500_000, 9), (100_000, 500_000, 30),
+                    (20_000_000, 12_000_000, 16), (20_000_000, 12_000_000, 60)):
+        assert buckets(n, m, k) == 0
+    opt = (ctypes.c_int32 * 8)(3)
+    for k in (32, 20, 17, 16, 9, 2):
+        for n, chunk in ((300_000, 300_000), (70_000, 20_000)):
+            assert partition(n, k, chunk, options=opt) == 0
+    for k in (4096, 3000, 1500):
+        assert partition(5_000, k, 5_000) == 0
+    limits = {}
+    for what, kernel, value in text():
+        if what == "attribute":
+            limits.setdefault(kernel, set()).add(int(value))
+    assert len(limits) > 8
+    for kernel, values in limits.items():
+        assert len(values) == 1, (kernel, values)
+    """)
+
+
+def test_without_the_memory_for_a_faster_form(fake):
+    _run(fake, """
+    def kernels():
+        return " ".join(x[1] for x in text() if x[0] == "launch")
+    # n, m: the binned form's pairs are what does not fit
+    for limit, binned in ((2**62, True), (140_000_000, False)):
+        reset(limit)
+        assert stream(5_000_000, 9_000_000, 1) == 0
+        t = kernels()
+        assert ("k_es_bin" in t) == binned and ("k_es_count" in t) == (not binned)
+    for limit, binned in ((2**62, True), (90_000_000, False)):
+        reset(limit)
+        assert buckets(20_000_000, 12_000_000, 16) == 0
+        t = kernels()
+        assert ("k_eb_bin" in t) == binned
+    for limit, fused in ((2**62, False), (40_000_000, True)):
+        reset(limit)
+        assert lib.grem_expected_cut(big, I(32), ends, L(12_000_000), big, D(0.1), big, None) == 0
+        assert any("k_xc_termsIiLb%d" % fused in x for x in kernels().split())
+    for limit, packed in ((2**62, True), (1_000_000, False)):
+        reset(limit)
+        assert lib.grem_edge_cut_r32(big, ends, L(4_000_000), big, big, None) == 0
+        assert ("k_pack_labels" in kernels()) == packed
+    # nothing fits: an error, and nothing is left allocated
+    reset(1000)
+    assert stream(5_000_000, 9_000_000, 1) == -2 and buckets(20_000_000, 12_000_000, 16) == -2
+    assert lib.grem_expected_cut(big, I(32), ends, L(12_000_000), big, D(0.1), big, None) == -2
+    t = text()
+    assert sum(x[0] == "malloc" for x in t) == sum(x[0] == "free" for x in t)
+    """, sizes="big, ends = mem(1 << 29), mem(1 << 27)")
