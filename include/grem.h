@@ -40,8 +40,9 @@
  *     (grem_set_workspace): calls that use it share it and must not overlap in time.
  *   - Host synchronisation: a call reads a few counters back before it enqueues its passes (the
  *     graph's largest degree and number of entries, the sizes of the re-laid-out copy, the seed's
- *     validity): one read-back on the plain route, two or three on the two-phase route;
- *     grem_partition_planned without a seed reads nothing back.
+ *     validity): one read-back on the plain route (a second one on graphs with long rows when chunks are more than 65,536,
+ *     long rows more than n/256 + 1024, or options.long_row_degree is below 8192), two or three on the two-phase
+ *     route; grem_partition_planned without a seed reads nothing back.
  */
 #ifndef GREM_H
 #define GREM_H

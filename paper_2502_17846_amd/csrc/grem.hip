@@ -16,6 +16,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <type_traits>
@@ -39,6 +40,7 @@ constexpr uint32_t kLongRowPart = 16384;   // ... that many entries per workgrou
 constexpr unsigned kLongRowGrid = 512;
 constexpr int kLongDegree = 8192;          // merged launches: rows this long (4096 and 16384 were slower) are dealt out in parts ...
 constexpr uint32_t kLongPart = 16384;      // ... of that many entries, of up to kLongPartMax when rows are longer than
+constexpr int64_t kLongChunks = 1 << 16;   // most chunks whose long rows the prepass counts, for its read-back to bring along
 constexpr uint32_t kLongPartMax = 65536;   // 64 parts: every part adds its k counts to the same row of estimates (rows of
                                            // 2M entries, k = 256: 92 ms in parts of 4096, 71.5 of 16384, 67.4 of 32768)
 constexpr int kSweepMaxK = 32;             // two-phase route: 16-bit counters for 2048 rows: 64 KB of LDS up to k = 16
@@ -54,9 +56,9 @@ constexpr int64_t kMinSlices = 256;        // slices per chunk wanted: one per C
                                            // share a tile's row of mover counts, never more than 256 tiles)
 constexpr int64_t kMaxSegments = 1ll << 22;   // chunks * column blocks
 constexpr int64_t kCutPackMinN = 1 << 20;  // edge cut: int32 labels of more vertices outgrow an XCD's 4 MB of L2
+constexpr size_t kScoreLds16 = 150 * 1024, kScoreLds32 = 158 * 1024;   // k_tp_score's LDS: with the static counters for k <= 16
 constexpr int64_t kPlaceGrid = 1024;       // workgroups of k_tp_place wanted: four per CU
 constexpr int kMaxParts = kPlanParts;      // parts of a slice (hub share) in the re-layout
-constexpr size_t kScoreLds16 = 150 * 1024, kScoreLds32 = 158 * 1024;   // k_tp_score's LDS: with the static counters for k <= 16
 
 // ---- process-wide state: the optional workspace and the measurement aids --------------------------
 struct Global {
@@ -623,6 +625,12 @@ template <typename LabelT> struct CallState {
     bool seed_complete = false;        // (host) the seed labels every vertex
 };
 
+// 64-bit words behind CallState::misc for the counts of the chunks' long rows and their parts
+size_t long_count_words(int64_t n, int64_t cl) {
+    const int64_t nchunks = (n + cl - 1) / cl;
+    return nchunks <= kLongChunks ? (size_t)((1 + kLongPartSizes) * nchunks + 1) / 2 : 0;
+}
+
 template <typename LabelT>
 void state_common(Carver &c, CallState<LabelT> &st, int64_t n, int64_t cl, int32_t k) {
     const size_t ntiles = (size_t)((cl + kAdmitTile - 1) / kAdmitTile);
@@ -637,21 +645,23 @@ void state_common(Carver &c, CallState<LabelT> &st, int64_t n, int64_t cl, int32
     c.take(st.fillRank, (size_t)k);
     c.take(st.fillSorted, (size_t)k);
     c.take(st.fillC, (size_t)k + 1);
-    c.take(st.misc, 32);
+    c.take(st.misc, 32 + long_count_words(n, cl));
 }
 
 // prepass: compact labels and sizes from the seed, its validity; with rowptr also the largest degree
 template <typename RowT, typename LabelT>
 void launch_prepass(Launcher &L, const RowT *rowptr_or_null, const int32_t *seed, int64_t n, int32_t k, long long P,
-                    CallState<LabelT> &st, uint32_t long_degree = 0xFFFFFFFFu) {
+                    CallState<LabelT> &st, uint32_t long_degree = 0xFFFFFFFFu, LongCounts lc = LongCounts{}) {
     hipStream_t stream = L.stream;
     L.memset(st.S, 0, (size_t)k * 8);
-    L.memset(st.misc, 0, 32 * 8);
+    const bool counts = lc.nchunks != 0;
+    if (counts) lc.count = (uint32_t *)(st.misc + 32);
+    L.memset(st.misc, 0, (32 + (counts ? long_count_words(n, lc.chunk) : 0)) * 8);
     int64_t blocks = (n + 255) / 256;
     if (blocks > 256 * 8) blocks = 256 * 8;      // (every workgroup adds its sums at the same few addresses)
     L.run(GREM_KERNEL_PREPASS, [&] {
         hipLaunchKernelGGL((k_prepass<RowT, LabelT>), dim3((unsigned)blocks), dim3(256), 0, stream, rowptr_or_null, seed,
-                           n, (int)k, st.Lc, (unsigned long long *)st.S, st.misc, long_degree);
+                           n, (int)k, st.Lc, (unsigned long long *)st.S, st.misc, long_degree, lc);
     });
     if (seed)
         L.run(GREM_KERNEL_PREPASS, [&] {
@@ -1033,11 +1043,12 @@ int plain_tile_rows(int32_t k, int lds_bytes) {
 }
 
 // Alg. 1's loop in the merged launches.  degrees[i]: rows of at least long_row_degree * 2^i entries and fewer than
-// twice as many (the last: and more).
+// twice as many (the last: and more).  long_counts: the prepass's counts by chunk (LongCounts), or null.
 template <typename RowT, typename LabelT>
 int run_plain_merged(const RowT *rowptr, const int32_t *colidx, int64_t n, int32_t k, double slack, int64_t cl, int32_t R,
                      const int32_t *seed, int32_t *labels_out, int64_t *sizes_out, uint32_t *estimates_out, const Opts &o,
-                     unsigned long long maxdeg, const unsigned long long *degrees, Arena &mem, Launcher &L, CallState<LabelT> &st) {
+                     unsigned long long maxdeg, const unsigned long long *degrees, const uint32_t *long_counts, Arena &mem, Launcher &L,
+                     CallState<LabelT> &st) {
     hipStream_t stream = L.stream;
     const long long P = grem_capacity(n, k, slack);
     const bool external_E = estimates_out != nullptr;
@@ -1057,7 +1068,8 @@ int run_plain_merged(const RowT *rowptr, const int32_t *colidx, int64_t n, int32
     // (at most 64 KB, which every kernel may have: k <= kPlainMaxK)
 
     // the long rows, chunk by chunk
-    std::vector<uint32_t> nrows, nparts, first;
+    std::unique_ptr<uint32_t[]> read;              // (nothing throws: allocated without)
+    const uint32_t *nrows = nullptr, *nparts = nullptr, *nrows_dev = x.nrows;
     unsigned long long degree = (unsigned long long)plain_long_degree(o), rows = 0;
     for (int i = 0; i < kLongClasses; ++i) rows += degrees[i];
     for (int i = 0; i < kLongClasses - 1 && rows > plain_long_rows(n); ++i) { rows -= degrees[i]; degree *= 2; }
@@ -1065,19 +1077,29 @@ int run_plain_merged(const RowT *rowptr, const int32_t *colidx, int64_t n, int32
     uint32_t part = kLongPart;
     while (part < kLongPartMax && maxdeg / part > 64) part *= 2;
     if (split_long) {
-        nrows.resize((size_t)nchunks);
-        nparts.resize((size_t)nchunks);
-        first.resize((size_t)nchunks);
         const unsigned blocks = (unsigned)((n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192);
-        L.memset(x.nrows, 0, (size_t)nchunks * 4);
-        L.memset(x.nparts, 0, (size_t)nchunks * 4);
         L.memset(x.cur, 0, (size_t)nchunks * 4);
+        const bool counted = long_counts && degree == (unsigned long long)plain_long_degree(o);
+        if (counted) {
+            int size = 0;
+            while ((kLongPart << size) < part) ++size;
+            nrows = long_counts;
+            nparts = long_counts + (size_t)(size + 1) * (size_t)nchunks;
+            nrows_dev = (uint32_t *)(st.misc + 32);
+        } else {
+            read.reset(new (std::nothrow) uint32_t[2 * (size_t)nchunks]);
+            if (!read) return GREM_ERR_NOMEM;
+            nrows = read.get();
+            nparts = read.get() + nchunks;
+            L.memset(x.nrows, 0, (size_t)nchunks * 4);
+            L.memset(x.nparts, 0, (size_t)nchunks * 4);
+            L.run(GREM_KERNEL_HUBS, [&] {
+                hipLaunchKernelGGL((k_long_count<RowT>), dim3(blocks), dim3(256), 0, stream, rowptr, n, cl, (uint32_t)degree,
+                                   part, x.nrows, x.nparts);
+            });
+        }
         L.run(GREM_KERNEL_HUBS, [&] {
-            hipLaunchKernelGGL((k_long_count<RowT>), dim3(blocks), dim3(256), 0, stream, rowptr, n, cl, (uint32_t)degree,
-                               part, x.nrows, x.nparts);
-        });
-        L.run(GREM_KERNEL_HUBS, [&] {
-            hipLaunchKernelGGL(k_long_offsets, dim3(1), dim3(kScanThreads), 0, stream, (const uint32_t *)x.nrows, nchunks, x.off);
+            hipLaunchKernelGGL(k_long_offsets, dim3(1), dim3(kScanThreads), 0, stream, nrows_dev, nchunks, x.off);
         });
         L.run(GREM_KERNEL_HUBS, [&] {
             hipLaunchKernelGGL((k_long_list<RowT>), dim3(blocks), dim3(256), 0, stream, rowptr, n, cl, (uint32_t)degree,
@@ -1085,18 +1107,20 @@ int run_plain_merged(const RowT *rowptr, const int32_t *colidx, int64_t n, int32
         });
         L.run(GREM_KERNEL_HUBS, [&] {
             hipLaunchKernelGGL((k_long_parts<RowT>), dim3((unsigned)(nchunks < 1024 ? nchunks : 1024)), dim3(256), 0, stream, rowptr,
-                               nchunks, part, (const uint32_t *)x.nrows, (const uint32_t *)x.off, (const uint32_t *)x.row, x.pref);
+                               nchunks, part, nrows_dev, (const uint32_t *)x.off, (const uint32_t *)x.row, x.pref);
         });
         L.run(GREM_KERNEL_HUBS, [&] {
             hipLaunchKernelGGL(k_long_clear, dim3((unsigned)(rows < 2048 ? rows : 2048)), dim3(256), 0, stream, (const uint32_t *)x.row,
                                (uint32_t)rows, E, (int)k);
         });
         if (L.err) return L.err;
-        if (hipMemcpyAsync(nrows.data(), x.nrows, (size_t)nchunks * 4, hipMemcpyDeviceToHost, stream) != hipSuccess)
-            return GREM_ERR_HIP;
-        if (!L.read_back(nparts.data(), x.nparts, (size_t)nchunks * 4)) return L.err;
-        uint32_t at = 0;
-        for (int64_t c = 0; c < nchunks; ++c) { first[(size_t)c] = at; at += nrows[(size_t)c]; }
+        if (!counted) {
+            if (hipMemcpyAsync(read.get(), x.nrows, (size_t)nchunks * 4, hipMemcpyDeviceToHost, stream) != hipSuccess) return GREM_ERR_HIP;
+            if (!L.read_back(read.get() + nchunks, x.nparts, (size_t)nchunks * 4)) {
+                (void)hipStreamSynchronize(stream);            // (the copy before it writes to memory that is about to go)
+                return L.err;
+            }
+        }
     }
     L.memset(x.cnt, 0, 2 * cells * 4);
     L.memset(x.coarse, 0, 2 * coarse_cells * 4);
@@ -1107,16 +1131,16 @@ int run_plain_merged(const RowT *rowptr, const int32_t *colidx, int64_t n, int32
     for (int pass = 0; pass <= R && !L.err; ++pass) {
         const int standing = pass > 0 ? kAllLabelled : seed ? kSomeLabelled : kNoneLabelled;
         const int store_e = (pass < R || external_E) ? 1 : 0;
-        for (int64_t c = 0; c < nchunks && !L.err; ++c) {
+        size_t first = 0;                          // the chunk's first long row
+        for (int64_t c = 0; c < nchunks && !L.err; first += split_long ? nrows[c] : 0, ++c) {
             const int64_t lo = c * cl;
             const int64_t hi = (lo + cl < n) ? lo + cl : n;
             const int64_t len = hi - lo;
             const unsigned tiles = (unsigned)((len + kAdmitTile - 1) / kAdmitTile);
             LongParts lr{nullptr, nullptr, nullptr, 0u, 0u, (uint32_t)degree, part};
-            if (split_long && nrows[(size_t)c] != 0)
-                lr = LongParts{x.row + first[(size_t)c], x.pref + first[(size_t)c],
-                               nparts[(size_t)c] <= kLongTicketParts ? x.ticket + first[(size_t)c] : (uint32_t *)nullptr, nrows[(size_t)c],
-                               nparts[(size_t)c], (uint32_t)degree, part};
+            if (split_long && nrows[c] != 0)
+                lr = LongParts{x.row + first, x.pref + first, nparts[c] <= kLongTicketParts ? x.ticket + first : (uint32_t *)nullptr,
+                               nrows[c], nparts[c], (uint32_t)degree, part};
             L.run(GREM_KERNEL_SCORE, [&] {
                 hipLaunchKernelGGL((k_score_tile<RowT, LabelT>), dim3(lr.parts + (unsigned)((len + tv - 1) / tv)), dim3(kScoreThreads),
                                    tile_lds, stream, rowptr, colidx, (const LabelT *)st.Lc, (const long long *)now, other, E, st.prop, cnt,
@@ -1327,17 +1351,26 @@ int run_partition(const RowT *rowptr, const int32_t *colidx, int64_t n, int32_t 
     if (!done) {
         const bool merged = plain_merged(k, cl, o.hist_mode);
         unsigned long long degrees[kLongClasses] = {0};
+        std::unique_ptr<unsigned long long[]> back;
+        const uint32_t *long_counts = nullptr;
         if (!try_sweep || merged) {        // (the merged launches want the rows' degrees by class)
-            launch_prepass<RowT, LabelT>(L, rowptr, seed, n, k, P, st, (uint32_t)plain_long_degree(o));
-            unsigned long long h[32] = {0};
-            if (!L.read_back(h, st.misc, sizeof(h))) { mem.release_all(); return L.err; }
+            // (a row of fewer entries is no rare one: their counts by chunk are then left for when they are known to be few)
+            const bool counts = merged && (uint32_t)plain_long_degree(o) >= (uint32_t)kLongDegree && long_count_words(n, cl) != 0;
+            const size_t words = 32 + (counts ? long_count_words(n, cl) : 0);
+            back.reset(new (std::nothrow) unsigned long long[words]);
+            if (!back) { mem.release_all(); return GREM_ERR_NOMEM; }
+            launch_prepass<RowT, LabelT>(L, rowptr, seed, n, k, P, st, (uint32_t)plain_long_degree(o),
+                                         counts ? LongCounts{nullptr, cl, (n + cl - 1) / cl, kLongPart} : LongCounts{});
+            const unsigned long long *h = back.get();
+            if (!L.read_back(back.get(), st.misc, words * 8)) { mem.release_all(); return L.err; }
             if (h[1] != 0 || h[2] != 0) { mem.release_all(); return GREM_ERR_SEED; }
             maxdeg = h[0];
             if (R >= 32 || (maxdeg << R) >= (1ull << 32)) { mem.release_all(); return GREM_ERR_RANGE; }
             for (int i = 0; i < kLongClasses; ++i) degrees[i] = h[16 + i];
+            if (counts) long_counts = (const uint32_t *)(h + 32);
         }
         rc = merged ? run_plain_merged<RowT, LabelT>(rowptr, colidx, n, k, slack, cl, R, seed, labels_out, sizes_out, estimates_out, o,
-                                                     maxdeg, degrees, mem, L, st)
+                                                     maxdeg, degrees, long_counts, mem, L, st)
                     : run_plain<RowT, LabelT>(rowptr, colidx, n, k, slack, cl, R, seed, labels_out, sizes_out, estimates_out, o,
                                      maxdeg, mem, L, st);
     }

@@ -48,14 +48,23 @@ __device__ __forceinline__ int owning_row(const uint32_t *rowrel, uint32_t i, in
 // misc[0] = max degree, misc[1] = number of invalid seed labels, misc[3] = number of entries,
 // misc[5] = number of vertices the seed leaves without a label, misc[16 + i] = rows of at least long_degree * 2^i and
 // fewer than long_degree * 2^(i+1) entries (i = 15: and more)
+// lc.count (may be null): for every chunk its rows of at least long_degree entries, then, in kLongPartSizes more arrays,
+// the parts of lc.part * 2^i entries that they make
 // ------------------------------------------------------------------------------------------------
 constexpr int kPrepassLdsK = 1024;      // up to this k the seed sizes are counted in LDS first
+constexpr int kLongPartSizes = 3;
+struct LongCounts {
+    uint32_t *count;
+    int64_t chunk, nchunks;
+    uint32_t part;
+};
 template <typename RowT, typename LabelT>
 __global__ __launch_bounds__(256) void k_prepass(const RowT *__restrict__ rowptr,
                                                  const int32_t *__restrict__ seed, int64_t n, int k,
                                                  LabelT *__restrict__ Lc,
                                                  unsigned long long *__restrict__ S,
-                                                 unsigned long long *__restrict__ misc, uint32_t long_degree) {
+                                                 unsigned long long *__restrict__ misc, uint32_t long_degree,
+                                                 LongCounts lc) {
     __shared__ unsigned int s_long[16];
     __shared__ unsigned long long s_maxdeg;
     __shared__ unsigned int s_bad, s_none;
@@ -78,6 +87,14 @@ __global__ __launch_bounds__(256) void k_prepass(const RowT *__restrict__ rowptr
                 const unsigned long long q = d / long_degree;
                 const int c = 63 - __clzll((long long)q);
                 atomicAdd(&s_long[c < 15 ? c : 15], 1u);
+                if (lc.count) {
+                    uint32_t *at = lc.count + v / lc.chunk;
+                    atomicAdd(at, 1u);
+                    for (int i = 0; i < kLongPartSizes; ++i) {
+                        const unsigned long long part = (unsigned long long)lc.part << i;
+                        atomicAdd(at + (i + 1) * lc.nchunks, (uint32_t)((d + part - 1) / part));
+                    }
+                }
             }
         }
         uint32_t lab = LabelTraits<LabelT>::kUnassigned;

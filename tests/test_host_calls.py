@@ -52,6 +52,28 @@ def _run(fake, body, sizes="big, ends = mem(1 << 27), mem(1 << 27)"):
     assert done.returncode == 0, done.stdout + done.stderr
 
 
+def test_one_read_back_on_the_plain_route(fake):
+    _run(fake, """
+    for k, chunk in ((8, 10_000), (300, 100_000), (1500, 100_000)):
+        for longest, rows in ((10, 0), (50_000, 1), (3_000_000, 7)):
+            reset()
+            fake.fake_prepass(0, ctypes.c_uint64(longest))
+            fake.fake_prepass(16 + 2, ctypes.c_uint64(rows))
+            assert partition(100_000, k, chunk) == 0
+            t = text()
+            assert sum(x[0] == "wait" for x in t) == 1, (k, chunk, longest, t)
+            assert any("k_long" in x[1] for x in t) == (longest > 10)
+    # more long rows than their list holds: the degree is doubled and the chunks counted again
+    reset()
+    fake.fake_prepass(0, ctypes.c_uint64(9_000))
+    fake.fake_prepass(16, ctypes.c_uint64(50_000))
+    fake.fake_prepass(17, ctypes.c_uint64(5))
+    assert partition(100_000, 8, 10_000) == 0
+    t = text()
+    assert sum(x[0] == "wait" for x in t) == 2 and any("k_long_count" in x[1] for x in t)
+    """)
+
+
 def test_a_limit_on_lds_does_not_depend_on_the_call(fake):
     _run(fake, """
     reset()
