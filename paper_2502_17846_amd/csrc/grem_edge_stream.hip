@@ -31,6 +31,7 @@
 
 #include <cstdint>
 #include <mutex>
+#include <new>
 #include <type_traits>
 #include <vector>
 
@@ -1276,14 +1277,9 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
     return hipGetLastError() == hipSuccess ? GREM_OK : GREM_ERR_HIP;
 }
 
-}  // namespace
-
-extern "C" {
-
-int grem_edge_stream_bipartition(const int32_t* src, const int32_t* dst, int64_t m, int64_t n,
-                                 int64_t c_size, int64_t P, const int32_t* seed_parts, int32_t mode,
-                                 int32_t* parts_out, int64_t* sizes_out, double* nbr_counts_out,
-                                 void* stream_)
+// The entry points' bodies.  ws: the call's scratch memory while it holds any; the caller gives it back if a body throws.
+int es_bipartition(const int32_t* src, const int32_t* dst, int64_t m, int64_t n, int64_t c_size, int64_t P, const int32_t* seed_parts,
+                   int32_t mode, int32_t* parts_out, int64_t* sizes_out, double* nbr_counts_out, void* stream_, uint8_t*& ws)
 {
     if (!src || !dst || !seed_parts || !parts_out || m < 1 || n < 1 || n > INT32_MAX || c_size < 1 ||
         P < 1 || 2 * P < n || (mode != GREM_EDGE_REFINE && mode != GREM_EDGE_FIXED))
@@ -1293,7 +1289,6 @@ int grem_edge_stream_bipartition(const int32_t* src, const int32_t* dst, int64_t
     const int64_t chunks = (m + c_size - 1) / c_size, ends = 2 * c_size;
     EsShape sh;
     EsMemory mem;
-    uint8_t* ws = nullptr;
     for (const bool bins : {true, false}) {
         sh = es_shape(n, 1, ends, chunks, bins);
         mem.layout(nullptr, sh, 1, ends, chunks, nbr_counts_out);
@@ -1332,9 +1327,8 @@ int grem_edge_stream_bipartition(const int32_t* src, const int32_t* dst, int64_t
     return rc;
 }
 
-int grem_recursive_bisection(const int32_t* src, const int32_t* dst, int64_t m, int64_t n, int32_t levels,
-                             int64_t chunks, double balance_slack, const int32_t* seed_bits, int32_t mode,
-                             int32_t* labels_out, void* stream_)
+int es_bisection(const int32_t* src, const int32_t* dst, int64_t m, int64_t n, int32_t levels, int64_t chunks, double balance_slack,
+                 const int32_t* seed_bits, int32_t mode, int32_t* labels_out, void* stream_, uint8_t*& ws)
 {
     if (!src || !dst || !seed_bits || !labels_out || m < 1 || n < 1 || n > INT32_MAX || levels < 1 || levels > 20 ||
         chunks < 1 || !(balance_slack >= 1.0) || (mode != GREM_EDGE_REFINE && mode != GREM_EDGE_FIXED))
@@ -1360,7 +1354,6 @@ int grem_recursive_bisection(const int32_t* src, const int32_t* dst, int64_t m, 
     size_t o_lev[4];                                   // two generations of the grouped edge list
     for (int i = 0; i < 4; ++i) o_lev[i] = carve((size_t)m * 4);
     const size_t o_run = off;                          // the state of a run is the last piece
-    uint8_t* ws = nullptr;
     for (const bool bins : {true, false}) {
         sh = es_shape(n, most_groups < kMaxBatch ? most_groups : kMaxBatch, ends, c_max, bins);
         mem.layout(nullptr, sh, kMaxBatch, ends, c_max, nullptr);
@@ -1468,6 +1461,44 @@ int grem_recursive_bisection(const int32_t* src, const int32_t* dst, int64_t m, 
     int rc = hipGetLastError() == hipSuccess ? GREM_OK : GREM_ERR_HIP;
     if (hipFreeAsync(ws, stream) != hipSuccess) rc = GREM_ERR_HIP;
     return rc;
+}
+
+// nothing throws at the C interface: host memory that cannot be had is an error like any other
+template <typename F>
+int es_guarded(void* stream_, F&& f)
+{
+    hipStream_t stream = (hipStream_t)stream_;
+    uint8_t* ws = nullptr;
+    try {
+        return f(ws);
+    } catch (const std::bad_alloc&) {
+        (void)hipStreamSynchronize(stream);
+        if (ws) (void)hipFreeAsync(ws, stream);
+        return GREM_ERR_NOMEM;
+    }
+}
+
+}  // namespace
+
+extern "C" {
+
+int grem_edge_stream_bipartition(const int32_t* src, const int32_t* dst, int64_t m, int64_t n,
+                                 int64_t c_size, int64_t P, const int32_t* seed_parts, int32_t mode,
+                                 int32_t* parts_out, int64_t* sizes_out, double* nbr_counts_out,
+                                 void* stream_)
+{
+    return es_guarded(stream_, [&](uint8_t*& ws) {
+        return es_bipartition(src, dst, m, n, c_size, P, seed_parts, mode, parts_out, sizes_out, nbr_counts_out, stream_, ws);
+    });
+}
+
+int grem_recursive_bisection(const int32_t* src, const int32_t* dst, int64_t m, int64_t n, int32_t levels,
+                             int64_t chunks, double balance_slack, const int32_t* seed_bits, int32_t mode,
+                             int32_t* labels_out, void* stream_)
+{
+    return es_guarded(stream_, [&](uint8_t*& ws) {
+        return es_bisection(src, dst, m, n, levels, chunks, balance_slack, seed_bits, mode, labels_out, stream_, ws);
+    });
 }
 
 int grem_edge_list_cut(const int32_t* src, const int32_t* dst, int64_t m, const int32_t* parts,

@@ -128,3 +128,21 @@ def test_without_the_memory_for_a_faster_form(fake):
     t = text()
     assert sum(x[0] == "malloc" for x in t) == sum(x[0] == "free" for x in t)
     """, sizes="big, ends = mem(1 << 29), mem(1 << 27)")
+
+
+def test_no_exception_where_host_memory_ends(fake):
+    # 20 levels: 12.6 MB of counters on the device and as much on the host, of which there is only half
+    _run(fake, """
+    import resource
+    def bisection(levels):
+        return lib.grem_recursive_bisection(ends, ends, L(1000), L(1000), I(levels), L(4), D(3.0), big, I(0), big, None)
+    assert bisection(2) == 0
+    size = int(open("/proc/self/statm").read().split()[0]) * 4096
+    resource.setrlimit(resource.RLIMIT_AS, (size + 20_000_000, resource.RLIM_INFINITY))
+    reset()
+    code = bisection(20)
+    resource.setrlimit(resource.RLIMIT_AS, (resource.RLIM_INFINITY, resource.RLIM_INFINITY))
+    t = text()
+    assert code == -2, code
+    assert sum(x[0] == "malloc" for x in t) == sum(x[0] == "free" for x in t)
+    """)
