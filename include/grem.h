@@ -378,10 +378,11 @@ int64_t grem_expected_cut_noalloc_max_n(void);
 int grem_edge_list_cut(const int32_t *src, const int32_t *dst, int64_t m, const int32_t *parts,
                        int64_t *cut_out, void *stream);
 
-/* Timing of the edge kernel (cnt_nbrs over a chunk's edges) with HIP events on the caller's stream,
- * for measurement: while enabled each launch is bracketed by two events; the read synchronises on
- * them, returns their total in milliseconds, the launch count and the number of edges those
- * launches processed (each may be NULL), and forgets them.  Calls made by
+/* Timing of the edge kernels (cnt_nbrs over a chunk's edges) with HIP events on the caller's stream,
+ * for measurement: while enabled the kernels of every chunk step are bracketed by two events: the one that counts in
+ * memory, or, from 2^22 nodes on, the ones that bin the edge ends and count the bins, the latter with the nodes' scoring,
+ * which is part of it.  The read synchronises on the events, returns their total in milliseconds, the number of
+ * chunk steps and the number of edges they processed (each may be NULL), and forgets them.  Calls made by
  * grem_recursive_bisection are included. */
 int grem_edge_stream_profile_enable(int32_t on);
 int grem_edge_stream_profile_read(double *count_ms, int64_t *launches, int64_t *edges);

@@ -1246,19 +1246,21 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
                 return GREM_ERR_HIP;
             (void)hipEventRecord(e0, stream);
         }
+        auto timed = [&] {                         // cnt_nbrs is done: binned, with the scoring that it is part of
+            if (!profile) return;
+            (void)hipEventRecord(e1, stream);
+            std::lock_guard<std::mutex> lock(es_prof.mu);
+            es_prof.count_events.emplace_back(e0, e1);
+            for (const EsGroup& g : groups)
+                if (i * g.c_size < g.m) es_prof.edges += g.m - i * g.c_size < g.c_size ? g.m - i * g.c_size : g.c_size;
+        };
         if (sh.binned)
             hipLaunchKernelGGL(k_es_bin, dim3((unsigned)((most + kBinTile - 1) / kBinTile), ng), dim3(kBlock), kBinTile * 8, stream, src, dst,
                                st, i, sh.cb, mem.cursors, mem.pairs);
         else
             hipLaunchKernelGGL(k_es_count, dim3((unsigned)grid_for((most + kCountUnroll - 1) / kCountUnroll, kCountBlock, 1 << 20), ng),
                                dim3(kCountBlock), 0, stream, src, dst, st, i, mem.hc);
-        if (profile) {
-            (void)hipEventRecord(e1, stream);
-            std::lock_guard<std::mutex> lock(es_prof.mu);
-            es_prof.count_events.emplace_back(e0, e1);
-            for (const EsGroup& g : groups)
-                if (i * g.c_size < g.m) es_prof.edges += g.m - i * g.c_size < g.c_size ? g.m - i * g.c_size : g.c_size;
-        }
+        if (!sh.binned) timed();
         const int first = i == 0 ? 1 : 0;
         if (sh.binned && crowded[(size_t)i])
             hipLaunchKernelGGL(k_es_crowd, dim3(kCrowdGrid), dim3(kBlock), bins_lds, stream, i, sh.cb, (uint32_t)sh.bn(), blocks,
@@ -1268,6 +1270,7 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
                                blocks, (const uint32_t*)mem.table, (const uint32_t*)mem.pairs, mem.crowd);
         else
             hipLaunchKernelGGL(k_es_score, dim3(blocks), dim3(kBlock), 0, stream, st, par, first, fixed, mem.hc);
+        if (sh.binned) timed();
         if (first) continue;
         hipLaunchKernelGGL(k_es_apply, dim3(ablocks), dim3(kBlock), slab, stream, st, par);
         hipLaunchKernelGGL(k_es_spill, dim3(ablocks), dim3(kBlock), 0, stream, st, par);

@@ -146,3 +146,21 @@ def test_no_exception_where_host_memory_ends(fake):
     assert code == -2, code
     assert sum(x[0] == "malloc" for x in t) == sum(x[0] == "free" for x in t)
     """)
+
+
+def test_the_edge_timing_spans_the_kernels_that_count(fake):
+    _run(fake, """
+    assert lib.grem_edge_stream_profile_enable(I(1)) == 0
+    for n, m, inside in ((20_000, 50_000, {"k_es_count"}), (5_000_000, 50_000, {"k_es_bin", "k_es_score_bins"})):
+        reset()
+        assert stream(n, m, 3) == 0
+        t = [x for x in text() if x[0] in ("record", "launch")]
+        at = [i for i, x in enumerate(t) if x[0] == "record"]
+        assert len(at) == 6
+        for a, b in zip(at[::2], at[1::2]):
+            got = [x[1] for x in t[a + 1:b]]
+            assert len(got) == len(inside) and all(any(k + "E" in g for g in got) for k in inside), got
+        ms, steps, edges = D(), L(), L()
+        assert lib.grem_edge_stream_profile_read(ctypes.byref(ms), ctypes.byref(steps), ctypes.byref(edges)) == 0
+        assert (ms.value, steps.value, edges.value) == (3.0, 3, m)
+    """)
