@@ -69,6 +69,20 @@ def test_an_end_out_of_range_and_a_bad_seed_are_refused():
         assert e.value.code == code
 
 
+# from 2^23 nodes on an admission block is two scoring blocks, also in groups that do not begin at the first one; a capacity
+# of exactly half: rejections and placements in every group
+@pytest.mark.parametrize("levels,slack", [(2, 1.0), (3, 1.004)])
+def test_bisection_of_groups_whose_admission_blocks_are_two_scoring_blocks(levels, slack):
+    n, m = (1 << 23) + 11_003, 9_000_000
+    src, dst = _stream(n, m, 29)
+    bits = np.random.default_rng(6).integers(0, 2, (levels, n)).astype(np.int32)
+    want = oracle.recursive_bisection(src, dst, n, levels, 3, slack, bits)
+    assert np.bincount(want, minlength=1 << levels).min() % 65_536 != 0
+    got = B.grem_recursive_bisection(torch.as_tensor(src).to(DEV), torch.as_tensor(dst).to(DEV), n, levels, 3, slack,
+                                     torch.as_tensor(bits).to(DEV).reshape(-1))
+    assert np.array_equal(got.cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("n,levels", [(4_300_001, 2), (200_003, 5), (1500, 11)])
 def test_bisection_of_groups_side_by_side(n, levels):
     # binned; groups of several blocks; more groups than nodes in a block, most of them empty, in several batches
