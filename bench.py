@@ -47,6 +47,11 @@ PMC_EDGE = {
 }
 
 
+def edge_kernels(n):
+    """The kernels that grem_edge_stream_profile_* times: from 2^22 nodes on the edge ends are binned."""
+    return "k_es_bin+k_es_score_bins" if n >= 1 << 22 else "k_es_count"
+
+
 def edge_sources_sha256():
     import hashlib
     with open(os.path.join(ROOT, "paper_2502_17846_amd", "csrc", "grem_edge_stream.hip"), "rb") as f:
@@ -288,10 +293,10 @@ def bench_edge_stream(args, w, dev):
     sizes = torch.bincount(parts[assigned], minlength=2)
     assert int(sizes.max()) <= P
 
-    # dominant kernel: k_es_count reads each edge's two ids once (8 bytes); its label look-ups and count
-    # atomics are random accesses whose useful bytes are 2 and 16 per edge
+    # dominant kernels: cnt_nbrs reads each edge's two ids once (8 bytes); its label look-ups are random accesses whose
+    # useful bytes are 2 per edge, the pairs it bins and the nodes' estimates are not counted
     roofline = {"bound": "hbm", "achieved": None, "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": None,
-                "traffic": None, "kernel": "k_es_count"}
+                "traffic": None, "kernel": edge_kernels(n)}
     if not args.no_kernel_timing:
         B.grem_edge_stream_profile_enable(True)
         step()
@@ -305,9 +310,9 @@ def bench_edge_stream(args, w, dev):
                         launches_per_step=launches, bytes_per_launch=bytes_per_launch,
                         count_ms_per_step=round(count_ms, 3))
         if args.workload == PMC_EDGE["workload"] and PMC_EDGE["sources_sha256"] == edge_sources_sha256():
-            kib = (PMC_EDGE["fetch_kib"]["k_es_count"] * PMC["fetch_factor"]
-                   + PMC_EDGE["write_kib"]["k_es_count"] * PMC["write_factor"])
-            roofline["traffic"] = kib * 1024.0 / PMC_EDGE["launches"]["k_es_count"]
+            kib = (sum(PMC_EDGE["fetch_kib"].values()) * PMC["fetch_factor"]
+                   + sum(PMC_EDGE["write_kib"].values()) * PMC["write_factor"])
+            roofline["traffic"] = kib * 1024.0 / PMC_EDGE["launches"]
     out = {
         "metric": "edges/sec per GREM pass", "value": m / (elapsed / args.steps), "unit": "edges/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_per_step,
@@ -465,7 +470,7 @@ def bench_buckets(args, w, dev):
         "largest_bucket": int(sizes.max()), "smallest_bucket": int(sizes.min()),
         "roofline": {"bound": "hbm", "achieved": 16.0 * m / sec / 1e9, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": 16.0 * m / sec / 1e9 / HBM_PEAK_GBPS, "traffic": None,
-                     "kernel": "whole call (k_eb_hist + k_eb_scatter and the scans, timed together)"},
+                     "kernel": "whole call (the keys, k_eb_scatter_lds and the scans, timed together)"},
     }
     if not args.no_cpu_baseline:
         import oracle
@@ -512,14 +517,14 @@ def bench_recursive(args, w, dev):
     sizes = torch.bincount(lab, minlength=k)
     cut = int(B.grem_edge_list_cut(es.src, es.dst, lab).item())
     roofline = {"bound": "hbm", "achieved": None, "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": None,
-                "traffic": None, "kernel": "k_es_count"}
+                "traffic": None, "kernel": edge_kernels(n)}
     if not args.no_kernel_timing:
         B.grem_edge_stream_profile_enable(True)
         step()
         torch.cuda.synchronize()
         count_ms, launches, streamed = B.grem_edge_stream_profile_read()
         B.grem_edge_stream_profile_enable(False)
-        # algorithmic bytes of k_es_count: the two ids of every edge it is handed
+        # algorithmic bytes of a chunk step's counting: the two ids of every edge it is handed
         bytes_per_launch = 8.0 * streamed / launches
         avg_s = 1e-3 * count_ms / launches
         achieved = bytes_per_launch / avg_s / 1e9
@@ -670,12 +675,12 @@ def main():
     P = B.grem_capacity(n, k, w["slack"])
     assert int(sizes.max()) <= P and int(sizes.sum()) == n and int(labels.min()) >= 0
 
-    label_bytes = 1 if k <= 255 else 2
+    label_bytes = 1 if k <= 256 else 2
     b_first, b_later, b_total = algorithmic_bytes(n, nnz, k, R, w["bits"] // 8, label_bytes)
     nchunks = (n + chunk - 1) // chunk
     frac_of_peak = lambda nbytes, ms: nbytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBPS
     roofline = {"bound": "hbm", "achieved": None, "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": None,
-                "traffic": None, "kernel": "k_score_lds" if k <= 128 else "k_score_global",
+                "traffic": None, "kernel": "k_score_tile" if k <= 1024 and chunk <= 1 << 20 else "k_score_lds or k_score_global",
                 "frac_is": "the dominant kernel's: algorithmic bytes of one chunk / its average launch time",
                 "whole_call_frac": frac_of_peak(b_total, ms_per_step),
                 "whole_call_frac_is": "algorithmic bytes of all passes / ms_per_step (validation, re-layout and "

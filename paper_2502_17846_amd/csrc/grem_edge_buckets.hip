@@ -554,7 +554,8 @@ __global__ __launch_bounds__(kEbBlock) void k_eb_scatter(const int32_t* __restri
 // order (bucket, then wave, then stream position = stable), every wave places its edges into LDS without
 // waiting for the others, and the sorted tile is written out with consecutive lanes on consecutive
 // addresses of a bucket's run.  Bound by latency under its barriers: with four waves to a workgroup (twelve per CU) and
-// one thread adding up the 256 partial counts 1.6e9 edges took 18.1 ms, 11.4 to 13 with eight and a wave's prefix sums.
+// one thread adding up the 256 partial counts 1.6e9 edges took 18.1 ms; with eight and a wave's prefix sums 9.3 to 12 in some
+// processes and 14.3 to 18 in others (the same within one; the distance between the output arrays does not matter).
 constexpr int kEbLdsBuckets = 1024;
 constexpr int kEbScatterThreads = 512;
 constexpr int kEbScatterWaves = kEbScatterThreads / 64;

@@ -560,7 +560,7 @@ __global__ __launch_bounds__(kBlock) void k_es_score(EsRun st, int par, int firs
         st.mv1[word0 + lane] = out1;
         if (myword) st.mark[word0 + lane] = 0ull;
     }
-    es_store_movers(st, lane < 64 ? (u64)__popcll(out0) : 0ull, (u64)__popcll(out1), blockIdx.x);
+    es_store_movers(st, (u64)__popcll(out0), (u64)__popcll(out1), blockIdx.x);
 }
 
 // cnt_nbrs, second half, from the binned pairs: a block counts the pairs of its bin that are its own in LDS (the
@@ -752,7 +752,7 @@ __global__ __launch_bounds__(kBlock) void k_es_apply(EsRun st, int par)
             for (int q = lane; q < wpw * 4; q += 64) labels4[q] = wslab4[q];
     }
     if (mine) st.ov[word0 + lane] = outo;
-    // (the three sums of a block fit 64 bits together: at most 65,536 nodes, the deltas offset to stay positive)
+    // (the two deltas share a word: at most 65,536 nodes of a block, offset to stay positive)
     u64 packed = (u64)__popcll(outo), deltas = (u64)(uint32_t)(delta0 + 256) | ((u64)(uint32_t)(delta1 + 256) << 32);
     es_block_sums(packed, deltas);
     if (threadIdx.x == 0) {

@@ -2,7 +2,7 @@
 // kPlainTiles admission tiles:
 //   k_score_tile   counts, blends and proposes (Alg. 2 cnt_nbrs, Alg. 1 blend, Alg. 2 assign) for tiles of rows
 //                  and, in the same launch, for the parts of the chunk's long rows; adds the movers up per
-//                  admission tile and per 16 of them
+//                  admission tile and per kPlainCoarse of them
 //   k_admit_tiles  admits by rank, relabels, adds to the sizes (Alg. 2 fix_sizes): every workgroup adds up the counts
 //                  of the earlier tiles itself
 //   k_spill_tiles  (first pass) places the rejected new vertices (Alg. 2 arg_min fallback)

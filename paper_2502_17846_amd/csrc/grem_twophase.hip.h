@@ -32,8 +32,8 @@
 // writes them to Lx, sub-segment by sub-segment (each a contiguous piece of some 40 bytes).  Before
 // chunk c is relabelled, k_tp_score has one workgroup per row slice stream that slice's tuples -- one
 // contiguous piece of R and of Lx -- into 16-bit LDS counters, then blends E and proposes.  (Seeded
-// runs: in their first pass a neighbour may be unassigned; the score kernel then reads the row
-// fields from a copy of R in which bit 0 marks such tuples.)
+// runs: in their first pass a neighbour may be unassigned; the label stored for it tells, see tp_count_eight,
+// except with 16 partitions in four bits: there the row fields come from a copy of R in which bit 0 marks such tuples.)
 //
 // Balance: every workgroup of k_tp_score also counts an equal part of one hub share's stream (32-bit
 // counters per hub the share touches) and adds its partial counts to a per-chunk table in global
@@ -1103,6 +1103,7 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(8, 8
                                                           const uint8_t *__restrict__ Lc,
                                                           const uint8_t *__restrict__ Lc4, int64_t n, int c0,
                                                           int cmin, int spb) {
+    static_assert((FROM_LDS || LB == 4) && (!WRITE_R || LB == 4), "a byte per label tells a missing one by itself");
     extern __shared__ uint32_t tab[];      // FROM_LDS: 2^cb labels, LB bits each
     const int tid = threadIdx.x;
     const int c = c0 + (int)blockIdx.y;
@@ -1255,7 +1256,7 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(8, 8
                     const int64_t v = block_lo + (int64_t)col[e];
                     const uint32_t l = v < chunk_hi ? (uint32_t)Lc[v] : 0xFFu;
                     if (l == 0xFFu) unassigned |= 1u << e;
-                    lab = LB == 4 ? (l & 15u) : l;
+                    lab = l & 15u;
                 }
                 if (LB == 4) word |= lab << (4 * e);
                 else if (e < 4) word |= lab << (8 * e);
