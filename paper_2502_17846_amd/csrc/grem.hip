@@ -1074,6 +1074,7 @@ int run_plain_merged(const RowT *rowptr, const int32_t *colidx, int64_t n, int32
     // the long rows, chunk by chunk
     std::unique_ptr<uint32_t[]> read;              // (nothing throws: allocated without)
     const uint32_t *nrows = nullptr, *nparts = nullptr, *nrows_dev = x.nrows;
+    bool counted = false;                          // by the prepass: nparts are then those beyond each row's first
     unsigned long long degree = (unsigned long long)plain_long_degree(o), rows = 0;
     for (int i = 0; i < kLongClasses; ++i) rows += degrees[i];
     for (int i = 0; i < kLongClasses - 1 && rows > plain_long_rows(n); ++i) { rows -= degrees[i]; degree *= 2; }
@@ -1083,7 +1084,7 @@ int run_plain_merged(const RowT *rowptr, const int32_t *colidx, int64_t n, int32
     if (split_long) {
         const unsigned blocks = (unsigned)((n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192);
         L.memset(x.cur, 0, (size_t)nchunks * 4);
-        const bool counted = long_counts && degree == (unsigned long long)plain_long_degree(o);
+        counted = long_counts && degree == (unsigned long long)plain_long_degree(o);
         if (counted) {
             int size = 0;
             while ((kLongPart << size) < part) ++size;
@@ -1142,9 +1143,11 @@ int run_plain_merged(const RowT *rowptr, const int32_t *colidx, int64_t n, int32
             const int64_t len = hi - lo;
             const unsigned tiles = (unsigned)((len + kAdmitTile - 1) / kAdmitTile);
             LongParts lr{nullptr, nullptr, nullptr, 0u, 0u, (uint32_t)degree, part};
-            if (split_long && nrows[c] != 0)
-                lr = LongParts{x.row + first, x.pref + first, nparts[c] <= kLongTicketParts ? x.ticket + first : (uint32_t *)nullptr,
-                               nrows[c], nparts[c], (uint32_t)degree, part};
+            if (split_long && nrows[c] != 0) {
+                const uint32_t parts = nparts[c] + (counted ? nrows[c] : 0u);
+                lr = LongParts{x.row + first, x.pref + first, parts <= kLongTicketParts ? x.ticket + first : (uint32_t *)nullptr,
+                               nrows[c], parts, (uint32_t)degree, part};
+            }
             L.run(GREM_KERNEL_SCORE, [&] {
                 hipLaunchKernelGGL((k_score_tile<RowT, LabelT>), dim3(lr.parts + (unsigned)((len + tv - 1) / tv)), dim3(kScoreThreads),
                                    tile_lds, stream, rowptr, colidx, (const LabelT *)st.Lc, (const long long *)now, other, E, st.prop, cnt,

@@ -49,10 +49,13 @@ __device__ __forceinline__ int owning_row(const uint32_t *rowrel, uint32_t i, in
 // misc[5] = number of vertices the seed leaves without a label, misc[16 + i] = rows of at least long_degree * 2^i and
 // fewer than long_degree * 2^(i+1) entries (i = 15: and more)
 // lc.count (may be null): for every chunk its rows of at least long_degree entries, then, in kLongPartSizes more arrays,
-// the parts of lc.part * 2^i entries that they make
+// the parts of lc.part * 2^i entries that they make beyond each row's first.  Adds at one address queue, about 10 ns
+// each: a row of one part costs one, and where there are few chunks the workgroups count in LDS first and add what is
+// not zero (8000 rows of 9000 entries in one chunk of 10^6 vertices: the run 0.9 ms; with four adds for every row 1.2).
 // ------------------------------------------------------------------------------------------------
 constexpr int kPrepassLdsK = 1024;      // up to this k the seed sizes are counted in LDS first
 constexpr int kLongPartSizes = 3;
+constexpr int kPrepassLdsChunks = 64;   // up to this many chunks their long rows are counted in LDS first
 struct LongCounts {
     uint32_t *count;
     int64_t chunk, nchunks;
@@ -70,11 +73,15 @@ __global__ __launch_bounds__(256) void k_prepass(const RowT *__restrict__ rowptr
     __shared__ unsigned int s_bad, s_none;
     // (a workgroup's vertices: at most n / gridDim.x + 256 < 2^32)
     __shared__ unsigned int s_size[kPrepassLdsK];
+    __shared__ unsigned int s_chunk[(1 + kLongPartSizes) * kPrepassLdsChunks];
+    const bool chunks_in_lds = lc.count && lc.nchunks <= kPrepassLdsChunks;
     const bool in_lds = seed && k <= kPrepassLdsK;
     if (threadIdx.x == 0) { s_maxdeg = 0; s_bad = 0; s_none = 0; }
     if (threadIdx.x < 16) s_long[threadIdx.x] = 0;
     if (in_lds)
         for (int j = threadIdx.x; j < k; j += 256) s_size[j] = 0;
+    if (chunks_in_lds)
+        for (int j = threadIdx.x; j < (1 + kLongPartSizes) * kPrepassLdsChunks; j += 256) s_chunk[j] = 0;
     __syncthreads();
     unsigned long long mymax = 0;
     unsigned int bad = 0, none = 0;
@@ -88,11 +95,12 @@ __global__ __launch_bounds__(256) void k_prepass(const RowT *__restrict__ rowptr
                 const int c = 63 - __clzll((long long)q);
                 atomicAdd(&s_long[c < 15 ? c : 15], 1u);
                 if (lc.count) {
-                    uint32_t *at = lc.count + v / lc.chunk;
-                    atomicAdd(at, 1u);
-                    for (int i = 0; i < kLongPartSizes; ++i) {
-                        const unsigned long long part = (unsigned long long)lc.part << i;
-                        atomicAdd(at + (i + 1) * lc.nchunks, (uint32_t)((d + part - 1) / part));
+                    const int64_t at = v / lc.chunk;
+                    for (int i = 0; i <= kLongPartSizes; ++i) {
+                        const uint32_t add = i == 0 ? 1u : (uint32_t)((d - 1) / ((unsigned long long)lc.part << (i - 1)));
+                        if (add == 0) break;           // (larger parts are no more of them)
+                        if (chunks_in_lds) atomicAdd(&s_chunk[at + i * lc.nchunks], add);
+                        else atomicAdd(lc.count + at + i * lc.nchunks, add);
                     }
                 }
             }
@@ -120,6 +128,9 @@ __global__ __launch_bounds__(256) void k_prepass(const RowT *__restrict__ rowptr
     if (in_lds)
         for (int j = threadIdx.x; j < k; j += 256)
             if (s_size[j]) atomicAdd(&S[j], (unsigned long long)s_size[j]);
+    if (chunks_in_lds)
+        for (int j = threadIdx.x; j < (1 + kLongPartSizes) * (int)lc.nchunks; j += 256)
+            if (s_chunk[j]) atomicAdd(&lc.count[j], s_chunk[j]);
     if (rowptr && threadIdx.x < 16 && s_long[threadIdx.x]) atomicAdd(&misc[16 + threadIdx.x], (unsigned long long)s_long[threadIdx.x]);
     if (threadIdx.x == 0) {
         // (few workgroups raise the maximum: the plain read spares the others the atomic)
