@@ -70,6 +70,16 @@ def test_long_rows(long_rows, degree):
         _check(rowptr, colidx, n, k, 1.05, chunk, 3, long_row_degree=degree)
 
 
+# chunks counted in LDS by the prepass (64, the most), and beyond; every size that the parts can have, rows that end with one
+@pytest.mark.parametrize("longest", [65_536, 1_100_000, 2_200_000])
+@pytest.mark.parametrize("chunk", [469, 461])
+def test_counts_of_the_chunks_long_rows(longest, chunk):
+    n = 30_000
+    assert -(-n // 469) == 64 and -(-n // 461) > 64
+    rowptr, colidx = _graph(n, 2, [longest, 8191, 8192, 16_384, 16_385, 32_768, 32_769, 65_537], 3)
+    _check(rowptr, colidx, n, 16, 1.05, chunk, 1)
+
+
 def test_inside_a_workspace_of_the_advertised_size():
     n, k, chunk = 50_000, 256, 9_000
     rowptr, colidx = _graph(n, 5, [20_000, 9_000], 5)
