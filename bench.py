@@ -28,22 +28,22 @@ HBM_PEAK_GBPS = 8000.0
 # at that time, and `traffic` is reported as null when the sources have changed since.
 PMC = {
     "workload": "chunglu-111M",
-    "sources_sha256": "d80c2ce30746ef584f9bde0885b6fb06e11bf52a7f017ac62f1b875e381130bd",
+    "sources_sha256": "e75747c4b512914c0cc05a103c6919bcf74da8f68c95343799185efaa5c6289f",
     "fetch_factor": 2.0,        # 2 GiB read  -> FETCH_SIZE 1,048,591 KiB
     "write_factor": 1.0,        # 2 GiB written -> WRITE_SIZE 2,097,152 KiB
-    "fetch_kib": {"k_tp_score": 1.42675e+07, "k_tp_lookup": 1.36588e+07},
-    "write_kib": {"k_tp_score": 7.32475e+06, "k_tp_lookup": 5.58938e+06},
+    "fetch_kib": {"k_tp_score": 1.42641e+07, "k_tp_lookup": 1.36608e+07},
+    "write_kib": {"k_tp_score": 7.32474e+06, "k_tp_lookup": 5.58395e+06},
     "launches": {"k_tp_score": 318, "k_tp_lookup": 317},
 }
 
 
-# The same for the edge-chunk path's dominant kernel on its 111M-node workload.
+# The same for the edge-chunk path's two dominant kernels (one launch each per chunk) on its 111M-node workload.
 PMC_EDGE = {
     "workload": "edges-chunglu-111M-c1pct",
-    "sources_sha256": "fc0898c9602363e23af93f339b153a474a59c5ea5fd2393b69a90557244403ac",
-    "fetch_kib": {"k_es_count": 1.928405e+08},
-    "write_kib": {"k_es_count": 9.980970e+07},
-    "launches": {"k_es_count": 100},
+    "sources_sha256": "3e9a2711e5648212a33a10248b756ab32a9165d0c0301be1bebe4041a5e3447b",
+    "fetch_kib": {"k_es_bin": 1.92977e+08, "k_es_score_bins": 6.91028e+07},
+    "write_kib": {"k_es_bin": 1.69295e+07, "k_es_score_bins": 4.75563e+07},
+    "launches": 100,
 }
 
 
