@@ -28,7 +28,7 @@ HBM_PEAK_GBPS = 8000.0
 # at that time, and `traffic` is reported as null when the sources have changed since.
 PMC = {
     "workload": "chunglu-111M",
-    "sources_sha256": "e75747c4b512914c0cc05a103c6919bcf74da8f68c95343799185efaa5c6289f",
+    "sources_sha256": "aa90ac2aa8f797fca04d5631d4a8087e2a24760424c364e60633321fa74a9fc0",
     "fetch_factor": 2.0,        # 2 GiB read  -> FETCH_SIZE 1,048,591 KiB
     "write_factor": 1.0,        # 2 GiB written -> WRITE_SIZE 2,097,152 KiB
     "fetch_kib": {"k_tp_score": 1.42641e+07, "k_tp_lookup": 1.36608e+07},

@@ -1289,7 +1289,7 @@ __global__ __launch_bounds__(256) void k_pack_labels(const int32_t *__restrict__
 // A workgroup takes tiles of 256 rows, their entries edge-parallel.  words == nullptr: no packed table (small graphs, whose
 // labels the L2 holds as they are).  With the columns in parts, a part's tiles make kCutTurns turns (every so-manieth tile)
 // for each of its XCDs' workgroups: the first is fixed, the others go to whoever is free, in the end to workgroups of
-// other parts too (ids in order of degree put half of all look-ups in the first part: 111M vertices, 16 labels: 61 ms
+// other parts too (ids in order of degree put half of all look-ups in the first part: 1.6e9 entries, 16 labels: 61 ms
 // with fixed shares, 30 so; a tile at a time from a counter took 43 ms on permuted ids for 22).
 constexpr uint32_t kCutTurns = 8;
 constexpr int kCutTile = 256;
