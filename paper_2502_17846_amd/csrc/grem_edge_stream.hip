@@ -13,10 +13,12 @@
 // padded to whole blocks, a block of nodes being what one workgroup of the per-node kernels owns.
 //
 // Data layout (device memory, by node of the state)
-//   Lb    uint8     label 0/1, 0xFF = unassigned (one byte per random look-up)
+//   Lw    uint64 per 32 nodes: low half = nodes that have a label, high half = those of partition 1 (no label: 0).  A quarter
+//                   of a byte per node is what the random look-ups go to; the per-node kernels take 64 nodes' labels in
+//                   one load and relabel them with a few bit operations
 //   est   double[2] Alg. 1's nbr_counts
-//   mv0, mv1, ov    bitmaps: nodes asking to move to partition 0 / 1, and new nodes whose request was
-//                   rejected.  Bitmaps are ordered sets: bit order is id order, so ranks by id are prefix
+//   mv0, mv1, nw    bitmaps: nodes asking to move to partition 0 / 1, and those of them that have no label
+//                   yet.  Bitmaps are ordered sets: bit order is id order, so ranks by id are prefix
 //                   pop-counts.
 //   mark            bitmap: v is an endpoint of a chunk edge whose other end has no label
 // The chunk's fresh counts (Alg. 2 cnt_nbrs) come in one of two ways, the same integers either way:
@@ -24,9 +26,9 @@
 //                   partition 1; k_es_count adds one 64-bit atomic per edge end, k_es_score reads and clears.
 //   binned (large graphs)     k_es_bin looks the other end's label up for every edge end and sorts the
 //                   (node, label) pairs by ranges of nodes; k_es_score_bins counts a block's pairs in LDS.
-// Per chunk: count or bin -> score (blend, assign, mover ballots) -> k_es_apply (ranks = movers of the earlier
-// blocks + pop-count prefix; admitted moves relabel) -> k_es_spill (closed-form target of the j-th rejected node,
-// sizes).  The sizes live in two copies that take turns from chunk to chunk.
+// Per chunk: count or bin -> score (blend, assign, mover ballots) -> k_es_admit (ranks = movers of the earlier
+// blocks + pop-count prefix; admitted moves relabel; closed-form target of the j-th rejected node; sizes).  The
+// sizes live in two copies that take turns from chunk to chunk.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -44,9 +46,11 @@ typedef unsigned long long u64;
 constexpr int kBlock = 1024;                 // per-node kernels: 16 waves
 constexpr int kWaves = kBlock / 64;
 constexpr int kMaxWaveWords = 64;            // most bitmap words a wave of the per-node kernels owns
-constexpr uint32_t kNone = 0xFFu;
+constexpr int kMaxAdmitWords = 256;          // ... of k_es_admit
+constexpr uint32_t kNone = 2u;               // label of a node that has none
 constexpr int kCountBlock = 256;
-constexpr int kCountUnroll = 4;              // edges in flight per thread of k_es_count
+constexpr int kCountUnroll = 4;              // edges in flight per thread of k_es_count ...
+constexpr int64_t kCountSparse = 1 << 17;    // ... one where they are no more than these
 constexpr int kTurn = 4;                     // bitmap words a wave has in flight
 
 // One group of a run.
@@ -64,17 +68,35 @@ struct EsRun {
     const EsGroup* groups;
     const uint32_t* blk_group;               // group of a block
     u64* S;                                  // [2][groups][2]: sizes, two copies
-    uint8_t* Lb;
+    u64* Lw;
     double2* est;
-    u64 *mark, *mv0, *mv1, *ov;
-    uint32_t *bs0, *bs1;                     // per block: movers to 0 / 1
-    uint32_t* bso;                           // per block of k_es_apply: rejected new nodes
-    int32_t *bd0, *bd1;                      // ... size changes
+    u64 *mark, *mv0, *mv1, *nw;
+    uint4* bs;                               // per block: movers to 0, to 1, those of either without a label
     uint32_t* flags;                         // [0] an endpoint out of range, [1] a bad seed
     uint32_t ngroups;
     int wpw;                                 // bitmap words per wave: a block is kBlock * wpw nodes
-    int awpw;                                // the same in k_es_apply and k_es_spill, a multiple of wpw
+    int awpw;                                // the same in k_es_admit, a multiple of wpw
 };
+
+// label of node v: 0, 1 or kNone
+__device__ __forceinline__ uint32_t es_label(u64 word, uint32_t v)
+{
+    const u64 x = word >> (v & 31u);
+    return (x & 1ull) ? (uint32_t)(x >> 32) & 1u : kNone;
+}
+
+// the labels of 64 nodes (bitmap word w): who has one, who is in partition 1
+struct EsLabels { u64 has, one; };
+__device__ __forceinline__ EsLabels es_load_labels(const EsRun& st, size_t w)
+{
+    const ulonglong2 x = reinterpret_cast<const ulonglong2*>(st.Lw)[w];
+    return {(x.x & 0xFFFFFFFFull) | x.y << 32, x.x >> 32 | (x.y & ~0xFFFFFFFFull)};
+}
+__device__ __forceinline__ void es_store_labels(const EsRun& st, size_t w, EsLabels l)
+{
+    reinterpret_cast<ulonglong2*>(st.Lw)[w] =
+        make_ulonglong2((l.has & 0xFFFFFFFFull) | l.one << 32, l.has >> 32 | (l.one & ~0xFFFFFFFFull));
+}
 
 // first and last edge of the group's chunk (an empty range past its last chunk)
 __device__ __forceinline__ void es_chunk(const EsGroup& g, int64_t chunk, int64_t& lo, int64_t& hi)
@@ -154,36 +176,54 @@ __device__ __forceinline__ u64 es_bcast(u64 x, int i)
     return ((u64)hi << 32) | lo;
 }
 
-__device__ __forceinline__ uint32_t es_wave_sum(uint32_t x)
+// x + the value of x that the cross-lane move CTRL brings (0 where it brings none, or where ROWS leaves the row out)
+template <int CTRL, int ROWS> __device__ __forceinline__ uint32_t es_dpp_add(uint32_t x)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-    return x;
+    return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
 }
-
-// exclusive prefix sum over the lanes of a wave
-__device__ __forceinline__ uint32_t es_wave_exclusive(uint32_t x, int lane)
+// inclusive prefix sum over the lanes of each row of 16 (row_shr by 1, 2, 4, 8), and over all 64 (row_bcast 15 and 31)
+__device__ __forceinline__ uint32_t es_row_inclusive(uint32_t x)
 {
-    uint32_t incl = x;
+    x = es_dpp_add<0x111, 0xF>(x);
+    x = es_dpp_add<0x112, 0xF>(x);
+    x = es_dpp_add<0x114, 0xF>(x);
+    return es_dpp_add<0x118, 0xF>(x);
+}
+__device__ __forceinline__ uint32_t es_wave_inclusive(uint32_t x)
+{
+    return es_dpp_add<0x143, 0xC>(es_dpp_add<0x142, 0xA>(es_row_inclusive(x)));
+}
+__device__ __forceinline__ uint32_t es_lane(uint32_t x, int i) { return (uint32_t)__builtin_amdgcn_readlane((int)x, i); }
+__device__ __forceinline__ uint32_t es_wave_sum(uint32_t x) { return es_lane(es_wave_inclusive(x), 63); }
+__device__ __forceinline__ int es_wave() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
+
+// sums over the workgroup (kBlock threads, all of them call it); every sum is below 2^32
+template <int N> __device__ __forceinline__ void es_block_sums(uint32_t (&x)[N])
+{
+    __shared__ uint32_t part[N][kWaves];
+    static_assert(kWaves == 16, "a row of lanes holds the waves' sums");
+    const int lane = threadIdx.x & 63, wave = es_wave();
+    __syncthreads();
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(incl, o);
-        if (lane >= o) incl += y;
+    for (int i = 0; i < N; ++i) {
+        const uint32_t sum = es_wave_sum(x[i]);
+        if (lane == 0) part[i][wave] = sum;
     }
-    return incl - x;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = es_lane(es_row_inclusive(part[i][lane & 15]), 15);
 }
 
-// sums of a and b over the workgroup (kBlock threads, all of them call it)
-__device__ __forceinline__ void es_block_sums(u64& a, u64& b)
+// exclusive prefix of x over the workgroup's threads and the sum over all of them; wsum: kWaves words of LDS
+__device__ __forceinline__ uint32_t es_block_exclusive(uint32_t x, uint32_t* wsum, uint32_t* total = nullptr)
 {
-    __shared__ u64 wa[kWaves], wb[kWaves];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { a += __shfl_xor(a, o); b += __shfl_xor(b, o); }
+    const int lane = threadIdx.x & 63, wave = es_wave();
+    const uint32_t incl = es_wave_inclusive(x);
+    if (lane == 63) wsum[wave] = incl;
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) { wa[threadIdx.x >> 6] = a; wb[threadIdx.x >> 6] = b; }
-    __syncthreads();
-    a = 0; b = 0;
-    for (int q = 0; q < kWaves; ++q) { a += wa[q]; b += wb[q]; }
+    const uint32_t waves = es_row_inclusive(wsum[lane & 15]);
+    if (total) *total = es_lane(waves, 15);
+    return incl - x + (wave ? es_lane(waves, wave - 1) : 0u);
 }
 
 // Alg. 1, first chunk: the chunk's nodes take seed_algo's labels; sizes are counted.
@@ -195,7 +235,7 @@ __global__ __launch_bounds__(kBlock) void k_es_seed(EsRun st, const int32_t* __r
     const EsGroup& g = st.groups[gi];
     const uint32_t word0 = ((uint32_t)blockIdx.x * kWaves + wave) * st.wpw;
     const u64 mine = lane < st.wpw ? st.mark[word0 + lane] : 0ull;
-    u64 n0 = 0, n1 = 0;
+    EsLabels labels{0ull, 0ull};
     for (int i0 = 0; i0 < st.wpw; i0 += kTurn) {
         int s[kTurn];
         bool on[kTurn];
@@ -206,17 +246,15 @@ __global__ __launch_bounds__(kBlock) void k_es_seed(EsRun st, const int32_t* __r
         }
 #pragma unroll
         for (int u = 0; u < kTurn; ++u) {
-            if (!on[u]) continue;
-            if (s[u] == 0 || s[u] == 1) st.Lb[(size_t)(word0 + i0 + u) * 64 + lane] = (uint8_t)s[u];
-            else st.flags[1] = 1u;
-            n0 += s[u] == 0; n1 += s[u] == 1;
+            if (on[u] && s[u] != 0 && s[u] != 1) st.flags[1] = 1u;
+            const u64 zeros = __ballot(on[u] && s[u] == 0), ones = __ballot(on[u] && s[u] == 1);
+            if (lane == i0 + u) labels = {zeros | ones, ones};
         }
     }
-    es_block_sums(n0, n1);
-    if (threadIdx.x == 0) {
-        if (n0) atomicAdd(&st.S[2 * gi], n0);
-        if (n1) atomicAdd(&st.S[2 * gi + 1], n1);
-    }
+    if (mine) es_store_labels(st, word0 + lane, labels);           // (no label before)
+    uint32_t sizes[2] = {(uint32_t)__popcll(labels.has & ~labels.one), (uint32_t)__popcll(labels.one)};
+    es_block_sums(sizes);
+    if (threadIdx.x < 2 && sizes[threadIdx.x]) atomicAdd(&st.S[2 * gi + threadIdx.x], (u64)sizes[threadIdx.x]);
 }
 
 // flags[1] = 1 if the seeds fill a partition beyond its capacity
@@ -231,35 +269,39 @@ __global__ __launch_bounds__(256) void k_es_seed_sizes(EsRun st)
 // ends keep for the partition of the other end (a loop counts once, for the node itself).  An
 // unassigned other end adds nothing; the node's bit in `mark` is set instead, so that a node of the
 // chunk is known by a non-zero count or its bit: one atomic per edge end either way.
-// Random look-ups and atomics, 39 G/s of them together once Lb and hc outgrow the L2 (then the ends are binned).
+// Random look-ups and atomics, 39 G/s of them together once labels and hc outgrow the L2 (then the ends are binned).
+template <int U>
 __global__ __launch_bounds__(kCountBlock) void k_es_count(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                                                           EsRun st, int64_t chunk, u64* hc)
 {
     const EsGroup g = st.groups[blockIdx.y];
     int64_t lo, hi;
     es_chunk(g, chunk, lo, hi);
-    const uint8_t* __restrict__ Lb = st.Lb + g.node0;
+    const u64* __restrict__ Lw = st.Lw + (g.node0 >> 5);           // (a group starts at a whole block)
     hc += g.node0;
-    u64* mark = st.mark + (g.node0 >> 6);          // (a group starts at a whole block)
+    u64* mark = st.mark + (g.node0 >> 6);
     const int64_t threads = (int64_t)gridDim.x * blockDim.x;
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (int64_t base = lo + tid; base < hi; base += threads * kCountUnroll) {
-        uint32_t s[kCountUnroll], d[kCountUnroll], ls[kCountUnroll], ld[kCountUnroll];
-        bool in[kCountUnroll];
+    for (int64_t base = lo + tid; base < hi; base += threads * U) {
+        uint32_t s[U], d[U], ls[U], ld[U];
+        u64 ws[U], wd[U];
+        bool in[U];
 #pragma unroll
-        for (int u = 0; u < kCountUnroll; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int64_t e = base + (int64_t)u * threads;
             in[u] = e < hi;
             s[u] = in[u] ? (uint32_t)src[e] : 0u;
             d[u] = in[u] ? (uint32_t)dst[e] : 0u;
         }
 #pragma unroll
-        for (int u = 0; u < kCountUnroll; ++u) {
-            ls[u] = in[u] ? (uint32_t)Lb[s[u]] : kNone;
-            ld[u] = in[u] ? (uint32_t)Lb[d[u]] : kNone;
+        for (int u = 0; u < U; ++u) {
+            ws[u] = in[u] ? Lw[s[u] >> 5] : 0ull;
+            wd[u] = in[u] ? Lw[d[u] >> 5] : 0ull;
         }
 #pragma unroll
-        for (int u = 0; u < kCountUnroll; ++u) {
+        for (int u = 0; u < U; ++u) { ls[u] = es_label(ws[u], s[u]); ld[u] = es_label(wd[u], d[u]); }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
             if (!in[u]) continue;
             if (ld[u] != kNone) atomicAdd(&hc[s[u]], ld[u] ? (1ull << 32) : 1ull);
             else atomicOr(&mark[s[u] >> 6], 1ull << (s[u] & 63u));
@@ -312,18 +354,6 @@ __global__ __launch_bounds__(kBlock) void k_es_hist(const int32_t* __restrict__ 
     __syncthreads();
     const uint32_t c = hist[threadIdx.x];
     if (c) atomicAdd(&table[(size_t)blockIdx.z * kBinTableStride + threadIdx.x], c);
-}
-
-// exclusive prefix of x over the workgroup's threads; wsum: kWaves words of LDS
-__device__ __forceinline__ uint32_t es_block_exclusive(uint32_t x, uint32_t* wsum)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t excl = es_wave_exclusive(x, lane);
-    if (lane == 63) wsum[wave] = excl + x;
-    __syncthreads();
-    uint32_t before = excl;
-    for (int q = 0; q < wave; ++q) before += wsum[q];
-    return before;
 }
 
 // The bins of more than `limit` pairs in a chunk, which no workgroup should count alone (k_es_crowd).
@@ -379,11 +409,11 @@ __global__ __launch_bounds__(kBlock) void k_es_bin(const int32_t* __restrict__ s
         a[u] = e < hi ? g.node0 + (uint32_t)src[e] : kNothing;
         b[u] = e < hi ? g.node0 + (uint32_t)dst[e] : kNothing;
     }
-    uint32_t la[kBinPer], lb[kBinPer];
+    u64 la[kBinPer], lb[kBinPer];
 #pragma unroll
     for (int u = 0; u < kBinPer; ++u) {
-        la[u] = a[u] != kNothing ? (uint32_t)st.Lb[a[u]] : 0u;
-        lb[u] = a[u] != kNothing ? (uint32_t)st.Lb[b[u]] : 0u;
+        la[u] = a[u] != kNothing ? st.Lw[a[u] >> 5] : 0ull;
+        lb[u] = a[u] != kNothing ? st.Lw[b[u] >> 5] : 0ull;
     }
     __syncthreads();
     uint32_t ra[kBinPer], rb[kBinPer];             // rank among the tile's pairs of the same bin
@@ -393,8 +423,9 @@ __global__ __launch_bounds__(kBlock) void k_es_bin(const int32_t* __restrict__ s
         ra[u] = atomicAdd(&hist[a[u] >> cb], 1u);
         const bool loop = a[u] == b[u];
         if (!loop) rb[u] = atomicAdd(&hist[b[u] >> cb], 1u);
-        a[u] |= (lb[u] < 2u ? lb[u] : 2u) << 30;
-        b[u] = loop ? kNothing : b[u] | (la[u] < 2u ? la[u] : 2u) << 30;
+        const uint32_t of_a = es_label(la[u], a[u]), of_b = es_label(lb[u], b[u]);
+        a[u] |= of_b << 30;
+        b[u] = loop ? kNothing : b[u] | of_a << 30;
     }
     __syncthreads();
     const uint32_t c = hist[tid];
@@ -424,8 +455,9 @@ __global__ __launch_bounds__(kBlock) void k_es_bin(const int32_t* __restrict__ s
 
 // Alg. 1 for the nodes of up to kTurn bitmap words, one lane per node and word: blend the stored estimate with
 // the fresh counts h when the node has a label, store the estimate, ask `assign` for a partition.  Sets the words of
-// nodes that want to move (lane i0 + u keeps word i0 + u).  on: the node belongs to the chunk.
-__device__ __forceinline__ void es_score_words(const EsRun& st, uint32_t word0, int i0, const bool (&on)[kTurn],
+// nodes that want to move (lane i0 + u keeps word i0 + u).  labels: lane i0 + u has those of word i0 + u.  on: the node belongs
+// to the chunk.
+__device__ __forceinline__ void es_score_words(const EsRun& st, uint32_t word0, int i0, const EsLabels& labels, const bool (&on)[kTurn],
                                                const uint32_t (&h0)[kTurn], const uint32_t (&h1)[kTurn], int first, int fixed,
                                                long long P, long long S0, long long S1, u64& out0, u64& out1)
 {
@@ -434,9 +466,9 @@ __device__ __forceinline__ void es_score_words(const EsRun& st, uint32_t word0, 
     double2 prev[kTurn];
     bool blend[kTurn];
 #pragma unroll
-    for (int u = 0; u < kTurn; ++u) old[u] = on[u] ? (uint32_t)st.Lb[(size_t)(word0 + i0 + u) * 64 + lane] : kNone;
-#pragma unroll
     for (int u = 0; u < kTurn; ++u) {
+        const u64 has = es_bcast(labels.has, (i0 + u) & 63), one = es_bcast(labels.one, (i0 + u) & 63);
+        old[u] = ((has >> lane) & 1ull) ? (uint32_t)(one >> lane) & 1u : kNone;
         blend[u] = on[u] && !first && old[u] != kNone && !fixed;
         if (blend[u]) prev[u] = st.est[(size_t)(word0 + i0 + u) * 64 + lane];
     }
@@ -460,10 +492,22 @@ __device__ __forceinline__ void es_score_words(const EsRun& st, uint32_t word0, 
     }
 }
 
-__device__ __forceinline__ void es_store_movers(const EsRun& st, u64 movers0, u64 movers1, uint32_t block)
+// a lane's word of movers: stored, and their numbers added to the lane's (to 0, to 1, those of either without a label)
+__device__ __forceinline__ void es_store_words(const EsRun& st, uint32_t word, u64 out0, u64 out1, const EsLabels& labels, uint32_t (&m)[4])
 {
-    es_block_sums(movers0, movers1);
-    if (threadIdx.x == 0) { st.bs0[block] = (uint32_t)movers0; st.bs1[block] = (uint32_t)movers1; }
+    const u64 fresh = (out0 | out1) & ~labels.has;
+    st.mv0[word] = out0;
+    st.mv1[word] = out1;
+    st.nw[word] = fresh;
+    m[0] += (uint32_t)__popcll(out0);
+    m[1] += (uint32_t)__popcll(out1);
+    m[2] += (uint32_t)__popcll(out0 & fresh);
+    m[3] += (uint32_t)__popcll(out1 & fresh);
+}
+__device__ __forceinline__ void es_store_movers(const EsRun& st, uint32_t (&m)[4], uint32_t block)
+{
+    es_block_sums(m);
+    if (threadIdx.x == 0) st.bs[block] = make_uint4(m[0], m[1], m[2], m[3]);
 }
 
 // The pairs of the chunk's crowded bins, counted before the scoring by all workgroups: a piece of a bin's pairs and one of
@@ -538,6 +582,7 @@ __global__ __launch_bounds__(kBlock) void k_es_score(EsRun st, int par, int firs
     const uint32_t word0 = ((uint32_t)blockIdx.x * kWaves + wave) * st.wpw;
     const bool mine = lane < st.wpw;
     const u64 myword = mine ? st.mark[word0 + lane] : 0ull;
+    const EsLabels labels = mine ? es_load_labels(st, word0 + lane) : EsLabels{0ull, 0ull};
     u64 out0 = 0ull, out1 = 0ull;
     for (int i0 = 0; i0 < st.wpw; i0 += kTurn) {
         u64 h[kTurn];
@@ -553,14 +598,14 @@ __global__ __launch_bounds__(kBlock) void k_es_score(EsRun st, int par, int firs
             h0[u] = (uint32_t)h[u];
             h1[u] = (uint32_t)(h[u] >> 32);
         }
-        es_score_words(st, word0, i0, on, h0, h1, first, fixed, P, S0, S1, out0, out1);
+        es_score_words(st, word0, i0, labels, on, h0, h1, first, fixed, P, S0, S1, out0, out1);
     }
+    uint32_t movers[4] = {0u, 0u, 0u, 0u};
     if (mine) {
-        st.mv0[word0 + lane] = out0;
-        st.mv1[word0 + lane] = out1;
+        es_store_words(st, word0 + lane, out0, out1, labels, movers);
         if (myword) st.mark[word0 + lane] = 0ull;
     }
-    es_store_movers(st, (u64)__popcll(out0), (u64)__popcll(out1), blockIdx.x);
+    es_store_movers(st, movers, blockIdx.x);
 }
 
 // cnt_nbrs, second half, from the binned pairs: a block counts the pairs of its bin that are its own in LDS (the
@@ -591,6 +636,8 @@ __global__ __launch_bounds__(kBlock) void k_es_score_bins(EsRun st, int par, int
     if (place) {                                   // counted by k_es_crowd
         u64* hc = crowd.hc + (((size_t)place - 1) << cb) + in_bin;
         uint32_t* was_seen = crowd.seen + ((((size_t)place - 1) << cb) + in_bin) / 32;
+        const uint32_t word0 = block * (bn / 64) + wave * st.wpw;
+        const EsLabels labels = lane < st.wpw ? es_load_labels(st, word0 + lane) : EsLabels{0ull, 0ull};
         u64 out0 = 0ull, out1 = 0ull;
         for (int i0 = 0; i0 < st.wpw; i0 += kTurn) {
             u64 h[kTurn];
@@ -611,19 +658,21 @@ __global__ __launch_bounds__(kBlock) void k_es_score_bins(EsRun st, int par, int
                 h0[u] = (uint32_t)h[u];
                 h1[u] = (uint32_t)(h[u] >> 32);
             }
-            es_score_words(st, block * (bn / 64) + wave * st.wpw, i0, on, h0, h1, first, fixed, P, S0, S1, out0, out1);
+            es_score_words(st, word0, i0, labels, on, h0, h1, first, fixed, P, S0, S1, out0, out1);
         }
-        const uint32_t word0 = block * (bn / 64) + wave * st.wpw;
-        if (lane < st.wpw) { st.mv0[word0 + lane] = out0; st.mv1[word0 + lane] = out1; }
-        es_store_movers(st, (u64)__popcll(out0), (u64)__popcll(out1), block);
+        uint32_t movers[4] = {0u, 0u, 0u, 0u};
+        if (lane < st.wpw) es_store_words(st, word0 + lane, out0, out1, labels, movers);
+        es_store_movers(st, movers, block);
         return;
     }
     const bool narrow = p1 - p0 <= 65535u;
     const int rounds = narrow ? 1 : 2;
     const uint32_t sub = bn / rounds;              // nodes per round
     const int nw = st.wpw / rounds;                // words per wave and round
-    u64 movers0 = 0, movers1 = 0;
+    uint32_t movers[4] = {0u, 0u, 0u, 0u};
     for (int round = 0; round < rounds; ++round) {
+        const uint32_t word0 = block * (bn / 64) + round * (sub / 64) + wave * nw;
+        const EsLabels labels = lane < nw ? es_load_labels(st, word0 + lane) : EsLabels{0ull, 0ull};
         __syncthreads();
         for (uint32_t i = tid; i < bn; i += kBlock) cnt[i] = 0u;
         for (uint32_t i = tid; i < bn / 32; i += kBlock) seen[i] = 0u;
@@ -645,7 +694,6 @@ __global__ __launch_bounds__(kBlock) void k_es_score_bins(EsRun st, int par, int
             if (p1 - i <= (uint32_t)(kBlock * U)) break;
         }
         __syncthreads();
-        const uint32_t word0 = block * (bn / 64) + round * (sub / 64) + wave * nw;
         u64 out0 = 0ull, out1 = 0ull;
         for (int i0 = 0; i0 < nw; i0 += kTurn) {
             bool on[kTurn];
@@ -664,161 +712,153 @@ __global__ __launch_bounds__(kBlock) void k_es_score_bins(EsRun st, int par, int
                 }
                 on[u] = (h0[u] | h1[u]) != 0u || (in && ((seen[rel >> 5] >> (rel & 31u)) & 1u));
             }
-            es_score_words(st, word0, i0, on, h0, h1, first, fixed, P, S0, S1, out0, out1);
+            es_score_words(st, word0, i0, labels, on, h0, h1, first, fixed, P, S0, S1, out0, out1);
         }
-        if (lane < nw) { st.mv0[word0 + lane] = out0; st.mv1[word0 + lane] = out1; }
-        movers0 += (u64)__popcll(out0);
-        movers1 += (u64)__popcll(out1);
+        if (lane < nw) es_store_words(st, word0 + lane, out0, out1, labels, movers);
     }
-    es_store_movers(st, movers0, movers1, block);
+    es_store_movers(st, movers, block);
+}
+
+// the first c set bits of x (c <= their number).  Between "none" and "all" there is one word per partition and chunk.
+__device__ __forceinline__ u64 es_first_bits(u64 x, long long c)
+{
+    if (c >= (long long)__popcll(x)) return x;
+    u64 rest = x;
+    for (; c > 0; --c) rest &= rest - 1ull;
+    return x ^ rest;
+}
+
+// The rejected new nodes of the group that asked for partition p (more movers ask for it than `room`), in blocks before
+// `own` and in all: every block's movers are in order, so all after the room-th of them are rejected; the block in
+// which the room runs out is looked at word by word.
+__device__ __forceinline__ void es_rejected(const EsRun& st, uint32_t blk0, uint32_t nblk, int p, long long room, uint32_t own, uint32_t& before, uint32_t& all)
+{
+    __shared__ uint32_t wsum[kWaves], s_block, s_first;
+    const u64* __restrict__ mv = p ? st.mv1 : st.mv0;
+    const uint32_t last = (uint32_t)room;          // rank of the first that is rejected
+    uint32_t carry = 0, out[2] = {0u, 0u};         // before own, in all
+    for (uint32_t base = blk0; base < blk0 + nblk; base += kBlock) {
+        const uint32_t b = base + threadIdx.x;
+        uint4 q = make_uint4(0u, 0u, 0u, 0u);
+        if (b < blk0 + nblk) q = st.bs[b];
+        const uint32_t x = p ? q.y : q.x, fresh = p ? q.w : q.z;
+        uint32_t turn;
+        const uint32_t first = carry + es_block_exclusive(x, wsum, &turn);
+        if (last >= first && last - first < x) { s_block = b; s_first = first; }
+        if (first > last) {                        // all of its movers are rejected
+            out[1] += fresh;
+            if (b < own) out[0] += fresh;
+        }
+        carry += turn;
+        __syncthreads();
+    }
+    // the block itself: a thread per word
+    const uint32_t block = s_block, words = (uint32_t)(kWaves * st.wpw), word = block * words + threadIdx.x;
+    const u64 m = threadIdx.x < words ? mv[word] : 0ull, fresh = threadIdx.x < words ? st.nw[word] : 0ull;       // (words <= kBlock)
+    const long long rank = (long long)s_first + es_block_exclusive((uint32_t)__popcll(m), wsum);
+    const uint32_t here = (uint32_t)__popcll((m & ~es_first_bits(m, room - rank)) & fresh);
+    out[1] += here;
+    if (block < own) out[0] += here;
+    es_block_sums(out);
+    before = out[0];
+    all = out[1];
+    __syncthreads();
 }
 
 // Admission: a mover whose rank among the chunk's requests for its target (ascending id) is below
-// the room the target had when the chunk started is relabelled (fix_sizes, Alg. 2, as per-block
-// deltas); a rejected node without a label is recorded in ov.  Every block adds up the movers of its group's
-// earlier blocks itself.  Few words per wave: a lane per node, word by word.  Many: a wave that has movers copies the
-// labels of its words into LDS with wide loads, every lane then walks the movers of its own
-// word there, and the labels are written back if any changed.
-constexpr int kApplyByNode = 4;
-__global__ __launch_bounds__(kBlock) void k_es_apply(EsRun st, int par)
+// the room the target had when the chunk started is relabelled (fix_sizes, Alg. 2).  Rejected new nodes are placed one by
+// one, ascending id, in the smaller partition (0 on a tie), in closed form: the first |difference| go to the smaller one,
+// the rest alternate 0,1,...  Every block adds up its group's movers itself, and where a partition has not room for all of
+// them also the rejected ones of the blocks before it; the group's first block writes the sizes after the chunk to
+// their other copy.
+// A lane takes W neighbouring words of 64 nodes (awpw = 64 * W words per wave, or fewer with W = 1): the admitted movers
+// of a word are its first bits, as many as there is room for, the alternation over rejected ones is a prefix parity, and labels
+// change in a few bit operations.  W and awpw: so many that 256 blocks or fewer do it, as each adds up all blocks' counts
+// (es_shape).  In two launches (admission, spill), with labels of a byte each and movers taken one by one: 103 us per chunk at
+// 111M nodes, 13 at 20,000; now 53 and 6.
+template <int W>
+__global__ __launch_bounds__(kBlock) void k_es_admit(EsRun st, int par)
 {
-    extern __shared__ uint4 slab4[];                  // wpw * 64 bytes per wave
-    __shared__ uint32_t c0[kWaves], c1[kWaves];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wpw = st.awpw;
-    const uint32_t b_own = (uint32_t)blockIdx.x * (uint32_t)(st.awpw / st.wpw);      // its first block of the scoring
-    const uint32_t gi = st.blk_group[b_own];
-    const long long P = st.groups[gi].P;
-    const uint32_t blk0 = st.groups[gi].blk0;
-    const uint32_t word0 = ((uint32_t)blockIdx.x * kWaves + wave) * wpw;
-    const bool mine = lane < wpw;
-    const u64 my0 = mine ? st.mv0[word0 + lane] : 0ull, my1 = mine ? st.mv1[word0 + lane] : 0ull;
-    u64 before0 = 0, before1 = 0;
-    for (uint32_t b = blk0 + threadIdx.x; b < b_own; b += kBlock) { before0 += st.bs0[b]; before1 += st.bs1[b]; }
-    const uint32_t p0 = __popcll(my0), p1 = __popcll(my1);
-    const uint32_t ex0 = es_wave_exclusive(p0, lane), ex1 = es_wave_exclusive(p1, lane);
-    if (lane == 63) { c0[wave] = ex0 + p0; c1[wave] = ex1 + p1; }
-    es_block_sums(before0, before1);
-    long long base0 = (long long)before0, base1 = (long long)before1;
-    for (int q = 0; q < wave; ++q) { base0 += c0[q]; base1 += c1[q]; }
-    const long long room0 = P - (long long)st.S[2 * (par * st.ngroups + gi)], room1 = P - (long long)st.S[2 * (par * st.ngroups + gi) + 1];
-    u64 outo = 0ull;
-    int32_t delta0 = 0, delta1 = 0;
-    if (wpw <= kApplyByNode) {
-        for (int i = 0; i < wpw; ++i) {
-            const u64 w0 = es_bcast(my0, i), w1 = es_bcast(my1, i);
-            if (!(w0 | w1)) continue;
-            const u64 below = (1ull << lane) - 1ull;
-            const bool to0 = (w0 >> lane) & 1ull, to1 = (w1 >> lane) & 1ull;
-            bool rejected = false;
-            if (to0 || to1) {
-                uint8_t* label = st.Lb + (size_t)(word0 + i) * 64 + lane;
-                const uint32_t old = *label;
-                const long long rank = to0 ? base0 + __builtin_amdgcn_readlane(ex0, i) + __popcll(w0 & below)
-                                           : base1 + __builtin_amdgcn_readlane(ex1, i) + __popcll(w1 & below);
-                if (rank < (to0 ? room0 : room1)) {
-                    *label = to0 ? 0 : 1;
-                    if (to0) { delta0 += 1; delta1 -= (int32_t)(old == 1u); }
-                    else { delta1 += 1; delta0 -= (int32_t)(old == 0u); }
-                } else {
-                    rejected = old == kNone;
-                }
-            }
-            const u64 o = __ballot(rejected);
-            if (lane == i) outo = o;
-        }
-    } else {
-        const u64 movers = __ballot((my0 | my1) != 0ull);
-        uint4* wslab4 = slab4 + wave * (wpw * 4);
-        uint4* labels4 = reinterpret_cast<uint4*>(st.Lb + (size_t)word0 * 64);
-        if (movers)
-            for (int q = lane; q < wpw * 4; q += 64) wslab4[q] = labels4[q];
-        // a lane walks the movers of its own word, in id order; ranks continue from the words before it
-        uint8_t* mine64 = reinterpret_cast<uint8_t*>(wslab4) + lane * 64;
-        bool dirty = false;
-        long long r0 = base0 + ex0, r1 = base1 + ex1;
-        for (u64 todo = my0; todo; todo &= todo - 1ull, ++r0) {
-            const int b = __builtin_ctzll(todo);
-            const uint32_t old = mine64[b];
-            if (r0 < room0) { mine64[b] = 0; dirty = true; delta0 += 1; delta1 -= (int32_t)(old == 1u); }
-            else if (old == kNone) outo |= 1ull << b;
-        }
-        for (u64 todo = my1; todo; todo &= todo - 1ull, ++r1) {
-            const int b = __builtin_ctzll(todo);
-            const uint32_t old = mine64[b];
-            if (r1 < room1) { mine64[b] = 1; dirty = true; delta1 += 1; delta0 -= (int32_t)(old == 0u); }
-            else if (old == kNone) outo |= 1ull << b;
-        }
-        if (__ballot(dirty))
-            for (int q = lane; q < wpw * 4; q += 64) labels4[q] = wslab4[q];
+    __shared__ uint32_t c0[kWaves], c1[kWaves], co[kWaves];
+    const int lane = threadIdx.x & 63, wave = es_wave(), awpw = st.awpw;
+    const uint32_t own = (uint32_t)blockIdx.x * (uint32_t)(awpw / st.wpw);            // its first block of the scoring
+    const uint32_t gi = st.blk_group[own];
+    const uint32_t blk0 = st.groups[gi].blk0, nblk = st.groups[gi].nblk;
+    const uint32_t word0 = ((uint32_t)blockIdx.x * kWaves + wave) * awpw + lane * W;
+    const bool mine = lane * W < awpw;
+    u64 my0[W], my1[W], fresh[W];
+    EsLabels old[W];
+    uint32_t n0 = 0, n1 = 0;
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        my0[i] = mine ? st.mv0[word0 + i] : 0ull;
+        my1[i] = mine ? st.mv1[word0 + i] : 0ull;
+        fresh[i] = mine ? st.nw[word0 + i] : 0ull;
+        old[i] = mine ? es_load_labels(st, word0 + i) : EsLabels{0ull, 0ull};
     }
-    if (mine) st.ov[word0 + lane] = outo;
-    // (the two deltas share a word: at most 65,536 nodes of a block, offset to stay positive)
-    u64 packed = (u64)__popcll(outo), deltas = (u64)(uint32_t)(delta0 + 256) | ((u64)(uint32_t)(delta1 + 256) << 32);
-    es_block_sums(packed, deltas);
-    if (threadIdx.x == 0) {
-        st.bso[blockIdx.x] = (uint32_t)packed;
-        st.bd0[blockIdx.x] = (int32_t)(uint32_t)deltas - 256 * kBlock;
-        st.bd1[blockIdx.x] = (int32_t)(uint32_t)(deltas >> 32) - 256 * kBlock;
-    }
-}
-
-// Rejected new nodes are placed one by one, ascending id, in the smaller partition (0 on a tie), in closed
-// form: the first |difference| go to the smaller one, the rest alternate 0,1,...  Every block adds up its
-// group's rejected nodes itself; the group's first block writes the sizes after the chunk to their other copy.
-__global__ __launch_bounds__(kBlock) void k_es_spill(EsRun st, int par)
-{
-    __shared__ uint32_t co[kWaves];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wpw = st.awpw;
-    const uint32_t each = (uint32_t)(st.awpw / st.wpw);
-    const uint32_t gi = st.blk_group[blockIdx.x * each];
-    const uint32_t blk0 = st.groups[gi].blk0 / each, nblk = st.groups[gi].nblk / each;
-    u64 total = 0, before = 0;
+    uint32_t sums[6] = {0u, 0u, 0u, 0u, 0u, 0u};   // movers to 0 and 1: in earlier blocks, in all; those of all without a label
     for (uint32_t b = blk0 + threadIdx.x; b < blk0 + nblk; b += kBlock) {
-        const uint32_t c = st.bso[b];
-        total += c;
-        if (b < blockIdx.x) before += c;
+        const uint4 q = st.bs[b];
+        if (b < own) { sums[0] += q.x; sums[1] += q.y; }
+        sums[2] += q.x; sums[3] += q.y;
+        sums[4] += q.z; sums[5] += q.w;
     }
-    es_block_sums(total, before);
-    const u64* S = st.S + 2 * (par * st.ngroups + gi);
-    if (total == 0 && blockIdx.x != blk0) return;
-    u64 d0 = 0, d1 = 0;
-    for (uint32_t b = blk0 + threadIdx.x; b < blk0 + nblk; b += kBlock) { d0 += (u64)(long long)st.bd0[b]; d1 += (u64)(long long)st.bd1[b]; }
-    es_block_sums(d0, d1);
-    const long long a = (long long)(S[0] + d0), b = (long long)(S[1] + d1);        // after the admissions
-    const long long gap = a <= b ? b - a : a - b;
-    if (blockIdx.x == blk0 && threadIdx.x == 0) {
-        const long long lead = (long long)total < gap ? (long long)total : gap;
-        const long long rest = (long long)total - lead;
+#pragma unroll
+    for (int i = 0; i < W; ++i) { n0 += (uint32_t)__popcll(my0[i]); n1 += (uint32_t)__popcll(my1[i]); }
+    es_block_sums(sums);
+    const long long P = st.groups[gi].P;
+    const long long S0 = (long long)st.S[2 * (par * st.ngroups + gi)], S1 = (long long)st.S[2 * (par * st.ngroups + gi) + 1];
+    const long long room0 = P - S0 > 0 ? P - S0 : 0, room1 = P - S1 > 0 ? P - S1 : 0;
+    long long rank0 = (long long)(sums[0] + es_block_exclusive(n0, c0)), rank1 = (long long)(sums[1] + es_block_exclusive(n1, c1));
+    const long long all0 = (long long)sums[2], all1 = (long long)sums[3];
+    // rejected new nodes: in earlier blocks, in all, by what they asked for
+    uint32_t out_before = 0, out0 = 0, out1 = 0;
+    if (all0 > room0) es_rejected(st, blk0, nblk, 0, room0, own, out_before, out0);
+    if (all1 > room1) { uint32_t more; es_rejected(st, blk0, nblk, 1, room1, own, more, out1); out_before += more; }
+    const long long adm0 = all0 < room0 ? all0 : room0, adm1 = all1 < room1 ? all1 : room1;
+    const long long new0 = (long long)(sums[4] - out0), new1 = (long long)(sums[5] - out1);      // admitted
+    const long long a = S0 + adm0 - (adm1 - new1), b = S1 + adm1 - (adm0 - new0);                // sizes after the admissions
+    const long long gap = a <= b ? b - a : a - b, total = (long long)out0 + (long long)out1;
+    if (own == blk0 && threadIdx.x == 0) {
+        const long long lead = total < gap ? total : gap, rest = total - lead;
         u64* next = st.S + 2 * ((par ^ 1) * st.ngroups + gi);
         next[0] = (u64)(a + (a <= b ? lead : 0) + (rest + 1) / 2);
         next[1] = (u64)(b + (a <= b ? 0 : lead) + rest / 2);
     }
-    if (total == 0) return;
-    const uint32_t word0 = ((uint32_t)blockIdx.x * kWaves + wave) * wpw;
-    const u64 myo = lane < wpw ? st.ov[word0 + lane] : 0ull;
-    const uint32_t p = __popcll(myo);
-    const uint32_t ex = es_wave_exclusive(p, lane);
-    if (lane == 63) co[wave] = ex + p;
-    __syncthreads();
-    long long base = (long long)before;
-    for (int q = 0; q < wave; ++q) base += co[q];
-    for (u64 todo = __ballot(myo != 0ull); todo; todo &= todo - 1ull) {
-        const int i = __builtin_ctzll(todo);
-        const u64 o = es_bcast(myo, i);
-        if ((o >> lane) & 1ull) {
-            const long long j = base + __builtin_amdgcn_readlane(ex, i) + __popcll(o & ((1ull << lane) - 1ull));
-            const int t = j < gap ? (a <= b ? 0 : 1) : (int)((j - gap) & 1);
-            st.Lb[(size_t)(word0 + i) * 64 + lane] = (uint8_t)t;
-        }
+    u64 to0[W], to1[W];
+    uint32_t outs = 0;
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        to0[i] = es_first_bits(my0[i], room0 - rank0);
+        to1[i] = es_first_bits(my1[i], room1 - rank1);
+        rank0 += __popcll(my0[i]);
+        rank1 += __popcll(my1[i]);
+        fresh[i] &= (my0[i] | my1[i]) & ~(to0[i] | to1[i]);                          // rejected
+        outs += (uint32_t)__popcll(fresh[i]);
+    }
+    long long j = (long long)out_before;                                             // placements before the lane's
+    if (total) j += (long long)es_block_exclusive(outs, co);
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        if (!(to0[i] | to1[i] | fresh[i])) continue;
+        const u64 lead = es_first_bits(fresh[i], gap - j), rest = fresh[i] ^ lead;
+        u64 odd = rest;                                                              // bit x: an odd number of bits of rest up to x
+        if (rest)
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) odd ^= odd << o;
+        const long long first = j + __popcll(lead) - gap;                            // of rest, among those that alternate
+        const u64 ones = to1[i] | (a <= b ? 0ull : lead) | (rest & ((first & 1) ? odd : ~odd));
+        es_store_labels(st, word0 + i, {old[i].has | to0[i] | to1[i] | fresh[i], (old[i].one & ~to0[i]) | ones});
+        j += __popcll(fresh[i]);
     }
 }
 
-__global__ __launch_bounds__(256) void k_es_expand(int64_t n, const uint8_t* __restrict__ Lb, int32_t* parts,
+__global__ __launch_bounds__(256) void k_es_expand(int64_t n, const u64* __restrict__ Lw, int32_t* parts,
                                                    const u64* S, int64_t* sizes_out)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
-        const uint32_t l = Lb[v];
+        const uint32_t l = es_label(Lw[v >> 5], (uint32_t)v);
         parts[v] = l == kNone ? -1 : (int32_t)l;
     }
     if (sizes_out && blockIdx.x == 0 && threadIdx.x < 2) sizes_out[threadIdx.x] = (int64_t)S[threadIdx.x];
@@ -861,16 +901,16 @@ constexpr int kSelTile = kSelBlock * kSelPer;
 __global__ __launch_bounds__(kBlock) void k_rb_count(EsRun st)
 {
     const EsGroup& g = st.groups[st.blk_group[blockIdx.x]];
-    const uint32_t bn = (uint32_t)(kBlock * st.wpw), v0 = blockIdx.x * bn;
-    u64 zeros = 0, nones = 0;
-    for (uint32_t i = threadIdx.x; i < bn; i += kBlock) {
-        if (v0 + i - g.node0 >= g.nv) break;
-        const uint32_t l = st.Lb[v0 + i];
-        zeros += l == 0u;
-        nones += l == kNone;
+    const uint32_t bw = (uint32_t)(kWaves * st.wpw), word = blockIdx.x * bw + threadIdx.x, v = word * 64u - g.node0;   // (a thread per word)
+    uint32_t n[2] = {0u, 0u};
+    if (threadIdx.x < bw && v < g.nv) {
+        const EsLabels l = es_load_labels(st, word);
+        const u64 in = g.nv - v < 64u ? (1ull << (g.nv - v)) - 1ull : ~0ull;
+        n[0] = (uint32_t)__popcll(l.has & ~l.one);
+        n[1] = (uint32_t)__popcll(in & ~l.has);
     }
-    es_block_sums(zeros, nones);
-    if (threadIdx.x == 0) { st.bs0[blockIdx.x] = (uint32_t)zeros; st.bs1[blockIdx.x] = (uint32_t)nones; }
+    es_block_sums(n);
+    if (threadIdx.x == 0) st.bs[blockIdx.x] = make_uint4(n[0], n[1], 0u, 0u);
 }
 
 // Nodes the two-partition run left without a label (no edge inside the group) are placed one by one, ascending id,
@@ -886,17 +926,17 @@ __global__ __launch_bounds__(kBlock) void k_rb_children(EsRun st, int par, const
                                                         long long* nodes0)
 {
     __shared__ uint32_t cz[kWaves], cn[kWaves];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wpw = st.wpw;
+    const int lane = threadIdx.x & 63, wave = es_wave(), wpw = st.wpw;
     const uint32_t gi = st.blk_group[blockIdx.x];
     const EsGroup g = st.groups[gi];
-    u64 zeros = 0, nones = 0, zeros_all = 0, nones_all = 0;
+    uint32_t sums[4] = {0u, 0u, 0u, 0u};          // zeros and nodes without a label: in earlier blocks, in all
     for (uint32_t b = g.blk0 + threadIdx.x; b < g.blk0 + g.nblk; b += kBlock) {
-        const uint32_t z = st.bs0[b], e = st.bs1[b];
-        zeros_all += z; nones_all += e;
-        if (b < blockIdx.x) { zeros += z; nones += e; }
+        const uint32_t z = st.bs[b].x, e = st.bs[b].y;
+        sums[2] += z; sums[3] += e;
+        if (b < blockIdx.x) { sums[0] += z; sums[1] += e; }
     }
-    es_block_sums(zeros, nones);
-    es_block_sums(zeros_all, nones_all);
+    es_block_sums(sums);
+    const uint32_t zeros_all = sums[2], nones_all = sums[3];
     const long long S0 = (long long)st.S[2 * (par * st.ngroups + gi)], S1 = (long long)st.S[2 * (par * st.ngroups + gi) + 1];
     const long long gap = S0 <= S1 ? S1 - S0 : S0 - S1;
     const bool lead0 = S0 <= S1;
@@ -908,22 +948,19 @@ __global__ __launch_bounds__(kBlock) void k_rb_children(EsRun st, int par, const
     if (blockIdx.x == g.blk0 && threadIdx.x == 0) nodes0[g.id] = count0;
     // a wave's nodes: its words one after the other; their counts of zeros and of nodes without a label
     const uint32_t first = ((uint32_t)blockIdx.x * kWaves + wave) * wpw * 64u;
-    uint32_t wz = 0, wn = 0;
-    for (int i = 0; i < wpw; ++i) {
-        const uint32_t v = first + i * 64u + lane;
-        const uint32_t l = v - g.node0 < g.nv ? (uint32_t)st.Lb[v] : 1u;
-        wz += (uint32_t)__popcll(__ballot(l == 0u));
-        wn += (uint32_t)__popcll(__ballot(l == kNone));
-    }
-    if (lane == 0) { cz[wave] = wz; cn[wave] = wn; }
-    __syncthreads();
-    for (int q = 0; q < wave; ++q) { zeros += cz[q]; nones += cn[q]; }
+    const uint32_t own0 = first - g.node0 + lane * 64u;          // first node of the lane's word
+    EsLabels mine{0ull, 0ull};
+    if (lane < wpw) mine = es_load_labels(st, first / 64u + lane);
+    const u64 nodes = lane >= wpw || own0 >= g.nv ? 0ull : g.nv - own0 < 64u ? (1ull << (g.nv - own0)) - 1ull : ~0ull;
+    const u64 my_zeros = mine.has & ~mine.one, my_nones = nodes & ~mine.has;
+    uint32_t zeros = sums[0] + es_lane(es_block_exclusive((uint32_t)__popcll(my_zeros), cz), 0);          // before the wave's
+    uint32_t nones = sums[1] + es_lane(es_block_exclusive((uint32_t)__popcll(my_nones), cn), 0);
     const u64 below = (1ull << lane) - 1ull;
     for (int i = 0; i < wpw; ++i) {
         const uint32_t v = first + i * 64u + lane;
         const bool in = v - g.node0 < g.nv;
-        const uint32_t l = in ? (uint32_t)st.Lb[v] : 1u;
-        const u64 bz = __ballot(l == 0u), bn = __ballot(l == kNone);
+        const u64 bz = es_bcast(my_zeros, i), bn = es_bcast(my_nones, i);
+        const uint32_t l = ((bz >> lane) & 1ull) ? 0u : ((bn >> lane) & 1ull) ? kNone : 1u;
         const long long z = (long long)zeros + __popcll(bz & below), j = (long long)nones + __popcll(bn & below);
         zeros += __popcll(bz);
         nones += __popcll(bn);
@@ -985,9 +1022,8 @@ __device__ uint32_t es_block_scan(uint32_t* p, int64_t len, uint32_t* wsum /* kW
     for (int64_t base = 0; base < len; base += kBlock) {
         const int64_t i = base + threadIdx.x;
         const uint32_t x = i < len ? p[i] : 0u;
-        const uint32_t excl = es_block_exclusive(x, wsum);
-        uint32_t all = 0;
-        for (int q = 0; q < kWaves; ++q) all += wsum[q];
+        uint32_t all;
+        const uint32_t excl = es_block_exclusive(x, wsum, &all);
         if (i < len) p[i] = carry + excl;
         carry += all;
         __syncthreads();
@@ -1034,7 +1070,7 @@ __global__ __launch_bounds__(kSelBlock) void k_rb_split_scatter(const EsGroup* _
             n0 += k[u] == 0; n1 += k[u] == 1;
         }
     }
-    const uint32_t x0 = es_wave_exclusive(n0, lane), x1 = es_wave_exclusive(n1, lane);
+    const uint32_t x0 = es_wave_inclusive(n0) - n0, x1 = es_wave_inclusive(n1) - n1;
     if (lane == 63) { c0[wave] = x0 + n0; c1[wave] = x1 + n1; }
     __syncthreads();
     int64_t p0 = g.e_lo + bo0[g.tile0 + blockIdx.x] + x0;
@@ -1074,8 +1110,8 @@ inline int grid_for(int64_t items, int block, int64_t cap)
 //           18.5 or 19.5 instead of 17.9 at 14M.
 //   blocks  otherwise kBlock * wpw nodes each: one word per wave up to a million nodes (the chip wants some 1024
 //           blocks), more words beyond it, so that a block can add up all blocks' counts itself.
-//   awpw    the admission walks a word per lane, so it wants 64 of them per wave (16: 88.2 ms for a bisection of 14M
-//           nodes, 32: 83.0, 64: 82.2), 32 where 64 would leave CUs without a workgroup.
+//   awpw    the admission's workgroups each add up all blocks' counts: as many words per wave as leave 256 workgroups or
+//           fewer, while the groups' padding stays within their nodes.
 struct EsShape {
     int wpw = 1, awpw = 1, cb = 0;
     bool binned = false;
@@ -1102,16 +1138,19 @@ EsShape es_shape(int64_t n, int64_t groups, int64_t ends, int64_t chunks, bool b
         const int64_t own = s.padded(n), pad = (groups - 1) * s.an();
         return own + (pad < own ? pad : own);
     };
-    s.wpw = kBinWaveWords;
-    s.awpw = n >= (1ll << 23) ? 64 : 32;
+    auto waves = [&](int wpw) {
+        s.wpw = s.awpw = wpw;
+        while (s.awpw < kMaxAdmitWords && n > s.an() * 256 && 2 * s.an() * groups <= n) s.awpw *= 2;
+    };
+    waves(kBinWaveWords);
     if (bins && n >= kBinMinNodes && room() < (1ll << 30) && ends <= 4 * n && chunks <= kBinMaxChunks) {
         s.binned = true;
         s.cb = 15;
         while ((room() >> s.cb) >= kBins) ++s.cb;          // (at most 20)
     } else {
-        s.wpw = 1;
-        while (s.wpw < kMaxWaveWords && n > s.bn() * 1024) s.wpw *= 2;
-        s.awpw = s.wpw;
+        int wpw = 1;
+        while (wpw < kMaxWaveWords && n > (int64_t)kBlock * wpw * 1024) wpw *= 2;
+        waves(wpw);
     }
     s.nodes = room();
     if (s.binned) {
@@ -1141,16 +1180,16 @@ struct EsMemory {
             p = ws ? reinterpret_cast<T*>(ws + off) : nullptr;
             off += align256(count * sizeof(T));
         };
-        const size_t blocks = (size_t)(nodes / sh.bn()), ablocks = (size_t)(nodes / sh.an()), words = (size_t)(nodes / 64);
+        const size_t blocks = (size_t)(nodes / sh.bn()), words = (size_t)(nodes / 64);
         take(st.flags, 2);
         take(groups, (size_t)ngroups);
         take(blk_group, blocks);
         take(st.S, (size_t)ngroups * 4);
-        take(st.Lb, (size_t)nodes);
+        take(st.Lw, (size_t)(nodes / 32));
         if (est_out) st.est = (double2*)est_out;
         else take(st.est, (size_t)nodes);
-        take(st.mark, words); take(st.mv0, words); take(st.mv1, words); take(st.ov, words);
-        take(st.bs0, blocks); take(st.bs1, blocks); take(st.bso, ablocks); take(st.bd0, ablocks); take(st.bd1, ablocks);
+        take(st.mark, words); take(st.mv0, words); take(st.mv1, words); take(st.nw, words);
+        take(st.bs, blocks);
         if (sh.binned) {
             table_words = (size_t)chunks * kBinTableStride;
             take(table, table_words);
@@ -1179,6 +1218,17 @@ void es_fill(hipStream_t stream, void* p, size_t bytes, u64 value)
         hipLaunchKernelGGL(k_es_fill64, dim3(grid_for((int64_t)count, 256, 16384)), dim3(256), 0, stream, (u64*)p, count, value);
 }
 
+// k_es_count: few edges are spread over as many workgroups as they make, many are taken kCountUnroll per thread
+void es_count(hipStream_t stream, int64_t most, unsigned ng, const int32_t* src, const int32_t* dst, const EsRun& st, int64_t chunk, u64* hc)
+{
+    if (most * ng <= kCountSparse)
+        hipLaunchKernelGGL(k_es_count<1>, dim3((unsigned)grid_for(most, kCountBlock, 1 << 20), ng), dim3(kCountBlock), 0, stream, src, dst, st,
+                           chunk, hc);
+    else
+        hipLaunchKernelGGL(k_es_count<kCountUnroll>, dim3((unsigned)grid_for((most + kCountUnroll - 1) / kCountUnroll, kCountBlock, 1 << 20), ng),
+                           dim3(kCountBlock), 0, stream, src, dst, st, chunk, hc);
+}
+
 // One run: everything from the cleared state to the last chunk's spill is enqueued.  groups_host: its groups, in the
 // order of their nodes (also at mem.groups on the device, with mem.blk_group filled).  check(): called once the first chunk's seeds are
 // counted and flags[] is complete, before anything uses the labels; its answer other than GREM_OK ends the run.
@@ -1198,7 +1248,7 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
         if (c > chunks) chunks = c;
     }
     es_fill(stream, st.S, align256((size_t)ng * 32), 0ull);
-    es_fill(stream, st.Lb, (size_t)nodes, ~0ull);
+    es_fill(stream, st.Lw, (size_t)nodes / 4, 0ull);
     es_fill(stream, st.est, (size_t)est_nodes * 16, 0ull);
     es_fill(stream, st.mark, (size_t)nodes / 8, 0ull);
     std::vector<uint32_t> crowded;                             // per chunk: its crowded bins
@@ -1224,14 +1274,12 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
             es_fill(stream, mem.crowd.seen, ((size_t)sh.crowd_bins << sh.cb) / 8, 0ull);
             break;
         }
-    const size_t slab = sh.awpw > kApplyByNode ? (size_t)kBlock * sh.awpw : 0;
     const size_t bins_lds = (size_t)sh.bn() * 4 + (size_t)sh.bn() / 8;
     // (always what any run may need: the limit is the process's, and other threads' runs are of other sizes)
-    if ((slab && hipFuncSetAttribute((const void*)k_es_apply, hipFuncAttributeMaxDynamicSharedMemorySize, kBlock * kMaxWaveWords) != hipSuccess) ||
-        (sh.binned &&
-         (hipFuncSetAttribute((const void*)k_es_bin, hipFuncAttributeMaxDynamicSharedMemorySize, kBinTile * 8) != hipSuccess ||
-          hipFuncSetAttribute((const void*)k_es_crowd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bins_lds) != hipSuccess ||
-          hipFuncSetAttribute((const void*)k_es_score_bins, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bins_lds) != hipSuccess)))
+    if (sh.binned &&
+        (hipFuncSetAttribute((const void*)k_es_bin, hipFuncAttributeMaxDynamicSharedMemorySize, kBinTile * 8) != hipSuccess ||
+         hipFuncSetAttribute((const void*)k_es_crowd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bins_lds) != hipSuccess ||
+         hipFuncSetAttribute((const void*)k_es_score_bins, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bins_lds) != hipSuccess))
         return GREM_ERR_HIP;
     bool profile;
     { std::lock_guard<std::mutex> lock(es_prof.mu); profile = es_prof.on; }
@@ -1258,8 +1306,7 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
             hipLaunchKernelGGL(k_es_bin, dim3((unsigned)((most + kBinTile - 1) / kBinTile), ng), dim3(kBlock), kBinTile * 8, stream, src, dst,
                                st, i, sh.cb, mem.cursors, mem.pairs);
         else
-            hipLaunchKernelGGL(k_es_count, dim3((unsigned)grid_for((most + kCountUnroll - 1) / kCountUnroll, kCountBlock, 1 << 20), ng),
-                               dim3(kCountBlock), 0, stream, src, dst, st, i, mem.hc);
+            es_count(stream, most, ng, src, dst, st, i, mem.hc);
         if (!sh.binned) timed();
         const int first = i == 0 ? 1 : 0;
         if (sh.binned && crowded[(size_t)i])
@@ -1272,8 +1319,9 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
             hipLaunchKernelGGL(k_es_score, dim3(blocks), dim3(kBlock), 0, stream, st, par, first, fixed, mem.hc);
         if (sh.binned) timed();
         if (first) continue;
-        hipLaunchKernelGGL(k_es_apply, dim3(ablocks), dim3(kBlock), slab, stream, st, par);
-        hipLaunchKernelGGL(k_es_spill, dim3(ablocks), dim3(kBlock), 0, stream, st, par);
+        if (sh.awpw <= 64) hipLaunchKernelGGL(k_es_admit<1>, dim3(ablocks), dim3(kBlock), 0, stream, st, par);
+        else if (sh.awpw == 128) hipLaunchKernelGGL(k_es_admit<2>, dim3(ablocks), dim3(kBlock), 0, stream, st, par);
+        else hipLaunchKernelGGL(k_es_admit<4>, dim3(ablocks), dim3(kBlock), 0, stream, st, par);
         par ^= 1;
     }
     *par_out = par;
@@ -1320,7 +1368,7 @@ int es_bipartition(const int32_t* src, const int32_t* dst, int64_t m, int64_t n,
         return flags[0] ? GREM_ERR_ARG : flags[1] ? GREM_ERR_SEED : GREM_OK;
     }, &par);
     if (rc == GREM_OK) {
-        hipLaunchKernelGGL(k_es_expand, dim3(grid_for(n, 256, 16384)), dim3(256), 0, stream, n, (const uint8_t*)mem.st.Lb, parts_out,
+        hipLaunchKernelGGL(k_es_expand, dim3(grid_for(n, 256, 16384)), dim3(256), 0, stream, n, (const u64*)mem.st.Lw, parts_out,
                            (const u64*)(mem.st.S + 2 * par), sizes_out);
         if (hipGetLastError() != hipSuccess) rc = GREM_ERR_HIP;
     } else {
