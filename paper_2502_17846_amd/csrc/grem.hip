@@ -34,6 +34,10 @@ constexpr int kLdsHistBytes = 32 * 1024;   // LDS spent on one tile's histograms
 constexpr int kTileHistBytes = 16 * 1024;  // merged launches: the same (32 KB: 117 ms where 16 KB take 106 and 8 KB 107)
 constexpr int kTileGrid = 2048;            // ... and workgroups per chunk (1024: 2.18 ms on a million vertices, 2048: 1.91,
                                            // 4096: 2.02, 8192: 2.52)
+constexpr int kPackMinK = 32;              // merged launches: estimates are packed from this many partitions on (fewer are
+                                           // mostly not zero) and where they outgrow the Infinity Cache: whole and packed,
+constexpr size_t kPackMinBytes = 256u << 20;   // 120 MB 1.50 and 1.53 ms, 256 MB 1.70 and 1.71, 480 MB 2.31 and 2.01, 528 MB 3.45
+                                           // and 3.22, 1 GB 4.2 and 3.6, 6.4 GB 15.6 and 12.3, 17 GB 63.8 and 50.9
 constexpr int kLdsMaxK = 1024;             // above this the histograms live in E's rows
 constexpr int kLongRowDegree = 16384;      // plain score kernels: rows this long get a grid of their own ...
 constexpr uint32_t kLongRowPart = 16384;   // ... that many entries per workgroup and turn
@@ -1017,9 +1021,32 @@ struct PlainExtra {
     uint32_t *cnt = nullptr, *coarse = nullptr;          // two tables of mover counts each
     unsigned long long *rej = nullptr;
     uint32_t *nrows = nullptr, *nparts = nullptr, *off = nullptr, *cur = nullptr, *row = nullptr, *pref = nullptr, *ticket = nullptr;
+    unsigned long long *bits = nullptr;                  // packed estimates: which cells are stored
 };
 
-void state_plain(Carver &c, PlainExtra &x, int64_t n, int64_t cl, int32_t k, int64_t nchunks, bool external_E, bool merged) {
+// rows per workgroup of the tile kernels by the LDS that their histograms may take
+int plain_tile_rows(int32_t k, int lds_bytes) {
+    int tv = 256;
+    while (tv > 1 && (size_t)tv * k * 4 > (size_t)lds_bytes) tv >>= 1;
+    return tv;
+}
+
+// ... of the merged launches: the histograms in 16 KB of LDS, and small enough for 2048 workgroups
+int merged_tile_rows(int32_t k, int64_t cl) {
+    int tv = plain_tile_rows(k, kTileHistBytes);
+    while (tv > 8 && (cl + tv - 1) / tv < kTileGrid) tv >>= 1;
+    return tv;
+}
+
+bool pack_estimates(int64_t n, int32_t k) { return k >= kPackMinK && (size_t)n * (size_t)k * 4 > kPackMinBytes; }
+
+// words of 64 cells that the packed estimates of a chunk's tiles make
+size_t packed_words(int32_t k, int64_t cl) {
+    const int tv = merged_tile_rows(k, cl);
+    return (size_t)((cl + tv - 1) / tv) * (((size_t)tv * k + 63) / 64);
+}
+
+void state_plain(Carver &c, PlainExtra &x, int64_t n, int64_t cl, int32_t k, int64_t nchunks, bool external_E, bool merged, bool packed = false) {
     c.take(x.E, external_E ? 0 : (size_t)n * (size_t)k);
     if (!merged) {
         c.take(x.long_cnt, (size_t)nchunks);
@@ -1037,13 +1064,7 @@ void state_plain(Carver &c, PlainExtra &x, int64_t n, int64_t cl, int32_t k, int
     c.take(x.row, rows);
     c.take(x.pref, rows);
     c.take(x.ticket, rows);
-}
-
-// rows per workgroup of the tile kernels by the LDS that their histograms may take
-int plain_tile_rows(int32_t k, int lds_bytes) {
-    int tv = 256;
-    while (tv > 1 && (size_t)tv * k * 4 > (size_t)lds_bytes) tv >>= 1;
-    return tv;
+    c.take(x.bits, packed ? (size_t)nchunks * packed_words(k, cl) : 0);
 }
 
 // Alg. 1's loop in the merged launches.  degrees[i]: rows of at least long_row_degree * 2^i entries and fewer than
@@ -1058,12 +1079,13 @@ int run_plain_merged(const RowT *rowptr, const int32_t *colidx, int64_t n, int32
     const bool external_E = estimates_out != nullptr;
     const int64_t nchunks = (n + cl - 1) / cl;
     PlainExtra x;
-    if (!carve(mem, [&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E, true); })) return GREM_ERR_NOMEM;
+    const bool pack = pack_estimates(n, k) && !external_E && R > 0;
+    if (!(pack && carve(mem, [&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E, true, true); })) &&
+        !carve(mem, [&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E, true); }))
+        return GREM_ERR_NOMEM;
     uint32_t *E = external_E ? estimates_out : x.E;
     if (maxdeg * (unsigned long long)plain_tile_rows(k, kLdsHistBytes) >= (1ull << 31)) return GREM_ERR_RANGE;
-    // rows per workgroup: the histograms in 16 KB of LDS, and small enough for 2048 workgroups
-    int tv = plain_tile_rows(k, kTileHistBytes);
-    while (tv > 8 && (cl + tv - 1) / tv < kTileGrid) tv >>= 1;
+    const int tv = merged_tile_rows(k, cl);
     const size_t tile_lds = ((size_t)tv * k + tv + 1 + 2 * (size_t)k) * 4;
     const int tiles_full = (int)((cl + kAdmitTile - 1) / kAdmitTile);
     const size_t cells = (size_t)tiles_full * (size_t)k;
@@ -1148,10 +1170,14 @@ int run_plain_merged(const RowT *rowptr, const int32_t *colidx, int64_t n, int32
                 lr = LongParts{x.row + first, x.pref + first, parts <= kLongTicketParts ? x.ticket + first : (uint32_t *)nullptr,
                                nrows[c], parts, (uint32_t)degree, part};
             }
+            auto score = [&](auto kernel, unsigned long long *bits) {
+                hipLaunchKernelGGL(kernel, dim3(lr.parts + (unsigned)((len + tv - 1) / tv)), dim3(kScoreThreads), tile_lds, stream, rowptr,
+                                   colidx, (const LabelT *)st.Lc, (const long long *)now, other, E, st.prop, cnt, coarse, lo, hi, (int)k,
+                                   tv, pass, P, standing == kNoneLabelled ? lo : n, standing, store_e, lr, bits);
+            };
             L.run(GREM_KERNEL_SCORE, [&] {
-                hipLaunchKernelGGL((k_score_tile<RowT, LabelT>), dim3(lr.parts + (unsigned)((len + tv - 1) / tv)), dim3(kScoreThreads),
-                                   tile_lds, stream, rowptr, colidx, (const LabelT *)st.Lc, (const long long *)now, other, E, st.prop, cnt,
-                                   coarse, lo, hi, (int)k, tv, pass, P, standing == kNoneLabelled ? lo : n, standing, store_e, lr);
+                if (x.bits) score(k_score_tile<RowT, LabelT, true>, x.bits + (size_t)c * packed_words(k, cl));
+                else score(k_score_tile<RowT, LabelT, false>, nullptr);
             });
             if (lr.rows != 0 && !lr.ticket)
                 L.run(GREM_KERNEL_HUBS, [&] {
@@ -1268,7 +1294,8 @@ int run_plain(const RowT *rowptr, const int32_t *colidx, int64_t n, int32_t k, d
     return L.err;
 }
 
-size_t plain_bytes(int64_t n, int32_t k, int64_t cl, bool external_E) {
+// packed: with the bits of packed estimates, without which a run keeps them whole
+size_t plain_bytes(int64_t n, int32_t k, int64_t cl, bool external_E, bool packed = true) {
     const int64_t nchunks = (n + cl - 1) / cl;
     PlainExtra x;
     size_t a;
@@ -1282,7 +1309,7 @@ size_t plain_bytes(int64_t n, int32_t k, int64_t cl, bool external_E) {
     // (whichever of the two forms takes more)
     const size_t one = carve_size([&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E, false); });
     const size_t two = plain_merged(k, cl, GREM_HIST_AUTO)
-                           ? carve_size([&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E, true); }) : 0;
+                           ? carve_size([&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E, true, packed && pack_estimates(n, k)); }) : 0;
     return a + (one > two ? one : two);
 }
 
@@ -1315,7 +1342,7 @@ int run_partition(const RowT *rowptr, const int32_t *colidx, int64_t n, int32_t 
         mem.cap = g.ws_bytes;
         L.level = g.prof_level;
     }
-    if (mem.base && mem.cap < plain_bytes(n, k, cl, external_E)) return GREM_ERR_NOMEM;
+    if (mem.base && mem.cap < plain_bytes(n, k, cl, external_E, false)) return GREM_ERR_NOMEM;
     L.mark();
 
     CallState<LabelT> st;

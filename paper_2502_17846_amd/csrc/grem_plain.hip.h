@@ -189,17 +189,31 @@ __global__ __launch_bounds__(kScoreThreads) void k_long_pick(const uint32_t *__r
     propose_long(v, [&](int j) { return erow[j]; }, smem, Lc, prop, cnt, coarse, chunk_lo, k, pass, standing);
 }
 
+// lane i's word in every lane, 0 for i >= 64 (i uniform over the wave)
+__device__ __forceinline__ unsigned long long wave_word(unsigned long long x, int i) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, i & 63);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), i & 63);
+    return i < 64 ? (unsigned long long)hi << 32 | lo : 0ull;
+}
+
 // What bounds it: the look-up of every entry's label (a miss of 64 bytes once the labels outgrow the L2) and the
 // tile's estimates, read before the counting starts and written once; on small graphs latency, hence tiles small
 // enough for 2048 workgroups per chunk and g = 256 / tv lanes per vertex for the proposals.  The last pass keeps the
 // estimates to itself unless the caller asked for them (store_e).
 constexpr int kEstAhead = 8;             // estimates per thread requested ahead of the counting
-template <typename RowT, typename LabelT>
+
+// Packed estimates (PACKED; kept by the library, never the caller's): of a tile without long rows only the estimates that
+// are not zero are stored, and a bit per cell that says which.  A wave owns up to 16 words of 64 cells; its values stand one
+// after the other at the start of its cells' place in E.  A row has no more of them than entries: chunks of 262,144 rows of 47
+// entries at k = 256 moved 268 MB of estimates in and out each, and a step of a refinement pass took 270 us; now 196 us, of
+// which some 100 are instructions issued (a choice among the non-zero cells alone instead of all 256 gained nothing).
+
+template <typename RowT, typename LabelT, bool PACKED>
 __global__ __launch_bounds__(kScoreThreads) void k_score_tile(
     const RowT *__restrict__ rowptr, const int32_t *__restrict__ colidx, const LabelT *__restrict__ Lc,
     const long long *__restrict__ S, long long *__restrict__ Snext, uint32_t *__restrict__ E, LabelT *__restrict__ prop,
     uint32_t *__restrict__ cnt, uint32_t *__restrict__ coarse, int64_t chunk_lo, int64_t chunk_hi, int k, int tv, int pass,
-    long long P, int64_t gather_limit, int standing, int store_e, LongParts lr) {
+    long long P, int64_t gather_limit, int standing, int store_e, LongParts lr, unsigned long long *__restrict__ bits) {
     extern __shared__ uint32_t smem[];
     __shared__ int s_last;
     constexpr int U = 8;
@@ -265,7 +279,17 @@ __global__ __launch_bounds__(kScoreThreads) void k_score_tile(
     const int64_t e0 = (int64_t)rowptr[v0];
     const int total = nv * k;
     uint32_t *Etile = E + (size_t)v0 * (size_t)k;
-    const bool ahead = pass > 0 && total <= kEstAhead * kScoreThreads;
+    // PACKED: the wave's words of the tile, from word0 on (lane i keeps word i), and its cells
+    const int nwords = PACKED ? (tv * k + 63) >> 6 : 0, wwords = (nwords + kScoreThreads / 64 - 1) / (kScoreThreads / 64);
+    const int lane = lane_id(), word0 = __builtin_amdgcn_readfirstlane(tid >> 6) * wwords;
+    const bool keeper = lane < wwords && word0 + lane < nwords;
+    uint32_t *Ewave = Etile + (size_t)word0 * 64;
+    unsigned long long word = 0ull;
+    if (PACKED) {
+        bits += (size_t)tile * nwords + word0;
+        if (pass > 0 && keeper) word = bits[lane];
+    }
+    const bool ahead = !PACKED && pass > 0 && total <= kEstAhead * kScoreThreads;
     uint32_t est[kEstAhead];
     if (ahead) {
 #pragma unroll
@@ -275,7 +299,8 @@ __global__ __launch_bounds__(kScoreThreads) void k_score_tile(
         }
     }
     for (int i = tid; i <= tv; i += kScoreThreads) rowrel[i] = (uint32_t)((int64_t)rowptr[v0 + (i < nv ? i : nv)] - e0);
-    for (int i = tid; i < tv * k; i += kScoreThreads) hist[i] = 0;
+    if (!PACKED || pass == 0)
+        for (int i = tid; i < tv * k; i += kScoreThreads) hist[i] = 0;
     for (int j = tid; j < k; j += kScoreThreads) {
         const long long s = S[j];
         room[j] = (uint32_t)(P - s);
@@ -290,6 +315,31 @@ __global__ __launch_bounds__(kScoreThreads) void k_score_tile(
         any_long = __syncthreads_or(mine ? 1 : 0) != 0;
     }
     auto is_long = [&](int r) { return any_long && rowrel[r + 1] - rowrel[r] >= lr.degree; };
+    // PACKED: the counts are added to the stored estimates, in LDS, as they are found
+    const uint32_t one = PACKED ? 1u << sh : 1u;
+    if (PACKED && pass > 0) {
+        if (any_long) {
+            for (int i = tid; i < total; i += kScoreThreads) hist[i] = __builtin_nontemporal_load(Etile + i);
+        } else {
+            constexpr int kAtOnce = 8;
+            uint32_t at = 0;
+            for (int w0 = 0; w0 < wwords; w0 += kAtOnce) {
+                uint32_t before[kAtOnce];
+#pragma unroll
+                for (int u = 0; u < kAtOnce; ++u) {
+                    const unsigned long long set = wave_word(word, w0 + u);
+                    before[u] = (set >> lane) & 1ull ? __builtin_nontemporal_load(Ewave + at + __popcll(set & lanes_below(lane))) : 0u;
+                    at += (uint32_t)__popcll(set);
+                }
+#pragma unroll
+                for (int u = 0; u < kAtOnce; ++u) {
+                    const int i = (word0 + w0 + u) * 64 + lane;
+                    if (w0 + u < wwords && i < tv * k) hist[i] = before[u];
+                }
+            }
+        }
+        __syncthreads();
+    }
 
     const int32_t *cbase = colidx + e0;
     // (the next turn's column ids are on their way while this turn's labels are looked up: a skewed tile takes many)
@@ -312,7 +362,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_score_tile(
             for (int u = 0; u < U; ++u) {
                 if (lab[u] != 0xFFFFFFFFu && !(check && lab[u] == none)) {
                     const int r = owning_row(rowrel, base + u * kScoreThreads, tv);
-                    atomicAdd(&hist[r * k + (int)lab[u]], 1u);
+                    atomicAdd(&hist[r * k + (int)lab[u]], one);
                 }
             }
         }
@@ -334,7 +384,23 @@ __global__ __launch_bounds__(kScoreThreads) void k_score_tile(
         hist[i] = e;
         if (store_e && !(any_long && is_long(i / k))) __builtin_nontemporal_store(e, Etile + i);
     };
-    if (ahead) {
+    if (PACKED) {
+        if (store_e && any_long) {
+            for (int i = tid; i < total; i += kScoreThreads)
+                if (!is_long(i / k)) __builtin_nontemporal_store(hist[i], Etile + i);
+        } else if (store_e) {
+            uint32_t at = 0;
+            for (int w = 0; w < wwords; ++w) {
+                const int i = (word0 + w) * 64 + lane;
+                const uint32_t e = i < total ? hist[i] : 0u;
+                const unsigned long long set = __ballot(e != 0u);
+                if (lane == w) word = set;
+                if (e) __builtin_nontemporal_store(e, Ewave + at + __popcll(set & lanes_below(lane)));
+                at += (uint32_t)__popcll(set);
+            }
+            if (keeper) bits[lane] = word;
+        }
+    } else if (ahead) {
 #pragma unroll
         for (int u = 0; u < kEstAhead; ++u) {
             const int i = tid + u * kScoreThreads;
@@ -343,7 +409,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_score_tile(
     } else {
         for (int i = tid; i < total; i += kScoreThreads) blend(i, pass == 0 ? 0u : __builtin_nontemporal_load(Etile + i));
     }
-    __syncthreads();
+    if (!PACKED) __syncthreads();
 
     // proposals, g lanes per vertex
     const int g = tv >= kScoreThreads ? 1 : tv * 64 <= kScoreThreads ? 64 : kScoreThreads / tv;
