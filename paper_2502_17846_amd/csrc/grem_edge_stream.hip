@@ -608,12 +608,66 @@ __global__ __launch_bounds__(kBlock) void k_es_score(EsRun st, int par, int firs
     es_store_movers(st, movers, blockIdx.x);
 }
 
+// LDS of k_es_score_bins after its counts and their bits: per wave a list of what to score, per word of nodes two of movers
+constexpr int kQuadTurn = 16 * kTurn;              // groups of four nodes a wave scores at a time
+constexpr int kQuadRoom = 2 * kQuadTurn;           // ... and has room for: those left over, and those of kTurn more words
+inline size_t es_bins_lds(int64_t bn) { return (size_t)bn * 4 + (size_t)bn / 8 + (size_t)kWaves * kQuadRoom * 2 + (size_t)bn / 64 * 16; }
+
+// a wave's LDS writes are seen by its other lanes
+__device__ __forceinline__ void es_wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Alg. 1 for the nodes of kQuadTurn groups of four or fewer, a lane each and kTurn of them at once: blend the stored
+// estimate with the fresh counts when the node has a label, store the estimate, ask `assign` for a partition.  quads: the groups'
+// places in the block (node0: its first node); counts(rel, h0, h1): whether the node belongs to the chunk, and its counts;
+// those that want to move get their bits in mv0 and mv1 (LDS).  (The stored estimate is asked for whether or not the node has a
+// label: the load need not wait for the label's.)
+template <typename Counts>
+__device__ __forceinline__ void es_score_quads(const EsRun& st, uint32_t node0, const uint16_t* quads, uint32_t count, Counts&& counts,
+                                               int first, int fixed, long long P, long long S0, long long S1, uint32_t* mv0, uint32_t* mv1)
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t rel[kTurn], h0[kTurn], h1[kTurn];
+    u64 word[kTurn];
+    double2 est[kTurn];
+    bool on[kTurn];
+#pragma unroll
+    for (int u = 0; u < kTurn; ++u) {
+        const uint32_t at = (uint32_t)(u * 16 + (lane >> 2));
+        rel[u] = at < count ? quads[at] * 4u + (lane & 3) : 0u;
+        on[u] = at < count && counts(rel[u], h0[u], h1[u]);
+        if (on[u]) word[u] = st.Lw[(node0 + rel[u]) >> 5];
+        if (on[u] && !first && !fixed) est[u] = st.est[node0 + rel[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < kTurn; ++u) {
+        if (!on[u]) continue;
+        const uint32_t old = es_label(word[u], rel[u]);            // (a block starts at a whole word)
+        if (fixed && !first && old != kNone) continue;
+        double nbrs0 = (double)h0[u], nbrs1 = (double)h1[u];
+        if (!first && !fixed && old != kNone) {
+            nbrs0 = (est[u].x + nbrs0) * 0.5;
+            nbrs1 = (est[u].y + nbrs1) * 0.5;
+        }
+        st.est[node0 + rel[u]] = make_double2(nbrs0, nbrs1);
+        if (first) continue;
+        const int t = es_assign(nbrs0, nbrs1, S0 - (old == 0u), S1 - (old == 1u), P);
+        if ((uint32_t)t != old) atomicOr(&(t ? mv1 : mv0)[rel[u] >> 5], 1u << (rel[u] & 31u));
+    }
+}
+
 // cnt_nbrs, second half, from the binned pairs: a block counts the pairs of its bin that are its own in LDS (the
 // blocks of one bin all read it, on one XCD, whose L2 then holds it), then scores its nodes.  A bin of at most 65,535
 // pairs cannot overflow 16 bits: the two counts of a node share a word; a larger one is counted in two rounds
 // of half the nodes with 32 bits each.  `seen`: nodes whose other ends have no label.
-// What is left to bound it is the estimates' 32 bytes per touched node; 111M nodes, 32M edge ends: 1.01 ms with the
-// counts in memory, 0.74 here.
+// One node in eleven belongs to a chunk of one per cent: a wave lists the groups of four nodes with such a node among them and
+// scores those, a lane per node.  Word by word, most lanes idle, 300 of 587 us went to issuing instructions (111M nodes, 32M
+// edge ends); with lists of the nodes themselves 581 us, of the groups 556 (14M nodes, 4M ends: 69, 53.7 and 52.5).  Of the
+// 556 the estimates take 270, 1 GB in pieces of 64 bytes, and the pairs, which four blocks read, 210.
 __global__ __launch_bounds__(kBlock) void k_es_score_bins(EsRun st, int par, int first, int fixed, int64_t chunk, int cb,
                                                           uint32_t nblocks, const uint32_t* __restrict__ table,
                                                           const uint32_t* __restrict__ pairs, EsCrowd crowd)
@@ -626,14 +680,14 @@ __global__ __launch_bounds__(kBlock) void k_es_score_bins(EsRun st, int par, int
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t bn = (uint32_t)(kBlock * st.wpw);
     uint32_t* seen = cnt + bn;
-    const uint32_t gi = st.blk_group[block];
-    const long long P = st.groups[gi].P;
-    const long long S0 = (long long)st.S[2 * (par * st.ngroups + gi)], S1 = (long long)st.S[2 * (par * st.ngroups + gi) + 1];
     const uint32_t bin = (block * bn) >> cb, in_bin = (block * bn) & ((1u << cb) - 1u);
     const uint32_t* row = table + (size_t)chunk * kBinTableStride + bin;
     const uint32_t p0 = row[0], p1 = row[1];
     const uint32_t place = crowd.place[(size_t)chunk * kBins + bin];
     if (place) {                                   // counted by k_es_crowd
+        const uint32_t gi = st.blk_group[block];
+        const long long P = st.groups[gi].P;
+        const long long S0 = (long long)st.S[2 * (par * st.ngroups + gi)], S1 = (long long)st.S[2 * (par * st.ngroups + gi) + 1];
         u64* hc = crowd.hc + (((size_t)place - 1) << cb) + in_bin;
         uint32_t* was_seen = crowd.seen + ((((size_t)place - 1) << cb) + in_bin) / 32;
         const uint32_t word0 = block * (bn / 64) + wave * st.wpw;
@@ -669,52 +723,86 @@ __global__ __launch_bounds__(kBlock) void k_es_score_bins(EsRun st, int par, int
     const int rounds = narrow ? 1 : 2;
     const uint32_t sub = bn / rounds;              // nodes per round
     const int nw = st.wpw / rounds;                // words per wave and round
+    uint16_t* quads = reinterpret_cast<uint16_t*>(seen + bn / 32) + wave * kQuadRoom;
+    uint32_t* mv0 = seen + bn / 32 + kWaves * kQuadRoom / 2;
+    uint32_t* mv1 = mv0 + bn / 32;
     uint32_t movers[4] = {0u, 0u, 0u, 0u};
     for (int round = 0; round < rounds; ++round) {
-        const uint32_t word0 = block * (bn / 64) + round * (sub / 64) + wave * nw;
-        const EsLabels labels = lane < nw ? es_load_labels(st, word0 + lane) : EsLabels{0ull, 0ull};
-        __syncthreads();
-        for (uint32_t i = tid; i < bn; i += kBlock) cnt[i] = 0u;
-        for (uint32_t i = tid; i < bn / 32; i += kBlock) seen[i] = 0u;
-        __syncthreads();
-        const uint32_t low = in_bin + round * sub;
-        constexpr int U = 8;
-        for (uint32_t i = p0 + tid; i < p1; i += kBlock * U) {
-            uint32_t x[U];
+        const uint32_t low = in_bin + round * sub, node0 = block * bn + round * sub, word0 = node0 / 64 + wave * nw;
+        // the pairs four at a time from the last whole four before them on (the list's end is padded), the next turn's on their way
+        constexpr int U = 3;
+        const uint4* fours = reinterpret_cast<const uint4*>(pairs);
+        const uint32_t q1 = (p1 + 3u) >> 2;
+        uint32_t q = (p0 >> 2) + tid;
+        uint4 x[U];
+        auto request = [&] {
 #pragma unroll
-            for (int u = 0; u < U; ++u) x[u] = p1 - i > (uint32_t)(u * kBlock) ? pairs[i + u * kBlock] : 0xFFFFFFFFu;
+            for (int u = 0; u < U; ++u)
+                if (q + u * kBlock < q1) x[u] = fours[q + u * kBlock];
+        };
+        request();
+        __syncthreads();
+        for (uint32_t i = tid; i < bn / 4; i += kBlock) reinterpret_cast<uint4*>(cnt)[i] = make_uint4(0u, 0u, 0u, 0u);
+        for (uint32_t i = tid; i < bn / 32; i += kBlock) seen[i] = mv0[i] = mv1[i] = 0u;
+        __syncthreads();
+        for (; q < q1;) {
+            uint4 y[U];
+            const uint32_t at = q;
+#pragma unroll
+            for (int u = 0; u < U; ++u) y[u] = x[u];
+            q += U * kBlock;
+            request();
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const uint32_t rel = (x[u] & ((1u << cb) - 1u)) - low, code = x[u] >> cb;
-                if (x[u] == 0xFFFFFFFFu || rel >= sub) continue;
-                if (code >= 2u) atomicOr(&seen[rel >> 5], 1u << (rel & 31u));
-                else if (narrow) atomicAdd(&cnt[rel], code ? 65536u : 1u);
-                else atomicAdd(&cnt[2u * rel + code], 1u);
+                if (at + u * kBlock >= q1) continue;
+                const uint32_t pair[4] = {y[u].x, y[u].y, y[u].z, y[u].w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t rel = (pair[i] & ((1u << cb) - 1u)) - low, code = pair[i] >> cb;
+                    if (4u * (at + u * kBlock) + i - p0 >= p1 - p0 || rel >= sub) continue;
+                    if (code >= 2u) atomicOr(&seen[rel >> 5], 1u << (rel & 31u));
+                    else if (narrow) atomicAdd(&cnt[rel], code ? 65536u : 1u);
+                    else atomicAdd(&cnt[2u * rel + code], 1u);
+                }
             }
-            if (p1 - i <= (uint32_t)(kBlock * U)) break;
         }
         __syncthreads();
-        u64 out0 = 0ull, out1 = 0ull;
-        for (int i0 = 0; i0 < nw; i0 += kTurn) {
-            bool on[kTurn];
-            uint32_t h0[kTurn], h1[kTurn];
-#pragma unroll
-            for (int u = 0; u < kTurn; ++u) {
-                const uint32_t rel = (uint32_t)(wave * nw + i0 + u) * 64u + lane;
-                const bool in = i0 + u < nw;
-                if (narrow) {
-                    const uint32_t c = in ? cnt[rel] : 0u;
-                    h0[u] = c & 0xFFFFu;
-                    h1[u] = c >> 16;
-                } else {
-                    h0[u] = in ? cnt[2u * rel] : 0u;
-                    h1[u] = in ? cnt[2u * rel + 1u] : 0u;
-                }
-                on[u] = (h0[u] | h1[u]) != 0u || (in && ((seen[rel >> 5] >> (rel & 31u)) & 1u));
+        auto counts = [&](uint32_t rel, uint32_t& h0, uint32_t& h1) {
+            if (narrow) {
+                h0 = cnt[rel] & 0xFFFFu;
+                h1 = cnt[rel] >> 16;
+            } else {
+                h0 = cnt[2u * rel];
+                h1 = cnt[2u * rel + 1u];
             }
-            es_score_words(st, word0, i0, labels, on, h0, h1, first, fixed, P, S0, S1, out0, out1);
+            return (h0 | h1) != 0u || ((seen[rel >> 5] >> (rel & 31u)) & 1u);
+        };
+        const uint32_t gi = st.blk_group[block];
+        const long long P = st.groups[gi].P, S0 = (long long)st.S[2 * (par * st.ngroups + gi)], S1 = (long long)st.S[2 * (par * st.ngroups + gi) + 1];
+        // a lane looks at four nodes of a word, 16 lanes at a word
+        uint32_t listed = 0;
+        for (int i0 = 0; i0 < nw; i0 += kTurn) {                   // (nw is a multiple of kTurn)
+            const uint32_t quad = (uint32_t)(wave * nw + i0) * 16u + lane;
+            const uint4* c4 = reinterpret_cast<const uint4*>(cnt);
+            uint4 c = narrow ? c4[quad] : c4[2u * quad];
+            uint32_t any = c.x | c.y | c.z | c.w | ((seen[quad >> 3] >> ((quad & 7u) * 4u)) & 15u);
+            if (!narrow) { c = c4[2u * quad + 1u]; any |= c.x | c.y | c.z | c.w; }
+            const u64 on = __ballot(any != 0u);
+            if (any) quads[listed + __builtin_amdgcn_mbcnt_hi((uint32_t)(on >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)on, 0u))] = (uint16_t)quad;
+            listed += (uint32_t)__popcll(on);
+            es_wave_sync();
+            const bool last = i0 + kTurn >= nw;
+            while (listed >= (uint32_t)kQuadTurn || (last && listed > 0)) {           // the list's end first: what is left stays in place
+                const uint32_t take = listed < (uint32_t)kQuadTurn ? listed : (uint32_t)kQuadTurn;
+                listed -= take;
+                es_score_quads(st, node0, quads + listed, take, counts, first, fixed, P, S0, S1, mv0, mv1);
+            }
+            es_wave_sync();
         }
-        if (lane < nw) es_store_words(st, word0 + lane, out0, out1, labels, movers);
+        const EsLabels labels = lane < nw ? es_load_labels(st, word0 + lane) : EsLabels{0ull, 0ull};
+        if (lane < nw)
+            es_store_words(st, word0 + lane, reinterpret_cast<const u64*>(mv0)[wave * nw + lane], reinterpret_cast<const u64*>(mv1)[wave * nw + lane],
+                           labels, movers);
     }
     es_store_movers(st, movers, block);
 }
@@ -1274,11 +1362,11 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
             es_fill(stream, mem.crowd.seen, ((size_t)sh.crowd_bins << sh.cb) / 8, 0ull);
             break;
         }
-    const size_t bins_lds = (size_t)sh.bn() * 4 + (size_t)sh.bn() / 8;
+    const size_t crowd_lds = (size_t)sh.bn() * 4 + (size_t)sh.bn() / 8, bins_lds = es_bins_lds(sh.bn());
     // (always what any run may need: the limit is the process's, and other threads' runs are of other sizes)
     if (sh.binned &&
         (hipFuncSetAttribute((const void*)k_es_bin, hipFuncAttributeMaxDynamicSharedMemorySize, kBinTile * 8) != hipSuccess ||
-         hipFuncSetAttribute((const void*)k_es_crowd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bins_lds) != hipSuccess ||
+         hipFuncSetAttribute((const void*)k_es_crowd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)crowd_lds) != hipSuccess ||
          hipFuncSetAttribute((const void*)k_es_score_bins, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bins_lds) != hipSuccess))
         return GREM_ERR_HIP;
     bool profile;
@@ -1310,7 +1398,7 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
         if (!sh.binned) timed();
         const int first = i == 0 ? 1 : 0;
         if (sh.binned && crowded[(size_t)i])
-            hipLaunchKernelGGL(k_es_crowd, dim3(kCrowdGrid), dim3(kBlock), bins_lds, stream, i, sh.cb, (uint32_t)sh.bn(), blocks,
+            hipLaunchKernelGGL(k_es_crowd, dim3(kCrowdGrid), dim3(kBlock), crowd_lds, stream, i, sh.cb, (uint32_t)sh.bn(), blocks,
                                (const uint32_t*)mem.table, (const uint32_t*)mem.pairs, mem.crowd);
         if (sh.binned)
             hipLaunchKernelGGL(k_es_score_bins, dim3((blocks + 7) / 8 * 8), dim3(kBlock), bins_lds, stream, st, par, first, fixed, i, sh.cb,
