@@ -1005,11 +1005,12 @@ __global__ __launch_bounds__(kBlock) void k_rb_count(EsRun st)
 // in the currently smaller half (0 on a tie): the first |difference| of them go to the smaller half, the rest
 // alternate 0,1,... .  So the node of half 0 with z labelled zeros and j unlabelled nodes before it is number
 // z + (zeros among the first j placements) of its half, and nothing but the two counts per block is needed.
-// packed[v] = the node's number inside its half with the half in bit 31; the halves' node lists (ids and next
-// level's seed bits) are written, half 0 first.  At the last level the labels 2 * group + half go out instead.  gof ==
-// nullptr: node i has id i.  nodes0[group]: nodes of half 0.
+// halves[]: per 32 nodes of the state the nodes of half 1 (low half) and how many of the group's nodes before them are of half
+// 0 (high half), from which a node's number inside its half follows: a quarter of a byte per node, which the L2s hold, is what
+// the edges' ends are looked up in.  The halves' node lists (ids and next level's seed bits) are written, half 0 first.  At the
+// last level the labels 2 * group + half go out instead.  gof == nullptr: node i has id i.  nodes0[group]: nodes of half 0.
 __global__ __launch_bounds__(kBlock) void k_rb_children(EsRun st, int par, const int32_t* __restrict__ gof,
-                                                        const int32_t* __restrict__ next_bits, uint32_t* packed,
+                                                        const int32_t* __restrict__ next_bits, u64* halves,
                                                         int32_t* gof_next, int32_t* seed_next, int32_t* labels_out,
                                                         long long* nodes0)
 {
@@ -1044,32 +1045,50 @@ __global__ __launch_bounds__(kBlock) void k_rb_children(EsRun st, int par, const
     uint32_t zeros = sums[0] + es_lane(es_block_exclusive((uint32_t)__popcll(my_zeros), cz), 0);          // before the wave's
     uint32_t nones = sums[1] + es_lane(es_block_exclusive((uint32_t)__popcll(my_nones), cn), 0);
     const u64 below = (1ull << lane) - 1ull;
+    u64 ones = 0ull;                                  // lane i: the nodes of half 1 of the wave's word i, and the group's nodes
+    uint32_t before = 0;                              // of half 0 before it
     for (int i = 0; i < wpw; ++i) {
         const uint32_t v = first + i * 64u + lane;
         const bool in = v - g.node0 < g.nv;
         const u64 bz = es_bcast(my_zeros, i), bn = es_bcast(my_nones, i);
         const uint32_t l = ((bz >> lane) & 1ull) ? 0u : ((bn >> lane) & 1ull) ? kNone : 1u;
         const long long z = (long long)zeros + __popcll(bz & below), j = (long long)nones + __popcll(bn & below);
+        const uint32_t half = l != kNone ? l : j < gap ? (lead0 ? 0u : 1u) : (uint32_t)((j - gap) & 1);
+        const u64 word = __ballot(in && half == 1u);
+        if (lane == i) { ones = word; before = zeros + (uint32_t)placed0((long long)nones); }
         zeros += __popcll(bz);
         nones += __popcll(bn);
         if (!in) continue;
-        const uint32_t half = l != kNone ? l : j < gap ? (lead0 ? 0u : 1u) : (uint32_t)((j - gap) & 1);
         const int64_t own = (int64_t)(v - g.node0);
         const int32_t id = gof ? gof[g.v_lo + own] : (int32_t)own;
         if (labels_out) { labels_out[id] = 2 * (int32_t)g.id + (int32_t)half; continue; }
         const long long r0 = z + placed0(j);          // nodes of half 0 before this one
         const long long num = half == 0u ? r0 : own - r0;
-        packed[g.v_lo + own] = (uint32_t)num | (half << 31);
         const int64_t at = g.v_lo + (half == 0u ? num : count0 + num);
         gof_next[at] = id;
         seed_next[at] = next_bits[id];
     }
+    // (of a word that ends inside, only the nodes that there are get looked up)
+    if (!labels_out && lane < wpw) {
+        const uint32_t next = before + 32u - (uint32_t)__popc((uint32_t)ones);
+        reinterpret_cast<ulonglong2*>(halves)[first / 64u + lane] =
+            make_ulonglong2((ones & 0xFFFFFFFFull) | (u64)before << 32, ones >> 32 | (u64)next << 32);
+    }
+}
+
+// half of the node in bit 31, its number inside the half below it
+__device__ __forceinline__ uint32_t rb_number(u64 word, uint32_t v)
+{
+    const uint32_t ones = (uint32_t)word, bit = 1u << (v & 31u);
+    const uint32_t zeros = (uint32_t)(word >> 32) + (uint32_t)__popc(~ones & (bit - 1u));
+    return ones & bit ? (v - zeros) | 0x80000000u : zeros;
 }
 
 // An edge of a group goes to the half both its ends are in (key 0 / 1) or is dropped (key 2); its
-// ends are rewritten in the halves' node numbers (tmp_s, tmp_d) for the scatter.
+// ends are rewritten in the halves' node numbers (tmp_s, tmp_d) for the scatter.  The random look-ups bound it: three levels of
+// 200M edges and 14M nodes took 15.5 ms from a table of 4 bytes per node, 3.4 from the 3.5 MB of `halves`.
 __global__ __launch_bounds__(kSelBlock) void k_rb_split_count(const EsGroup* __restrict__ groups, const int32_t* __restrict__ src,
-                                                              const int32_t* __restrict__ dst, const uint32_t* __restrict__ packed,
+                                                              const int32_t* __restrict__ dst, const u64* __restrict__ halves,
                                                               uint8_t* __restrict__ key, int32_t* __restrict__ tmp_s,
                                                               int32_t* __restrict__ tmp_d, uint32_t* bc0, uint32_t* bc1)
 {
@@ -1077,21 +1096,29 @@ __global__ __launch_bounds__(kSelBlock) void k_rb_split_count(const EsGroup* __r
     const EsGroup g = groups[blockIdx.y];
     if ((int64_t)blockIdx.x * kSelTile >= g.m) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t* __restrict__ own = packed + g.v_lo;
+    const u64* __restrict__ own = halves + (g.node0 >> 5);           // (a group starts at a whole block)
     const int64_t end = g.e_lo + g.m;
-    const int64_t e0 = g.e_lo + (int64_t)blockIdx.x * kSelTile + (int64_t)threadIdx.x * kSelPer;
-    uint32_t n0 = 0, n1 = 0;
+    const int64_t e0 = g.e_lo + (int64_t)blockIdx.x * kSelTile + threadIdx.x;
+    uint32_t n0 = 0, n1 = 0, s[kSelPer], d[kSelPer];
+    u64 a[kSelPer], b[kSelPer];
 #pragma unroll
     for (int u = 0; u < kSelPer; ++u) {
-        const int64_t e = e0 + u;
-        if (e < end) {
-            const uint32_t a = own[src[e]], b = own[dst[e]];
-            const int k = (a >> 31) == (b >> 31) ? (int)(a >> 31) : 2;
-            key[e] = (uint8_t)k;
-            tmp_s[e] = (int32_t)(a & 0x7FFFFFFFu);
-            tmp_d[e] = (int32_t)(b & 0x7FFFFFFFu);
-            n0 += k == 0; n1 += k == 1;
-        }
+        const int64_t e = e0 + u * kSelBlock;
+        s[u] = e < end ? (uint32_t)__builtin_nontemporal_load(src + e) : 0u;
+        d[u] = e < end ? (uint32_t)__builtin_nontemporal_load(dst + e) : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < kSelPer; ++u) { a[u] = own[s[u] >> 5]; b[u] = own[d[u] >> 5]; }
+#pragma unroll
+    for (int u = 0; u < kSelPer; ++u) {
+        const int64_t e = e0 + u * kSelBlock;
+        if (e >= end) continue;
+        const uint32_t x = rb_number(a[u], s[u]), y = rb_number(b[u], d[u]);
+        const int k = (x >> 31) == (y >> 31) ? (int)(x >> 31) : 2;
+        __builtin_nontemporal_store((uint8_t)k, key + e);
+        __builtin_nontemporal_store((int32_t)(x & 0x7FFFFFFFu), tmp_s + e);
+        __builtin_nontemporal_store((int32_t)(y & 0x7FFFFFFFu), tmp_d + e);
+        n0 += k == 0; n1 += k == 1;
     }
     n0 = es_wave_sum(n0); n1 = es_wave_sum(n1);
     if (lane == 0) { c0[wave] = n0; c1[wave] = n1; }
@@ -1487,14 +1514,14 @@ int es_bisection(const int32_t* src, const int32_t* dst, int64_t m, int64_t n, i
     const size_t o_totals = carve((size_t)most_groups * 24);     // per group: edges kept per half, nodes in half 0
     size_t o_gof[2], o_seed[2];                        // two generations of the groups' node lists
     for (int i = 0; i < 2; ++i) { o_gof[i] = carve((size_t)n * 4); o_seed[i] = carve((size_t)n * 4); }
-    const size_t o_packed = carve((size_t)n * 4);
     const size_t o_bc0 = carve((size_t)sel_blocks * 4), o_bc1 = carve((size_t)sel_blocks * 4);
     const size_t o_tmps = carve((size_t)m * 4), o_tmpd = carve((size_t)m * 4), o_key = carve((size_t)m);
     size_t o_lev[4];                                   // two generations of the grouped edge list
     for (int i = 0; i < 4; ++i) o_lev[i] = carve((size_t)m * 4);
-    const size_t o_run = off;                          // the state of a run is the last piece
+    size_t o_halves = off, o_run = off;                // sized by the run's nodes; its state is the last piece
     for (const bool bins : {true, false}) {
         sh = es_shape(n, most_groups < kMaxBatch ? most_groups : kMaxBatch, ends, c_max, bins);
+        o_run = o_halves + align256((size_t)sh.nodes / 4);
         mem.layout(nullptr, sh, kMaxBatch, ends, c_max, nullptr);
         if (hipMallocAsync((void**)&ws, o_run + mem.bytes, stream) == hipSuccess) break;
         (void)hipGetLastError();
@@ -1505,7 +1532,7 @@ int es_bisection(const int32_t* src, const int32_t* dst, int64_t m, int64_t n, i
     auto fail = [&](int code) { (void)hipGetLastError(); (void)hipStreamSynchronize(stream); (void)hipFreeAsync(ws, stream); return code; };
     long long* totals = (long long*)(ws + o_totals);
     long long* nodes0 = totals + 2 * most_groups;
-    uint32_t* packed = (uint32_t*)(ws + o_packed);
+    u64* halves = (u64*)(ws + o_halves);
     uint32_t *bc0 = (uint32_t*)(ws + o_bc0), *bc1 = (uint32_t*)(ws + o_bc1);
     int32_t *tmp_s = (int32_t*)(ws + o_tmps), *tmp_d = (int32_t*)(ws + o_tmpd);
     uint8_t* key = ws + o_key;
@@ -1566,7 +1593,7 @@ int es_bisection(const int32_t* src, const int32_t* dst, int64_t m, int64_t n, i
             }, &par);
             if (rc != GREM_OK) return fail(rc);
             hipLaunchKernelGGL(k_rb_count, dim3(blocks), dim3(kBlock), 0, stream, mem.st);
-            hipLaunchKernelGGL(k_rb_children, dim3(blocks), dim3(kBlock), 0, stream, mem.st, par, cur_gof, next_bits, packed, gof_next,
+            hipLaunchKernelGGL(k_rb_children, dim3(blocks), dim3(kBlock), 0, stream, mem.st, par, cur_gof, next_bits, halves, gof_next,
                                seed_next, last ? labels_out : (int32_t*)nullptr, nodes0);
             // the groups' edges that stay inside a half, in the halves' numbers, for the next level
             int64_t most = 0;
@@ -1574,7 +1601,7 @@ int es_bisection(const int32_t* src, const int32_t* dst, int64_t m, int64_t n, i
             if (!last && most > 0) {
                 const dim3 grid((unsigned)((most + kSelTile - 1) / kSelTile), ng);
                 hipLaunchKernelGGL(k_rb_split_count, grid, dim3(kSelBlock), 0, stream, (const EsGroup*)mem.groups, cur_s, cur_d,
-                                   (const uint32_t*)packed, key, tmp_s, tmp_d, bc0, bc1);
+                                   (const u64*)halves, key, tmp_s, tmp_d, bc0, bc1);
                 hipLaunchKernelGGL(k_rb_split_scan, dim3(ng), dim3(kBlock), 0, stream, (const EsGroup*)mem.groups, bc0, bc1, totals);
                 hipLaunchKernelGGL(k_rb_split_scatter, grid, dim3(kSelBlock), 0, stream, (const EsGroup*)mem.groups, (const int32_t*)tmp_s,
                                    (const int32_t*)tmp_d, (const uint8_t*)key, (const uint32_t*)bc0, (const uint32_t*)bc1, out_s, out_d,
