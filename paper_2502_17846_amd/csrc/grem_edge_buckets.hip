@@ -15,7 +15,7 @@
 //   k_eb_scatter  the tile again, 256 edges at a time in stream order: lanes with equal keys are matched
 //                 inside a wave (one ballot per key bit), the waves take their ranges from the LDS
 //                 cursors one after the other, every edge is written to cursor + rank
-//   k_eb_scatter_lds  (tiles of 4,096 edges, up to 1,024 buckets) the tile is sorted in LDS first and then
+//   k_eb_scatter_lds  (tiles of 4,096 or 8,192 edges, up to 1,024 buckets) the tile is sorted in LDS first and then
 //                 written out run by run
 #include <hip/hip_runtime.h>
 
@@ -31,7 +31,8 @@ constexpr int kEbBlock = 256;
 constexpr int kEbWaves = kEbBlock / 64;
 constexpr int kEbMaxK = 128;                       // k*k*4 bytes of LDS: 64 KB at k = 128
 constexpr int64_t kEbMaxCells = (int64_t)1 << 27;  // tiles * k*k
-constexpr int64_t kEbMinTile = 4096;
+constexpr int64_t kEbWideMinM = 1 << 24;           // from here on tiles of 8192 edges, below of 4096 (4,096 and 8,192: 4M edges 241
+                                                   // and 261 us, 20M 470 and 460, 200M of 14M nodes, k = 16, 4.6 and 4.2 ms)
 constexpr uint32_t kBadLabel = 0xFFu;
 constexpr int64_t kEbBinMinN = 1ll << 23, kEbBinMinM = 1 << 22, kEbBinMinNM = 200'000'000'000'000;
 
@@ -548,63 +549,59 @@ __global__ __launch_bounds__(kEbBlock) void k_eb_scatter(const int32_t* __restri
     }
 }
 
-// The same placement for tiles of kEbMinTile edges and at most kEbLdsBuckets buckets, with the tile sorted
-// in LDS first so that the output is written in whole runs: each of the eight waves owns an eighth of the
-// tile (consecutive stream positions), counts it, the counts become per-wave cursors into the tile's sorted
+// The same placement for tiles of 8 edges per thread and at most kEbLdsBuckets buckets, with the tile sorted
+// in LDS first so that the output is written in whole runs: each wave owns 512 edges of the
+// tile (consecutive stream positions), counts them, the counts become per-wave cursors into the tile's sorted
 // order (bucket, then wave, then stream position = stable), every wave places its edges into LDS without
 // waiting for the others, and the sorted tile is written out with consecutive lanes on consecutive
-// addresses of a bucket's run.  Bound by latency under its barriers: with four waves to a workgroup (twelve per CU) and
-// one thread adding up the 256 partial counts 1.6e9 edges took 18.1 ms; with eight and a wave's prefix sums 9.3 to 12 in some
-// processes and 14.3 to 18 in others (the same within one; the distance between the output arrays does not matter).
+// addresses of a bucket's run: the sources first, then, through the same LDS, the targets.  Bound by the runs, pieces of the
+// output of 128 bytes at 256 buckets: with both ends in LDS, tiles of 4,096 edges and runs of 64 bytes, 1.6e9 edges took 9.3 to
+// 12 ms in some processes and 14.3 to 18 in others (the same within one); tiles of 8,192 and two workgroups of sixteen
+// waves per CU take 10.6 to 11.0, tiles of 4,096 in this form 12.7 to 17.
 constexpr int kEbLdsBuckets = 1024;
-constexpr int kEbScatterThreads = 512;
-constexpr int kEbScatterWaves = kEbScatterThreads / 64;
-constexpr int kEbSeg = (int)(kEbMinTile / kEbScatterWaves);
-constexpr int kEbSegTurns = kEbSeg / 64;
-inline size_t eb_scatter_lds_bytes(int32_t k2) { return (size_t)kEbMinTile * 10 + (size_t)k2 * (4 + 2 + 2 * kEbScatterWaves) + 16; }
-
-__global__ __launch_bounds__(kEbScatterThreads) void k_eb_scatter_lds(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                                                      int64_t m, const uint16_t* __restrict__ key16, int32_t k2,
-                                                                      int32_t key_bits, const uint32_t* __restrict__ H,
-                                                                      int32_t* __restrict__ out_src, int32_t* __restrict__ out_dst)
+constexpr int kEbTurns = 8;                             // edges per thread
+template <int THREADS> constexpr int kEbScatterTile = THREADS * kEbTurns;
+template <int THREADS> constexpr size_t eb_scatter_lds_bytes(int32_t k2)
 {
+    return (size_t)kEbScatterTile<THREADS> * 6 + (size_t)k2 * (4 + 2 * (THREADS / 64)) + 16;
+}
+
+template <int THREADS>
+__global__ __launch_bounds__(THREADS, 8) void k_eb_scatter_lds(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                                                               int64_t m, const uint16_t* __restrict__ key16, int32_t k2,
+                                                               int32_t key_bits, const uint32_t* __restrict__ H,
+                                                               int32_t* __restrict__ out_src, int32_t* __restrict__ out_dst)
+{
+    constexpr int kTile = kEbScatterTile<THREADS>, kWaves = THREADS / 64, kSeg = 64 * kEbTurns;
     extern __shared__ uint32_t lds[];
-    int32_t* ssrc = (int32_t*)lds;                          // kEbMinTile
-    int32_t* sdst = ssrc + kEbMinTile;                      // kEbMinTile
-    uint32_t* gstart = (uint32_t*)(sdst + kEbMinTile);      // k2: output position of the tile's first edge of a bucket
-    uint16_t* lstart = (uint16_t*)(gstart + k2);            // k2: the same inside the sorted tile
-    uint16_t* curw = lstart + k2;                           // kEbScatterWaves * k2: counts, then cursors, per wave
-    uint16_t* skey = curw + kEbScatterWaves * k2;           // kEbMinTile
-    __shared__ uint32_t wsum[kEbScatterWaves];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t lo = (int64_t)blockIdx.x * kEbMinTile, hi = lo + kEbMinTile < m ? lo + kEbMinTile : m;
+    int32_t* ends = (int32_t*)lds;                          // kTile
+    uint32_t* delta = (uint32_t*)(ends + kTile);            // k2: output position of a bucket's edge less that in the sorted tile
+    uint16_t* curw = (uint16_t*)(delta + k2);               // kWaves * k2: counts, then cursors, per wave
+    uint16_t* skey = curw + kWaves * k2;                    // kTile
+    __shared__ uint32_t wsum[kWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t lo = (int64_t)blockIdx.x * kTile, hi = lo + kTile < m ? lo + kTile : m;
     const int count = (int)(hi - lo);
     const uint32_t* row = H + (size_t)blockIdx.x * (size_t)k2;
-    // the wave's edges, kEbSegTurns per lane, requested at once: the keys are needed twice, the ids at the end
-    const int seg0 = wave * kEbSeg, seg1 = seg0 + kEbSeg < count ? seg0 + kEbSeg : count;
-    uint32_t key[kEbSegTurns];
-    int32_t s[kEbSegTurns], d[kEbSegTurns];
+    // the wave's edges, kEbTurns per lane: the keys first, the sources while the counts are added up, the targets while the
+    // sources are written (all of them held at once spilled)
+    const int seg0 = wave * kSeg, seg1 = seg0 + kSeg < count ? seg0 + kSeg : count;
+    uint32_t key[kEbTurns];
 #pragma unroll
-    for (int u = 0; u < kEbSegTurns; ++u) {
+    for (int u = 0; u < kEbTurns; ++u) {
         const int p = seg0 + u * 64 + lane;
         key[u] = p < seg1 ? (uint32_t)key16[lo + p] : 0u;
     }
-#pragma unroll
-    for (int u = 0; u < kEbSegTurns; ++u) {
-        const int p = seg0 + u * 64 + lane;
-        s[u] = p < seg1 ? __builtin_nontemporal_load(src + lo + p) : 0;
-        d[u] = p < seg1 ? __builtin_nontemporal_load(dst + lo + p) : 0;
-    }
-    for (int b = threadIdx.x; b < k2; b += kEbScatterThreads) gstart[b] = row[b];
-    for (int b = threadIdx.x; b < kEbScatterWaves * k2; b += kEbScatterThreads) curw[b] = 0;
+    for (int b = tid; b < k2; b += THREADS) delta[b] = row[b];
+    for (int b = tid; b < kWaves * k2; b += THREADS) curw[b] = 0;
     __syncthreads();
-    // counts of the wave's eighth: the first lane of those with equal keys adds them up (a wave's own row of curw: no
+    // counts of the wave's edges: the first lane of those with equal keys adds them up (a wave's own row of curw: no
     // atomics; the ranks inside the 64 are kept for the placement)
     uint16_t* mine = curw + wave * k2;
     const u64 below = (1ull << lane) - 1ull;
-    uint32_t rank[kEbSegTurns];                             // rank | number of equal keys << 8 | first such lane << 16
+    uint32_t rank[kEbTurns];                                // rank | number of equal keys << 8 | first such lane << 16
 #pragma unroll
-    for (int u = 0; u < kEbSegTurns; ++u) {
+    for (int u = 0; u < kEbTurns; ++u) {
         const bool valid = seg0 + u * 64 + lane < seg1;
         u64 same = __ballot(valid);
         for (int bit = 0; bit < key_bits; ++bit) {
@@ -616,14 +613,20 @@ __global__ __launch_bounds__(kEbScatterThreads) void k_eb_scatter_lds(const int3
         rank[u] = r | (n << 8) | ((uint32_t)(valid ? __builtin_ctzll(same) : lane) << 16);
         if (valid && r == 0u) mine[key[u]] = (uint16_t)(mine[key[u]] + n);
     }
+    int32_t s[kEbTurns];
+#pragma unroll
+    for (int u = 0; u < kEbTurns; ++u) {
+        const int p = seg0 + u * 64 + lane;
+        s[u] = p < seg1 ? __builtin_nontemporal_load(src + lo + p) : 0;
+    }
     __syncthreads();
-    // exclusive sums over (bucket, wave): a thread owns up to kEbLdsBuckets / kEbScatterThreads consecutive buckets
-    const int per = (k2 + kEbScatterThreads - 1) / kEbScatterThreads;
-    const int b0 = threadIdx.x * per, b1 = b0 + per < k2 ? b0 + per : k2;
+    // exclusive sums over (bucket, wave): a thread owns up to kEbLdsBuckets / THREADS consecutive buckets
+    const int per = (k2 + THREADS - 1) / THREADS;
+    const int b0 = tid * per, b1 = b0 + per < k2 ? b0 + per : k2;
     uint32_t own = 0;
     for (int b = b0; b < b1; ++b)
 #pragma unroll
-        for (int w = 0; w < kEbScatterWaves; ++w) own += curw[w * k2 + b];
+        for (int w = 0; w < kWaves; ++w) own += curw[w * k2 + b];
     uint32_t incl = own;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -635,27 +638,44 @@ __global__ __launch_bounds__(kEbScatterThreads) void k_eb_scatter_lds(const int3
     uint32_t run = incl - own;
     for (int w = 0; w < wave; ++w) run += wsum[w];
     for (int b = b0; b < b1; ++b) {
-        lstart[b] = (uint16_t)run;
+        delta[b] -= run;
 #pragma unroll
-        for (int w = 0; w < kEbScatterWaves; ++w) { const uint32_t c = curw[w * k2 + b]; curw[w * k2 + b] = (uint16_t)run; run += c; }
+        for (int w = 0; w < kWaves; ++w) { const uint32_t c = curw[w * k2 + b]; curw[w * k2 + b] = (uint16_t)run; run += c; }
     }
     __syncthreads();
-    // every wave places its eighth, 64 edges at a time in stream order
+    // every wave places its edges, 64 at a time in stream order
 #pragma unroll
-    for (int u = 0; u < kEbSegTurns; ++u) {
+    for (int u = 0; u < kEbTurns; ++u) {
         const bool valid = seg0 + u * 64 + lane < seg1;
         const uint32_t r = rank[u] & 0xFFu, n = (rank[u] >> 8) & 0xFFu;
         uint32_t first = 0u;
         if (valid && r == 0u) { first = mine[key[u]]; mine[key[u]] = (uint16_t)(first + n); }
-        const uint32_t pos = __shfl(first, (int)(rank[u] >> 16)) + r;
-        if (valid) { ssrc[pos] = s[u]; sdst[pos] = d[u]; skey[pos] = (uint16_t)key[u]; }
+        rank[u] = __shfl(first, (int)(rank[u] >> 16)) + r;  // from here on the place
+        if (valid) { ends[rank[u]] = s[u]; skey[rank[u]] = (uint16_t)key[u]; }
+    }
+    int32_t d[kEbTurns];
+#pragma unroll
+    for (int u = 0; u < kEbTurns; ++u) {
+        const int p = seg0 + u * 64 + lane;
+        d[u] = p < seg1 ? __builtin_nontemporal_load(dst + lo + p) : 0;
     }
     __syncthreads();
-    for (int p = threadIdx.x; p < count; p += kEbScatterThreads) {
-        const uint32_t kk = skey[p];
-        const uint32_t at = gstart[kk] + ((uint32_t)p - lstart[kk]);
-        out_src[at] = ssrc[p];
-        out_dst[at] = sdst[p];
+    uint32_t at[kEbTurns];
+#pragma unroll
+    for (int u = 0; u < kEbTurns; ++u) {
+        const int p = u * THREADS + tid;
+        at[u] = p < count ? delta[skey[p]] + (uint32_t)p : 0u;
+        if (p < count) out_src[at[u]] = ends[p];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kEbTurns; ++u)
+        if (seg0 + u * 64 + lane < seg1) ends[rank[u]] = d[u];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kEbTurns; ++u) {
+        const int p = u * THREADS + tid;
+        if (p < count) out_dst[at[u]] = ends[p];
     }
 }
 
@@ -673,7 +693,8 @@ extern "C" int grem_edge_buckets(const int32_t* src, const int32_t* dst, int64_t
     hipStream_t stream = (hipStream_t)stream_;
     const int32_t k2 = k * k;
     int64_t tile = (m * k2 + kEbMaxCells - 1) / kEbMaxCells;
-    if (tile < kEbMinTile) tile = kEbMinTile;
+    const int64_t least = m >= kEbWideMinM ? kEbScatterTile<1024> : kEbScatterTile<512>;
+    if (tile < least) tile = least;
     tile = (tile + kEbBlock - 1) / kEbBlock * kEbBlock;
     const int64_t tiles = (m + tile - 1) / tile;
     int32_t S = 65536 / k2;
@@ -772,13 +793,15 @@ extern "C" int grem_edge_buckets(const int32_t* src, const int32_t* dst, int64_t
     hipLaunchKernelGGL(k_eb_colsum, dim3(grid(cells, 1 << 20)), dim3(256), 0, stream, H, tiles, k2, S, seg_len, partial);
     hipLaunchKernelGGL(k_eb_bases, dim3(1), dim3(1024), 0, stream, partial, cells, k2, S, m, bucket_offsets);
     hipLaunchKernelGGL(k_eb_colscan, dim3(grid(cells, 1 << 20)), dim3(256), 0, stream, H, tiles, k2, S, seg_len, partial);
-    if (tile == kEbMinTile && k2 <= kEbLdsBuckets) {
-        const size_t lds2 = eb_scatter_lds_bytes(k2);
-        if (hipFuncSetAttribute((const void*)k_eb_scatter_lds, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)eb_scatter_lds_bytes(kEbLdsBuckets)) != hipSuccess)
+    if (tile == least && k2 <= kEbLdsBuckets) {
+        auto scatter = [&](auto kernel, int threads, size_t lds2, size_t most_lds) {
+            if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most_lds) != hipSuccess) return false;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(threads), lds2, stream, src, dst, m, key16, k2, key_bits, H, out_src, out_dst);
+            return true;
+        };
+        if (!(least == kEbScatterTile<1024> ? scatter(k_eb_scatter_lds<1024>, 1024, eb_scatter_lds_bytes<1024>(k2), eb_scatter_lds_bytes<1024>(kEbLdsBuckets))
+                                            : scatter(k_eb_scatter_lds<512>, 512, eb_scatter_lds_bytes<512>(k2), eb_scatter_lds_bytes<512>(kEbLdsBuckets))))
             return fail(GREM_ERR_HIP);
-        hipLaunchKernelGGL(k_eb_scatter_lds, dim3((unsigned)tiles), dim3(kEbScatterThreads), lds2, stream, src, dst, m, key16, k2, key_bits, H,
-                           out_src, out_dst);
     } else {
         hipLaunchKernelGGL(k_eb_scatter, dim3((unsigned)tiles), dim3(kEbBlock), lds, stream, src, dst, m, tile, key16, k2, key_bits, H,
                            out_src, out_dst);

@@ -1,0 +1,29 @@
+"""Edge buckets of lists long enough for tiles of 8,192 edges (2^24 and more) against the oracle: last tiles of one edge and of
+all but one, one bucket, runs of a few edges and of whole tiles, more buckets than the sorting in LDS takes."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2502_17846_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("m,k,skew", [((1 << 24) - 1, 16, False), (1 << 24, 16, False), ((1 << 24) + 1, 17, False),
+                                      ((1 << 24) + 8191, 32, False), ((1 << 24) + 777, 33, False), ((1 << 24) + 64, 1, False),
+                                      ((1 << 24) + 513, 12, True)])
+def test_wide_tiles(m, k, skew):
+    n = 50_021
+    rng = np.random.default_rng(m % 1000 + k)
+    src = rng.integers(0, n, m).astype(np.int32)
+    dst = rng.integers(0, n, m).astype(np.int32)
+    labels = rng.integers(0, k, n).astype(np.int32)
+    if skew:                                       # most of the edges in one bucket, sorted by source
+        labels[rng.random(n) < 0.95] = k - 1
+        src.sort()
+    got = B.grem_edge_buckets(*(torch.as_tensor(x).to(DEV) for x in (src, dst)), n, torch.as_tensor(labels).to(DEV), k)
+    want = oracle.edge_buckets(src, dst, labels, k)
+    for g, w in zip(got, want):
+        assert np.array_equal(g.cpu().numpy(), w)
