@@ -31,8 +31,8 @@ constexpr int kEbBlock = 256;
 constexpr int kEbWaves = kEbBlock / 64;
 constexpr int kEbMaxK = 128;                       // k*k*4 bytes of LDS: 64 KB at k = 128
 constexpr int64_t kEbMaxCells = (int64_t)1 << 27;  // tiles * k*k
-constexpr int64_t kEbWideMinM = 1 << 24;           // from here on tiles of 8192 edges, below of 4096 (4,096 and 8,192: 4M edges 241
-                                                   // and 261 us, 20M 470 and 460, 200M of 14M nodes, k = 16, 4.6 and 4.2 ms)
+constexpr int64_t kEbWideMinM = 1 << 25;           // from here on tiles of 8192 edges, below of 4096 (4,096 and 8,192: 18M edges, k = 8,
+                                                   // 388 and 421 us, 40M 1.14 and 1.13 ms, 200M, k = 16, 4.9 and 4.2 ms)
 constexpr uint32_t kBadLabel = 0xFFu;
 constexpr int64_t kEbBinMinN = 1ll << 23, kEbBinMinM = 1 << 22, kEbBinMinNM = 200'000'000'000'000;
 
@@ -554,28 +554,32 @@ __global__ __launch_bounds__(kEbBlock) void k_eb_scatter(const int32_t* __restri
 // tile (consecutive stream positions), counts them, the counts become per-wave cursors into the tile's sorted
 // order (bucket, then wave, then stream position = stable), every wave places its edges into LDS without
 // waiting for the others, and the sorted tile is written out with consecutive lanes on consecutive
-// addresses of a bucket's run: the sources first, then, through the same LDS, the targets.  Bound by the runs, pieces of the
-// output of 128 bytes at 256 buckets: with both ends in LDS, tiles of 4,096 edges and runs of 64 bytes, 1.6e9 edges took 9.3 to
-// 12 ms in some processes and 14.3 to 18 in others (the same within one); tiles of 8,192 and two workgroups of sixteen
-// waves per CU take 10.6 to 11.0, tiles of 4,096 in this form 12.7 to 17.
+// addresses of a bucket's run; with 1024 threads the sources first, then, through the same LDS, the targets, so that two workgroups
+// of sixteen waves stand on a CU.  Bound by the runs, pieces of the output of 128 bytes at 256 buckets: with tiles of 4,096
+// edges and runs of 64 bytes 1.6e9 edges took 9.3 to 12 ms in some processes and 14.3 to 18 in others (the same within one),
+// with 8,192 10.6 to 11.0 (13.8 in a form of 36 registers, with the same loads and stores, that spills nothing).  Shorter lists,
+// which the caches hold, want both ends at once (a list whose whole call takes 416 us took 438 with turns for them).
 constexpr int kEbLdsBuckets = 1024;
 constexpr int kEbTurns = 8;                             // edges per thread
 template <int THREADS> constexpr int kEbScatterTile = THREADS * kEbTurns;
+template <int THREADS> constexpr bool kEbTurnsForEnds = THREADS == 1024;
 template <int THREADS> constexpr size_t eb_scatter_lds_bytes(int32_t k2)
 {
-    return (size_t)kEbScatterTile<THREADS> * 6 + (size_t)k2 * (4 + 2 * (THREADS / 64)) + 16;
+    return (size_t)kEbScatterTile<THREADS> * (kEbTurnsForEnds<THREADS> ? 6 : 10) + (size_t)k2 * (4 + 2 * (THREADS / 64)) + 16;
 }
 
 template <int THREADS>
-__global__ __launch_bounds__(THREADS, 8) void k_eb_scatter_lds(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+__global__ __launch_bounds__(THREADS, kEbTurnsForEnds<THREADS> ? 8 : 1) void k_eb_scatter_lds(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                                                                int64_t m, const uint16_t* __restrict__ key16, int32_t k2,
                                                                int32_t key_bits, const uint32_t* __restrict__ H,
                                                                int32_t* __restrict__ out_src, int32_t* __restrict__ out_dst)
 {
     constexpr int kTile = kEbScatterTile<THREADS>, kWaves = THREADS / 64, kSeg = 64 * kEbTurns;
+    constexpr bool kTurns = kEbTurnsForEnds<THREADS>;
     extern __shared__ uint32_t lds[];
     int32_t* ends = (int32_t*)lds;                          // kTile
-    uint32_t* delta = (uint32_t*)(ends + kTile);            // k2: output position of a bucket's edge less that in the sorted tile
+    int32_t* others = kTurns ? ends : ends + kTile;         // kTile
+    uint32_t* delta = (uint32_t*)(others + kTile);          // k2: output position of a bucket's edge less that in the sorted tile
     uint16_t* curw = (uint16_t*)(delta + k2);               // kWaves * k2: counts, then cursors, per wave
     uint16_t* skey = curw + kWaves * k2;                    // kTile
     __shared__ uint32_t wsum[kWaves];
@@ -583,15 +587,24 @@ __global__ __launch_bounds__(THREADS, 8) void k_eb_scatter_lds(const int32_t* __
     const int64_t lo = (int64_t)blockIdx.x * kTile, hi = lo + kTile < m ? lo + kTile : m;
     const int count = (int)(hi - lo);
     const uint32_t* row = H + (size_t)blockIdx.x * (size_t)k2;
-    // the wave's edges, kEbTurns per lane: the keys first, the sources while the counts are added up, the targets while the
-    // sources are written (all of them held at once spilled)
+    // the wave's edges, kEbTurns per lane: the keys first; where the ends take turns, the sources while the counts are added up
+    // and the targets while the sources are written (all of them held at once spilled)
     const int seg0 = wave * kSeg, seg1 = seg0 + kSeg < count ? seg0 + kSeg : count;
     uint32_t key[kEbTurns];
+    int32_t s[kEbTurns], d[kEbTurns];
+    auto load = [&](const int32_t* __restrict__ from, int32_t (&to)[kEbTurns]) {
+#pragma unroll
+        for (int u = 0; u < kEbTurns; ++u) {
+            const int p = seg0 + u * 64 + lane;
+            to[u] = p < seg1 ? __builtin_nontemporal_load(from + lo + p) : 0;
+        }
+    };
 #pragma unroll
     for (int u = 0; u < kEbTurns; ++u) {
         const int p = seg0 + u * 64 + lane;
         key[u] = p < seg1 ? (uint32_t)key16[lo + p] : 0u;
     }
+    if (!kTurns) { load(src, s); load(dst, d); }
     for (int b = tid; b < k2; b += THREADS) delta[b] = row[b];
     for (int b = tid; b < kWaves * k2; b += THREADS) curw[b] = 0;
     __syncthreads();
@@ -613,12 +626,7 @@ __global__ __launch_bounds__(THREADS, 8) void k_eb_scatter_lds(const int32_t* __
         rank[u] = r | (n << 8) | ((uint32_t)(valid ? __builtin_ctzll(same) : lane) << 16);
         if (valid && r == 0u) mine[key[u]] = (uint16_t)(mine[key[u]] + n);
     }
-    int32_t s[kEbTurns];
-#pragma unroll
-    for (int u = 0; u < kEbTurns; ++u) {
-        const int p = seg0 + u * 64 + lane;
-        s[u] = p < seg1 ? __builtin_nontemporal_load(src + lo + p) : 0;
-    }
+    if (kTurns) load(src, s);
     __syncthreads();
     // exclusive sums over (bucket, wave): a thread owns up to kEbLdsBuckets / THREADS consecutive buckets
     const int per = (k2 + THREADS - 1) / THREADS;
@@ -652,13 +660,9 @@ __global__ __launch_bounds__(THREADS, 8) void k_eb_scatter_lds(const int32_t* __
         if (valid && r == 0u) { first = mine[key[u]]; mine[key[u]] = (uint16_t)(first + n); }
         rank[u] = __shfl(first, (int)(rank[u] >> 16)) + r;  // from here on the place
         if (valid) { ends[rank[u]] = s[u]; skey[rank[u]] = (uint16_t)key[u]; }
+        if (valid && !kTurns) others[rank[u]] = d[u];
     }
-    int32_t d[kEbTurns];
-#pragma unroll
-    for (int u = 0; u < kEbTurns; ++u) {
-        const int p = seg0 + u * 64 + lane;
-        d[u] = p < seg1 ? __builtin_nontemporal_load(dst + lo + p) : 0;
-    }
+    if (kTurns) load(dst, d);
     __syncthreads();
     uint32_t at[kEbTurns];
 #pragma unroll
@@ -666,7 +670,9 @@ __global__ __launch_bounds__(THREADS, 8) void k_eb_scatter_lds(const int32_t* __
         const int p = u * THREADS + tid;
         at[u] = p < count ? delta[skey[p]] + (uint32_t)p : 0u;
         if (p < count) out_src[at[u]] = ends[p];
+        if (p < count && !kTurns) out_dst[at[u]] = others[p];
     }
+    if (!kTurns) return;
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < kEbTurns; ++u)

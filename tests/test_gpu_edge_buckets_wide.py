@@ -1,4 +1,4 @@
-"""Edge buckets of lists long enough for tiles of 8,192 edges (2^24 and more) against the oracle: last tiles of one edge and of
+"""Edge buckets of lists long enough for tiles of 8,192 edges (2^25 and more) against the oracle: last tiles of one edge and of
 all but one, one bucket, runs of a few edges and of whole tiles, more buckets than the sorting in LDS takes."""
 import numpy as np
 import pytest
@@ -11,9 +11,9 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("m,k,skew", [((1 << 24) - 1, 16, False), (1 << 24, 16, False), ((1 << 24) + 1, 17, False),
-                                      ((1 << 24) + 8191, 32, False), ((1 << 24) + 777, 33, False), ((1 << 24) + 64, 1, False),
-                                      ((1 << 24) + 513, 12, True)])
+@pytest.mark.parametrize("m,k,skew", [((1 << 25) - 1, 16, False), (1 << 25, 16, False), ((1 << 25) + 1, 17, False),
+                                      ((1 << 25) + 8191, 32, False), ((1 << 25) + 777, 33, False), ((1 << 25) + 64, 1, False),
+                                      ((1 << 25) + 513, 12, True)])
 def test_wide_tiles(m, k, skew):
     n = 50_021
     rng = np.random.default_rng(m % 1000 + k)
