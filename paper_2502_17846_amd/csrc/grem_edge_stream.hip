@@ -271,8 +271,8 @@ __global__ __launch_bounds__(256) void k_es_seed_sizes(EsRun st)
 // chunk is known by a non-zero count or its bit: one atomic per edge end either way.
 // Random look-ups and atomics, 39 G/s of them together once labels and hc outgrow the L2 (then the ends are binned).
 template <int U>
-__global__ __launch_bounds__(kCountBlock) void k_es_count(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                                          EsRun st, int64_t chunk, u64* hc)
+__device__ __forceinline__ void es_count_edges(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, const EsRun& st,
+                                               int64_t chunk, u64* hc)
 {
     const EsGroup g = st.groups[blockIdx.y];
     int64_t lo, hi;
@@ -311,6 +311,18 @@ __global__ __launch_bounds__(kCountBlock) void k_es_count(const int32_t* __restr
             }
         }
     }
+}
+
+// an edge per thread and turn where there are few, kCountUnroll where there are many
+__global__ __launch_bounds__(kCountBlock) void k_es_count(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                                                          EsRun st, int64_t chunk, u64* hc)
+{
+    es_count_edges<1>(src, dst, st, chunk, hc);
+}
+__global__ __launch_bounds__(kCountBlock) void k_es_count_many(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                                                               EsRun st, int64_t chunk, u64* hc)
+{
+    es_count_edges<kCountUnroll>(src, dst, st, chunk, hc);
 }
 
 // ---- the chunk's edge ends binned by ranges of nodes -------------------------------------------------------
@@ -667,7 +679,7 @@ __device__ __forceinline__ void es_score_quads(const EsRun& st, uint32_t node0, 
 // One node in eleven belongs to a chunk of one per cent: a wave lists the groups of four nodes with such a node among them and
 // scores those, a lane per node.  Word by word, most lanes idle, 300 of 587 us went to issuing instructions (111M nodes, 32M
 // edge ends); with lists of the nodes themselves 581 us, of the groups 556 (14M nodes, 4M ends: 69, 53.7 and 52.5).  Of the
-// 556 the estimates take 270, 1 GB in pieces of 64 bytes, and the pairs, which four blocks read, 210.
+// 556 the estimates take 270, lines of 128 bytes with one node of the chunk in most, and the pairs, which four blocks read, 210.
 __global__ __launch_bounds__(kBlock) void k_es_score_bins(EsRun st, int par, int first, int fixed, int64_t chunk, int cb,
                                                           uint32_t nblocks, const uint32_t* __restrict__ table,
                                                           const uint32_t* __restrict__ pairs, EsCrowd crowd)
@@ -1337,10 +1349,10 @@ void es_fill(hipStream_t stream, void* p, size_t bytes, u64 value)
 void es_count(hipStream_t stream, int64_t most, unsigned ng, const int32_t* src, const int32_t* dst, const EsRun& st, int64_t chunk, u64* hc)
 {
     if (most * ng <= kCountSparse)
-        hipLaunchKernelGGL(k_es_count<1>, dim3((unsigned)grid_for(most, kCountBlock, 1 << 20), ng), dim3(kCountBlock), 0, stream, src, dst, st,
+        hipLaunchKernelGGL(k_es_count, dim3((unsigned)grid_for(most, kCountBlock, 1 << 20), ng), dim3(kCountBlock), 0, stream, src, dst, st,
                            chunk, hc);
     else
-        hipLaunchKernelGGL(k_es_count<kCountUnroll>, dim3((unsigned)grid_for((most + kCountUnroll - 1) / kCountUnroll, kCountBlock, 1 << 20), ng),
+        hipLaunchKernelGGL(k_es_count_many, dim3((unsigned)grid_for((most + kCountUnroll - 1) / kCountUnroll, kCountBlock, 1 << 20), ng),
                            dim3(kCountBlock), 0, stream, src, dst, st, chunk, hc);
 }
 
