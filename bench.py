@@ -28,11 +28,11 @@ HBM_PEAK_GBPS = 8000.0
 # at that time, and `traffic` is reported as null when the sources have changed since.
 PMC = {
     "workload": "chunglu-111M",
-    "sources_sha256": "aa90ac2aa8f797fca04d5631d4a8087e2a24760424c364e60633321fa74a9fc0",
+    "sources_sha256": "02d0b74690999b8c96ff3e89fa031a829744141f0269d45a1f91e637d9f6c5bc",
     "fetch_factor": 2.0,        # 2 GiB read  -> FETCH_SIZE 1,048,591 KiB
     "write_factor": 1.0,        # 2 GiB written -> WRITE_SIZE 2,097,152 KiB
-    "fetch_kib": {"k_tp_score": 1.42641e+07, "k_tp_lookup": 1.36608e+07},
-    "write_kib": {"k_tp_score": 7.32474e+06, "k_tp_lookup": 5.58395e+06},
+    "fetch_kib": {"k_tp_score": 1.42622e+07, "k_tp_lookup": 1.36601e+07},
+    "write_kib": {"k_tp_score": 7.32475e+06, "k_tp_lookup": 5.5879e+06},
     "launches": {"k_tp_score": 318, "k_tp_lookup": 317},
 }
 
@@ -40,9 +40,9 @@ PMC = {
 # The same for the edge-chunk path's two dominant kernels (one launch each per chunk) on its 111M-node workload.
 PMC_EDGE = {
     "workload": "edges-chunglu-111M-c1pct",
-    "sources_sha256": "3e9a2711e5648212a33a10248b756ab32a9165d0c0301be1bebe4041a5e3447b",
-    "fetch_kib": {"k_es_bin": 1.92977e+08, "k_es_score_bins": 6.91028e+07},
-    "write_kib": {"k_es_bin": 1.69295e+07, "k_es_score_bins": 4.75563e+07},
+    "sources_sha256": "0cb16dd125dc6f98c4bb34fd1d46aa9b5c14a0ae0622bf1f239a7dc692010b78",
+    "fetch_kib": {"k_es_bin": 1.71828e+08, "k_es_score_bins": 6.93709e+07},
+    "write_kib": {"k_es_bin": 1.5865e+07, "k_es_score_bins": 4.90064e+07},
     "launches": 100,
 }
 
