@@ -28,7 +28,7 @@ HBM_PEAK_GBPS = 8000.0
 # at that time, and `traffic` is reported as null when the sources have changed since.
 PMC = {
     "workload": "chunglu-111M",
-    "sources_sha256": "02d0b74690999b8c96ff3e89fa031a829744141f0269d45a1f91e637d9f6c5bc",
+    "sources_sha256": "159cbd1f5bb023d1c52ed59c66123f55dd3101613726e7c5d39452314c426dd4",
     "fetch_factor": 2.0,        # 2 GiB read  -> FETCH_SIZE 1,048,591 KiB
     "write_factor": 1.0,        # 2 GiB written -> WRITE_SIZE 2,097,152 KiB
     "fetch_kib": {"k_tp_score": 1.42622e+07, "k_tp_lookup": 1.36601e+07},

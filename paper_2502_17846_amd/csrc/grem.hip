@@ -34,10 +34,12 @@ constexpr int kLdsHistBytes = 32 * 1024;   // LDS spent on one tile's histograms
 constexpr int kTileHistBytes = 16 * 1024;  // merged launches: the same (32 KB: 117 ms where 16 KB take 106 and 8 KB 107)
 constexpr int kTileGrid = 2048;            // ... and workgroups per chunk (1024: 2.18 ms on a million vertices, 2048: 1.91,
                                            // 4096: 2.02, 8192: 2.52)
-constexpr int kPackMinK = 32;              // merged launches: estimates are packed from this many partitions on (fewer are
-                                           // mostly not zero) and where they outgrow the Infinity Cache: whole and packed,
-constexpr size_t kPackMinBytes = 256u << 20;   // 120 MB 1.50 and 1.53 ms, 256 MB 1.70 and 1.71, 480 MB 2.31 and 2.01, 528 MB 3.45
-                                           // and 3.22, 1 GB 4.2 and 3.6, 6.4 GB 15.6 and 12.3, 17 GB 63.8 and 50.9
+// Merged launches: estimates are packed where they outgrow the Infinity Cache, from 32 partitions on (fewer are mostly not
+// zero; below 128 of them half of a row may be, and the estimates must outgrow it twice).  Whole and packed: k = 40, 480 MB 4.51 and
+// 4.53 ms; 48, 768 MB 3.84 and 3.42; 64, 256 MB 1.70 and 1.71, 1 GB 4.2 and 3.6; 100, 120 MB 1.50 and 1.53; 256, 17 GB 63.8
+// and 50.9; 400, 480 MB 2.31 and 2.01, 6.4 GB 15.6 and 12.3.
+constexpr int kPackMinK = 32, kPackManyK = 128;
+constexpr size_t kPackMinBytes = 256u << 20;
 constexpr int kLdsMaxK = 1024;             // above this the histograms live in E's rows
 constexpr int kLongRowDegree = 16384;      // plain score kernels: rows this long get a grid of their own ...
 constexpr uint32_t kLongRowPart = 16384;   // ... that many entries per workgroup and turn
@@ -1038,7 +1040,9 @@ int merged_tile_rows(int32_t k, int64_t cl) {
     return tv;
 }
 
-bool pack_estimates(int64_t n, int32_t k) { return k >= kPackMinK && (size_t)n * (size_t)k * 4 > kPackMinBytes; }
+bool pack_estimates(int64_t n, int32_t k) {
+    return k >= kPackMinK && (size_t)n * (size_t)k * 4 > (k >= kPackManyK ? kPackMinBytes : 2 * kPackMinBytes);
+}
 
 // words of 64 cells that the packed estimates of a chunk's tiles make
 size_t packed_words(int32_t k, int64_t cl) {
