@@ -31,8 +31,18 @@ constexpr int kEbBlock = 256;
 constexpr int kEbWaves = kEbBlock / 64;
 constexpr int kEbMaxK = 128;                       // k*k*4 bytes of LDS: 64 KB at k = 128
 constexpr int64_t kEbMaxCells = (int64_t)1 << 27;  // tiles * k*k
-constexpr int64_t kEbWideMinM = 1 << 25;           // from here on tiles of 8192 edges, below of 4096 (4,096 and 8,192: 18M edges, k = 8,
-                                                   // 388 and 421 us, 40M 1.14 and 1.13 ms, 200M, k = 16, 4.9 and 4.2 ms)
+// Tiles of 8192 edges for long lists with many buckets, of 4096 for all others.  Few buckets make long runs in either, and the
+// larger tile's kernel is the slower one by itself; it wins where runs of a 4,096-edge tile are short (64 edges: k = 8) and the
+// table of the tiles' counts outgrows the L2 (m * k * k = 6.5e9: 6.3 MB of it).  All kernels of a call, 4096 | 8192, ms:
+//   34M edges   k = 2 0.53 | 0.57, 8 0.62 | 0.65, 12 0.68 | 0.69, 16 0.72 | 0.71, 32 0.92 | 0.89, 33 1.42 | 1.40, 64 1.81 | 1.64
+//   68M         k = 4 1.20 | 1.28, 8 1.28 | 1.31, 10 1.34 | 1.33, 12 1.39 | 1.36, 16 1.45 | 1.40
+//   200M        k = 2 3.53 | 3.69, 4 3.54 | 3.63, 6 3.72 | 3.67, 8 3.80 | 3.72, 16 4.80 | 3.95
+//   400M        k = 2 7.4 | 7.6, 8 7.5-8.2 | 7.6, 10 7.8-8.7 | 7.7, 16 9.2-9.9 | 8.1, 32 11.5 | 10.6, 33 16.2-17.7 | 15.6
+//   1.6e9       k = 2 33.1 | 34.0, 3 31.8 | 33.9, 6 33.2 | 34.1, 8 33.7 | 34.3, 10 34.4 | 34.5, 16 39.4-42.5 | 35.4
+// (k >= 33 does not fit k_eb_scatter_lds and gains by the smaller table alone.)
+constexpr int64_t kEbWideMinM = 1 << 25, kEbWideMinCells = 6'500'000'000;
+constexpr int32_t kEbWideMinBuckets = 64;
+inline bool eb_wide(int64_t m, int32_t k2) { return m >= kEbWideMinM && k2 >= kEbWideMinBuckets && m * k2 >= kEbWideMinCells; }
 constexpr uint32_t kBadLabel = 0xFFu;
 constexpr int64_t kEbBinMinN = 1ll << 23, kEbBinMinM = 1 << 22, kEbBinMinNM = 200'000'000'000'000;
 
@@ -554,11 +564,12 @@ __global__ __launch_bounds__(kEbBlock) void k_eb_scatter(const int32_t* __restri
 // tile (consecutive stream positions), counts them, the counts become per-wave cursors into the tile's sorted
 // order (bucket, then wave, then stream position = stable), every wave places its edges into LDS without
 // waiting for the others, and the sorted tile is written out with consecutive lanes on consecutive
-// addresses of a bucket's run; with 1024 threads the sources first, then, through the same LDS, the targets, so that two workgroups
-// of sixteen waves stand on a CU.  Bound by the runs, pieces of the output of 128 bytes at 256 buckets: with tiles of 4,096
-// edges and runs of 64 bytes 1.6e9 edges took 9.3 to 12 ms in some processes and 14.3 to 18 in others (the same within one),
-// with 8,192 10.6 to 11.0 (13.8 in a form of 36 registers, with the same loads and stores, that spills nothing).  Shorter lists,
-// which the caches hold, want both ends at once (a list whose whole call takes 416 us took 438 with turns for them).
+// addresses of a bucket's run; with 1024 threads the sources first, then, through the same LDS, the targets, so that up to k = 30
+// two workgroups of sixteen waves stand on a CU (their 64 registers leave 44 bytes per lane in scratch).  Bound by the runs,
+// pieces of the output of 128 bytes at 256 buckets: with tiles of 4,096 edges and runs of 64 bytes 1.6e9 edges took 9.3 to 12 ms
+// in some processes and 14.3 to 18 in others (the same within one), with 8,192 10.6 to 11.0; a form of 36 registers, with the same
+// loads and stores, that spills nothing took 13.8 (its cause was not found).  Shorter lists, which the caches hold, want both
+// ends at once (a list whose whole call takes 416 us took 438 with turns for them).
 constexpr int kEbLdsBuckets = 1024;
 constexpr int kEbTurns = 8;                             // edges per thread
 template <int THREADS> constexpr int kEbScatterTile = THREADS * kEbTurns;
@@ -588,7 +599,7 @@ __global__ __launch_bounds__(THREADS, kEbTurnsForEnds<THREADS> ? 8 : 1) void k_e
     const int count = (int)(hi - lo);
     const uint32_t* row = H + (size_t)blockIdx.x * (size_t)k2;
     // the wave's edges, kEbTurns per lane: the keys first; where the ends take turns, the sources while the counts are added up
-    // and the targets while the sources are written (all of them held at once spilled)
+    // and the targets while the sources are written (all of them at once spilled more)
     const int seg0 = wave * kSeg, seg1 = seg0 + kSeg < count ? seg0 + kSeg : count;
     uint32_t key[kEbTurns];
     int32_t s[kEbTurns], d[kEbTurns];
@@ -699,7 +710,7 @@ extern "C" int grem_edge_buckets(const int32_t* src, const int32_t* dst, int64_t
     hipStream_t stream = (hipStream_t)stream_;
     const int32_t k2 = k * k;
     int64_t tile = (m * k2 + kEbMaxCells - 1) / kEbMaxCells;
-    const int64_t least = m >= kEbWideMinM ? kEbScatterTile<1024> : kEbScatterTile<512>;
+    const int64_t least = eb_wide(m, k2) ? kEbScatterTile<1024> : kEbScatterTile<512>;
     if (tile < least) tile = least;
     tile = (tile + kEbBlock - 1) / kEbBlock * kEbBlock;
     const int64_t tiles = (m + tile - 1) / tile;

@@ -1,5 +1,6 @@
-"""Edge buckets of lists long enough for tiles of 8,192 edges (2^25 and more) against the oracle: last tiles of one edge and of
-all but one, one bucket, runs of a few edges and of whole tiles, more buckets than the sorting in LDS takes."""
+"""Edge buckets of lists long enough for tiles of 8,192 edges (2^25 and more, with 14 or more partitions) against the oracle: last
+tiles of one edge and of all but one, runs of a few edges and of whole tiles, more buckets than the sorting in LDS takes; and
+lists as long with so few buckets that their tiles have 4,096 edges."""
 import numpy as np
 import pytest
 import torch
@@ -13,7 +14,7 @@ DEV = "cuda:0"
 
 @pytest.mark.parametrize("m,k,skew", [((1 << 25) - 1, 16, False), (1 << 25, 16, False), ((1 << 25) + 1, 17, False),
                                       ((1 << 25) + 8191, 32, False), ((1 << 25) + 777, 33, False), ((1 << 25) + 64, 1, False),
-                                      ((1 << 25) + 513, 12, True)])
+                                      ((1 << 25) + 513, 12, True), ((1 << 25) + 513, 14, True)])
 def test_wide_tiles(m, k, skew):
     n = 50_021
     rng = np.random.default_rng(m % 1000 + k)

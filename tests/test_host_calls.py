@@ -130,6 +130,18 @@ def test_without_the_memory_for_a_faster_form(fake):
     """, sizes="big, ends = mem(1 << 29), mem(1 << 27)")
 
 
+def test_bucket_tiles_by_edges_and_buckets(fake):
+    # tiles of 8,192 edges: 2^25 edges or more, 64 buckets or more, and 6.5e9 edges times buckets
+    _run(fake, """
+    for m, k, wide in ((2**25 - 1, 32, 0), (2**25, 16, 1), (2**25, 13, 0), (2**25, 2, 0), (45_138_888, 12, 0), (45_138_889, 12, 1),
+                       (101_562_499, 8, 0), (101_562_500, 8, 1), (200_000_000, 7, 0), (200_000_000, 1, 0), (2**25, 32, 1)):
+        reset()
+        assert buckets(50_000, m, k) == 0
+        names = [x[1] for x in text() if x[0] == "launch" and "k_eb_scatter" in x[1]]
+        assert len(names) == 1 and ("ILi1024E" if wide else "ILi512E") in names[0], (m, k, names)
+    """)
+
+
 def test_no_exception_where_host_memory_ends(fake):
     # 20 levels: 12.6 MB of counters on the device and as much on the host, of which there is only half
     _run(fake, """
