@@ -49,8 +49,6 @@ constexpr int kMaxWaveWords = 64;            // most bitmap words a wave of the 
 constexpr int kMaxAdmitWords = 256;          // ... of k_es_admit
 constexpr uint32_t kNone = 2u;               // label of a node that has none
 constexpr int kCountBlock = 256;
-constexpr int kCountUnroll = 4;              // edges in flight per thread of k_es_count ...
-constexpr int64_t kCountSparse = 1 << 17;    // ... one where they are no more than these
 constexpr int kTurn = 4;                     // bitmap words a wave has in flight
 
 // One group of a run.
@@ -270,9 +268,10 @@ __global__ __launch_bounds__(256) void k_es_seed_sizes(EsRun st)
 // unassigned other end adds nothing; the node's bit in `mark` is set instead, so that a node of the
 // chunk is known by a non-zero count or its bit: one atomic per edge end either way.
 // Random look-ups and atomics, 39 G/s of them together once labels and hc outgrow the L2 (then the ends are binned).
-template <int U>
-__device__ __forceinline__ void es_count_edges(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, const EsRun& st,
-                                               int64_t chunk, u64* hc)
+// An edge per thread: with four in flight each, nothing was faster at chunks of 2,000 to 100M edges, and those of 6,000 took
+// 7.1 us for 3.8.
+__global__ __launch_bounds__(kCountBlock) void k_es_count(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                                                          EsRun st, int64_t chunk, u64* hc)
 {
     const EsGroup g = st.groups[blockIdx.y];
     int64_t lo, hi;
@@ -281,48 +280,16 @@ __device__ __forceinline__ void es_count_edges(const int32_t* __restrict__ src, 
     hc += g.node0;
     u64* mark = st.mark + (g.node0 >> 6);
     const int64_t threads = (int64_t)gridDim.x * blockDim.x;
-    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (int64_t base = lo + tid; base < hi; base += threads * U) {
-        uint32_t s[U], d[U], ls[U], ld[U];
-        u64 ws[U], wd[U];
-        bool in[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t e = base + (int64_t)u * threads;
-            in[u] = e < hi;
-            s[u] = in[u] ? (uint32_t)src[e] : 0u;
-            d[u] = in[u] ? (uint32_t)dst[e] : 0u;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            ws[u] = in[u] ? Lw[s[u] >> 5] : 0ull;
-            wd[u] = in[u] ? Lw[d[u] >> 5] : 0ull;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) { ls[u] = es_label(ws[u], s[u]); ld[u] = es_label(wd[u], d[u]); }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (!in[u]) continue;
-            if (ld[u] != kNone) atomicAdd(&hc[s[u]], ld[u] ? (1ull << 32) : 1ull);
-            else atomicOr(&mark[s[u] >> 6], 1ull << (s[u] & 63u));
-            if (d[u] != s[u]) {
-                if (ls[u] != kNone) atomicAdd(&hc[d[u]], ls[u] ? (1ull << 32) : 1ull);
-                else atomicOr(&mark[d[u] >> 6], 1ull << (d[u] & 63u));
-            }
-        }
+    for (int64_t e = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < hi; e += threads) {
+        const uint32_t s = (uint32_t)src[e], d = (uint32_t)dst[e];
+        const u64 ws = Lw[s >> 5], wd = Lw[d >> 5];
+        const uint32_t ls = es_label(ws, s), ld = es_label(wd, d);
+        if (ld != kNone) atomicAdd(&hc[s], ld ? (1ull << 32) : 1ull);
+        else atomicOr(&mark[s >> 6], 1ull << (s & 63u));
+        if (d == s) continue;
+        if (ls != kNone) atomicAdd(&hc[d], ls ? (1ull << 32) : 1ull);
+        else atomicOr(&mark[d >> 6], 1ull << (d & 63u));
     }
-}
-
-// an edge per thread and turn where there are few, kCountUnroll where there are many
-__global__ __launch_bounds__(kCountBlock) void k_es_count(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                                          EsRun st, int64_t chunk, u64* hc)
-{
-    es_count_edges<1>(src, dst, st, chunk, hc);
-}
-__global__ __launch_bounds__(kCountBlock) void k_es_count_many(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                                               EsRun st, int64_t chunk, u64* hc)
-{
-    es_count_edges<kCountUnroll>(src, dst, st, chunk, hc);
 }
 
 // ---- the chunk's edge ends binned by ranges of nodes -------------------------------------------------------
@@ -1345,17 +1312,6 @@ void es_fill(hipStream_t stream, void* p, size_t bytes, u64 value)
         hipLaunchKernelGGL(k_es_fill64, dim3(grid_for((int64_t)count, 256, 16384)), dim3(256), 0, stream, (u64*)p, count, value);
 }
 
-// k_es_count: few edges are spread over as many workgroups as they make, many are taken kCountUnroll per thread
-void es_count(hipStream_t stream, int64_t most, unsigned ng, const int32_t* src, const int32_t* dst, const EsRun& st, int64_t chunk, u64* hc)
-{
-    if (most * ng <= kCountSparse)
-        hipLaunchKernelGGL(k_es_count, dim3((unsigned)grid_for(most, kCountBlock, 1 << 20), ng), dim3(kCountBlock), 0, stream, src, dst, st,
-                           chunk, hc);
-    else
-        hipLaunchKernelGGL(k_es_count_many, dim3((unsigned)grid_for((most + kCountUnroll - 1) / kCountUnroll, kCountBlock, 1 << 20), ng),
-                           dim3(kCountBlock), 0, stream, src, dst, st, chunk, hc);
-}
-
 // One run: everything from the cleared state to the last chunk's spill is enqueued.  groups_host: its groups, in the
 // order of their nodes (also at mem.groups on the device, with mem.blk_group filled).  check(): called once the first chunk's seeds are
 // counted and flags[] is complete, before anything uses the labels; its answer other than GREM_OK ends the run.
@@ -1433,7 +1389,8 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
             hipLaunchKernelGGL(k_es_bin, dim3((unsigned)((most + kBinTile - 1) / kBinTile), ng), dim3(kBlock), kBinTile * 8, stream, src, dst,
                                st, i, sh.cb, mem.cursors, mem.pairs);
         else
-            es_count(stream, most, ng, src, dst, st, i, mem.hc);
+            hipLaunchKernelGGL(k_es_count, dim3((unsigned)grid_for(most, kCountBlock, 1 << 20), ng), dim3(kCountBlock), 0, stream, src, dst, st,
+                               i, mem.hc);
         if (!sh.binned) timed();
         const int first = i == 0 ? 1 : 0;
         if (sh.binned && crowded[(size_t)i])

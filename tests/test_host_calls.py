@@ -163,7 +163,7 @@ def test_no_exception_where_host_memory_ends(fake):
 def test_the_edge_timing_spans_the_kernels_that_count(fake):
     _run(fake, """
     assert lib.grem_edge_stream_profile_enable(I(1)) == 0
-    for n, m, inside in ((20_000, 50_000, {"k_es_count"}), (5_000_000, 50_000, {"k_es_bin", "k_es_score_bins"})):
+    for n, m, inside in ((20_000, 50_000, {"k_es_count"}), (20_000, 900_000, {"k_es_count"}), (5_000_000, 50_000, {"k_es_bin", "k_es_score_bins"})):
         reset()
         assert stream(n, m, 3) == 0
         t = [x for x in text() if x[0] in ("record", "launch")]
