@@ -28,3 +28,17 @@ def test_wide_tiles(m, k, skew):
     want = oracle.edge_buckets(src, dst, labels, k)
     for g, w in zip(got, want):
         assert np.array_equal(g.cpu().numpy(), w)
+
+
+# the look-ups binned by ranges of 2^16 and of 2^17 nodes, up to 16 partitions and more, with tiles of 8,192 edges
+@pytest.mark.parametrize("n,m,k", [(8_400_001, (1 << 25) + 4097, 16), (8_400_001, (1 << 25) + 77, 33), ((1 << 26) + 4099, (1 << 25) + 8191, 16),
+                                   ((1 << 26) + 4099, 1 << 25, 31)])
+def test_wide_tiles_after_binned_look_ups(n, m, k):
+    rng = np.random.default_rng(n % 1000 + k)
+    src = rng.integers(0, n, m, dtype=np.int32)
+    dst = rng.integers(0, n, m, dtype=np.int32)
+    labels = rng.integers(0, k, n, dtype=np.int32)
+    got = B.grem_edge_buckets(*(torch.as_tensor(x).to(DEV) for x in (src, dst)), n, torch.as_tensor(labels).to(DEV), k)
+    want = oracle.edge_buckets(src, dst, labels, k)
+    for g, w in zip(got, want):
+        assert np.array_equal(g.cpu().numpy(), w)

@@ -60,3 +60,17 @@ def test_a_bisection_whose_groups_end_inside_words():
     s, d, sd = (torch.as_tensor(a).to(DEV) for a in (src, dst, seeds.reshape(-1)))
     got = B.grem_recursive_bisection(s, d, n, levels, 10, 1.01, sd, B.EDGE_REFINE)
     assert np.array_equal(got.cpu().numpy(), oracle.recursive_bisection(src, dst, n, levels, 10, 1.01, seeds, B.EDGE_REFINE))
+
+
+# groups side by side from the second level on, whose halves all fill: a lane per word (with fewer words than lanes), per two and
+# per four words of 64 nodes
+@pytest.mark.parametrize("n,levels,chunks", [(300_007, 3, 8), (17_000_003, 2, 4), (34_000_001, 2, 3)])
+@pytest.mark.parametrize("mode", [B.EDGE_REFINE, B.EDGE_FIXED])
+def test_bisections_whose_halves_fill(n, levels, chunks, mode):
+    src, dst, _ = _towards_one_side(n, 0.9, 0, n % 89)
+    rng = np.random.default_rng(n % 83)
+    seeds = rng.integers(0, 2, (levels, n), dtype=np.int32)
+    seeds[:, :1000] = rng.random((levels, 1000)) < 0.3                      # most of the others follow these to half 0
+    got = B.grem_recursive_bisection(*(torch.as_tensor(a).to(DEV) for a in (src, dst)), n, levels, chunks, 1.0,
+                                     torch.as_tensor(seeds.reshape(-1)).to(DEV), mode)
+    assert np.array_equal(got.cpu().numpy(), oracle.recursive_bisection(src, dst, n, levels, chunks, 1.0, seeds, mode))
