@@ -37,7 +37,12 @@ constexpr int kTileGrid = 2048;            // ... and workgroups per chunk (1024
 // Merged launches: estimates are packed where they outgrow the Infinity Cache, from 32 partitions on (fewer are mostly not
 // zero; below 128 of them half of a row may be, and the estimates must outgrow it twice).  Whole and packed: k = 40, 480 MB 4.51 and
 // 4.53 ms; 48, 768 MB 3.84 and 3.42; 64, 256 MB 1.70 and 1.71, 1 GB 4.2 and 3.6; 100, 120 MB 1.50 and 1.53; 256, 17 GB 63.8
-// and 50.9; 400, 480 MB 2.31 and 2.01, 6.4 GB 15.6 and 12.3.
+// and 50.9; 400, 480 MB 2.31 and 2.01, 6.4 GB 15.6 and 12.3.  Rows of many entries gain less and lose nothing: 250 entries, k = 256
+// 4.49 and 3.9 ms; 500 to 2,000 entries, k = 64 to 1024 within 2 %.
+// Nor are they packed in tiles of fewer than kEstAhead * kScoreThreads = 2,048 cells, which chunks of few rows make: whole, a
+// thread asks for all of its estimates before the counting starts, packed it has to see the bits first.  Three passes: k = 40, tiles of
+// 640 cells 8.91 and 9.18, 1,280 5.14 and 5.15, 2,560 4.63 and 4.26; 64, 512 9.24 and 9.52, 2,048 4.75 and 4.80, 4,096 3.12 and 2.74;
+// 100, 800 6.82 and 7.00, 1,600 4.23 and 4.23, 3,200 3.37 and 2.98; 128, 1,024 2.79 and 2.83, 2,048 1.87 and 1.85, 4,096 1.58 and 1.37.
 constexpr int kPackMinK = 32, kPackManyK = 128;
 constexpr size_t kPackMinBytes = 256u << 20;
 constexpr int kLdsMaxK = 1024;             // above this the histograms live in E's rows
@@ -1040,8 +1045,9 @@ int merged_tile_rows(int32_t k, int64_t cl) {
     return tv;
 }
 
-bool pack_estimates(int64_t n, int32_t k) {
-    return k >= kPackMinK && (size_t)n * (size_t)k * 4 > (k >= kPackManyK ? kPackMinBytes : 2 * kPackMinBytes);
+bool pack_estimates(int64_t n, int32_t k, int64_t cl) {
+    return k >= kPackMinK && (size_t)n * (size_t)k * 4 > (k >= kPackManyK ? kPackMinBytes : 2 * kPackMinBytes) &&
+           merged_tile_rows(k, cl) * k >= kEstAhead * kScoreThreads;
 }
 
 // words of 64 cells that the packed estimates of a chunk's tiles make
@@ -1083,7 +1089,7 @@ int run_plain_merged(const RowT *rowptr, const int32_t *colidx, int64_t n, int32
     const bool external_E = estimates_out != nullptr;
     const int64_t nchunks = (n + cl - 1) / cl;
     PlainExtra x;
-    const bool pack = pack_estimates(n, k) && !external_E && R > 0;
+    const bool pack = pack_estimates(n, k, cl) && !external_E && R > 0;
     if (!(pack && carve(mem, [&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E, true, true); })) &&
         !carve(mem, [&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E, true); }))
         return GREM_ERR_NOMEM;
@@ -1313,7 +1319,7 @@ size_t plain_bytes(int64_t n, int32_t k, int64_t cl, bool external_E, bool packe
     // (whichever of the two forms takes more)
     const size_t one = carve_size([&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E, false); });
     const size_t two = plain_merged(k, cl, GREM_HIST_AUTO)
-                           ? carve_size([&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E, true, packed && pack_estimates(n, k)); }) : 0;
+                           ? carve_size([&](Carver &c) { state_plain(c, x, n, cl, k, nchunks, external_E, true, packed && pack_estimates(n, k, cl)); }) : 0;
     return a + (one > two ? one : two);
 }
 

@@ -1,4 +1,4 @@
-"""Estimates of the plain route kept packed (more than 512 MB of them, from 128 partitions on 256 MB): rows of cells that are
+"""Estimates of the plain route kept packed (more than 512 MB of them, from 128 partitions on 256 MB; tiles of 2,048 cells): rows of cells that are
 no multiple of a word, one and two bytes per label, tiles with long rows in them, short last tiles, a workspace without
 room for the bits.  Whole numbers: equal to the oracle's."""
 import numpy as np
@@ -16,7 +16,10 @@ DEV = "cuda:0"
 @pytest.mark.parametrize("n,k,chunk,R,seeded", [
     (4_068_000, 33, 270_001, 1, 0.0),      # the fewest partitions; tiles of 64 rows, the last one short
     ((1 << 21) + 1, 64, 1 << 20, 2, 0.2),  # just above the line; a last chunk of one row
-    (1_390_000, 97, 33_333, 2, 1.0),         # tiles of 16 rows of 97 cells: words that end inside a row
+    (1_390_000, 97, 33_333, 2, 1.0),         # tiles of 16 rows of 97 cells: too few to be packed
+    (1_390_000, 97, 70_001, 2, 1.0),         # ... and of 32: words that end inside a row
+    ((1 << 21) + 1, 64, 65_504, 1, 0.0),   # the most rows that make tiles of 16 rows of 64 cells
+    ((1 << 21) + 1, 64, 65_505, 1, 0.0),   # ... and the fewest that make tiles of 32
     (263_000, 256, 50_001, 3, 0.0),        # a byte per label up to the last one
     (263_000, 257, 50_000, 2, 0.3),
     (66_000, 1024, 20_003, 3, 0.0),        # four rows to a tile

@@ -142,6 +142,19 @@ def test_bucket_tiles_by_edges_and_buckets(fake):
     """)
 
 
+def test_estimates_are_packed_by_their_bytes_and_a_tiles_cells(fake):
+    # 512 MB of estimates (256 MB from 128 partitions on), and tiles of 2,048 cells: 32 rows of 64, 8 of 256 or of 257
+    _run(fake, """
+    for n, k, chunk, packed in ((2_200_000, 64, 200_000, 1), (2_200_000, 64, 65_505, 1), (2_200_000, 64, 65_504, 0), (2_200_000, 64, 20_000, 0),
+                                (4_200_000, 33, 270_001, 1), (4_200_000, 33, 65_536, 0), (2_000_000, 64, 200_000, 0), (600_000, 128, 20_000, 0),
+                                (600_000, 128, 32_753, 1), (300_000, 256, 2_000, 1), (250_000, 256, 100_000, 0), (300_000, 257, 2_000, 1)):
+        reset()
+        assert partition(n, k, chunk) == 0
+        names = {x[1] for x in text() if x[0] == "launch" and "k_score_tile" in x[1]}
+        assert len(names) == 1 and ("Lb%dE" % packed) in names.pop(), (n, k, chunk, packed)
+    """)
+
+
 def test_no_exception_where_host_memory_ends(fake):
     # 20 levels: 12.6 MB of counters on the device and as much on the host, of which there is only half
     _run(fake, """
