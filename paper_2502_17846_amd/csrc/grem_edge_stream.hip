@@ -362,11 +362,11 @@ __global__ __launch_bounds__(kBins) void k_es_hist_scan(uint32_t* table, uint32_
 }
 
 // cnt_nbrs, first half: for every edge end the label of the other end, the pairs sorted by bin.  A pair is the
-// node's place in its bin and 0, 1 or 2 (no label) above it.  What bounds it is the look-up of the labels (57 G/s
-// once they outgrow the L2); the pairs cost 4 bytes written and read where an atomic on the node's counts costs a
+// node's place in its bin and 0, 1 or 2 (no label) above it.  What bounds it is the look-up of the labels (59 G/s
+// in the 28 MB of 111M nodes, which outgrow the L2); the pairs cost 4 bytes written and read where an atomic on the node's counts costs a
 // read and a write of 64.  A tile's pairs are collected in LDS bin by bin and written in runs (16,384 pairs into
 // 848 bins at 111M nodes: some 77 bytes each).
-// 32M edge ends of 111M nodes: 1.61 ms with an atomic per end, 0.62 here.
+// 32M edge ends of 111M nodes: 1.61 ms with an atomic per end and a byte per label, 0.62 so sorted, 0.55 with two bits per label.
 __global__ __launch_bounds__(kBlock) void k_es_bin(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                                                    EsRun st, int64_t chunk, int cb, uint32_t* __restrict__ cursors,
                                                    uint32_t* __restrict__ pairs)
@@ -840,8 +840,8 @@ __device__ __forceinline__ void es_rejected(const EsRun& st, uint32_t blk0, uint
 // their other copy.
 // A lane takes W neighbouring words of 64 nodes (awpw = 64 * W words per wave, or fewer with W = 1): the admitted movers
 // of a word are its first bits, as many as there is room for, the alternation over rejected ones is a prefix parity, and labels
-// change in a few bit operations.  W and awpw: so many that 256 blocks or fewer do it, as each adds up all blocks' counts
-// (es_shape).  In two launches (admission, spill), with labels of a byte each and movers taken one by one: 103 us per chunk at
+// change in a few bit operations.  W and awpw: so many that 256 blocks or fewer do it up to 67M nodes in one group, as each adds up
+// all blocks' counts; beyond that a block takes 262,144 nodes, 424 of them 111M (es_shape).  In two launches (admission, spill), with labels of a byte each and movers taken one by one: 103 us per chunk at
 // 111M nodes, 13 at 20,000; now 53 and 6.
 template <int W>
 __global__ __launch_bounds__(kBlock) void k_es_admit(EsRun st, int par)
@@ -985,8 +985,8 @@ __global__ __launch_bounds__(kBlock) void k_rb_count(EsRun st)
 // alternate 0,1,... .  So the node of half 0 with z labelled zeros and j unlabelled nodes before it is number
 // z + (zeros among the first j placements) of its half, and nothing but the two counts per block is needed.
 // halves[]: per 32 nodes of the state the nodes of half 1 (low half) and how many of the group's nodes before them are of half
-// 0 (high half), from which a node's number inside its half follows: a quarter of a byte per node, which the L2s hold, is what
-// the edges' ends are looked up in.  The halves' node lists (ids and next level's seed bits) are written, half 0 first.  At the
+// 0 (high half), from which a node's number inside its half follows: a quarter of a byte per node, which every L2 holds up to
+// some 16M nodes (28 MB at 111M), is what the edges' ends are looked up in.  The halves' node lists (ids and next level's seed bits) are written, half 0 first.  At the
 // last level the labels 2 * group + half go out instead.  gof == nullptr: node i has id i.  nodes0[group]: nodes of half 0.
 __global__ __launch_bounds__(kBlock) void k_rb_children(EsRun st, int par, const int32_t* __restrict__ gof,
                                                         const int32_t* __restrict__ next_bits, u64* halves,
@@ -1200,12 +1200,13 @@ inline int grid_for(int64_t items, int block, int64_t cap)
 //   binned  from 4M nodes on (128 blocks; the counts in memory, 8 bytes per node, then far outgrow the L2), if a
 //           chunk's pairs take no more room than the estimates and the table of the chunks' bins stays small.  A
 //           block's counts fill a CU's LDS, 32,768 nodes: with 16,384 or 8,192 nodes and two or four workgroups per CU
-//           a whole run took 163 or 191 ms instead of 150 at 111M nodes (every block of a bin reads all its pairs),
-//           18.5 or 19.5 instead of 17.9 at 14M.
+//           a whole run takes 126 or 145 ms instead of 119 at 111M nodes (every block of a bin reads all its pairs),
+//           12.1 or 13.0 instead of 11.6 at 14M (100 chunks each).
 //   blocks  otherwise kBlock * wpw nodes each: one word per wave up to a million nodes (the chip wants some 1024
 //           blocks), more words beyond it, so that a block can add up all blocks' counts itself.
 //   awpw    the admission's workgroups each add up all blocks' counts: as many words per wave as leave 256 workgroups or
-//           fewer, while the groups' padding stays within their nodes.
+//           fewer, up to kMaxAdmitWords (262,144 nodes per workgroup: more than 256 of them from 67M nodes on) and while the
+//           groups' padding stays within their nodes (so with several groups there may be more from fewer nodes on).
 struct EsShape {
     int wpw = 1, awpw = 1, cb = 0;
     bool binned = false;
