@@ -28,11 +28,11 @@ HBM_PEAK_GBPS = 8000.0
 # at that time, and `traffic` is reported as null when the sources have changed since.
 PMC = {
     "workload": "chunglu-111M",
-    "sources_sha256": "159cbd1f5bb023d1c52ed59c66123f55dd3101613726e7c5d39452314c426dd4",
+    "sources_sha256": "403af8245d638131ab4102c3fd4d2e34c6415a3ce170162cc5b1fc5f8e934924",
     "fetch_factor": 2.0,        # 2 GiB read  -> FETCH_SIZE 1,048,591 KiB
     "write_factor": 1.0,        # 2 GiB written -> WRITE_SIZE 2,097,152 KiB
-    "fetch_kib": {"k_tp_score": 1.42622e+07, "k_tp_lookup": 1.36601e+07},
-    "write_kib": {"k_tp_score": 7.32475e+06, "k_tp_lookup": 5.5879e+06},
+    "fetch_kib": {"k_tp_score": 1.42622e+07, "k_tp_lookup": 1.36622e+07},
+    "write_kib": {"k_tp_score": 7.32475e+06, "k_tp_lookup": 5.58579e+06},
     "launches": {"k_tp_score": 318, "k_tp_lookup": 317},
 }
 
@@ -40,9 +40,9 @@ PMC = {
 # The same for the edge-chunk path's two dominant kernels (one launch each per chunk) on its 111M-node workload.
 PMC_EDGE = {
     "workload": "edges-chunglu-111M-c1pct",
-    "sources_sha256": "0cb16dd125dc6f98c4bb34fd1d46aa9b5c14a0ae0622bf1f239a7dc692010b78",
-    "fetch_kib": {"k_es_bin": 1.71828e+08, "k_es_score_bins": 6.93709e+07},
-    "write_kib": {"k_es_bin": 1.5865e+07, "k_es_score_bins": 4.90064e+07},
+    "sources_sha256": "d22306e150e0289bf821a1eefbccf649692f3b9fd1b842a9c790228a6509ce11",
+    "fetch_kib": {"k_es_bin": 1.71843e+08, "k_es_score_bins": 6.93455e+07},
+    "write_kib": {"k_es_bin": 1.58725e+07, "k_es_score_bins": 4.90061e+07},
     "launches": 100,
 }
 
