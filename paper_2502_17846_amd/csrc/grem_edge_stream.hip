@@ -16,7 +16,7 @@
 //   Lw    uint64 per 32 nodes: low half = nodes that have a label, high half = those of partition 1 (no label: 0).  A quarter
 //                   of a byte per node is what the random look-ups go to; the per-node kernels take 64 nodes' labels in
 //                   one load and relabel them with a few bit operations
-//   est   double[2] Alg. 1's nbr_counts
+//   est   double[2] Alg. 1's nbr_counts; on large graphs 8 bytes per node hold them while they fit (es_blend_packed)
 //   mv0, mv1, nw    bitmaps: nodes asking to move to partition 0 / 1, and those of them that have no label
 //                   yet.  Bitmaps are ordered sets: bit order is id order, so ranks by id are prefix
 //                   pop-counts.
@@ -25,12 +25,14 @@
 //   in memory (small graphs)  hc, uint64 per node: low half = neighbours in partition 0, high half = in
 //                   partition 1; k_es_count adds one 64-bit atomic per edge end, k_es_score reads and clears.
 //   binned (large graphs)     k_es_bin looks the other end's label up for every edge end and sorts the
-//                   (node, label) pairs by ranges of nodes; k_es_score_bins counts a block's pairs in LDS.
+//                   (node, label) pairs by ranges of nodes; k_es_score_bins counts a block's pairs in LDS.  Where the
+//                   labels outgrow the L2s, k_es_ask and k_es_answer do k_es_bin's work with labels in LDS.
 // Per chunk: count or bin -> score (blend, assign, mover ballots) -> k_es_admit (ranks = movers of the earlier
 // blocks + pop-count prefix; admitted moves relabel; closed-form target of the j-th rejected node; sizes).  The
 // sizes live in two copies that take turns from chunk to chunk.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <mutex>
 #include <new>
@@ -67,7 +69,9 @@ struct EsRun {
     const uint32_t* blk_group;               // group of a block
     u64* S;                                  // [2][groups][2]: sizes, two copies
     u64* Lw;
-    double2* est;
+    double2* est;                            // counts in memory: the estimates; binned: those of `packed` that have outgrown it
+    u64* packed;                             // binned: the estimates in 8 bytes each
+    uint32_t* wide;                          // ... and per block how many have outgrown them
     u64 *mark, *mv0, *mv1, *nw;
     uint4* bs;                               // per block: movers to 0, to 1, those of either without a label
     uint32_t* flags;                         // [0] an endpoint out of range, [1] a bad seed
@@ -156,14 +160,57 @@ __global__ __launch_bounds__(kCountBlock) void k_es_mark(const int32_t* __restri
 // The two-partition choice of Alg. 2, on sizes from which the node itself has been taken out: the
 // side that holds strictly more of the node's neighbours wins when it still has room; with no such
 // side (equal estimates, or the richer side full) the smaller partition takes the node, 0 on a tie.
-__device__ __forceinline__ int es_assign(double nbrs0, double nbrs1, long long s0, long long s1, long long P)
+// lean: +1 where side 1 holds more, -1 where side 0 does, 0: neither
+__device__ __forceinline__ int es_assign(int lean, long long s0, long long s1, long long P)
 {
-    const int lean = (nbrs1 > nbrs0) - (nbrs0 > nbrs1);   // +1: towards 1, -1: towards 0, 0: neither
     if (lean != 0) {
         const int p = lean > 0;
         if ((p ? s1 : s0) < P) return p;
     }
     return s1 < s0;
+}
+
+// An estimate in 8 bytes: both counts as whole numbers of 29 bits and, in the six bits above them, how many times they have
+// been halved, which is all of the doubles' value while no bit of it is lost.  Once one does not fit (a node has 29 edge ends or
+// more by then) the two are doubles in `est` and the 58 bits say where.
+constexpr uint32_t kPackBits = 29, kPackMask = (1u << kPackBits) - 1u, kPackWide = 7u << kPackBits;
+__device__ __forceinline__ bool es_is_wide(uint2 word) { return word.y >= kPackWide; }
+__device__ __forceinline__ size_t es_wide_place(uint2 word) { return (word.x & kPackMask) | (size_t)(word.y & kPackMask) << kPackBits; }
+__device__ __forceinline__ uint2 es_pack(uint32_t x, uint32_t y, uint32_t halved)
+{
+    return make_uint2(x | halved << kPackBits, y | (halved >> 3) << kPackBits);
+}
+__device__ __forceinline__ double2 es_unpack(uint2 word)
+{
+    const int halved = (int)(word.x >> kPackBits | (word.y >> kPackBits) << 3);
+    return make_double2(ldexp((double)(word.x & kPackMask), -halved), ldexp((double)(word.y & kPackMask), -halved));
+}
+// Alg. 1's blend of a packed estimate with the fresh counts, stored; the comparison of the two sides.  word, doubles: the stored
+// estimate, zero for a node that is not blended.  Where it grows out of 29 bits, the sum is rounded on its way into
+// the doubles as the doubles' own sum would be.
+__device__ __forceinline__ int es_blend_packed(const EsRun& st, size_t node, uint2 word, double2 doubles, bool blend, uint32_t h0, uint32_t h1,
+                                               size_t first_wide, uint32_t* wide)
+{
+    uint2* const packed = reinterpret_cast<uint2*>(st.packed) + node;
+    if (es_is_wide(word)) {
+        const double x = (doubles.x + (double)h0) * 0.5, y = (doubles.y + (double)h1) * 0.5;
+        st.est[es_wide_place(word)] = make_double2(x, y);
+        return (y > x) - (x > y);
+    }
+    const uint32_t b = word.x >> kPackBits | (word.y >> kPackBits) << 3, halved = b + (blend ? 1u : 0u);
+    const uint32_t x0 = word.x & kPackMask, y0 = word.y & kPackMask;
+    if (b < kPackBits && ((h0 | h1) >> (kPackBits - b)) == 0u) {
+        const uint32_t x = x0 + (h0 << b), y = y0 + (h1 << b);
+        if (((x | y) >> kPackBits) == 0u) {
+            *packed = es_pack(x, y, halved);
+            return (y > x) - (x > y);
+        }
+    }
+    const u64 x = x0 + ((u64)h0 << b), y = y0 + ((u64)h1 << b);
+    const size_t at = first_wide + atomicAdd(wide, 1u);
+    st.est[at] = make_double2(ldexp((double)x, -(int)halved), ldexp((double)y, -(int)halved));
+    *packed = make_uint2((uint32_t)at & kPackMask, (uint32_t)(at >> kPackBits) | kPackWide);
+    return (y > x) - (x > y);
 }
 
 // value of x in lane i, i uniform over the wave
@@ -294,45 +341,74 @@ __global__ __launch_bounds__(kCountBlock) void k_es_count(const int32_t* __restr
 
 // ---- the chunk's edge ends binned by ranges of nodes -------------------------------------------------------
 //
-// A bin is 2^cb nodes of the state, at most kBins of them.  All chunks' bin sizes are counted beforehand
-// (k_es_hist, with the range check of the endpoints); table[chunk][bin], scanned (k_es_hist_scan), is where the
-// bin's pairs of that chunk start.
-constexpr int kBins = 1024;
-constexpr int kBinTile = 8192;               // edges per workgroup: 64 KB of pairs, two workgroups per CU
+// A bin is 2^cb nodes of the state, at most kBins of them (nb: how many, a multiple of kBlock).  All chunks' bin sizes are counted
+// beforehand (k_es_hist, with the range check of the endpoints).  Where a chunk has many tiles, a bin's room is split among eight
+// classes of tiles (neighbours; ends[chunk][class][bin]): workgroups go to the XCDs in turn, so that what the tiles of a class
+// write one after the other meets in one L2, and a run need not fill a line.  (Nothing but the time depends on where they go.)
+// ends[] holds first the sizes, then the starts (k_es_hist_scan), which k_es_bin moves on to the ends.
+constexpr int kBins = 4096;
+constexpr int kBinTile = 8192;               // most edges per workgroup: 64 KB of pairs, two workgroups per CU
 constexpr int kBinPer = kBinTile / kBlock;
-constexpr int kBinTableStride = kBins + 1;
 
+struct EsBins {
+    uint32_t* ends;
+    uint32_t nb;
+    int cb, classes;
+    // the pairs of a bin once they are all there
+    __device__ __forceinline__ void range(int64_t chunk, uint32_t bin, uint32_t& p0, uint32_t& p1) const
+    {
+        const uint32_t* row = ends + ((size_t)chunk * classes + (classes - 1)) * nb;
+        p0 = bin ? row[bin - 1u] : 0u;
+        p1 = row[bin];
+    }
+};
+
+// (gridDim.x is a multiple of the classes; tile: edges of a workgroup of k_es_bin or k_es_ask; hist: a word per bin or, where
+// labels are asked for, per bin and class)
 __global__ __launch_bounds__(kBlock) void k_es_hist(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                                    EsRun st, int cb, uint32_t* __restrict__ table)
+                                                    EsRun st, EsBins bins, EsBins ranges, int tile)
 {
-    __shared__ uint32_t hist[kBins];
+    extern __shared__ uint32_t hist[];
     const EsGroup g = st.groups[blockIdx.y];
     int64_t lo, hi;
     es_chunk(g, blockIdx.z, lo, hi);
-    if (lo + (int64_t)blockIdx.x * kBinTile >= hi) return;
-    hist[threadIdx.x] = 0u;
+    if (lo + (int64_t)blockIdx.x * tile >= hi) return;
+    const bool asked = ranges.ends != nullptr;
+    const uint32_t per = asked ? (uint32_t)bins.classes : 1u, cells = bins.nb * per;
+    for (uint32_t i = threadIdx.x; i < cells; i += kBlock) hist[i] = 0u;
     __syncthreads();
     bool bad = false;
-    for (int64_t t = lo + (int64_t)blockIdx.x * kBinTile; t < hi; t += (int64_t)gridDim.x * kBinTile) {
+    for (int64_t t = lo + (int64_t)blockIdx.x * tile; t < hi; t += (int64_t)gridDim.x * tile) {
+        const int64_t end = hi - t < tile ? hi : t + tile;
         uint32_t s[kBinPer], d[kBinPer];
 #pragma unroll
         for (int u = 0; u < kBinPer; ++u) {
             const int64_t e = t + u * kBlock + threadIdx.x;
-            s[u] = e < hi ? (uint32_t)src[e] : g.nv;
-            d[u] = e < hi ? (uint32_t)dst[e] : g.nv;
-            bad |= e < hi && (s[u] >= g.nv || d[u] >= g.nv);
+            s[u] = e < end ? (uint32_t)src[e] : g.nv;
+            d[u] = e < end ? (uint32_t)dst[e] : g.nv;
+            bad |= e < end && (s[u] >= g.nv || d[u] >= g.nv);
         }
 #pragma unroll
         for (int u = 0; u < kBinPer; ++u) {
             if (s[u] >= g.nv || d[u] >= g.nv) continue;
-            atomicAdd(&hist[(g.node0 + s[u]) >> cb], 1u);
-            if (s[u] != d[u]) atomicAdd(&hist[(g.node0 + d[u]) >> cb], 1u);
+            const uint32_t x = g.node0 + s[u], y = g.node0 + d[u];
+            atomicAdd(&hist[asked ? (y >> ranges.cb) % per * bins.nb + (x >> bins.cb) : x >> bins.cb], 1u);
+            if (x != y) atomicAdd(&hist[asked ? (x >> ranges.cb) % per * bins.nb + (y >> bins.cb) : y >> bins.cb], 1u);
         }
     }
     if (bad) st.flags[0] = 1u;
     __syncthreads();
-    const uint32_t c = hist[threadIdx.x];
-    if (c) atomicAdd(&table[(size_t)blockIdx.z * kBinTableStride + threadIdx.x], c);
+    uint32_t* table = bins.ends + (size_t)blockIdx.z * bins.nb * bins.classes;
+    const int own = (int)(blockIdx.x % (unsigned)bins.classes);
+    for (uint32_t i = threadIdx.x; i < cells; i += kBlock)
+        if (hist[i]) atomicAdd(&table[asked ? i : own * bins.nb + i], hist[i]);
+    if (!asked) return;
+    const uint32_t each = 1u << (ranges.cb - bins.cb);             // (a range asks as often as it is asked: every edge has two ends)
+    for (uint32_t i = threadIdx.x; i < bins.nb / each; i += kBlock) {
+        uint32_t c = 0;
+        for (uint32_t j = 0; j < each * per; ++j) c += hist[j / each * bins.nb + i * each + j % each];
+        if (c) atomicAdd(&ranges.ends[((size_t)blockIdx.z * ranges.classes + own) * ranges.nb + i], c);
+    }
 }
 
 // The bins of more than `limit` pairs in a chunk, which no workgroup should count alone (k_es_crowd).
@@ -344,88 +420,308 @@ struct EsCrowd {
     uint32_t limit;
 };
 
-// sizes -> starts (one workgroup per chunk); cursors: a second copy, which k_es_bin moves on
-__global__ __launch_bounds__(kBins) void k_es_hist_scan(uint32_t* table, uint32_t* cursors, EsCrowd crowd)
+// sizes -> starts (one workgroup per chunk, neighbouring bins a thread's)
+__global__ __launch_bounds__(kBlock) void k_es_hist_scan(EsBins bins, EsCrowd crowd, uint32_t* totals)
 {
     __shared__ uint32_t wsum[kWaves];
-    uint32_t* row = table + (size_t)blockIdx.x * kBinTableStride;
-    const uint32_t c = row[threadIdx.x];
-    const uint32_t excl = es_block_exclusive(c, wsum);
-    row[threadIdx.x] = excl;
-    cursors[(size_t)blockIdx.x * kBins + threadIdx.x] = excl;
-    if (threadIdx.x == kBins - 1) row[kBins] = excl + c;
+    const uint32_t own = bins.nb / kBlock, first = threadIdx.x * own;
+    uint32_t* row = bins.ends + (size_t)blockIdx.x * bins.nb * bins.classes + first;
+    uint32_t sum = 0, crowded = 0;
+    for (uint32_t i = 0; i < own; ++i) {
+        uint32_t c = 0;
+        for (int k = 0; k < bins.classes; ++k) c += row[(size_t)k * bins.nb + i];
+        sum += c;
+        crowded += crowd.place && c > crowd.limit ? 1u : 0u;
+    }
+    uint32_t at = es_block_exclusive(sum, wsum);
     __syncthreads();
-    const uint32_t crowded = c > crowd.limit ? 1u : 0u;
-    const uint32_t place = es_block_exclusive(crowded, wsum);
-    crowd.place[(size_t)blockIdx.x * kBins + threadIdx.x] = crowded ? (uint16_t)(place + 1u) : (uint16_t)0;
-    if (threadIdx.x == kBins - 1) crowd.bins[blockIdx.x] = place + crowded;
+    uint32_t place = es_block_exclusive(crowded, wsum);
+    for (uint32_t i = 0; i < own; ++i) {
+        const uint32_t start = at;
+        for (int k = 0; k < bins.classes; ++k) {
+            const uint32_t c = row[(size_t)k * bins.nb + i];
+            row[(size_t)k * bins.nb + i] = at;
+            at += c;
+        }
+        if (totals && threadIdx.x == kBlock - 1 && i + 1u == own) totals[blockIdx.x] = at;
+        if (!crowd.place) continue;
+        const bool is = at - start > crowd.limit;
+        crowd.place[(size_t)blockIdx.x * bins.nb + first + i] = is ? (uint16_t)(++place) : (uint16_t)0;
+    }
+    if (crowd.place && threadIdx.x == kBlock - 1) crowd.bins[blockIdx.x] = place;
+}
+
+// LDS of a tile's sorting: its items, per bin a word (how many, then where they go) and 16 bits (where they start)
+inline size_t es_sort_lds(size_t items, size_t item_bytes, uint32_t nb) { return items * item_bytes + (size_t)nb * 6; }
+
+// The bins' counts of a tile become starts in the sorted order and places in memory (minus the start): from hist[] to at[] (the
+// same array) and start[]; returns the number of items.  cursors: the tile's class of the chunk's row.  (Bins kBlock apart are a
+// thread's and neighbours in the order: a wave's atomics go to neighbouring words.)
+__device__ __forceinline__ uint32_t es_sort_scan(uint32_t* at, uint16_t* start, const EsBins& bins, uint32_t* cursors, uint32_t* wsum)
+{
+    uint32_t c[kBins / kBlock], sum = 0, total;
+#pragma unroll
+    for (int i = 0; i < kBins / kBlock; ++i) {
+        const uint32_t bin = i * kBlock + threadIdx.x;
+        c[i] = bin < bins.nb ? at[bin] : 0u;
+        sum += c[i];
+    }
+    uint32_t place[kBins / kBlock];
+#pragma unroll
+    for (int i = 0; i < kBins / kBlock; ++i)
+        if (c[i]) place[i] = atomicAdd(&cursors[i * kBlock + threadIdx.x], c[i]);
+    uint32_t excl = es_block_exclusive(sum, wsum, &total);
+#pragma unroll
+    for (int i = 0; i < kBins / kBlock; ++i) {
+        const uint32_t bin = i * kBlock + threadIdx.x;
+        if (bin >= bins.nb) continue;
+        start[bin] = (uint16_t)excl;
+        if (c[i]) at[bin] = place[i] - excl;
+        excl += c[i];
+    }
+    __syncthreads();
+    return total;
 }
 
 // cnt_nbrs, first half: for every edge end the label of the other end, the pairs sorted by bin.  A pair is the
 // node's place in its bin and 0, 1 or 2 (no label) above it.  What bounds it is the look-up of the labels (59 G/s
 // in the 28 MB of 111M nodes, which outgrow the L2); the pairs cost 4 bytes written and read where an atomic on the node's counts costs a
-// read and a write of 64.  A tile's pairs are collected in LDS bin by bin and written in runs (16,384 pairs into
-// 848 bins at 111M nodes: some 77 bytes each).
+// read and a write of 64.  A tile's pairs are collected in LDS bin by bin and written in runs.
 // 32M edge ends of 111M nodes: 1.61 ms with an atomic per end and a byte per label, 0.62 so sorted, 0.55 with two bits per label.
-__global__ __launch_bounds__(kBlock) void k_es_bin(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                                   EsRun st, int64_t chunk, int cb, uint32_t* __restrict__ cursors,
-                                                   uint32_t* __restrict__ pairs)
+template <int PER>
+__device__ __forceinline__ void es_bin_tile(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                                            const EsRun& st, int64_t chunk, const EsBins& bins, uint32_t* __restrict__ pairs)
 {
-    extern __shared__ uint32_t items[];            // 2 * kBinTile
-    __shared__ uint32_t hist[kBins], start[kBins], at[kBins], wsum[kWaves];
+    extern __shared__ uint32_t items[];            // 2 * PER * kBlock, then at[], start[]
+    __shared__ uint32_t wsum[kWaves];
+    uint32_t* at = items + 2 * PER * kBlock;
+    uint16_t* start = reinterpret_cast<uint16_t*>(at + bins.nb);
     const EsGroup g = st.groups[blockIdx.y];
     int64_t lo, hi;
     es_chunk(g, chunk, lo, hi);
-    lo += (int64_t)blockIdx.x * kBinTile;
+    lo += (int64_t)blockIdx.x * (PER * kBlock);
     if (lo >= hi) return;
-    const int tid = threadIdx.x;
-    hist[tid] = 0u;
+    const int tid = threadIdx.x, cb = bins.cb;
+    for (uint32_t i = tid; i < bins.nb; i += kBlock) at[i] = 0u;
     constexpr uint32_t kNothing = 0xFFFFFFFFu;
-    uint32_t a[kBinPer], b[kBinPer];               // node of the state | label code << 30 (fewer than 2^30 nodes)
+    uint32_t a[PER], b[PER];                       // node of the state | label code << 30 (fewer than 2^30 nodes)
 #pragma unroll
-    for (int u = 0; u < kBinPer; ++u) {
+    for (int u = 0; u < PER; ++u) {
         const int64_t e = lo + u * kBlock + tid;
         a[u] = e < hi ? g.node0 + (uint32_t)src[e] : kNothing;
         b[u] = e < hi ? g.node0 + (uint32_t)dst[e] : kNothing;
     }
-    u64 la[kBinPer], lb[kBinPer];
+    u64 la[PER], lb[PER];
 #pragma unroll
-    for (int u = 0; u < kBinPer; ++u) {
+    for (int u = 0; u < PER; ++u) {
         la[u] = a[u] != kNothing ? st.Lw[a[u] >> 5] : 0ull;
         lb[u] = a[u] != kNothing ? st.Lw[b[u] >> 5] : 0ull;
     }
     __syncthreads();
-    uint32_t ra[kBinPer], rb[kBinPer];             // rank among the tile's pairs of the same bin
+    uint32_t ra[PER], rb[PER];                     // rank among the tile's pairs of the same bin
 #pragma unroll
-    for (int u = 0; u < kBinPer; ++u) {
+    for (int u = 0; u < PER; ++u) {
         if (a[u] == kNothing) continue;
-        ra[u] = atomicAdd(&hist[a[u] >> cb], 1u);
+        ra[u] = atomicAdd(&at[a[u] >> cb], 1u);
         const bool loop = a[u] == b[u];
-        if (!loop) rb[u] = atomicAdd(&hist[b[u] >> cb], 1u);
+        if (!loop) rb[u] = atomicAdd(&at[b[u] >> cb], 1u);
         const uint32_t of_a = es_label(la[u], a[u]), of_b = es_label(lb[u], b[u]);
         a[u] |= of_b << 30;
         b[u] = loop ? kNothing : b[u] | of_a << 30;
     }
     __syncthreads();
-    const uint32_t c = hist[tid];
-    const uint32_t excl = es_block_exclusive(c, wsum);
-    start[tid] = excl;
-    if (c) at[tid] = atomicAdd(&cursors[(size_t)chunk * kBins + tid], c) - excl;
-    __syncthreads();
+    const uint32_t total = es_sort_scan(at, start, bins, bins.ends + ((size_t)chunk * bins.classes + blockIdx.x % (unsigned)bins.classes) * bins.nb, wsum);
     auto place = [&](uint32_t x, uint32_t rank) {
         const uint32_t node = x & 0x3FFFFFFFu, bin = node >> cb;
-        items[start[bin] + rank] = (node & ((1u << cb) - 1u)) | (x >> 30) << cb | bin << (cb + 2);      // (cb <= 20)
+        items[start[bin] + rank] = (node & ((1u << cb) - 1u)) | (x >> 30) << cb | bin << (cb + 2);      // (cb <= 18, 4096 bins)
     };
 #pragma unroll
-    for (int u = 0; u < kBinPer; ++u) {
+    for (int u = 0; u < PER; ++u) {
         if (a[u] != kNothing) place(a[u], ra[u]);
         if (b[u] != kNothing) place(b[u], rb[u]);
     }
     __syncthreads();
-    const uint32_t total = start[kBins - 1] + hist[kBins - 1];
     for (uint32_t i = tid; i < total; i += kBlock) {
         const uint32_t x = items[i];
         pairs[at[x >> (cb + 2)] + i] = x & ((1u << (cb + 2)) - 1u);
+    }
+}
+__global__ __launch_bounds__(kBlock, 8) void k_es_bin(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, EsRun st, int64_t chunk,
+                                                      EsBins bins, uint32_t* __restrict__ pairs)
+{
+    es_bin_tile<4>(src, dst, st, chunk, bins, pairs);
+}
+__global__ __launch_bounds__(kBlock, 8) void k_es_bin6(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, EsRun st, int64_t chunk,
+                                                       EsBins bins, uint32_t* __restrict__ pairs)
+{
+    es_bin_tile<6>(src, dst, st, chunk, bins, pairs);
+}
+__global__ __launch_bounds__(kBlock, 8) void k_es_bin8(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, EsRun st, int64_t chunk,
+                                                       EsBins bins, uint32_t* __restrict__ pairs)
+{
+    es_bin_tile<8>(src, dst, st, chunk, bins, pairs);
+}
+
+// ---- labels looked up in LDS --------------------------------------------------------------------------------
+//
+// Where the labels outgrow the L2s, look-ups run at 59 G/s (28 MB, 111M nodes) and each reads a line of 128 bytes.  Then an edge
+// end asks for the other's label: k_es_ask sorts the asks (asked node, asking node) by ranges of asked nodes, and
+// k_es_answer, which has a range's labels in LDS, sorts the answers into the bins.  32M ends of 111M nodes: 129 + 175 us instead of k_es_bin's 544, and the bins
+// can be a block's nodes each (848 bins that four blocks read were as many as k_es_bin could serve: 700 us with 3392).
+
+// The ranges' numbers class by class: 0, 8, 16, ..., 1, 9, ...  (as for the tiles of edges, a class's tiles go to one XCD)
+__device__ __forceinline__ uint32_t es_ask_range(const EsBins& ranges, uint32_t i)
+{
+    const uint32_t each = ranges.nb / ranges.classes;
+    return i % each * ranges.classes + i / each;
+}
+// A tile is kAskTile asks of a range or fewer; first[chunk][i]: tiles of the ranges before the i-th (one workgroup per chunk; the
+// ranges' starts are known, the last one ends where the bins do).
+constexpr int kAskTile = 16384;
+__global__ __launch_bounds__(kBlock) void k_es_ask_tiles(EsBins ranges, const uint32_t* __restrict__ totals, uint32_t* first)
+{
+    __shared__ uint32_t wsum[kWaves];
+    const uint32_t own = ranges.nb / kBlock, at = threadIdx.x * own;
+    const uint32_t* row = ranges.ends + (size_t)blockIdx.x * ranges.nb * ranges.classes;
+    auto tiles = [&](uint32_t i) {
+        const uint32_t range = es_ask_range(ranges, i);
+        const uint32_t end = range + 1u < ranges.nb ? row[range + 1u] : totals[blockIdx.x];
+        return (end - row[range] + kAskTile - 1u) / kAskTile;
+    };
+    uint32_t sum = 0, total;
+    for (uint32_t i = 0; i < own; ++i) sum += tiles(at + i);
+    uint32_t before = es_block_exclusive(sum, wsum, &total);
+    uint32_t* out = first + (size_t)blockIdx.x * (ranges.nb + 1u);
+    for (uint32_t i = 0; i < own; ++i) {
+        out[at + i] = before;
+        before += tiles(at + i);
+    }
+    if (threadIdx.x == kBlock - 1) out[ranges.nb] = total;
+}
+
+// The ends' asks sorted by range: tile after tile of a class, the next one's edges on their way while a tile is written.
+// (A word per range and tile is moved on in memory, neighbouring words by a wave: with the classes' words next to each other those
+// atomics, a line each, were most of the time here and in k_es_answer, which took 451 us for 204 at 111M nodes.)
+constexpr int kAskPer = 4, kAskEdges = kAskPer * kBlock;
+__global__ __launch_bounds__(kBlock, 8) void k_es_ask(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                                                      EsRun st, int64_t chunk, EsBins ranges, uint2* __restrict__ asks)
+{
+    extern __shared__ uint32_t items[];            // 2 * kAskEdges of two words, then at[], start[]
+    __shared__ uint32_t wsum[kWaves];
+    uint2* sorted = reinterpret_cast<uint2*>(items);
+    uint32_t* at = items + 4 * kAskEdges;
+    uint16_t* start = reinterpret_cast<uint16_t*>(at + ranges.nb);
+    const EsGroup g = st.groups[blockIdx.y];
+    int64_t lo, hi;
+    es_chunk(g, chunk, lo, hi);
+    lo += (int64_t)blockIdx.x * kAskEdges;
+    const int tid = threadIdx.x, cb = ranges.cb;
+    constexpr uint32_t kNothing = 0xFFFFFFFFu;
+    uint32_t* const cursors = ranges.ends + ((size_t)chunk * ranges.classes + blockIdx.x % (unsigned)ranges.classes) * ranges.nb;
+    uint32_t a[kAskPer], b[kAskPer];
+    auto request = [&] {
+#pragma unroll
+        for (int u = 0; u < kAskPer; ++u) {
+            const int64_t e = lo + u * kBlock + tid;
+            a[u] = e < hi ? g.node0 + (uint32_t)src[e] : kNothing;
+            b[u] = e < hi ? g.node0 + (uint32_t)dst[e] : kNothing;
+        }
+    };
+    request();
+    for (; lo < hi;) {
+        for (uint32_t i = tid; i < ranges.nb; i += kBlock) at[i] = 0u;
+        __syncthreads();
+        uint32_t ra[kAskPer], rb[kAskPer];         // rank among the tile's asks of the same range
+#pragma unroll
+        for (int u = 0; u < kAskPer; ++u) {
+            if (a[u] == kNothing) continue;
+            ra[u] = atomicAdd(&at[a[u] >> cb], 1u);
+            if (a[u] != b[u]) rb[u] = atomicAdd(&at[b[u] >> cb], 1u);
+        }
+        __syncthreads();
+        const uint32_t total = es_sort_scan(at, start, ranges, cursors, wsum);
+#pragma unroll
+        for (int u = 0; u < kAskPer; ++u) {
+            if (a[u] == kNothing) continue;
+            sorted[start[a[u] >> cb] + ra[u]] = make_uint2(a[u], b[u]);
+            if (a[u] != b[u]) sorted[start[b[u] >> cb] + rb[u]] = make_uint2(b[u], a[u]);
+        }
+        lo += (int64_t)gridDim.x * kAskEdges;
+        request();
+        __syncthreads();
+        for (uint32_t i = tid; i < total; i += kBlock) {
+            const uint2 x = sorted[i];
+            asks[at[x.x >> cb] + i] = x;
+        }
+        __syncthreads();
+    }
+}
+
+// A workgroup answers a tile of a range's asks after another, the next one's asks on their way while it writes.
+__global__ __launch_bounds__(kBlock) void k_es_answer(EsRun st, int64_t chunk, EsBins ranges, const uint32_t* __restrict__ first,
+                                                      const uint2* __restrict__ asks, EsBins bins, uint32_t nodes, uint32_t* __restrict__ pairs)
+{
+    extern __shared__ uint32_t items[];            // kAskTile, then the range's labels, at[], start[]
+    __shared__ uint32_t wsum[kWaves];
+    constexpr int PER = kAskTile / kBlock;
+    const int tid = threadIdx.x, lane = tid & 63, cb = bins.cb;
+    const uint32_t words = 1u << (ranges.cb - 5);
+    u64* labels = reinterpret_cast<u64*>(items + kAskTile);
+    uint32_t* at = items + kAskTile + 2 * words;
+    uint16_t* start = reinterpret_cast<uint16_t*>(at + bins.nb);
+    const uint32_t own = blockIdx.x % (unsigned)ranges.classes, each = ranges.nb / ranges.classes;
+    const uint32_t* row = first + (size_t)chunk * (ranges.nb + 1) + own * each;
+    const uint32_t tile1 = row[each], step = gridDim.x / (unsigned)ranges.classes;
+    uint32_t* const cursors = bins.ends + ((size_t)chunk * bins.classes + own) * bins.nb;
+    uint32_t tile = row[0] + blockIdx.x / (unsigned)ranges.classes, range = 0, p0 = 0, count = 0;
+    uint2 ask[PER];
+    auto request = [&] {                           // the tile's place, and its asks on their way
+        if (tile >= tile1) return;
+        uint32_t i = 0;                            // the last range that begins at the tile or before it
+        for (uint32_t j = 0; j < each; j += 64) i += (uint32_t)__popcll(__ballot(j + lane < each && row[j + lane] <= tile));
+        --i;
+        const uint32_t t0 = row[i], tiles = row[i + 1u] - t0;
+        range = es_ask_range(ranges, own * each + i);
+        uint32_t p1;
+        ranges.range(chunk, range, p0, p1);
+        const uint32_t per = (p1 - p0 + tiles - 1u) / tiles;       // (kAskTile or fewer)
+        p0 += (tile - t0) * per;
+        count = p0 >= p1 ? 0u : p1 - p0 < per ? p1 - p0 : per;
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if ((uint32_t)(u * kBlock + tid) < count) ask[u] = asks[p0 + u * kBlock + tid];
+    };
+    request();
+    for (; tile < tile1;) {
+        const ulonglong2* from = reinterpret_cast<const ulonglong2*>(st.Lw + (size_t)range * words);
+        const uint32_t held = nodes / 32u - range * words < words ? nodes / 32u - range * words : words;       // (a range asked for begins inside)
+        for (uint32_t i = tid; i < held / 2; i += kBlock) reinterpret_cast<ulonglong2*>(labels)[i] = from[i];
+        for (uint32_t i = tid; i < bins.nb; i += kBlock) at[i] = 0u;
+        __syncthreads();
+        uint32_t rank[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            if ((uint32_t)(u * kBlock + tid) >= count) continue;
+            const uint32_t asked = ask[u].x & ((1u << ranges.cb) - 1u);
+            ask[u].x = es_label(labels[asked >> 5], asked);
+            rank[u] = atomicAdd(&at[ask[u].y >> cb], 1u);
+        }
+        __syncthreads();
+        const uint32_t total = es_sort_scan(at, start, bins, cursors, wsum);
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            if ((uint32_t)(u * kBlock + tid) >= count) continue;
+            const uint32_t node = ask[u].y, bin = node >> cb;
+            items[start[bin] + rank[u]] = (node & ((1u << cb) - 1u)) | ask[u].x << cb | bin << (cb + 2);
+        }
+        tile += step;
+        request();
+        __syncthreads();
+        for (uint32_t i = tid; i < total; i += kBlock) {
+            const uint32_t x = items[i];
+            pairs[at[x >> (cb + 2)] + i] = x & ((1u << (cb + 2)) - 1u);
+        }
+        __syncthreads();
     }
 }
 
@@ -462,7 +758,7 @@ __device__ __forceinline__ void es_score_words(const EsRun& st, uint32_t word0, 
             }
             st.est[(size_t)(word0 + i0 + u) * 64 + lane] = make_double2(nbrs0, nbrs1);
             if (!first) {
-                const int t = es_assign(nbrs0, nbrs1, S0 - (old[u] == 0u), S1 - (old[u] == 1u), P);
+                const int t = es_assign((nbrs1 > nbrs0) - (nbrs0 > nbrs1), S0 - (old[u] == 0u), S1 - (old[u] == 1u), P);
                 if ((uint32_t)t != old[u]) want = t;
             }
         }
@@ -494,31 +790,45 @@ __device__ __forceinline__ void es_store_movers(const EsRun& st, uint32_t (&m)[4
 // order of degree put a quarter of all ends in one bin, whose four blocks each walked 8M pairs twice: a chunk of 16M
 // edges of 111M nodes took 4.7 ms in k_es_score_bins, 0.75 on permuted ids.
 constexpr uint32_t kCrowdPiece = 65535;            // pairs per turn: the two counts of a node fit 16 bits each
-__global__ __launch_bounds__(kBlock) void k_es_crowd(int64_t chunk, int cb, uint32_t bn, uint32_t nblocks,
-                                                     const uint32_t* __restrict__ table, const uint32_t* __restrict__ pairs, EsCrowd crowd)
+__global__ __launch_bounds__(kBlock) void k_es_crowd(int64_t chunk, EsBins tab, uint32_t bn, uint32_t nblocks,
+                                                     const uint32_t* __restrict__ pairs, EsCrowd crowd)
 {
     extern __shared__ uint32_t cnt[];              // bn words, then as many bits
-    __shared__ uint32_t wsum[kWaves], bin_of[kBins], first[kBins + 1];
+    __shared__ uint32_t wsum[kWaves], first[kBins + 1];
+    __shared__ uint16_t bin_of[kBins];
     uint32_t* seen = cnt + bn;
-    const int tid = threadIdx.x;
-    const uint32_t* row = table + (size_t)chunk * kBinTableStride;
+    const int tid = threadIdx.x, cb = tab.cb;
     const uint32_t bins = crowd.bins[chunk], blocks = (1u << cb) / bn;
-    const uint32_t place = crowd.place[(size_t)chunk * kBins + tid];
-    if (place) bin_of[place - 1u] = (uint32_t)tid;
+    const uint32_t own = tab.nb / kBlock;          // neighbouring places of a thread
+    for (uint32_t i = tid; i < tab.nb; i += kBlock) {
+        const uint32_t place = crowd.place[(size_t)chunk * tab.nb + i];
+        if (place) bin_of[place - 1u] = (uint16_t)i;
+    }
     __syncthreads();
-    const uint32_t bin_t = (uint32_t)tid < bins ? bin_of[tid] : 0u;
-    const uint32_t items = (uint32_t)tid < bins ? (row[bin_t + 1u] - row[bin_t] + kCrowdPiece - 1u) / kCrowdPiece * blocks : 0u;
-    const uint32_t excl = es_block_exclusive(items, wsum);
-    first[tid] = excl;
-    if (tid == kBins - 1) first[kBins] = excl + items;
+    auto turns = [&](uint32_t at) {
+        if (at >= bins) return 0u;
+        uint32_t p0, p1;
+        tab.range(chunk, bin_of[at], p0, p1);
+        return (p1 - p0 + kCrowdPiece - 1u) / kCrowdPiece * blocks;
+    };
+    uint32_t items = 0;
+    for (uint32_t i = 0; i < own; ++i) items += turns(tid * own + i);
+    uint32_t excl = es_block_exclusive(items, wsum);
+    for (uint32_t i = 0; i < own; ++i) {
+        first[tid * own + i] = excl;
+        excl += turns(tid * own + i);
+    }
+    if (tid == kBlock - 1) first[tab.nb] = excl;
     __syncthreads();
     uint32_t at = 0;                               // the crowded bin of the item
-    for (uint32_t item = blockIdx.x; item < first[kBins]; item += gridDim.x) {
+    for (uint32_t item = blockIdx.x; item < first[tab.nb]; item += gridDim.x) {
         while (item >= first[at + 1u]) ++at;
         const uint32_t bin = bin_of[at], part = item - first[at], low = part % blocks * bn;
         if (((bin << cb) + low) / bn >= nblocks) continue;                   // (past the last block; the same for all threads)
-        const uint32_t p0 = row[bin] + part / blocks * kCrowdPiece;
-        const uint32_t p1 = row[bin + 1u] - p0 < kCrowdPiece ? row[bin + 1u] : p0 + kCrowdPiece;
+        uint32_t p0, p1;
+        tab.range(chunk, bin, p0, p1);
+        p0 += part / blocks * kCrowdPiece;
+        if (p1 - p0 > kCrowdPiece) p1 = p0 + kCrowdPiece;
         for (uint32_t i = tid; i < bn; i += kBlock) cnt[i] = 0u;
         for (uint32_t i = tid; i < bn / 32; i += kBlock) seen[i] = 0u;
         __syncthreads();
@@ -587,143 +897,26 @@ __global__ __launch_bounds__(kBlock) void k_es_score(EsRun st, int par, int firs
     es_store_movers(st, movers, blockIdx.x);
 }
 
-// LDS of k_es_score_bins after its counts and their bits: per wave a list of what to score, per word of nodes two of movers
-constexpr int kQuadTurn = 16 * kTurn;              // groups of four nodes a wave scores at a time
-constexpr int kQuadRoom = 2 * kQuadTurn;           // ... and has room for: those left over, and those of kTurn more words
-inline size_t es_bins_lds(int64_t bn) { return (size_t)bn * 4 + (size_t)bn / 8 + (size_t)kWaves * kQuadRoom * 2 + (size_t)bn / 64 * 16; }
+// LDS of k_es_score_bins: two words per 32 nodes, and six bytes for each of `room` nodes of the chunk or, where a count is kept
+// for every node, four and a bit per node
+inline size_t es_bins_lds(int64_t bn, int64_t room) { return (size_t)bn / 4 + (size_t)room * 6; }
 
-// a wave's LDS writes are seen by its other lanes
-__device__ __forceinline__ void es_wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Alg. 1 for the nodes of kQuadTurn groups of four or fewer, a lane each and kTurn of them at once: blend the stored
-// estimate with the fresh counts when the node has a label, store the estimate, ask `assign` for a partition.  quads: the groups'
-// places in the block (node0: its first node); counts(rel, h0, h1): whether the node belongs to the chunk, and its counts;
-// those that want to move get their bits in mv0 and mv1 (LDS).  (The stored estimate is asked for whether or not the node has a
-// label: the load need not wait for the label's.)
-template <typename Counts>
-__device__ __forceinline__ void es_score_quads(const EsRun& st, uint32_t node0, const uint16_t* quads, uint32_t count, Counts&& counts,
-                                               int first, int fixed, long long P, long long S0, long long S1, uint32_t* mv0, uint32_t* mv1)
-{
-    const int lane = threadIdx.x & 63;
-    uint32_t rel[kTurn], h0[kTurn], h1[kTurn];
-    u64 word[kTurn];
-    double2 est[kTurn];
-    bool on[kTurn];
+// The pairs [p0, p1), four at a time from the last whole four before them on (the list's end is padded), U fours per lane
+// and turn, the next turn's on their way.
+struct EsPairs {
+    static constexpr int U = 2;
+    const uint4* fours;
+    uint32_t p0, p1, q1, q;
+    uint4 x[U];
+    __device__ __forceinline__ void request()
+    {
 #pragma unroll
-    for (int u = 0; u < kTurn; ++u) {
-        const uint32_t at = (uint32_t)(u * 16 + (lane >> 2));
-        rel[u] = at < count ? quads[at] * 4u + (lane & 3) : 0u;
-        on[u] = at < count && counts(rel[u], h0[u], h1[u]);
-        if (on[u]) word[u] = st.Lw[(node0 + rel[u]) >> 5];
-        if (on[u] && !first && !fixed) est[u] = st.est[node0 + rel[u]];
+        for (int u = 0; u < U; ++u)
+            if (q + u * kBlock < q1) x[u] = fours[q + u * kBlock];
     }
-#pragma unroll
-    for (int u = 0; u < kTurn; ++u) {
-        if (!on[u]) continue;
-        const uint32_t old = es_label(word[u], rel[u]);            // (a block starts at a whole word)
-        if (fixed && !first && old != kNone) continue;
-        double nbrs0 = (double)h0[u], nbrs1 = (double)h1[u];
-        if (!first && !fixed && old != kNone) {
-            nbrs0 = (est[u].x + nbrs0) * 0.5;
-            nbrs1 = (est[u].y + nbrs1) * 0.5;
-        }
-        st.est[node0 + rel[u]] = make_double2(nbrs0, nbrs1);
-        if (first) continue;
-        const int t = es_assign(nbrs0, nbrs1, S0 - (old == 0u), S1 - (old == 1u), P);
-        if ((uint32_t)t != old) atomicOr(&(t ? mv1 : mv0)[rel[u] >> 5], 1u << (rel[u] & 31u));
-    }
-}
-
-// cnt_nbrs, second half, from the binned pairs: a block counts the pairs of its bin that are its own in LDS (the
-// blocks of one bin all read it, on one XCD, whose L2 then holds it), then scores its nodes.  A bin of at most 65,535
-// pairs cannot overflow 16 bits: the two counts of a node share a word; a larger one is counted in two rounds
-// of half the nodes with 32 bits each.  `seen`: nodes whose other ends have no label.
-// One node in eleven belongs to a chunk of one per cent: a wave lists the groups of four nodes with such a node among them and
-// scores those, a lane per node.  Word by word, most lanes idle, 300 of 587 us went to issuing instructions (111M nodes, 32M
-// edge ends); with lists of the nodes themselves 581 us, of the groups 556 (14M nodes, 4M ends: 69, 53.7 and 52.5).  Of the
-// 556 the estimates take 270, lines of 128 bytes with one node of the chunk in most, and the pairs, which four blocks read, 210.
-__global__ __launch_bounds__(kBlock) void k_es_score_bins(EsRun st, int par, int first, int fixed, int64_t chunk, int cb,
-                                                          uint32_t nblocks, const uint32_t* __restrict__ table,
-                                                          const uint32_t* __restrict__ pairs, EsCrowd crowd)
-{
-    extern __shared__ uint32_t cnt[];              // kBlock * wpw words, then as many bits
-    // contiguous ranges of blocks per XCD (workgroups go to the XCDs in turn)
-    const uint32_t per = gridDim.x >> 3;
-    const uint32_t block = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
-    if (block >= nblocks) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t bn = (uint32_t)(kBlock * st.wpw);
-    uint32_t* seen = cnt + bn;
-    const uint32_t bin = (block * bn) >> cb, in_bin = (block * bn) & ((1u << cb) - 1u);
-    const uint32_t* row = table + (size_t)chunk * kBinTableStride + bin;
-    const uint32_t p0 = row[0], p1 = row[1];
-    const uint32_t place = crowd.place[(size_t)chunk * kBins + bin];
-    if (place) {                                   // counted by k_es_crowd
-        const uint32_t gi = st.blk_group[block];
-        const long long P = st.groups[gi].P;
-        const long long S0 = (long long)st.S[2 * (par * st.ngroups + gi)], S1 = (long long)st.S[2 * (par * st.ngroups + gi) + 1];
-        u64* hc = crowd.hc + (((size_t)place - 1) << cb) + in_bin;
-        uint32_t* was_seen = crowd.seen + ((((size_t)place - 1) << cb) + in_bin) / 32;
-        const uint32_t word0 = block * (bn / 64) + wave * st.wpw;
-        const EsLabels labels = lane < st.wpw ? es_load_labels(st, word0 + lane) : EsLabels{0ull, 0ull};
-        u64 out0 = 0ull, out1 = 0ull;
-        for (int i0 = 0; i0 < st.wpw; i0 += kTurn) {
-            u64 h[kTurn];
-            uint32_t bits[kTurn], h0[kTurn], h1[kTurn];
-            bool on[kTurn];
-#pragma unroll
-            for (int u = 0; u < kTurn; ++u) {
-                const uint32_t rel = (uint32_t)(wave * st.wpw + i0 + u) * 64u + lane;
-                h[u] = i0 + u < st.wpw ? hc[rel] : 0ull;
-                bits[u] = i0 + u < st.wpw ? was_seen[rel >> 5] : 0u;
-            }
-#pragma unroll
-            for (int u = 0; u < kTurn; ++u) {
-                const uint32_t rel = (uint32_t)(wave * st.wpw + i0 + u) * 64u + lane;
-                on[u] = h[u] != 0ull || ((bits[u] >> (rel & 31u)) & 1u);
-                if (h[u]) hc[rel] = 0ull;
-                if (bits[u] && (rel & 31u) == 0u) was_seen[rel >> 5] = 0u;
-                h0[u] = (uint32_t)h[u];
-                h1[u] = (uint32_t)(h[u] >> 32);
-            }
-            es_score_words(st, word0, i0, labels, on, h0, h1, first, fixed, P, S0, S1, out0, out1);
-        }
-        uint32_t movers[4] = {0u, 0u, 0u, 0u};
-        if (lane < st.wpw) es_store_words(st, word0 + lane, out0, out1, labels, movers);
-        es_store_movers(st, movers, block);
-        return;
-    }
-    const bool narrow = p1 - p0 <= 65535u;
-    const int rounds = narrow ? 1 : 2;
-    const uint32_t sub = bn / rounds;              // nodes per round
-    const int nw = st.wpw / rounds;                // words per wave and round
-    uint16_t* quads = reinterpret_cast<uint16_t*>(seen + bn / 32) + wave * kQuadRoom;
-    uint32_t* mv0 = seen + bn / 32 + kWaves * kQuadRoom / 2;
-    uint32_t* mv1 = mv0 + bn / 32;
-    uint32_t movers[4] = {0u, 0u, 0u, 0u};
-    for (int round = 0; round < rounds; ++round) {
-        const uint32_t low = in_bin + round * sub, node0 = block * bn + round * sub, word0 = node0 / 64 + wave * nw;
-        // the pairs four at a time from the last whole four before them on (the list's end is padded), the next turn's on their way
-        constexpr int U = 3;
-        const uint4* fours = reinterpret_cast<const uint4*>(pairs);
-        const uint32_t q1 = (p1 + 3u) >> 2;
-        uint32_t q = (p0 >> 2) + tid;
-        uint4 x[U];
-        auto request = [&] {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (q + u * kBlock < q1) x[u] = fours[q + u * kBlock];
-        };
-        request();
-        __syncthreads();
-        for (uint32_t i = tid; i < bn / 4; i += kBlock) reinterpret_cast<uint4*>(cnt)[i] = make_uint4(0u, 0u, 0u, 0u);
-        for (uint32_t i = tid; i < bn / 32; i += kBlock) seen[i] = mv0[i] = mv1[i] = 0u;
-        __syncthreads();
+    __device__ __forceinline__ void start() { q = (p0 >> 2) + threadIdx.x; request(); }
+    template <typename F> __device__ __forceinline__ void each(F&& f)
+    {
         for (; q < q1;) {
             uint4 y[U];
             const uint32_t at = q;
@@ -733,57 +926,183 @@ __global__ __launch_bounds__(kBlock) void k_es_score_bins(EsRun st, int par, int
             request();
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                if (at + u * kBlock >= q1) continue;
-                const uint32_t pair[4] = {y[u].x, y[u].y, y[u].z, y[u].w};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint32_t rel = (pair[i] & ((1u << cb) - 1u)) - low, code = pair[i] >> cb;
-                    if (4u * (at + u * kBlock) + i - p0 >= p1 - p0 || rel >= sub) continue;
-                    if (code >= 2u) atomicOr(&seen[rel >> 5], 1u << (rel & 31u));
-                    else if (narrow) atomicAdd(&cnt[rel], code ? 65536u : 1u);
-                    else atomicAdd(&cnt[2u * rel + code], 1u);
+                const uint32_t i = 4u * (at + u * kBlock);
+                if (i >= p0 && i + 4u <= p1) {
+                    f(y[u].x); f(y[u].y); f(y[u].z); f(y[u].w);
+                } else {                           // the list's ends
+                    if (i - p0 < p1 - p0) f(y[u].x);
+                    if (i + 1u - p0 < p1 - p0) f(y[u].y);
+                    if (i + 2u - p0 < p1 - p0) f(y[u].z);
+                    if (i + 3u - p0 < p1 - p0) f(y[u].w);
                 }
             }
         }
-        __syncthreads();
-        auto counts = [&](uint32_t rel, uint32_t& h0, uint32_t& h1) {
-            if (narrow) {
-                h0 = cnt[rel] & 0xFFFFu;
-                h1 = cnt[rel] >> 16;
-            } else {
-                h0 = cnt[2u * rel];
-                h1 = cnt[2u * rel + 1u];
-            }
-            return (h0 | h1) != 0u || ((seen[rel >> 5] >> (rel & 31u)) & 1u);
-        };
-        const uint32_t gi = st.blk_group[block];
-        const long long P = st.groups[gi].P, S0 = (long long)st.S[2 * (par * st.ngroups + gi)], S1 = (long long)st.S[2 * (par * st.ngroups + gi) + 1];
-        // a lane looks at four nodes of a word, 16 lanes at a word
-        uint32_t listed = 0;
-        for (int i0 = 0; i0 < nw; i0 += kTurn) {                   // (nw is a multiple of kTurn)
-            const uint32_t quad = (uint32_t)(wave * nw + i0) * 16u + lane;
-            const uint4* c4 = reinterpret_cast<const uint4*>(cnt);
-            uint4 c = narrow ? c4[quad] : c4[2u * quad];
-            uint32_t any = c.x | c.y | c.z | c.w | ((seen[quad >> 3] >> ((quad & 7u) * 4u)) & 15u);
-            if (!narrow) { c = c4[2u * quad + 1u]; any |= c.x | c.y | c.z | c.w; }
-            const u64 on = __ballot(any != 0u);
-            if (any) quads[listed + __builtin_amdgcn_mbcnt_hi((uint32_t)(on >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)on, 0u))] = (uint16_t)quad;
-            listed += (uint32_t)__popcll(on);
-            es_wave_sync();
-            const bool last = i0 + kTurn >= nw;
-            while (listed >= (uint32_t)kQuadTurn || (last && listed > 0)) {           // the list's end first: what is left stays in place
-                const uint32_t take = listed < (uint32_t)kQuadTurn ? listed : (uint32_t)kQuadTurn;
-                listed -= take;
-                es_score_quads(st, node0, quads + listed, take, counts, first, fixed, P, S0, S1, mv0, mv1);
-            }
-            es_wave_sync();
-        }
-        const EsLabels labels = lane < nw ? es_load_labels(st, word0 + lane) : EsLabels{0ull, 0ull};
-        if (lane < nw)
-            es_store_words(st, word0 + lane, reinterpret_cast<const u64*>(mv0)[wave * nw + lane], reinterpret_cast<const u64*>(mv1)[wave * nw + lane],
-                           labels, movers);
     }
+};
+
+// cnt_nbrs, second half, from the binned pairs: a block counts the pairs of its bin that are its own in LDS, then scores its nodes.
+// One node in eight belongs to a chunk of one per cent: a bitmap of the chunk's nodes, ranked, gives each of them a place in a
+// list and in the counts, so that the LDS holds six bytes for a node of the chunk instead of four for every node, two workgroups
+// share a CU, and a lane has a node of the chunk each time.  Where chunks hold most nodes (`sparse` is not set), in a bin with more of them
+// than there is `room` for, and in one of more than 65,535 pairs (a count then takes 32 bits), every node has its count (`direct`), in
+// rounds of as many nodes as fit; those of a crowded bin come from memory (k_es_crowd).
+// What bounds it is the estimates: the 64-byte pieces that hold one of the chunk's nodes are written (8 bytes per node: 450 MB at 111M
+// nodes and 32M ends, 14M nodes of the chunk), and 128-byte lines read (1 GB).  With doubles, 16 bytes per node, stores alone were 225 us of 555; now 410.
+// 14M nodes, 4M ends: 65 -> 42 us.  Nontemporal loads or stores of the estimates were slower, or no faster; four nodes per lane in flight spill.
+constexpr int kScoreTurn = 2;                      // nodes a lane has in flight
+__global__ __launch_bounds__(kBlock, 8) void k_es_score_bins(EsRun st, int par, int first, int fixed, int64_t chunk, EsBins tab,
+                                                             uint32_t nblocks, uint32_t room, int sparse,
+                                                             const uint32_t* __restrict__ pairs, EsCrowd crowd)
+{
+    extern __shared__ uint32_t bits[];             // list: the chunk's nodes among the block's
+    __shared__ uint32_t wsum[kWaves], wide;
+    // contiguous ranges of blocks per XCD (workgroups go to the XCDs in turn)
+    const uint32_t block = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (block >= nblocks) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, cb = tab.cb;
+    const uint32_t bn = (uint32_t)(kBlock * st.wpw), node0 = block * bn;
+    const uint32_t bin = node0 >> cb, in_bin = node0 & ((1u << cb) - 1u);
+    uint32_t p0, p1;
+    tab.range(chunk, bin, p0, p1);
+    const uint32_t place = crowd.place[(size_t)chunk * tab.nb + bin];                // not 0: counted by k_es_crowd
+    if (place) p1 = p0;
+    EsPairs list{reinterpret_cast<const uint4*>(pairs), p0, p1, (p1 + 3u) >> 2, 0u, {}};
+    list.start();
+    const uint32_t gi = st.blk_group[block];
+    const long long P = st.groups[gi].P, S0 = (long long)st.S[2 * (par * st.ngroups + gi)], S1 = (long long)st.S[2 * (par * st.ngroups + gi) + 1];
+    // what `assign` answers, by label and lean: bit 3 * label + lean + 1
+    const uint32_t answers = (uint32_t)__ballot(lane < 9 && es_assign(lane % 3 - 1, S0 - (lane < 3), S1 - (lane >= 3 && lane < 6), P));
+    const uint32_t words = bn / 32;
+    uint32_t *mv0 = bits, *mv1 = bits + words, *base = mv1;                          // base: the chunk's nodes before a word
+    uint32_t* cnt = bits + 2 * words;
+    uint16_t* nodes = reinterpret_cast<uint16_t*>(cnt + room);
+    if (tid == 0) wide = st.wide[block];
+
+    // counts of `count` nodes from `low` on (or, listed, of those in nodes[]) are there: their scores
+    auto score = [&](uint32_t count, uint32_t low, bool listed, bool narrow, const uint32_t* seen) {
+        for (uint32_t i0 = tid; i0 < count; i0 += kBlock * kScoreTurn) {
+            uint32_t rel[kScoreTurn], h0[kScoreTurn], h1[kScoreTurn], old[kScoreTurn];
+            uint2 est[kScoreTurn];
+            bool on[kScoreTurn];
+#pragma unroll
+            for (int u = 0; u < kScoreTurn; ++u) {
+                const uint32_t i = i0 + u * kBlock;
+                on[u] = i < count;
+                const uint32_t at = on[u] ? i : 0u;
+                rel[u] = listed ? nodes[at] : low + at;
+                if (narrow) {
+                    h0[u] = cnt[at] & 0xFFFFu;
+                    h1[u] = cnt[at] >> 16;
+                } else {
+                    h0[u] = cnt[2u * at];
+                    h1[u] = cnt[2u * at + 1u];
+                }
+                if (!listed) on[u] &= (h0[u] | h1[u]) != 0u || ((seen[at >> 5] >> (at & 31u)) & 1u);
+                est[u] = make_uint2(0u, 0u);
+                u64 labels = 0ull;
+                if (on[u]) labels = st.Lw[(node0 + rel[u]) >> 5];
+                if (on[u] && !first && !fixed) est[u] = reinterpret_cast<const uint2*>(st.packed)[node0 + rel[u]];
+                old[u] = es_label(labels, rel[u]);                 // (a block starts at a whole word)
+            }
+#pragma unroll
+            for (int u = 0; u < kScoreTurn; ++u) {
+                if (!on[u] || (fixed && !first && old[u] != kNone)) continue;
+                const bool blend = !first && !fixed && old[u] != kNone;
+                double2 doubles = make_double2(0.0, 0.0);
+                if (!blend) est[u] = make_uint2(0u, 0u);
+                if (es_is_wide(est[u])) doubles = st.est[es_wide_place(est[u])];
+                const int lean = es_blend_packed(st, node0 + rel[u], est[u], doubles, blend, h0[u], h1[u], node0, &wide);
+                if (first) continue;
+                const uint32_t t = answers >> (3u * old[u] + (uint32_t)(lean + 1)) & 1u;
+                if (t != old[u]) atomicOr(&(t ? mv1 : mv0)[rel[u] >> 5], 1u << (rel[u] & 31u));
+            }
+        }
+    };
+
+    bool direct = !sparse || place || p1 - p0 > 65535u;
+    if (!direct) {
+        for (uint32_t i = tid; i < words; i += kBlock) bits[i] = 0u;
+        __syncthreads();
+        list.each([&](uint32_t pair) {
+            const uint32_t rel = (pair & ((1u << cb) - 1u)) - in_bin;
+            if (rel < bn) atomicOr(&bits[rel >> 5], 1u << (rel & 31u));
+        });
+        list.start();
+        __syncthreads();
+        const uint32_t own = words > (uint32_t)kBlock ? words / kBlock : 1u;       // neighbouring words of a thread
+        uint32_t in_own = 0, total;
+        for (uint32_t i = 0; i < own; ++i) in_own += tid * own + i < words ? (uint32_t)__popc(bits[tid * own + i]) : 0u;
+        uint32_t before = es_block_exclusive(in_own, wsum, &total);
+        direct = total > room;
+        if (!direct) {
+            for (uint32_t i = 0; i < own && tid * own + i < words; ++i) {
+                const uint32_t w = tid * own + i;
+                base[w] = before;
+                for (uint32_t rest = bits[w]; rest; rest &= rest - 1u) nodes[before++] = (uint16_t)(w * 32u + (uint32_t)__builtin_ctz(rest));
+            }
+            for (uint32_t i = tid; i < total; i += kBlock) cnt[i] = 0u;
+            __syncthreads();
+            list.each([&](uint32_t pair) {
+                const uint32_t rel = (pair & ((1u << cb) - 1u)) - in_bin, code = pair >> cb;
+                if (rel >= bn) return;
+                const uint32_t at = base[rel >> 5] + (uint32_t)__popc(bits[rel >> 5] & ((1u << (rel & 31u)) - 1u));
+                if (code < 2u) atomicAdd(&cnt[at], code ? 65536u : 1u);
+            });
+            __syncthreads();
+            for (uint32_t i = tid; i < words; i += kBlock) mv0[i] = mv1[i] = 0u;
+            __syncthreads();
+            score(total, 0u, true, true, nullptr);
+        } else {
+            __syncthreads();                       // (bits are read no more)
+        }
+    }
+    if (direct) {
+        // counts for every node, in rounds of as many as there is room for
+        const bool narrow = !place && p1 - p0 <= 65535u;
+        uint32_t sub = bn;
+        while ((narrow ? sub : 2u * sub) + sub / 32u > room + room / 2u) sub /= 2u;
+        uint32_t* seen = cnt + (narrow ? sub : 2u * sub);
+        for (uint32_t i = tid; i < words; i += kBlock) mv0[i] = mv1[i] = 0u;
+        for (uint32_t low = 0; low < bn; low += sub) {
+            if (place) {                           // what is taken from memory is cleared there
+                u64* hc = crowd.hc + (((size_t)place - 1) << cb) + in_bin + low;
+                uint32_t* was_seen = crowd.seen + ((((size_t)place - 1) << cb) + in_bin + low) / 32;
+                for (uint32_t i = tid; i < sub; i += kBlock) {
+                    const u64 h = hc[i];
+                    cnt[2u * i] = (uint32_t)h;
+                    cnt[2u * i + 1u] = (uint32_t)(h >> 32);
+                    if (h) hc[i] = 0ull;
+                }
+                for (uint32_t i = tid; i < sub / 32u; i += kBlock) {
+                    seen[i] = was_seen[i];
+                    if (seen[i]) was_seen[i] = 0u;
+                }
+            } else {
+                list.start();
+                for (uint32_t i = tid; i < (narrow ? sub : 2u * sub) + sub / 32u; i += kBlock) cnt[i] = 0u;
+                __syncthreads();
+                list.each([&](uint32_t pair) {
+                    const uint32_t rel = (pair & ((1u << cb) - 1u)) - in_bin - low, code = pair >> cb;
+                    if (rel >= sub) return;
+                    if (code >= 2u) atomicOr(&seen[rel >> 5], 1u << (rel & 31u));
+                    else if (narrow) atomicAdd(&cnt[rel], code ? 65536u : 1u);
+                    else atomicAdd(&cnt[2u * rel + code], 1u);
+                });
+            }
+            __syncthreads();
+            score(sub, low, false, narrow, seen);
+            __syncthreads();
+        }
+    }
+    __syncthreads();
+    uint32_t movers[4] = {0u, 0u, 0u, 0u};
+    const int nw = st.wpw;
+    const uint32_t word0 = node0 / 64 + wave * nw;
+    if (lane < nw)
+        es_store_words(st, word0 + lane, reinterpret_cast<const u64*>(mv0)[wave * nw + lane], reinterpret_cast<const u64*>(mv1)[wave * nw + lane],
+                       es_load_labels(st, word0 + lane), movers);
     es_store_movers(st, movers, block);
+    if (tid == 0) st.wide[block] = wide;
 }
 
 // the first c set bits of x (c <= their number).  Between "none" and "all" there is one word per partition and chunk.
@@ -929,6 +1248,16 @@ __global__ __launch_bounds__(256) void k_es_expand(int64_t n, const u64* __restr
         parts[v] = l == kNone ? -1 : (int32_t)l;
     }
     if (sizes_out && blockIdx.x == 0 && threadIdx.x < 2) sizes_out[threadIdx.x] = (int64_t)S[threadIdx.x];
+}
+
+// nbr_counts_out of a binned run
+__global__ __launch_bounds__(256) void k_es_expand_packed(int64_t n, EsRun st, double2* out)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
+        const uint2 word = reinterpret_cast<const uint2*>(st.packed)[v];
+        out[v] = es_is_wide(word) ? st.est[es_wide_place(word)] : es_unpack(word);
+    }
 }
 
 // listed edges whose ends carry different labels (Sec. 1)
@@ -1197,19 +1526,31 @@ inline int grid_for(int64_t items, int block, int64_t cap)
 }
 
 // How a run is laid out.
-//   binned  from 4M nodes on (128 blocks; the counts in memory, 8 bytes per node, then far outgrow the L2), if a
-//           chunk's pairs take no more room than the estimates and the table of the chunks' bins stays small.  A
-//           block's counts fill a CU's LDS, 32,768 nodes: with 16,384 or 8,192 nodes and two or four workgroups per CU
-//           a whole run takes 126 or 145 ms instead of 119 at 111M nodes (every block of a bin reads all its pairs),
-//           12.1 or 13.0 instead of 11.6 at 14M (100 chunks each).
+//   binned  from 4M nodes on (the counts in memory, 8 bytes per node, then far outgrow the L2), if a chunk's pairs take no more
+//           room than the estimates and the table of the chunks' bins stays small.  A block is 32,768 nodes where a chunk has 0.34 ends per node or
+//           fewer, or half as many (4M nodes: 256 blocks); two of them fit a CU's LDS either way.  Up to 0.72 ends per node its nodes are listed, above that
+//           each has its count (14M nodes in chunks of 5 and 10 %: 5.8 and 5.8 ms so, 6.1 and 6.1 listed).  A bin is a block's nodes up to 67M or
+//           134M nodes, 4096 bins, several blocks' beyond.
+//   tile    8192 edges where that makes 512 tiles, or 4096 (14M nodes in groups, steps of 0.2 to 2M edges: bisection 39.7 -> 38.4 ms), and
+//           fewer where the bins' words leave less room in half a CU's LDS.
+//   asked   from 2^25 nodes on, or 2^24 and 2^24 ends in a step (100 chunks of 20M nodes: 14.4 ms asked, 13.3 looked up; 10 chunks 7.0 and 7.3; 50 of 27M
+//           12.7 and 12.7; 50 of 40M 18.0 and 21.2).
+//   classes 8 where a step has 256 tiles or more (14M nodes 9.1 ms, 9.6 with one; 111M 82 and 92), or one: the table is the smaller.
 //   blocks  otherwise kBlock * wpw nodes each: one word per wave up to a million nodes (the chip wants some 1024
 //           blocks), more words beyond it, so that a block can add up all blocks' counts itself.
 //   awpw    the admission's workgroups each add up all blocks' counts: as many words per wave as leave 256 workgroups or
 //           fewer, up to kMaxAdmitWords (262,144 nodes per workgroup: more than 256 of them from 67M nodes on) and while the
 //           groups' padding stays within their nodes (so with several groups there may be more from fewer nodes on).
 struct EsShape {
-    int wpw = 1, awpw = 1, cb = 0;
+    int wpw = 1, awpw = 1;
+    int cb = 0, classes = 1, tile = 0;     // binned: nodes of a bin (2^cb), classes of tiles, edges of a tile
+    uint32_t nb = 0;                       // ... and bins, rounded up
+    bool asked = false;                    // binned: labels are looked up in LDS
+    int ask_cb = 0, ask_tile = 0;          // ... nodes of a range (2^ask_cb)
+    uint32_t ask_nb = 0;                   // ... and ranges, rounded up
     bool binned = false;
+    bool sparse = false;                   // binned: a chunk's nodes are so few that a block lists them
+    int64_t room = 0;                      // ... and of how many it has room for the counts
     int64_t nodes = 0;                     // room for the state: the nodes and the groups' padding
     uint32_t crowd_limit = 0;              // binned: a bin of more pairs is crowded ...
     int64_t crowd_bins = 0;                // ... and most bins of a chunk that can be
@@ -1217,11 +1558,17 @@ struct EsShape {
     int64_t an() const { return (int64_t)kBlock * awpw; }
     int64_t padded(int64_t nv) const { return (nv + an() - 1) / an() * an(); }
 };
-constexpr int kBinWaveWords = 32;
+constexpr int kBinWaveWords = 16;
+constexpr int64_t kWideSparse = 340, kSparse = 720;
+constexpr int64_t kAskMinNodes = 1ll << 25, kAskMinEnds = 1ll << 24;
+constexpr int kAskBits = 17;                                 // 32 KB of labels
 constexpr int64_t kBinMinNodes = 1ll << 22;
 constexpr int64_t kBinMaxChunks = 8192;
 constexpr int64_t kCrowdMin = 65535, kCrowdMean = 8;         // a crowded bin: more pairs than these, and than so many bins hold on
                                                              // average (their counts then take a byte per node at most)
+constexpr int64_t kCrowdNodes = 32768;                       // a workgroup of k_es_crowd counts so many at a time
+constexpr int64_t kHalfLds = 80 * 1000;
+constexpr int kSortLds = 160000;
 constexpr unsigned kCrowdGrid = 512;                         // workgroups of k_es_crowd: one per CU at a time
 // n: nodes of the run; groups: most groups side by side; ends: of a chunk's edge ends over all groups; bins: false
 // where there was no memory for the pairs (the counts take 8 bytes per node, the pairs up to 16)
@@ -1237,11 +1584,27 @@ EsShape es_shape(int64_t n, int64_t groups, int64_t ends, int64_t chunks, bool b
         s.wpw = s.awpw = wpw;
         while (s.awpw < kMaxAdmitWords && n > s.an() * 256 && 2 * s.an() * groups <= n) s.awpw *= 2;
     };
-    waves(kBinWaveWords);
+    const int64_t per_mille = ends * 1000 / n;                 // ends of a chunk per thousand nodes
+    waves(per_mille <= kWideSparse && n >= 2 * kBinMinNodes ? 2 * kBinWaveWords : kBinWaveWords);
     if (bins && n >= kBinMinNodes && room() < (1ll << 30) && ends <= 4 * n && chunks <= kBinMaxChunks) {
         s.binned = true;
-        s.cb = 15;
-        while ((room() >> s.cb) >= kBins) ++s.cb;          // (at most 20)
+        s.cb = s.wpw == kBinWaveWords ? 14 : 15;
+        while ((room() >> s.cb) >= kBins) ++s.cb;          // (at most 18)
+        auto number = [&](int cb) { return (uint32_t)((room() >> cb) / kBlock + 1) * kBlock; };
+        s.nb = number(s.cb);
+        s.sparse = per_mille <= kSparse;
+        // (two workgroups share a CU; a bin with more nodes of the chunk than there is room for is counted node by node)
+        s.room = (kHalfLds - s.bn() / 4) / 6 / 64 * 64;
+        s.asked = n >= kAskMinNodes || (2 * n >= kAskMinNodes && ends >= kAskMinEnds);
+        if (s.asked) {
+            s.ask_cb = s.cb > kAskBits ? s.cb : kAskBits;
+            s.ask_nb = number(s.ask_cb);
+            s.tile = kAskEdges;
+        } else {
+            s.tile = ends / 2 >= 512 * kBinTile ? kBinTile : kBinTile / 2;
+            while (es_sort_lds(2 * s.tile, 4, s.nb) > kHalfLds) s.tile -= 2048;
+        }
+        s.classes = ends / 2 / s.tile >= 256 ? 8 : 1;
     } else {
         int wpw = 1;
         while (wpw < kMaxWaveWords && n > (int64_t)kBlock * wpw * 1024) wpw *= 2;
@@ -1262,9 +1625,11 @@ struct EsMemory {
     EsGroup* groups = nullptr;
     uint32_t* blk_group = nullptr;
     u64* hc = nullptr;
-    uint32_t *table = nullptr, *cursors = nullptr, *pairs = nullptr;
+    EsBins bins{}, ranges{};
+    uint32_t *pairs = nullptr, *totals = nullptr, *ask_tiles = nullptr;
+    uint2* asks = nullptr;
     EsCrowd crowd{};
-    size_t table_words = 0, bytes = 0;
+    size_t bytes = 0;
 
     void layout(uint8_t* ws, const EsShape& sh, int64_t ngroups, int64_t ends, int64_t chunks, double* est_out)
     {
@@ -1281,16 +1646,28 @@ struct EsMemory {
         take(blk_group, blocks);
         take(st.S, (size_t)ngroups * 4);
         take(st.Lw, (size_t)(nodes / 32));
-        if (est_out) st.est = (double2*)est_out;
+        if (est_out && !sh.binned) st.est = (double2*)est_out;
         else take(st.est, (size_t)nodes);
         take(st.mark, words); take(st.mv0, words); take(st.mv1, words); take(st.nw, words);
         take(st.bs, blocks);
         if (sh.binned) {
-            table_words = (size_t)chunks * kBinTableStride;
-            take(table, table_words);
-            take(cursors, (size_t)chunks * kBins);
+            bins.nb = sh.nb;
+            bins.cb = sh.cb;
+            bins.classes = sh.classes;
+            take(bins.ends, (size_t)chunks * sh.nb * bins.classes);
             take(pairs, (size_t)ends);
-            take(crowd.place, (size_t)chunks * kBins);
+            if (sh.asked) {
+                ranges.nb = sh.ask_nb;
+                ranges.cb = sh.ask_cb;
+                ranges.classes = sh.classes;
+                take(ranges.ends, (size_t)chunks * sh.ask_nb * sh.classes);
+                take(totals, (size_t)chunks);
+                take(ask_tiles, (size_t)chunks * (sh.ask_nb + 1));
+                take(asks, (size_t)ends);
+            }
+            take(st.packed, (size_t)nodes);
+            take(st.wide, blocks);
+            take(crowd.place, (size_t)chunks * sh.nb);
             take(crowd.bins, (size_t)chunks);
             take(crowd.hc, (size_t)sh.crowd_bins << sh.cb);
             take(crowd.seen, ((size_t)sh.crowd_bins << sh.cb) / 32);
@@ -1333,19 +1710,29 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
     }
     es_fill(stream, st.S, align256((size_t)ng * 32), 0ull);
     es_fill(stream, st.Lw, (size_t)nodes / 4, 0ull);
-    es_fill(stream, st.est, (size_t)est_nodes * 16, 0ull);
     es_fill(stream, st.mark, (size_t)nodes / 8, 0ull);
+    auto round = [&](int64_t grid) { return (grid + sh.classes - 1) / sh.classes * sh.classes; };
     std::vector<uint32_t> crowded;                             // per chunk: its crowded bins
     if (sh.binned) {
-        es_fill(stream, mem.table, align256((size_t)chunks * kBinTableStride * 4), 0ull);
+        es_fill(stream, mem.bins.ends, align256((size_t)chunks * sh.nb * mem.bins.classes * 4), 0ull);
+        if (sh.asked) es_fill(stream, mem.ranges.ends, align256((size_t)chunks * sh.ask_nb * sh.classes * 4), 0ull);
+        es_fill(stream, st.packed, (size_t)nodes * 8, 0ull);
+        es_fill(stream, st.wide, align256((size_t)blocks * 4), 0ull);
         // (workgroups of several tiles each: a workgroup's 1024 counts are added to the table once)
-        const int parts = grid_for((most + kBinTile - 1) / kBinTile, 4, 256);
-        hipLaunchKernelGGL(k_es_hist, dim3((unsigned)parts, ng, (unsigned)chunks), dim3(kBlock), 0, stream, src, dst, st, sh.cb, mem.table);
-        hipLaunchKernelGGL(k_es_hist_scan, dim3((unsigned)chunks), dim3(kBins), 0, stream, mem.table, mem.cursors, mem.crowd);
+        const int64_t parts = round(grid_for((most + sh.tile - 1) / sh.tile, 4, 256));
+        const size_t hist_lds = (size_t)sh.nb * 4 * (sh.asked ? sh.classes : 1);
+        if (hipFuncSetAttribute((const void*)k_es_hist, hipFuncAttributeMaxDynamicSharedMemorySize, kBins * 4 * 8) != hipSuccess) return GREM_ERR_HIP;
+        hipLaunchKernelGGL(k_es_hist, dim3((unsigned)parts, ng, (unsigned)chunks), dim3(kBlock), hist_lds, stream, src, dst, st, mem.bins, mem.ranges, sh.tile);
+        hipLaunchKernelGGL(k_es_hist_scan, dim3((unsigned)chunks), dim3(kBlock), 0, stream, mem.bins, mem.crowd, mem.totals);
+        if (sh.asked) {
+            hipLaunchKernelGGL(k_es_hist_scan, dim3((unsigned)chunks), dim3(kBlock), 0, stream, mem.ranges, EsCrowd{}, (uint32_t*)nullptr);
+            hipLaunchKernelGGL(k_es_ask_tiles, dim3((unsigned)chunks), dim3(kBlock), 0, stream, mem.ranges, (const uint32_t*)mem.totals, mem.ask_tiles);
+        }
         crowded.resize((size_t)chunks);
         if (hipMemcpyAsync(crowded.data(), mem.crowd.bins, (size_t)chunks * 4, hipMemcpyDeviceToHost, stream) != hipSuccess) return GREM_ERR_HIP;
     } else {
         es_fill(stream, mem.hc, (size_t)nodes * 8, 0ull);
+        es_fill(stream, st.est, (size_t)est_nodes * 16, 0ull);
     }
     hipLaunchKernelGGL(k_es_mark, dim3((unsigned)grid_for(most, kCountBlock, 8192), ng), dim3(kCountBlock), 0, stream, src, dst, st);
     hipLaunchKernelGGL(k_es_seed, dim3(blocks), dim3(kBlock), 0, stream, st, seed);
@@ -1358,12 +1745,16 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
             es_fill(stream, mem.crowd.seen, ((size_t)sh.crowd_bins << sh.cb) / 8, 0ull);
             break;
         }
-    const size_t crowd_lds = (size_t)sh.bn() * 4 + (size_t)sh.bn() / 8, bins_lds = es_bins_lds(sh.bn());
+    const int64_t crowd_bn = sh.bn() < kCrowdNodes ? sh.bn() : kCrowdNodes;
+    const size_t crowd_lds = (size_t)crowd_bn * 4 + (size_t)crowd_bn / 8, bins_lds = es_bins_lds(sh.bn(), sh.room);
+    const auto bin = sh.tile == 8192 ? k_es_bin8 : sh.tile == 6144 ? k_es_bin6 : k_es_bin;
     // (always what any run may need: the limit is the process's, and other threads' runs are of other sizes)
     if (sh.binned &&
-        (hipFuncSetAttribute((const void*)k_es_bin, hipFuncAttributeMaxDynamicSharedMemorySize, kBinTile * 8) != hipSuccess ||
-         hipFuncSetAttribute((const void*)k_es_crowd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)crowd_lds) != hipSuccess ||
-         hipFuncSetAttribute((const void*)k_es_score_bins, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bins_lds) != hipSuccess))
+        (hipFuncSetAttribute((const void*)k_es_ask, hipFuncAttributeMaxDynamicSharedMemorySize, kSortLds) != hipSuccess ||
+         hipFuncSetAttribute((const void*)k_es_answer, hipFuncAttributeMaxDynamicSharedMemorySize, kSortLds) != hipSuccess ||
+         hipFuncSetAttribute((const void*)bin, hipFuncAttributeMaxDynamicSharedMemorySize, kSortLds) != hipSuccess ||
+         hipFuncSetAttribute((const void*)k_es_crowd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kCrowdNodes * 4 + kCrowdNodes / 8)) != hipSuccess ||
+         hipFuncSetAttribute((const void*)k_es_score_bins, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kHalfLds) != hipSuccess))
         return GREM_ERR_HIP;
     bool profile;
     { std::lock_guard<std::mutex> lock(es_prof.mu); profile = es_prof.on; }
@@ -1386,20 +1777,27 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
             for (const EsGroup& g : groups)
                 if (i * g.c_size < g.m) es_prof.edges += g.m - i * g.c_size < g.c_size ? g.m - i * g.c_size : g.c_size;
         };
-        if (sh.binned)
-            hipLaunchKernelGGL(k_es_bin, dim3((unsigned)((most + kBinTile - 1) / kBinTile), ng), dim3(kBlock), kBinTile * 8, stream, src, dst,
-                               st, i, sh.cb, mem.cursors, mem.pairs);
+        if (sh.asked) {
+            // k_es_ask: two workgroups per CU; k_es_answer: one
+            const int64_t asks = round(std::min((most + sh.tile - 1) / sh.tile, std::max<int64_t>(512 / ng, 1)));
+            const int64_t answers = round(std::min<int64_t>((int64_t)ng * ((2 * most + kAskTile - 1) / kAskTile) + sh.ask_nb, 256));
+            hipLaunchKernelGGL(k_es_ask, dim3((unsigned)asks, ng), dim3(kBlock), es_sort_lds((size_t)kAskEdges * 2, 8, sh.ask_nb), stream, src, dst, st, i,
+                               mem.ranges, mem.asks);
+            hipLaunchKernelGGL(k_es_answer, dim3((unsigned)answers), dim3(kBlock), es_sort_lds(kAskTile, 4, sh.nb) + ((size_t)1 << sh.ask_cb) / 4, stream,
+                               st, i, mem.ranges, (const uint32_t*)mem.ask_tiles, (const uint2*)mem.asks, mem.bins, (uint32_t)nodes, mem.pairs);
+        } else if (sh.binned)
+            hipLaunchKernelGGL(bin, dim3((unsigned)round((most + sh.tile - 1) / sh.tile), ng), dim3(kBlock), es_sort_lds((size_t)sh.tile * 2, 4, sh.nb), stream, src, dst, st, i, mem.bins, mem.pairs);
         else
             hipLaunchKernelGGL(k_es_count, dim3((unsigned)grid_for(most, kCountBlock, 1 << 20), ng), dim3(kCountBlock), 0, stream, src, dst, st,
                                i, mem.hc);
         if (!sh.binned) timed();
         const int first = i == 0 ? 1 : 0;
         if (sh.binned && crowded[(size_t)i])
-            hipLaunchKernelGGL(k_es_crowd, dim3(kCrowdGrid), dim3(kBlock), crowd_lds, stream, i, sh.cb, (uint32_t)sh.bn(), blocks,
-                               (const uint32_t*)mem.table, (const uint32_t*)mem.pairs, mem.crowd);
+            hipLaunchKernelGGL(k_es_crowd, dim3(kCrowdGrid), dim3(kBlock), crowd_lds, stream, i, mem.bins, (uint32_t)crowd_bn, (uint32_t)(nodes / crowd_bn),
+                               (const uint32_t*)mem.pairs, mem.crowd);
         if (sh.binned)
-            hipLaunchKernelGGL(k_es_score_bins, dim3((blocks + 7) / 8 * 8), dim3(kBlock), bins_lds, stream, st, par, first, fixed, i, sh.cb,
-                               blocks, (const uint32_t*)mem.table, (const uint32_t*)mem.pairs, mem.crowd);
+            hipLaunchKernelGGL(k_es_score_bins, dim3((blocks + 7) / 8 * 8), dim3(kBlock), bins_lds, stream, st, par, first, fixed, i,
+                               mem.bins, blocks, (uint32_t)sh.room, sh.sparse ? 1 : 0, (const uint32_t*)mem.pairs, mem.crowd);
         else
             hipLaunchKernelGGL(k_es_score, dim3(blocks), dim3(kBlock), 0, stream, st, par, first, fixed, mem.hc);
         if (sh.binned) timed();
@@ -1455,6 +1853,8 @@ int es_bipartition(const int32_t* src, const int32_t* dst, int64_t m, int64_t n,
     if (rc == GREM_OK) {
         hipLaunchKernelGGL(k_es_expand, dim3(grid_for(n, 256, 16384)), dim3(256), 0, stream, n, (const u64*)mem.st.Lw, parts_out,
                            (const u64*)(mem.st.S + 2 * par), sizes_out);
+        if (sh.binned && nbr_counts_out)
+            hipLaunchKernelGGL(k_es_expand_packed, dim3(grid_for(n, 256, 16384)), dim3(256), 0, stream, n, mem.st, (double2*)nbr_counts_out);
         if (hipGetLastError() != hipSuccess) rc = GREM_ERR_HIP;
     } else {
         (void)hipGetLastError();
