@@ -13,6 +13,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -23,6 +25,7 @@
 #include <vector>
 
 #include "grem_kernels.hip.h"
+#include "grem_one.hip.h"
 #include "grem_plain.hip.h"
 #include "grem_twophase.hip.h"
 
@@ -45,6 +48,10 @@ constexpr int kTileGrid = 2048;            // ... and workgroups per chunk (1024
 // 100, 800 6.82 and 7.00, 1,600 4.23 and 4.23, 3,200 3.37 and 2.98; 128, 1,024 2.79 and 2.83, 2,048 1.87 and 1.85, 4,096 1.58 and 1.37.
 constexpr int kPackMinK = 32, kPackManyK = 128;
 constexpr size_t kPackMinBytes = 256u << 20;
+// One workgroup does the whole run (grem_one.hip.h) where a step's entries and one and a half times its counters are no more than this: it
+// takes some 1.3 us, 0.35 ns for an entry and 0.2 to 0.6 for a counter, the launches 12 to 15 us.  Calls in launches | so: 10,100 entries and 4,096
+// counters 387 | 223 us; 15,000 and 4,000 980 | 710; 15,750 and 8,400 607 | 525; 16,000 and 4,000 223 | 187; 16,000 and 25,600 1060 | 1700; 40,000 and 8,000 568 | 787
+constexpr unsigned long long kOneWork = 28672;
 constexpr int kLdsMaxK = 1024;             // above this the histograms live in E's rows
 constexpr int kLongRowDegree = 16384;      // plain score kernels: rows this long get a grid of their own ...
 constexpr uint32_t kLongRowPart = 16384;   // ... that many entries per workgroup and turn
@@ -1218,6 +1225,39 @@ int run_plain_merged(const RowT *rowptr, const int32_t *colidx, int64_t n, int32
     return L.err;
 }
 
+// A run that one workgroup does (grem_one.hip.h); nnz: entries of the graph.
+bool one_takes(int64_t n, int32_t k, int64_t cl, unsigned long long maxdeg, unsigned long long nnz, const Opts &o) {
+    const int64_t nchunks = (n + cl - 1) / cl;
+    return o.hist_mode == GREM_HIST_AUTO && o.long_row_degree == 0 && k <= kOneMaxK && n <= kOneMaxN && cl <= kOneMaxChunk &&
+           nchunks <= kOneMaxChunks && maxdeg < 65536 && nnz < (1ull << 31) && nnz / (unsigned long long)nchunks + (unsigned long long)(cl * k + cl * k / 2) <= kOneWork &&
+           one_lds_bytes(n, cl, k) <= kOneLds;
+}
+
+// (false: no memory for it, nothing enqueued)
+template <typename RowT>
+bool run_one(const RowT *rowptr, const int32_t *colidx, int64_t n, int32_t k, double slack, int64_t cl, int32_t R, int32_t *labels_out,
+             int64_t *sizes_out, uint32_t *estimates_out, unsigned long long nnz, Arena &mem, Launcher &L, CallState<uint8_t> &st) {
+    uint32_t *E = nullptr, *rec = nullptr;
+    const bool external_E = estimates_out != nullptr;
+    if (!carve(mem, [&](Carver &c) { c.take(E, external_E || R == 0 ? 0 : (size_t)n * (size_t)k); c.take(rec, (size_t)nnz + 16); })) return false;
+    const auto kernel = k <= 4 ? k_one_run<RowT, 4> : k_one_run<RowT, 8>;
+    if (!set_lds((const void *)kernel, one_lds_bytes(n, cl, k), kOneLds)) { L.err = GREM_ERR_HIP; return true; }
+    if (external_E) E = estimates_out;
+    L.mark();
+    if (nnz)
+        L.run(GREM_KERNEL_RELAYOUT, [&] {
+            hipLaunchKernelGGL((k_one_entries<RowT>), dim3((unsigned)((n + 3) / 4 < 2048 ? (n + 3) / 4 : 2048)), dim3(256), 0, L.stream, rowptr, colidx,
+                               n, cl, rec);
+        });
+    L.run(GREM_KERNEL_SCORE, [&] {
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(kOneThreads), one_lds_bytes(n, cl, k), L.stream, rowptr, (const uint32_t *)rec, (int)n,
+                           (int)k, (int)cl, (int)R, (int)std::min<int64_t>(grem_capacity(n, k, slack), 1 << 30), (const uint8_t *)st.Lc, (const long long *)st.S, E,
+                           external_E ? 1 : 0, labels_out, sizes_out);
+    });
+    for (int i = 0; i <= R + 1; ++i) L.mark();       // (one launch: its passes have no bounds of their own)
+    return true;
+}
+
 // Alg. 1's loop straight on the CSR.  `st` is prepared (prepass run, seed and degrees validated).
 template <typename RowT, typename LabelT>
 int run_plain(const RowT *rowptr, const int32_t *colidx, int64_t n, int32_t k, double slack, int64_t cl, int32_t R,
@@ -1412,6 +1452,12 @@ int run_partition(const RowT *rowptr, const int32_t *colidx, int64_t n, int32_t 
             if (R >= 32 || (maxdeg << R) >= (1ull << 32)) { mem.release_all(); return GREM_ERR_RANGE; }
             for (int i = 0; i < kLongClasses; ++i) degrees[i] = h[16 + i];
             if (counts) long_counts = (const uint32_t *)(h + 32);
+            if constexpr (sizeof(LabelT) == 1)
+                if (one_takes(n, k, cl, maxdeg, h[3], o) &&
+                    run_one<RowT>(rowptr, colidx, n, k, slack, cl, R, labels_out, sizes_out, estimates_out, h[3], mem, L, st)) {
+                    mem.release_all();
+                    return L.err;
+                }
         }
         rc = merged ? run_plain_merged<RowT, LabelT>(rowptr, colidx, n, k, slack, cl, R, seed, labels_out, sizes_out, estimates_out, o,
                                                      maxdeg, degrees, long_counts, mem, L, st)
