@@ -78,7 +78,15 @@ struct EsRun {
     uint32_t ngroups;
     int wpw;                                 // bitmap words per wave: a block is kBlock * wpw nodes
     int awpw;                                // the same in k_es_admit, a multiple of wpw
+    EsGroup only;                            // a run of one group: that group (groups and blk_group are not looked at: two loads
+                                             // less, one after the other, at the head of every launch)
 };
+__device__ __forceinline__ uint32_t es_group_of(const EsRun& st, uint32_t block) { return st.ngroups == 1u ? 0u : st.blk_group[block]; }
+__device__ __forceinline__ EsGroup es_group(const EsRun& st, uint32_t gi)
+{
+    if (st.ngroups == 1u) return st.only;
+    return st.groups[gi];
+}
 
 // label of node v: 0, 1 or kNone
 __device__ __forceinline__ uint32_t es_label(u64 word, uint32_t v)
@@ -115,7 +123,20 @@ __global__ __launch_bounds__(256) void k_es_fill64(u64* p, size_t count, u64 val
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride) p[i] = value;
 }
 
-__global__ void k_es_one_group(EsGroup* groups, EsGroup g) { if (threadIdx.x == 0) groups[0] = g; }
+// several arrays at once: a run of 20,000 nodes spent some 4 us on each launch of its own
+struct EsClears {
+    static constexpr int kMost = 8;
+    u64* p[kMost];
+    size_t words[kMost];
+    int n = 0;
+    void add(void* at, size_t bytes) { p[n] = (u64*)at; words[n++] = bytes / 8; }
+};
+__global__ __launch_bounds__(256) void k_es_clear(EsClears c)
+{
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    for (int k = 0; k < c.n; ++k)
+        for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < c.words[k]; i += stride) c.p[k][i] = 0ull;
+}
 
 __global__ __launch_bounds__(256) void k_es_blk_groups(const EsGroup* __restrict__ groups, uint32_t* blk_group)
 {
@@ -137,24 +158,40 @@ __global__ __launch_bounds__(256) void k_es_check(const int32_t* __restrict__ sr
 // c_nodes of the first chunk as a bitmap (Alg. 1: unique_nodes_in_edges).  Runs before the range check has
 // been read back: ends out of range are passed over.  Most ends find their bit set already: a plain look
 // spares them the atomic (a stale word only costs one).
+__device__ __forceinline__ void es_mark_ends(const EsRun& st, const EsGroup& g, uint32_t s, uint32_t d)
+{
+    const uint32_t end[2] = {s, d};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        if (end[i] >= g.nv) continue;
+        const uint32_t v = g.node0 + end[i];
+        const u64 bit = 1ull << (v & 63u);
+        if (!(__hip_atomic_load(&st.mark[v >> 6], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit))
+            atomicOr(&st.mark[v >> 6], bit);
+    }
+}
 __global__ __launch_bounds__(kCountBlock) void k_es_mark(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                                                          EsRun st)
 {
-    const EsGroup g = st.groups[blockIdx.y];
+    const EsGroup g = es_group(st, blockIdx.y);
     int64_t lo, hi;
     es_chunk(g, 0, lo, hi);
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < hi; e += stride) {
-        const uint32_t end[2] = {(uint32_t)src[e], (uint32_t)dst[e]};
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            if (end[i] >= g.nv) continue;
-            const uint32_t v = g.node0 + end[i];
-            const u64 bit = 1ull << (v & 63u);
-            if (!(__hip_atomic_load(&st.mark[v >> 6], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit))
-                atomicOr(&st.mark[v >> 6], bit);
-        }
+    for (int64_t e = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < hi; e += stride) es_mark_ends(st, g, (uint32_t)src[e], (uint32_t)dst[e]);
+}
+
+// both for a run of one group: all of its edges checked, the first chunk's ends marked
+__global__ __launch_bounds__(kCountBlock) void k_es_check_mark(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, EsRun st)
+{
+    const EsGroup g = st.only;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    bool bad = false;
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < g.m; e += stride) {
+        const uint32_t s = (uint32_t)src[e], d = (uint32_t)dst[e];
+        bad |= (s >= g.nv) | (d >= g.nv);
+        if (e < g.c_size) es_mark_ends(st, g, s, d);
     }
+    if (bad) st.flags[0] = 1u;
 }
 
 // The two-partition choice of Alg. 2, on sizes from which the node itself has been taken out: the
@@ -276,8 +313,8 @@ __device__ __forceinline__ uint32_t es_block_exclusive(uint32_t x, uint32_t* wsu
 __global__ __launch_bounds__(kBlock) void k_es_seed(EsRun st, const int32_t* __restrict__ seed)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t gi = st.blk_group[blockIdx.x];
-    const EsGroup& g = st.groups[gi];
+    const uint32_t gi = es_group_of(st, blockIdx.x);
+    const EsGroup g = es_group(st, gi);
     const uint32_t word0 = ((uint32_t)blockIdx.x * kWaves + wave) * st.wpw;
     const u64 mine = lane < st.wpw ? st.mark[word0 + lane] : 0ull;
     EsLabels labels{0ull, 0ull};
@@ -306,8 +343,9 @@ __global__ __launch_bounds__(kBlock) void k_es_seed(EsRun st, const int32_t* __r
 __global__ __launch_bounds__(256) void k_es_seed_sizes(EsRun st)
 {
     const uint32_t gi = blockIdx.x * blockDim.x + threadIdx.x;
-    if (gi < st.ngroups && ((long long)st.S[2 * gi] > st.groups[gi].P || (long long)st.S[2 * gi + 1] > st.groups[gi].P))
-        st.flags[1] = 1u;
+    if (gi >= st.ngroups) return;
+    const long long P = es_group(st, gi).P;
+    if ((long long)st.S[2 * gi] > P || (long long)st.S[2 * gi + 1] > P) st.flags[1] = 1u;
 }
 
 // cnt_nbrs (Alg. 2) for every node of the chunk at once, in memory: each edge adds one to the count its two
@@ -320,7 +358,7 @@ __global__ __launch_bounds__(256) void k_es_seed_sizes(EsRun st)
 __global__ __launch_bounds__(kCountBlock) void k_es_count(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                                                           EsRun st, int64_t chunk, u64* hc)
 {
-    const EsGroup g = st.groups[blockIdx.y];
+    const EsGroup g = es_group(st, blockIdx.y);
     int64_t lo, hi;
     es_chunk(g, chunk, lo, hi);
     const u64* __restrict__ Lw = st.Lw + (g.node0 >> 5);           // (a group starts at a whole block)
@@ -369,7 +407,7 @@ __global__ __launch_bounds__(kBlock) void k_es_hist(const int32_t* __restrict__ 
                                                     EsRun st, EsBins bins, EsBins ranges, int tile)
 {
     extern __shared__ uint32_t hist[];
-    const EsGroup g = st.groups[blockIdx.y];
+    const EsGroup g = es_group(st, blockIdx.y);
     int64_t lo, hi;
     es_chunk(g, blockIdx.z, lo, hi);
     if (lo + (int64_t)blockIdx.x * tile >= hi) return;
@@ -496,7 +534,7 @@ __device__ __forceinline__ void es_bin_tile(const int32_t* __restrict__ src, con
     __shared__ uint32_t wsum[kWaves];
     uint32_t* at = items + 2 * PER * kBlock;
     uint16_t* start = reinterpret_cast<uint16_t*>(at + bins.nb);
-    const EsGroup g = st.groups[blockIdx.y];
+    const EsGroup g = es_group(st, blockIdx.y);
     int64_t lo, hi;
     es_chunk(g, chunk, lo, hi);
     lo += (int64_t)blockIdx.x * (PER * kBlock);
@@ -611,7 +649,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_es_ask(const int32_t* __restrict_
     uint2* sorted = reinterpret_cast<uint2*>(items);
     uint32_t* at = items + 4 * kAskEdges;
     uint16_t* start = reinterpret_cast<uint16_t*>(at + ranges.nb);
-    const EsGroup g = st.groups[blockIdx.y];
+    const EsGroup g = es_group(st, blockIdx.y);
     int64_t lo, hi;
     es_chunk(g, chunk, lo, hi);
     lo += (int64_t)blockIdx.x * kAskEdges;
@@ -865,8 +903,8 @@ __global__ __launch_bounds__(kBlock) void k_es_crowd(int64_t chunk, EsBins tab, 
 __global__ __launch_bounds__(kBlock) void k_es_score(EsRun st, int par, int first, int fixed, u64* hc)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t gi = st.blk_group[blockIdx.x];
-    const long long P = st.groups[gi].P;
+    const uint32_t gi = es_group_of(st, blockIdx.x);
+    const long long P = es_group(st, gi).P;
     const long long S0 = (long long)st.S[2 * (par * st.ngroups + gi)], S1 = (long long)st.S[2 * (par * st.ngroups + gi) + 1];
     const uint32_t word0 = ((uint32_t)blockIdx.x * kWaves + wave) * st.wpw;
     const bool mine = lane < st.wpw;
@@ -968,8 +1006,8 @@ __global__ __launch_bounds__(kBlock, 8) void k_es_score_bins(EsRun st, int par, 
     if (place) p1 = p0;
     EsPairs list{reinterpret_cast<const uint4*>(pairs), p0, p1, (p1 + 3u) >> 2, 0u, {}};
     list.start();
-    const uint32_t gi = st.blk_group[block];
-    const long long P = st.groups[gi].P, S0 = (long long)st.S[2 * (par * st.ngroups + gi)], S1 = (long long)st.S[2 * (par * st.ngroups + gi) + 1];
+    const uint32_t gi = es_group_of(st, block);
+    const long long P = es_group(st, gi).P, S0 = (long long)st.S[2 * (par * st.ngroups + gi)], S1 = (long long)st.S[2 * (par * st.ngroups + gi) + 1];
     // what `assign` answers, by label and lean: bit 3 * label + lean + 1
     const uint32_t answers = (uint32_t)__ballot(lane < 9 && es_assign(lane % 3 - 1, S0 - (lane < 3), S1 - (lane >= 3 && lane < 6), P));
     const uint32_t words = bn / 32;
@@ -1168,8 +1206,9 @@ __global__ __launch_bounds__(kBlock) void k_es_admit(EsRun st, int par)
     __shared__ uint32_t c0[kWaves], c1[kWaves], co[kWaves];
     const int lane = threadIdx.x & 63, wave = es_wave(), awpw = st.awpw;
     const uint32_t own = (uint32_t)blockIdx.x * (uint32_t)(awpw / st.wpw);            // its first block of the scoring
-    const uint32_t gi = st.blk_group[own];
-    const uint32_t blk0 = st.groups[gi].blk0, nblk = st.groups[gi].nblk;
+    const uint32_t gi = es_group_of(st, own);
+    const EsGroup g = es_group(st, gi);
+    const uint32_t blk0 = g.blk0, nblk = g.nblk;
     const uint32_t word0 = ((uint32_t)blockIdx.x * kWaves + wave) * awpw + lane * W;
     const bool mine = lane * W < awpw;
     u64 my0[W], my1[W], fresh[W];
@@ -1192,7 +1231,7 @@ __global__ __launch_bounds__(kBlock) void k_es_admit(EsRun st, int par)
 #pragma unroll
     for (int i = 0; i < W; ++i) { n0 += (uint32_t)__popcll(my0[i]); n1 += (uint32_t)__popcll(my1[i]); }
     es_block_sums(sums);
-    const long long P = st.groups[gi].P;
+    const long long P = g.P;
     const long long S0 = (long long)st.S[2 * (par * st.ngroups + gi)], S1 = (long long)st.S[2 * (par * st.ngroups + gi) + 1];
     const long long room0 = P - S0 > 0 ? P - S0 : 0, room1 = P - S1 > 0 ? P - S1 : 0;
     long long rank0 = (long long)(sums[0] + es_block_exclusive(n0, c0)), rank1 = (long long)(sums[1] + es_block_exclusive(n1, c1));
@@ -1296,7 +1335,7 @@ constexpr int kSelTile = kSelBlock * kSelPer;
 // per block: its nodes with label 0 and its nodes without a label
 __global__ __launch_bounds__(kBlock) void k_rb_count(EsRun st)
 {
-    const EsGroup& g = st.groups[st.blk_group[blockIdx.x]];
+    const EsGroup g = es_group(st, es_group_of(st, blockIdx.x));
     const uint32_t bw = (uint32_t)(kWaves * st.wpw), word = blockIdx.x * bw + threadIdx.x, v = word * 64u - g.node0;   // (a thread per word)
     uint32_t n[2] = {0u, 0u};
     if (threadIdx.x < bw && v < g.nv) {
@@ -1324,8 +1363,8 @@ __global__ __launch_bounds__(kBlock) void k_rb_children(EsRun st, int par, const
 {
     __shared__ uint32_t cz[kWaves], cn[kWaves];
     const int lane = threadIdx.x & 63, wave = es_wave(), wpw = st.wpw;
-    const uint32_t gi = st.blk_group[blockIdx.x];
-    const EsGroup g = st.groups[gi];
+    const uint32_t gi = es_group_of(st, blockIdx.x);
+    const EsGroup g = es_group(st, gi);
     uint32_t sums[4] = {0u, 0u, 0u, 0u};          // zeros and nodes without a label: in earlier blocks, in all
     for (uint32_t b = g.blk0 + threadIdx.x; b < g.blk0 + g.nblk; b += kBlock) {
         const uint32_t z = st.bs[b].x, e = st.bs[b].y;
@@ -1641,10 +1680,10 @@ struct EsMemory {
             off += align256(count * sizeof(T));
         };
         const size_t blocks = (size_t)(nodes / sh.bn()), words = (size_t)(nodes / 64);
-        take(st.flags, 2);
+        take(st.flags, 2);                       // (S follows: one read-back brings both)
+        take(st.S, (size_t)ngroups * 4);
         take(groups, (size_t)ngroups);
         take(blk_group, blocks);
-        take(st.S, (size_t)ngroups * 4);
         take(st.Lw, (size_t)(nodes / 32));
         if (est_out && !sh.binned) st.est = (double2*)est_out;
         else take(st.est, (size_t)nodes);
@@ -1693,10 +1732,11 @@ void es_fill(hipStream_t stream, void* p, size_t bytes, u64 value)
 // One run: everything from the cleared state to the last chunk's spill is enqueued.  groups_host: its groups, in the
 // order of their nodes (also at mem.groups on the device, with mem.blk_group filled).  check(): called once the first chunk's seeds are
 // counted and flags[] is complete, before anything uses the labels; its answer other than GREM_OK ends the run.
-// check() waits for the stream where the run is binned.  est_nodes: entries of est to clear.  *par_out: which copy of the sizes is the final one.
+// check_ends (one group): flags[] and the endpoints' range are this call's business too, and the seeds' sizes check()'s.  check() waits for the
+// stream where the run is binned.  est_nodes: entries of est to clear.  *par_out: which copy of the sizes is the final one.
 template <typename Check>
 int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vector<EsGroup>& groups, int64_t nodes, int64_t est_nodes,
-           const int32_t* src, const int32_t* dst, const int32_t* seed, int32_t mode, Check&& check, int* par_out)
+           const int32_t* src, const int32_t* dst, const int32_t* seed, int32_t mode, bool check_ends, Check&& check, int* par_out)
 {
     EsRun& st = mem.st;
     st.ngroups = (uint32_t)groups.size();
@@ -1708,16 +1748,25 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
         const int64_t c = (g.m + g.c_size - 1) / g.c_size;
         if (c > chunks) chunks = c;
     }
-    es_fill(stream, st.S, align256((size_t)ng * 32), 0ull);
-    es_fill(stream, st.Lw, (size_t)nodes / 4, 0ull);
-    es_fill(stream, st.mark, (size_t)nodes / 8, 0ull);
+    if (ng == 1) st.only = groups[0];
+    EsClears clears;
+    if (check_ends) clears.add(st.flags, 8);
+    clears.add(st.S, align256((size_t)ng * 32));
+    clears.add(st.Lw, (size_t)nodes / 4);
+    clears.add(st.mark, (size_t)nodes / 8);
+    if (sh.binned) {
+        clears.add(mem.bins.ends, align256((size_t)chunks * sh.nb * mem.bins.classes * 4));
+        if (sh.asked) clears.add(mem.ranges.ends, align256((size_t)chunks * sh.ask_nb * sh.classes * 4));
+        clears.add(st.packed, (size_t)nodes * 8);
+        clears.add(st.wide, align256((size_t)blocks * 4));
+    } else {
+        clears.add(mem.hc, (size_t)nodes * 8);
+        clears.add(st.est, (size_t)est_nodes * 16);
+    }
+    hipLaunchKernelGGL(k_es_clear, dim3(grid_for((sh.binned ? 8 : 24) * nodes / 64, 256, 16384)), dim3(256), 0, stream, clears);
     auto round = [&](int64_t grid) { return (grid + sh.classes - 1) / sh.classes * sh.classes; };
     std::vector<uint32_t> crowded;                             // per chunk: its crowded bins
     if (sh.binned) {
-        es_fill(stream, mem.bins.ends, align256((size_t)chunks * sh.nb * mem.bins.classes * 4), 0ull);
-        if (sh.asked) es_fill(stream, mem.ranges.ends, align256((size_t)chunks * sh.ask_nb * sh.classes * 4), 0ull);
-        es_fill(stream, st.packed, (size_t)nodes * 8, 0ull);
-        es_fill(stream, st.wide, align256((size_t)blocks * 4), 0ull);
         // (workgroups of several tiles each: a workgroup's 1024 counts are added to the table once)
         const int64_t parts = round(grid_for((most + sh.tile - 1) / sh.tile, 4, 256));
         const size_t hist_lds = (size_t)sh.nb * 4 * (sh.asked ? sh.classes : 1);
@@ -1730,13 +1779,14 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
         }
         crowded.resize((size_t)chunks);
         if (hipMemcpyAsync(crowded.data(), mem.crowd.bins, (size_t)chunks * 4, hipMemcpyDeviceToHost, stream) != hipSuccess) return GREM_ERR_HIP;
-    } else {
-        es_fill(stream, mem.hc, (size_t)nodes * 8, 0ull);
-        es_fill(stream, st.est, (size_t)est_nodes * 16, 0ull);
     }
-    hipLaunchKernelGGL(k_es_mark, dim3((unsigned)grid_for(most, kCountBlock, 8192), ng), dim3(kCountBlock), 0, stream, src, dst, st);
+    // (a binned run has checked the endpoints where it counted the bins)
+    if (check_ends && !sh.binned)
+        hipLaunchKernelGGL(k_es_check_mark, dim3((unsigned)grid_for(groups[0].m, kCountBlock, 8192)), dim3(kCountBlock), 0, stream, src, dst, st);
+    else
+        hipLaunchKernelGGL(k_es_mark, dim3((unsigned)grid_for(most, kCountBlock, 8192), ng), dim3(kCountBlock), 0, stream, src, dst, st);
     hipLaunchKernelGGL(k_es_seed, dim3(blocks), dim3(kBlock), 0, stream, st, seed);
-    hipLaunchKernelGGL(k_es_seed_sizes, dim3((ng + 255) / 256), dim3(256), 0, stream, st);
+    if (!check_ends) hipLaunchKernelGGL(k_es_seed_sizes, dim3((ng + 255) / 256), dim3(256), 0, stream, st);
     const int rc = check();
     if (rc != GREM_OK) return rc;
     for (int64_t i = 0; i < (int64_t)crowded.size(); ++i)
@@ -1835,20 +1885,16 @@ int es_bipartition(const int32_t* src, const int32_t* dst, int64_t m, int64_t n,
     mem.layout(ws, sh, 1, ends, chunks, nbr_counts_out);
     std::vector<EsGroup> groups(1);
     groups[0] = EsGroup{0, m, c_size, (long long)P, 0, 0u, (uint32_t)n, 0u, (uint32_t)(nodes / sh.bn()), 0u, 0u};
-    es_fill(stream, mem.st.flags, 8, 0ull);
-    hipLaunchKernelGGL(k_es_one_group, dim3(1), dim3(64), 0, stream, mem.groups, groups[0]);
-    hipLaunchKernelGGL(k_es_blk_groups, dim3(1), dim3(256), 0, stream, (const EsGroup*)mem.groups, mem.blk_group);
-    // (a binned run checks the endpoints where it counts the bins)
-    if (!sh.binned)
-        hipLaunchKernelGGL(k_es_check, dim3(grid_for(m, 256, 8192)), dim3(256), 0, stream, src, dst, m, (uint32_t)n, mem.st.flags);
     int par = 0;
     // the range check must be known before any kernel indexes with the endpoints
-    int rc = es_run(stream, mem, sh, groups, nodes, n, src, dst, seed_parts, mode, [&]() -> int {
-        uint32_t flags[2] = {0, 0};
-        if (hipMemcpyAsync(flags, mem.st.flags, sizeof(flags), hipMemcpyDeviceToHost, stream) != hipSuccess ||
+    int rc = es_run(stream, mem, sh, groups, nodes, n, src, dst, seed_parts, mode, true, [&]() -> int {
+        struct { uint32_t flags[64]; u64 S[2]; } back{};
+        static_assert(sizeof(back) == 256 + 16, "as EsMemory lays them out");
+        if (hipMemcpyAsync(&back, mem.st.flags, sizeof(back), hipMemcpyDeviceToHost, stream) != hipSuccess ||
             hipStreamSynchronize(stream) != hipSuccess)
             return GREM_ERR_HIP;
-        return flags[0] ? GREM_ERR_ARG : flags[1] ? GREM_ERR_SEED : GREM_OK;
+        const bool full = (long long)back.S[0] > P || (long long)back.S[1] > P;
+        return back.flags[0] ? GREM_ERR_ARG : back.flags[1] || full ? GREM_ERR_SEED : GREM_OK;
     }, &par);
     if (rc == GREM_OK) {
         hipLaunchKernelGGL(k_es_expand, dim3(grid_for(n, 256, 16384)), dim3(256), 0, stream, n, (const u64*)mem.st.Lw, parts_out,
@@ -1958,7 +2004,7 @@ int es_bisection(const int32_t* src, const int32_t* dst, int64_t m, int64_t n, i
             hipLaunchKernelGGL(k_es_blk_groups, dim3(ng), dim3(256), 0, stream, (const EsGroup*)mem.groups, mem.blk_group);
             int par = 0;
             // a bad seed is looked for at the end of the level: until then it only leaves a node without a label
-            const int rc = es_run(stream, mem, sh, groups, nodes, nodes, cur_s, cur_d, cur_seed, mode, [&] {
+            const int rc = es_run(stream, mem, sh, groups, nodes, nodes, cur_s, cur_d, cur_seed, mode, false, [&] {
                 return sh.binned && hipStreamSynchronize(stream) != hipSuccess ? GREM_ERR_HIP : GREM_OK;
             }, &par);
             if (rc != GREM_OK) return fail(rc);
