@@ -48,7 +48,7 @@ typedef unsigned long long u64;
 constexpr int kBlock = 1024;                 // per-node kernels: 16 waves
 constexpr int kWaves = kBlock / 64;
 constexpr int kMaxWaveWords = 64;            // most bitmap words a wave of the per-node kernels owns
-constexpr int kMaxAdmitWords = 256;          // ... of k_es_admit
+constexpr int kMaxAdmitWords = 128;          // ... of k_es_admit
 constexpr uint32_t kNone = 2u;               // label of a node that has none
 constexpr int kCountBlock = 256;
 constexpr int kTurn = 4;                     // bitmap words a wave has in flight
@@ -1198,7 +1198,7 @@ __device__ __forceinline__ void es_rejected(const EsRun& st, uint32_t blk0, uint
 // A lane takes W neighbouring words of 64 nodes (awpw = 64 * W words per wave, or fewer with W = 1): the admitted movers
 // of a word are its first bits, as many as there is room for, the alternation over rejected ones is a prefix parity, and labels
 // change in a few bit operations.  W and awpw: so many that 256 blocks or fewer do it up to 67M nodes in one group, as each adds up
-// all blocks' counts; beyond that a block takes 262,144 nodes, 424 of them 111M (es_shape).  In two launches (admission, spill), with labels of a byte each and movers taken one by one: 103 us per chunk at
+// all blocks' counts; beyond that a block takes 131,072 nodes, 848 of them 111M (es_shape; with twice as many, and 92 registers, 52 us for 43).  In two launches (admission, spill), with labels of a byte each and movers taken one by one: 103 us per chunk at
 // 111M nodes, 13 at 20,000; now 53 and 6.
 template <int W>
 __global__ __launch_bounds__(kBlock) void k_es_admit(EsRun st, int par)
@@ -1578,7 +1578,7 @@ inline int grid_for(int64_t items, int block, int64_t cap)
 //   blocks  otherwise kBlock * wpw nodes each: one word per wave up to a million nodes (the chip wants some 1024
 //           blocks), more words beyond it, so that a block can add up all blocks' counts itself.
 //   awpw    the admission's workgroups each add up all blocks' counts: as many words per wave as leave 256 workgroups or
-//           fewer, up to kMaxAdmitWords (262,144 nodes per workgroup: more than 256 of them from 67M nodes on) and while the
+//           fewer, up to kMaxAdmitWords (131,072 nodes per workgroup: more than 256 of them from 33M nodes on) and while the
 //           groups' padding stays within their nodes (so with several groups there may be more from fewer nodes on).
 struct EsShape {
     int wpw = 1, awpw = 1;
@@ -1768,7 +1768,8 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
     std::vector<uint32_t> crowded;                             // per chunk: its crowded bins
     if (sh.binned) {
         // (workgroups of several tiles each: a workgroup's 1024 counts are added to the table once)
-        const int64_t parts = round(grid_for((most + sh.tile - 1) / sh.tile, 4, 256));
+        // (asked: 128 KB of counts each; with 256 workgroups a chunk 4.4 ms at 111M nodes and 100 chunks, with 48 3.7)
+        const int64_t parts = round(grid_for((most + sh.tile - 1) / sh.tile, 4, sh.asked ? std::min<int64_t>(std::max<int64_t>(4096 / (chunks * ng), 32), 256) : 256));
         const size_t hist_lds = (size_t)sh.nb * 4 * (sh.asked ? sh.classes : 1);
         if (hipFuncSetAttribute((const void*)k_es_hist, hipFuncAttributeMaxDynamicSharedMemorySize, kBins * 4 * 8) != hipSuccess) return GREM_ERR_HIP;
         hipLaunchKernelGGL(k_es_hist, dim3((unsigned)parts, ng, (unsigned)chunks), dim3(kBlock), hist_lds, stream, src, dst, st, mem.bins, mem.ranges, sh.tile);
@@ -1853,8 +1854,7 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
         if (sh.binned) timed();
         if (first) continue;
         if (sh.awpw <= 64) hipLaunchKernelGGL(k_es_admit<1>, dim3(ablocks), dim3(kBlock), 0, stream, st, par);
-        else if (sh.awpw == 128) hipLaunchKernelGGL(k_es_admit<2>, dim3(ablocks), dim3(kBlock), 0, stream, st, par);
-        else hipLaunchKernelGGL(k_es_admit<4>, dim3(ablocks), dim3(kBlock), 0, stream, st, par);
+        else hipLaunchKernelGGL(k_es_admit<2>, dim3(ablocks), dim3(kBlock), 0, stream, st, par);
         par ^= 1;
     }
     *par_out = par;
