@@ -75,6 +75,8 @@ constexpr int64_t kMinSlices = 256;        // slices per chunk wanted: one per C
 constexpr int64_t kMaxSegments = 1ll << 22;   // chunks * column blocks
 constexpr int64_t kCutPackMinN = 1 << 20;  // edge cut: int32 labels of more vertices outgrow an XCD's 4 MB of L2
 constexpr size_t kScoreLds16 = 150 * 1024, kScoreLds32 = 158 * 1024;   // k_tp_score's LDS: with the static counters for k <= 16
+constexpr int64_t kLookupSweep = 8192;     // workgroups of a look-up launch over many chunks: each copies a block's labels first (13.9M vertices, 106 blocks,
+                                           // with one per 8192 entries 49,000 of them: 0.74 ms, so 0.38; 4096: k = 24 1.05 ms for 0.97, 16,384: k = 16 0.93 for 0.90)
 constexpr int64_t kPlaceGrid = 1024;       // workgroups of k_tp_place wanted: four per CU
 constexpr int kMaxParts = kPlanParts;      // parts of a slice (hub share) in the re-layout
 
@@ -853,6 +855,7 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
         int spb = P.lookup_target / geo.nbc;
         const int64_t by_work = per_block / 8192 + 1;
         if (spb > by_work) spb = (int)by_work;
+        if (count > 1 && spb > kLookupSweep / ((int64_t)count * geo.nbc)) spb = (int)(kLookupSweep / ((int64_t)count * geo.nbc));
         if (spb < 1) spb = 1;
         const dim3 grid((unsigned)(geo.nbc * spb), (unsigned)count);
         auto go = [&](auto kernel, size_t lds) {
@@ -880,6 +883,31 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
         }
     }
     L.mark();
+    if (fixed_labels) {                     // counts only: nothing to admit, no new labels to look up
+        const bool skip = partly && k == 32;
+        auto counts = [&](auto kernel) {
+            if (!set_lds((const void *)kernel, score_lds, most_score)) { L.err = GREM_ERR_HIP; return; }
+            L.run(GREM_KERNEL_HUBS, [&] {
+                hipLaunchKernelGGL(k_tp_clear_hubs, dim3((unsigned)std::min<size_t>((size_t)P.total_hubs * k / 256 + 1, 2048)), dim3(256), 0, stream,
+                                   (const int32_t *)pl.hub_row, (size_t)P.total_hubs, (int)k, E32);
+            });
+            L.run(GREM_KERNEL_SCORE, [&] {
+                hipLaunchKernelGGL(kernel, dim3((unsigned)((size_t)geo.nch * (size_t)geo.nsl)), dim3(kTpThreads), score_lds, stream,
+                                   marks ? (const uint16_t *)t.Rdyn : (const uint16_t *)P.R, (const uint32_t *)t.Lx, tb, pl, n, cl, (int)k, P.share_hubs, E32);
+            });
+        };
+        auto rows = [&](auto sr) {
+            constexpr int SR = decltype(sr)::value;
+            if (wide) { if (skip) counts(k_tp_counts<32, false, SR, true>); else counts(k_tp_counts<32, false, SR, false>); }
+            else if (k <= 8) counts(k_tp_counts<16, true, SR, false>);
+            else counts(k_tp_counts<16, false, SR, false>);
+        };
+        if (geo.srows == 512) rows(std::integral_constant<int, 512>{});
+        else if (geo.srows == 1024) rows(std::integral_constant<int, 1024>{});
+        else rows(std::integral_constant<int, kSliceRows>{});
+        L.mark();
+        return L.err;
+    }
     const size_t max_chunk_hubs = (size_t)P.max_chunk_hubs;
     uint32_t prev_hubs = 0;                 // hubs of the chunk before (whose counts the admission clears)
     // first pass, chunks of at most kSpillSmallTiles tiles: the spill is one launch that reads the sizes from one
@@ -961,7 +989,6 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
                                        (uint8_t *)st.prop, st.cnt, (int)c, lo, (int)k, pass, store_e, ncells, cell_rows,
                                        st.tot);
             });
-            if (fixed_labels) continue;          // counts only: nothing to admit, no new labels to look up
             // admission: the score kernel has counted the movers per tile and taken the sizes' snapshot, and
             // the tiles are few enough that every workgroup adds up the earlier tiles' counts itself
             L.run(GREM_KERNEL_APPLY, [&] {

@@ -1681,6 +1681,92 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(KP =
 }
 
 // ------------------------------------------------------------------------------------------------
+// cnt_nbrs (Alg. 2) of every vertex under labels that stay as they are, all chunks in one launch: a workgroup counts a slice's
+// stream and its part of a hub share's as k_tp_score does, and writes the counts of the slice's rows.  A hub's row starts at zero
+// (k_tp_clear_hubs) and takes the shares' counts as atomic adds.
+// 13.9M vertices, 400M entries, k = 16: 106 chunks of 11.4 + 4.0 us in launches of their own, 1.63 ms; now 0.36.  Bound by the streams (1.0 GB read, 0.9 GB
+// of counts written) and by the counters' LDS atomics.
+// LDS: hist[SR * KP / 2] (as in k_tp_score), flags[SR / 32], hhist[share_hubs * k]
+// ------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void k_tp_clear_hubs(const int32_t *__restrict__ hub_row, size_t hubs, int k, uint32_t *__restrict__ E) {
+    const size_t cells = hubs * (size_t)k, stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < cells; i += stride)
+        E[(size_t)hub_row[i / (size_t)k] * (size_t)k + i % (size_t)k] = 0u;
+}
+
+template <int KP, bool SW, int SR, bool MARK>
+__global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(KP == 32 && SR == kSliceRows ? 4 : 8, KP == 32 && SR == kSliceRows ? 4 : 8))) void k_tp_counts(
+    const uint16_t *__restrict__ R, const uint32_t *__restrict__ Lx, TpTables tb, SweepPlan pl, int64_t n, int64_t cl, int k, int share_hubs,
+    uint32_t *__restrict__ E) {
+    extern __shared__ uint32_t smem[];
+    constexpr int LB = KP == 16 ? 4 : 8;
+    constexpr int hist_words = SR * KP / 2;
+    __shared__ uint32_t hist_static[KP == 16 ? hist_words : 1];
+    uint32_t *hist = KP == 16 ? hist_static : smem;
+    uint32_t *flags = KP == 16 ? smem : smem + hist_words;
+    uint32_t *hhist = flags + SR / 32;
+    const int tid = threadIdx.x;
+    // (contiguous ranges of slices per XCD, as in k_tp_score)
+    const unsigned xcd = blockIdx.x & 7u, turn = blockIdx.x >> 3;
+    const unsigned id = xcd * (gridDim.x >> 3) + (xcd < (gridDim.x & 7u) ? xcd : (gridDim.x & 7u)) + turn;
+    const int c = (int)(id / (unsigned)tb.nsl);
+    const unsigned slice = id % (unsigned)tb.nsl;
+    const int64_t chunk_lo = (int64_t)c * cl, chunk_hi = chunk_lo + cl < n ? chunk_lo + cl : n, v0 = chunk_lo + (int64_t)slice * SR;
+    if (v0 >= chunk_hi) return;                                 // (the last chunk has fewer slices)
+    const unsigned slices = (unsigned)((chunk_hi - chunk_lo + SR - 1) / SR);
+    const int nv = chunk_hi - v0 < SR ? (int)(chunk_hi - v0) : SR;
+    const uint32_t nvs = pl.ch_nvs[c];
+    const uint32_t share = nvs ? slice % nvs : 0u;
+    const u64 *ss = tb.sstart + (size_t)c * tb.nr;
+    const size_t gs = (size_t)c * tb.nsl + slice;
+    const uint32_t hr = (uint32_t)tb.nsl + share;
+    const u64 sbeg = ss[slice], send = ss[slice + 1];
+    const bool any_hub = nvs != 0 && pl.share_nhs[(size_t)c * tb.nsl + share] != 0;
+    const uint32_t snh = pl.sl_nh[gs];
+    for (int q = tid; q < hist_words / 4; q += kTpThreads) reinterpret_cast<u32x4 *>(hist)[q] = (u32x4)(0u);
+    for (int q = tid; q < SR / 32; q += kTpThreads) flags[q] = 0u;
+    if (any_hub)
+        for (int q = tid; q < share_hubs * k; q += kTpThreads) hhist[q] = 0u;
+    __syncthreads();
+    for (uint32_t i = tid; i < snh; i += kTpThreads) {
+        const uint32_t at = (uint32_t)((int64_t)pl.hub_row[pl.ch_hub0[c] + pl.sl_hub_start[gs] + i] - v0);
+        atomicOr(&flags[at >> 5], 1u << (at & 31u));
+    }
+    tp_count_stream<true, KP, LB, 3, SW, MARK>(R, Lx, sbeg, 0u, (uint32_t)(send - sbeg) >> 3, k, hist);
+    if (any_hub) {
+        const uint32_t cls = slice / nvs, ncls = (slices - share + nvs - 1) / nvs;       // this workgroup's part, and how many there are
+        const u64 groups = (ss[hr + 1] - ss[hr]) >> 3;
+        tp_count_stream<false, KP, LB, 2, false, MARK>(R, Lx, ss[hr], (uint32_t)(groups * cls / ncls), (uint32_t)(groups * (cls + 1) / ncls), k, hhist);
+    }
+    __syncthreads();
+    if (any_hub) {
+        const u64 hub0 = pl.ch_hub0[c] + pl.share_h0[(size_t)c * tb.nsl + share];
+        for (int q = tid; q < share_hubs * k; q += kTpThreads) {
+            const uint32_t x = hhist[q];
+            if (x) atomicAdd(&E[(size_t)pl.hub_row[hub0 + (uint32_t)q / (uint32_t)k] * (size_t)k + (uint32_t)q % (uint32_t)k], x);
+        }
+    }
+    uint32_t *out = E + (size_t)v0 * (size_t)k;
+    auto is_hub = [&](uint32_t t) { return (flags[t >> 5] >> (t & 31u)) & 1u; };
+    if ((k & 3) == 0) {                                         // four partitions at a time
+        const uint32_t k4 = (uint32_t)k / 4u;
+        for (uint32_t i = tid; i < (uint32_t)nv * k4; i += kTpThreads) {
+            const uint32_t t = i / k4, p = i % k4;
+            const uint2 w = *reinterpret_cast<const uint2 *>(hist + t * (KP / 2) + 2u * (SW ? p ^ ((t >> 3) & 3u) : p));
+            u32x4 o;
+            o.x = w.x & 0xFFFFu; o.y = w.x >> 16; o.z = w.y & 0xFFFFu; o.w = w.y >> 16;
+            if (!is_hub(t)) __builtin_nontemporal_store(o, reinterpret_cast<u32x4 *>(out) + i);
+        }
+    } else {
+        for (uint32_t i = tid; i < (uint32_t)(nv * k); i += kTpThreads) {
+            const uint32_t t = i / (uint32_t)k, j = i % (uint32_t)k;
+            const uint32_t cell = t * KP + (SW ? j ^ (((t >> 3) & 3u) << 2) : j);
+            if (!is_hub(t)) __builtin_nontemporal_store((hist[cell >> 1] >> (16u * (cell & 1u))) & 0xFFFFu, out + i);
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
 // hubs of the chunk: counts from the hub table (complete once k_tp_score has finished), blend,
 // propose, add the movers to their tiles' counts; the table row is cleared for the next chunk.
 // KP lanes per hub, lane j takes partition j (k <= KP).
