@@ -75,6 +75,8 @@ constexpr int64_t kMinSlices = 256;        // slices per chunk wanted: one per C
 constexpr int64_t kMaxSegments = 1ll << 22;   // chunks * column blocks
 constexpr int64_t kCutPackMinN = 1 << 20;  // edge cut: int32 labels of more vertices outgrow an XCD's 4 MB of L2
 constexpr size_t kScoreLds16 = 150 * 1024, kScoreLds32 = 158 * 1024;   // k_tp_score's LDS: with the static counters for k <= 16
+constexpr int kLookupGrid = 256;           // workgroups of a chunk's look-up launch (planned runs, 512 | 256: 13.9M vertices in chunks of 2^17 and k = 32 8.75 | 8.33 ms,
+                                           // k = 16 6.85 | 6.56; 20M in chunks of 300,000 6.80 | 6.53; 25M and 111M in chunks of 2^20 the same; 128 and 384 were slower)
 constexpr int64_t kLookupSweep = 8192;     // workgroups of a look-up launch over many chunks: each copies a block's labels first (13.9M vertices, 106 blocks,
                                            // with one per 8192 entries 49,000 of them: 0.74 ms, so 0.38; 4096: k = 24 1.05 ms for 0.97, 16,384: k = 16 0.93 for 0.90)
 constexpr int64_t kPlaceGrid = 1024;       // workgroups of k_tp_place wanted: four per CU
@@ -335,7 +337,6 @@ struct PlanData {
     std::vector<u64> chunk_hub0;            // hubs of the chunks before it (host copy of pl.ch_hub0)
     int share_hubs = 0;
     int max_k = 0;                          // largest k whose score workgroups fit the LDS
-    int lookup_target = 512;
 };
 
 // Sizes of the plan's pieces as functions of what is known at each stage; the same functions serve the
@@ -563,7 +564,6 @@ int build_plan(PlanData &P, const RowT *rowptr, const int32_t *colidx, int64_t n
     tb.prows = geo.srows / npr;
     tb.pstep = geo.srows / kPlanThreads / npr;
     tb.nps = nps;
-    P.lookup_target = geo.cb > 17 ? 256 : 512;
 
     const Arena::Mark tmark = temp.mark();
     const size_t subs = (size_t)geo.nch * (size_t)d.nr * (size_t)geo.nblk;
@@ -852,7 +852,7 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
     auto lookup = [&](int c0, int count, int cmin, bool from_lds, bool mark, const uint8_t *labels4 = nullptr) {
         if (cmin >= geo.nch) return;
         const int64_t per_block = P.nnz / geo.nblk + 1;
-        int spb = P.lookup_target / geo.nbc;
+        int spb = kLookupGrid / geo.nbc;
         const int64_t by_work = per_block / 8192 + 1;
         if (spb > by_work) spb = (int)by_work;
         if (count > 1 && spb > kLookupSweep / ((int64_t)count * geo.nbc)) spb = (int)(kLookupSweep / ((int64_t)count * geo.nbc));
