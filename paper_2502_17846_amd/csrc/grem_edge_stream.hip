@@ -589,6 +589,11 @@ __global__ __launch_bounds__(kBlock, 8) void k_es_bin(const int32_t* __restrict_
 {
     es_bin_tile<4>(src, dst, st, chunk, bins, pairs);
 }
+__global__ __launch_bounds__(kBlock, 8) void k_es_bin2(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, EsRun st, int64_t chunk,
+                                                       EsBins bins, uint32_t* __restrict__ pairs)
+{
+    es_bin_tile<2>(src, dst, st, chunk, bins, pairs);
+}
 __global__ __launch_bounds__(kBlock, 8) void k_es_bin6(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, EsRun st, int64_t chunk,
                                                        EsBins bins, uint32_t* __restrict__ pairs)
 {
@@ -1597,6 +1602,9 @@ struct EsShape {
     int64_t an() const { return (int64_t)kBlock * awpw; }
     int64_t padded(int64_t nv) const { return (nv + an() - 1) / an() * an(); }
 };
+// of 4096 edges: a step of fewer is binned in tiles of 2048 (bisection of 14M nodes 38.3 -> 36.3 ms, 100 chunks of 5M nodes 4.67 -> 4.33; 488 tiles, 14M nodes,
+// 9.6 ms in tiles of 4096 and 10.3 of 2048)
+constexpr int64_t kBinFewTiles = 400;
 constexpr int kBinWaveWords = 16;
 constexpr int64_t kWideSparse = 340, kSparse = 720;
 constexpr int64_t kAskMinNodes = 1ll << 25, kAskMinEnds = 1ll << 24;
@@ -1748,6 +1756,10 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
         const int64_t c = (g.m + g.c_size - 1) / g.c_size;
         if (c > chunks) chunks = c;
     }
+    // (a step of few tiles is a tile's latency: smaller ones, several to a CU)
+    int64_t step = 0;
+    for (const EsGroup& g : groups) step += g.c_size < g.m ? g.c_size : g.m;
+    const int tile = sh.binned && !sh.asked && sh.tile == kBinTile / 2 && step < kBinFewTiles * sh.tile ? sh.tile / 2 : sh.tile;
     if (ng == 1) st.only = groups[0];
     EsClears clears;
     if (check_ends) clears.add(st.flags, 8);
@@ -1769,10 +1781,10 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
     if (sh.binned) {
         // (workgroups of several tiles each: a workgroup's 1024 counts are added to the table once)
         // (asked: 128 KB of counts each; with 256 workgroups a chunk 4.4 ms at 111M nodes and 100 chunks, with 48 3.7)
-        const int64_t parts = round(grid_for((most + sh.tile - 1) / sh.tile, 4, sh.asked ? std::min<int64_t>(std::max<int64_t>(4096 / (chunks * ng), 32), 256) : 256));
+        const int64_t parts = round(grid_for((most + tile - 1) / tile, 4, sh.asked ? std::min<int64_t>(std::max<int64_t>(4096 / (chunks * ng), 32), 256) : 256));
         const size_t hist_lds = (size_t)sh.nb * 4 * (sh.asked ? sh.classes : 1);
         if (hipFuncSetAttribute((const void*)k_es_hist, hipFuncAttributeMaxDynamicSharedMemorySize, kBins * 4 * 8) != hipSuccess) return GREM_ERR_HIP;
-        hipLaunchKernelGGL(k_es_hist, dim3((unsigned)parts, ng, (unsigned)chunks), dim3(kBlock), hist_lds, stream, src, dst, st, mem.bins, mem.ranges, sh.tile);
+        hipLaunchKernelGGL(k_es_hist, dim3((unsigned)parts, ng, (unsigned)chunks), dim3(kBlock), hist_lds, stream, src, dst, st, mem.bins, mem.ranges, tile);
         hipLaunchKernelGGL(k_es_hist_scan, dim3((unsigned)chunks), dim3(kBlock), 0, stream, mem.bins, mem.crowd, mem.totals);
         if (sh.asked) {
             hipLaunchKernelGGL(k_es_hist_scan, dim3((unsigned)chunks), dim3(kBlock), 0, stream, mem.ranges, EsCrowd{}, (uint32_t*)nullptr);
@@ -1798,7 +1810,7 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
         }
     const int64_t crowd_bn = sh.bn() < kCrowdNodes ? sh.bn() : kCrowdNodes;
     const size_t crowd_lds = (size_t)crowd_bn * 4 + (size_t)crowd_bn / 8, bins_lds = es_bins_lds(sh.bn(), sh.room);
-    const auto bin = sh.tile == 8192 ? k_es_bin8 : sh.tile == 6144 ? k_es_bin6 : k_es_bin;
+    const auto bin = tile == 8192 ? k_es_bin8 : tile == 6144 ? k_es_bin6 : tile == 4096 ? k_es_bin : k_es_bin2;
     // (always what any run may need: the limit is the process's, and other threads' runs are of other sizes)
     if (sh.binned &&
         (hipFuncSetAttribute((const void*)k_es_ask, hipFuncAttributeMaxDynamicSharedMemorySize, kSortLds) != hipSuccess ||
@@ -1830,14 +1842,14 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
         };
         if (sh.asked) {
             // k_es_ask: two workgroups per CU; k_es_answer: one
-            const int64_t asks = round(std::min((most + sh.tile - 1) / sh.tile, std::max<int64_t>(512 / ng, 1)));
+            const int64_t asks = round(std::min((most + tile - 1) / tile, std::max<int64_t>(512 / ng, 1)));
             const int64_t answers = round(std::min<int64_t>((int64_t)ng * ((2 * most + kAskTile - 1) / kAskTile) + sh.ask_nb, 256));
             hipLaunchKernelGGL(k_es_ask, dim3((unsigned)asks, ng), dim3(kBlock), es_sort_lds((size_t)kAskEdges * 2, 8, sh.ask_nb), stream, src, dst, st, i,
                                mem.ranges, mem.asks);
             hipLaunchKernelGGL(k_es_answer, dim3((unsigned)answers), dim3(kBlock), es_sort_lds(kAskTile, 4, sh.nb) + ((size_t)1 << sh.ask_cb) / 4, stream,
                                st, i, mem.ranges, (const uint32_t*)mem.ask_tiles, (const uint2*)mem.asks, mem.bins, (uint32_t)nodes, mem.pairs);
         } else if (sh.binned)
-            hipLaunchKernelGGL(bin, dim3((unsigned)round((most + sh.tile - 1) / sh.tile), ng), dim3(kBlock), es_sort_lds((size_t)sh.tile * 2, 4, sh.nb), stream, src, dst, st, i, mem.bins, mem.pairs);
+            hipLaunchKernelGGL(bin, dim3((unsigned)round((most + tile - 1) / tile), ng), dim3(kBlock), es_sort_lds((size_t)tile * 2, 4, sh.nb), stream, src, dst, st, i, mem.bins, mem.pairs);
         else
             hipLaunchKernelGGL(k_es_count, dim3((unsigned)grid_for(most, kCountBlock, 1 << 20), ng), dim3(kCountBlock), 0, stream, src, dst, st,
                                i, mem.hc);
