@@ -584,12 +584,12 @@ __device__ __forceinline__ void es_bin_tile(const int32_t* __restrict__ src, con
         pairs[at[x >> (cb + 2)] + i] = x & ((1u << (cb + 2)) - 1u);
     }
 }
-__global__ __launch_bounds__(kBlock, 8) void k_es_bin(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, EsRun st, int64_t chunk,
+__global__ __launch_bounds__(kBlock, 8) void k_es_bin4(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, EsRun st, int64_t chunk,
                                                       EsBins bins, uint32_t* __restrict__ pairs)
 {
     es_bin_tile<4>(src, dst, st, chunk, bins, pairs);
 }
-__global__ __launch_bounds__(kBlock, 8) void k_es_bin2(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, EsRun st, int64_t chunk,
+__global__ __launch_bounds__(kBlock, 8) void k_es_bin(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, EsRun st, int64_t chunk,
                                                        EsBins bins, uint32_t* __restrict__ pairs)
 {
     es_bin_tile<2>(src, dst, st, chunk, bins, pairs);
@@ -1810,7 +1810,7 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
         }
     const int64_t crowd_bn = sh.bn() < kCrowdNodes ? sh.bn() : kCrowdNodes;
     const size_t crowd_lds = (size_t)crowd_bn * 4 + (size_t)crowd_bn / 8, bins_lds = es_bins_lds(sh.bn(), sh.room);
-    const auto bin = tile == 8192 ? k_es_bin8 : tile == 6144 ? k_es_bin6 : tile == 4096 ? k_es_bin : k_es_bin2;
+    const auto bin = tile == 8192 ? k_es_bin8 : tile == 6144 ? k_es_bin6 : tile == 4096 ? k_es_bin4 : k_es_bin;
     // (always what any run may need: the limit is the process's, and other threads' runs are of other sizes)
     if (sh.binned &&
         (hipFuncSetAttribute((const void*)k_es_ask, hipFuncAttributeMaxDynamicSharedMemorySize, kSortLds) != hipSuccess ||
