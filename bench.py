@@ -28,28 +28,29 @@ HBM_PEAK_GBPS = 8000.0
 # at that time, and `traffic` is reported as null when the sources have changed since.
 PMC = {
     "workload": "chunglu-111M",
-    "sources_sha256": "403af8245d638131ab4102c3fd4d2e34c6415a3ce170162cc5b1fc5f8e934924",
+    "sources_sha256": "71ee0937c601eef1713c44a3f4bb2b124b6a2ad627e724483ce7401e6246e898",
     "fetch_factor": 2.0,        # 2 GiB read  -> FETCH_SIZE 1,048,591 KiB
     "write_factor": 1.0,        # 2 GiB written -> WRITE_SIZE 2,097,152 KiB
-    "fetch_kib": {"k_tp_score": 1.42622e+07, "k_tp_lookup": 1.36622e+07},
-    "write_kib": {"k_tp_score": 7.32475e+06, "k_tp_lookup": 5.58579e+06},
+    "fetch_kib": {"k_tp_score": 1.42621e+07, "k_tp_lookup": 1.37060e+07},
+    "write_kib": {"k_tp_score": 7.32475e+06, "k_tp_lookup": 5.17638e+06},
     "launches": {"k_tp_score": 318, "k_tp_lookup": 317},
 }
 
 
-# The same for the edge-chunk path's two dominant kernels (one launch each per chunk) on its 111M-node workload.
+# The same for the edge-chunk path's three dominant kernels (one launch each per chunk) on its 111M-node workload.
 PMC_EDGE = {
     "workload": "edges-chunglu-111M-c1pct",
-    "sources_sha256": "d22306e150e0289bf821a1eefbccf649692f3b9fd1b842a9c790228a6509ce11",
-    "fetch_kib": {"k_es_bin": 1.71843e+08, "k_es_score_bins": 6.93455e+07},
-    "write_kib": {"k_es_bin": 1.58725e+07, "k_es_score_bins": 4.90061e+07},
+    "sources_sha256": "631f9189af6c224b0f4e4d29e8f72f136d3ad27d31805c1ebb1df3980e2b6db5",
+    "fetch_kib": {"k_es_ask": 6.31422e+06, "k_es_answer": 1.39492e+07, "k_es_score_bins": 5.35641e+07},
+    "write_kib": {"k_es_ask": 2.93644e+07, "k_es_answer": 1.87781e+07, "k_es_score_bins": 4.52095e+07},
     "launches": 100,
 }
 
 
 def edge_kernels(n):
-    """The kernels that grem_edge_stream_profile_* times: from 2^22 nodes on the edge ends are binned."""
-    return "k_es_bin+k_es_score_bins" if n >= 1 << 22 else "k_es_count"
+    """The kernels that grem_edge_stream_profile_* times: from 2^22 nodes on the edge ends are binned, from 2^25 on their labels
+    asked for beforehand."""
+    return "k_es_ask+k_es_answer+k_es_score_bins" if n >= 1 << 25 else "k_es_bin+k_es_score_bins" if n >= 1 << 22 else "k_es_count"
 
 
 def edge_sources_sha256():
