@@ -55,8 +55,11 @@ def edge_kernels(n):
 
 def edge_sources_sha256():
     import hashlib
-    with open(os.path.join(ROOT, "paper_2502_17846_amd", "csrc", "grem_edge_stream.hip"), "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    h = hashlib.sha256()
+    for name in ("grem_edge_stream.hip", "grem_es_estimate.hip.h"):
+        with open(os.path.join(ROOT, "paper_2502_17846_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def sources_sha256():

@@ -40,6 +40,7 @@
 #include <vector>
 
 #include "grem.h"
+#include "grem_es_estimate.hip.h"
 
 namespace {
 
@@ -207,47 +208,22 @@ __device__ __forceinline__ int es_assign(int lean, long long s0, long long s1, l
     return s1 < s0;
 }
 
-// An estimate in 8 bytes: both counts as whole numbers of 29 bits and, in the six bits above them, how many times they have
-// been halved, which is all of the doubles' value while no bit of it is lost.  Once one does not fit (a node has 29 edge ends or
-// more by then) the two are doubles in `est` and the 58 bits say where.
-constexpr uint32_t kPackBits = 29, kPackMask = (1u << kPackBits) - 1u, kPackWide = 7u << kPackBits;
-__device__ __forceinline__ bool es_is_wide(uint2 word) { return word.y >= kPackWide; }
-__device__ __forceinline__ size_t es_wide_place(uint2 word) { return (word.x & kPackMask) | (size_t)(word.y & kPackMask) << kPackBits; }
-__device__ __forceinline__ uint2 es_pack(uint32_t x, uint32_t y, uint32_t halved)
-{
-    return make_uint2(x | halved << kPackBits, y | (halved >> 3) << kPackBits);
-}
-__device__ __forceinline__ double2 es_unpack(uint2 word)
-{
-    const int halved = (int)(word.x >> kPackBits | (word.y >> kPackBits) << 3);
-    return make_double2(ldexp((double)(word.x & kPackMask), -halved), ldexp((double)(word.y & kPackMask), -halved));
-}
-// Alg. 1's blend of a packed estimate with the fresh counts, stored; the comparison of the two sides.  word, doubles: the stored
-// estimate, zero for a node that is not blended.  Where it grows out of 29 bits, the sum is rounded on its way into
-// the doubles as the doubles' own sum would be.
+// Alg. 1's blend of a packed estimate with the fresh counts (es_blend), stored; the comparison of the two sides.
 __device__ __forceinline__ int es_blend_packed(const EsRun& st, size_t node, uint2 word, double2 doubles, bool blend, uint32_t h0, uint32_t h1,
                                                size_t first_wide, uint32_t* wide)
 {
     uint2* const packed = reinterpret_cast<uint2*>(st.packed) + node;
-    if (es_is_wide(word)) {
-        const double x = (doubles.x + (double)h0) * 0.5, y = (doubles.y + (double)h1) * 0.5;
-        st.est[es_wide_place(word)] = make_double2(x, y);
-        return (y > x) - (x > y);
+    const EsBlended now = es_blend(word, doubles, blend, h0, h1);
+    if (now.fits) {
+        *packed = now.word;
+    } else if (es_is_wide(word)) {
+        st.est[es_wide_place(word)] = now.sums;
+    } else {
+        const size_t at = first_wide + atomicAdd(wide, 1u);
+        st.est[at] = now.sums;
+        *packed = es_wide_word(at);
     }
-    const uint32_t b = word.x >> kPackBits | (word.y >> kPackBits) << 3, halved = b + (blend ? 1u : 0u);
-    const uint32_t x0 = word.x & kPackMask, y0 = word.y & kPackMask;
-    if (b < kPackBits && ((h0 | h1) >> (kPackBits - b)) == 0u) {
-        const uint32_t x = x0 + (h0 << b), y = y0 + (h1 << b);
-        if (((x | y) >> kPackBits) == 0u) {
-            *packed = es_pack(x, y, halved);
-            return (y > x) - (x > y);
-        }
-    }
-    const u64 x = x0 + ((u64)h0 << b), y = y0 + ((u64)h1 << b);
-    const size_t at = first_wide + atomicAdd(wide, 1u);
-    st.est[at] = make_double2(ldexp((double)x, -(int)halved), ldexp((double)y, -(int)halved));
-    *packed = make_uint2((uint32_t)at & kPackMask, (uint32_t)(at >> kPackBits) | kPackWide);
-    return (y > x) - (x > y);
+    return now.lean;
 }
 
 // value of x in lane i, i uniform over the wave
