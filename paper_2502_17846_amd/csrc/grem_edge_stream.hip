@@ -70,8 +70,8 @@ struct EsRun {
     const uint32_t* blk_group;               // group of a block
     u64* S;                                  // [2][groups][2]: sizes, two copies
     u64* Lw;
-    double2* est;                            // counts in memory: the estimates; binned: those of `packed` that have outgrown it
-    u64* packed;                             // binned: the estimates in 8 bytes each
+    double2* est;                            // the estimates, a node's at its own place, or those of `packed` that have outgrown it
+    u64* packed;                             // binned, where there is memory for it: the estimates in 8 bytes each
     uint32_t* wide;                          // ... and per block how many have outgrown them
     u64 *mark, *mv0, *mv1, *nw;
     uint4* bs;                               // per block: movers to 0, to 1, those of either without a label
@@ -995,7 +995,8 @@ __global__ __launch_bounds__(kBlock, 8) void k_es_score_bins(EsRun st, int par, 
     uint32_t *mv0 = bits, *mv1 = bits + words, *base = mv1;                          // base: the chunk's nodes before a word
     uint32_t* cnt = bits + 2 * words;
     uint16_t* nodes = reinterpret_cast<uint16_t*>(cnt + room);
-    if (tid == 0) wide = st.wide[block];
+    const bool whole = st.packed == nullptr;                                         // the estimates are all doubles
+    if (tid == 0 && !whole) wide = st.wide[block];
 
     // counts of `count` nodes from `low` on (or, listed, of those in nodes[]) are there: their scores
     auto score = [&](uint32_t count, uint32_t low, bool listed, bool narrow, const uint32_t* seen) {
@@ -1020,7 +1021,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_es_score_bins(EsRun st, int par, 
                 est[u] = make_uint2(0u, 0u);
                 u64 labels = 0ull;
                 if (on[u]) labels = st.Lw[(node0 + rel[u]) >> 5];
-                if (on[u] && !first && !fixed) est[u] = reinterpret_cast<const uint2*>(st.packed)[node0 + rel[u]];
+                if (on[u] && !first && !fixed && !whole) est[u] = reinterpret_cast<const uint2*>(st.packed)[node0 + rel[u]];
                 old[u] = es_label(labels, rel[u]);                 // (a block starts at a whole word)
             }
 #pragma unroll
@@ -1029,7 +1030,8 @@ __global__ __launch_bounds__(kBlock, 8) void k_es_score_bins(EsRun st, int par, 
                 const bool blend = !first && !fixed && old[u] != kNone;
                 double2 doubles = make_double2(0.0, 0.0);
                 if (!blend) est[u] = make_uint2(0u, 0u);
-                if (es_is_wide(est[u])) doubles = st.est[es_wide_place(est[u])];
+                if (whole) est[u] = es_wide_word(node0 + rel[u]);
+                if (blend && es_is_wide(est[u])) doubles = st.est[es_wide_place(est[u])];
                 const int lean = es_blend_packed(st, node0 + rel[u], est[u], doubles, blend, h0[u], h1[u], node0, &wide);
                 if (first) continue;
                 const uint32_t t = answers >> (3u * old[u] + (uint32_t)(lean + 1)) & 1u;
@@ -1121,7 +1123,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_es_score_bins(EsRun st, int par, 
         es_store_words(st, word0 + lane, reinterpret_cast<const u64*>(mv0)[wave * nw + lane], reinterpret_cast<const u64*>(mv1)[wave * nw + lane],
                        es_load_labels(st, word0 + lane), movers);
     es_store_movers(st, movers, block);
-    if (tid == 0) st.wide[block] = wide;
+    if (tid == 0 && !whole) st.wide[block] = wide;
 }
 
 // the first c set bits of x (c <= their number).  Between "none" and "all" there is one word per partition and chunk.
@@ -1270,7 +1272,7 @@ __global__ __launch_bounds__(256) void k_es_expand(int64_t n, const u64* __restr
     if (sizes_out && blockIdx.x == 0 && threadIdx.x < 2) sizes_out[threadIdx.x] = (int64_t)S[threadIdx.x];
 }
 
-// nbr_counts_out of a binned run
+// nbr_counts_out of a run that kept its estimates in 8 bytes
 __global__ __launch_bounds__(256) void k_es_expand_packed(int64_t n, EsRun st, double2* out)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -1569,6 +1571,7 @@ struct EsShape {
     int ask_cb = 0, ask_tile = 0;          // ... nodes of a range (2^ask_cb)
     uint32_t ask_nb = 0;                   // ... and ranges, rounded up
     bool binned = false;
+    bool packed = false;                   // binned: the estimates in 8 bytes
     bool sparse = false;                   // binned: a chunk's nodes are so few that a block lists them
     int64_t room = 0;                      // ... and of how many it has room for the counts
     int64_t nodes = 0;                     // room for the state: the nodes and the groups' padding
@@ -1593,9 +1596,14 @@ constexpr int64_t kCrowdNodes = 32768;                       // a workgroup of k
 constexpr int64_t kHalfLds = 80 * 1000;
 constexpr int kSortLds = 160000;
 constexpr unsigned kCrowdGrid = 512;                         // workgroups of k_es_crowd: one per CU at a time
-// n: nodes of the run; groups: most groups side by side; ends: of a chunk's edge ends over all groups; bins: false
-// where there was no memory for the pairs (the counts take 8 bytes per node, the pairs up to 16)
-EsShape es_shape(int64_t n, int64_t groups, int64_t ends, int64_t chunks, bool bins = true)
+// The forms of a run, each of less memory than the one before it:
+//   full     binned, with estimates in 8 bytes beside the doubles and, where they pay, asks
+//   lean     binned, the estimates all doubles (in the caller's array if there is one), labels looked up, 1024 bins, one class, few blocks: 17 bytes per
+//            node (one with a caller's array) for 25, and a third of the bytes per end where labels are asked for
+//   counted  the counts in memory (8 bytes per node, the lean form's pairs up to 16)
+enum class EsForm { full, lean, counted };
+// n: nodes of the run; groups: most groups side by side; ends: of a chunk's edge ends over all groups
+EsShape es_shape(int64_t n, int64_t groups, int64_t ends, int64_t chunks, EsForm form)
 {
     EsShape s;
     // padding for every group, but no more than the nodes themselves take (a level of tiny groups goes in batches)
@@ -1608,17 +1616,19 @@ EsShape es_shape(int64_t n, int64_t groups, int64_t ends, int64_t chunks, bool b
         while (s.awpw < kMaxAdmitWords && n > s.an() * 256 && 2 * s.an() * groups <= n) s.awpw *= 2;
     };
     const int64_t per_mille = ends * 1000 / n;                 // ends of a chunk per thousand nodes
-    waves(per_mille <= kWideSparse && n >= 2 * kBinMinNodes ? 2 * kBinWaveWords : kBinWaveWords);
-    if (bins && n >= kBinMinNodes && room() < (1ll << 30) && ends <= 4 * n && chunks <= kBinMaxChunks) {
+    waves(form == EsForm::lean || (per_mille <= kWideSparse && n >= 2 * kBinMinNodes) ? 2 * kBinWaveWords : kBinWaveWords);
+    if (form != EsForm::counted && n >= kBinMinNodes && room() < (1ll << 30) && ends <= 4 * n && chunks <= kBinMaxChunks) {
+        const bool full = form == EsForm::full;
         s.binned = true;
+        s.packed = full;
         s.cb = s.wpw == kBinWaveWords ? 14 : 15;
-        while ((room() >> s.cb) >= kBins) ++s.cb;          // (at most 18)
+        while ((room() >> s.cb) >= (full ? kBins : kBlock)) ++s.cb;              // (at most 18; 20)
         auto number = [&](int cb) { return (uint32_t)((room() >> cb) / kBlock + 1) * kBlock; };
         s.nb = number(s.cb);
         s.sparse = per_mille <= kSparse;
         // (two workgroups share a CU; a bin with more nodes of the chunk than there is room for is counted node by node)
         s.room = (kHalfLds - s.bn() / 4) / 6 / 64 * 64;
-        s.asked = n >= kAskMinNodes || (2 * n >= kAskMinNodes && ends >= kAskMinEnds);
+        s.asked = full && (n >= kAskMinNodes || (2 * n >= kAskMinNodes && ends >= kAskMinEnds));
         if (s.asked) {
             s.ask_cb = s.cb > kAskBits ? s.cb : kAskBits;
             s.ask_nb = number(s.ask_cb);
@@ -1627,7 +1637,7 @@ EsShape es_shape(int64_t n, int64_t groups, int64_t ends, int64_t chunks, bool b
             s.tile = ends / 2 >= 512 * kBinTile ? kBinTile : kBinTile / 2;
             while (es_sort_lds(2 * s.tile, 4, s.nb) > kHalfLds) s.tile -= 2048;
         }
-        s.classes = ends / 2 / s.tile >= 256 ? 8 : 1;
+        s.classes = full && ends / 2 / s.tile >= 256 ? 8 : 1;
     } else {
         int wpw = 1;
         while (wpw < kMaxWaveWords && n > (int64_t)kBlock * wpw * 1024) wpw *= 2;
@@ -1669,7 +1679,7 @@ struct EsMemory {
         take(groups, (size_t)ngroups);
         take(blk_group, blocks);
         take(st.Lw, (size_t)(nodes / 32));
-        if (est_out && !sh.binned) st.est = (double2*)est_out;
+        if (est_out && !sh.packed) st.est = (double2*)est_out;
         else take(st.est, (size_t)nodes);
         take(st.mark, words); take(st.mv0, words); take(st.mv1, words); take(st.nw, words);
         take(st.bs, blocks);
@@ -1688,8 +1698,8 @@ struct EsMemory {
                 take(ask_tiles, (size_t)chunks * (sh.ask_nb + 1));
                 take(asks, (size_t)ends);
             }
-            take(st.packed, (size_t)nodes);
-            take(st.wide, blocks);
+            if (sh.packed) take(st.packed, (size_t)nodes);
+            if (sh.packed) take(st.wide, blocks);
             take(crowd.place, (size_t)chunks * sh.nb);
             take(crowd.bins, (size_t)chunks);
             take(crowd.hc, (size_t)sh.crowd_bins << sh.cb);
@@ -1745,13 +1755,15 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
     if (sh.binned) {
         clears.add(mem.bins.ends, align256((size_t)chunks * sh.nb * mem.bins.classes * 4));
         if (sh.asked) clears.add(mem.ranges.ends, align256((size_t)chunks * sh.ask_nb * sh.classes * 4));
-        clears.add(st.packed, (size_t)nodes * 8);
-        clears.add(st.wide, align256((size_t)blocks * 4));
+        if (sh.packed) {
+            clears.add(st.packed, (size_t)nodes * 8);
+            clears.add(st.wide, align256((size_t)blocks * 4));
+        }
     } else {
         clears.add(mem.hc, (size_t)nodes * 8);
-        clears.add(st.est, (size_t)est_nodes * 16);
     }
-    hipLaunchKernelGGL(k_es_clear, dim3(grid_for((sh.binned ? 8 : 24) * nodes / 64, 256, 16384)), dim3(256), 0, stream, clears);
+    if (!sh.packed) clears.add(st.est, (size_t)est_nodes * 16);
+    hipLaunchKernelGGL(k_es_clear, dim3(grid_for((sh.packed ? 8 : sh.binned ? 16 : 24) * nodes / 64, 256, 16384)), dim3(256), 0, stream, clears);
     auto round = [&](int64_t grid) { return (grid + sh.classes - 1) / sh.classes * sh.classes; };
     std::vector<uint32_t> crowded;                             // per chunk: its crowded bins
     if (sh.binned) {
@@ -1861,8 +1873,8 @@ int es_bipartition(const int32_t* src, const int32_t* dst, int64_t m, int64_t n,
     const int64_t chunks = (m + c_size - 1) / c_size, ends = 2 * c_size;
     EsShape sh;
     EsMemory mem;
-    for (const bool bins : {true, false}) {
-        sh = es_shape(n, 1, ends, chunks, bins);
+    for (const EsForm form : {EsForm::full, EsForm::lean, EsForm::counted}) {
+        sh = es_shape(n, 1, ends, chunks, form);
         mem.layout(nullptr, sh, 1, ends, chunks, nbr_counts_out);
         if (hipMallocAsync((void**)&ws, mem.bytes, stream) == hipSuccess) break;
         (void)hipGetLastError();
@@ -1887,7 +1899,7 @@ int es_bipartition(const int32_t* src, const int32_t* dst, int64_t m, int64_t n,
     if (rc == GREM_OK) {
         hipLaunchKernelGGL(k_es_expand, dim3(grid_for(n, 256, 16384)), dim3(256), 0, stream, n, (const u64*)mem.st.Lw, parts_out,
                            (const u64*)(mem.st.S + 2 * par), sizes_out);
-        if (sh.binned && nbr_counts_out)
+        if (sh.packed && nbr_counts_out)
             hipLaunchKernelGGL(k_es_expand_packed, dim3(grid_for(n, 256, 16384)), dim3(256), 0, stream, n, mem.st, (double2*)nbr_counts_out);
         if (hipGetLastError() != hipSuccess) rc = GREM_ERR_HIP;
     } else {
@@ -1923,8 +1935,8 @@ int es_bisection(const int32_t* src, const int32_t* dst, int64_t m, int64_t n, i
     size_t o_lev[4];                                   // two generations of the grouped edge list
     for (int i = 0; i < 4; ++i) o_lev[i] = carve((size_t)m * 4);
     size_t o_halves = off, o_run = off;                // sized by the run's nodes; its state is the last piece
-    for (const bool bins : {true, false}) {
-        sh = es_shape(n, most_groups < kMaxBatch ? most_groups : kMaxBatch, ends, c_max, bins);
+    for (const EsForm form : {EsForm::full, EsForm::lean, EsForm::counted}) {
+        sh = es_shape(n, most_groups < kMaxBatch ? most_groups : kMaxBatch, ends, c_max, form);
         o_run = o_halves + align256((size_t)sh.nodes / 4);
         mem.layout(nullptr, sh, kMaxBatch, ends, c_max, nullptr);
         if (hipMallocAsync((void**)&ws, o_run + mem.bytes, stream) == hipSuccess) break;

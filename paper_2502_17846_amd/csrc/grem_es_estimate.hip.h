@@ -31,13 +31,14 @@ struct EsBlended {
     double2 sums;
     int lean;         // +1 where side 1 holds more, -1 where side 0 does, 0: neither
 };
-// word, doubles: the stored estimate (doubles: of a wide word), zero for a node that is not blended.  Where it grows out of 29
-// bits, the sums are rounded on their way into the doubles as the doubles' own sums would be, and it is the doubles that are compared.
+// word, doubles: the stored estimate (doubles: of a wide word), zero for a node that is not blended (or a wide word and zeros, where
+// all estimates are doubles).  Where it grows out of 29 bits, the sums are rounded on their way into the doubles as the doubles' own sums would be, and it is the doubles that are compared.
 __host__ __device__ __forceinline__ EsBlended es_blend(uint2 word, double2 doubles, bool blend, uint32_t h0, uint32_t h1)
 {
     EsBlended r{};
     if (es_is_wide(word)) {
-        r.sums = make_double2((doubles.x + (double)h0) * 0.5, (doubles.y + (double)h1) * 0.5);
+        const double share = blend ? 0.5 : 1.0;
+        r.sums = make_double2((doubles.x + (double)h0) * share, (doubles.y + (double)h1) * share);
     } else {
         const uint32_t b = es_halved(word), halved = b + (blend ? 1u : 0u);
         const uint32_t x0 = word.x & kPackMask, y0 = word.y & kPackMask;

@@ -130,6 +130,26 @@ def test_without_the_memory_for_a_faster_form(fake):
     """, sizes="big, ends = mem(1 << 29), mem(1 << 27)")
 
 
+def test_edge_chunks_in_as_little_memory_as_the_binned_form_can_do_with(fake):
+    # bytes that a binned run takes whose estimates are all doubles, and one less: 17 per node (one with the caller's array), the pairs, 6 to 7 KB per chunk
+    _run(fake, """
+    def stream(n, m, chunks, counts):
+        return lib.grem_edge_stream_bipartition(ends, ends, L(m), L(n), L(-(-m // chunks)), L(n), big, I(0), big, None, big if counts else None, None)
+    def bisection(n, m, levels, chunks):
+        return lib.grem_recursive_bisection(ends, ends, L(m), L(n), I(levels), L(chunks), D(2.0), big, I(0), big, None)
+    for f, a, most in ((stream, (5_000_000, 9_000_000, 4, 1), 26_864_384), (stream, (5_000_000, 9_000_000, 4, 0), 107_080_448),
+                       (stream, (4_200_000, 1_000_000, 10, 1), 4_875_776), (stream, (16_000_000, 14_000_000, 1, 1), 140_304_384),
+                       (stream, (9_000_000, 3_000_000, 20, 1), 9_260_032), (bisection, (5_000_000, 9_000_000, 3, 10), 404_398_848)):
+        reset()
+        assert f(*a) == 0 and sum(x[0] == "refused" for x in text()) == 0
+        reset(most)
+        assert f(*a) == 0, a
+        t = text()
+        assert sum(x[0] == "refused" for x in t) == 1 and any("k_es_bin" in x[1] for x in t if x[0] == "launch"), (a, t[:4])
+        assert not any("k_es_count" in x[1] or "packed" in x[1] for x in t)
+    """, sizes="big, ends = mem(1 << 28), mem(1 << 26)")
+
+
 def test_bucket_tiles_by_edges_and_buckets(fake):
     # tiles of 8,192 edges: 2^25 edges or more, 64 buckets or more, and 6.5e9 edges times buckets
     _run(fake, """
