@@ -67,7 +67,7 @@ def sources_sha256():
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2502_17846_amd", "csrc")
     # the files the two profiled kernels are compiled from
-    for name in ("grem.hip", "grem_kernels.hip.h", "grem_twophase.hip.h"):
+    for name in ("grem.hip", "grem_kernels.hip.h", "grem_lookup_shares.hip.h", "grem_twophase.hip.h"):
         with open(os.path.join(csrc, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()

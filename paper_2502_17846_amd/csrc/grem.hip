@@ -75,9 +75,9 @@ constexpr int64_t kMinSlices = 256;        // slices per chunk wanted: one per C
 constexpr int64_t kMaxSegments = 1ll << 22;   // chunks * column blocks
 constexpr int64_t kCutPackMinN = 1 << 20;  // edge cut: int32 labels of more vertices outgrow an XCD's 4 MB of L2
 constexpr size_t kScoreLds16 = 150 * 1024, kScoreLds32 = 158 * 1024;   // k_tp_score's LDS: with the static counters for k <= 16
-constexpr int kLookupGrid = 256;           // workgroups of a chunk's look-up launch (planned runs, 512 | 256: 13.9M vertices in chunks of 2^17 and k = 32 8.75 | 8.33 ms,
-                                           // k = 16 6.85 | 6.56; 20M in chunks of 300,000 6.80 | 6.53; 25M and 111M in chunks of 2^20 the same; 128 and 384 were slower)
-constexpr int64_t kLookupSweep = 8192;     // workgroups of a look-up launch over many chunks: each copies a block's labels first (13.9M vertices, 106 blocks,
+constexpr uint32_t kLookupFew = 256, kLookupMany = 512;   // workgroups of a chunk's look-up launch: short shares, long ones (grem_lookup_shares.hip.h; 128
+                                           // and 384 for 256 were slower, at 25M and 111M vertices in chunks of 2^20 any was the same)
+constexpr uint64_t kLookupSweep = 8192;    // workgroups of a look-up launch over all chunks: each copies a block's labels first (13.9M vertices, 106 blocks,
                                            // with one per 8192 entries 49,000 of them: 0.74 ms, so 0.38; 4096: k = 24 1.05 ms for 0.97, 16,384: k = 16 0.93 for 0.90)
 constexpr int64_t kPlaceGrid = 1024;       // workgroups of k_tp_place wanted: four per CU
 constexpr int kMaxParts = kPlanParts;      // parts of a slice (hub share) in the re-layout
@@ -335,6 +335,7 @@ struct PlanData {
     std::vector<uint32_t> nvs;              // hub shares per chunk (host copy of pl.ch_nvs)
     std::vector<uint32_t> chunk_hubs;       // hubs per chunk (host copy of pl.ch_nh)
     std::vector<u64> chunk_hub0;            // hubs of the chunks before it (host copy of pl.ch_hub0)
+    std::vector<u64> chunk_entries;         // entries of the chunk's rows (0 in a graph without hubs)
     int share_hubs = 0;
     int max_k = 0;                          // largest k whose score workgroups fit the LDS
 };
@@ -374,7 +375,7 @@ void plan_stage1(Carver &c, const PlanDims &d, SweepPlan &pl, u64 *&pmisc) {
     c.take(pl.ch_nvs, nch);
     c.take(pl.ch_hbase, nch + 1);
     c.take(pl.ch_reg0, nch + 1);
-    c.take(pl.ch_hub0, nch + 1);
+    c.take(pl.ch_hub0, nch + 1);                 // (behind the two before it: one copy to the host brings the three)
     c.take(pmisc, 16);
 }
 
@@ -468,13 +469,19 @@ int build_plan(PlanData &P, const RowT *rowptr, const int32_t *colidx, int64_t n
     P.nvs.assign((size_t)geo.nch, 0u);
     P.chunk_hubs.assign((size_t)geo.nch, 0u);
     P.chunk_hub0.assign((size_t)geo.nch + 1, 0ull);
+    P.chunk_entries.assign((size_t)geo.nch, 0ull);
     if (P.total_hubs != 0) {
+        std::vector<u64> starts((size_t)(pl.ch_hub0 - pl.ch_hbase) + (size_t)geo.nch + 1);
         if (hipMemcpyAsync(P.nvs.data(), pl.ch_nvs, (size_t)geo.nch * 4, hipMemcpyDeviceToHost, stream) != hipSuccess ||
             hipMemcpyAsync(P.chunk_hubs.data(), pl.ch_nh, (size_t)geo.nch * 4, hipMemcpyDeviceToHost, stream) != hipSuccess ||
-            hipMemcpyAsync(P.chunk_hub0.data(), pl.ch_hub0, ((size_t)geo.nch + 1) * 8, hipMemcpyDeviceToHost, stream) !=
-                hipSuccess)
+            hipMemcpyAsync(starts.data(), pl.ch_hbase, starts.size() * 8, hipMemcpyDeviceToHost, stream) != hipSuccess) {
+            (void)hipStreamSynchronize(stream);
             return GREM_ERR_HIP;
+        }
         if (!L.read_back(h, P.pmisc, sizeof(h))) return L.err;
+        const u64 *hub = starts.data(), *regular = hub + (pl.ch_reg0 - pl.ch_hbase), *hubs = hub + (pl.ch_hub0 - pl.ch_hbase);
+        for (int c = 0; c < geo.nch; ++c) P.chunk_entries[c] = hub[c + 1] - hub[c] + regular[c + 1] - regular[c];
+        P.chunk_hub0.assign(hubs, hubs + geo.nch + 1);
     } else if (L.err) {
         return L.err;
     }
@@ -844,23 +851,33 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
     const size_t coarse_row = (size_t)(kAdmitTilesMax / kCoarseTiles) * (size_t)k;
     if (hubs_in_admission) L.memset(t.coarse, 0, 2 * coarse_row * 4);
 
-    // look-ups of the labels of chunks [c0, c0 + count): shares per column block sized so that one
-    // launch fills the chip without cutting the blocks' streams into crumbs
+    // look-ups of the labels of chunk c0, or of all chunks (c0 < 0)
     // `mark`: seeded runs, first pass: the row fields the score kernels read are those of Rdyn, where
     // bit 0 also marks the tuples whose neighbour is unassigned (set by the initial look-up from global
     // memory, cleared by the look-up of the neighbour's chunk)
-    auto lookup = [&](int c0, int count, int cmin, bool from_lds, bool mark, const uint8_t *labels4 = nullptr) {
+    auto lookup = [&](int c0, int cmin, bool from_lds, bool mark, const uint8_t *labels4 = nullptr) {
         if (cmin >= geo.nch) return;
-        const int64_t per_block = P.nnz / geo.nblk + 1;
-        int spb = kLookupGrid / geo.nbc;
-        const int64_t by_work = per_block / 8192 + 1;
-        if (spb > by_work) spb = (int)by_work;
-        if (count > 1 && spb > kLookupSweep / ((int64_t)count * geo.nbc)) spb = (int)(kLookupSweep / ((int64_t)count * geo.nbc));
-        if (spb < 1) spb = 1;
-        const dim3 grid((unsigned)(geo.nbc * spb), (unsigned)count);
+        const uint64_t groups = P.slots / 8;
+        LookupShares deal{1u, 1u, 0u};
+        if (c0 < 0) {
+            deal.per = (uint32_t)std::max<uint64_t>(groups / kLookupSweep + 1, 1024);
+        } else {
+            // (workgroups beyond the blocks' shares cost 2 us a launch, so that `many` are launched for a chunk of long rows only: as a
+            // graph's entries go both ways, its columns are then as long.  Whole eights where there are as many: a share has
+            // the same place among the XCDs whatever its block, see k_tp_lookup)
+            const uint32_t by_work = (uint32_t)std::min<int64_t>(P.nnz / geo.nblk / 8192 + 1, kLookupMany);
+            auto per_block = [&](uint32_t all) {
+                const uint32_t w = std::max(std::min(all / (uint32_t)geo.nbc, by_work), 1u);
+                return w < 8 ? w : w / 8 * 8;
+            };
+            const bool lengthy = geo.cb <= 17 && P.chunk_entries[(size_t)c0] / 8 > (u64)kLookupFew * kLookupLong;       // (128 KB of labels: one workgroup per CU)
+            deal.few = per_block(kLookupFew);
+            deal.many = lengthy ? per_block(kLookupMany) : deal.few;
+        }
+        const dim3 grid(c0 < 0 ? lookup_sweep_grid(groups, (uint32_t)geo.nblk, deal) : (uint32_t)geo.nbc * deal.many);
         auto go = [&](auto kernel, size_t lds) {
             hipLaunchKernelGGL(kernel, grid, dim3(kTpThreads), lds, stream, P.T, t.Lx, P.R, t.Rdyn, tb,
-                               (const uint8_t *)st.Lc, labels4, n, c0, cmin, spb);
+                               (const uint8_t *)st.Lc, labels4, n, c0, cmin, deal);
         };
         L.run(GREM_KERNEL_LOOKUP, [&] {
             if (wide) {
@@ -876,12 +893,7 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
     // with 16 partitions in four bits, where the first pass reads its row fields from Rdyn and the initial look-up,
     // from global memory, marks the entries there.
     const bool partly = seed != nullptr && !st.seed_complete, marks = partly && k == 16;
-    if (seed) {        // the seeds are the labels every first-pass look-up starts from
-        for (int c0 = 0; c0 < geo.nch; c0 += 32768) {
-            const int count = geo.nch - c0 < 32768 ? geo.nch - c0 : 32768;
-            lookup(c0, count, 0, !marks, marks);
-        }
-    }
+    if (seed) lookup(-1, 0, !marks, marks);          // the seeds are the labels every first-pass look-up starts from
     L.mark();
     if (fixed_labels) {                     // counts only: nothing to admit, no new labels to look up
         const bool skip = partly && k == 32;
@@ -1022,7 +1034,7 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
             }
             // the chunk's new labels, looked up for every row that will read them: rows of later chunks in
             // this pass, rows of this and earlier chunks in the next pass (if there is one)
-            lookup((int)c, 1, pass == R ? (int)c + 1 : 0, true, marks && pass == 0, packed_now);
+            lookup((int)c, pass == R ? (int)c + 1 : 0, true, marks && pass == 0, packed_now);
         }
         L.mark();
     }

@@ -45,6 +45,7 @@
 #include <stdint.h>
 
 #include "grem_kernels.hip.h"
+#include "grem_lookup_shares.hip.h"
 
 namespace grem {
 
@@ -1070,10 +1071,9 @@ __global__ __launch_bounds__(kPlaceThreads) __attribute__((amdgpu_waves_per_eu(8
 }
 
 // ------------------------------------------------------------------------------------------------
-// look-up (phase 1 of the score): the tuples of the column blocks of chunk `c0 + blockIdx.y`,
-// restricted to row chunks >= cmin, get their labels.  Workgroup blockIdx.x handles share
-// (blockIdx.x % spb) of block (blockIdx.x / spb) of the chunk: an equal part of the block's tuples
-// in T, which are one contiguous piece.
+// look-up (phase 1 of the score): the tuples of the column blocks of chunk `c0`, or of all chunks (a sweep), restricted to row
+// chunks >= cmin, get their labels.  A workgroup handles a share of a block (grem_lookup_shares.hip.h): an equal part of the
+// block's tuples in T, which are one contiguous piece.
 //   T  (read)   : per group of eight tuples 24 bytes: the index of the word of Lx their labels go to,
 //                 then their columns in the block, 20 bits each
 //   Lx (written): the label of every tuple, LB = 4 bits each (8 when k > 16), sub-segments ordered (c', r, jb): a group's
@@ -1102,12 +1102,28 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(8, 8
                                                           uint16_t *__restrict__ Rdyn, TpTables tb,
                                                           const uint8_t *__restrict__ Lc,
                                                           const uint8_t *__restrict__ Lc4, int64_t n, int c0,
-                                                          int cmin, int spb) {
+                                                          int cmin, LookupShares deal) {
     static_assert((FROM_LDS || LB == 4) && (!WRITE_R || LB == 4), "a byte per label tells a missing one by itself");
     extern __shared__ uint32_t tab[];      // FROM_LDS: 2^cb labels, LB bits each
     const int tid = threadIdx.x;
-    const int c = c0 + (int)blockIdx.y;
-    const int m = (int)blockIdx.x / spb, s = (int)blockIdx.x % spb;
+    int c, m, s;
+    if (deal.per) {                        // the last block whose first workgroup is this one or one before it
+        int first = 0, end = tb.nblk;
+        auto first_of = [&](int j) { return lookup_first((uint32_t)(tb.tstart[(size_t)j * tb.nch] >> 3), (uint32_t)j, deal); };
+        while (end - first > 1) {
+            const int step = (end - first + 63) / 64, at = first + lane_id() * step;
+            const unsigned long long yes = __ballot(at < end && first_of(at) <= blockIdx.x);
+            first += (__popcll(yes) - 1) * step;
+            if (end > first + step) end = first + step;
+        }
+        c = first / tb.nbc;
+        m = first % tb.nbc;
+        s = (int)(blockIdx.x - first_of(first));
+    } else {
+        c = c0;
+        m = (int)(blockIdx.x / deal.many);
+        s = (int)(blockIdx.x % deal.many);
+    }
     const int64_t chunk_lo = (int64_t)c * tb.chunk;
     const int64_t chunk_hi = (chunk_lo + tb.chunk < n) ? chunk_lo + tb.chunk : n;
     const int64_t block_lo = chunk_lo + ((int64_t)m << tb.cb);
@@ -1115,7 +1131,9 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(8, 8
     const int jb = c * tb.nbc + m;
     const u64 *ts = tb.tstart + (size_t)jb * tb.nch;       // ts[c'] for c' = 0..nch (ts[nch] = end of block)
     const u64 lo = ts[cmin], hi = ts[tb.nch];
-    const u64 groups = (hi - lo) >> 3;                      // (every sub-segment is a multiple of 8 tuples)
+    const u64 groups = (hi - lo) >> 3;                      // (every sub-segment is a multiple of 8 tuples; fewer than 2^32 groups)
+    const int spb = (int)(deal.per ? lookup_sweep_shares((uint32_t)(lo >> 3), (uint32_t)(hi >> 3), deal) : lookup_chunk_shares((uint32_t)groups, deal));
+    if (s >= spb) return;
     const u64 g0 = groups * (u64)s / (u64)spb, g1 = groups * (u64)(s + 1) / (u64)spb;
     if (g0 >= g1) return;
     const uint32_t ng = (uint32_t)(g1 - g0);
