@@ -1275,17 +1275,17 @@ bool one_takes(int64_t n, int32_t k, int64_t cl, unsigned long long maxdeg, unsi
 // (false: no memory for it, nothing enqueued)
 template <typename RowT>
 bool run_one(const RowT *rowptr, const int32_t *colidx, int64_t n, int32_t k, double slack, int64_t cl, int32_t R, int32_t *labels_out,
-             int64_t *sizes_out, uint32_t *estimates_out, unsigned long long nnz, Arena &mem, Launcher &L, CallState<uint8_t> &st) {
+             int64_t *sizes_out, uint32_t *estimates_out, unsigned long long nnz, unsigned long long maxdeg, Arena &mem, Launcher &L, CallState<uint8_t> &st) {
     uint32_t *E = nullptr, *rec = nullptr;
     const bool external_E = estimates_out != nullptr;
     if (!carve(mem, [&](Carver &c) { c.take(E, external_E || R == 0 ? 0 : (size_t)n * (size_t)k); c.take(rec, (size_t)nnz + 16); })) return false;
-    const auto kernel = k <= 4 ? k_one_run<RowT, 4> : k_one_run<RowT, 8>;
+    const auto kernel = k <= 2 ? k_one_run<RowT, 2> : k <= 4 ? k_one_run<RowT, 4> : k_one_run<RowT, 8>;
     if (!set_lds((const void *)kernel, one_lds_bytes(n, cl, k), kOneLds)) { L.err = GREM_ERR_HIP; return true; }
     if (external_E) E = estimates_out;
     L.mark();
     if (nnz)
         L.run(GREM_KERNEL_RELAYOUT, [&] {
-            hipLaunchKernelGGL((k_one_entries<RowT>), dim3((unsigned)((n + 3) / 4 < 2048 ? (n + 3) / 4 : 2048)), dim3(256), 0, L.stream, rowptr, colidx,
+            hipLaunchKernelGGL((k_one_entries<RowT>), dim3((unsigned)((n + 3) / 4 < 2048 ? (n + 3) / 4 : 2048), (unsigned)((maxdeg + kOnePart - 1) / kOnePart)), dim3(256), 0, L.stream, rowptr, colidx,
                                n, cl, rec);
         });
     L.run(GREM_KERNEL_SCORE, [&] {
@@ -1493,7 +1493,7 @@ int run_partition(const RowT *rowptr, const int32_t *colidx, int64_t n, int32_t 
             if (counts) long_counts = (const uint32_t *)(h + 32);
             if constexpr (sizeof(LabelT) == 1)
                 if (one_takes(n, k, cl, maxdeg, h[3], o) &&
-                    run_one<RowT>(rowptr, colidx, n, k, slack, cl, R, labels_out, sizes_out, estimates_out, h[3], mem, L, st)) {
+                    run_one<RowT>(rowptr, colidx, n, k, slack, cl, R, labels_out, sizes_out, estimates_out, h[3], maxdeg, mem, L, st)) {
                     mem.release_all();
                     return L.err;
                 }

@@ -21,22 +21,41 @@ constexpr size_t kOneLds = 148 * 1024;
 // counters of 16 bits, whole words per row; then the labels
 inline size_t one_lds_bytes(int64_t n, int64_t cl, int k) { return (size_t)cl * ((k + 1) / 2) * 4 + (size_t)(n + 1 + 15) / 16 * 16; }
 
-// rec[e] = column | row in its chunk << 16, a wave per row; a column that is no vertex becomes n
+// rec[e] = column | row in its chunk << 16; a column that is no vertex becomes n.  A wave per row for a row's first kOnePart entries
+// (blockIdx.y = 0), and for part y of the rows that are so long a wave per 64 rows, which finds them: one wave's 940 turns were
+// a row of 60,000 entries.
+constexpr int kOnePart = 2048;
 template <typename RowT>
 __global__ __launch_bounds__(256) void k_one_entries(const RowT *__restrict__ rowptr, const int32_t *__restrict__ colidx, int64_t n, int64_t cl,
                                                      uint32_t *__restrict__ rec) {
-    const int64_t waves = (int64_t)gridDim.x * 4;
-    for (int64_t v = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); v < n; v += waves) {
+    const int64_t waves = (int64_t)gridDim.x * 4, first = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), skip = (int64_t)blockIdx.y * kOnePart;
+    auto part = [&](int64_t v, int64_t begin, int64_t end) {
         const uint32_t row = (uint32_t)(v % cl) << 16;
-        for (int64_t e = (int64_t)rowptr[v] + lane_id(); e < (int64_t)rowptr[v + 1]; e += 64) {
+        begin += skip;
+        if (end - begin > kOnePart) end = begin + kOnePart;
+        for (int64_t e = begin + lane_id(); e < end; e += 64) {
             const uint32_t col = (uint32_t)colidx[e];
             rec[e] = (col < (uint32_t)n ? col : (uint32_t)n) | row;
+        }
+    };
+    if (blockIdx.y == 0) {
+        for (int64_t v = first; v < n; v += waves) part(v, (int64_t)rowptr[v], (int64_t)rowptr[v + 1]);
+        return;
+    }
+    for (int64_t v0 = first * 64; v0 < n; v0 += waves * 64) {
+        const int64_t v = v0 + lane_id();
+        unsigned long long some = __ballot(v < n && (int64_t)rowptr[v + 1] - (int64_t)rowptr[v] > skip);
+        for (; some; some &= some - 1ull) {
+            const int64_t u = v0 + __builtin_ctzll(some);
+            part(u, (int64_t)rowptr[u], (int64_t)rowptr[u + 1]);
         }
     }
 }
 
-// KM: room for k partitions (4 or 8).  A thread takes eight neighbouring entries at a time: the lanes of a wave are then
-// in different rows more often than not, and their counters seldom the same word (an entry per lane: 269 us for 229).
+// KM: room for k partitions (2, 4 or 8).  A thread takes eight neighbouring entries at a time: the lanes of a wave are then
+// in different rows more often than not, and their counters seldom the same word (an entry per lane: 269 us for 229).  With a word
+// per row, lanes in one long row would all queue at it (10,000 vertices, k = 2, 250,000 entries, most of
+// them in rows of 200 to 60,000: 500 to 660 us, so 235 to 270; in launches 390 to 550).
 template <typename RowT, int KM>
 __global__ __launch_bounds__(kOneThreads) void k_one_run(const RowT *__restrict__ rowptr, const uint32_t *__restrict__ rec, int n, int k, int cl,
                                                          int R, int P, const uint8_t *__restrict__ Lc, const long long *__restrict__ S,
@@ -78,9 +97,20 @@ __global__ __launch_bounds__(kOneThreads) void k_one_run(const RowT *__restrict_
         uint32_t l[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) l[u] = q * U + u - f0 < f1 - f0 ? lab[r[u] & 0xFFFFu] : none;
+        if constexpr (KM == 2) {                     // (a word per row: what neighbouring entries of a row add is added up first)
+            uint32_t sum = 0;
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (l[u] != none) atomicAdd(&hist[(r[u] >> 16) * kk + (l[u] >> 1)], l[u] & 1u ? 65536u : 1u);
+            for (int u = 0; u < U; ++u) {
+                sum += l[u] == none ? 0u : l[u] ? 65536u : 1u;
+                if (u + 1 < U && r[u] >> 16 == r[u + 1 < U ? u + 1 : u] >> 16) continue;
+                if (sum) atomicAdd(&hist[r[u] >> 16], sum);
+                sum = 0;
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (l[u] != none) atomicAdd(&hist[(r[u] >> 16) * kk + (l[u] >> 1)], l[u] & 1u ? 65536u : 1u);
+        }
     };
     request(ahead, first[0] / U + tid, 0);
     for (int pass = 0; pass <= R; ++pass) {

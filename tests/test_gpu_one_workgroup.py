@@ -7,6 +7,7 @@ import torch
 
 import oracle
 from paper_2502_17846_amd import binding as B
+from tests.test_gpu_id_orders import _ms
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -48,6 +49,43 @@ def test_equals_the_oracle(n, degree, k, chunk, passes, slack, seeded, hubs, bit
     assert np.array_equal(est.cpu().numpy().view(np.uint32).reshape(n, k), want[2].reshape(n, k))
     again = B.grem_partition_seeded(rp, ci, n, k, slack, chunk, passes, sd)
     assert torch.equal(lab, again)
+
+
+# rows of several parts of k_one_entries, on their edges; a count of 65,535 in either half of a word, and a row too long for it
+@pytest.mark.parametrize("k", [1, 2, 3, 8])
+@pytest.mark.parametrize("longest", [2048, 2049, 4096, 60_001, 65_535, 65_536])
+def test_long_rows(longest, k):
+    n, chunk, passes = 5000, 700, 2
+    rng = np.random.default_rng(longest)
+    deg = rng.poisson(3, n)
+    deg[[0, 699, 700, 4000, n - 1]] = longest, 2047, longest - 1, 2 * 2048 + 1, longest
+    rowptr = np.zeros(n + 1, np.int64)
+    np.cumsum(deg, out=rowptr[1:])
+    colidx = rng.integers(0, n, rowptr[-1]).astype(np.int32)
+    seed = (np.arange(n) % k).astype(np.int32)
+    for row, of in ((0, 0), (n - 1, k - 1)):             # all neighbours in one partition
+        colidx[rowptr[row]:rowptr[row + 1]] = rng.integers(0, (n - k) // k, longest) * k + of
+    want = oracle.partition_seeded(rowptr, colidx, n, k, 1.05, chunk, passes, seed, return_state=True)
+    rp, ci, sd = (torch.as_tensor(a).to(DEV) for a in (rowptr, colidx, seed))
+    lab, sizes, est = B.grem_partition_state(rp, ci, n, k, 1.05, chunk, passes, sd)
+    assert np.array_equal(lab.cpu().numpy(), want[0])
+    assert sizes.cpu().numpy().tolist() == want[1].tolist()
+    assert np.array_equal(est.cpu().numpy().view(np.uint32).reshape(n, k), want[2].reshape(n, k))
+
+
+# measured, in one workgroup and in launches (which a long_row_degree asks for): 266 and 465 us, 261 and 412, 211 and 430
+@pytest.mark.parametrize("rows,longest", [(3, 60_000), (200, 1000), (1, 60_000)])
+def test_long_rows_are_no_slower_than_in_launches(rows, longest):
+    n, k = 10_000, 2
+    rng = np.random.default_rng(1)
+    deg = rng.poisson(5, n)
+    deg[rng.choice(n, rows, replace=False)] = longest
+    rowptr = np.zeros(n + 1, np.int64)
+    np.cumsum(deg, out=rowptr[1:])
+    rp, ci = torch.as_tensor(rowptr).to(DEV), torch.as_tensor(rng.integers(0, n, rowptr[-1]).astype(np.int32)).to(DEV)
+    took = [_ms(lambda: B.grem_partition(rp, ci, n, k, 1.05, 1024, 2, options=o), 20) for o in (B.options(), B.options(long_row_degree=16_384))]
+    print(f"[result] {rows} rows of {longest}: {took} ms", flush=True)
+    assert took[0] <= 1.1 * took[1]
 
 
 def test_without_room_for_it_in_the_workspace():
