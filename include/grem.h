@@ -286,7 +286,7 @@ int grem_profile_read_marks(double *ms_out, int32_t capacity);
  * src, dst: m int32 each; seed_parts: n int32, read only at the first chunk's nodes; parts_out: n
  * int32; sizes_out: 2 int64 or NULL; nbr_counts_out: n*2 doubles, row-major, or NULL (when given it
  * may be the working storage).  All device pointers.  Scratch memory is allocated on `stream` for the
- * call (about 10n bytes, 16n more when nbr_counts_out is NULL; or, from 2^22 nodes on if there is memory for it, 25n + 8*c_size,
+ * call (about 10n bytes, 16n more when nbr_counts_out is NULL; or, from 2^22 nodes on if there is memory for it, 26n + 8*c_size,
  * from 2^24 or 2^25 nodes on 16*c_size more, plus 6 to 290 KB per chunk, or else 18n + 8*c_size, 2n + 8*c_size when nbr_counts_out is
  * given, plus 7 KB per chunk).  The call checks the endpoints' range and the seed (one small read-back) before
  * it enqueues the remaining chunks.
@@ -311,7 +311,7 @@ int grem_edge_stream_bipartition(const int32_t *src, const int32_t *dst, int64_t
  * smaller half (0 on a tie).  A node of group g in half b moves to group 2g + b.
  * seed_bits: levels*n int32; labels_out: n int32, each in [0, 2^levels).  Device pointers.  Scratch
  * (25 bytes per edge and 46 per node, up to 71 with many groups of few nodes; from 2^22 nodes on, if there is memory for
- * it, 47 to 73 per node instead, or 39 to 57, 8 to 24 bytes per edge of a chunk and 6 to 290 KB per chunk) is allocated on `stream`; the groups
+ * it, 48 to 74 per node instead, or 39 to 57, 8 to 24 bytes per edge of a chunk and 6 to 290 KB per chunk) is allocated on `stream`; the groups
  * of a level run side by side, and the call reads back a few counters per level and batch of 1024 groups.  Errors as for grem_edge_stream_bipartition, plus GREM_ERR_ARG for levels
  * outside 1..20, chunks < 1, balance_slack < 1. */
 int grem_recursive_bisection(const int32_t *src, const int32_t *dst, int64_t m, int64_t n,

@@ -378,7 +378,7 @@ struct EsBins {
 };
 
 // (gridDim.x is a multiple of the classes; tile: edges of a workgroup of k_es_bin or k_es_ask; hist: a word per bin or, where
-// labels are asked for, per bin and class)
+// labels are asked for, per bin and class.  kBinTile is a multiple of the tile, the tile of kBlock.)
 __global__ __launch_bounds__(kBlock) void k_es_hist(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                                                     EsRun st, EsBins bins, EsBins ranges, int tile)
 {
@@ -392,15 +392,16 @@ __global__ __launch_bounds__(kBlock) void k_es_hist(const int32_t* __restrict__ 
     for (uint32_t i = threadIdx.x; i < cells; i += kBlock) hist[i] = 0u;
     __syncthreads();
     bool bad = false;
-    for (int64_t t = lo + (int64_t)blockIdx.x * tile; t < hi; t += (int64_t)gridDim.x * tile) {
-        const int64_t end = hi - t < tile ? hi : t + tile;
+    // (as many of its tiles at a time as make kBinTile edges)
+    const int64_t step = (int64_t)gridDim.x * tile;
+    for (int64_t t = lo + (int64_t)blockIdx.x * tile; t < hi; t += kBinTile / tile * step) {
         uint32_t s[kBinPer], d[kBinPer];
 #pragma unroll
         for (int u = 0; u < kBinPer; ++u) {
-            const int64_t e = t + u * kBlock + threadIdx.x;
-            s[u] = e < end ? (uint32_t)src[e] : g.nv;
-            d[u] = e < end ? (uint32_t)dst[e] : g.nv;
-            bad |= e < end && (s[u] >= g.nv || d[u] >= g.nv);
+            const int64_t e = t + u * kBlock / tile * step + u * kBlock % tile + threadIdx.x;
+            s[u] = e < hi ? (uint32_t)src[e] : g.nv;
+            d[u] = e < hi ? (uint32_t)dst[e] : g.nv;
+            bad |= e < hi && (s[u] >= g.nv || d[u] >= g.nv);
         }
 #pragma unroll
         for (int u = 0; u < kBinPer; ++u) {
@@ -569,11 +570,6 @@ __global__ __launch_bounds__(kBlock, 8) void k_es_bin(const int32_t* __restrict_
                                                        EsBins bins, uint32_t* __restrict__ pairs)
 {
     es_bin_tile<2>(src, dst, st, chunk, bins, pairs);
-}
-__global__ __launch_bounds__(kBlock, 8) void k_es_bin6(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, EsRun st, int64_t chunk,
-                                                       EsBins bins, uint32_t* __restrict__ pairs)
-{
-    es_bin_tile<6>(src, dst, st, chunk, bins, pairs);
 }
 __global__ __launch_bounds__(kBlock, 8) void k_es_bin8(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, EsRun st, int64_t chunk,
                                                        EsBins bins, uint32_t* __restrict__ pairs)
@@ -962,24 +958,32 @@ struct EsPairs {
 // cnt_nbrs, second half, from the binned pairs: a block counts the pairs of its bin that are its own in LDS, then scores its nodes.
 // One node in eight belongs to a chunk of one per cent: a bitmap of the chunk's nodes, ranked, gives each of them a place in a
 // list and in the counts, so that the LDS holds six bytes for a node of the chunk instead of four for every node, two workgroups
-// share a CU, and a lane has a node of the chunk each time.  Where chunks hold most nodes (`sparse` is not set), in a bin with more of them
-// than there is `room` for, and in one of more than 65,535 pairs (a count then takes 32 bits), every node has its count (`direct`), in
-// rounds of as many nodes as fit; those of a crowded bin come from memory (k_es_crowd).
+// share a CU, and a lane has a node of the chunk each time.  Where chunks hold most nodes (`sparse` is not set) and in a bin with more of them
+// than there is `room` for, every node has its count (`direct`; of 32 bits in a bin of more than 65,535 pairs), in
+// rounds of as many nodes as fit; those of a crowded bin come from memory (k_es_crowd).  In an order of degree such blocks are what a
+// launch waits for: labels and estimates are asked for before the counts are looked at, crowded bins take one round, and neighbours go to
+// different XCDs (14M nodes by degree, 4M ends: 85 -> 66 us).
 // What bounds it is the estimates: the 64-byte pieces that hold one of the chunk's nodes are written (8 bytes per node: 450 MB at 111M
 // nodes and 32M ends, 14M nodes of the chunk), and 128-byte lines read (1 GB).  With doubles, 16 bytes per node, stores alone were 225 us of 555; now 410.
 // 14M nodes, 4M ends: 65 -> 42 us.  Nontemporal loads or stores of the estimates were slower, or no faster; four nodes per lane in flight spill.
 constexpr int kScoreTurn = 2;                      // nodes a lane has in flight
+constexpr int kPlaceTurn = 2;                      // ... whose counts come from memory
+constexpr uint32_t kListPairs = 4;                 // a block whose bin has more pairs than so many times `room` (50,000: a count fits 16 bits) does not try a list
+                                                   // (14M nodes, four partitions by degree, sixteen permuted: 2 30.7 and 39.6 ms, 3 30.8 and 36.6, 4 30.6 and
+                                                   // 33.5, any 31.5 and 34.0: a dense group's bins have many pairs of few nodes)
 __global__ __launch_bounds__(kBlock, 8) void k_es_score_bins(EsRun st, int par, int first, int fixed, int64_t chunk, EsBins tab,
                                                              uint32_t nblocks, uint32_t room, int sparse,
                                                              const uint32_t* __restrict__ pairs, EsCrowd crowd)
 {
     extern __shared__ uint32_t bits[];             // list: the chunk's nodes among the block's
     __shared__ uint32_t wsum[kWaves], wide;
-    // contiguous ranges of blocks per XCD (workgroups go to the XCDs in turn)
-    const uint32_t block = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    if (block >= nblocks) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, cb = tab.cb;
-    const uint32_t bn = (uint32_t)(kBlock * st.wpw), node0 = block * bn;
+    const uint32_t bn = (uint32_t)(kBlock * st.wpw);
+    // Workgroups go to the XCDs in turn.  Neighbouring blocks, which in an order of degree or a sorted list are alike, to different ones, unless
+    // they read the same bin.
+    const uint32_t block = bn >> cb ? blockIdx.x : (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (block >= nblocks) return;
+    const uint32_t node0 = block * bn;
     const uint32_t bin = node0 >> cb, in_bin = node0 & ((1u << cb) - 1u);
     uint32_t p0, p1;
     tab.range(chunk, bin, p0, p1);
@@ -998,11 +1002,27 @@ __global__ __launch_bounds__(kBlock, 8) void k_es_score_bins(EsRun st, int par, 
     const bool whole = st.packed == nullptr;                                         // the estimates are all doubles
     if (tid == 0 && !whole) wide = st.wide[block];
 
+    // the score of a node of the chunk: its label's word, its estimate as stored (if any is looked at) and its counts
+    const bool stored = !first && !fixed && !whole;
+    auto settle = [&](uint32_t rel, u64 labels, uint2 est, uint32_t h0, uint32_t h1) {
+        const uint32_t old = es_label(labels, rel);                // (a block starts at a whole word)
+        if (fixed && !first && old != kNone) return;
+        const bool blend = !first && !fixed && old != kNone;
+        double2 doubles = make_double2(0.0, 0.0);
+        if (!blend) est = make_uint2(0u, 0u);
+        if (whole) est = es_wide_word(node0 + rel);
+        if (blend && es_is_wide(est)) doubles = st.est[es_wide_place(est)];
+        const int lean = es_blend_packed(st, node0 + rel, est, doubles, blend, h0, h1, node0, &wide);
+        if (first) return;
+        const uint32_t t = answers >> (3u * old + (uint32_t)(lean + 1)) & 1u;
+        if (t != old) atomicOr(&(t ? mv1 : mv0)[rel >> 5], 1u << (rel & 31u));
+    };
     // counts of `count` nodes from `low` on (or, listed, of those in nodes[]) are there: their scores
     auto score = [&](uint32_t count, uint32_t low, bool listed, bool narrow, const uint32_t* seen) {
         for (uint32_t i0 = tid; i0 < count; i0 += kBlock * kScoreTurn) {
-            uint32_t rel[kScoreTurn], h0[kScoreTurn], h1[kScoreTurn], old[kScoreTurn];
+            uint32_t rel[kScoreTurn], h0[kScoreTurn], h1[kScoreTurn];
             uint2 est[kScoreTurn];
+            u64 labels[kScoreTurn];
             bool on[kScoreTurn];
 #pragma unroll
             for (int u = 0; u < kScoreTurn; ++u) {
@@ -1019,29 +1039,45 @@ __global__ __launch_bounds__(kBlock, 8) void k_es_score_bins(EsRun st, int par, 
                 }
                 if (!listed) on[u] &= (h0[u] | h1[u]) != 0u || ((seen[at >> 5] >> (at & 31u)) & 1u);
                 est[u] = make_uint2(0u, 0u);
-                u64 labels = 0ull;
-                if (on[u]) labels = st.Lw[(node0 + rel[u]) >> 5];
-                if (on[u] && !first && !fixed && !whole) est[u] = reinterpret_cast<const uint2*>(st.packed)[node0 + rel[u]];
-                old[u] = es_label(labels, rel[u]);                 // (a block starts at a whole word)
+                labels[u] = 0ull;
+                if (on[u] || !listed) labels[u] = st.Lw[(node0 + rel[u]) >> 5];
+                if ((on[u] || !listed) && stored) est[u] = reinterpret_cast<const uint2*>(st.packed)[node0 + rel[u]];
             }
 #pragma unroll
-            for (int u = 0; u < kScoreTurn; ++u) {
-                if (!on[u] || (fixed && !first && old[u] != kNone)) continue;
-                const bool blend = !first && !fixed && old[u] != kNone;
-                double2 doubles = make_double2(0.0, 0.0);
-                if (!blend) est[u] = make_uint2(0u, 0u);
-                if (whole) est[u] = es_wide_word(node0 + rel[u]);
-                if (blend && es_is_wide(est[u])) doubles = st.est[es_wide_place(est[u])];
-                const int lean = es_blend_packed(st, node0 + rel[u], est[u], doubles, blend, h0[u], h1[u], node0, &wide);
-                if (first) continue;
-                const uint32_t t = answers >> (3u * old[u] + (uint32_t)(lean + 1)) & 1u;
-                if (t != old[u]) atomicOr(&(t ? mv1 : mv0)[rel[u] >> 5], 1u << (rel[u] & 31u));
-            }
+            for (int u = 0; u < kScoreTurn; ++u)
+                if (on[u]) settle(rel[u], labels[u], est[u], h0[u], h1[u]);
         }
     };
 
-    bool direct = !sparse || place || p1 - p0 > 65535u;
-    if (!direct) {
+    if (place) {
+        // counted in memory, where what is taken is cleared; most of its nodes belong to the chunk, and everything is asked for at once
+        u64* hc = crowd.hc + (((size_t)place - 1) << cb) + in_bin;
+        uint32_t* was_seen = crowd.seen + ((((size_t)place - 1) << cb) + in_bin) / 32;
+        for (uint32_t i = tid; i < words; i += kBlock) mv0[i] = mv1[i] = 0u;
+        __syncthreads();
+        for (uint32_t i0 = tid; i0 < bn; i0 += kBlock * kPlaceTurn) {             // (bn is a multiple of it)
+            u64 h[kPlaceTurn], labels[kPlaceTurn];
+            uint32_t seen[kPlaceTurn];
+            uint2 est[kPlaceTurn];
+#pragma unroll
+            for (int u = 0; u < kPlaceTurn; ++u) {
+                const uint32_t rel = i0 + u * kBlock;
+                h[u] = hc[rel];
+                seen[u] = was_seen[rel >> 5];
+                labels[u] = st.Lw[(node0 + rel) >> 5];
+                est[u] = stored ? reinterpret_cast<const uint2*>(st.packed)[node0 + rel] : make_uint2(0u, 0u);
+            }
+#pragma unroll
+            for (int u = 0; u < kPlaceTurn; ++u) {
+                const uint32_t rel = i0 + u * kBlock;
+                if (h[u]) hc[rel] = 0ull;
+                if (seen[u] && (rel & 31u) == 0u) was_seen[rel >> 5] = 0u;       // (read by this wave alone)
+                if (h[u] || ((seen[u] >> (rel & 31u)) & 1u)) settle(rel, labels[u], est[u], (uint32_t)h[u], (uint32_t)(h[u] >> 32));
+            }
+        }
+    }
+    bool direct = !sparse || p1 - p0 > kListPairs * room;
+    if (!direct && !place) {
         for (uint32_t i = tid; i < words; i += kBlock) bits[i] = 0u;
         __syncthreads();
         list.each([&](uint32_t pair) {
@@ -1077,39 +1113,24 @@ __global__ __launch_bounds__(kBlock, 8) void k_es_score_bins(EsRun st, int par, 
             __syncthreads();                       // (bits are read no more)
         }
     }
-    if (direct) {
+    if (direct && !place) {
         // counts for every node, in rounds of as many as there is room for
-        const bool narrow = !place && p1 - p0 <= 65535u;
+        const bool narrow = p1 - p0 <= 65535u;
         uint32_t sub = bn;
         while ((narrow ? sub : 2u * sub) + sub / 32u > room + room / 2u) sub /= 2u;
         uint32_t* seen = cnt + (narrow ? sub : 2u * sub);
         for (uint32_t i = tid; i < words; i += kBlock) mv0[i] = mv1[i] = 0u;
         for (uint32_t low = 0; low < bn; low += sub) {
-            if (place) {                           // what is taken from memory is cleared there
-                u64* hc = crowd.hc + (((size_t)place - 1) << cb) + in_bin + low;
-                uint32_t* was_seen = crowd.seen + ((((size_t)place - 1) << cb) + in_bin + low) / 32;
-                for (uint32_t i = tid; i < sub; i += kBlock) {
-                    const u64 h = hc[i];
-                    cnt[2u * i] = (uint32_t)h;
-                    cnt[2u * i + 1u] = (uint32_t)(h >> 32);
-                    if (h) hc[i] = 0ull;
-                }
-                for (uint32_t i = tid; i < sub / 32u; i += kBlock) {
-                    seen[i] = was_seen[i];
-                    if (seen[i]) was_seen[i] = 0u;
-                }
-            } else {
-                list.start();
-                for (uint32_t i = tid; i < (narrow ? sub : 2u * sub) + sub / 32u; i += kBlock) cnt[i] = 0u;
-                __syncthreads();
-                list.each([&](uint32_t pair) {
-                    const uint32_t rel = (pair & ((1u << cb) - 1u)) - in_bin - low, code = pair >> cb;
-                    if (rel >= sub) return;
-                    if (code >= 2u) atomicOr(&seen[rel >> 5], 1u << (rel & 31u));
-                    else if (narrow) atomicAdd(&cnt[rel], code ? 65536u : 1u);
-                    else atomicAdd(&cnt[2u * rel + code], 1u);
-                });
-            }
+            list.start();
+            for (uint32_t i = tid; i < (narrow ? sub : 2u * sub) + sub / 32u; i += kBlock) cnt[i] = 0u;
+            __syncthreads();
+            list.each([&](uint32_t pair) {
+                const uint32_t rel = (pair & ((1u << cb) - 1u)) - in_bin - low, code = pair >> cb;
+                if (rel >= sub) return;
+                if (code >= 2u) atomicOr(&seen[rel >> 5], 1u << (rel & 31u));
+                else if (narrow) atomicAdd(&cnt[rel], code ? 65536u : 1u);
+                else atomicAdd(&cnt[2u * rel + code], 1u);
+            });
             __syncthreads();
             score(sub, low, false, narrow, seen);
             __syncthreads();
@@ -1553,8 +1574,8 @@ inline int grid_for(int64_t items, int block, int64_t cap)
 //           fewer, or half as many (4M nodes: 256 blocks); two of them fit a CU's LDS either way.  Up to 0.72 ends per node its nodes are listed, above that
 //           each has its count (14M nodes in chunks of 5 and 10 %: 5.8 and 5.8 ms so, 6.1 and 6.1 listed).  A bin is a block's nodes up to 67M or
 //           134M nodes, 4096 bins, several blocks' beyond.
-//   tile    8192 edges where that makes 512 tiles, or 4096 (14M nodes in groups, steps of 0.2 to 2M edges: bisection 39.7 -> 38.4 ms), and
-//           fewer where the bins' words leave less room in half a CU's LDS.
+//   tile    8192 edges where that makes 512 tiles, or 4096 (14M nodes in groups, steps of 0.2 to 2M edges: bisection 39.7 -> 38.4 ms) and
+//           where the bins' words leave less room in half a CU's LDS.
 //   asked   from 2^25 nodes on, or 2^24 and 2^24 ends in a step (100 chunks of 20M nodes: 14.4 ms asked, 13.3 looked up; 10 chunks 7.0 and 7.3; 50 of 27M
 //           12.7 and 12.7; 50 of 40M 18.0 and 21.2).
 //   classes 8 where a step has 256 tiles or more (14M nodes 9.1 ms, 9.6 with one; 111M 82 and 92), or one: the table is the smaller.
@@ -1590,8 +1611,8 @@ constexpr int64_t kAskMinNodes = 1ll << 25, kAskMinEnds = 1ll << 24;
 constexpr int kAskBits = 17;                                 // 32 KB of labels
 constexpr int64_t kBinMinNodes = 1ll << 22;
 constexpr int64_t kBinMaxChunks = 8192;
-constexpr int64_t kCrowdMin = 65535, kCrowdMean = 8;         // a crowded bin: more pairs than these, and than so many bins hold on
-                                                             // average (their counts then take a byte per node at most)
+constexpr int64_t kCrowdMin = 65535, kCrowdMean = 6, kCrowdMeanLean = 8;     // a crowded bin: more pairs than these, and than so many bins hold on
+                                                             // average (their counts then take 1.3 bytes per node at most, or one)
 constexpr int64_t kCrowdNodes = 32768;                       // a workgroup of k_es_crowd counts so many at a time
 constexpr int64_t kHalfLds = 80 * 1000;
 constexpr int kSortLds = 160000;
@@ -1599,7 +1620,7 @@ constexpr unsigned kCrowdGrid = 512;                         // workgroups of k_
 // The forms of a run, each of less memory than the one before it:
 //   full     binned, with estimates in 8 bytes beside the doubles and, where they pay, asks
 //   lean     binned, the estimates all doubles (in the caller's array if there is one), labels looked up, 1024 bins, one class, few blocks: 17 bytes per
-//            node (one with a caller's array) for 25, and a third of the bytes per end where labels are asked for
+//            node (one with a caller's array) for 26, and a third of the bytes per end where labels are asked for
 //   counted  the counts in memory (8 bytes per node, the lean form's pairs up to 16)
 enum class EsForm { full, lean, counted };
 // n: nodes of the run; groups: most groups side by side; ends: of a chunk's edge ends over all groups
@@ -1635,7 +1656,7 @@ EsShape es_shape(int64_t n, int64_t groups, int64_t ends, int64_t chunks, EsForm
             s.tile = kAskEdges;
         } else {
             s.tile = ends / 2 >= 512 * kBinTile ? kBinTile : kBinTile / 2;
-            while (es_sort_lds(2 * s.tile, 4, s.nb) > kHalfLds) s.tile -= 2048;
+            if (es_sort_lds(2 * s.tile, 4, s.nb) > kHalfLds) s.tile = kBinTile / 2;
         }
         s.classes = full && ends / 2 / s.tile >= 256 ? 8 : 1;
     } else {
@@ -1645,7 +1666,7 @@ EsShape es_shape(int64_t n, int64_t groups, int64_t ends, int64_t chunks, EsForm
     }
     s.nodes = room();
     if (s.binned) {
-        const int64_t nbins = (s.nodes + (1ll << s.cb) - 1) >> s.cb, most = kCrowdMean * (ends / nbins + 1);
+        const int64_t nbins = (s.nodes + (1ll << s.cb) - 1) >> s.cb, most = (s.packed ? kCrowdMean : kCrowdMeanLean) * (ends / nbins + 1);
         s.crowd_limit = (uint32_t)(most > kCrowdMin ? most : kCrowdMin);
         s.crowd_bins = ends / ((int64_t)s.crowd_limit + 1);
     }
@@ -1767,9 +1788,9 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
     auto round = [&](int64_t grid) { return (grid + sh.classes - 1) / sh.classes * sh.classes; };
     std::vector<uint32_t> crowded;                             // per chunk: its crowded bins
     if (sh.binned) {
-        // (workgroups of several tiles each: a workgroup's 1024 counts are added to the table once)
+        // (workgroups of several tiles each: a workgroup's counts are added to the table once)
         // (asked: 128 KB of counts each; with 256 workgroups a chunk 4.4 ms at 111M nodes and 100 chunks, with 48 3.7)
-        const int64_t parts = round(grid_for((most + tile - 1) / tile, 4, sh.asked ? std::min<int64_t>(std::max<int64_t>(4096 / (chunks * ng), 32), 256) : 256));
+        const int64_t per = sh.asked ? tile : kBinTile, parts = round(grid_for((most + per - 1) / per, 4, sh.asked ? std::min<int64_t>(std::max<int64_t>(4096 / (chunks * ng), 32), 256) : 256));
         const size_t hist_lds = (size_t)sh.nb * 4 * (sh.asked ? sh.classes : 1);
         if (hipFuncSetAttribute((const void*)k_es_hist, hipFuncAttributeMaxDynamicSharedMemorySize, kBins * 4 * 8) != hipSuccess) return GREM_ERR_HIP;
         hipLaunchKernelGGL(k_es_hist, dim3((unsigned)parts, ng, (unsigned)chunks), dim3(kBlock), hist_lds, stream, src, dst, st, mem.bins, mem.ranges, tile);
@@ -1798,7 +1819,7 @@ int es_run(hipStream_t stream, EsMemory& mem, const EsShape& sh, const std::vect
         }
     const int64_t crowd_bn = sh.bn() < kCrowdNodes ? sh.bn() : kCrowdNodes;
     const size_t crowd_lds = (size_t)crowd_bn * 4 + (size_t)crowd_bn / 8, bins_lds = es_bins_lds(sh.bn(), sh.room);
-    const auto bin = tile == 8192 ? k_es_bin8 : tile == 6144 ? k_es_bin6 : tile == 4096 ? k_es_bin4 : k_es_bin;
+    const auto bin = tile == 8192 ? k_es_bin8 : tile == 4096 ? k_es_bin4 : k_es_bin;
     // (always what any run may need: the limit is the process's, and other threads' runs are of other sizes)
     if (sh.binned &&
         (hipFuncSetAttribute((const void*)k_es_ask, hipFuncAttributeMaxDynamicSharedMemorySize, kSortLds) != hipSuccess ||
