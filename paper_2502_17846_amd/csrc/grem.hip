@@ -851,30 +851,33 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
     const size_t coarse_row = (size_t)(kAdmitTilesMax / kCoarseTiles) * (size_t)k;
     if (hubs_in_admission) L.memset(t.coarse, 0, 2 * coarse_row * 4);
 
-    // look-ups of the labels of chunk c0, or of all chunks (c0 < 0)
-    // `mark`: seeded runs, first pass: the row fields the score kernels read are those of Rdyn, where
-    // bit 0 also marks the tuples whose neighbour is unassigned (set by the initial look-up from global
-    // memory, cleared by the look-up of the neighbour's chunk)
-    auto lookup = [&](int c0, int cmin, bool from_lds, bool mark, const uint8_t *labels4 = nullptr) {
+    // Ids in order of degree: a chunk has more than twice its share of the entries, and its columns, as a graph's entries go both ways, too.
+    // A sweep then finds each workgroup's block by the blocks' sizes, which costs it some 2 us (25M vertices, 250M entries, permuted: 0.82 -> 0.87 ms;
+    // 13.9M by degree, k = 32 0.69 -> 0.42).
+    const bool lopsided = *std::max_element(P.chunk_entries.begin(), P.chunk_entries.end()) * (u64)geo.nch > 2 * (u64)P.nnz;
+    // look-ups of the labels of chunks [c0, c0 + count)
+    auto lookup = [&](int c0, int count, int cmin, bool from_lds, bool mark, const uint8_t *labels4 = nullptr) {
         if (cmin >= geo.nch) return;
-        const uint64_t groups = P.slots / 8;
-        LookupShares deal{1u, 1u, 0u};
-        if (c0 < 0) {
+        // (whole eights where there are as many: a share has the same place among the XCDs whatever its block, see k_tp_lookup)
+        const uint32_t by_work = (uint32_t)std::min<int64_t>(P.nnz / geo.nblk / 8192 + 1, kLookupMany);
+        auto per_block = [&](uint32_t all) {
+            const uint32_t w = std::max(std::min(all / (uint32_t)geo.nbc, by_work), 1u);
+            return w < 8 ? w : w / 8 * 8;
+        };
+        LookupShares deal{per_block(kLookupFew), 0u, 0u};
+        dim3 grid;
+        if (count == geo.nch && lopsided) {
+            const uint64_t groups = P.slots / 8;
             deal.per = (uint32_t)std::max<uint64_t>(groups / kLookupSweep + 1, 1024);
+            grid = dim3(lookup_sweep_grid(groups, (uint32_t)geo.nblk, deal));
         } else {
             // (workgroups beyond the blocks' shares cost 2 us a launch, so that `many` are launched for a chunk of long rows only: as a
-            // graph's entries go both ways, its columns are then as long.  Whole eights where there are as many: a share has
-            // the same place among the XCDs whatever its block, see k_tp_lookup)
-            const uint32_t by_work = (uint32_t)std::min<int64_t>(P.nnz / geo.nblk / 8192 + 1, kLookupMany);
-            auto per_block = [&](uint32_t all) {
-                const uint32_t w = std::max(std::min(all / (uint32_t)geo.nbc, by_work), 1u);
-                return w < 8 ? w : w / 8 * 8;
-            };
-            const bool lengthy = geo.cb <= 17 && P.chunk_entries[(size_t)c0] / 8 > (u64)kLookupFew * kLookupLong;       // (128 KB of labels: one workgroup per CU)
-            deal.few = per_block(kLookupFew);
+            // graph's entries go both ways, its columns are then as long.  128 KB of labels: one workgroup per CU)
+            const bool lengthy = count == 1 && geo.cb <= 17 && P.chunk_entries[(size_t)c0] / 8 > (u64)kLookupFew * kLookupLong;
+            if (count > 1) deal.few = (uint32_t)std::max<uint64_t>(std::min<uint64_t>(std::min(kLookupFew / (uint32_t)geo.nbc, by_work), kLookupSweep / ((uint64_t)count * geo.nbc)), 1);
             deal.many = lengthy ? per_block(kLookupMany) : deal.few;
+            grid = dim3((uint32_t)geo.nbc * deal.many, (unsigned)count);
         }
-        const dim3 grid(c0 < 0 ? lookup_sweep_grid(groups, (uint32_t)geo.nblk, deal) : (uint32_t)geo.nbc * deal.many);
         auto go = [&](auto kernel, size_t lds) {
             hipLaunchKernelGGL(kernel, grid, dim3(kTpThreads), lds, stream, P.T, t.Lx, P.R, t.Rdyn, tb,
                                (const uint8_t *)st.Lc, labels4, n, c0, cmin, deal);
@@ -893,7 +896,10 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
     // with 16 partitions in four bits, where the first pass reads its row fields from Rdyn and the initial look-up,
     // from global memory, marks the entries there.
     const bool partly = seed != nullptr && !st.seed_complete, marks = partly && k == 16;
-    if (seed) lookup(-1, 0, !marks, marks);          // the seeds are the labels every first-pass look-up starts from
+    if (seed) {        // the seeds are the labels every first-pass look-up starts from
+        const int most = lopsided ? geo.nch : 32768;
+        for (int c0 = 0; c0 < geo.nch; c0 += most) lookup(c0, std::min(geo.nch - c0, most), 0, !marks, marks);
+    }
     L.mark();
     if (fixed_labels) {                     // counts only: nothing to admit, no new labels to look up
         const bool skip = partly && k == 32;
@@ -1034,7 +1040,7 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
             }
             // the chunk's new labels, looked up for every row that will read them: rows of later chunks in
             // this pass, rows of this and earlier chunks in the next pass (if there is one)
-            lookup((int)c, pass == R ? (int)c + 1 : 0, true, marks && pass == 0, packed_now);
+            lookup((int)c, 1, pass == R ? (int)c + 1 : 0, true, marks && pass == 0, packed_now);
         }
         L.mark();
     }

@@ -1071,8 +1071,8 @@ __global__ __launch_bounds__(kPlaceThreads) __attribute__((amdgpu_waves_per_eu(8
 }
 
 // ------------------------------------------------------------------------------------------------
-// look-up (phase 1 of the score): the tuples of the column blocks of chunk `c0`, or of all chunks (a sweep), restricted to row
-// chunks >= cmin, get their labels.  A workgroup handles a share of a block (grem_lookup_shares.hip.h): an equal part of the
+// look-up (phase 1 of the score): the tuples of the column blocks of chunk `c0 + blockIdx.y`, or of all chunks (a sweep), restricted to
+// row chunks >= cmin, get their labels.  A workgroup handles a share of a block (grem_lookup_shares.hip.h): an equal part of the
 // block's tuples in T, which are one contiguous piece.
 //   T  (read)   : per group of eight tuples 24 bytes: the index of the word of Lx their labels go to,
 //                 then their columns in the block, 20 bits each
@@ -1120,7 +1120,7 @@ __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(8, 8
         m = first % tb.nbc;
         s = (int)(blockIdx.x - first_of(first));
     } else {
-        c = c0;
+        c = c0 + (int)blockIdx.y;
         m = (int)(blockIdx.x / deal.many);
         s = (int)(blockIdx.x % deal.many);
     }
