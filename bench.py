@@ -47,10 +47,15 @@ PMC_EDGE = {
 }
 
 
-def edge_kernels(n):
-    """The kernels that grem_edge_stream_profile_* times: from 2^22 nodes on the edge ends are binned, from 2^25 on their labels
-    asked for beforehand."""
-    return "k_es_ask+k_es_answer+k_es_score_bins" if n >= 1 << 25 else "k_es_bin+k_es_score_bins" if n >= 1 << 22 else "k_es_count"
+def edge_kernels(n, c_size, chunks):
+    """The kernels that grem_edge_stream_profile_* times in chunks of c_size edges (over all groups): from 2^22 nodes on the edge ends are
+    binned (by one of k_es_bin, k_es_bin4 and k_es_bin8, as the chunks are long) if a chunk has four per node or fewer, from 2^25 on, or 2^24 and as
+    many ends, their labels asked for beforehand.  (Where there is memory for that.)"""
+    ends = 2 * c_size
+    if n < 1 << 22 or ends > 4 * n or chunks > 8192:
+        return "k_es_count"
+    asked = n >= 1 << 25 or (n >= 1 << 24 and ends >= 1 << 24)
+    return "k_es_ask+k_es_answer+k_es_score_bins" if asked else "k_es_bin+k_es_score_bins"
 
 
 def edge_sources_sha256():
@@ -300,7 +305,7 @@ def bench_edge_stream(args, w, dev):
     # dominant kernels: cnt_nbrs reads each edge's two ids once (8 bytes); its label look-ups are random accesses whose
     # useful bytes are 2 per edge, the pairs it bins and the nodes' estimates are not counted
     roofline = {"bound": "hbm", "achieved": None, "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": None,
-                "traffic": None, "kernel": edge_kernels(n)}
+                "traffic": None, "kernel": edge_kernels(n, c_size, nchunks)}
     if not args.no_kernel_timing:
         B.grem_edge_stream_profile_enable(True)
         step()
@@ -521,7 +526,7 @@ def bench_recursive(args, w, dev):
     sizes = torch.bincount(lab, minlength=k)
     cut = int(B.grem_edge_list_cut(es.src, es.dst, lab).item())
     roofline = {"bound": "hbm", "achieved": None, "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": None,
-                "traffic": None, "kernel": edge_kernels(n)}
+                "traffic": None, "kernel": edge_kernels(n, -(-m // min(chunks, m)) + 1024, chunks)}
     if not args.no_kernel_timing:
         B.grem_edge_stream_profile_enable(True)
         step()

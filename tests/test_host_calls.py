@@ -209,3 +209,19 @@ def test_the_edge_timing_spans_the_kernels_that_count(fake):
         assert lib.grem_edge_stream_profile_read(ctypes.byref(ms), ctypes.byref(steps), ctypes.byref(edges)) == 0
         assert (ms.value, steps.value, edges.value) == (3.0, 3, m)
     """)
+
+
+def test_the_bench_names_the_edge_kernels_that_run(fake):
+    _run(fake, f"""
+    sys.path.insert(0, {os.path.dirname(HERE)!r})
+    from bench import edge_kernels
+    for n, m, chunks in ((20_000, 50_000, 3), ((1 << 22) - 1, 100_000, 2), (1 << 22, 100_000, 2), (1 << 22, 9_000_000, 1), (5_000_000, 16_000_000, 1),
+                         (17_000_000, 16_000_000, 1), (17_000_000, 16_000_000, 2), (16_000_000, 16_000_000, 1), (1 << 25, 100_000, 10), (1 << 22, 100_000, 8193)):
+        reset()
+        c_size = -(-m // chunks)
+        chunks = -(-m // c_size)
+        assert lib.grem_edge_stream_bipartition(ends, ends, L(m), L(n), L(c_size), L(n), big, I(0), big, None, None, None) == 0
+        run = [x[1] for x in text() if x[0] == "launch"]
+        for k in ("k_es_count", "k_es_bin", "k_es_ask", "k_es_answer", "k_es_score_bins"):
+            assert any(k in x for x in run) == (k in edge_kernels(n, c_size, chunks).split("+")), (n, m, chunks, k)
+    """, sizes="big, ends = mem(1 << 28), mem(1 << 26)")
