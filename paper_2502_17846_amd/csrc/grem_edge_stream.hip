@@ -21,12 +21,12 @@
 //                   yet.  Bitmaps are ordered sets: bit order is id order, so ranks by id are prefix
 //                   pop-counts.
 //   mark            bitmap: v is an endpoint of a chunk edge whose other end has no label
-// The chunk's fresh counts (Alg. 2 cnt_nbrs) come in one of two ways, the same integers either way:
+// The chunk's fresh counts (Alg. 2 cnt_nbrs) come in one of three ways, the same integers any way:
 //   in memory (small graphs)  hc, uint64 per node: low half = neighbours in partition 0, high half = in
 //                   partition 1; k_es_count adds one 64-bit atomic per edge end, k_es_score reads and clears.
-//   binned (large graphs)     k_es_bin looks the other end's label up for every edge end and sorts the
-//                   (node, label) pairs by ranges of nodes; k_es_score_bins counts a block's pairs in LDS.  Where the
-//                   labels outgrow the L2s, k_es_ask and k_es_answer do k_es_bin's work with labels in LDS.
+//   binned (large graphs)     k_es_bin (k_es_bin4, k_es_bin8: of four and eight edges per thread instead of two) looks the other end's label
+//                   up for every edge end and sorts the (node, label) pairs by ranges of nodes; k_es_score_bins counts a block's pairs in LDS
+//   asked (larger ones)       where the labels outgrow the L2s, k_es_ask and k_es_answer do k_es_bin's work with labels in LDS
 // Per chunk: count or bin -> score (blend, assign, mover ballots) -> k_es_admit (ranks = movers of the earlier
 // blocks + pop-count prefix; admitted moves relabel; closed-form target of the j-th rejected node; sizes).  The
 // sizes live in two copies that take turns from chunk to chunk.
@@ -1201,9 +1201,9 @@ __device__ __forceinline__ void es_rejected(const EsRun& st, uint32_t blk0, uint
 // their other copy.
 // A lane takes W neighbouring words of 64 nodes (awpw = 64 * W words per wave, or fewer with W = 1): the admitted movers
 // of a word are its first bits, as many as there is room for, the alternation over rejected ones is a prefix parity, and labels
-// change in a few bit operations.  W and awpw: so many that 256 blocks or fewer do it up to 67M nodes in one group, as each adds up
-// all blocks' counts; beyond that a block takes 131,072 nodes, 848 of them 111M (es_shape; with twice as many, and 92 registers, 52 us for 43).  In two launches (admission, spill), with labels of a byte each and movers taken one by one: 103 us per chunk at
-// 111M nodes, 13 at 20,000; now 53 and 6.
+// change in a few bit operations.  W and awpw: so many that 256 blocks or fewer do it up to 33M nodes in one group, as each adds up
+// all blocks' counts; beyond that a block takes 131,072 nodes, 848 of them 111M (es_shape; with twice as many, and 92 registers, 52 us for 43).  In two
+// launches (admission, spill), with labels of a byte each and movers taken one by one: 103 us per chunk at 111M nodes, 13 at 20,000; so 43 and 6.
 template <int W>
 __global__ __launch_bounds__(kBlock) void k_es_admit(EsRun st, int par)
 {
@@ -1589,7 +1589,7 @@ struct EsShape {
     int cb = 0, classes = 1, tile = 0;     // binned: nodes of a bin (2^cb), classes of tiles, edges of a tile
     uint32_t nb = 0;                       // ... and bins, rounded up
     bool asked = false;                    // binned: labels are looked up in LDS
-    int ask_cb = 0, ask_tile = 0;          // ... nodes of a range (2^ask_cb)
+    int ask_cb = 0;                        // ... nodes of a range (2^ask_cb)
     uint32_t ask_nb = 0;                   // ... and ranges, rounded up
     bool binned = false;
     bool packed = false;                   // binned: the estimates in 8 bytes
