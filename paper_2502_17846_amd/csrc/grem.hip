@@ -874,7 +874,12 @@ int run_two_phase(const PlanData &P, int32_t k, double slack, int32_t R, const i
             // (workgroups beyond the blocks' shares cost 2 us a launch, so that `many` are launched for a chunk of long rows only: as a
             // graph's entries go both ways, its columns are then as long.  128 KB of labels: one workgroup per CU)
             const bool lengthy = count == 1 && geo.cb <= 17 && P.chunk_entries[(size_t)c0] / 8 > (u64)kLookupFew * kLookupLong;
-            if (count > 1) deal.few = (uint32_t)std::max<uint64_t>(std::min<uint64_t>(std::min(kLookupFew / (uint32_t)geo.nbc, by_work), kLookupSweep / ((uint64_t)count * geo.nbc)), 1);
+            if (count > 1) {
+                // (from global memory: no labels to copy, so as many workgroups as there is work for.  Planned, k = 16, a tenth seeded, chunks of 2^20:
+                // 13.9M vertices 4.77 | 4.73 ms, 40M 9.06 | 8.96)
+                const uint64_t most = from_lds ? std::min<uint64_t>(kLookupFew / (uint32_t)geo.nbc, kLookupSweep / ((uint64_t)count * geo.nbc)) : kLookupMany / (uint32_t)geo.nbc;
+                deal.few = (uint32_t)std::max<uint64_t>(std::min<uint64_t>(most, by_work), 1);
+            }
             deal.many = lengthy ? per_block(kLookupMany) : deal.few;
             grid = dim3((uint32_t)geo.nbc * deal.many, (unsigned)count);
         }
