@@ -28,11 +28,11 @@ HBM_PEAK_GBPS = 8000.0
 # at that time, and `traffic` is reported as null when the sources have changed since.
 PMC = {
     "workload": "chunglu-111M",
-    "sources_sha256": "71ee0937c601eef1713c44a3f4bb2b124b6a2ad627e724483ce7401e6246e898",
+    "sources_sha256": "179a95ccdf1d573add98cd4f6abbf2fe331936ea75d57a1924d23743cd43c234",
     "fetch_factor": 2.0,        # 2 GiB read  -> FETCH_SIZE 1,048,591 KiB
     "write_factor": 1.0,        # 2 GiB written -> WRITE_SIZE 2,097,152 KiB
-    "fetch_kib": {"k_tp_score": 1.42621e+07, "k_tp_lookup": 1.37060e+07},
-    "write_kib": {"k_tp_score": 7.32475e+06, "k_tp_lookup": 5.17638e+06},
+    "fetch_kib": {"k_tp_score": 1.42582e+07, "k_tp_lookup": 1.37094e+07},
+    "write_kib": {"k_tp_score": 7.32476e+06, "k_tp_lookup": 5.17017e+06},
     "launches": {"k_tp_score": 318, "k_tp_lookup": 317},
 }
 
@@ -40,9 +40,9 @@ PMC = {
 # The same for the edge-chunk path's three dominant kernels (one launch each per chunk) on its 111M-node workload.
 PMC_EDGE = {
     "workload": "edges-chunglu-111M-c1pct",
-    "sources_sha256": "631f9189af6c224b0f4e4d29e8f72f136d3ad27d31805c1ebb1df3980e2b6db5",
-    "fetch_kib": {"k_es_ask": 6.31422e+06, "k_es_answer": 1.39492e+07, "k_es_score_bins": 5.35641e+07},
-    "write_kib": {"k_es_ask": 2.93644e+07, "k_es_answer": 1.87781e+07, "k_es_score_bins": 4.52095e+07},
+    "sources_sha256": "b9b8e75f34ec08f12ec695e84ae6551856899aa868c9a365d885d0d6e97365be",
+    "fetch_kib": {"k_es_ask": 6.31235e+06, "k_es_answer": 1.39533e+07, "k_es_score_bins": 5.46446e+07},
+    "write_kib": {"k_es_ask": 2.93685e+07, "k_es_answer": 1.87050e+07, "k_es_score_bins": 4.48423e+07},
     "launches": 100,
 }
 

@@ -1570,7 +1570,7 @@ inline int grid_for(int64_t items, int block, int64_t cap)
 
 // How a run is laid out.
 //   binned  from 4M nodes on (the counts in memory, 8 bytes per node, then far outgrow the L2), if a chunk's pairs take no more
-//           room than the estimates and the table of the chunks' bins stays small.  A block is 32,768 nodes where a chunk has 0.34 ends per node or
+//           room than the estimates (asks take twice the pairs' beside them) and the table of the chunks' bins stays small.  A block is 32,768 nodes where a chunk has 0.34 ends per node or
 //           fewer, or half as many (4M nodes: 256 blocks); two of them fit a CU's LDS either way.  Up to 0.72 ends per node its nodes are listed, above that
 //           each has its count (14M nodes in chunks of 5 and 10 %: 5.8 and 5.8 ms so, 6.1 and 6.1 listed).  A bin is a block's nodes up to 67M or
 //           134M nodes, 4096 bins, several blocks' beyond.
